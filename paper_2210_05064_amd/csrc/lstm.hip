@@ -328,6 +328,7 @@ struct LstmWs {
     float* part;       // partial sums of the two-stage reductions
     float* part_b;     // [row blocks][64]: the heads' bias gradients per row block
     float* gemm_part;  // partial tiles of GEMMs whose contraction is split over workgroups
+    char* ring;        // [8 groups] exchange rings of the time loops (lstm_few.h)
     float* db_part;    // [2][8][4H]: per layer of a launch and group, the sum of the gate gradients over the group's rows
     size_t bytes;
 };
@@ -389,6 +390,7 @@ inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws)
     ws->part_b = cv.take<float>((size_t)(M + HW_ROWS - 1) / HW_ROWS * 64);
     ws->gemm_part = cv.take<float>(gemm_part_max(c, M));
     ws->db_part = cv.take<float>((size_t)2 * REC_GROUPS * 4 * H);
+    ws->ring = cv.take<char>(REC_GROUPS * few_ring_bytes(c.compute ? MODE_BF16 : MODE_F32, 4 * c.hidden));
     ws->bytes = cv.used;
 }
 
@@ -462,10 +464,10 @@ inline size_t pipe_worker_lds() {
 // sticky time-out word at the start of the workspace, and writes the plans of both launches of the minibatch (the
 // backward call runs on the packing of the forward call whose activations it finds in the workspace).  Before the
 // backward launch only the words are cleared.
-inline void pipe_prepare_fwd(LstmWs& ws, int M, const int32_t* info, const int32_t* batch_sizes, hipStream_t s) {
+inline void pipe_prepare_fwd(LstmWs& ws, int mode, bool wide, int M, const int32_t* info, const int32_t* batch_sizes, hipStream_t s) {
     int* last = ws.pipe + ws.pipe_words;
     hipLaunchKernelGGL(lstm_pipe_plan_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, info, batch_sizes, M, ws.plan[0], ws.plan[1],
-                       ws.plan_scratch, ws.err, (int)(last - ws.err), PLAN_COST_FWD, PLAN_COST_BWD);
+                       ws.plan_scratch, ws.err, (int)(last - ws.err), plan_cost(mode, wide, true), plan_cost(mode, wide, false));
 }
 inline void pipe_work(const LstmWs& ws, int dir, int M, const int32_t* t_off, PipeWork* pw) {
     pw->M = M;
@@ -499,6 +501,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     const size_t red_per_tile = (size_t)ks * mt * 64 * 16 + (size_t)16 * 4 * mt * sizeof(E);   // partial sums + new h
     const int ntc = rec_tiles(tile, red_per_tile);
     size_t lds = ntc * (tile + red_per_tile);
+    if (few_lds_bytes(MODE, 16 * mt) > lds) lds = few_lds_bytes(MODE, 16 * mt);
     if (pipelined && pipe_worker_lds<MODE>() > lds) lds = pipe_worker_lds<MODE>();
     const int nb = (H / ks) / RecGeom<MODE>::KBLK;
 
@@ -543,6 +546,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         RecFwdArgs ra;
         ra.info = info; ra.batch_sizes = batch_sizes; ra.t_off = t_off;
         ra.gates = L.gates; ra.c = L.c; ra.hout = L.hout; ra.hprev = L.hprev; ra.hcopy = L.hcopy; ra.whh = L.whh;
+        ra.ring = ws.ring + (pipelined && l == 1 ? PIPE_GROUPS * few_ring_bytes(MODE, H) : 0);
         ra.h0 = h0 ? h0 + (size_t)l * seq_cap * H : nullptr;
         ra.c0 = c0 ? c0 + (size_t)l * seq_cap * H : nullptr;
         ra.H = H; ra.seq_cap = seq_cap; ra.M = M; ra.flags = ws.flags; ra.ticket = ws.flags + 8 * REC_MAX_GROUP;
@@ -572,7 +576,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     prep_all();
     if (pipelined) {
         project(0);
-        pipe_prepare_fwd(ws, M, info, batch_sizes, s);
+        pipe_prepare_fwd(ws, MODE, wide, M, info, batch_sizes, s);
         PipeFwdArgs pa;
         pa.l0 = rec_args(0);
         pa.l1 = rec_args(1);
@@ -629,6 +633,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     const size_t red_per_tile = (size_t)ks * mt * 64 * 16 + (size_t)16 * 16 * mt * sizeof(float);   // partial sums + carried dh
     const int ntc = rec_tiles(tile, red_per_tile);
     size_t lds = ntc * (tile + red_per_tile);
+    if (few_lds_bytes(MODE, 16 * mt) > lds) lds = few_lds_bytes(MODE, 16 * mt);
     if (pipelined && pipe_worker_lds<MODE>() > lds) lds = pipe_worker_lds<MODE>();
     const int ni = (4 * H / ks) / RecGeom<MODE>::KBLK;
 
@@ -640,6 +645,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         ra.info = info; ra.batch_sizes = batch_sizes; ra.t_off = t_off;
         ra.gates = L.gates; ra.c = L.c; ra.c0 = c0 ? c0 + (size_t)l * seq_cap * H : nullptr;
         ra.dh_above = dh_above; ra.dz = dz_of(l); ra.whhT = L.whhT;
+        ra.ring = ws.ring + (pipelined && l == 0 ? PIPE_GROUPS * few_ring_bytes(MODE, 4 * H) : 0);
         // the two layers of a shared launch carry their state in separate halves of the scratch
         ra.dh_state = ws.dh_state + (pipelined ? (size_t)l * M * H : 0);
         ra.dc_state = ws.dc_state + (pipelined ? (size_t)l * M * H : 0);
@@ -654,7 +660,9 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         if (ok) hipLaunchKernelGGL((KERNEL<MODE, MT_, KS_, N_>), dim3(REC_GRID), dim3(REC_THREADS), lds, s, ARGS); } while (0)
 #define VER_BWD_DISPATCH(KERNEL, ARGS) do { \
         if (wide) { \
-            if (ni == 32) VER_BWD_LAUNCH(KERNEL, ARGS, 2, 4, 32); else VER_BWD_LAUNCH(KERNEL, ARGS, 2, 4, 0); \
+            if constexpr (MODE == MODE_BF16) {   /* (fp32: hidden <= 512) */ \
+                if (ni == 32) VER_BWD_LAUNCH(KERNEL, ARGS, 2, 4, 32); else VER_BWD_LAUNCH(KERNEL, ARGS, 2, 4, 0); \
+            } \
         } else { \
             if (ni == 16) VER_BWD_LAUNCH(KERNEL, ARGS, 1, 8, 16); \
             else if (ni == 8) VER_BWD_LAUNCH(KERNEL, ARGS, 1, 8, 8); \

@@ -1,0 +1,718 @@
+// The time loops while a group has few alive pieces (included by lstm_rec.h).  gfx950 only.
+//
+// A timestep with a handful of alive pieces is all latency: the flag protocol of lstm_rec.h passes through a store
+// acknowledgement, a workgroup barrier, a flag store, a poll, a barrier, the copy of the rows into LDS and another
+// barrier before the first MFMA, and every wave's wait for its stores also waits for the saved activations.  Here
+// the exchanged values announce themselves:
+//  * Rows are exchanged through a ring of FEW_RING slots per group that stays in the XCD's L2.  An empty 32-bit word
+//    of a slot holds FEW_EMPTY, which no published word equals (see few_word), so a reader polls the values it needs
+//    and has them when the poll succeeds: no flag, no wait for a store's acknowledgement, no barrier, no copy.
+//  * Each of the 8 waves owns an eighth of the contraction (all gate rows of the workgroup) and polls just that
+//    slice of the rows, straight into the operand registers of the product: no staging in LDS.  With P pieces the 16
+//    rows of an operand hold P pieces x 16/P operand blocks, so that a load instruction is full; the blocks are
+//    brought to rows 0 .. P-1 by rotating the lanes of a row (DPP), the other rows of the operand are whatever
+//    they are (a row of A only reaches the same row of the result).  fp32 reads its values as DPP broadcasts.
+//  * The partial sums of the waves meet in LDS (two buffers, one barrier per timestep); a thread then owns one
+//    (piece, unit) and keeps its cell state (backward: both carried gradients) in registers.
+//  * Everything that is not on the way from one exchange to the next (saved activations, copies for other XCDs,
+//    prefetches) is issued right after a poll has succeeded, so that it completes behind the product: memory
+//    operations of a wave complete in order, and what is queued before a poll delays it.
+// Reuse of a slot: a workgroup that has read the rows of one timestep from all workgroups knows that all of them
+// are done with the rows of the timestep before; each clears its own words of that slot then, and publishes at least
+// once more after the clearing stores have completed before anyone polls the slot again.
+//
+// Bound by the latency of its phases: about 0.6 us for the exchange alone (a kernel that does nothing else), 0.43 us for
+// the MFMAs of one 16-row tile at H = 1024, then the partial sums through LDS and the cell update.  Microseconds per
+// timestep (one layer, bf16, H = 1024), flag protocol -> this form:
+//     alive pieces     1             2             4             8             16
+//     forward     2.36 -> 1.57  2.36 -> 1.60  2.44 -> 1.81  2.69 -> 2.13  3.31 -> 2.74
+//     backward    2.23 -> 1.85  3.11 -> 2.27  3.26 -> 3.03  3.79 -> 3.42  4.80 -> 5.25 (not used)
+// fp32, H = 512: forward 1 piece 2.20 -> 1.41, 4 pieces 3.75 -> 2.53; backward 2.78 -> 1.63, 4.30 -> 3.95.
+#pragma once
+
+namespace ver {
+
+constexpr int FEW_RING = 4;
+constexpr unsigned FEW_EMPTY = 0xffffffffu;
+// Alive pieces up to which a group runs this form: beyond, the copy of the rows into LDS (every row once per
+// workgroup, in whole lines) beats the polls (figures above; backward rows are four times as long; an fp32 piece more
+// costs the vector ALUs as much as the first).
+template <int MODE> struct FewMax {
+    static constexpr int fwd = MODE == MODE_BF16 ? 16 : 4, bwd = MODE == MODE_BF16 ? 8 : 4;
+};
+// Operand blocks per wave: the contraction (H forward, 4H backward) over 8 waves.
+template <int MODE, bool WIDE> struct FewBlocks {
+    static constexpr int fwd = MODE == MODE_BF16 ? (WIDE ? 4 : 2) : 4;
+    static constexpr int bwd = MODE == MODE_BF16 ? (WIDE ? 16 : 8) : 16;
+};
+constexpr int few_slot_rows(int mode) { return mode == MODE_BF16 ? 16 : 4; }
+inline __host__ __device__ size_t few_slot_bytes(int mode, int row_elems) {
+    return (size_t)few_slot_rows(mode) * (mode == MODE_BF16 ? 2 : 4) * row_elems;
+}
+inline __host__ __device__ size_t few_ring_bytes(int mode, int row_elems) { return FEW_RING * few_slot_bytes(mode, row_elems); }
+// LDS: two buffers of [8 waves][pieces][columns + 4] partial sums.
+constexpr int few_row(int cols) { return cols + 4; }   // (16 bytes more: the four row groups of a fragment hit different banks)
+inline __host__ __device__ size_t few_lds_bytes(int mode, int cols) {
+    return (size_t)2 * REC_WAVES * (mode == MODE_BF16 ? 16 : 4) * few_row(cols) * sizeof(float);
+}
+
+template <int I> struct FewIdx { static constexpr int value = I; };
+template <int N, int I = 0, typename F> __device__ __forceinline__ void few_for(F&& f) {
+    if constexpr (I < N) {
+        f(FewIdx<I>{});
+        few_for<N, I + 1>(f);
+    }
+}
+template <int CTRL> __device__ __forceinline__ unsigned few_dpp(unsigned v) {
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+// Lane i of every row of 16 gets the value of lane (i + S) % 16.
+template <int S> __device__ __forceinline__ f32x4_t few_rot(u32x4_t v) {
+    if constexpr (S != 0) {
+        constexpr int CTRL = 0x120 + 16 - S;   // row_ror:(16 - S)
+        v = u32x4_t{few_dpp<CTRL>(v[0]), few_dpp<CTRL>(v[1]), few_dpp<CTRL>(v[2]), few_dpp<CTRL>(v[3])};
+    }
+    return __builtin_bit_cast(f32x4_t, v);
+}
+// acc + sum of w[e] * (v[e] of lane I of the lane's row of 16).  Written out because the compiler makes a move and a
+// multiply-add of every term; the wait states are those between a write of a register and its use through DPP.
+template <int I> __device__ __forceinline__ float few_fma4(float acc, u32x4_t v, f32x4_t w) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %1, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %2, %6 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %3, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %4, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+        : "+v"(acc)
+        : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "n"(I));
+    return acc;
+}
+__device__ __forceinline__ void few_swap16(float& a, float& b) {   // odd rows of a <-> even rows of b
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void few_swap32(float& a, float& b) {   // upper half of a <-> lower half of b
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
+}
+// A word to publish: never FEW_EMPTY (only a pair of NaNs, or an fp32 NaN, has these bits; it stays NaN).
+__device__ __forceinline__ unsigned few_word(unsigned v) { return v == FEW_EMPTY ? FEW_EMPTY - 1 : v; }
+
+// Reads L x 16 bytes per lane at base + off[j]; with `check` again and again until no word is empty.  The loads
+// bypass the CU's L1 (sc0 sc1) and are written out because the compiler waits for every volatile load by itself.
+// Lanes that do not `take` part keep what raw holds.  False: the wait was abandoned (time-out here or in another
+// workgroup).
+template <int L>
+__device__ __forceinline__ bool few_read(const unsigned char* base, const unsigned (&off)[L], bool take, bool check, u32x4_t (&raw)[L], int* err) {
+    static_assert(L == 1 || L == 2 || L == 4, "loads per poll");
+    long long spins = 0;
+    for (;;) {
+        unsigned m = 0;
+        if (take) {
+            if constexpr (L == 1)
+                asm volatile("global_load_dwordx4 %0, %1, %2 sc0 sc1\n\ts_waitcnt vmcnt(0)" : "+&v"(raw[0]) : "v"(off[0]), "s"(base) : "memory");
+            else if constexpr (L == 2)
+                asm volatile("global_load_dwordx4 %0, %2, %4 sc0 sc1\n\tglobal_load_dwordx4 %1, %3, %4 sc0 sc1\n\ts_waitcnt vmcnt(0)"
+                             : "+&v"(raw[0]), "+&v"(raw[1]) : "v"(off[0]), "v"(off[1]), "s"(base) : "memory");
+            else
+                asm volatile("global_load_dwordx4 %0, %4, %8 sc0 sc1\n\tglobal_load_dwordx4 %1, %5, %8 sc0 sc1\n\t"
+                             "global_load_dwordx4 %2, %6, %8 sc0 sc1\n\tglobal_load_dwordx4 %3, %7, %8 sc0 sc1\n\ts_waitcnt vmcnt(0)"
+                             : "+&v"(raw[0]), "+&v"(raw[1]), "+&v"(raw[2]), "+&v"(raw[3])
+                             : "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "memory");
+#pragma unroll
+            for (int j = 0; j < L; ++j) m = max(max(m, max(raw[j][0], raw[j][1])), max(raw[j][2], raw[j][3]));
+        }
+        if (!check || __all(m != FEW_EMPTY)) return true;
+        ++spins;
+        if ((spins & 1023) == 0 && (spins > REC_SPIN_LIMIT || ld_agent(err) != 0)) {
+            st_agent(err, 1);
+            return false;
+        }
+    }
+}
+// Offsets of the L loads of a lane: block blk + j * BPL of the slice, or block blk again where the slice has no such
+// block (its weights are zero).
+template <int L, int BPL, int STRIDE>
+__device__ __forceinline__ void few_offsets(unsigned (&off)[L], unsigned first, int blk, int n_blk) {
+#pragma unroll
+    for (int j = 0; j < L; ++j) off[j] = first + (blk + j * BPL < n_blk ? j * STRIDE : 0);
+}
+
+// Product of the operand blocks [B0, B0 + L * BPL) of this wave's slice with all its tiles, added into acc.
+// bf16: pieces are the rows of A, a tile's gate rows (units) the columns: lane l holds column l % 16 and rows (pieces)
+// (l / 16) * 4 + e.  fp32: acc[tile][piece] on the vector ALUs, a lane's share of the contraction.
+template <int MODE, int MT, int NB, int P, int B0, int L>
+__device__ __forceinline__ void few_product(const f32x4_t (&w)[MT * NB], const u32x4_t (&raw)[L], int bs, f32x4_t (&acc)[MT]) {
+    constexpr int BPL = 16 / P, N = NB - B0 < L * BPL ? NB - B0 : L * BPL;
+    if constexpr (MODE == MODE_BF16) {
+        few_for<N>([&](auto ib) {
+            constexpr int b = decltype(ib)::value;
+            const f32x4_t op = few_rot<P * (b % BPL)>(raw[b / BPL]);
+#pragma unroll
+            for (int j = 0; j < MT; ++j) acc[j] = mfma_block<MODE>(op, w[j * NB + B0 + b], acc[j]);
+        });
+    } else {
+        few_for<P>([&](auto ip) {
+            constexpr int p = decltype(ip)::value;
+            if (p < bs)
+                few_for<N>([&](auto ib) {
+                    constexpr int b = decltype(ib)::value;
+#pragma unroll
+                    for (int j = 0; j < MT; ++j) acc[j][p] = few_fma4<p + P * (b % BPL)>(acc[j][p], raw[b / BPL], w[j * NB + B0 + b]);
+                });
+        });
+    }
+}
+// Leaves the wave's partial sums in LDS: s[piece * few_row(16 MT) + column].
+template <int MODE, int MT, int P>
+__device__ __forceinline__ void few_write(const f32x4_t (&acc)[MT], int bs, float* s) {
+    constexpr int ROW = few_row(16 * MT);
+    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+    if constexpr (MODE == MODE_BF16 && P > 4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (lk * 4 + e < bs)
+#pragma unroll
+                for (int j = 0; j < MT; ++j) s[(lk * 4 + e) * ROW + j * 16 + lr] = acc[j][e];
+    } else if constexpr (MODE == MODE_BF16) {   // pieces 0 .. P-1 <= 3 sit in lanes 0..15: gather up to four tiles in one store
+#pragma unroll
+        for (int e = 0; e < P; ++e)
+            if (e < bs) {
+                if constexpr (MT >= 4) {
+#pragma unroll
+                    for (int g = 0; g < MT; g += 4) {
+                        float a = acc[g][e], b = acc[g + 1][e], c = acc[g + 2][e], d = acc[g + 3][e];
+                        few_swap16(a, b);
+                        few_swap16(c, d);
+                        few_swap32(a, c);
+                        s[e * ROW + g * 16 + lane] = a;
+                    }
+                } else if constexpr (MT == 2) {
+                    float a = acc[0][e], b = acc[1][e];
+                    few_swap16(a, b);
+                    if (lane < 32) s[e * ROW + lane] = a;
+                } else {
+                    if (lane < 16) s[e * ROW + lane] = acc[0][e];
+                }
+            }
+    } else {   // fp32: the four lane groups hold shares of every sum
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+            if (p < bs) {
+                if constexpr (MT == 4) {
+                    float a = acc[0][p], b = acc[1][p], c = acc[2][p], d = acc[3][p];
+                    few_swap16(a, b);
+                    few_swap16(c, d);
+                    float u = a + b, v = c + d;
+                    few_swap32(u, v);
+                    s[p * ROW + lane] = u + v;
+                } else {
+                    static_assert(MT == 1, "tiles of the fp32 loops");
+                    float a = acc[0][p], b = a;
+                    few_swap32(a, b);
+                    float u = a + b, v = u;
+                    few_swap16(u, v);
+                    if (lane < 16) s[p * ROW + lane] = u + v;
+                }
+            }
+    }
+}
+
+// Batch sizes of 128 consecutive timesteps, two per lane: a scalar read costs no memory access.  DIR = 1: the
+// window moves up, -1: down.
+template <int DIR>
+struct FewWindow {
+    const int32_t* bs;
+    int T, lo;       // cur: timesteps lo .. lo + 63; other: the 64 after (DIR = 1) or before (DIR = -1)
+    int cur, other;
+    __device__ __forceinline__ int fetch(int first) const {
+        const int t = first + (int)(threadIdx.x & 63);
+        return t >= 0 && t < T ? bs[t] : 0;
+    }
+    __device__ __forceinline__ void init(const int32_t* b, int n, int t) {
+        bs = b; T = n;
+        lo = DIR > 0 ? t : t - 63;
+        cur = fetch(lo);
+        other = fetch(lo + DIR * 64);
+    }
+    __device__ __forceinline__ int at(int t) const {
+        const int d = t - lo;
+        const bool in = d >= 0 && d < 64;
+        return in ? __builtin_amdgcn_readlane(cur, d) : __builtin_amdgcn_readlane(other, d - DIR * 64);
+    }
+    __device__ __forceinline__ void advance(int t) {   // t: the timestep read next
+        const int d = t - lo;
+        if (d >= 0 && d < 64) return;
+        cur = other;
+        lo += DIR * 64;
+        other = fetch(lo + DIR * 64);
+    }
+};
+
+// Empties this workgroup's words of every slot (cols elements from column j0).
+template <int MODE>
+__device__ __forceinline__ void few_clear_ring(unsigned char* ring, int row_elems, int j0, int cols) {
+    constexpr int es = (int)sizeof(typename RecGeom<MODE>::E), MAX = few_slot_rows(MODE);
+    const int words = cols * es / 4;
+    for (int i = threadIdx.x; i < FEW_RING * MAX * words; i += REC_THREADS)
+        reinterpret_cast<unsigned*>(ring)[(size_t)(i / words) * (row_elems * es / 4) + j0 * es / 4 + i % words] = FEW_EMPTY;
+}
+
+// ---- forward ------------------------------------------------------------------------------------------------
+// What a group's workgroup carries through its timesteps with few pieces.
+template <int MODE, int MT, int NB>
+struct FewFwd {
+    f32x4_t w[MT * NB];
+    FewWindow<1> win;
+    int bs_a, bs_b;              // alive pieces of all groups at t, t + 1
+    int base, base_prev;         // first row of timesteps t, t - 1
+    int t0;                      // first timestep of this form
+    int c_wait;                  // consumer: the chunk it has to wait for next
+    int n_slices, slice, n_blk;  // slices with work, this wave's slice, its operand blocks
+    float c;                     // this thread's cell state
+    f32x4_t z;                   // its input projection of timestep t
+    f32x4_t s_g; float s_c, s_h; unsigned s_w;   // results of the timestep before, not yet stored
+    int* fail;                   // LDS
+    float* part;                 // LDS
+};
+
+template <int MODE, int MT, int NB, int PIPE>
+__device__ __forceinline__ void few_fwd_store(const FewFwd<MODE, MT, NB>& s, const RecFwdArgs& a, const PieceSet& ps, int j0, int bs_prev,
+                                              int base, int bs) {
+    typedef typename RecGeom<MODE>::E E;
+    constexpr int UH = 4 * MT, es = (int)sizeof(E);
+    const int m = threadIdx.x / UH, u = threadIdx.x % UH, n = m * ps.X + ps.x, H = a.H;
+    if (m >= bs_prev) return;
+    constexpr int WHOLE = (int)0x80000000u;
+    const unsigned col = (unsigned)(n * H + j0 + u);
+    const unsigned so = (unsigned)s.base_prev * (unsigned)H;   // elements of an [M, H] array
+    const __amdgpu_buffer_rsrc_t rs_g = __builtin_amdgcn_make_buffer_rsrc(a.gates, 0, WHOLE, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_c = __builtin_amdgcn_make_buffer_rsrc(a.c, 0, WHOLE, 0x00020000);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, s.s_g), rs_g, col * 16u, so * 16u, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s.s_c), rs_c, col * 4u, so * 4u, 0);
+    if (PIPE != PIPE_PRODUCER) {
+        const __amdgpu_buffer_rsrc_t rs_h = __builtin_amdgcn_make_buffer_rsrc(a.hout, 0, WHOLE, 0x00020000);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s.s_h), rs_h, col * 4u, so * 4u, 0);
+    }
+    if (MODE == MODE_F32 || (u & 1) == 0) {   // operand type: a bf16 pair per even lane
+        if (m < bs) {
+            const __amdgpu_buffer_rsrc_t rs_hp = __builtin_amdgcn_make_buffer_rsrc(a.hprev, 0, WHOLE, 0x00020000);
+            __builtin_amdgcn_raw_buffer_store_b32(s.s_w, rs_hp, col * es, (unsigned)base * (unsigned)(H * es), 0);
+        }
+        if (PIPE == PIPE_PRODUCER) {   // written through: input of the workers' GEMM
+            const __amdgpu_buffer_rsrc_t rs_hc = __builtin_amdgcn_make_buffer_rsrc(a.hcopy, 0, WHOLE, 0x00020000);
+            __builtin_amdgcn_raw_buffer_store_b32(s.s_w, rs_hc, col * es, so * es, 17);
+        }
+    }
+}
+
+// Runs timesteps while more than `down_to` (and at most P) pieces are alive.  False: a wait was abandoned.
+template <int MODE, int MT, int NB, int P, int PIPE>
+__device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const RecFwdArgs& a, const PieceSet& ps, int rank, int* flags,
+                                              unsigned char* ring, const PipeLink& pl, int& t, int T, int down_to) {
+    typedef typename RecGeom<MODE>::E E;
+    constexpr int es = (int)sizeof(E), KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC;
+    constexpr int UH = 4 * MT, COLS = 16 * MT, ROW = few_row(COLS), MAX = few_slot_rows(MODE);
+    constexpr int BPL = 16 / P, L = (NB + BPL - 1) / BPL, STRIDE = BPL * KBLK * es;
+    const int X = ps.X, x = ps.x, H = a.H;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = tid / UH, u = tid % UH, j0 = rank * UH;
+    const int piece = lr % P, blk = lr / P;
+    const unsigned k_off = (unsigned)((s.slice * NB + blk) * KBLK + lk * VEC) * es;   // this lane's first 16 bytes inside a row
+    const unsigned slot = (unsigned)few_slot_bytes(MODE, H);
+    const unsigned w_off = (unsigned)(m * H + j0 + u) * es;   // where this thread's value goes inside a slot
+    const bool polls = s.slice < s.n_slices;
+    unsigned off[L];
+    few_offsets<L, BPL, STRIDE>(off, (unsigned)(piece * H) * es + k_off, blk, s.n_blk);
+    u32x4_t raw[L];
+#pragma unroll
+    for (int j = 0; j < L; ++j) raw[j] = u32x4_t{0u, 0u, 0u, 0u};
+    constexpr int WHOLE = (int)0x80000000u;
+    const __amdgpu_buffer_rsrc_t rs_g = __builtin_amdgcn_make_buffer_rsrc(a.gates, 0, WHOLE, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_ring = __builtin_amdgcn_make_buffer_rsrc(ring, 0, (int)(FEW_RING * slot), 0x00020000);
+
+    auto step = [&](f32x4_t& z, f32x4_t& z_next) -> bool {
+        const int bs = grp_count(s.bs_a, ps), bs_next = t + 1 < T ? grp_count(s.bs_b, ps) : 0;
+        const int base_next = s.base + s.bs_a;
+        if (PIPE == PIPE_CONSUMER && t + 1 < T && t + 1 == s.c_wait * pl.ct) {
+            if (!pipe_wait_chunk(pl, s.c_wait, a.err)) return false;
+            ++s.c_wait;
+        }
+        bool ok = true;
+        if (t == s.t0) {
+            // the rows were written under the flag protocol (initial states, or the timestep before with more pieces)
+            if (!rec_wait(flags, a.G, t + 1, a.err)) return false;
+            if (PIPE == PIPE_PRODUCER && rank == 0 && tid == 0 && t > 0) st_agent(pl.progress, t);
+            if (polls) {
+                unsigned first[L];
+                few_offsets<L, BPL, STRIDE>(first, (unsigned)(piece * X * H) * es + k_off, blk, s.n_blk);
+                few_read<L>(reinterpret_cast<const unsigned char*>(static_cast<const E*>(a.hprev) + (size_t)(s.base + x) * H), first,
+                            piece < bs && blk < s.n_blk, false, raw, a.err);
+            }
+        } else if (polls) {
+            ok = few_read<L>(ring + (unsigned)((t - 1) & (FEW_RING - 1)) * slot, off, piece < bs && blk < s.n_blk, true, raw, a.err);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (also: this wave's stores of two timesteps ago have completed)
+        if (!ok) *s.fail = 1;
+        const int bs_c = s.win.at(t + 2);
+        s.win.advance(t + 3);
+        // off the critical path: results of the timestep before, the input projection of the next one
+        if (m < bs_next)
+            z_next = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs_g, (unsigned)((m * X + x) * H + j0 + u) * 16u,
+                                                                                        (unsigned)base_next * (unsigned)H * 16u, 0));
+        if (t > s.t0) few_fwd_store<MODE, MT, NB, PIPE>(s, a, ps, j0, grp_count(s.base - s.base_prev, ps), s.base, bs);
+        float* part = s.part + (t & 1) * (REC_WAVES * MAX * ROW);
+        if (polls) {
+            f32x4_t acc[MT];
+#pragma unroll
+            for (int j = 0; j < MT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            few_product<MODE, MT, NB, P, 0, L>(s.w, raw, bs, acc);
+            few_write<MODE, MT, P>(acc, bs, part + s.slice * (MAX * ROW));
+        }
+        bar_lds();
+        if (*s.fail) return false;
+        // Every workgroup has published the rows of timestep t-1, which it did after its stores for timestep t-3 had
+        // completed (they are issued in timestep t-2 and waited for in timestep t-1).
+        if (PIPE == PIPE_PRODUCER && rank == 0 && tid == REC_THREADS - 1 && t - 2 > s.t0) st_agent(pl.progress, t - 2);
+        if (m < bs) {
+            f32x4_t q = z;
+            const float* p = part + m * ROW + u * 4;
+#pragma unroll
+            for (int k = 0; k < REC_WAVES; ++k)
+                if (k < s.n_slices) {
+                    const f32x4_t o = *reinterpret_cast<const f32x4_t*>(p + k * (MAX * ROW));
+                    q[0] += o[0]; q[1] += o[1]; q[2] += o[2]; q[3] += o[3];
+                }
+            const float gi = sigmoidf_(q[0]), gf = sigmoidf_(q[1]), gg = tanhf_(q[2]), go = sigmoidf_(q[3]);
+            s.c = gf * s.c + gi * gg;
+            const float h = go * tanhf_(s.c);
+            s.s_g = f32x4_t{gi, gf, gg, go};
+            s.s_c = s.c;
+            s.s_h = h;
+            if constexpr (MODE == MODE_BF16) {
+                const unsigned b = to_bf16_finite(h);
+                s.s_w = few_word(b | (few_dpp<0xb1>(b) << 16));   // (quad_perm 1,0,3,2: the neighbour's value)
+            } else {
+                s.s_w = few_word(__float_as_uint(h));
+            }
+            if ((MODE == MODE_F32 || (u & 1) == 0) && m < bs_next) {
+                __builtin_amdgcn_raw_buffer_store_b32(s.s_w, rs_ring, w_off, (unsigned)(t & (FEW_RING - 1)) * slot, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(FEW_EMPTY, rs_ring, w_off, (unsigned)((t + 2) & (FEW_RING - 1)) * slot, 0);
+            }
+        }
+        s.base_prev = s.base;
+        s.base = base_next;
+        s.bs_a = s.bs_b;
+        s.bs_b = bs_c;
+        ++t;
+        return true;
+    };
+    // (two steps per iteration: a prefetched value is used where it was loaded, a move would wait for the load)
+    f32x4_t z2 = s.z;
+    while (t < T && grp_count(s.bs_a, ps) > down_to) {
+        if (!step(s.z, z2)) return false;
+        if (!(t < T && grp_count(s.bs_a, ps) > down_to)) {
+            s.z = z2;
+            break;
+        }
+        if (!step(z2, s.z)) return false;
+    }
+    return true;
+}
+
+// Timesteps [t0, T): at most FewMax pieces of the group are alive.  The rows of h_{t0-1} are in hprev, announced by
+// flag value t0 + 1.  False: a wait was abandoned.
+template <int MODE, int MT, int PIPE>
+__device__ __forceinline__ bool few_fwd(const RecFwdArgs& a, const PieceSet& ps, int rank, int t0, int T, int* flags, const PipeLink& pl,
+                                        int c_wait, unsigned char* ring, unsigned char* smem) {
+    typedef typename RecGeom<MODE>::E E;
+    constexpr int KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC, UH = 4 * MT;
+    constexpr int NB = FewBlocks<MODE, MT == 8>::fwd;
+    __shared__ int s_fail;
+    const int H = a.H, X = ps.X, x = ps.x;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
+    const int m = tid / UH, u = tid % UH, j0 = rank * UH;
+    FewFwd<MODE, MT, NB> s;
+    s.fail = &s_fail;
+    s.part = reinterpret_cast<float*>(smem);
+    if (tid == 0) s_fail = 0;
+    bar_lds();
+    const int blocks = H / KBLK;
+    s.n_slices = (blocks + NB - 1) / NB;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // which slice a wave takes rotates with the rank: the workgroups poll the same rows at the same moment
+    s.slice = s.n_slices == REC_WAVES ? (wave + rank) % REC_WAVES : wave;
+    s.n_blk = min(NB, blocks - s.slice * NB);
+#pragma unroll
+    for (int j = 0; j < MT; ++j) {
+        const E* wrow = static_cast<const E*>(a.whh) + ((size_t)j0 * 4 + j * 16 + lr) * H + s.slice * NB * KBLK + lk * VEC;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            s.w[j * NB + b] = b < s.n_blk ? *reinterpret_cast<const f32x4_t*>(wrow + b * KBLK) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    // (a use of the registers: the loads are complete before the time loop, see rec_fwd_body)
+#pragma unroll
+    for (int i = 0; i < MT * NB; ++i) asm volatile("" : "+v"(s.w[i]));
+    s.t0 = t0;
+    s.c_wait = c_wait;
+    s.win.init(a.batch_sizes, T, t0);
+    s.bs_a = s.win.at(t0);
+    s.bs_b = s.win.at(t0 + 1);
+    s.base = a.t_off[t0];
+    s.base_prev = t0 > 0 ? a.t_off[t0 - 1] : 0;
+    s.c = 0.f;
+    s.z = s.s_g = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    s.s_c = s.s_h = 0.f;
+    s.s_w = 0;
+    if (m < grp_count(s.bs_a, ps)) {
+        const int n = m * X + x;
+        s.z = *reinterpret_cast<const f32x4_t*>(a.gates + ((size_t)s.base + n) * 4 * H + (size_t)(j0 + u) * 4);
+        if (t0 > 0) s.c = a.c[((size_t)s.base_prev + n) * H + j0 + u];
+        else if (a.c0 && n < a.seq_cap) s.c = a.c0[(size_t)n * H + j0 + u];
+    }
+    int t = t0;
+    if constexpr (MODE == MODE_BF16)
+        if (!few_fwd_phase<MODE, MT, NB, 16, PIPE>(s, a, ps, rank, flags, ring, pl, t, T, 4)) return false;
+    if (!few_fwd_phase<MODE, MT, NB, 4, PIPE>(s, a, ps, rank, flags, ring, pl, t, T, 0)) return false;
+    few_fwd_store<MODE, MT, NB, PIPE>(s, a, ps, j0, grp_count(s.base - s.base_prev, ps), s.base, 0);
+    if (PIPE == PIPE_PRODUCER) rec_publish(flags, rank, T + 1);
+    return true;
+}
+
+// ---- backward -----------------------------------------------------------------------------------------------
+struct FewSaved {
+    f32x4_t g;                 // activated gates
+    float c_prev, dh_above;
+    float c;                   // only loaded for a piece whose last timestep this is
+};
+template <int MODE, int MT, int NB>
+struct FewBwd {
+    f32x4_t w[MT * NB];
+    FewWindow<-1> win;
+    int bs_up, bs_t, bs_m1, bs_m2;   // alive pieces of all groups at t + 1, t, t - 1, t - 2
+    int base;                        // first row of timestep t
+    int c_wait;                      // consumer: the lowest chunk it has waited for
+    int n_slices, slice, n_blk;
+    FewSaved sv, sv2;                // what the forward pass saved for timesteps t and t - 1
+    float dh, dc, c;                 // carried gradients, cell state of timestep t
+    float db[4];                     // sums of the gate gradients of this thread's unit
+    int* fail;
+    float* part;
+};
+
+// Requests the saved activations of timestep q (rows from base_q, of timestep q - 1 from base_q1).
+__device__ __forceinline__ void few_load_saved(FewSaved& sv, const RecBwdArgs& a, int m, int n, int j, int q, int bs_q, int bs_q_up, int base_q,
+                                               int base_q1) {
+    if (m >= bs_q) return;
+    constexpr int WHOLE = (int)0x80000000u;
+    const unsigned H = (unsigned)a.H, col = (unsigned)n * H + (unsigned)j, so = (unsigned)base_q * H;
+    const __amdgpu_buffer_rsrc_t rs_g = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.gates), 0, WHOLE, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_c = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.c), 0, WHOLE, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.dh_above), 0, WHOLE, 0x00020000);
+    sv.g = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs_g, col * 16u, so * 16u, 0));
+    sv.dh_above = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_a, col * 4u, so * 4u, 0));
+    if (q > 0) sv.c_prev = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_c, col * 4u, (unsigned)base_q1 * H * 4u, 0));
+    else sv.c_prev = (a.c0 && n < a.seq_cap) ? a.c0[(size_t)n * a.H + j] : 0.f;
+    if (bs_q > bs_q_up && m >= bs_q_up) sv.c = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_c, col * 4u, so * 4u, 0));
+}
+
+// Runs timesteps t, t-1, ... >= t_stop while at most `up_to` (<= P) pieces are alive.  False: a wait was abandoned.
+template <int MODE, int MT, int NB, int P, int PIPE>
+__device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const RecBwdArgs& a, const PieceSet& ps, int rank, unsigned char* ring,
+                                              const PipeLink& pl, int& t, int T, int t_stop, int up_to) {
+    typedef typename RecGeom<MODE>::E E;
+    constexpr int es = (int)sizeof(E), KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC;
+    constexpr int UH = 16 * MT, ROW = few_row(UH), MAX = few_slot_rows(MODE);
+    constexpr int BPL = 16 / P, L = (NB + BPL - 1) / BPL, STRIDE = BPL * KBLK * es;
+    constexpr int LH = L > 4 ? 4 : L;   // operand registers for this many loads at a time
+    const int X = ps.X, x = ps.x, H = a.H, K = 4 * H;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
+    const int m = tid / UH, u = tid % UH, j0 = rank * UH, n = m * X + x, j = j0 + u;
+    const int piece = lr % P, blk = lr / P;
+    const unsigned k_off = (unsigned)((s.slice * NB + blk) * KBLK + lk * VEC) * es;
+    const unsigned slot = (unsigned)few_slot_bytes(MODE, K);
+    const unsigned w_off = (unsigned)(m * K + j * 4) * es;
+    const bool polls = s.slice < s.n_slices;
+    unsigned off[L / LH][LH];
+    few_for<L / LH>([&](auto ig) {
+        constexpr int g = decltype(ig)::value;
+        const int b = blk + g * LH * BPL < s.n_blk ? blk + g * LH * BPL : blk;
+        few_offsets<LH, BPL, STRIDE>(off[g], (unsigned)(piece * K) * es + k_off + (unsigned)(b - blk) * (KBLK * es), b, s.n_blk);
+    });
+    u32x4_t raw[LH];
+#pragma unroll
+    for (int i = 0; i < LH; ++i) raw[i] = u32x4_t{0u, 0u, 0u, 0u};
+    constexpr int WHOLE = (int)0x80000000u;
+    const __amdgpu_buffer_rsrc_t rs_dz = __builtin_amdgcn_make_buffer_rsrc(a.dz, 0, WHOLE, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_ring = __builtin_amdgcn_make_buffer_rsrc(ring, 0, (int)(FEW_RING * slot), 0x00020000);
+    typedef unsigned wv_t __attribute__((ext_vector_type(MODE == MODE_BF16 ? 2 : 4)));
+    auto store = [&](wv_t v, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned so, auto aux) {
+        if constexpr (MODE == MODE_BF16) __builtin_amdgcn_raw_buffer_store_b64(v, rs, off, so, decltype(aux)::value);
+        else __builtin_amdgcn_raw_buffer_store_b128(v, rs, off, so, decltype(aux)::value);
+    };
+
+    auto step = [&](FewSaved& sv) -> bool {
+        const int bs = grp_count(s.bs_t, ps), bs_up = t + 1 < T ? grp_count(s.bs_up, ps) : 0;
+        wv_t word;
+#pragma unroll
+        for (int i = 0; i < (MODE == MODE_BF16 ? 2 : 4); ++i) word[i] = 0u;
+        // A. gate gradients of this thread's (piece, unit)
+        if (m < bs) {
+            const bool carried = m < bs_up;
+            const float gi = sv.g[0], gf = sv.g[1], gg = sv.g[2], go = sv.g[3];
+            const float dh = carried ? sv.dh_above + s.dh : sv.dh_above;
+            const float tc = tanhf_(carried ? s.c : sv.c);
+            const float dc = (carried ? s.dc : 0.f) + dh * go * (1.f - tc * tc);
+            const float dzi = dc * gg * gi * (1.f - gi), dzf = dc * sv.c_prev * gf * (1.f - gf), dzg = dc * gi * (1.f - gg * gg),
+                        dzo = dh * tc * go * (1.f - go);
+            if constexpr (MODE == MODE_BF16) {
+                word[0] = few_word((unsigned)to_bf16_finite(dzi) | ((unsigned)to_bf16_finite(dzf) << 16));
+                word[1] = few_word((unsigned)to_bf16_finite(dzg) | ((unsigned)to_bf16_finite(dzo) << 16));
+            } else {
+                word[0] = few_word(__float_as_uint(dzi)); word[1] = few_word(__float_as_uint(dzf));
+                word[2] = few_word(__float_as_uint(dzg)); word[3] = few_word(__float_as_uint(dzo));
+            }
+            if (t > 0) store(word, rs_ring, w_off, (unsigned)(t & (FEW_RING - 1)) * slot, FewIdx<0>{});
+            s.db[0] += dzi; s.db[1] += dzf; s.db[2] += dzg; s.db[3] += dzo;
+            s.dc = dc * gf;
+            s.c = sv.c_prev;
+        }
+        const unsigned so_dz = (unsigned)s.base * (unsigned)(K * es);
+        if (t == 0) {   // nothing is carried before the first timestep
+            if (m < bs) store(word, rs_dz, (unsigned)(n * K + j * 4) * es, so_dz, FewIdx<PIPE == PIPE_PRODUCER ? 17 : 0>{});
+            --t;
+            return true;
+        }
+        if (PIPE == PIPE_CONSUMER && t >= 2 && t - 2 < s.c_wait * pl.ct) {
+            --s.c_wait;
+            if (!pipe_wait_chunk(pl, s.c_wait, a.err)) return false;
+        }
+        // B. dh carried to t-1: dh[piece][k] = sum_q dz[piece][q] * W_hh[q][k] for this workgroup's columns k
+        const unsigned char* src = ring + (unsigned)(t & (FEW_RING - 1)) * slot;
+        f32x4_t acc[MT];
+#pragma unroll
+        for (int i = 0; i < MT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        bool ok = true;
+        if (polls) {
+            few_for<L / LH>([&](auto ig) {
+                constexpr int g = decltype(ig)::value;
+                if constexpr (g > 0) few_product<MODE, MT, NB, P, (g - 1) * LH * BPL, LH>(s.w, raw, bs, acc);
+                if (ok) ok = few_read<LH>(src, off[g], piece < bs && blk < s.n_blk, true, raw, a.err);
+            });
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (also: this wave's dz rows of timestep t+1 have completed)
+        if (!ok) *s.fail = 1;
+        const int bs_m3 = s.win.at(t - 3);
+        s.win.advance(t - 4);
+        // off the critical path: the dz rows of this timestep, the saved activations of timestep t-2
+        if (m < bs) store(word, rs_dz, (unsigned)(n * K + j * 4) * es, so_dz, FewIdx<PIPE == PIPE_PRODUCER ? 17 : 0>{});
+        if (t >= 2) {
+            const int base_2 = s.base - s.bs_m1 - s.bs_m2;
+            few_load_saved(sv, a, m, n, j, t - 2, grp_count(s.bs_m2, ps), grp_count(s.bs_m1, ps), base_2, base_2 - bs_m3);
+        }
+        float* part = s.part + (t & 1) * (REC_WAVES * MAX * ROW);
+        if (polls) {
+            few_product<MODE, MT, NB, P, (L - LH) * BPL, LH>(s.w, raw, bs, acc);
+            few_write<MODE, MT, P>(acc, bs, part + s.slice * (MAX * ROW));
+        }
+        bar_lds();
+        if (*s.fail) return false;
+        // Every workgroup has published the rows of timestep t, which it did after its dz rows of timestep t+2 had
+        // completed (they are stored in that timestep and waited for in timestep t+1).
+        if (PIPE == PIPE_PRODUCER && rank == 0 && tid == REC_THREADS - 1 && t + 2 < T) st_agent(pl.progress, T - (t + 2));
+        if (m < bs) {
+            store(wv_t(FEW_EMPTY), rs_ring, w_off, (unsigned)((t + 1) & (FEW_RING - 1)) * slot, FewIdx<0>{});
+            float q = 0.f;
+            const float* p = part + m * ROW + u;
+#pragma unroll
+            for (int k = 0; k < REC_WAVES; ++k)
+                if (k < s.n_slices) q += p[k * (MAX * ROW)];
+            s.dh = q;
+        }
+        s.base -= s.bs_m1;
+        s.bs_up = s.bs_t;
+        s.bs_t = s.bs_m1;
+        s.bs_m1 = s.bs_m2;
+        s.bs_m2 = bs_m3;
+        --t;
+        return true;
+    };
+    while (t >= t_stop && grp_count(s.bs_t, ps) <= up_to) {
+        if (!step(s.sv)) return false;
+        if (!(t >= t_stop && grp_count(s.bs_t, ps) <= up_to)) {
+            const FewSaved o = s.sv;
+            s.sv = s.sv2;
+            s.sv2 = o;
+            break;
+        }
+        if (!step(s.sv2)) return false;
+    }
+    return true;
+}
+
+// Timesteps T-1 .. t_stop: at most FewMax pieces of the group are alive.  Leaves the carried gradients of this
+// thread's (piece, unit), the sums of its gate gradients and the lowest chunk waited for.  False: a wait was abandoned.
+template <int MODE, int MT, int PIPE>
+__device__ __forceinline__ bool few_bwd(const RecBwdArgs& a, const PieceSet& ps, int rank, int t_stop, int T, const PipeLink& pl, int& c_wait,
+                                        unsigned char* ring, unsigned char* smem, float& dh, float& dc, float (&db)[4]) {
+    typedef typename RecGeom<MODE>::E E;
+    constexpr int KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC, UH = 16 * MT;
+    constexpr int NB = FewBlocks<MODE, MT == 2>::bwd, LOW = 16 / NB;
+    __shared__ int s_fail;
+    const int H = a.H, K = 4 * H, X = ps.X, x = ps.x;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
+    const int m = tid / UH, j = rank * UH + tid % UH, n = m * X + x;
+    FewBwd<MODE, MT, NB> s;
+    s.fail = &s_fail;
+    s.part = reinterpret_cast<float*>(smem);
+    if (tid == 0) s_fail = 0;
+    bar_lds();
+    const int blocks = K / KBLK;
+    s.n_slices = (blocks + NB - 1) / NB;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    s.slice = s.n_slices == REC_WAVES ? (wave + rank) % REC_WAVES : wave;
+    s.n_blk = min(NB, blocks - s.slice * NB);
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        const E* wrow = static_cast<const E*>(a.whhT) + ((size_t)rank * UH + i * 16 + lr) * K + s.slice * NB * KBLK + lk * VEC;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            s.w[i * NB + b] = b < s.n_blk ? *reinterpret_cast<const f32x4_t*>(wrow + b * KBLK) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int i = 0; i < MT * NB; ++i) asm volatile("" : "+v"(s.w[i]));
+    s.c_wait = c_wait;
+    s.win.init(a.batch_sizes, T, T - 1);
+    s.bs_up = 0;
+    s.bs_t = s.win.at(T - 1);
+    s.bs_m1 = s.win.at(T - 2);
+    s.bs_m2 = s.win.at(T - 3);
+    s.base = a.t_off[T - 1];
+    s.dh = s.dc = s.c = 0.f;
+    s.sv.g = s.sv2.g = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    s.sv.c_prev = s.sv.dh_above = s.sv.c = s.sv2.c_prev = s.sv2.dh_above = s.sv2.c = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s.db[i] = db[i];
+    few_load_saved(s.sv, a, m, n, j, T - 1, grp_count(s.bs_t, ps), 0, s.base, s.base - s.bs_m1);
+    if (T > 1) {
+        if (PIPE == PIPE_CONSUMER && T - 2 < s.c_wait * pl.ct) {
+            --s.c_wait;
+            if (!pipe_wait_chunk(pl, s.c_wait, a.err)) return false;
+        }
+        const int base_1 = s.base - s.bs_m1;
+        few_load_saved(s.sv2, a, m, n, j, T - 2, grp_count(s.bs_m1, ps), grp_count(s.bs_t, ps), base_1, base_1 - s.bs_m2);
+    }
+    int t = T - 1;
+    if (!few_bwd_phase<MODE, MT, NB, LOW, PIPE>(s, a, ps, rank, ring, pl, t, T, t_stop, LOW)) return false;
+    if (!few_bwd_phase<MODE, MT, NB, 4, PIPE>(s, a, ps, rank, ring, pl, t, T, t_stop, 4)) return false;
+    if constexpr (MODE == MODE_BF16)
+        if (!few_bwd_phase<MODE, MT, NB, 8, PIPE>(s, a, ps, rank, ring, pl, t, T, t_stop, 8)) return false;
+    c_wait = s.c_wait;
+    dh = s.dh;
+    dc = s.dc;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) db[i] = s.db[i];
+    return true;
+}
+
+}  // namespace ver

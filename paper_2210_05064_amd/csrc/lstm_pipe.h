@@ -56,9 +56,8 @@ constexpr int PIPE_CT_MIN = 4;
 inline __host__ __device__ int pipe_done_stride(int M) { return M / PIPE_CT_MIN + 2; }
 inline __host__ __device__ int pipe_sync_words(int M) { return 16 + PIPE_GROUPS * pipe_done_stride(M); }
 
-// Predicted microseconds of a timestep: step + piece * b + tile * (ceil(b / 16) - 1) (b alive pieces of the group;
-// least-squares fit to the measured times of the groups of 16 minibatches of the paper's largest configuration:
-// residual 26 us (forward) and 31 us (backward) rms on group times of 0.8-2 ms), and the timesteps per chunk: at most ct0 for group 0 (every timestep of a chunk delays the
+// Predicted microseconds of a timestep: step + piece * b + tile * (ceil(b / 16) - 1) (b alive pieces of the group),
+// and the timesteps per chunk: at most ct0 for group 0 (every timestep of a chunk delays the
 // end of the launch once), at most ct for the other groups (which have time to spare: fewer, fuller tiles), and
 // no more than chunk_rows / (pieces of the group): the consumer of a group ends one chunk of GEMM tiles and one
 // chunk of its own steps after the producer, and starts as much later.
@@ -66,20 +65,21 @@ struct PlanCost {
     float step, piece, tile;
     int ct0, ct, chunk_rows;
 };
-#ifndef VER_PLAN_CT0
-#define VER_PLAN_CT0 8
-#endif
-#ifndef VER_PLAN_CT
-#define VER_PLAN_CT 16
-#endif
-#ifndef VER_PLAN_CHUNK_ROWS
-#define VER_PLAN_CHUNK_ROWS 256
-#endif
-constexpr PlanCost PLAN_COST_FWD = {2.96f, 0.082f, 1.48f, VER_PLAN_CT0, VER_PLAN_CT, VER_PLAN_CHUNK_ROWS};
-#ifndef VER_PLAN_CT0_BWD
-#define VER_PLAN_CT0_BWD VER_PLAN_CT0
-#endif
-constexpr PlanCost PLAN_COST_BWD = {2.83f, 0.167f, 1.95f, VER_PLAN_CT0_BWD, VER_PLAN_CT, VER_PLAN_CHUNK_ROWS};
+constexpr int PLAN_CT0 = 8, PLAN_CTN = 16, PLAN_CHUNK_ROWS = 256;
+// Fitted by hand to the time per timestep of launches over equally long pieces, 1 .. 64 per group (us):
+//   pieces               1     2     4     8    16    32    64
+//   bf16 H=1024 fwd   1.66  1.72  1.92  2.37  3.0   5.7  12.5      bwd  1.86  2.23  3.0   3.45  4.9   9.0  18
+//   bf16 H=512  fwd   1.41  1.42  1.52  1.62  1.85  3.05           bwd  1.64  1.69  2.0   2.7   3.1   4.4
+//   fp32 H=512  fwd   1.52  1.82  2.5   4.0   4.6   8.9            bwd  1.66  2.37  3.8   4.7   5.7  10.5
+// (timesteps with up to 16 pieces forward, 8 backward, 4 in fp32 run in the form of lstm_few.h).
+inline PlanCost plan_cost(int mode, bool wide, bool fwd) {
+    PlanCost c;
+    if (mode == MODE_F32) c = fwd ? PlanCost{1.35f, 0.23f, 0.2f} : PlanCost{1.7f, 0.29f, 0.f};
+    else if (wide) c = fwd ? PlanCost{1.58f, 0.09f, 1.4f} : PlanCost{1.85f, 0.2f, 1.f};
+    else c = fwd ? PlanCost{1.35f, 0.035f, 0.6f} : PlanCost{1.55f, 0.1f, 0.f};
+    c.ct0 = PLAN_CT0; c.ct = PLAN_CTN; c.chunk_rows = PLAN_CHUNK_ROWS;
+    return c;
+}
 
 struct PipeWork {
     const void* A;      // producer rows [M, K], operand type (forward: h, backward: dz)

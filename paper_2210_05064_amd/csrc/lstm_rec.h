@@ -33,6 +33,8 @@
 //    no cross-lane traffic;
 //  * 4H (forward) or H (backward) sits on the MFMA M dimension and the alive
 //    pieces on N, so a ragged tail of one or two pieces wastes only N padding;
+//  * timesteps with few alive pieces, which are most of the timesteps that bound a launch, run in another form with
+//    another exchange (lstm_few.h); what follows here is the form for many pieces;
 //  * every wait is bounded and sticky: on time-out the error word is set, every
 //    workgroup that sees it leaves the kernel, so the grid always drains.
 #pragma once
@@ -473,39 +475,6 @@ __device__ __forceinline__ void mma_rows(const f32x4_t (&wreg)[TPW * NBW], const
     }
 }
 
-// ---- few alive pieces in fp32: the vector ALUs instead of the matrix cores --------------------------------
-// An fp32 MFMA (16x16x4) takes a weight through the matrix core at 2 per cycle and SIMD whatever the number of
-// alive pieces; a vector FMA takes 16 per cycle and piece.  Up to REC_VALU_ROWS alive pieces of a group the
-// product of a timestep is therefore computed piece by piece on the vector ALUs, from the same registers: a lane
-// holds 4 consecutive weights of gate row lr per operand block (the MFMA's A layout), reads the matching 4 values
-// of the piece's row from LDS (the same address in the 16 lanes of a row group: a broadcast), and the four
-// partial sums of a row (lk = 0..3) are added across the wave.  The result goes where the MFMA's accumulator of
-// the same (tile, piece) would have gone: out[...] is the f32x4 fragment array of piece tile 0 (64 lanes: column
-// = piece, element e of lane group lk = row lk*4 + e).  bf16 gains nothing from this (a packed dot product takes
-// 32 weights per cycle, as the bf16 MFMA does).
-constexpr int REC_VALU_ROWS = 3;   // (measured on the 2 x 512 fp32 workloads: 2 to 4 within 1 % of each other, 6 and 8 slower)
-template <int NW>
-__device__ __forceinline__ float valu_row_sum(const f32x4_t (&wreg)[NW], int w0, int n, const float* prow, int nb_rt, int rot,
-                                              int nbw, bool is_static) {
-    float p0 = 0.f, p1 = 0.f;   // two chains
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        if (i >= n) break;
-        if (is_static || i < nb_rt) {
-            const int v = i + rot;
-            const int blk = is_static ? v % nbw : (v >= nb_rt ? v - nb_rt : v);
-            const f32x4_t b = *reinterpret_cast<const f32x4_t*>(prow + blk * RecGeom<MODE_F32>::KBLK);
-            const f32x4_t w = wreg[w0 + i];
-            p0 = fmaf(w[0], b[0], p0); p1 = fmaf(w[1], b[1], p1);
-            p0 = fmaf(w[2], b[2], p0); p1 = fmaf(w[3], b[3], p1);
-        }
-    }
-    float p = p0 + p1;
-    p += __shfl_xor(p, 16, VER_WAVE);
-    p += __shfl_xor(p, 32, VER_WAVE);
-    return p;
-}
-
 // ======================================================================================================
 struct RecFwdArgs {
     const int32_t* info;
@@ -517,6 +486,7 @@ struct RecFwdArgs {
     void* hprev;        // [M, H] operand type: row p = h_{t-1} of the piece in row p
     void* hcopy;        // [M, H] operand type: row p = h_t, written through for the workers (producer layer only)
     const void* whh;    // [4H, H] operand type, interleaved rows
+    void* ring;         // exchange ring of the layer's groups (lstm_few.h)
     const float* h0;    // [seq_cap, H] of this layer, or NULL
     const float* c0;
     int H, seq_cap, M;
@@ -528,6 +498,35 @@ struct RecFwdArgs {
     long long* prof;    // [16] phase cycle counters (only touched by builds with VER_REC_PROF)
     long long* prof_all;   // start of the profiling words
 };
+struct RecBwdArgs {
+    const int32_t* info;
+    const int32_t* batch_sizes;
+    const int32_t* t_off;
+    const float* gates;     // [M, 4H] activated gates (interleaved)
+    const float* c;         // [M, H]
+    const float* c0;        // [seq_cap, H] of this layer or NULL
+    const float* dh_above;  // [M, H] gradient arriving at h_t from the layer above / the heads
+    void* dz;               // [M, 4H] operand type (out): gradient at the gate pre-activations
+    const void* whhT;       // [H, 4H] operand type: row k = column k of the interleaved W_hh
+    float* dh_state;        // [n_cap, H] recurrent gradient carried to the previous timestep
+    float* dc_state;        // [n_cap, H]
+    void* ring;             // exchange ring of the layer's groups (lstm_few.h)
+    float* db_part;         // [groups, 4H] (out): every group's sum of dz over its rows, interleaved columns
+    int H, seq_cap;
+    int G;                  // participating workgroups; each owns 16*MT hidden units
+    int ntc;
+    int* flags;
+    int* ticket;
+    int* err;
+    long long* prof;
+    long long* prof_all;
+};
+
+}  // namespace ver
+
+#include "lstm_few.h"
+
+namespace ver {
 
 // Waves are (row group rg, contraction share ks): REC_WAVES = RG * KS; a wave multiplies TPW tiles of 16 gate
 // rows over 1/KS of the contraction; the workgroup owns MT = RG*TPW tiles = 4*MT hidden units.  In the
@@ -559,6 +558,23 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
     const int nb = (H / KS) / KBLK;
     const int rot = (rank / KS) % nb;
 
+    // initial hidden state of every piece, this workgroup's columns
+    for (int i = tid; i < n_seq * (UH / 4); i += REC_THREADS) {
+        const int n = (i / (UH / 4)) * X + x, u = (i % (UH / 4)) * 4;
+        f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+        if (a.h0 && n < a.seq_cap) v = *reinterpret_cast<const f32x4_t*>(a.h0 + (size_t)n * H + j0 + u);
+        st_row4<E>(hprev + (size_t)n * H + j0 + u, v[0], v[1], v[2], v[3]);
+    }
+    // From timestep t0 on at most FewMax pieces of the group are alive: those timesteps run in the form of lstm_few.h.
+    const int t0 = n_seq > FewMax<MODE>::fwd ? grp_steps(a.batch_sizes, T, FewMax<MODE>::fwd * X + x) : 0;
+    unsigned char* ring = static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, H);
+    few_clear_ring<MODE>(ring, H, j0, UH);
+    rec_publish(flags, rank, 1);
+    REC_PROF_DECL
+    REC_PROF_START();
+    if (PIPE == PIPE_CONSUMER && T > 0 && !pipe_wait_chunk(pl, 0, a.err, REC_PROF_CHUNK_ACC(a, rank, ps))) return;
+    int c_wait = 1;   // consumer: the chunk it has to wait for next
+    if (t0 > 0) {
     // this wave's rows of W_hh (its share of the contraction) -> registers, in MFMA operand layout
     f32x4_t wreg[TPW * NBW];
 #pragma unroll
@@ -575,16 +591,6 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
     // activations), ending in a wait for everything after the last MFMA of every timestep.
 #pragma unroll
     for (int i = 0; i < TPW * NBW; ++i) asm volatile("" : "+v"(wreg[i]));
-    // initial hidden state of every piece, this workgroup's columns
-    for (int i = tid; i < n_seq * (UH / 4); i += REC_THREADS) {
-        const int n = (i / (UH / 4)) * X + x, u = (i % (UH / 4)) * 4;
-        f32x4_t v = {0.f, 0.f, 0.f, 0.f};
-        if (a.h0 && n < a.seq_cap) v = *reinterpret_cast<const f32x4_t*>(a.h0 + (size_t)n * H + j0 + u);
-        st_row4<E>(hprev + (size_t)n * H + j0 + u, v[0], v[1], v[2], v[3]);
-    }
-    rec_publish(flags, rank, 1);
-    REC_PROF_DECL
-    REC_PROF_START();
     // epilogue role: wave `wave` owns row tile `wave` (units j0 + wave*4 .. +3); its lane holds the four gates of
     // unit wave*4 + lk for piece lr of a piece tile
     const bool has_tile = wave < MT;
@@ -599,9 +605,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
         zpre[q] = znext[q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         goff[q] = ((unsigned)((q * 16 + lr) * X + x) * 4u * (unsigned)H + (unsigned)je * 4u) * 4u;
     }
-    if (PIPE == PIPE_CONSUMER && T > 0 && !pipe_wait_chunk(pl, 0, a.err, REC_PROF_CHUNK_ACC(a, rank, ps))) return;
-    int c_wait = 1;   // consumer: the chunk it has to wait for next
-    if (has_tile && T > 0) {
+    if (has_tile) {
         const int bs0 = grp_count(a.batch_sizes[0], ps);
 #pragma unroll
         for (int q = 0; q < REC_PRE; ++q)
@@ -627,7 +631,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
     const __amdgpu_buffer_rsrc_t rs_h = __builtin_amdgcn_make_buffer_rsrc(a.hout, 0, WHOLE, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_hp = __builtin_amdgcn_make_buffer_rsrc(hprev, 0, WHOLE, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_hcopy = __builtin_amdgcn_make_buffer_rsrc(a.hcopy, 0, PIPE == PIPE_PRODUCER ? WHOLE : 0, 0x00020000);
-    for (int t = 0; t < T; ++t) {
+    for (int t = 0; t < t0; ++t) {
         // (the compiler reads it with a vector load, since it cannot prove the array constant; left alone it would
         // wait for that load, and for every store in flight before it, right here at the top of the step: the
         // value is kept in a vector register and made uniform only where the step waits for its stores anyway)
@@ -666,19 +670,6 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
                                                                 rs_g, qq * 16 + lr < bs_next ? goff[qq] : OUT_OF_RANGE, so_gnext, 0));
             }
             REC_PROF_MARK(1);
-            if (MODE == MODE_F32 && rows <= REC_VALU_ROWS) {
-                if constexpr (MODE == MODE_F32) {
-                    for (int pc = 0; pc < rows; ++pc) {
-                        const float* prow = reinterpret_cast<const float*>(sB) + pc * stride + k_lo + lk * VEC;
-#pragma unroll
-                        for (int tt = 0; tt < TPW; ++tt) {
-                            const float p = valu_row_sum<TPW * NBW>(wreg, tt * NBW, NBW, prow, nb, rot, NBW, STATIC);
-                            if (lk == 0)
-                                reinterpret_cast<float*>(&sRed[((ks * MT + rg * TPW + tt) * ntc + 0) * 64 + pc + 16 * (lr >> 2)])[lr & 3] = p;
-                        }
-                    }
-                }
-            } else
 #pragma unroll 1
             for (int q = 0; q < nt; ++q) {
                 // dead lanes of the last tile read its first row: equal addresses are broadcast by the LDS
@@ -770,6 +761,8 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
         REC_PROF_MARK(4);
         REC_PROF_STEP();
     }
+    }
+    if (t0 < T && !few_fwd<MODE, MT, PIPE>(a, ps, rank, t0, T, flags, pl, c_wait, ring, smem)) return;
     if (PIPE == PIPE_PRODUCER && rank == 0) {   // the last timestep is complete once every flag says so
         if (T > 0 && !rec_wait(flags, G, T + 1, a.err)) return;
         if (tid == 0) st_agent(pl.progress, T);
@@ -789,29 +782,6 @@ __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
 }
 
 // ======================================================================================================
-struct RecBwdArgs {
-    const int32_t* info;
-    const int32_t* batch_sizes;
-    const int32_t* t_off;
-    const float* gates;     // [M, 4H] activated gates (interleaved)
-    const float* c;         // [M, H]
-    const float* c0;        // [seq_cap, H] of this layer or NULL
-    const float* dh_above;  // [M, H] gradient arriving at h_t from the layer above / the heads
-    void* dz;               // [M, 4H] operand type (out): gradient at the gate pre-activations
-    const void* whhT;       // [H, 4H] operand type: row k = column k of the interleaved W_hh
-    float* dh_state;        // [n_cap, H] recurrent gradient carried to the previous timestep
-    float* dc_state;        // [n_cap, H]
-    float* db_part;         // [groups, 4H] (out): every group's sum of dz over its rows, interleaved columns
-    int H, seq_cap;
-    int G;                  // participating workgroups; each owns 16*MT hidden units
-    int ntc;
-    int* flags;
-    int* ticket;
-    int* err;
-    long long* prof;
-    long long* prof_all;
-};
-
 // What the gate-gradient step needs from the forward pass for one (piece, unit).
 struct BwdSaved {
     f32x4_t g4;   // activated gates i, f, g, o
@@ -853,16 +823,6 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& a, int rank, cons
     const int k_lo = ks * (K / KS);
     const int ni = (K / KS) / KBLK;
 
-    f32x4_t wreg[NW];
-    {
-        const E* wrow = static_cast<const E*>(a.whhT) + ((size_t)j0 + mt * 16 + lr) * K + k_lo + lk * VEC;
-#pragma unroll
-        for (int i = 0; i < NW; ++i)
-            wreg[i] = (i < ni) ? *reinterpret_cast<const f32x4_t*>(wrow + i * KBLK) : f32x4_t{0.f, 0.f, 0.f, 0.f};
-        // (a use of the registers: the loads are complete before the time loop, see the forward kernel)
-#pragma unroll
-        for (int i = 0; i < NW; ++i) asm volatile("" : "+v"(wreg[i]));
-    }
     // The arrays as buffers that never change during the loop (host code guarantees that each is shorter than
     // 2^31 bytes); where a timestep's rows begin is the scalar offset of an access, and this thread's first
     // (piece, unit) sits at the same place inside every timestep's rows.
@@ -873,29 +833,65 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& a, int rank, cons
     const __amdgpu_buffer_rsrc_t rs_above = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.dh_above), 0, WHOLE, 0x00020000);
     const unsigned poff = (unsigned)(((tid / UH) * X + x) * H + j0 + (tid % UH)) * 4u;   // bytes inside an [rows, H] fp32 array
     const unsigned row_h = 4u * (unsigned)H;
-    BwdSaved pre;   // saved activations of this thread's first (piece, unit) of the coming timestep
-    pre.g4 = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    pre.c = pre.c_prev = pre.dh_above = 0.f;
-    float dcreg = 0.f;   // cell-state gradient of that (piece, unit), carried from timestep to timestep
+    float dcreg = 0.f;   // cell-state gradient of this thread's first (piece, unit), carried from timestep to timestep
     // Bias gradient: a thread always works on the same unit (the stride of its items is a multiple of UH), so it
     // adds up that unit's four gate gradients over all its items in registers; summed over threads after the loop.
     static_assert(REC_THREADS % UH == 0, "a thread keeps its unit");
-    float db0 = 0.f, db1 = 0.f, db2 = 0.f, db3 = 0.f;
+    float db[4] = {0.f, 0.f, 0.f, 0.f};
     int c_wait = T > 0 ? (T - 1) / pl.ct : 0;   // consumer: the chunk of the timestep it runs next
     if (PIPE == PIPE_CONSUMER && T > 0 && !pipe_wait_chunk(pl, c_wait, a.err, REC_PROF_CHUNK_ACC(a, rank, ps))) return;
+    // Timesteps >= t_few have at most FewMax alive pieces and run in the form of lstm_few.h (flag value 1: the
+    // workgroup has emptied its words of the exchange ring).
+    const int n_seq = grp_count(a.info[0], ps);
+    const int t_few = n_seq > FewMax<MODE>::bwd ? grp_steps(a.batch_sizes, T, FewMax<MODE>::bwd * X + x) : 0;
+    unsigned char* ring = static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, K);
+    float dh_few = 0.f;
+    if (t_few < T) {
+        few_clear_ring<MODE>(ring, K, j0 * 4, UH * 4);
+        rec_publish(flags, rank, 1);
+        if (!rec_wait(flags, G, 1, a.err)) return;
+        if (!few_bwd<MODE, MT, PIPE>(a, ps, rank, t_few, T, pl, c_wait, ring, smem, dh_few, dcreg, db)) return;
+        if (t_few == 0 && PIPE == PIPE_PRODUCER) {   // the last rows are complete once every flag says so
+            rec_publish(flags, rank, T + 1);
+            if (rank == 0) {
+                if (!rec_wait(flags, G, T + 1, a.err)) return;
+                if (tid == 0) st_agent(pl.progress, T);
+            }
+        }
+    }
+    if (t_few > 0) {
+    f32x4_t wreg[NW];
+    {
+        const E* wrow = static_cast<const E*>(a.whhT) + ((size_t)j0 + mt * 16 + lr) * K + k_lo + lk * VEC;
+#pragma unroll
+        for (int i = 0; i < NW; ++i)
+            wreg[i] = (i < ni) ? *reinterpret_cast<const f32x4_t*>(wrow + i * KBLK) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        // (a use of the registers: the loads are complete before the time loop, see the forward kernel)
+#pragma unroll
+        for (int i = 0; i < NW; ++i) asm volatile("" : "+v"(wreg[i]));
+    }
+    BwdSaved pre;   // saved activations of this thread's first (piece, unit) of the coming timestep
+    pre.g4 = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    pre.c = pre.c_prev = pre.dh_above = 0.f;
     // batch sizes of timesteps t+1, t, t-1, t-2 (t-3 is fetched a step ahead, see the forward kernel); row offsets
     // follow by subtraction
-    int bs_up = 0, bs_t = T > 0 ? a.batch_sizes[T - 1] : 0, bs_m1 = T > 1 ? a.batch_sizes[T - 2] : 0,
-        bs_m2 = T > 2 ? a.batch_sizes[T - 3] : 0;
-    int base = T > 0 ? a.t_off[T - 1] : 0;
-    if (T > 0) {
+    const int t1 = t_few - 1;
+    int bs_up = t1 + 1 < T ? a.batch_sizes[t1 + 1] : 0, bs_t = a.batch_sizes[t1], bs_m1 = t1 > 0 ? a.batch_sizes[t1 - 1] : 0,
+        bs_m2 = t1 > 1 ? a.batch_sizes[t1 - 2] : 0;
+    int base = a.t_off[t1];
+    {
         const int bs_l = grp_count(bs_t, ps);
         if (tid < bs_l * UH)
-            pre = load_saved(a, T - 1, base, base - bs_m1, (tid / UH) * X + x, j0 + (tid % UH), H);
+            pre = load_saved(a, t1, base, base - bs_m1, (tid / UH) * X + x, j0 + (tid % UH), H);
+        if (t_few < T) {   // the gradients carried from timestep t_few
+            bar_lds();     // (the partial sums of the other form have been read)
+            if (tid < grp_count(bs_up, ps) * UH) sDh[tid] = dh_few;
+            bar_lds();
+        }
     }
     REC_PROF_DECL
     REC_PROF_START();
-    for (int t = T - 1; t >= 0; --t) {
+    for (int t = t1; t >= 0; --t) {
         // bs, bs_next: this group's alive pieces; its piece m sits in packed row base + m * X + x
         // (kept in a vector register and made uniform only at the end of the step, where everything the step loaded
         // has long arrived: see the forward kernel; read as a scalar right here, the step would open with a wait for
@@ -931,13 +927,13 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& a, int rank, cons
                         const float dzi = dc * gg * gi * (1.f - gi), dzf = dc * sv.c_prev * gf * (1.f - gf), dzg = dc * gi * (1.f - gg * gg),
                         dzo = dh * tc * go * (1.f - go);
             st_row4_buf<E, PIPE == PIPE_PRODUCER ? 17 : 0>(rs_dzall, (n * K + j * 4) * (int)sizeof(E), so_dz, dzi, dzf, dzg, dzo);
-            db0 += dzi; db1 += dzf; db2 += dzg; db3 += dzo;
+            db[0] += dzi; db[1] += dzf; db[2] += dzg; db[3] += dzo;
             if (first) dcreg = dc * gf;
             else a.dc_state[(size_t)n * H + j] = dc * gf;
         }
         if (t == 0 && PIPE != PIPE_PRODUCER) break;  // nothing is carried before the first timestep
         REC_PROF_MARK(8);
-        rec_publish(flags, rank, T - t);
+        rec_publish(flags, rank, T - t + 1);
         REC_PROF_MARK(9);
         if (t == 0 && rank != 0) break;
         if (t > 0) {
@@ -964,7 +960,7 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& a, int rank, cons
                 }
             }
         }
-        if (!rec_wait(flags, G, T - t, a.err, REC_WAVES - 1)) return;
+        if (!rec_wait(flags, G, T - t + 1, a.err, REC_WAVES - 1)) return;
         // every workgroup of the group has completed the dz rows of timesteps >= t
         if (PIPE == PIPE_PRODUCER && rank == 0 && tid == 0) st_agent(pl.progress, T - t);
         if (t == 0) break;
@@ -977,21 +973,11 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& a, int rank, cons
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             bar_lds();
             REC_PROF_MARK(11);
-            if (MODE == MODE_F32 && rows <= REC_VALU_ROWS) {
-                if constexpr (MODE == MODE_F32) {   // few pieces in fp32: the vector ALUs (see valu_row_sum)
-                    for (int pc = 0; pc < rows; ++pc) {
-                        const float* prow = reinterpret_cast<const float*>(sB) + pc * stride + k_lo + lk * VEC;
-                        const float p = valu_row_sum<NW>(wreg, 0, NW, prow, ni, 0, NW, false);
-                        if (lk == 0) reinterpret_cast<float*>(&sRed[((ks * MT + mt) * ntc + 0) * 64 + pc + 16 * (lr >> 2)])[lr & 3] = p;
-                    }
-                }
-            } else {
             f32x4_t acc[REC_NTC];
             mma_dispatch<MODE, NI, NW>(wreg, sB + lr * stride + k_lo + lk * VEC, stride, ni, rows, lr, acc);
 #pragma unroll
             for (int q = 0; q < REC_NTC; ++q)
                 if (q * 16 < rows) sRed[((ks * MT + mt) * ntc + q) * 64 + lane] = acc[q];
-            }
             bar_lds();
             // wave w adds the KS partial sums of (unit tile w / REC_NTC, piece tile w % REC_NTC):
             // its lane holds units lk*4..lk*4+3 of piece n
@@ -1023,10 +1009,11 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& a, int rank, cons
         REC_PROF_MARK(12);
         REC_PROF_STEP();
     }
+    }
     // bias gradient of this workgroup's units: the REC_THREADS / UH threads of a unit, added in thread order
     bar_lds();   // (the staging area is free)
     f32x4_t* s_db = reinterpret_cast<f32x4_t*>(smem);
-    s_db[tid] = f32x4_t{db0, db1, db2, db3};
+    s_db[tid] = f32x4_t{db[0], db[1], db[2], db[3]};
     bar_lds();
     if (tid < UH) {
         f32x4_t sum = s_db[tid];

@@ -232,3 +232,15 @@ def test_grouped_weight_gradients(ver, input_dim, layer_by_layer):
     eight: one), more than 32 columns or no remainder take column tiles of their own."""
     case(ver, wl.scaled(wl.WORKLOADS["manip"], budget=420, n_envs=9, hidden=256, input_dim=input_dim, p_done=0.02,
                         minibatches=1), seed=41, compute=1, x_bf16=True, layer_by_layer=layer_by_layer)
+
+
+@pytest.mark.parametrize("compute,hidden", [(0, 64), (0, 320), (0, 512), (1, 64), (1, 320), (1, 512), (1, 704), (1, 1024)])
+@pytest.mark.parametrize("n_layers,n_envs", [(1, 150), (2, 60)])
+def test_forms_of_the_time_loops(ver, compute, hidden, n_layers, n_envs):
+    """A group's timesteps change form with its alive pieces (more than 16, 16 .. 5, 4 .. 1 forward; 8, 4 and 1 or 2
+    backward; 4 and 1 in fp32): groups that start with about 20 pieces and end with one pass through all of
+    them, at widths with whole, partly filled and empty shares of the contraction."""
+    w = wl.scaled(wl.WORKLOADS["manip"], budget=6 * n_envs, n_envs=n_envs, n_layers=n_layers, hidden=hidden, input_dim=20,
+                  p_done=0.01, minibatches=1, speed_sigma=0.8)
+    _, meta = case(ver, w, seed=17 + hidden, compute=compute, x_bf16=bool(compute))
+    assert meta["n_seq"] > 16 * (8 if n_layers == 1 else 3) and meta["batch_sizes"][-1] <= 8
