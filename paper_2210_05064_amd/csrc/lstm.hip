@@ -363,8 +363,8 @@ inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws)
     // the hand-over words sit right behind, so that one fill clears everything a launch needs cleared
     ws->pipe_words = pipe_sync_words(M);
     ws->pipe = cv.take<int>(ws->pipe_words);
-    ws->plan[0] = cv.take<int>(plan_words(M));
-    ws->plan[1] = cv.take<int>(plan_words(M));
+    ws->plan[0] = cv.take<int>(PLAN_WORDS);
+    ws->plan[1] = cv.take<int>(PLAN_WORDS);
     ws->plan_scratch = cv.take<float>(plan_scratch_floats(M));
     for (int l = 0; l < c.n_layers; ++l) {
         const size_t D = l == 0 ? c.input_dim : H;
@@ -426,11 +426,10 @@ inline bool set_lds(K kernel, size_t bytes) {
 inline bool launch_proj_dma(const void* A, const void* B, float* C, const float* bias, int M, int N, int K, hipStream_t s) {
     if ((size_t)M * K * 2 >= 0x7fffffff || (size_t)N * K * 2 >= 0x7fffffff || (size_t)M * N * 4 >= 0x7fffffff) return false;
     if (!set_lds(lstm_proj_dma_kernel, (size_t)PIPE_STAGES * PIPE_STAGE_BYTES)) return false;
-    PipeWork pw{};
-    pw.A = A; pw.B = B; pw.C = C; pw.bias = bias; pw.K = K; pw.N = N; pw.M = M;
+    const ProjWork pw = {A, B, C, bias, K, N, M};
     const int tiles_n = (N + PIPE_BN - 1) / PIPE_BN, tiles_m = (M + PIPE_BM - 1) / PIPE_BM;
     hipLaunchKernelGGL(lstm_proj_dma_kernel, dim3(tiles_m * tiles_n), dim3(REC_THREADS), (size_t)PIPE_STAGES * PIPE_STAGE_BYTES, s,
-                       pw, M, tiles_n);
+                       pw, tiles_n);
     return true;
 }
 
@@ -454,12 +453,6 @@ inline int device_fits_time_loops() {
     return known[dev] > 0 ? VER_OK : VER_EUNSUPPORTED;
 }
 
-// LDS of a worker of a two-layer launch: one 128 x BK and one 256 x BK operand tile.
-template <int MODE>
-inline size_t pipe_worker_lds() {
-    if (MODE == MODE_BF16) return (size_t)PIPE_STAGES * PIPE_STAGE_BYTES;
-    return (size_t)(PIPE_BM + PIPE_BN) * GemmGeom<MODE>::LDS_STRIDE * sizeof(typename LdsElem<MODE>::type);
-}
 // Before the forward two-layer launch: one small kernel zeroes the flags, ticket counters, hand-over words and the
 // sticky time-out word at the start of the workspace, and writes the plans of both launches of the minibatch (the
 // backward call runs on the packing of the forward call whose activations it finds in the workspace).  Before the
@@ -475,7 +468,6 @@ inline void pipe_work(const LstmWs& ws, int dir, int M, const int32_t* t_off, Pi
     pw->plan = ws.plan[dir];
     pw->sync = ws.pipe;
     pw->err = ws.err;
-    pw->prof_all = ws.prof;
 }
 
 template <int MODE>
@@ -501,8 +493,10 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     const size_t red_per_tile = (size_t)ks * mt * 64 * 16 + (size_t)16 * 4 * mt * sizeof(E);   // partial sums + new h
     const int ntc = rec_tiles(tile, red_per_tile);
     size_t lds = ntc * (tile + red_per_tile);
-    if (few_lds_bytes(MODE, 16 * mt) > lds) lds = few_lds_bytes(MODE, 16 * mt);
-    if (pipelined && pipe_worker_lds<MODE>() > lds) lds = pipe_worker_lds<MODE>();
+    const int few_nb = wide ? FewBlocks<MODE, true>::fwd : FewBlocks<MODE, false>::fwd;
+    if (few_lds_bytes(16 * mt, few_nb) > lds) lds = few_lds_bytes(16 * mt, few_nb);
+    const size_t work_lds = work_lds_bytes(16 * mt, few_nb);
+    if (pipelined && work_lds > lds) lds = work_lds;
     const int nb = (H / ks) / RecGeom<MODE>::KBLK;
 
     // operand-type copies of every layer's weights (and their transposes) and the summed biases: one launch
@@ -583,7 +577,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         pa.work.A = ws.layer[0].hcopy; pa.work.B = ws.layer[1].wih; pa.work.C = ws.layer[1].gates;
         pa.work.bias = ws.layer[1].bias; pa.work.K = H; pa.work.N = 4 * H;
         pipe_work(ws, 0, M, t_off, &pa.work);
-        pa.tiles_n = (4 * H + PIPE_BN - 1) / PIPE_BN;
+        pa.work.G = pa.l0.G;
         ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
         VER_FWD_DISPATCH(lstm_pipe_fwd_kernel, pa);
         if (!ok) return VER_EHIP;
@@ -633,8 +627,10 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     const size_t red_per_tile = (size_t)ks * mt * 64 * 16 + (size_t)16 * 16 * mt * sizeof(float);   // partial sums + carried dh
     const int ntc = rec_tiles(tile, red_per_tile);
     size_t lds = ntc * (tile + red_per_tile);
-    if (few_lds_bytes(MODE, 16 * mt) > lds) lds = few_lds_bytes(MODE, 16 * mt);
-    if (pipelined && pipe_worker_lds<MODE>() > lds) lds = pipe_worker_lds<MODE>();
+    const int few_nb = wide ? FewBlocks<MODE, true>::bwd : FewBlocks<MODE, false>::bwd;
+    if (few_lds_bytes(16 * mt, few_nb) > lds) lds = few_lds_bytes(16 * mt, few_nb);
+    const size_t work_lds = work_lds_bytes(16 * mt, few_nb);
+    if (pipelined && work_lds > lds) lds = work_lds;
     const int ni = (4 * H / ks) / RecGeom<MODE>::KBLK;
 
     // ws.dh[l == nl-1 ? 0 : 1 ...]: gradient arriving at layer l's h; dz_of(l): its gate gradients
@@ -732,7 +728,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         pa.work.A = ws.dz[1]; pa.work.B = ws.layer[1].wihT; pa.work.C = ws.dh[1]; pa.work.bias = nullptr;
         pa.work.K = 4 * H; pa.work.N = H;
         pipe_work(ws, 1, M, t_off, &pa.work);
-        pa.tiles_n = (H + PIPE_BN - 1) / PIPE_BN;
+        pa.work.G = pa.l1.G;
         {
         ProfScope prof(VER_PROF_LSTM_REC_BWD, s);
         VER_BWD_DISPATCH(lstm_pipe_bwd_kernel, pa);

@@ -8,10 +8,12 @@
 //    of a slot holds FEW_EMPTY, which no published word equals (see few_word), so a reader polls the values it needs
 //    and has them when the poll succeeds: no flag, no wait for a store's acknowledgement, no barrier, no copy.
 //  * Each of the 8 waves owns an eighth of the contraction (all gate rows of the workgroup) and polls just that
-//    slice of the rows, straight into the operand registers of the product: no staging in LDS.  With P pieces the 16
-//    rows of an operand hold P pieces x 16/P operand blocks, so that a load instruction is full; the blocks are
-//    brought to rows 0 .. P-1 by rotating the lanes of a row (DPP), the other rows of the operand are whatever
-//    they are (a row of A only reaches the same row of the result).  fp32 reads its values as DPP broadcasts.
+//    slice of the rows.  Up to 4 pieces: straight into the operand registers of the product.  The 16 rows of an
+//    operand hold P pieces x 16/P operand blocks, so that a load instruction is full and four neighbouring lanes
+//    read 64 contiguous bytes (lanes of a quad that read different lines cost a cycle each); a block is brought to
+//    its piece's first row by rotating the lanes of a row (DPP), the other rows of the operand are whatever they are (a
+//    row of A only reaches the same row of the result).  fp32 reads its values as DPP broadcasts.  More pieces: in
+//    the order of memory into registers, and through a piece of LDS of the wave's own into operand order.
 //  * The partial sums of the waves meet in LDS (two buffers, one barrier per timestep); a thread then owns one
 //    (piece, unit) and keeps its cell state (backward: both carried gradients) in registers.
 //  * Everything that is not on the way from one exchange to the next (saved activations, copies for other XCDs,
@@ -22,38 +24,39 @@
 // once more after the clearing stores have completed before anyone polls the slot again.
 //
 // Bound by the latency of its phases: about 0.6 us for the exchange alone (a kernel that does nothing else), 0.43 us for
-// the MFMAs of one 16-row tile at H = 1024, then the partial sums through LDS and the cell update.  Microseconds per
-// timestep (one layer, bf16, H = 1024), flag protocol -> this form:
-//     alive pieces     1             2             4             8             16
-//     forward     2.36 -> 1.57  2.36 -> 1.60  2.44 -> 1.81  2.69 -> 2.13  3.31 -> 2.74
-//     backward    2.23 -> 1.85  3.11 -> 2.27  3.26 -> 3.03  3.79 -> 3.42  4.80 -> 5.25 (not used)
-// fp32, H = 512: forward 1 piece 2.20 -> 1.41, 4 pieces 3.75 -> 2.53; backward 2.78 -> 1.63, 4.30 -> 3.95.
+// the MFMAs of one 16-row tile at H = 1024 (1.7 us in fp32 at H = 512), then the partial sums through LDS and the cell
+// update.  Microseconds per timestep (one layer), flag protocol -> this form:
+//     alive pieces                     1             2             4             8             16
+//     bf16, H = 1024   forward    2.36 -> 1.43  2.36 -> 1.35  2.44 -> 1.40  2.69 -> 1.86  3.31 -> 2.04
+//                      backward   2.23 -> 1.65  3.11 -> 1.83  3.26 -> 2.22  3.79 -> 2.26  4.80 -> 2.99
+//     fp32, H = 512    forward    2.20 -> 1.24  2.73 -> 1.54  3.75 -> 2.37  3.86 -> 3.16  4.38 -> 3.27
+//                      backward   2.78 -> 1.37  3.65 -> 2.01  4.30 -> 3.29  4.69 -> 3.72  5.70 -> 4.45
+// What mattered after the exchange itself: four neighbouring lanes on contiguous memory (16 pieces forward 2.74 -> 2.04 us,
+// backward 5.25 -> 2.99), and reading the eight partial sums without a branch per share (0.2 us per timestep).
 #pragma once
 
 namespace ver {
 
 constexpr int FEW_RING = 4;
 constexpr unsigned FEW_EMPTY = 0xffffffffu;
-// Alive pieces up to which a group runs this form: beyond, the copy of the rows into LDS (every row once per
-// workgroup, in whole lines) beats the polls (figures above; backward rows are four times as long; an fp32 piece more
-// costs the vector ALUs as much as the first).
-template <int MODE> struct FewMax {
-    static constexpr int fwd = MODE == MODE_BF16 ? 16 : 4, bwd = MODE == MODE_BF16 ? 8 : 4;
-};
+// Alive pieces up to which a group runs this form: one MFMA tile.
+constexpr int FEW_MAX = 16;
 // Operand blocks per wave: the contraction (H forward, 4H backward) over 8 waves.
 template <int MODE, bool WIDE> struct FewBlocks {
     static constexpr int fwd = MODE == MODE_BF16 ? (WIDE ? 4 : 2) : 4;
     static constexpr int bwd = MODE == MODE_BF16 ? (WIDE ? 16 : 8) : 16;
 };
-constexpr int few_slot_rows(int mode) { return mode == MODE_BF16 ? 16 : 4; }
 inline __host__ __device__ size_t few_slot_bytes(int mode, int row_elems) {
-    return (size_t)few_slot_rows(mode) * (mode == MODE_BF16 ? 2 : 4) * row_elems;
+    return (size_t)FEW_MAX * (mode == MODE_BF16 ? 2 : 4) * row_elems;
 }
 inline __host__ __device__ size_t few_ring_bytes(int mode, int row_elems) { return FEW_RING * few_slot_bytes(mode, row_elems); }
-// LDS: two buffers of [8 waves][pieces][columns + 4] partial sums.
-constexpr int few_row(int cols) { return cols + 4; }   // (16 bytes more: the four row groups of a fragment hit different banks)
-inline __host__ __device__ size_t few_lds_bytes(int mode, int cols) {
-    return (size_t)2 * REC_WAVES * (mode == MODE_BF16 ? 16 : 4) * few_row(cols) * sizeof(float);
+// LDS: partial sums, [8 waves][16 pieces][columns + 4] or two buffers of [8 waves][4 pieces][columns + 4], then (more than
+// 4 pieces) 16 rows of NB operand blocks per wave.
+constexpr int few_row(int cols) { return cols + 4; }   // (16 bytes more: 16 pieces of a fragment hit different banks)
+constexpr int few_part_floats(int cols) { return REC_WAVES * 16 * few_row(cols); }
+constexpr int few_stage_bytes(int nb) { return 16 * nb * 64; }   // per wave
+inline __host__ __device__ size_t few_lds_bytes(int cols, int nb) {
+    return (size_t)few_part_floats(cols) * sizeof(float) + (size_t)REC_WAVES * few_stage_bytes(nb);
 }
 
 template <int I> struct FewIdx { static constexpr int value = I; };
@@ -103,7 +106,7 @@ __device__ __forceinline__ unsigned few_word(unsigned v) { return v == FEW_EMPTY
 // workgroup).
 template <int L>
 __device__ __forceinline__ bool few_read(const unsigned char* base, const unsigned (&off)[L], bool take, bool check, u32x4_t (&raw)[L], int* err) {
-    static_assert(L == 1 || L == 2 || L == 4, "loads per poll");
+    static_assert(L == 1 || L == 2 || L == 4 || L == 8, "loads per poll");
     long long spins = 0;
     for (;;) {
         unsigned m = 0;
@@ -113,11 +116,19 @@ __device__ __forceinline__ bool few_read(const unsigned char* base, const unsign
             else if constexpr (L == 2)
                 asm volatile("global_load_dwordx4 %0, %2, %4 sc0 sc1\n\tglobal_load_dwordx4 %1, %3, %4 sc0 sc1\n\ts_waitcnt vmcnt(0)"
                              : "+&v"(raw[0]), "+&v"(raw[1]) : "v"(off[0]), "v"(off[1]), "s"(base) : "memory");
-            else
+            else if constexpr (L == 4)
                 asm volatile("global_load_dwordx4 %0, %4, %8 sc0 sc1\n\tglobal_load_dwordx4 %1, %5, %8 sc0 sc1\n\t"
                              "global_load_dwordx4 %2, %6, %8 sc0 sc1\n\tglobal_load_dwordx4 %3, %7, %8 sc0 sc1\n\ts_waitcnt vmcnt(0)"
                              : "+&v"(raw[0]), "+&v"(raw[1]), "+&v"(raw[2]), "+&v"(raw[3])
                              : "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "memory");
+            else
+                asm volatile("global_load_dwordx4 %0, %8, %16 sc0 sc1\n\tglobal_load_dwordx4 %1, %9, %16 sc0 sc1\n\t"
+                             "global_load_dwordx4 %2, %10, %16 sc0 sc1\n\tglobal_load_dwordx4 %3, %11, %16 sc0 sc1\n\t"
+                             "global_load_dwordx4 %4, %12, %16 sc0 sc1\n\tglobal_load_dwordx4 %5, %13, %16 sc0 sc1\n\t"
+                             "global_load_dwordx4 %6, %14, %16 sc0 sc1\n\tglobal_load_dwordx4 %7, %15, %16 sc0 sc1\n\ts_waitcnt vmcnt(0)"
+                             : "+&v"(raw[0]), "+&v"(raw[1]), "+&v"(raw[2]), "+&v"(raw[3]), "+&v"(raw[4]), "+&v"(raw[5]), "+&v"(raw[6]), "+&v"(raw[7])
+                             : "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "v"(off[4]), "v"(off[5]), "v"(off[6]), "v"(off[7]), "s"(base)
+                             : "memory");
 #pragma unroll
             for (int j = 0; j < L; ++j) m = max(max(m, max(raw[j][0], raw[j][1])), max(raw[j][2], raw[j][3]));
         }
@@ -131,33 +142,34 @@ __device__ __forceinline__ bool few_read(const unsigned char* base, const unsign
 }
 // Offsets of the L loads of a lane: block blk + j * BPL of the slice, or block blk again where the slice has no such
 // block (its weights are zero).
-template <int L, int BPL, int STRIDE>
+template <int L, int BPL>
 __device__ __forceinline__ void few_offsets(unsigned (&off)[L], unsigned first, int blk, int n_blk) {
 #pragma unroll
-    for (int j = 0; j < L; ++j) off[j] = first + (blk + j * BPL < n_blk ? j * STRIDE : 0);
+    for (int j = 0; j < L; ++j) off[j] = first + (blk + j * BPL < n_blk ? j * BPL * 16 : 0);
 }
 
-// Product of the operand blocks [B0, B0 + L * BPL) of this wave's slice with all its tiles, added into acc.
-// bf16: pieces are the rows of A, a tile's gate rows (units) the columns: lane l holds column l % 16 and rows (pieces)
-// (l / 16) * 4 + e.  fp32: acc[tile][piece] on the vector ALUs, a lane's share of the contraction.
-template <int MODE, int MT, int NB, int P, int B0, int L>
+// ---- up to 4 pieces: operands in the registers they were loaded into --------------------------------------------
+// Register j of lane (lr, lk) holds, of piece lr / BPL, the 16 bytes lk of operand block j * BPL + lr % BPL, BPL = 16 / P.
+// Adds the product with all tiles of the wave into acc.  bf16: pieces are the rows 0, BPL, 2 BPL, ... of A, so that lane
+// group p * BPL / 4 holds piece p of the result, element 0.  fp32: acc[tile][piece] on the vector ALUs, a lane's share.
+template <int MODE, int MT, int NB, int P, int L>
 __device__ __forceinline__ void few_product(const f32x4_t (&w)[MT * NB], const u32x4_t (&raw)[L], int bs, f32x4_t (&acc)[MT]) {
-    constexpr int BPL = 16 / P, N = NB - B0 < L * BPL ? NB - B0 : L * BPL;
+    constexpr int BPL = 16 / P;
     if constexpr (MODE == MODE_BF16) {
-        few_for<N>([&](auto ib) {
+        few_for<NB>([&](auto ib) {
             constexpr int b = decltype(ib)::value;
-            const f32x4_t op = few_rot<P * (b % BPL)>(raw[b / BPL]);
+            const f32x4_t op = few_rot<b % BPL>(raw[b / BPL]);
 #pragma unroll
-            for (int j = 0; j < MT; ++j) acc[j] = mfma_block<MODE>(op, w[j * NB + B0 + b], acc[j]);
+            for (int j = 0; j < MT; ++j) acc[j] = mfma_block<MODE>(op, w[j * NB + b], acc[j]);
         });
     } else {
         few_for<P>([&](auto ip) {
             constexpr int p = decltype(ip)::value;
             if (p < bs)
-                few_for<N>([&](auto ib) {
+                few_for<NB>([&](auto ib) {
                     constexpr int b = decltype(ib)::value;
 #pragma unroll
-                    for (int j = 0; j < MT; ++j) acc[j][p] = few_fma4<p + P * (b % BPL)>(acc[j][p], raw[b / BPL], w[j * NB + B0 + b]);
+                    for (int j = 0; j < MT; ++j) acc[j][p] = few_fma4<p * BPL + b % BPL>(acc[j][p], raw[b / BPL], w[j * NB + b]);
                 });
         });
     }
@@ -165,35 +177,13 @@ __device__ __forceinline__ void few_product(const f32x4_t (&w)[MT * NB], const u
 // Leaves the wave's partial sums in LDS: s[piece * few_row(16 MT) + column].
 template <int MODE, int MT, int P>
 __device__ __forceinline__ void few_write(const f32x4_t (&acc)[MT], int bs, float* s) {
-    constexpr int ROW = few_row(16 * MT);
+    constexpr int ROW = few_row(16 * MT), BPL = 16 / P;
     const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
-    if constexpr (MODE == MODE_BF16 && P > 4) {
+    if constexpr (MODE == MODE_BF16) {
+        const int p = lk * 4 / BPL;   // the piece of this lane group, if it has one
+        if (lk * 4 % BPL == 0 && p < bs)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (lk * 4 + e < bs)
-#pragma unroll
-                for (int j = 0; j < MT; ++j) s[(lk * 4 + e) * ROW + j * 16 + lr] = acc[j][e];
-    } else if constexpr (MODE == MODE_BF16) {   // pieces 0 .. P-1 <= 3 sit in lanes 0..15: gather up to four tiles in one store
-#pragma unroll
-        for (int e = 0; e < P; ++e)
-            if (e < bs) {
-                if constexpr (MT >= 4) {
-#pragma unroll
-                    for (int g = 0; g < MT; g += 4) {
-                        float a = acc[g][e], b = acc[g + 1][e], c = acc[g + 2][e], d = acc[g + 3][e];
-                        few_swap16(a, b);
-                        few_swap16(c, d);
-                        few_swap32(a, c);
-                        s[e * ROW + g * 16 + lane] = a;
-                    }
-                } else if constexpr (MT == 2) {
-                    float a = acc[0][e], b = acc[1][e];
-                    few_swap16(a, b);
-                    if (lane < 32) s[e * ROW + lane] = a;
-                } else {
-                    if (lane < 16) s[e * ROW + lane] = acc[0][e];
-                }
-            }
+            for (int j = 0; j < MT; ++j) s[p * ROW + j * 16 + lr] = acc[j][0];
     } else {   // fp32: the four lane groups hold shares of every sum
 #pragma unroll
         for (int p = 0; p < P; ++p)
@@ -215,6 +205,89 @@ __device__ __forceinline__ void few_write(const f32x4_t (&acc)[MT], int bs, floa
                 }
             }
     }
+}
+
+// ---- up to 16 rows through LDS ----------------------------------------------------------------------------------
+// A wave's staging area: 16 rows of C = 4 NB chunks of 16 bytes; position q of row r holds chunk q ^ key(r), which makes
+// the operand reads (the same chunk of 16 rows) hit all banks.  Lane i of load j fills position i % C of row
+// j * (64 / C) + i / C, i.e. 1 KB in lane order.
+template <int NB> struct FewStage {
+    static constexpr int C = 4 * NB, RPL = 64 / C, LOADS = 16 / RPL;   // chunks per row, rows per load, loads for 16 rows
+    static_assert((C & (C - 1)) == 0 && C <= 64 && C >= 8, "blocks per wave");
+    static __device__ __forceinline__ int key(int r) { return C >= 16 ? (r & 15) : ((r >> 1) & 7); }
+    static __device__ __forceinline__ int row(int j) { return j * RPL + (int)(threadIdx.x & 63) / C; }
+    // byte offset, inside the slice, of what this lane loads of row r (chunk 0 where the slice has no such chunk: its
+    // weights are zero)
+    static __device__ __forceinline__ unsigned src(int r, int n_blk) {
+        const int c = ((int)(threadIdx.x & 63) % C) ^ key(r);
+        return (unsigned)(c < 4 * n_blk ? c : 0) * 16u;
+    }
+};
+// Product of the staged rows with all tiles, added into acc: rows are columns of the result, lane l holds row l % 16 and
+// columns (l / 16) * 4 + e of a tile.
+template <int MODE, int MT, int NB>
+__device__ __forceinline__ void few_stage_product(const f32x4_t (&w)[MT * NB], const unsigned char* stage, int n_blk, f32x4_t (&acc)[MT]) {
+    constexpr int GRP = NB < 8 ? NB : 8;   // operands in flight
+    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+    const unsigned char* row = stage + lr * (FewStage<NB>::C * 16);
+    const int key = FewStage<NB>::key(lr);
+#pragma unroll
+    for (int b0 = 0; b0 < NB; b0 += GRP) {
+        f32x4_t op[GRP];
+#pragma unroll
+        for (int b = 0; b < GRP; ++b) op[b] = *reinterpret_cast<const f32x4_t*>(row + ((min(lk * n_blk + b0 + b, 4 * n_blk - 1) ^ key) << 4));
+#pragma unroll
+        for (int b = 0; b < GRP; ++b)
+#pragma unroll
+            for (int j = 0; j < MT; ++j) acc[j] = mfma_block<MODE>(w[j * NB + b0 + b], op[b], acc[j]);
+    }
+}
+template <int MT>
+__device__ __forceinline__ void few_stage_write(const f32x4_t (&acc)[MT], int rows, float* s) {
+    constexpr int ROW = few_row(16 * MT);
+    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+    if (lr < rows)
+#pragma unroll
+        for (int j = 0; j < MT; ++j) *reinterpret_cast<f32x4_t*>(s + lr * ROW + j * 16 + lk * 4) = acc[j];
+}
+// Polls rows 0 .. bs-1 (row_bytes apart from base) and leaves this wave's slice of them in its staging area.
+template <int NB>
+__device__ __forceinline__ bool few_stage_read(const unsigned char* base, unsigned row_bytes, unsigned slice_off, int n_blk, int bs, bool check,
+                                               unsigned char* stage, int* err) {
+    typedef FewStage<NB> S;
+    constexpr int L = S::LOADS < 8 ? S::LOADS : 8;
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int j0 = 0; j0 < S::LOADS; j0 += L) {
+        if (j0 * S::RPL >= bs) break;
+        u32x4_t raw[L];
+        unsigned off[L];
+#pragma unroll
+        for (int j = 0; j < L; ++j) {   // (a row beyond the last: the last one again)
+            raw[j] = u32x4_t{0u, 0u, 0u, 0u};
+            const int r = S::row(j0 + j);
+            off[j] = (unsigned)min(r, bs - 1) * row_bytes + slice_off + S::src(r, n_blk);
+        }
+        if (L == 8 && bs - j0 * S::RPL <= 4 * S::RPL) {   // half of the loads cover the rows that are there
+            u32x4_t half[4] = {raw[0], raw[1], raw[2], raw[3]};
+            const unsigned off4[4] = {off[0], off[1], off[2], off[3]};
+            if (!few_read<4>(base, off4, true, check, half, err)) return false;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) *reinterpret_cast<u32x4_t*>(stage + (j0 + j) * 1024 + lane * 16) = half[j];
+        } else {
+            if (!few_read<L>(base, off, true, check, raw, err)) return false;
+#pragma unroll
+            for (int j = 0; j < L; ++j) *reinterpret_cast<u32x4_t*>(stage + (j0 + j) * 1024 + lane * 16) = raw[j];
+        }
+    }
+    return true;
+}
+
+// Zeroes the partial sums: a wave without a share of the contraction never writes its own, and the sum over all eight
+// is read without a branch (guarded reads come one after the other).
+template <int COLS>
+__device__ __forceinline__ void few_clear_part(float* part) {
+    for (int i = threadIdx.x; i < few_part_floats(COLS); i += REC_THREADS) part[i] = 0.f;
 }
 
 // Batch sizes of 128 consecutive timesteps, two per lane: a scalar read costs no memory access.  DIR = 1: the
@@ -251,9 +324,9 @@ struct FewWindow {
 // Empties this workgroup's words of every slot (cols elements from column j0).
 template <int MODE>
 __device__ __forceinline__ void few_clear_ring(unsigned char* ring, int row_elems, int j0, int cols) {
-    constexpr int es = (int)sizeof(typename RecGeom<MODE>::E), MAX = few_slot_rows(MODE);
+    constexpr int es = (int)sizeof(typename RecGeom<MODE>::E);
     const int words = cols * es / 4;
-    for (int i = threadIdx.x; i < FEW_RING * MAX * words; i += REC_THREADS)
+    for (int i = threadIdx.x; i < FEW_RING * FEW_MAX * words; i += REC_THREADS)
         reinterpret_cast<unsigned*>(ring)[(size_t)(i / words) * (row_elems * es / 4) + j0 * es / 4 + i % words] = FEW_EMPTY;
 }
 
@@ -267,11 +340,12 @@ struct FewFwd {
     int base, base_prev;         // first row of timesteps t, t - 1
     int t0;                      // first timestep of this form
     int c_wait;                  // consumer: the chunk it has to wait for next
+    bool ready;                  // that chunk has been seen finished
     int n_slices, slice, n_blk;  // slices with work, this wave's slice, its operand blocks
     float c;                     // this thread's cell state
     f32x4_t z;                   // its input projection of timestep t
     f32x4_t s_g; float s_c, s_h; unsigned s_w;   // results of the timestep before, not yet stored
-    int* fail;                   // LDS
+    int* fail;                   // LDS: a wait was abandoned; the counter of a chunk
     float* part;                 // LDS
 };
 
@@ -311,22 +385,28 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
                                               unsigned char* ring, const PipeLink& pl, int& t, int T, int down_to) {
     typedef typename RecGeom<MODE>::E E;
     constexpr int es = (int)sizeof(E), KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC;
-    constexpr int UH = 4 * MT, COLS = 16 * MT, ROW = few_row(COLS), MAX = few_slot_rows(MODE);
-    constexpr int BPL = 16 / P, L = (NB + BPL - 1) / BPL, STRIDE = BPL * KBLK * es;
+    constexpr int UH = 4 * MT, COLS = 16 * MT, ROW = few_row(COLS), PP = P > 4 ? 16 : 4;
+    constexpr bool STAGED = P > 4;
+    constexpr int BPL = 16 / P, L = STAGED ? 1 : (NB + BPL - 1) / BPL;
     const int X = ps.X, x = ps.x, H = a.H;
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = tid / UH, u = tid % UH, j0 = rank * UH;
-    const int piece = lr % P, blk = lr / P;
-    const unsigned k_off = (unsigned)((s.slice * NB + blk) * KBLK + lk * VEC) * es;   // this lane's first 16 bytes inside a row
+    const int piece = lr / BPL, blk = lr % BPL;
+    const unsigned slice_off = (unsigned)(s.slice * NB) * 64u;                          // bytes: an operand block is 64
+    const unsigned k_off = slice_off + (unsigned)(lk * s.n_blk + blk) * 16u;   // this lane's first 16 bytes inside a row
     const unsigned slot = (unsigned)few_slot_bytes(MODE, H);
     const unsigned w_off = (unsigned)(m * H + j0 + u) * es;   // where this thread's value goes inside a slot
     const bool polls = s.slice < s.n_slices;
     unsigned off[L];
-    few_offsets<L, BPL, STRIDE>(off, (unsigned)(piece * H) * es + k_off, blk, s.n_blk);
+    few_offsets<L, BPL>(off, (unsigned)(piece * H) * es + k_off, blk, s.n_blk);
     u32x4_t raw[L];
 #pragma unroll
     for (int j = 0; j < L; ++j) raw[j] = u32x4_t{0u, 0u, 0u, 0u};
+    unsigned char* stage = reinterpret_cast<unsigned char*>(s.part + few_part_floats(COLS)) + wave * few_stage_bytes(NB);
+    bar_lds();   // (the partial sums of the phase before have been read)
+    few_clear_part<COLS>(s.part);
+    bar_lds();
     constexpr int WHOLE = (int)0x80000000u;
     const __amdgpu_buffer_rsrc_t rs_g = __builtin_amdgcn_make_buffer_rsrc(a.gates, 0, WHOLE, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_ring = __builtin_amdgcn_make_buffer_rsrc(ring, 0, (int)(FEW_RING * slot), 0x00020000);
@@ -335,8 +415,9 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
         const int bs = grp_count(s.bs_a, ps), bs_next = t + 1 < T ? grp_count(s.bs_b, ps) : 0;
         const int base_next = s.base + s.bs_a;
         if (PIPE == PIPE_CONSUMER && t + 1 < T && t + 1 == s.c_wait * pl.ct) {
-            if (!pipe_wait_chunk(pl, s.c_wait, a.err)) return false;
+            if (!s.ready && !pipe_wait_chunk(pl, s.c_wait, a.err)) return false;
             ++s.c_wait;
+            s.ready = false;
         }
         bool ok = true;
         if (t == s.t0) {
@@ -344,13 +425,19 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
             if (!rec_wait(flags, a.G, t + 1, a.err)) return false;
             if (PIPE == PIPE_PRODUCER && rank == 0 && tid == 0 && t > 0) st_agent(pl.progress, t);
             if (polls) {
-                unsigned first[L];
-                few_offsets<L, BPL, STRIDE>(first, (unsigned)(piece * X * H) * es + k_off, blk, s.n_blk);
-                few_read<L>(reinterpret_cast<const unsigned char*>(static_cast<const E*>(a.hprev) + (size_t)(s.base + x) * H), first,
-                            piece < bs && blk < s.n_blk, false, raw, a.err);
+                const unsigned char* rows = reinterpret_cast<const unsigned char*>(static_cast<const E*>(a.hprev) + (size_t)(s.base + x) * H);
+                if constexpr (STAGED) {
+                    few_stage_read<NB>(rows, (unsigned)(X * H) * es, slice_off, s.n_blk, bs, false, stage, a.err);
+                } else {
+                    unsigned first[L];
+                    few_offsets<L, BPL>(first, (unsigned)(piece * X * H) * es + k_off, blk, s.n_blk);
+                    few_read<L>(rows, first, piece < bs && blk < s.n_blk, false, raw, a.err);
+                }
             }
         } else if (polls) {
-            ok = few_read<L>(ring + (unsigned)((t - 1) & (FEW_RING - 1)) * slot, off, piece < bs && blk < s.n_blk, true, raw, a.err);
+            const unsigned char* rows = ring + (unsigned)((t - 1) & (FEW_RING - 1)) * slot;
+            if constexpr (STAGED) ok = few_stage_read<NB>(rows, (unsigned)H * es, slice_off, s.n_blk, bs, true, stage, a.err);
+            else ok = few_read<L>(rows, off, piece < bs && blk < s.n_blk, true, raw, a.err);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (also: this wave's stores of two timesteps ago have completed)
         if (!ok) *s.fail = 1;
@@ -360,17 +447,28 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
         if (m < bs_next)
             z_next = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs_g, (unsigned)((m * X + x) * H + j0 + u) * 16u,
                                                                                         (unsigned)base_next * (unsigned)H * 16u, 0));
+        // a look at the chunk that the next timestep asks for: usually finished, which saves that wait its round trip
+        const bool look = PIPE == PIPE_CONSUMER && t + 2 < T && t + 2 == s.c_wait * pl.ct;
+        int have = 0;
+        if (look && tid == REC_THREADS - 1) have = ld_agent(&pl.done[s.c_wait]);
         if (t > s.t0) few_fwd_store<MODE, MT, NB, PIPE>(s, a, ps, j0, grp_count(s.base - s.base_prev, ps), s.base, bs);
-        float* part = s.part + (t & 1) * (REC_WAVES * MAX * ROW);
+        float* part = s.part + (STAGED ? 0 : (t & 1) * (REC_WAVES * PP * ROW));
         if (polls) {
             f32x4_t acc[MT];
 #pragma unroll
             for (int j = 0; j < MT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            few_product<MODE, MT, NB, P, 0, L>(s.w, raw, bs, acc);
-            few_write<MODE, MT, P>(acc, bs, part + s.slice * (MAX * ROW));
+            if constexpr (STAGED) {
+                few_stage_product<MODE, MT, NB>(s.w, stage, s.n_blk, acc);
+                few_stage_write<MT>(acc, bs, part + s.slice * (PP * ROW));
+            } else {
+                few_product<MODE, MT, NB, P, L>(s.w, raw, bs, acc);
+                few_write<MODE, MT, P>(acc, bs, part + s.slice * (PP * ROW));
+            }
         }
+        if (look && tid == REC_THREADS - 1) s.fail[1] = have;
         bar_lds();
         if (*s.fail) return false;
+        if (look) s.ready = s.fail[1] >= pl.need;
         // Every workgroup has published the rows of timestep t-1, which it did after its stores for timestep t-3 had
         // completed (they are issued in timestep t-2 and waited for in timestep t-1).
         if (PIPE == PIPE_PRODUCER && rank == 0 && tid == REC_THREADS - 1 && t - 2 > s.t0) st_agent(pl.progress, t - 2);
@@ -378,11 +476,10 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
             f32x4_t q = z;
             const float* p = part + m * ROW + u * 4;
 #pragma unroll
-            for (int k = 0; k < REC_WAVES; ++k)
-                if (k < s.n_slices) {
-                    const f32x4_t o = *reinterpret_cast<const f32x4_t*>(p + k * (MAX * ROW));
-                    q[0] += o[0]; q[1] += o[1]; q[2] += o[2]; q[3] += o[3];
-                }
+            for (int k = 0; k < REC_WAVES; ++k) {
+                const f32x4_t o = *reinterpret_cast<const f32x4_t*>(p + k * (PP * ROW));
+                q[0] += o[0]; q[1] += o[1]; q[2] += o[2]; q[3] += o[3];
+            }
             const float gi = sigmoidf_(q[0]), gf = sigmoidf_(q[1]), gg = tanhf_(q[2]), go = sigmoidf_(q[3]);
             s.c = gf * s.c + gi * gg;
             const float h = go * tanhf_(s.c);
@@ -400,6 +497,7 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
                 __builtin_amdgcn_raw_buffer_store_b32(FEW_EMPTY, rs_ring, w_off, (unsigned)((t + 2) & (FEW_RING - 1)) * slot, 0);
             }
         }
+        if (STAGED) bar_lds();   // (one buffer of partial sums: it has been read)
         s.base_prev = s.base;
         s.base = base_next;
         s.bs_a = s.bs_b;
@@ -420,7 +518,7 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
     return true;
 }
 
-// Timesteps [t0, T): at most FewMax pieces of the group are alive.  The rows of h_{t0-1} are in hprev, announced by
+// Timesteps [t0, T): at most FEW_MAX pieces of the group are alive.  The rows of h_{t0-1} are in hprev, announced by
 // flag value t0 + 1.  False: a wait was abandoned.
 template <int MODE, int MT, int PIPE>
 __device__ __forceinline__ bool few_fwd(const RecFwdArgs& a, const PieceSet& ps, int rank, int t0, int T, int* flags, const PipeLink& pl,
@@ -428,15 +526,15 @@ __device__ __forceinline__ bool few_fwd(const RecFwdArgs& a, const PieceSet& ps,
     typedef typename RecGeom<MODE>::E E;
     constexpr int KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC, UH = 4 * MT;
     constexpr int NB = FewBlocks<MODE, MT == 8>::fwd;
-    __shared__ int s_fail;
+    __shared__ int s_fail[2];
     const int H = a.H, X = ps.X, x = ps.x;
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
     const int m = tid / UH, u = tid % UH, j0 = rank * UH;
     FewFwd<MODE, MT, NB> s;
-    s.fail = &s_fail;
+    s.fail = s_fail;
     s.part = reinterpret_cast<float*>(smem);
-    if (tid == 0) s_fail = 0;
-    bar_lds();
+    if (tid == 0) s_fail[0] = 0;
+    bar_lds();   // (LDS of the other form has been read)
     const int blocks = H / KBLK;
     s.n_slices = (blocks + NB - 1) / NB;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -445,16 +543,17 @@ __device__ __forceinline__ bool few_fwd(const RecFwdArgs& a, const PieceSet& ps,
     s.n_blk = min(NB, blocks - s.slice * NB);
 #pragma unroll
     for (int j = 0; j < MT; ++j) {
-        const E* wrow = static_cast<const E*>(a.whh) + ((size_t)j0 * 4 + j * 16 + lr) * H + s.slice * NB * KBLK + lk * VEC;
+        const E* wrow = static_cast<const E*>(a.whh) + ((size_t)j0 * 4 + j * 16 + lr) * H + (s.slice * NB * 4 + lk * s.n_blk) * VEC;
 #pragma unroll
         for (int b = 0; b < NB; ++b)
-            s.w[j * NB + b] = b < s.n_blk ? *reinterpret_cast<const f32x4_t*>(wrow + b * KBLK) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+            s.w[j * NB + b] = b < s.n_blk ? *reinterpret_cast<const f32x4_t*>(wrow + b * VEC) : f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
     // (a use of the registers: the loads are complete before the time loop, see rec_fwd_body)
 #pragma unroll
     for (int i = 0; i < MT * NB; ++i) asm volatile("" : "+v"(s.w[i]));
     s.t0 = t0;
     s.c_wait = c_wait;
+    s.ready = false;
     s.win.init(a.batch_sizes, T, t0);
     s.bs_a = s.win.at(t0);
     s.bs_b = s.win.at(t0 + 1);
@@ -471,8 +570,7 @@ __device__ __forceinline__ bool few_fwd(const RecFwdArgs& a, const PieceSet& ps,
         else if (a.c0 && n < a.seq_cap) s.c = a.c0[(size_t)n * H + j0 + u];
     }
     int t = t0;
-    if constexpr (MODE == MODE_BF16)
-        if (!few_fwd_phase<MODE, MT, NB, 16, PIPE>(s, a, ps, rank, flags, ring, pl, t, T, 4)) return false;
+    if (!few_fwd_phase<MODE, MT, NB, 16, PIPE>(s, a, ps, rank, flags, ring, pl, t, T, 4)) return false;
     if (!few_fwd_phase<MODE, MT, NB, 4, PIPE>(s, a, ps, rank, flags, ring, pl, t, T, 0)) return false;
     few_fwd_store<MODE, MT, NB, PIPE>(s, a, ps, j0, grp_count(s.base - s.base_prev, ps), s.base, 0);
     if (PIPE == PIPE_PRODUCER) rec_publish(flags, rank, T + 1);
@@ -492,6 +590,7 @@ struct FewBwd {
     int bs_up, bs_t, bs_m1, bs_m2;   // alive pieces of all groups at t + 1, t, t - 1, t - 2
     int base;                        // first row of timestep t
     int c_wait;                      // consumer: the lowest chunk it has waited for
+    bool ready;                      // the chunk below has been seen finished
     int n_slices, slice, n_blk;
     FewSaved sv, sv2;                // what the forward pass saved for timesteps t and t - 1
     float dh, dc, c;                 // carried gradients, cell state of timestep t
@@ -522,26 +621,28 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
                                               const PipeLink& pl, int& t, int T, int t_stop, int up_to) {
     typedef typename RecGeom<MODE>::E E;
     constexpr int es = (int)sizeof(E), KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC;
-    constexpr int UH = 16 * MT, ROW = few_row(UH), MAX = few_slot_rows(MODE);
-    constexpr int BPL = 16 / P, L = (NB + BPL - 1) / BPL, STRIDE = BPL * KBLK * es;
-    constexpr int LH = L > 4 ? 4 : L;   // operand registers for this many loads at a time
+    constexpr int UH = 16 * MT, ROW = few_row(UH), PP = P > 4 ? 16 : 4;
+    constexpr bool STAGED = P > 4;
+    constexpr int BPL = 16 / P, L = STAGED ? 1 : (NB + BPL - 1) / BPL;
     const int X = ps.X, x = ps.x, H = a.H, K = 4 * H;
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
     const int m = tid / UH, u = tid % UH, j0 = rank * UH, n = m * X + x, j = j0 + u;
-    const int piece = lr % P, blk = lr / P;
-    const unsigned k_off = (unsigned)((s.slice * NB + blk) * KBLK + lk * VEC) * es;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int piece = lr / BPL, blk = lr % BPL;
+    const unsigned slice_off = (unsigned)(s.slice * NB) * 64u;
+    const unsigned k_off = slice_off + (unsigned)(lk * s.n_blk + blk) * 16u;
     const unsigned slot = (unsigned)few_slot_bytes(MODE, K);
     const unsigned w_off = (unsigned)(m * K + j * 4) * es;
     const bool polls = s.slice < s.n_slices;
-    unsigned off[L / LH][LH];
-    few_for<L / LH>([&](auto ig) {
-        constexpr int g = decltype(ig)::value;
-        const int b = blk + g * LH * BPL < s.n_blk ? blk + g * LH * BPL : blk;
-        few_offsets<LH, BPL, STRIDE>(off[g], (unsigned)(piece * K) * es + k_off + (unsigned)(b - blk) * (KBLK * es), b, s.n_blk);
-    });
-    u32x4_t raw[LH];
+    unsigned off[L];
+    few_offsets<L, BPL>(off, (unsigned)(piece * K) * es + k_off, blk, s.n_blk);
+    u32x4_t raw[L];
 #pragma unroll
-    for (int i = 0; i < LH; ++i) raw[i] = u32x4_t{0u, 0u, 0u, 0u};
+    for (int i = 0; i < L; ++i) raw[i] = u32x4_t{0u, 0u, 0u, 0u};
+    unsigned char* stage = reinterpret_cast<unsigned char*>(s.part + few_part_floats(UH)) + wave * few_stage_bytes(NB);
+    bar_lds();   // (the partial sums of the phase before have been read)
+    few_clear_part<UH>(s.part);
+    bar_lds();
     constexpr int WHOLE = (int)0x80000000u;
     const __amdgpu_buffer_rsrc_t rs_dz = __builtin_amdgcn_make_buffer_rsrc(a.dz, 0, WHOLE, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_ring = __builtin_amdgcn_make_buffer_rsrc(ring, 0, (int)(FEW_RING * slot), 0x00020000);
@@ -585,20 +686,15 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
         }
         if (PIPE == PIPE_CONSUMER && t >= 2 && t - 2 < s.c_wait * pl.ct) {
             --s.c_wait;
-            if (!pipe_wait_chunk(pl, s.c_wait, a.err)) return false;
+            if (!s.ready && !pipe_wait_chunk(pl, s.c_wait, a.err)) return false;
+            s.ready = false;
         }
         // B. dh carried to t-1: dh[piece][k] = sum_q dz[piece][q] * W_hh[q][k] for this workgroup's columns k
         const unsigned char* src = ring + (unsigned)(t & (FEW_RING - 1)) * slot;
-        f32x4_t acc[MT];
-#pragma unroll
-        for (int i = 0; i < MT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         bool ok = true;
         if (polls) {
-            few_for<L / LH>([&](auto ig) {
-                constexpr int g = decltype(ig)::value;
-                if constexpr (g > 0) few_product<MODE, MT, NB, P, (g - 1) * LH * BPL, LH>(s.w, raw, bs, acc);
-                if (ok) ok = few_read<LH>(src, off[g], piece < bs && blk < s.n_blk, true, raw, a.err);
-            });
+            if constexpr (STAGED) ok = few_stage_read<NB>(src, (unsigned)K * es, slice_off, s.n_blk, bs, true, stage, a.err);
+            else ok = few_read<L>(src, off, piece < bs && blk < s.n_blk, true, raw, a.err);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (also: this wave's dz rows of timestep t+1 have completed)
         if (!ok) *s.fail = 1;
@@ -610,13 +706,27 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
             const int base_2 = s.base - s.bs_m1 - s.bs_m2;
             few_load_saved(sv, a, m, n, j, t - 2, grp_count(s.bs_m2, ps), grp_count(s.bs_m1, ps), base_2, base_2 - bs_m3);
         }
-        float* part = s.part + (t & 1) * (REC_WAVES * MAX * ROW);
+        // a look at the chunk that the next timestep asks for, see the forward loop
+        const bool look = PIPE == PIPE_CONSUMER && t >= 3 && t - 3 == s.c_wait * pl.ct - 1;
+        int have = 0;
+        if (look && tid == REC_THREADS - 1) have = ld_agent(&pl.done[s.c_wait - 1]);
+        float* part = s.part + (STAGED ? 0 : (t & 1) * (REC_WAVES * PP * ROW));
         if (polls) {
-            few_product<MODE, MT, NB, P, (L - LH) * BPL, LH>(s.w, raw, bs, acc);
-            few_write<MODE, MT, P>(acc, bs, part + s.slice * (MAX * ROW));
+            f32x4_t acc[MT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if constexpr (STAGED) {
+                few_stage_product<MODE, MT, NB>(s.w, stage, s.n_blk, acc);
+                few_stage_write<MT>(acc, bs, part + s.slice * (PP * ROW));
+            } else {
+                few_product<MODE, MT, NB, P, L>(s.w, raw, bs, acc);
+                few_write<MODE, MT, P>(acc, bs, part + s.slice * (PP * ROW));
+            }
         }
+        if (look && tid == REC_THREADS - 1) s.fail[1] = have;
         bar_lds();
         if (*s.fail) return false;
+        if (look) s.ready = s.fail[1] >= pl.need;
         // Every workgroup has published the rows of timestep t, which it did after its dz rows of timestep t+2 had
         // completed (they are stored in that timestep and waited for in timestep t+1).
         if (PIPE == PIPE_PRODUCER && rank == 0 && tid == REC_THREADS - 1 && t + 2 < T) st_agent(pl.progress, T - (t + 2));
@@ -625,10 +735,10 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
             float q = 0.f;
             const float* p = part + m * ROW + u;
 #pragma unroll
-            for (int k = 0; k < REC_WAVES; ++k)
-                if (k < s.n_slices) q += p[k * (MAX * ROW)];
+            for (int k = 0; k < REC_WAVES; ++k) q += p[k * (PP * ROW)];
             s.dh = q;
         }
+        if (STAGED) bar_lds();   // (one buffer of partial sums: it has been read)
         s.base -= s.bs_m1;
         s.bs_up = s.bs_t;
         s.bs_t = s.bs_m1;
@@ -650,7 +760,7 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
     return true;
 }
 
-// Timesteps T-1 .. t_stop: at most FewMax pieces of the group are alive.  Leaves the carried gradients of this
+// Timesteps T-1 .. t_stop: at most FEW_MAX pieces of the group are alive.  Leaves the carried gradients of this
 // thread's (piece, unit), the sums of its gate gradients and the lowest chunk waited for.  False: a wait was abandoned.
 template <int MODE, int MT, int PIPE>
 __device__ __forceinline__ bool few_bwd(const RecBwdArgs& a, const PieceSet& ps, int rank, int t_stop, int T, const PipeLink& pl, int& c_wait,
@@ -658,14 +768,14 @@ __device__ __forceinline__ bool few_bwd(const RecBwdArgs& a, const PieceSet& ps,
     typedef typename RecGeom<MODE>::E E;
     constexpr int KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC, UH = 16 * MT;
     constexpr int NB = FewBlocks<MODE, MT == 2>::bwd, LOW = 16 / NB;
-    __shared__ int s_fail;
+    __shared__ int s_fail[2];
     const int H = a.H, K = 4 * H, X = ps.X, x = ps.x;
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
     const int m = tid / UH, j = rank * UH + tid % UH, n = m * X + x;
     FewBwd<MODE, MT, NB> s;
-    s.fail = &s_fail;
+    s.fail = s_fail;
     s.part = reinterpret_cast<float*>(smem);
-    if (tid == 0) s_fail = 0;
+    if (tid == 0) s_fail[0] = 0;
     bar_lds();
     const int blocks = K / KBLK;
     s.n_slices = (blocks + NB - 1) / NB;
@@ -674,14 +784,15 @@ __device__ __forceinline__ bool few_bwd(const RecBwdArgs& a, const PieceSet& ps,
     s.n_blk = min(NB, blocks - s.slice * NB);
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
-        const E* wrow = static_cast<const E*>(a.whhT) + ((size_t)rank * UH + i * 16 + lr) * K + s.slice * NB * KBLK + lk * VEC;
+        const E* wrow = static_cast<const E*>(a.whhT) + ((size_t)rank * UH + i * 16 + lr) * K + (s.slice * NB * 4 + lk * s.n_blk) * VEC;
 #pragma unroll
         for (int b = 0; b < NB; ++b)
-            s.w[i * NB + b] = b < s.n_blk ? *reinterpret_cast<const f32x4_t*>(wrow + b * KBLK) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+            s.w[i * NB + b] = b < s.n_blk ? *reinterpret_cast<const f32x4_t*>(wrow + b * VEC) : f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
     for (int i = 0; i < MT * NB; ++i) asm volatile("" : "+v"(s.w[i]));
     s.c_wait = c_wait;
+    s.ready = false;
     s.win.init(a.batch_sizes, T, T - 1);
     s.bs_up = 0;
     s.bs_t = s.win.at(T - 1);
@@ -705,8 +816,7 @@ __device__ __forceinline__ bool few_bwd(const RecBwdArgs& a, const PieceSet& ps,
     int t = T - 1;
     if (!few_bwd_phase<MODE, MT, NB, LOW, PIPE>(s, a, ps, rank, ring, pl, t, T, t_stop, LOW)) return false;
     if (!few_bwd_phase<MODE, MT, NB, 4, PIPE>(s, a, ps, rank, ring, pl, t, T, t_stop, 4)) return false;
-    if constexpr (MODE == MODE_BF16)
-        if (!few_bwd_phase<MODE, MT, NB, 8, PIPE>(s, a, ps, rank, ring, pl, t, T, t_stop, 8)) return false;
+    if (!few_bwd_phase<MODE, MT, NB, 16, PIPE>(s, a, ps, rank, ring, pl, t, T, t_stop, 16)) return false;
     c_wait = s.c_wait;
     dh = s.dh;
     dc = s.dc;

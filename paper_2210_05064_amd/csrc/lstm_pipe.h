@@ -7,9 +7,8 @@
 //
 //   XCD 0..2   time loop of the producer layer (forward: layer 0; backward: layer 1), one group per XCD
 //   XCD 3..5   time loop of the consumer layer, group g on XCD 3 + g
-//   XCD 6..7   workers: for every finished chunk of a group's timesteps, the GEMM that turns the producer's rows
-//              into the consumer's input (forward: gates_1 = h_0 W_ih1^T + b; backward: dh_0 = dz_1 W_ih1),
-//              one 128 x 256 tile at a time
+//   XCD 6..7   workers: for every finished chunk of a group's timesteps, the product that turns the producer's rows
+//              into the consumer's input (forward: gates_1 = h_0 W_ih1^T + b; backward: dh_0 = dz_1 W_ih1)
 //
 // Which pieces a group runs.  A timestep of a time loop costs a fixed latency (one exchange between the group's
 // workgroups, ~3 us) plus a little per alive piece, and the launch lasts as long as its slowest group.  The
@@ -27,12 +26,11 @@
 // the pieces dealt round-robin all groups had to march in step, and every step paid for a third of all alive pieces.
 //
 // Hand-over (lstm_rec.h, PipeLink): producer rows are written through to memory and their completion is
-// published per group; a worker takes the next tile of a group's queue, waits for that group's producer, reads
-// the chunk's rows with loads that bypass the non-coherent caches, writes its tile through, waits for the stores
-// and counts the tile in done[group][chunk]; the consumer group waits until that count has reached the number of
-// tiles of the chunk.  Waiting only ever points backwards along producer -> worker -> consumer and a queue hands
-// out a group's tiles in the order its consumer needs them, so the launch cannot deadlock; every wait is bounded
-// and raises the shared error word on time-out.
+// published per group; the workers of one XCD, which hold all of W_ih1 in their registers, take the chunk, write
+// their columns of the result through, wait for the stores and count themselves in done[group][chunk]; the consumer
+// group waits until that count has reached the number of workers.  Waiting only ever points backwards along
+// producer -> worker -> consumer and every worker takes a group's chunks in the order its consumer needs them,
+// so the launch cannot deadlock; every wait is bounded and raises the shared error word on time-out.
 #pragma once
 #include "lstm_rec.h"
 
@@ -40,45 +38,37 @@ namespace ver {
 
 constexpr int PIPE_GROUPS = 3;       // groups (XCDs) per layer
 constexpr int PIPE_XCDS = 8;         // XCDs of the chip: those beyond the two layers' groups are workers
-constexpr int PIPE_WORKERS = (PIPE_XCDS - 2 * PIPE_GROUPS) * REC_MAX_GROUP;
-static_assert(PIPE_XCDS - 2 * PIPE_GROUPS == 2, "the workers split the column tiles between two XCDs");
+static_assert(PIPE_XCDS - 2 * PIPE_GROUPS == 2, "the chunks alternate between two worker XCDs");
 
 // The plan of a launch (ints in global memory, written by lstm_pipe_plan_kernel):
 constexpr int PLAN_KB = 0;           // [PIPE_GROUPS + 1] first piece of every group's block, then the number of pieces
 constexpr int PLAN_T = 8;            // [PIPE_GROUPS] timesteps of the group (those of its first piece; 0 if it has none)
 constexpr int PLAN_CT = 12;          // [PIPE_GROUPS] timesteps per chunk
-constexpr int PLAN_HDR = 16;         // then rp[PIPE_GROUPS][M + 1]: rows of the group in the timesteps before t
-inline __host__ __device__ size_t plan_words(int M) { return PLAN_HDR + (size_t)PIPE_GROUPS * ((size_t)M + 1); }
+constexpr int PLAN_WORDS = 16;
 inline __host__ __device__ size_t plan_scratch_floats(int M) { return 2 * ((size_t)M + 1); }
-// The words a launch synchronises through (zero at launch): progress[g] at g, queue[g][half] at 8 + g + PIPE_GROUPS * half, then
-// done[g][chunk] from 16 with PIPE_GROUPS rows of pipe_done_stride(M) words.
-constexpr int PIPE_CT_MIN = 4;
+// The words a launch synchronises through (zero at launch): progress[g] at g, then done[g][chunk] from 16 with
+// PIPE_GROUPS rows of pipe_done_stride(M) words.
+constexpr int PIPE_CT_MIN = 2, PIPE_CT_MAX = 8;
 inline __host__ __device__ int pipe_done_stride(int M) { return M / PIPE_CT_MIN + 2; }
 inline __host__ __device__ int pipe_sync_words(int M) { return 16 + PIPE_GROUPS * pipe_done_stride(M); }
 
-// Predicted microseconds of a timestep: step + piece * b + tile * (ceil(b / 16) - 1) (b alive pieces of the group),
-// and the timesteps per chunk: at most ct0 for group 0 (every timestep of a chunk delays the
-// end of the launch once), at most ct for the other groups (which have time to spare: fewer, fuller tiles), and
-// no more than chunk_rows / (pieces of the group): the consumer of a group ends one chunk of GEMM tiles and one
-// chunk of its own steps after the producer, and starts as much later.
+// Predicted microseconds of a timestep: step + piece * b + tile * (ceil(b / 16) - 1) (b alive pieces of the group).
 struct PlanCost {
     float step, piece, tile;
-    int ct0, ct, chunk_rows;
 };
-constexpr int PLAN_CT0 = 8, PLAN_CTN = 16, PLAN_CHUNK_ROWS = 256;
+// Timesteps per chunk by the pieces of the group: a chunk is handed on when it is complete, so the consumer starts and
+// ends that much later than the producer; it costs a worker about 4 us beside the product of its rows.
+constexpr int PLAN_CT_FEW = 4, PLAN_CT_MID = 4, PLAN_CT_MANY = 2;   // up to 4, up to 16, more pieces
 // Fitted by hand to the time per timestep of launches over equally long pieces, 1 .. 64 per group (us):
 //   pieces               1     2     4     8    16    32    64
-//   bf16 H=1024 fwd   1.66  1.72  1.92  2.37  3.0   5.7  12.5      bwd  1.86  2.23  3.0   3.45  4.9   9.0  18
-//   bf16 H=512  fwd   1.41  1.42  1.52  1.62  1.85  3.05           bwd  1.64  1.69  2.0   2.7   3.1   4.4
-//   fp32 H=512  fwd   1.52  1.82  2.5   4.0   4.6   8.9            bwd  1.66  2.37  3.8   4.7   5.7  10.5
-// (timesteps with up to 16 pieces forward, 8 backward, 4 in fp32 run in the form of lstm_few.h).
+//   bf16 H=1024 fwd   1.43  1.35  1.40  1.86  2.04   5.1  12.5      bwd  1.65  1.83  2.2   2.26  3.0   9.1  18
+//   bf16 H=512  fwd   1.19  1.18  1.20  1.36  1.54   3.1            bwd  1.42  1.34  1.6   1.65  2.0   4.4
+//   fp32 H=512  fwd   1.52  1.62  2.26  3.9   3.75   6.6            bwd  1.7   2.05  3.05  4.5   5.35  9.6
+// (timesteps with up to 16 pieces, 4 in fp32, run in the form of lstm_few.h).
 inline PlanCost plan_cost(int mode, bool wide, bool fwd) {
-    PlanCost c;
-    if (mode == MODE_F32) c = fwd ? PlanCost{1.35f, 0.23f, 0.2f} : PlanCost{1.7f, 0.29f, 0.f};
-    else if (wide) c = fwd ? PlanCost{1.58f, 0.09f, 1.4f} : PlanCost{1.85f, 0.2f, 1.f};
-    else c = fwd ? PlanCost{1.35f, 0.035f, 0.6f} : PlanCost{1.55f, 0.1f, 0.f};
-    c.ct0 = PLAN_CT0; c.ct = PLAN_CTN; c.chunk_rows = PLAN_CHUNK_ROWS;
-    return c;
+    if (mode == MODE_F32) return fwd ? PlanCost{1.45f, 0.19f, 1.f} : PlanCost{1.6f, 0.27f, 0.f};
+    if (wide) return fwd ? PlanCost{1.38f, 0.042f, 2.4f} : PlanCost{1.75f, 0.08f, 4.6f};
+    return fwd ? PlanCost{1.17f, 0.023f, 1.2f} : PlanCost{1.38f, 0.04f, 1.7f};
 }
 
 struct PipeWork {
@@ -89,9 +79,9 @@ struct PipeWork {
     int K, N, M;
     const int32_t* t_off;
     const int* plan;
-    int* sync;          // progress, queues, done counters (see above)
+    int* sync;          // progress, done counters (see above)
     int* err;
-    long long* prof_all;   // profiling words (only touched by builds with VER_REC_PROF)
+    int G;              // workers per XCD; each owns N / G columns
 };
 
 constexpr int PLAN_THREADS = 1024;
@@ -137,9 +127,8 @@ template <bool IN_LDS>
 __device__ __forceinline__ void plan_body(const int32_t* __restrict__ batch_sizes, int M, int n_seq, int T, int* __restrict__ plan_fwd,
                                           int* __restrict__ plan_bwd, float* __restrict__ scratch, int* s_bs, float* s_len, float* s_S1,
                                           const PlanCost& pc_fwd, const PlanCost& pc_bwd) {
-    constexpr int WAVES = PLAN_THREADS / 64, NR = PLAN_DIRS * PIPE_GROUPS;
+    constexpr int WAVES = PLAN_THREADS / 64;
     __shared__ float s_wf[WAVES];
-    __shared__ int s_wi[WAVES * NR];
     __shared__ float s_obj[WAVES];
     __shared__ int s_k1[WAVES], s_k2[WAVES];
     __shared__ int s_kb[PLAN_DIRS][PIPE_GROUPS + 1];
@@ -213,44 +202,13 @@ __device__ __forceinline__ void plan_body(const int32_t* __restrict__ batch_size
         for (int g = 0; g <= PIPE_GROUPS; ++g) plan[PLAN_KB + g] = s_kb[dir][g];
     }
     __syncthreads();
-    // per plan and group: its timesteps, its chunk length, and its rows before every timestep (all six prefix sums at once)
-    int lo_[NR], cap_[NR], Tg_[NR], carry[NR];
-    int Tmax = 0;
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        const int d = r / PIPE_GROUPS, g = r % PIPE_GROUPS;
-        lo_[r] = s_kb[d][g];
-        cap_[r] = s_kb[d][g + 1] - lo_[r];
-        Tg_[r] = cap_[r] > 0 ? (int)len[lo_[r]] : 0;
-        carry[r] = 0;
-        Tmax = max(Tmax, Tg_[r]);
-        if (tid == 0) {
-            int* plan = d == 0 ? plan_fwd : plan_bwd;
-            const PlanCost& c = d == 0 ? pc_fwd : pc_bwd;
-            plan[PLAN_T + g] = Tg_[r];
-            plan[PLAN_CT + g] = min(g == 0 ? c.ct0 : c.ct, max(PIPE_CT_MIN, c.chunk_rows / max(cap_[r], 1)));
-        }
+    if (tid < PLAN_DIRS * PIPE_GROUPS) {   // per plan and group: its timesteps and its chunk length
+        const int d = tid / PIPE_GROUPS, g = tid % PIPE_GROUPS;
+        const int lo = s_kb[d][g], cap = s_kb[d][g + 1] - lo;
+        int* plan = d == 0 ? plan_fwd : plan_bwd;
+        plan[PLAN_T + g] = cap > 0 ? (int)len[lo] : 0;
+        plan[PLAN_CT + g] = cap <= 4 ? PLAN_CT_FEW : (cap <= 16 ? PLAN_CT_MID : PLAN_CT_MANY);
     }
-    for (int b0 = 0; b0 < Tmax; b0 += PLAN_THREADS) {
-        const int t = b0 + tid;
-        const int b = t < Tmax ? bs[t] : 0;
-        int cnt[NR], tot[NR];
-#pragma unroll
-        for (int r = 0; r < NR; ++r) cnt[r] = t < Tg_[r] ? min(max(b - lo_[r], 0), cap_[r]) : 0;
-        plan_scan<int, NR>(cnt, s_wi, tot);
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            int* rp = (r / PIPE_GROUPS == 0 ? plan_fwd : plan_bwd) + PLAN_HDR + (size_t)(r % PIPE_GROUPS) * ((size_t)M + 1);
-            if (t < Tg_[r]) rp[t] = carry[r] + cnt[r];
-            carry[r] += tot[r];
-        }
-    }
-    if (tid == 0)
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            int* rp = (r / PIPE_GROUPS == 0 ? plan_fwd : plan_bwd) + PLAN_HDR + (size_t)(r % PIPE_GROUPS) * ((size_t)M + 1);
-            rp[Tg_[r]] = carry[r];
-        }
 }
 
 // One workgroup, in front of the forward launch: clears that launch's synchronisation words and writes the plans of
@@ -269,177 +227,35 @@ __global__ __launch_bounds__(PLAN_THREADS) void lstm_pipe_plan_kernel(const int3
         plan_body<false>(batch_sizes, M, n_seq, T, plan_fwd, plan_bwd, scratch, s_bs, s_len, s_S1, pc_fwd, pc_bwd);
 }
 
-template <typename E, typename T> __device__ __forceinline__ Quad<E> load_quad_coh(__amdgpu_buffer_rsrc_t r, int byte_off);
-template <> __device__ __forceinline__ Quad<float> load_quad_coh<float, float>(__amdgpu_buffer_rsrc_t r, int byte_off) {
-    const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 17);
-    return Quad<float>{{__uint_as_float(t[0]), __uint_as_float(t[1]), __uint_as_float(t[2]), __uint_as_float(t[3])}};
-}
-template <> __device__ __forceinline__ Quad<bf16_t> load_quad_coh<bf16_t, bf16_t>(__amdgpu_buffer_rsrc_t r, int byte_off) {
-    const u32x2_t t = __builtin_amdgcn_raw_buffer_load_b64(r, byte_off, 0, 17);
-    return Quad<bf16_t>{{(bf16_t)(t.x & 0xffff), (bf16_t)(t.x >> 16), (bf16_t)(t.y & 0xffff), (bf16_t)(t.y >> 16)}};
-}
-
-// A row that a tile does not have: an offset beyond every buffer (loads return zero, stores are dropped), which
-// stays there when a K-tile's offset is added.
-constexpr int PIPE_NO_ROW = (int)0x80000000u;
-
-// One 128 x 256 tile of C = A B^T (+ bias) for the rows rowmap[0 .. 127] (LDS; -1: none) and columns from col0,
-// by 8 waves (2 x 4 of 64 x 64).  Same K-tile pipeline as gemm_kernel: the next K-tile's global loads are in
-// flight while the current one is multiplied out of LDS.
-// nrows: the tile's rows are its first nrows; a wave whose 64 rows hold none of them does not multiply, one that holds
-// at most 16 multiplies only its first 16-row tile (an fp32 tile is bound by its MFMAs, 16 times slower per FLOP
-// than bf16 ones: the tiles of a group with one or two pieces would otherwise cost as much as full ones).
-template <int MODE, typename TA>
-__device__ __forceinline__ void pipe_gemm_tile(const PipeWork& w, const int* rowmap, int nrows, int col0, unsigned char* smem) {
-    typedef typename LdsElem<MODE>::type E;
-    constexpr int BK = GemmGeom<MODE>::BK, STRIDE = GemmGeom<MODE>::LDS_STRIDE;
-    constexpr int CPR = BK / 4, RPP = REC_THREADS / CPR, QA = PIPE_BM / RPP, QB = PIPE_BN / RPP;
-    E* sA = reinterpret_cast<E*>(smem);
-    E* sB = sA + PIPE_BM * STRIDE;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = (wave >> 2) * 64, wn = (wave & 3) * 64;
-    const int lr = lane & 15, lk = lane >> 4;
-    const int c = tid % CPR, r = tid / CPR;
-    const int K = w.K, N = w.N;
-    __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<TA*>(static_cast<const TA*>(w.A)), 0,
-                                                                   w.M * K * (int)sizeof(TA), 0x00020000);
-    const E* Bp = static_cast<const E*>(w.B);
-    int rowoff[QA];
-#pragma unroll
-    for (int i = 0; i < QA; ++i) {
-        const int g = rowmap[r + i * RPP];
-        rowoff[i] = g >= 0 ? g * K * (int)sizeof(TA) : PIPE_NO_ROW;
-    }
-
-    f32x4_t acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-    Quad<E> ra[QA], rb[QB];
-    auto load_tiles = [&](int k0) {
-#pragma unroll
-        for (int i = 0; i < QA; ++i) {
-            ra[i] = load_quad_coh<E, TA>(rsA, rowoff[i] + (k0 + c * 4) * (int)sizeof(TA));   // rows the tile does not have read zero
-        }
-#pragma unroll
-        for (int i = 0; i < QB; ++i) {
-            const int n = col0 + r + i * RPP;
-            rb[i] = n < N ? load_quad<E, E>(Bp + (size_t)n * K + k0 + c * 4) : zero_quad<E>();
-        }
-    };
-    load_tiles(0);
-    for (int k0 = 0; k0 < K; k0 += BK) {
-#pragma unroll
-        for (int i = 0; i < QA; ++i) store_quad(sA + (r + i * RPP) * STRIDE + c * 4, ra[i]);
-#pragma unroll
-        for (int i = 0; i < QB; ++i) store_quad(sB + (r + i * RPP) * STRIDE + c * 4, rb[i]);
-        bar_lds();
-        if (k0 + BK < K) load_tiles(k0 + BK);
-        const int nr = nrows - wm;   // rows of the tile among this wave's 64 (uniform in the wave)
-        if (nr <= 0) {
-            // nothing to multiply
-        } else if (MODE == MODE_F32 && nr <= 16) {
-#pragma unroll
-            for (int ks = 0; ks < BK; ks += 16) {
-                const f32x4_t a0 = *reinterpret_cast<const f32x4_t*>(reinterpret_cast<const float*>(sA) + (wm + lr) * STRIDE + ks + lk * 4);
-                f32x4_t b[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    b[j] = *reinterpret_cast<const f32x4_t*>(reinterpret_cast<const float*>(sB) + (wn + j * 16 + lr) * STRIDE + ks + lk * 4);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[0][j] = mfma_f32_16x16x4(a0[e], b[j][e], acc[0][j]);
-            }
-        } else if (MODE == MODE_BF16) {
-#pragma unroll
-            for (int ks = 0; ks < BK; ks += 32) {
-                u16x8_t a[4], b[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    a[i] = *reinterpret_cast<const u16x8_t*>(reinterpret_cast<const bf16_t*>(sA) + (wm + i * 16 + lr) * STRIDE + ks + lk * 8);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    b[j] = *reinterpret_cast<const u16x8_t*>(reinterpret_cast<const bf16_t*>(sB) + (wn + j * 16 + lr) * STRIDE + ks + lk * 8);
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = mfma_bf16_16x16x32(a[i], b[j], acc[i][j]);
-            }
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < BK; ks += 16) {
-                f32x4_t a[4], b[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    a[i] = *reinterpret_cast<const f32x4_t*>(reinterpret_cast<const float*>(sA) + (wm + i * 16 + lr) * STRIDE + ks + lk * 4);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    b[j] = *reinterpret_cast<const f32x4_t*>(reinterpret_cast<const float*>(sB) + (wn + j * 16 + lr) * STRIDE + ks + lk * 4);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) acc[i][j] = mfma_f32_16x16x4(a[i][e], b[j][e], acc[i][j]);
-            }
-        }
-        bar_lds();
-    }
-    // C fragment: element e of lane l is row (l / 16) * 4 + e, column l % 16 of the 16x16 tile; written through
-    __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(w.C, 0, w.M * N * 4, 0x00020000);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        int crow[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int g = rowmap[wm + i * 16 + lk * 4 + e];
-            crow[e] = g >= 0 ? g * N * 4 : PIPE_NO_ROW;   // rows the tile does not have are dropped (buffer bounds)
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = col0 + wn + j * 16 + lr;
-            if (n >= N) continue;
-            const float bv = w.bias ? w.bias[n] : 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][e] + bv), rsC, crow[e] + n * 4, 0, 17);
-        }
-    }
-}
-
-// The same tile for bf16 operands on both sides, built for a workgroup that has the CU to itself: K-tiles of
-// 64 go from global memory straight into LDS (three stages, two K-tiles in flight while one is multiplied,
-// one barrier per K-tile, no registers or LDS stores in between).  An LDS row is the 128 bytes of a tile row,
-// as 8 chunks of 16 bytes; chunk position p of row r holds chunk p ^ ((r >> 1) & 7), which makes the 16-byte
-// MFMA operand reads of 16 consecutive rows hit all banks once.  A load instruction fills 8 rows (lane -> row
+// One 128 x 256 tile of C[M, N] = A[M, K] B[N, K]^T + bias for bf16 operands, by 8 waves (2 x 4 of 64 x 64) of a workgroup
+// that has the CU to itself: K-tiles of 64 go from global memory straight into LDS (three stages, two K-tiles in flight
+// while one is multiplied, one barrier per K-tile, no registers or LDS stores in between).  An LDS row is the 128 bytes
+// of a tile row, as 8 chunks of 16 bytes; chunk position p of row r holds chunk p ^ ((r >> 1) & 7), which makes the
+// 16-byte MFMA operand reads of 16 consecutive rows hit all banks once.  A load instruction fills 8 rows (lane -> row
 // lane / 8, position lane % 8), so the swizzle is applied on the global side.
+constexpr int PIPE_BM = 128;         // rows per GEMM tile
+constexpr int PIPE_BN = 256;         // columns per GEMM tile
 constexpr int PIPE_STAGES = 3;
 constexpr int PIPE_STAGE_BYTES = (PIPE_BM + PIPE_BN) * 128;
 // K need not be a multiple of 64 (it is a multiple of 4): the last K-tile then also fetches what follows the rows'
 // ends (the next row, or zeros past the end of the arrays), and the A operand is cleared beyond K in registers, so
 // that whatever was fetched on the B side is multiplied by zero.
-// COHERENT (a worker's tile): the tile's rows are rowmap[0 .. 127] (LDS; -1: none), A is being written by other
-// XCDs during this launch and C is read by them (loads and stores that bypass the non-coherent caches).
-// Otherwise (a launch of its own): the rows [row0, row_end).
-// nrows: the tile's rows are its first nrows (a worker's tile of a group with few pieces holds a handful): the waves
-// whose 64 rows hold none of them neither read operands from LDS nor multiply (they still load and synchronise).
-template <bool COHERENT>
-__device__ __forceinline__ void pipe_gemm_tile_dma(const PipeWork& w, const int* rowmap, int row0, int row_end, int nrows, int col0,
-                                                   unsigned char* smem) {
+struct ProjWork {
+    const void* A;      // [M, K]
+    const void* B;      // [N, K]
+    float* C;           // [M, N]
+    const float* bias;  // [N] or NULL
+    int K, N, M;
+};
+__device__ __forceinline__ void proj_tile_dma(const ProjWork& w, int row0, int row_end, int col0, unsigned char* smem) {
     constexpr int BK = 64;
-    constexpr int AUX = COHERENT ? 17 : 0;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = (wave >> 2) * 64, wn = (wave & 3) * 64;
     const int lr = lane & 15, lk = lane >> 4;
     const int K = w.K, N = w.N, nk = (K + BK - 1) / BK, k_tail = K % BK;
     const int ncols = min(N - col0, PIPE_BN);
-    __amdgpu_buffer_rsrc_t rsA = COHERENT
-        ? __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(static_cast<const bf16_t*>(w.A)), 0, w.M * K * 2, 0x00020000)
-        : __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(static_cast<const bf16_t*>(w.A)) + (size_t)row0 * K, 0,
-                                            (row_end - row0) * K * 2, 0x00020000);
+    __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(static_cast<const bf16_t*>(w.A)) + (size_t)row0 * K, 0, (row_end - row0) * K * 2, 0x00020000);
     __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<bf16_t*>(static_cast<const bf16_t*>(w.B)) + (size_t)col0 * K, 0, ncols * K * 2, 0x00020000);
     // source offsets of this lane in the 2 (A) + 4 (B) load instructions of this wave per K-tile
@@ -448,12 +264,7 @@ __device__ __forceinline__ void pipe_gemm_tile_dma(const PipeWork& w, const int*
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int row = (wave * 2 + j) * 8 + row_in;
-        int src = row * K * 2;
-        if (COHERENT) {
-            const int g = rowmap[row];
-            src = g >= 0 ? g * K * 2 : PIPE_NO_ROW;
-        }
-        voffA[j] = src + ((pos ^ ((row >> 1) & 7)) << 4);
+        voffA[j] = row * K * 2 + ((pos ^ ((row >> 1) & 7)) << 4);
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -463,8 +274,8 @@ __device__ __forceinline__ void pipe_gemm_tile_dma(const PipeWork& w, const int*
     auto issue = [&](int kt) {
         unsigned char* st = smem + (kt % PIPE_STAGES) * PIPE_STAGE_BYTES;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)   // producer rows: written by other XCDs during this launch
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_ptr_t)(st + (wave * 2 + j) * 1024), 16, voffA[j], kt * BK * 2, 0, AUX);
+        for (int j = 0; j < 2; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_ptr_t)(st + (wave * 2 + j) * 1024), 16, voffA[j], kt * BK * 2, 0, 0);
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, (lds_ptr_t)(st + PIPE_BM * 128 + (wave * 4 + j) * 1024), 16, voffB[j],
@@ -493,22 +304,6 @@ __device__ __forceinline__ void pipe_gemm_tile_dma(const PipeWork& w, const int*
         bar_lds();   // ... and so have everyone's; everyone has also finished reading stage kt-1
         if (kt + 2 < nk) issue(kt + 2);   // into the stage that was read in iteration kt-1
         const unsigned char* st = smem + (kt % PIPE_STAGES) * PIPE_STAGE_BYTES;
-        if (COHERENT && nrows <= wm) continue;   // (uniform in the wave)
-        if (COHERENT && nrows - wm <= 16) {
-            // at most 16 rows (the tiles of a group with one or two pieces): only the first of the four 16-row tiles
-            // (the workers' K is a whole number of K-tiles: no tail to clear)
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                const u16x8_t a0 = *reinterpret_cast<const u16x8_t*>(st + arow[0] + (((ks * 4 + lk) ^ asw[0]) << 4));
-                u16x8_t b[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    b[j] = *reinterpret_cast<const u16x8_t*>(st + brow[j] + (((ks * 4 + lk) ^ bsw[j]) << 4));
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[0][j] = mfma_bf16_16x16x32(a0, b[j], acc[0][j]);
-            }
-            continue;
-        }
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             u16x8_t a[4], b[4];
@@ -535,21 +330,11 @@ __device__ __forceinline__ void pipe_gemm_tile_dma(const PipeWork& w, const int*
                 for (int j = 0; j < 4; ++j) acc[i][j] = mfma_bf16_16x16x32(a[i], b[j], acc[i][j]);
         }
     }
-    // C fragment: element e of lane l is row (l / 16) * 4 + e, column l % 16 of the 16x16 tile; written through
-    __amdgpu_buffer_rsrc_t rsC = COHERENT ? __builtin_amdgcn_make_buffer_rsrc(w.C, 0, w.M * N * 4, 0x00020000)
-                                          : __builtin_amdgcn_make_buffer_rsrc(w.C + (size_t)row0 * N, 0, (row_end - row0) * N * 4, 0x00020000);
+    // C fragment: element e of lane l is row (l / 16) * 4 + e, column l % 16 of the 16x16 tile
+    __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(w.C + (size_t)row0 * N, 0, (row_end - row0) * N * 4, 0x00020000);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        int crow[4];   // rows the tile does not have are dropped (buffer bounds)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int lrow = wm + i * 16 + lk * 4 + e;
-            crow[e] = lrow * N * 4;
-            if (COHERENT) {
-                const int g = rowmap[lrow];
-                crow[e] = g >= 0 ? g * N * 4 : PIPE_NO_ROW;
-            }
-        }
+        const int crow = (wm + i * 16 + lk * 4) * N * 4;   // rows the tile does not have are dropped (buffer bounds)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int n = col0 + wn + j * 16 + lr;
@@ -557,28 +342,27 @@ __device__ __forceinline__ void pipe_gemm_tile_dma(const PipeWork& w, const int*
             const float bv = w.bias ? w.bias[n] : 0.f;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][e] + bv), rsC, crow[e] + n * 4, 0, AUX);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][e] + bv), rsC, crow + (e * N + n) * 4, 0, 0);
         }
     }
 }
 
-// The same tiles as a launch of its own: C[M, N] = A[M, K] B[N, K]^T + bias, bf16 operands (the input projection
-// of the first layer).  One workgroup per tile; consecutive workgroups (dealt round-robin to the XCDs) take the
-// column tiles of one row tile, so that a row tile of A is fetched from memory by one round of workgroups.
-__global__ __launch_bounds__(REC_THREADS) void lstm_proj_dma_kernel(PipeWork w, int M, int tiles_n) {
+// C[M, N] = A[M, K] B[N, K]^T + bias (the input projection of the first layer).  One workgroup per tile; consecutive
+// workgroups (dealt round-robin to the XCDs) take the column tiles of one row tile, so that a row tile of A is fetched
+// from memory by one round of workgroups.
+__global__ __launch_bounds__(REC_THREADS) void lstm_proj_dma_kernel(ProjWork w, int tiles_n) {
     extern __shared__ __attribute__((aligned(16))) unsigned char proj_smem[];
     const int rt = blockIdx.x / tiles_n, ct = blockIdx.x % tiles_n;
-    pipe_gemm_tile_dma<false>(w, nullptr, rt * PIPE_BM, min(M, (rt + 1) * PIPE_BM), PIPE_BM, ct * PIPE_BN, proj_smem);
+    proj_tile_dma(w, rt * PIPE_BM, min(w.M, (rt + 1) * PIPE_BM), ct * PIPE_BN, proj_smem);
 }
 
 // One group's view of the hand-over words, from the plan.
-__device__ __forceinline__ PipeLink pipe_link_of(const int* plan, int* sync, int M, int tiles_n, int g) {
+__device__ __forceinline__ PipeLink pipe_link_of(const int* plan, int* sync, int M, int need, int g) {
     PipeLink pl;
     pl.progress = sync + g;
     pl.done = sync + 16 + g * pipe_done_stride(M);
-    pl.rp = plan + PLAN_HDR + (size_t)g * ((size_t)M + 1);
+    pl.need = need;
     pl.ct = plan[PLAN_CT + g];
-    pl.tiles_n = tiles_n;
     pl.T = plan[PLAN_T + g];
     return pl;
 }
@@ -587,107 +371,185 @@ __device__ __forceinline__ PieceSet pipe_pieces_of(const int* plan, int g) {
     return PieceSet{lo, 1, plan[PLAN_KB + g + 1] - lo, g};
 }
 
-// Worker loop.  A worker serves one group's queue until it is empty, then the next group's (it starts with the
-// group `home`).  The items of a queue are the tiles of the group's chunks in the order the consumer needs the
-// chunks (DESCEND: last chunk first); item -> (chunk, row tile, column tile) is found by walking the chunks,
-// which a worker only ever does forwards because a queue hands out increasing items.
-// half: which of the two worker XCDs this is.  Each takes one half of the column tiles (a queue per group and half), so
-// that the slab of the weights it streams again and again is half as large (4 MB at H = 1024: the size of its L2):
-// counters show 0.8 instead of 1.4 GB fetched per forward launch and 1.1 instead of 1.5 GB per backward launch of the
-// largest configuration, at the same launch times (the re-reads were served by the memory-side cache before).
-template <int MODE, bool DESCEND>
-__device__ __forceinline__ void pipe_worker(const PipeWork& w, int tiles_n, int home, int half, unsigned char* smem) {
-    const int tn_lo = (tiles_n + 1) / 2;
-    const int my_tn = half == 0 ? tn_lo : tiles_n - tn_lo, col_first = half == 0 ? 0 : tn_lo;
-    if (my_tn == 0) return;   // (a single column tile: the other XCD's)
-    __shared__ int s_item[4];    // chunk, local tile, ok (0: leave, 1: tile, 2: queue empty)
-    __shared__ int s_rp[PIPE_CT_MAX + 1], s_to[PIPE_CT_MAX];
-    __shared__ int s_rowmap[PIPE_BM];
-    const int tid = threadIdx.x;
-#ifdef VER_REC_PROF
-    long long* wst = w.prof_all + 96 + home * 4;   // per home group: tiles, time in tiles, time waiting for producers, time in the queue (100 MHz)
-    long long wt = 0;
-#endif
-    for (int visit = 0; visit < PIPE_GROUPS; ++visit) {
-        const int g = (home + visit) % PIPE_GROUPS;
-        const PipeLink pl = pipe_link_of(w.plan, w.sync, w.M, tiles_n, g);
-        const int lo = w.plan[PLAN_KB + g];
-        int* queue = w.sync + 8 + g + PIPE_GROUPS * half;
-        const int n_chunks = (pl.T + pl.ct - 1) / pl.ct;
-        int cur = 0, prefix = 0;     // thread 0's cursor: chunks [0, cur) in queue order hold items [0, prefix)
-        for (;;) {
-            if (tid == 0) {
-#ifdef VER_REC_PROF
-                wt = wall_clock64();
-#endif
-                int ok = 2, c = 0, local = 0;
-                if (cur < n_chunks) {
-                    const int item = __hip_atomic_fetch_add(queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    while (cur < n_chunks) {
-                        c = DESCEND ? n_chunks - 1 - cur : cur;
-                        const int tiles = pipe_chunk_tiles(pl, c) / tiles_n * my_tn;   // this half's tiles of the chunk
-                        if (item < prefix + tiles) { local = item - prefix; ok = 1; break; }
-                        prefix += tiles;
-                        ++cur;
-                    }
+// ---- workers -------------------------------------------------------------------------------------------------
+// The 32 CUs of an XCD hold 8 MB of weights in their registers, which is all of W_ih1 (as it is all of a W_hh): a worker
+// keeps the weights of its N / G columns resident, in the layout of the time loops of lstm_few.h (8 waves, each an
+// eighth of the contraction), and turns 16 rows at a time into the consumer's input.  What bounds it: the 16 MFMA
+// cycles per weight operand and 16 rows (0.43 us at H = 1024), the partial sums of 16 rows through LDS (64 KB forward),
+// and per chunk the round trips of progress word, rows and stores (about 4 us).  (128 x 256 tiles that streamed the
+// weights from L2 through LDS took 18 us forward and 54 us backward each, 14 and 38 us for a handful of rows: the
+// consumer started and ended that much later, and 32768 rows kept the two XCDs busy for 2.9 ms.)
+// The chunks of a group go to the two XCDs in turn.
+constexpr int WORK_LDS_T = 2047;   // timesteps whose row offsets are kept in LDS
+inline __host__ __device__ size_t work_lds_bytes(int cols, int nb) {
+    return (size_t)few_part_floats(cols) * sizeof(float) + (size_t)REC_WAVES * few_stage_bytes(nb) + (WORK_LDS_T + 1) * sizeof(int);
+}
+
+__device__ __forceinline__ void work_load_lds(__amdgpu_buffer_rsrc_t rs, unsigned char* lds, unsigned off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)lds, 16, off, 0, 0, 17);
+}
+// Requests this wave's slice of 16 rows (numbers in LDS) into its staging area; a lane's LDS address is the load's base + 16 * lane.
+template <int NB>
+__device__ __forceinline__ void work_request(__amdgpu_buffer_rsrc_t rs, unsigned char* stage, const int* rows, unsigned row_bytes, int slice, int n_blk) {
+#pragma unroll
+    for (int j = 0; j < FewStage<NB>::LOADS; ++j) {
+        const int r = FewStage<NB>::row(j);
+        work_load_lds(rs, stage + j * 1024, (unsigned)rows[r] * row_bytes + (unsigned)(slice * NB) * 64u + FewStage<NB>::src(r, n_blk));
+    }
+}
+
+// FWD: 16 * MT columns per worker, four of them (a unit's gates) per thread; else one column per thread.
+template <int MODE, int MT, int NB, bool FWD>
+__device__ __forceinline__ void pipe_worker(const PipeWork& w, int rank, int half, unsigned char* smem) {
+    typedef typename RecGeom<MODE>::E E;
+    constexpr int es = (int)sizeof(E), KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC;
+    constexpr int COLS = 16 * MT, ROW = few_row(COLS), PER = FWD ? 4 : 1, TPR = COLS / PER;   // threads per row
+    static_assert(16 * TPR <= REC_THREADS, "a thread per row and column group");
+    constexpr bool DESCEND = !FWD;   // the backward consumer needs the last chunk first
+    __shared__ int s_sel[2];
+    __shared__ int s_row[REC_THREADS];
+    float* part = reinterpret_cast<float*>(smem);
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    unsigned char* stage = smem + (size_t)few_part_floats(COLS) * sizeof(float) + wave * few_stage_bytes(NB);
+    int* s_toff = reinterpret_cast<int*>(smem + (size_t)few_part_floats(COLS) * sizeof(float) + REC_WAVES * few_stage_bytes(NB));
+    const int K = w.K, N = w.N, blocks = K / KBLK, n_slices = (blocks + NB - 1) / NB;
+    // (which slice a wave takes rotates with the rank: all workers read the same rows at the same moment)
+    const int slice = n_slices == REC_WAVES ? (wave + rank) % REC_WAVES : wave;
+    const int n_blk = min(NB, blocks - slice * NB);
+    f32x4_t wreg[MT * NB];
+#pragma unroll
+    for (int j = 0; j < MT; ++j) {
+        const E* wrow = static_cast<const E*>(w.B) + ((size_t)rank * COLS + j * 16 + lr) * K + (slice * NB * 4 + lk * n_blk) * VEC;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            wreg[j * NB + b] = b < n_blk ? *reinterpret_cast<const f32x4_t*>(wrow + b * VEC) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int i = 0; i < MT * NB; ++i) asm volatile("" : "+v"(wreg[i]));
+    const int m = tid / TPR, col = rank * COLS + (tid % TPR) * PER;
+    f32x4_t bias = {0.f, 0.f, 0.f, 0.f};
+    if (FWD && w.bias) bias = *reinterpret_cast<const f32x4_t*>(w.bias + rank * COLS + (tid % TPR) * 4);
+    int lo[PIPE_GROUPS], cap[PIPE_GROUPS], T[PIPE_GROUPS], ct[PIPE_GROUPS], at[PIPE_GROUPS], t_max = 0;
+#pragma unroll
+    for (int g = 0; g < PIPE_GROUPS; ++g) {
+        lo[g] = w.plan[PLAN_KB + g];
+        cap[g] = w.plan[PLAN_KB + g + 1] - lo[g];
+        T[g] = w.plan[PLAN_T + g];
+        ct[g] = w.plan[PLAN_CT + g];
+        const int n = (T[g] + ct[g] - 1) / ct[g];
+        // this XCD's first chunk of the group in the consumer's order
+        at[g] = DESCEND ? n - 1 - ((n - 1 + g + half) & 1) : ((g + half) & 1);
+        t_max = max(t_max, T[g]);
+    }
+    for (int t = tid; t <= min(t_max, WORK_LDS_T); t += REC_THREADS) s_toff[t] = w.t_off[t];
+    few_clear_part<COLS>(part);
+    bar_lds();
+    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(w.A), 0, w.M * K * es, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(w.C, 0, w.M * N * 4, 0x00020000);
+    int have = lane < PIPE_GROUPS && wave == 0 ? ld_agent(w.sync + lane) : 0;   // the producers' progress
+    for (;;) {
+        // The next chunk: the first group (group 0 bounds the launch) whose producer has completed its next one.
+        if (wave == 0) {
+            int sel = -1;
+            long long spins = 0;
+            for (;;) {
+                bool left = false;
+#pragma unroll
+                for (int g = PIPE_GROUPS - 1; g >= 0; --g) {
+                    const bool more = DESCEND ? at[g] >= 0 : at[g] * ct[g] < T[g];
+                    const int need = DESCEND ? T[g] - at[g] * ct[g] : min((at[g] + 1) * ct[g], T[g]);
+                    left = left || more;
+                    if (more && __builtin_amdgcn_readlane(have, g) >= need) sel = g;
                 }
-#ifdef VER_REC_PROF
-                { const long long now = wall_clock64(); atomicAdd((unsigned long long*)&wst[3], (unsigned long long)(now - wt)); wt = now; }
-#endif
-                if (ok == 1) {
-                    // the group's producer must have completed the chunk's timesteps
-                    const int t_lo = c * pl.ct, t_hi = min(t_lo + pl.ct, pl.T);
-                    const int need = DESCEND ? pl.T - t_lo : t_hi;
-                    long long spins = 0;
-                    while (ld_agent(pl.progress) < need) {
-                        ++spins;
-                        if ((spins & 255) == 0 && (spins > REC_SPIN_LIMIT || ld_agent(w.err) != 0)) {
-                            st_agent(w.err, 1);
-                            ok = 0;
-                            break;
-                        }
-                    }
+                if (sel >= 0 || !left) break;
+                if ((++spins & 255) == 0 && (spins > REC_SPIN_LIMIT || ld_agent(w.err) != 0)) {
+                    if (lane == 0) st_agent(w.err, 1);
+                    break;
                 }
-                s_item[0] = c; s_item[1] = local; s_item[2] = ok;
-#ifdef VER_REC_PROF
-                { const long long now = wall_clock64(); atomicAdd((unsigned long long*)&wst[2], (unsigned long long)(now - wt)); wt = now; }
-#endif
+                have = lane < PIPE_GROUPS ? ld_agent(w.sync + lane) : 0;
             }
-            bar_lds();
-            const int c = s_item[0], local = s_item[1], ok = s_item[2];
-            if (ok == 0) return;
-            if (ok == 2) { bar_lds(); break; }   // this queue is empty: on to the next group
-            // the rows of the tile: the group's rows of the chunk's timesteps, in time order, PIPE_BM at a time
-            const int t0 = c * pl.ct, nt = min(pl.ct, pl.T - t0);
-            const int rt = local / my_tn, ctile = col_first + local % my_tn;
-            if (tid <= nt) s_rp[tid] = pl.rp[t0 + tid];
-            if (tid < nt) s_to[tid] = w.t_off[t0 + tid];
-            bar_lds();                      // (s_item may be rewritten from here on)
-            if (tid < PIPE_BM) {
-                const int slot = s_rp[0] + rt * PIPE_BM + tid;
-                int row = -1;
-                if (slot < s_rp[nt]) {
-                    int i = 0;
-                    while (s_rp[i + 1] <= slot) ++i;   // ends: s_rp[nt] > slot
-                    row = s_to[i] + lo + (slot - s_rp[i]);
-                }
-                s_rowmap[tid] = row;
-            }
-            bar_lds();
-            if constexpr (MODE == MODE_BF16)
-                pipe_gemm_tile_dma<true>(w, s_rowmap, 0, 0, min(PIPE_BM, s_rp[nt] - s_rp[0] - rt * PIPE_BM), ctile * PIPE_BN, smem);
-            else
-                pipe_gemm_tile<MODE, typename LdsElem<MODE>::type>(w, s_rowmap, min(PIPE_BM, s_rp[nt] - s_rp[0] - rt * PIPE_BM), ctile * PIPE_BN, smem);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            bar_lds();
-            if (tid == 0) __hip_atomic_fetch_add(&pl.done[c], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#ifdef VER_REC_PROF
-            if (tid == 0) {
-                atomicAdd((unsigned long long*)&wst[1], (unsigned long long)(wall_clock64() - wt));
-                atomicAdd((unsigned long long*)&wst[0], 1ull);
-            }
-#endif
+            if (lane == 0) s_sel[0] = sel;
         }
+        bar_lds();
+        const int sel = __builtin_amdgcn_readfirstlane(s_sel[0]);
+        if (sel < 0) return;   // nothing left, or the wait was abandoned
+        int g_lo = lo[0], g_cap = cap[0], g_T = T[0], g_ct = ct[0], c = at[0];
+#pragma unroll
+        for (int g = 0; g < PIPE_GROUPS; ++g)
+            if (sel == g) {
+                g_lo = lo[g]; g_cap = cap[g]; g_T = T[g]; g_ct = ct[g]; c = at[g];
+                at[g] += DESCEND ? -2 : 2;
+            }
+        // The group's rows of the chunk in time order: lane k holds what is needed of its timestep k.
+        const int t0 = c * g_ct, nt = min(g_ct, g_T - t0);
+        const int tk = t0 + min(lane, nt);
+        const int off_k = tk <= WORK_LDS_T ? s_toff[tk] : w.t_off[tk];
+        const int off_k1 = __shfl(off_k, min(lane + 1, nt), VER_WAVE);   // (all lanes active: lane nt is read)
+        const int cnt = lane < nt ? min(max(off_k1 - off_k - g_lo, 0), g_cap) : 0;
+        int before = cnt;   // inclusive prefix over the lanes, then exclusive
+#pragma unroll
+        for (int d = 1; d < 2 * PIPE_CT_MAX; d <<= 1) {
+            const int o = __shfl_up(before, d, VER_WAVE);
+            if (lane >= d) before += o;
+        }
+        const int total = __builtin_amdgcn_readlane(before, nt - 1);
+        before -= cnt;
+        const int row_k = off_k + g_lo - before;   // row of slot s of timestep k: row_k + s
+        auto row_of = [&](int s) {
+            int k = 0;
+            for (int j = 1; j < nt; ++j) k += s >= __builtin_amdgcn_readlane(before, j) ? 1 : 0;
+            return __shfl(row_k, k, VER_WAVE) + s;
+        };
+        // 16 rows at a time, their numbers from a table of up to REC_THREADS rows.  A wave's slice of the rows goes from memory
+        // straight into its staging area (few_stage_product says how it lies there); the next tile's is requested as
+        // soon as this one's operands have been read, and arrives behind the partial sums.  (Every store is issued, out of
+        // range for rows that a tile does not have: a store that may or may not be there makes the wait for the loads
+        // before it a wait for the store.)
+        const bool works = slice < n_slices;
+        for (int b0 = 0; b0 < total; b0 += REC_THREADS) {
+            const int n = min(total - b0, REC_THREADS);
+            s_row[tid] = row_of(min(b0 + tid, total - 1));
+            bar_lds();
+            if (works) work_request<NB>(rsA, stage, s_row, (unsigned)(K * es), slice, n_blk);
+            for (int r0 = 0; r0 < n; r0 += 16) {
+                const int rows = min(16, n - r0);
+                const int out_row = s_row[r0 + min(m, 15)];
+                if (r0 == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(1)" ::: "memory");   // (the store of the tile before)
+                if (works) {
+                    f32x4_t acc[MT];
+#pragma unroll
+                    for (int j = 0; j < MT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                    few_stage_product<MODE, MT, NB>(wreg, stage, n_blk, acc);
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the operands have been read)
+                    if (r0 + 16 < n) work_request<NB>(rsA, stage, s_row + r0 + 16, (unsigned)(K * es), slice, n_blk);
+                    few_stage_write<MT>(acc, rows, part + slice * (16 * ROW));
+                }
+                bar_lds();
+                const float* q = part + min(m, 15) * ROW + (tid % TPR) * PER;
+                const unsigned out = m < rows ? ((unsigned)out_row * (unsigned)N + col) * 4u : 0xFFFFFFF0u;
+                if constexpr (FWD) {
+                    f32x4_t v = bias;
+#pragma unroll
+                    for (int k = 0; k < REC_WAVES; ++k) {
+                        const f32x4_t o = *reinterpret_cast<const f32x4_t*>(q + k * (16 * ROW));
+                        v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3];
+                    }
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), rsC, out, 0, 17);
+                } else {
+                    float v = 0.f;
+#pragma unroll
+                    for (int k = 0; k < REC_WAVES; ++k) v += q[k * (16 * ROW)];
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsC, out, 0, 17);
+                }
+                bar_lds();   // (the partial sums have been read)
+            }
+        }
+        if (wave == 0) have = lane < PIPE_GROUPS ? ld_agent(w.sync + lane) : 0;   // (arrives while the stores complete)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        bar_lds();
+        if (tid == 0) __hip_atomic_fetch_add(w.sync + 16 + sel * pipe_done_stride(w.M) + c, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -716,15 +578,7 @@ __device__ __forceinline__ const A& pipe_args_in_place(const A&) {
 struct PipeFwdArgs {
     RecFwdArgs l0, l1;   // producer (layer 0) and consumer (layer 1)
     PipeWork work;
-    int tiles_n;         // column tiles per row tile of the workers' GEMM
 };
-// Which group's queue a worker serves first: group 0's chunks are short and its consumer must never wait long,
-// the last group has the most rows.
-__device__ __forceinline__ int pipe_worker_home(int xcc, int rank) {
-    const int wid = (xcc - 2 * PIPE_GROUPS) * REC_MAX_GROUP + rank;
-    const int k = wid & 7;
-    return k < 3 ? 0 : (k < 5 ? 1 : 2);
-}
 template <int MODE, int TPW, int KS, int NBW, bool STATIC>
 __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_pipe_fwd_kernel(PipeFwdArgs p_by_value) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -738,7 +592,7 @@ __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     if (stamp) tl[0] = wall_clock64();
 #endif
     if (xcc < 2 * PIPE_GROUPS) {
-        const PipeLink link = pipe_link_of(p.work.plan, p.work.sync, p.work.M, p.tiles_n, g);
+        const PipeLink link = pipe_link_of(p.work.plan, p.work.sync, p.work.M, p.work.G, g);
         const PieceSet ps = pipe_pieces_of(p.work.plan, g);
         if (xcc < PIPE_GROUPS) {
             if (rank < p.l0.G)
@@ -747,8 +601,9 @@ __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
             if (rank < p.l1.G)
                 rec_fwd_body<MODE, TPW, KS, NBW, STATIC, PIPE_CONSUMER>(p.l1, rank, ps, link.T, p.l1.flags + xcc * REC_MAX_GROUP, link, smem);
         }
-    } else if (xcc < PIPE_XCDS && rank < REC_MAX_GROUP) {
-        pipe_worker<MODE, false>(p.work, p.tiles_n, pipe_worker_home(xcc, rank), xcc - 2 * PIPE_GROUPS, smem);
+    } else if (xcc < PIPE_XCDS && rank < p.work.G) {
+        constexpr int WMT = REC_WAVES / KS * TPW;
+        pipe_worker<MODE, WMT, FewBlocks<MODE, WMT == 8>::fwd, true>(p.work, rank, xcc - 2 * PIPE_GROUPS, smem);
     }
 #ifdef VER_REC_PROF
     if (stamp) tl[1] = wall_clock64();
@@ -758,7 +613,6 @@ __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
 struct PipeBwdArgs {
     RecBwdArgs l1, l0;   // producer (layer 1) and consumer (layer 0)
     PipeWork work;
-    int tiles_n;
 };
 template <int MODE, int MT, int KS, int NI>
 __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_pipe_bwd_kernel(PipeBwdArgs p_by_value) {
@@ -773,7 +627,7 @@ __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     if (stamp) tl[0] = wall_clock64();
 #endif
     if (xcc < 2 * PIPE_GROUPS) {
-        const PipeLink link = pipe_link_of(p.work.plan, p.work.sync, p.work.M, p.tiles_n, g);
+        const PipeLink link = pipe_link_of(p.work.plan, p.work.sync, p.work.M, p.work.G, g);
         const PieceSet ps = pipe_pieces_of(p.work.plan, g);
         if (xcc < PIPE_GROUPS) {
             if (rank < p.l1.G)
@@ -782,8 +636,8 @@ __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
             if (rank < p.l0.G)
                 rec_bwd_body<MODE, MT, KS, NI, PIPE_CONSUMER>(p.l0, rank, ps, link.T, p.l0.flags + xcc * REC_MAX_GROUP, link, smem);
         }
-    } else if (xcc < PIPE_XCDS && rank < REC_MAX_GROUP) {
-        pipe_worker<MODE, true>(p.work, p.tiles_n, pipe_worker_home(xcc, rank), xcc - 2 * PIPE_GROUPS, smem);
+    } else if (xcc < PIPE_XCDS && rank < p.work.G) {
+        pipe_worker<MODE, MT, FewBlocks<MODE, MT == 2>::bwd, false>(p.work, rank, xcc - 2 * PIPE_GROUPS, smem);
     }
 #ifdef VER_REC_PROF
     if (stamp) tl[1] = wall_clock64();

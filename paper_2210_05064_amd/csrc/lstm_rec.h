@@ -333,28 +333,19 @@ __device__ __forceinline__ void mma_dispatch(const f32x4_t (&wreg)[NW], const ty
 // With two layers, both time loops run in the same launch on different XCDs.  Group g of the first
 // ("producer") layer and group g of the second ("consumer") layer run the same block of consecutive pieces
 // (lstm_pipe.h says how the blocks are chosen); a producer group publishes how far it is; workgroups on the
-// remaining XCDs ("workers") turn each finished chunk of a group's timesteps into the consumer group's input (a
-// GEMM tile at a time); a consumer group waits for the chunk that holds its next timestep.  Groups never wait
+// remaining XCDs ("workers") turn each finished chunk of a group's timesteps into the consumer group's input
+// (16 rows at a time); a consumer group waits for the chunk that holds its next timestep.  Groups never wait
 // for each other.  Everything that crosses XCDs is written through to memory (the L2s of different XCDs are not
 // coherent), completed (s_waitcnt) before it is announced, and announced/read with agent-scope atomics.
-constexpr int PIPE_BM = 128;         // rows per GEMM tile
-constexpr int PIPE_BN = 256;         // columns per GEMM tile
-constexpr int PIPE_CT_MAX = 32;      // at most this many timesteps per chunk
 enum { PIPE_NONE = 0, PIPE_PRODUCER = 1, PIPE_CONSUMER = 2 };
 // One group's view of the hand-over (producer and consumer groups with the same index run the same pieces).
 struct PipeLink {
     int* progress;   // the group's word: timesteps whose producer rows are complete in memory
-    int* done;       // the group's [chunks]: GEMM tiles finished per chunk
-    const int* rp;   // the group's [T + 1]: rows of the group in the timesteps before t
+    int* done;       // the group's [chunks]: workers that have finished the chunk
+    int need;        // workers of a chunk
     int ct;          // timesteps per chunk of the group: chunk c = timesteps [c*ct, (c+1)*ct)
-    int tiles_n;     // column tiles per row tile of the GEMM
     int T;           // the group's timesteps
 };
-// GEMM tiles that cover the group's rows of chunk c.
-__device__ __forceinline__ int pipe_chunk_tiles(const PipeLink& pl, int c) {
-    const int t0 = c * pl.ct, t1 = min(t0 + pl.ct, pl.T);
-    return (pl.rp[t1] - pl.rp[t0] + PIPE_BM - 1) / PIPE_BM * pl.tiles_n;
-}
 // Consumer: blocks until the workers have finished chunk c.  False if the wait was abandoned.
 __device__ __forceinline__ bool pipe_wait_chunk(const PipeLink& pl, int c, int* err, long long* waited = nullptr) {
     __shared__ int s_ok2;
@@ -362,11 +353,10 @@ __device__ __forceinline__ bool pipe_wait_chunk(const PipeLink& pl, int c, int* 
 #ifdef VER_REC_PROF
         const long long w0 = wall_clock64();
 #endif
-        int have = ld_agent(&pl.done[c]);            // (in flight together with the two loads behind `need`)
-        const int need = pipe_chunk_tiles(pl, c);
+        int have = ld_agent(&pl.done[c]);
         long long spins = 0;
         bool alive = true;
-        while (have < need) {
+        while (have < pl.need) {
             have = ld_agent(&pl.done[c]);
             ++spins;
             if ((spins & 255) == 0 && (spins > REC_SPIN_LIMIT || ld_agent(err) != 0)) {
@@ -565,8 +555,8 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
         if (a.h0 && n < a.seq_cap) v = *reinterpret_cast<const f32x4_t*>(a.h0 + (size_t)n * H + j0 + u);
         st_row4<E>(hprev + (size_t)n * H + j0 + u, v[0], v[1], v[2], v[3]);
     }
-    // From timestep t0 on at most FewMax pieces of the group are alive: those timesteps run in the form of lstm_few.h.
-    const int t0 = n_seq > FewMax<MODE>::fwd ? grp_steps(a.batch_sizes, T, FewMax<MODE>::fwd * X + x) : 0;
+    // From timestep t0 on at most FEW_MAX pieces of the group are alive: those timesteps run in the form of lstm_few.h.
+    const int t0 = n_seq > FEW_MAX ? grp_steps(a.batch_sizes, T, FEW_MAX * X + x) : 0;
     unsigned char* ring = static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, H);
     few_clear_ring<MODE>(ring, H, j0, UH);
     rec_publish(flags, rank, 1);
@@ -840,10 +830,10 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& a, int rank, cons
     float db[4] = {0.f, 0.f, 0.f, 0.f};
     int c_wait = T > 0 ? (T - 1) / pl.ct : 0;   // consumer: the chunk of the timestep it runs next
     if (PIPE == PIPE_CONSUMER && T > 0 && !pipe_wait_chunk(pl, c_wait, a.err, REC_PROF_CHUNK_ACC(a, rank, ps))) return;
-    // Timesteps >= t_few have at most FewMax alive pieces and run in the form of lstm_few.h (flag value 1: the
+    // Timesteps >= t_few have at most FEW_MAX alive pieces and run in the form of lstm_few.h (flag value 1: the
     // workgroup has emptied its words of the exchange ring).
     const int n_seq = grp_count(a.info[0], ps);
-    const int t_few = n_seq > FewMax<MODE>::bwd ? grp_steps(a.batch_sizes, T, FewMax<MODE>::bwd * X + x) : 0;
+    const int t_few = n_seq > FEW_MAX ? grp_steps(a.batch_sizes, T, FEW_MAX * X + x) : 0;
     unsigned char* ring = static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, K);
     float dh_few = 0.f;
     if (t_few < T) {
