@@ -97,6 +97,11 @@ __device__ __forceinline__ void few_swap32(float& a, float& b) {   // upper half
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
 }
+// A use of registers whose loads are known to have completed (the wait of a poll is written out, which the compiler does
+// not see): without it the first real use, in the middle of a timestep, waits for everything requested since.
+__device__ __forceinline__ void few_touch(f32x4_t& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void few_touch(float& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void few_touch(int& v) { asm volatile("" : "+v"(v)); }
 // A word to publish: never FEW_EMPTY (only a pair of NaNs, or an fp32 NaN, has these bits; it stays NaN).
 __device__ __forceinline__ unsigned few_word(unsigned v) { return v == FEW_EMPTY ? FEW_EMPTY - 1 : v; }
 
@@ -414,6 +419,7 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
     auto step = [&](f32x4_t& z, f32x4_t& z_next) -> bool {
         const int bs = grp_count(s.bs_a, ps), bs_next = t + 1 < T ? grp_count(s.bs_b, ps) : 0;
         const int base_next = s.base + s.bs_a;
+        s.win.advance(t + 2);
         if (PIPE == PIPE_CONSUMER && t + 1 < T && t + 1 == s.c_wait * pl.ct) {
             if (!s.ready && !pipe_wait_chunk(pl, s.c_wait, a.err)) return false;
             ++s.c_wait;
@@ -440,9 +446,11 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
             else ok = few_read<L>(rows, off, piece < bs && blk < s.n_blk, true, raw, a.err);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (also: this wave's stores of two timesteps ago have completed)
+        few_touch(z);
+        few_touch(s.win.cur);
+        few_touch(s.win.other);
         if (!ok) *s.fail = 1;
         const int bs_c = s.win.at(t + 2);
-        s.win.advance(t + 3);
         // off the critical path: results of the timestep before, the input projection of the next one
         if (m < bs_next)
             z_next = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs_g, (unsigned)((m * X + x) * H + j0 + u) * 16u,
@@ -467,18 +475,19 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
         }
         if (look && tid == REC_THREADS - 1) s.fail[1] = have;
         bar_lds();
-        if (*s.fail) return false;
+        const int failed = *s.fail;   // (looked at after the publication: its read is not waited for by itself)
         if (look) s.ready = s.fail[1] >= pl.need;
         // Every workgroup has published the rows of timestep t-1, which it did after its stores for timestep t-3 had
         // completed (they are issued in timestep t-2 and waited for in timestep t-1).
         if (PIPE == PIPE_PRODUCER && rank == 0 && tid == REC_THREADS - 1 && t - 2 > s.t0) st_agent(pl.progress, t - 2);
         if (m < bs) {
-            f32x4_t q = z;
+            f32x4_t q = z, o[REC_WAVES];
             const float* p = part + m * ROW + u * 4;
 #pragma unroll
+            for (int k = 0; k < REC_WAVES; ++k) o[k] = *reinterpret_cast<const f32x4_t*>(p + k * (PP * ROW));
+#pragma unroll
             for (int k = 0; k < REC_WAVES; ++k) {
-                const f32x4_t o = *reinterpret_cast<const f32x4_t*>(p + k * (PP * ROW));
-                q[0] += o[0]; q[1] += o[1]; q[2] += o[2]; q[3] += o[3];
+                q[0] += o[k][0]; q[1] += o[k][1]; q[2] += o[k][2]; q[3] += o[k][3];
             }
             const float gi = sigmoidf_(q[0]), gf = sigmoidf_(q[1]), gg = tanhf_(q[2]), go = sigmoidf_(q[3]);
             s.c = gf * s.c + gi * gg;
@@ -497,6 +506,7 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
                 __builtin_amdgcn_raw_buffer_store_b32(FEW_EMPTY, rs_ring, w_off, (unsigned)((t + 2) & (FEW_RING - 1)) * slot, 0);
             }
         }
+        if (failed) return false;
         if (STAGED) bar_lds();   // (one buffer of partial sums: it has been read)
         s.base_prev = s.base;
         s.base = base_next;
@@ -652,7 +662,9 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
         else __builtin_amdgcn_raw_buffer_store_b128(v, rs, off, so, decltype(aux)::value);
     };
 
-    auto step = [&](FewSaved& sv) -> bool {
+    // sv: what the forward pass saved for timestep t; other: for timestep t - 1, requested a timestep ago
+    auto step = [&](FewSaved& sv, FewSaved& other) -> bool {
+        s.win.advance(t - 3);
         const int bs = grp_count(s.bs_t, ps), bs_up = t + 1 < T ? grp_count(s.bs_up, ps) : 0;
         wv_t word;
 #pragma unroll
@@ -697,9 +709,14 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
             else ok = few_read<L>(src, off, piece < bs && blk < s.n_blk, true, raw, a.err);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (also: this wave's dz rows of timestep t+1 have completed)
+        few_touch(other.g);
+        few_touch(other.c_prev);
+        few_touch(other.dh_above);
+        few_touch(other.c);
+        few_touch(s.win.cur);
+        few_touch(s.win.other);
         if (!ok) *s.fail = 1;
         const int bs_m3 = s.win.at(t - 3);
-        s.win.advance(t - 4);
         // off the critical path: the dz rows of this timestep, the saved activations of timestep t-2
         if (m < bs) store(word, rs_dz, (unsigned)(n * K + j * 4) * es, so_dz, FewIdx<PIPE == PIPE_PRODUCER ? 17 : 0>{});
         if (t >= 2) {
@@ -725,19 +742,22 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
         }
         if (look && tid == REC_THREADS - 1) s.fail[1] = have;
         bar_lds();
-        if (*s.fail) return false;
+        const int failed = *s.fail;
         if (look) s.ready = s.fail[1] >= pl.need;
         // Every workgroup has published the rows of timestep t, which it did after its dz rows of timestep t+2 had
         // completed (they are stored in that timestep and waited for in timestep t+1).
         if (PIPE == PIPE_PRODUCER && rank == 0 && tid == REC_THREADS - 1 && t + 2 < T) st_agent(pl.progress, T - (t + 2));
         if (m < bs) {
-            store(wv_t(FEW_EMPTY), rs_ring, w_off, (unsigned)((t + 1) & (FEW_RING - 1)) * slot, FewIdx<0>{});
-            float q = 0.f;
+            float q = 0.f, o[REC_WAVES];
             const float* p = part + m * ROW + u;
 #pragma unroll
-            for (int k = 0; k < REC_WAVES; ++k) q += p[k * (PP * ROW)];
+            for (int k = 0; k < REC_WAVES; ++k) o[k] = p[k * (PP * ROW)];
+#pragma unroll
+            for (int k = 0; k < REC_WAVES; ++k) q += o[k];
             s.dh = q;
+            store(wv_t(FEW_EMPTY), rs_ring, w_off, (unsigned)((t + 1) & (FEW_RING - 1)) * slot, FewIdx<0>{});
         }
+        if (failed) return false;
         if (STAGED) bar_lds();   // (one buffer of partial sums: it has been read)
         s.base -= s.bs_m1;
         s.bs_up = s.bs_t;
@@ -748,14 +768,14 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
         return true;
     };
     while (t >= t_stop && grp_count(s.bs_t, ps) <= up_to) {
-        if (!step(s.sv)) return false;
+        if (!step(s.sv, s.sv2)) return false;
         if (!(t >= t_stop && grp_count(s.bs_t, ps) <= up_to)) {
             const FewSaved o = s.sv;
             s.sv = s.sv2;
             s.sv2 = o;
             break;
         }
-        if (!step(s.sv2)) return false;
+        if (!step(s.sv2, s.sv)) return false;
     }
     return true;
 }

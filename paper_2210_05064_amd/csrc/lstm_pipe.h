@@ -58,7 +58,7 @@ struct PlanCost {
 };
 // Timesteps per chunk by the pieces of the group: a chunk is handed on when it is complete, so the consumer starts and
 // ends that much later than the producer; it costs a worker about 4 us beside the product of its rows.
-constexpr int PLAN_CT_FEW = 4, PLAN_CT_MID = 4, PLAN_CT_MANY = 2;   // up to 4, up to 16, more pieces
+constexpr int PLAN_CT_FEW = 8, PLAN_CT_MID = 8, PLAN_CT_MANY = 2;   // up to 4, up to 16, more pieces
 // Fitted by hand to the time per timestep of launches over equally long pieces, 1 .. 64 per group (us):
 //   pieces               1     2     4     8    16    32    64
 //   bf16 H=1024 fwd   1.43  1.35  1.40  1.86  2.04   5.1  12.5      bwd  1.65  1.83  2.2   2.26  3.0   9.1  18
