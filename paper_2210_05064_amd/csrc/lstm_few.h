@@ -346,6 +346,7 @@ struct FewFwd {
     int t0;                      // first timestep of this form
     int c_wait;                  // consumer: the chunk it has to wait for next
     bool ready;                  // that chunk has been seen finished
+    int have;                    // its counter, requested a timestep ago
     int n_slices, slice, n_blk;  // slices with work, this wave's slice, its operand blocks
     float c;                     // this thread's cell state
     f32x4_t z;                   // its input projection of timestep t
@@ -449,16 +450,22 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
         few_touch(z);
         few_touch(s.win.cur);
         few_touch(s.win.other);
+        if (PIPE == PIPE_CONSUMER) few_touch(s.have);
         if (!ok) *s.fail = 1;
         const int bs_c = s.win.at(t + 2);
         // off the critical path: results of the timestep before, the input projection of the next one
         if (m < bs_next)
             z_next = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs_g, (unsigned)((m * X + x) * H + j0 + u) * 16u,
                                                                                         (unsigned)base_next * (unsigned)H * 16u, 0));
-        // a look at the chunk that the next timestep asks for: usually finished, which saves that wait its round trip
+        // A look at the chunk that the next timestep asks for: usually finished, which saves that wait its round trip.  Its
+        // counter was requested a timestep earlier (a load waited for in the timestep that requests it, under a condition,
+        // makes the compiler wait in every timestep).
         const bool look = PIPE == PIPE_CONSUMER && t + 2 < T && t + 2 == s.c_wait * pl.ct;
-        int have = 0;
-        if (look && tid == REC_THREADS - 1) have = ld_agent(&pl.done[s.c_wait]);
+        if (PIPE == PIPE_CONSUMER) {
+            if (look && tid == REC_THREADS - 1) s.fail[1] = s.have;
+            if (look) s.have = 0;
+            if (t + 3 < T && t + 3 == s.c_wait * pl.ct && tid == REC_THREADS - 1) s.have = ld_agent(&pl.done[s.c_wait]);
+        }
         if (t > s.t0) few_fwd_store<MODE, MT, NB, PIPE>(s, a, ps, j0, grp_count(s.base - s.base_prev, ps), s.base, bs);
         float* part = s.part + (STAGED ? 0 : (t & 1) * (REC_WAVES * PP * ROW));
         if (polls) {
@@ -473,7 +480,6 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
                 few_write<MODE, MT, P>(acc, bs, part + s.slice * (PP * ROW));
             }
         }
-        if (look && tid == REC_THREADS - 1) s.fail[1] = have;
         bar_lds();
         const int failed = *s.fail;   // (looked at after the publication: its read is not waited for by itself)
         if (look) s.ready = s.fail[1] >= pl.need;
@@ -564,6 +570,7 @@ __device__ __forceinline__ bool few_fwd(const RecFwdArgs& a, const PieceSet& ps,
     s.t0 = t0;
     s.c_wait = c_wait;
     s.ready = false;
+    s.have = 0;
     s.win.init(a.batch_sizes, T, t0);
     s.bs_a = s.win.at(t0);
     s.bs_b = s.win.at(t0 + 1);
@@ -601,6 +608,7 @@ struct FewBwd {
     int base;                        // first row of timestep t
     int c_wait;                      // consumer: the lowest chunk it has waited for
     bool ready;                      // the chunk below has been seen finished
+    int have;                        // its counter, requested a timestep ago
     int n_slices, slice, n_blk;
     FewSaved sv, sv2;                // what the forward pass saved for timesteps t and t - 1
     float dh, dc, c;                 // carried gradients, cell state of timestep t
@@ -715,6 +723,7 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
         few_touch(other.c);
         few_touch(s.win.cur);
         few_touch(s.win.other);
+        if (PIPE == PIPE_CONSUMER) few_touch(s.have);
         if (!ok) *s.fail = 1;
         const int bs_m3 = s.win.at(t - 3);
         // off the critical path: the dz rows of this timestep, the saved activations of timestep t-2
@@ -725,8 +734,11 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
         }
         // a look at the chunk that the next timestep asks for, see the forward loop
         const bool look = PIPE == PIPE_CONSUMER && t >= 3 && t - 3 == s.c_wait * pl.ct - 1;
-        int have = 0;
-        if (look && tid == REC_THREADS - 1) have = ld_agent(&pl.done[s.c_wait - 1]);
+        if (PIPE == PIPE_CONSUMER) {
+            if (look && tid == REC_THREADS - 1) s.fail[1] = s.have;
+            if (look) s.have = 0;
+            if (t >= 4 && t - 4 == s.c_wait * pl.ct - 1 && tid == REC_THREADS - 1) s.have = ld_agent(&pl.done[s.c_wait - 1]);
+        }
         float* part = s.part + (STAGED ? 0 : (t & 1) * (REC_WAVES * PP * ROW));
         if (polls) {
             f32x4_t acc[MT];
@@ -740,7 +752,6 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
                 few_write<MODE, MT, P>(acc, bs, part + s.slice * (PP * ROW));
             }
         }
-        if (look && tid == REC_THREADS - 1) s.fail[1] = have;
         bar_lds();
         const int failed = *s.fail;
         if (look) s.ready = s.fail[1] >= pl.need;
@@ -813,6 +824,7 @@ __device__ __forceinline__ bool few_bwd(const RecBwdArgs& a, const PieceSet& ps,
     for (int i = 0; i < MT * NB; ++i) asm volatile("" : "+v"(s.w[i]));
     s.c_wait = c_wait;
     s.ready = false;
+    s.have = 0;
     s.win.init(a.batch_sizes, T, T - 1);
     s.bs_up = 0;
     s.bs_t = s.win.at(T - 1);
