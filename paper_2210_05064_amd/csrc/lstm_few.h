@@ -27,12 +27,13 @@
 // the MFMAs of one 16-row tile at H = 1024 (1.7 us in fp32 at H = 512), then the partial sums through LDS and the cell
 // update.  Microseconds per timestep (one layer), flag protocol -> this form:
 //     alive pieces                     1             2             4             8             16
-//     bf16, H = 1024   forward    2.36 -> 1.43  2.36 -> 1.35  2.44 -> 1.40  2.69 -> 1.86  3.31 -> 2.04
-//                      backward   2.23 -> 1.65  3.11 -> 1.83  3.26 -> 2.22  3.79 -> 2.26  4.80 -> 2.99
-//     fp32, H = 512    forward    2.20 -> 1.24  2.73 -> 1.54  3.75 -> 2.37  3.86 -> 3.16  4.38 -> 3.27
-//                      backward   2.78 -> 1.37  3.65 -> 2.01  4.30 -> 3.29  4.69 -> 3.72  5.70 -> 4.45
+//     bf16, H = 1024   forward    2.36 -> 1.31  2.36 -> 1.28  2.44 -> 1.32  2.69 -> 1.91  3.31 -> 2.04
+//                      backward   2.23 -> 1.56  3.11 -> 1.85  3.26 -> 2.05  3.79 -> 2.32  4.80 -> 3.09
+//     fp32, H = 512    forward    2.20 -> 1.16  2.73 -> 1.47  3.75 -> 2.23  3.86 -> 3.00  4.38 -> 3.26
+//                      backward   2.78 -> 1.37  3.65 -> 2.03  4.30 -> 3.31  4.69 -> 3.73  5.70 -> 4.58
 // What mattered after the exchange itself: four neighbouring lanes on contiguous memory (16 pieces forward 2.74 -> 2.04 us,
-// backward 5.25 -> 2.99), and reading the eight partial sums without a branch per share (0.2 us per timestep).
+// backward 5.25 -> 2.99), reading the eight partial sums without a branch per share (0.2 us per timestep), and no wait
+// for a prefetch before the next poll (0.1 us).
 #pragma once
 
 namespace ver {
