@@ -11,6 +11,13 @@
 //                      K sequences / n_seq pieces, far below a microsecond of
 //                      HBM time, so one CU with LDS-staged prefix sums and
 //                      wave ballots beats a multi-launch device-wide version.
+//                      Bound by dependent loads and, from about a thousand
+//                      sequences on, by the K^2 comparisons of the ranking.
+//                      512 / 8192 / 32768 / 65536 steps with about 10 / 80 /
+//                      420 / 3800 sequences: 8.5 / 16.4 / 32 / 346 us (9.6 /
+//                      22 / 87 / 1504 with up to 8 loads in flight, a key
+//                      fetched where its sequence was found, and one key and
+//                      three comparisons per LDS read).
 //   pack_gather_kernel a workgroup per 4 or 8 packed rows: resolves their flat steps
 //                      (one search in t_off per workgroup) and copies the rows'
 //                      fields with 16-byte accesses.  This is the HBM-bound part:
@@ -61,6 +68,77 @@ __device__ __forceinline__ int block_scan_incl(int v, int* s_w, int* total) {
     return v + s_w[wave];
 }
 
+// How many of the n keys in LDS come before this thread's element (key `my`, index `at` in the tile, which may lie outside
+// it): smaller keys, and equal ones with a smaller index.  The indices of a wave's elements start at `first`, a
+// multiple of 64, so what lies before or behind all of them needs one comparison per key.  Keys beyond n up to the
+// next multiple of 4 must be ~0: they lie behind every element and count for none.
+__device__ __forceinline__ int rank_in_tile(const uint32_t* s_key, int n, int first, int at, uint32_t my) {
+    const uint4* key4 = reinterpret_cast<const uint4*>(s_key);
+    const int n4 = (n + 3) / 4;
+    first = __builtin_amdgcn_readfirstlane(first);
+    const int a = min(max(first, 0) / 4, n4), b = min(max(first + VER_WAVE, 0) / 4, n4);
+    int rank = 0;
+    for (int q = 0; q < a; ++q) {
+        const uint4 o = key4[q];
+        rank += (o.x <= my) + (o.y <= my) + (o.z <= my) + (o.w <= my);
+    }
+    for (int q = a; q < b; ++q) {
+        const uint4 o = key4[q];
+        const int i = 4 * q;
+        rank += (o.x < my || (o.x == my && i < at)) + (o.y < my || (o.y == my && i + 1 < at)) +
+                (o.z < my || (o.z == my && i + 2 < at)) + (o.w < my || (o.w == my && i + 3 < at));
+    }
+    for (int q = b; q < n4; ++q) {
+        const uint4 o = key4[q];
+        rank += (o.x < my) + (o.y < my) + (o.z < my) + (o.w < my);
+    }
+    return rank;
+}
+
+// The passes over the steps are bound by the latency of their loads: IDX_LOADS of them in flight per thread, and as many
+// as there are steps per thread (2) where the 16 would mostly be masked off.
+constexpr int IDX_LOADS = 16;
+constexpr int IDX_FEW_STEPS = 2 * IDX_THREADS;
+
+// flags[k] = 3 where the step before k ends an episode, else 0.
+template <int L>
+__device__ __forceinline__ void mark_episode_starts(const uint8_t* __restrict__ dones, int S, uint8_t* __restrict__ flags) {
+    for (unsigned k0 = threadIdx.x; k0 < (unsigned)S; k0 += L * IDX_THREADS) {
+        unsigned char d[L];
+#pragma unroll
+        for (int u = 0; u < L; ++u) {
+            const unsigned k = k0 + u * IDX_THREADS;   // (unsigned: does not wrap for any S)
+            d[u] = dones[k > 0 && k < (unsigned)S ? k - 1 : 0];   // (the value of a step outside 1 .. S-1 is not used)
+        }
+#pragma unroll
+        for (int u = 0; u < L; ++u) {
+            const unsigned k = k0 + u * IDX_THREADS;
+            if (k < (unsigned)S) flags[k] = (k > 0 && d[u]) ? 3 : 0;
+        }
+    }
+}
+
+// Calls f(i, k) for the wave's i-th sequence start k in steps c_lo .. c_hi-1 and returns their number.
+template <int L, class F>
+__device__ __forceinline__ int visit_starts(const uint8_t* flags, int c_lo, int c_hi, F f) {
+    const int lane = threadIdx.x & (VER_WAVE - 1);
+    int base = 0;
+    for (unsigned k0 = c_lo; k0 < (unsigned)c_hi; k0 += L * VER_WAVE) {
+        unsigned char v[L];
+#pragma unroll
+        for (int u = 0; u < L; ++u) v[u] = flags[min(k0 + u * VER_WAVE + lane, (unsigned)c_hi - 1u)];
+#pragma unroll
+        for (int u = 0; u < L; ++u) {
+            const unsigned k = k0 + u * VER_WAVE + lane;
+            const bool st = k < (unsigned)c_hi && (v[u] & 1) != 0;
+            const unsigned long long mask = __ballot(st);
+            if (st) f(base + __popcll(mask & ((1ull << lane) - 1ull)), (int)k);
+            base += __popcll(mask);
+        }
+    }
+    return base;
+}
+
 constexpr int IDX_SL_CACHE = 4096;   // sorted piece lengths kept in LDS for the per-timestep counts
 
 // One minibatch's part of an index launch: workgroup i of the launch builds the integer outputs of job i.  The
@@ -97,8 +175,7 @@ __global__ __launch_bounds__(IDX_THREADS) void pack_index_kernel(
     int32_t* __restrict__ t_off = job.t_off;
     __shared__ int s_w[IDX_WAVES + 1];
     __shared__ int s_cnt[IDX_WAVES + 1];
-    __shared__ uint32_t s_key[IDX_THREADS];
-    __shared__ int s_len[IDX_THREADS];
+    __shared__ __align__(16) uint32_t s_key[IDX_THREADS];
     __shared__ int s_misc[4];
     const int tid = threadIdx.x;
     const int lane = tid & (VER_WAVE - 1), wave = tid / VER_WAVE;
@@ -106,7 +183,9 @@ __global__ __launch_bounds__(IDX_THREADS) void pack_index_kernel(
     const int lo = b * M, hi = lo + M;
 
     // 1. start flags: the step after an episode end ...
-    for (int k = tid; k < S; k += IDX_THREADS) ws.flags[k] = (k > 0 && dones[k - 1]) ? 3 : 0;
+    const bool few_steps = S <= IDX_FEW_STEPS;
+    if (few_steps) mark_episode_starts<IDX_FEW_STEPS / IDX_THREADS>(dones, S, ws.flags);
+    else mark_episode_starts<IDX_LOADS>(dones, S, ws.flags);
     __syncthreads();
     // ... and the first step of every non-empty stretch (whose episode flag comes from the caller)
     for (int i = tid; i < N; i += IDX_THREADS) {
@@ -119,17 +198,8 @@ __global__ __launch_bounds__(IDX_THREADS) void pack_index_kernel(
     // 2. compaction: each wave owns a contiguous chunk of steps; count with ballots, then place.
     const int chunk = ((S + IDX_WAVES - 1) / IDX_WAVES + VER_WAVE - 1) / VER_WAVE * VER_WAVE;
     const int c_lo = min(S, wave * chunk), c_hi = min(S, c_lo + chunk);
-    int cnt = 0;
-    for (int k0 = c_lo; k0 < c_hi; k0 += 8 * VER_WAVE) {   // 8 loads in flight per lane
-        unsigned char f[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int k = k0 + u * VER_WAVE + lane;
-            f[u] = k < c_hi ? ws.flags[k] : 0;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) cnt += __popcll(__ballot((f[u] & 1) != 0));
-    }
+    const int cnt = few_steps ? visit_starts<IDX_FEW_STEPS / IDX_THREADS>(ws.flags, c_lo, c_hi, [](int, int) {})
+                              : visit_starts<IDX_LOADS>(ws.flags, c_lo, c_hi, [](int, int) {});
     if (lane == 0) s_cnt[wave] = cnt;
     __syncthreads();
     if (tid == 0) {
@@ -143,29 +213,19 @@ __global__ __launch_bounds__(IDX_THREADS) void pack_index_kernel(
     }
     __syncthreads();
     const int K = s_cnt[IDX_WAVES];
-    int base = s_cnt[wave];
-    for (int k0 = c_lo; k0 < c_hi; k0 += 8 * VER_WAVE) {
-        unsigned char f[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int k = k0 + u * VER_WAVE + lane;
-            f[u] = k < c_hi ? ws.flags[k] : 0;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int k = k0 + u * VER_WAVE + lane;
-            const bool st = (f[u] & 1) != 0;
-            const unsigned long long mask = __ballot(st);
-            if (st) {
-                const int id = base + __popcll(mask & ((1ull << lane) - 1ull));
-                ws.sf[id] = k;
-                ws.skey[id] = seq_key[k];
-            }
-            base += __popcll(mask);
-        }
+    const int base = s_cnt[wave];
+    const auto place = [&](int at, int k) { ws.sf[base + at] = k; };
+    if (few_steps) visit_starts<IDX_FEW_STEPS / IDX_THREADS>(ws.flags, c_lo, c_hi, place);
+    else visit_starts<IDX_LOADS>(ws.flags, c_lo, c_hi, place);
+    __syncthreads();
+    // (the keys are fetched here, a sequence per thread: inside the loop above every group of 64 steps with a start
+    // in it would wait for its own fetch)
+    for (int s = tid; s < K; s += IDX_THREADS) {
+        const int k = ws.sf[s];
+        ws.sl[s] = ((s + 1 < K) ? ws.sf[s + 1] : S) - k;
+        ws.skey[s] = seq_key[k];
     }
     __syncthreads();
-    for (int s = tid; s < K; s += IDX_THREADS) ws.sl[s] = ((s + 1 < K) ? ws.sf[s + 1] : S) - ws.sf[s];
 
     // 3. random order: rank of (key, id) by counting, keys tiled through LDS.
     for (int s0 = 0; s0 < K; s0 += IDX_THREADS) {
@@ -174,14 +234,9 @@ __global__ __launch_bounds__(IDX_THREADS) void pack_index_kernel(
         int rank = 0;
         for (int q0 = 0; q0 < K; q0 += IDX_THREADS) {
             __syncthreads();
-            if (q0 + tid < K) s_key[tid] = ws.skey[q0 + tid];
+            s_key[tid] = q0 + tid < K ? ws.skey[q0 + tid] : ~0u;
             __syncthreads();
-            const int n = min(IDX_THREADS, K - q0);
-            if (s < K)
-                for (int q = 0; q < n; ++q) {
-                    const uint32_t other = s_key[q];
-                    rank += (other < my || (other == my && q0 + q < s)) ? 1 : 0;
-                }
+            rank += rank_in_tile(s_key, min(IDX_THREADS, K - q0), s0 + wave * VER_WAVE - q0, s - q0, my);
         }
         if (s < K) ws.order[rank] = s;
     }
@@ -224,18 +279,13 @@ __global__ __launch_bounds__(IDX_THREADS) void pack_index_kernel(
     // 6. longest first, ties in stream order: rank by counting, lengths tiled through LDS.
     for (int j0 = 0; j0 < n_seq; j0 += IDX_THREADS) {
         const int j = j0 + tid;
-        const int my = (j < n_seq) ? ws.plen[j] : 0;
+        const int my = (j < n_seq) ? ws.plen[j] : 0;   // (complemented for the ranking: the longest is the smallest)
         int rank = 0;
         for (int q0 = 0; q0 < n_seq; q0 += IDX_THREADS) {
             __syncthreads();
-            if (q0 + tid < n_seq) s_len[tid] = ws.plen[q0 + tid];
+            s_key[tid] = q0 + tid < n_seq ? ~(uint32_t)ws.plen[q0 + tid] : ~0u;
             __syncthreads();
-            const int n = min(IDX_THREADS, n_seq - q0);
-            if (j < n_seq)
-                for (int q = 0; q < n; ++q) {
-                    const int other = s_len[q];
-                    rank += (other > my || (other == my && q0 + q < j)) ? 1 : 0;
-                }
+            rank += rank_in_tile(s_key, min(IDX_THREADS, n_seq - q0), j0 + wave * VER_WAVE - q0, j - q0, ~(uint32_t)my);
         }
         if (j < n_seq) {
             seq_first[rank] = ws.pf[j];

@@ -88,6 +88,20 @@ def test_ragged_edge_cases(ver, seed, n_envs, max_len, p_done, B):
         compare_meta(out.meta(), opack.pack_minibatch(dones, off, key, B, b, eps))
 
 
+@pytest.mark.parametrize("K", [1, 3, 63, 64, 65, 1023, 1024, 1025, 2113])
+def test_ranking_at_tile_edges(ver, K):
+    """Sequences counted at the edges of a wave and of a tile of 1024 keys, with ties and with keys of all ones (the
+    value that fills up a tile); the lengths have ties as well."""
+    rng = np.random.default_rng(K)
+    L = rng.integers(1, 4, size=K)
+    off = np.concatenate([[0], np.cumsum(L)]).astype(np.int32)
+    S = int(off[-1])
+    dones = np.zeros(S, np.uint8)
+    key = rng.choice(np.array([0, 1, 0x80000000, 0xffffffff], np.uint32), size=S)
+    out = run_pack(ver, dones, off, key, 1, 0)
+    compare_meta(out.meta(), opack.pack_minibatch(dones, off, key, 1, 0))
+
+
 @pytest.mark.parametrize("budget,n_envs", [(512, 8), (1 << 17, 700)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_gathered_fields(ver, bf16, budget, n_envs):
