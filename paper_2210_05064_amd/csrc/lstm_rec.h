@@ -146,7 +146,8 @@ struct PieceSet {
 __device__ __forceinline__ int grp_count(int bs, const PieceSet& ps) {
     return bs > ps.x ? min((bs - ps.x + ps.X - 1) / ps.X, ps.cap) : 0;
 }
-// Timesteps at which piece x is alive: batch sizes never grow, so that is how many exceed x.
+// Timesteps at which piece x is alive: batch sizes never grow, so that is how many exceed x.  A workgroup may call it
+// again: the last barrier keeps the word from being cleared for the next count before every wave has read this one.
 __device__ __forceinline__ int grp_steps(const int32_t* batch_sizes, int T, int x) {
     __shared__ int s_T;
     if (threadIdx.x == 0) s_T = 0;
@@ -155,7 +156,9 @@ __device__ __forceinline__ int grp_steps(const int32_t* batch_sizes, int T, int 
     for (int t = threadIdx.x; t < T; t += blockDim.x) cnt += batch_sizes[t] > x ? 1 : 0;
     if (cnt) atomicAdd(&s_T, cnt);
     __syncthreads();
-    return s_T;
+    const int steps = s_T;
+    __syncthreads();
+    return steps;
 }
 
 // ---- exchange through the XCD's L2 --------------------------------------------------------------------
