@@ -38,7 +38,7 @@ namespace ver {
 
 constexpr int PIPE_GROUPS = 3;       // groups (XCDs) per layer
 constexpr int PIPE_XCDS = 8;         // XCDs of the chip: those beyond the two layers' groups are workers
-static_assert(PIPE_XCDS - 2 * PIPE_GROUPS == 2, "the chunks alternate between two worker XCDs");
+static_assert(PIPE_XCDS - 2 * PIPE_GROUPS == 2, "two worker XCDs");
 
 // The plan of a launch (ints in global memory, written by lstm_pipe_plan_kernel):
 constexpr int PLAN_KB = 0;           // [PIPE_GROUPS + 1] first piece of every group's block, then the number of pieces
@@ -356,12 +356,26 @@ __global__ __launch_bounds__(REC_THREADS) void lstm_proj_dma_kernel(ProjWork w, 
     proj_tile_dma(w, rt * PIPE_BM, min(w.M, (rt + 1) * PIPE_BM), ct * PIPE_BN, proj_smem);
 }
 
+// How the chunks of a group of `cap` pieces are dealt to the workers.  G workers hold the weights once (a team); both XCDs
+// together hold WORK_COUNT / G teams, which form sets: the chunks go to the sets in turn, and the teams of a set share the
+// rows of a chunk.  Up to 16 pieces a chunk is a handful of tiles of 16 rows and every team is a set of its own; with
+// more, an even number of teams is two sets, so that a chunk of hundreds of rows does not wait for a single team.
+// A team that has no place in a set (team >= sets * parts) takes no chunk.
+constexpr int WORK_COUNT = (PIPE_XCDS - 2 * PIPE_GROUPS) * REC_MAX_GROUP;
+struct WorkDeal {
+    int sets, parts;
+};
+inline __host__ __device__ WorkDeal work_deal(int G, int cap) {
+    const int teams = WORK_COUNT / G;
+    return cap > 16 && teams % 2 == 0 ? WorkDeal{2, teams / 2} : WorkDeal{teams, 1};
+}
+
 // One group's view of the hand-over words, from the plan.
-__device__ __forceinline__ PipeLink pipe_link_of(const int* plan, int* sync, int M, int need, int g) {
+__device__ __forceinline__ PipeLink pipe_link_of(const int* plan, int* sync, int M, int G, int g) {
     PipeLink pl;
     pl.progress = sync + g;
     pl.done = sync + 16 + g * pipe_done_stride(M);
-    pl.need = need;
+    pl.need = G * work_deal(G, plan[PLAN_KB + g + 1] - plan[PLAN_KB + g]).parts;
     pl.ct = plan[PLAN_CT + g];
     pl.T = plan[PLAN_T + g];
     return pl;
@@ -379,7 +393,8 @@ __device__ __forceinline__ PieceSet pipe_pieces_of(const int* plan, int g) {
 // and per chunk the round trips of progress word, rows and stores (about 4 us).  (128 x 256 tiles that streamed the
 // weights from L2 through LDS took 18 us forward and 54 us backward each, 14 and 38 us for a handful of rows: the
 // consumer started and ended that much later, and 32768 rows kept the two XCDs busy for 2.9 ms.)
-// The chunks of a group go to the two XCDs in turn.
+// A net of up to 320 units needs fewer than half of the 64 workers for its weights: the others hold them again (work_deal).
+// One team per XCD left 28 of 32 CUs idle at H = 64 and made the workers the bound of launches over hundreds of pieces.
 constexpr int WORK_LDS_T = 2047;   // timesteps whose row offsets are kept in LDS
 inline __host__ __device__ size_t work_lds_bytes(int cols, int nb) {
     return (size_t)few_part_floats(cols) * sizeof(float) + (size_t)REC_WAVES * few_stage_bytes(nb) + (WORK_LDS_T + 1) * sizeof(int);
@@ -400,12 +415,13 @@ __device__ __forceinline__ void work_request(__amdgpu_buffer_rsrc_t rs, unsigned
 
 // FWD: 16 * MT columns per worker, four of them (a unit's gates) per thread; else one column per thread.
 template <int MODE, int MT, int NB, bool FWD>
-__device__ __forceinline__ void pipe_worker(const PipeWork& w, int rank, int half, unsigned char* smem) {
+__device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned char* smem) {
     typedef typename RecGeom<MODE>::E E;
     constexpr int es = (int)sizeof(E), KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC;
     constexpr int COLS = 16 * MT, ROW = few_row(COLS), PER = FWD ? 4 : 1, TPR = COLS / PER;   // threads per row
     static_assert(16 * TPR <= REC_THREADS, "a thread per row and column group");
     constexpr bool DESCEND = !FWD;   // the backward consumer needs the last chunk first
+    const int team = id / w.G, rank = id % w.G;
     __shared__ int s_sel[2];
     __shared__ int s_row[REC_THREADS];
     float* part = reinterpret_cast<float*>(smem);
@@ -438,8 +454,10 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int rank, int hal
         T[g] = w.plan[PLAN_T + g];
         ct[g] = w.plan[PLAN_CT + g];
         const int n = (T[g] + ct[g] - 1) / ct[g];
-        // this XCD's first chunk of the group in the consumer's order
-        at[g] = DESCEND ? n - 1 - ((n - 1 + g + half) & 1) : ((g + half) & 1);
+        // this team's first chunk of the group in the consumer's order (none: behind the last)
+        const WorkDeal d = work_deal(w.G, cap[g]);
+        const int first = team < d.sets * d.parts ? (team / d.parts + g) % d.sets : n;
+        at[g] = DESCEND ? n - 1 - first : first;
         t_max = max(t_max, T[g]);
     }
     for (int t = tid; t <= min(t_max, WORK_LDS_T); t += REC_THREADS) s_toff[t] = w.t_off[t];
@@ -479,7 +497,7 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int rank, int hal
         for (int g = 0; g < PIPE_GROUPS; ++g)
             if (sel == g) {
                 g_lo = lo[g]; g_cap = cap[g]; g_T = T[g]; g_ct = ct[g]; c = at[g];
-                at[g] += DESCEND ? -2 : 2;
+                at[g] += DESCEND ? -work_deal(w.G, cap[g]).sets : work_deal(w.G, cap[g]).sets;
             }
         // The group's rows of the chunk in time order: lane k holds what is needed of its timestep k.
         const int t0 = c * g_ct, nt = min(g_ct, g_T - t0);
@@ -496,6 +514,9 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int rank, int hal
         const int total = __builtin_amdgcn_readlane(before, nt - 1);
         before -= cnt;
         const int row_k = off_k + g_lo - before;   // row of slot s of timestep k: row_k + s
+        // this team's share of the chunk: whole tiles
+        const int parts = work_deal(w.G, g_cap).parts, part_id = team % parts, tiles = (total + 15) / 16;
+        const int s_lo = tiles * part_id / parts * 16, s_hi = min(tiles * (part_id + 1) / parts * 16, total);
         auto row_of = [&](int s) {
             int k = 0;
             for (int j = 1; j < nt; ++j) k += s >= __builtin_amdgcn_readlane(before, j) ? 1 : 0;
@@ -507,8 +528,8 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int rank, int hal
         // range for rows that a tile does not have: a store that may or may not be there makes the wait for the loads
         // before it a wait for the store.)
         const bool works = slice < n_slices;
-        for (int b0 = 0; b0 < total; b0 += REC_THREADS) {
-            const int n = min(total - b0, REC_THREADS);
+        for (int b0 = s_lo; b0 < s_hi; b0 += REC_THREADS) {
+            const int n = min(s_hi - b0, REC_THREADS);
             s_row[tid] = row_of(min(b0 + tid, total - 1));
             bar_lds();
             if (works) work_request<NB>(rsA, stage, s_row, (unsigned)(K * es), slice, n_blk);
@@ -601,9 +622,9 @@ __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
             if (rank < p.l1.G)
                 rec_fwd_body<MODE, TPW, KS, NBW, STATIC, PIPE_CONSUMER>(p.l1, rank, ps, link.T, p.l1.flags + xcc * REC_MAX_GROUP, link, smem);
         }
-    } else if (xcc < PIPE_XCDS && rank < p.work.G) {
+    } else if (xcc < PIPE_XCDS && rank < REC_MAX_GROUP) {
         constexpr int WMT = REC_WAVES / KS * TPW;
-        pipe_worker<MODE, WMT, FewBlocks<MODE, WMT == 8>::fwd, true>(p.work, rank, xcc - 2 * PIPE_GROUPS, smem);
+        pipe_worker<MODE, WMT, FewBlocks<MODE, WMT == 8>::fwd, true>(p.work, (xcc - 2 * PIPE_GROUPS) * REC_MAX_GROUP + rank, smem);
     }
 #ifdef VER_REC_PROF
     if (stamp) tl[1] = wall_clock64();
@@ -636,8 +657,8 @@ __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
             if (rank < p.l0.G)
                 rec_bwd_body<MODE, MT, KS, NI, PIPE_CONSUMER>(p.l0, rank, ps, link.T, p.l0.flags + xcc * REC_MAX_GROUP, link, smem);
         }
-    } else if (xcc < PIPE_XCDS && rank < p.work.G) {
-        pipe_worker<MODE, MT, FewBlocks<MODE, MT == 2>::bwd, false>(p.work, rank, xcc - 2 * PIPE_GROUPS, smem);
+    } else if (xcc < PIPE_XCDS && rank < REC_MAX_GROUP) {
+        pipe_worker<MODE, MT, FewBlocks<MODE, MT == 2>::bwd, false>(p.work, (xcc - 2 * PIPE_GROUPS) * REC_MAX_GROUP + rank, smem);
     }
 #ifdef VER_REC_PROF
     if (stamp) tl[1] = wall_clock64();

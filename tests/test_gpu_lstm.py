@@ -244,3 +244,16 @@ def test_forms_of_the_time_loops(ver, compute, hidden, n_layers, n_envs):
                   p_done=0.01, minibatches=1, speed_sigma=0.8)
     _, meta = case(ver, w, seed=17 + hidden, compute=compute, x_bf16=bool(compute))
     assert meta["n_seq"] > 16 * (8 if n_layers == 1 else 3) and meta["batch_sizes"][-1] <= 8
+
+
+@pytest.mark.parametrize("compute", [0, 1])
+@pytest.mark.parametrize("hidden", [64, 128, 192, 256, 320, 576])
+def test_workers_hold_the_weights_several_times(ver, compute, hidden):
+    """Two-layer launch at widths whose W_ih1 fits the workers 16, 8, 5, 4 and 3 times: groups of about 40 pieces, whose
+    chunks several teams share (an even number of teams) or take in turn (5 and 3)."""
+    if compute == 0 and hidden > 512:
+        pytest.skip("fp32 holds its weights up to 512 units")
+    w = wl.scaled(wl.WORKLOADS["manip"], budget=1500, n_envs=100, n_layers=2, hidden=hidden, input_dim=12, p_done=0.01,
+                  minibatches=1, speed_sigma=0.6)
+    _, meta = case(ver, w, seed=60 + hidden, compute=compute, x_bf16=bool(compute))
+    assert meta["n_seq"] > 3 * 32
