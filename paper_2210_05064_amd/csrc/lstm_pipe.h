@@ -359,15 +359,15 @@ __global__ __launch_bounds__(REC_THREADS) void lstm_proj_dma_kernel(ProjWork w, 
 // How the chunks of a group of `cap` pieces are dealt to the workers.  G workers hold the weights once (a team); both XCDs
 // together hold WORK_COUNT / G teams, which form sets: the chunks go to the sets in turn, and the teams of a set share the
 // rows of a chunk.  Up to 16 pieces a chunk is a handful of tiles of 16 rows and every team is a set of its own; with
-// more, an even number of teams is two sets, so that a chunk of hundreds of rows does not wait for a single team.
-// A team that has no place in a set (team >= sets * parts) takes no chunk.
+// more, 16, 8 and 4 teams are two sets, so that a chunk of hundreds of rows does not wait for a single team.
 constexpr int WORK_COUNT = (PIPE_XCDS - 2 * PIPE_GROUPS) * REC_MAX_GROUP;
 struct WorkDeal {
-    int sets, parts;
+    int sets, share;   // a set is 1 << share teams
 };
 inline __host__ __device__ WorkDeal work_deal(int G, int cap) {
     const int teams = WORK_COUNT / G;
-    return cap > 16 && teams % 2 == 0 ? WorkDeal{2, teams / 2} : WorkDeal{teams, 1};
+    const int share = cap > 16 && teams % 2 == 0 ? __builtin_ctz(teams) - 1 : 0;
+    return WorkDeal{teams >> share, share};
 }
 
 // One group's view of the hand-over words, from the plan.
@@ -375,7 +375,7 @@ __device__ __forceinline__ PipeLink pipe_link_of(const int* plan, int* sync, int
     PipeLink pl;
     pl.progress = sync + g;
     pl.done = sync + 16 + g * pipe_done_stride(M);
-    pl.need = G * work_deal(G, plan[PLAN_KB + g + 1] - plan[PLAN_KB + g]).parts;
+    pl.need = G << work_deal(G, plan[PLAN_KB + g + 1] - plan[PLAN_KB + g]).share;
     pl.ct = plan[PLAN_CT + g];
     pl.T = plan[PLAN_T + g];
     return pl;
@@ -446,7 +446,7 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned 
     const int m = tid / TPR, col = rank * COLS + (tid % TPR) * PER;
     f32x4_t bias = {0.f, 0.f, 0.f, 0.f};
     if (FWD && w.bias) bias = *reinterpret_cast<const f32x4_t*>(w.bias + rank * COLS + (tid % TPR) * 4);
-    int lo[PIPE_GROUPS], cap[PIPE_GROUPS], T[PIPE_GROUPS], ct[PIPE_GROUPS], at[PIPE_GROUPS], t_max = 0;
+    int lo[PIPE_GROUPS], cap[PIPE_GROUPS], T[PIPE_GROUPS], ct[PIPE_GROUPS], at[PIPE_GROUPS], step[PIPE_GROUPS], share[PIPE_GROUPS], t_max = 0;
 #pragma unroll
     for (int g = 0; g < PIPE_GROUPS; ++g) {
         lo[g] = w.plan[PLAN_KB + g];
@@ -456,8 +456,10 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned 
         const int n = (T[g] + ct[g] - 1) / ct[g];
         // this team's first chunk of the group in the consumer's order (none: behind the last)
         const WorkDeal d = work_deal(w.G, cap[g]);
-        const int first = team < d.sets * d.parts ? (team / d.parts + g) % d.sets : n;
+        const int first = team < d.sets << d.share ? ((team >> d.share) + g) % d.sets : n;
         at[g] = DESCEND ? n - 1 - first : first;
+        step[g] = DESCEND ? -d.sets : d.sets;
+        share[g] = d.share;
         t_max = max(t_max, T[g]);
     }
     for (int t = tid; t <= min(t_max, WORK_LDS_T); t += REC_THREADS) s_toff[t] = w.t_off[t];
@@ -492,12 +494,12 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned 
         bar_lds();
         const int sel = __builtin_amdgcn_readfirstlane(s_sel[0]);
         if (sel < 0) return;   // nothing left, or the wait was abandoned
-        int g_lo = lo[0], g_cap = cap[0], g_T = T[0], g_ct = ct[0], c = at[0];
+        int g_lo = lo[0], g_cap = cap[0], g_T = T[0], g_ct = ct[0], g_share = share[0], c = at[0];
 #pragma unroll
         for (int g = 0; g < PIPE_GROUPS; ++g)
             if (sel == g) {
-                g_lo = lo[g]; g_cap = cap[g]; g_T = T[g]; g_ct = ct[g]; c = at[g];
-                at[g] += DESCEND ? -work_deal(w.G, cap[g]).sets : work_deal(w.G, cap[g]).sets;
+                g_lo = lo[g]; g_cap = cap[g]; g_T = T[g]; g_ct = ct[g]; g_share = share[g]; c = at[g];
+                at[g] += step[g];
             }
         // The group's rows of the chunk in time order: lane k holds what is needed of its timestep k.
         const int t0 = c * g_ct, nt = min(g_ct, g_T - t0);
@@ -515,8 +517,8 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned 
         before -= cnt;
         const int row_k = off_k + g_lo - before;   // row of slot s of timestep k: row_k + s
         // this team's share of the chunk: whole tiles
-        const int parts = work_deal(w.G, g_cap).parts, part_id = team % parts, tiles = (total + 15) / 16;
-        const int s_lo = tiles * part_id / parts * 16, s_hi = min(tiles * (part_id + 1) / parts * 16, total);
+        const int mine = team & ((1 << g_share) - 1), tiles = (total + 15) >> 4;
+        const int s_lo = (tiles * mine >> g_share) << 4, s_hi = min((tiles * (mine + 1) >> g_share) << 4, total);
         auto row_of = [&](int s) {
             int k = 0;
             for (int j = 1; j < nt; ++j) k += s >= __builtin_amdgcn_readlane(before, j) ? 1 : 0;

@@ -18,7 +18,7 @@ def deal(tmp_path_factory):
     (tmp / "deal.cpp").write_text(
         "#include <cstdio>\n#include <initializer_list>\n#define __host__\n#define __device__\nconstexpr int WORK_COUNT = 64;\n" + rule +
         "int main() { for (int G = 4; G <= 32; ++G) for (int cap : {0, 1, 16, 17, 3000})\n"
-        '    printf("%d %d %d %d\\n", G, cap, work_deal(G, cap).sets, work_deal(G, cap).parts); }\n')
+        '    printf("%d %d %d %d\\n", G, cap, work_deal(G, cap).sets, 1 << work_deal(G, cap).share); }\n')
     subprocess.check_call(["g++", "-o", str(tmp / "deal"), str(tmp / "deal.cpp")])
     rows = [tuple(map(int, l.split())) for l in subprocess.check_output([str(tmp / "deal")], text=True).splitlines()]
     return {(g, cap): (sets, parts) for g, cap, sets, parts in rows}
