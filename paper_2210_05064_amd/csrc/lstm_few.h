@@ -53,7 +53,7 @@ inline __host__ __device__ size_t few_slot_bytes(int mode, int row_elems) {
 inline __host__ __device__ size_t few_ring_bytes(int mode, int row_elems) { return FEW_RING * few_slot_bytes(mode, row_elems); }
 // LDS: partial sums, [8 waves][16 pieces][columns + 4] or two buffers of [8 waves][4 pieces][columns + 4], then (more than
 // 4 pieces) 16 rows of NB operand blocks per wave.
-constexpr int few_row(int cols) { return cols + 4; }   // (16 bytes more: 16 pieces of a fragment hit different banks)
+constexpr int few_row(int cols) { return cols + 4; }   // (16 bytes more, always zero: 16 pieces of a fragment hit different banks)
 constexpr int few_part_floats(int cols) { return REC_WAVES * 16 * few_row(cols); }
 constexpr int few_stage_bytes(int nb) { return 16 * nb * 64; }   // per wave
 inline __host__ __device__ size_t few_lds_bytes(int cols, int nb) {
@@ -146,8 +146,13 @@ __device__ __forceinline__ bool few_read(const unsigned char* base, const unsign
         }
     }
 }
+// The last slice of a wide bf16 layer may have half of the blocks (n_blk = NB / 2; every other slice is whole).  The
+// weights of the blocks it does not have are zero, but zero times an infinite value would not be: they are skipped, or
+// multiplied with zeros where a branch costs more (forward, 4 blocks: 445 us instead of 473 for two layers of 1024 on
+// 4096 rows in 64 pieces).
+template <int MODE, int MT> constexpr bool few_always_whole() { return !(MODE == MODE_BF16 && (MT == 8 || MT == 2)); }
 // Offsets of the L loads of a lane: block blk + j * BPL of the slice, or block blk again where the slice has no such
-// block (its weights are zero).
+// block (which is not multiplied).
 template <int L, int BPL>
 __device__ __forceinline__ void few_offsets(unsigned (&off)[L], unsigned first, int blk, int n_blk) {
 #pragma unroll
@@ -159,15 +164,20 @@ __device__ __forceinline__ void few_offsets(unsigned (&off)[L], unsigned first, 
 // Adds the product with all tiles of the wave into acc.  bf16: pieces are the rows 0, BPL, 2 BPL, ... of A, so that lane
 // group p * BPL / 4 holds piece p of the result, element 0.  fp32: acc[tile][piece] on the vector ALUs, a lane's share.
 template <int MODE, int MT, int NB, int P, int L>
-__device__ __forceinline__ void few_product(const f32x4_t (&w)[MT * NB], const u32x4_t (&raw)[L], int bs, f32x4_t (&acc)[MT]) {
+__device__ __forceinline__ void few_product(const f32x4_t (&w)[MT * NB], const u32x4_t (&raw)[L], int bs, int n_blk, f32x4_t (&acc)[MT]) {
     constexpr int BPL = 16 / P;
     if constexpr (MODE == MODE_BF16) {
-        few_for<NB>([&](auto ib) {
-            constexpr int b = decltype(ib)::value;
-            const f32x4_t op = few_rot<b % BPL>(raw[b / BPL]);
+        auto half = [&](auto first) {
+            few_for<NB / 2>([&](auto ib) {
+                constexpr int b = decltype(first)::value + decltype(ib)::value;
+                const f32x4_t op = few_rot<b % BPL>(raw[b / BPL]);
 #pragma unroll
-            for (int j = 0; j < MT; ++j) acc[j] = mfma_block<MODE>(op, w[j * NB + b], acc[j]);
-        });
+                for (int j = 0; j < MT; ++j) acc[j] = mfma_block<MODE>(op, w[j * NB + b], acc[j]);
+            });
+        };
+        half(FewIdx<0>{});
+        // (a single load: the lanes of the blocks that are not there read nothing and keep their zeros)
+        if (few_always_whole<MODE, MT>() || L == 1 || n_blk == NB) half(FewIdx<NB / 2>{});
     } else {
         few_for<P>([&](auto ip) {
             constexpr int p = decltype(ip)::value;
@@ -222,26 +232,32 @@ template <int NB> struct FewStage {
     static_assert((C & (C - 1)) == 0 && C <= 64 && C >= 8, "blocks per wave");
     static __device__ __forceinline__ int key(int r) { return C >= 16 ? (r & 15) : ((r >> 1) & 7); }
     static __device__ __forceinline__ int row(int j) { return j * RPL + (int)(threadIdx.x & 63) / C; }
-    // byte offset, inside the slice, of what this lane loads of row r (chunk 0 where the slice has no such chunk: its
-    // weights are zero)
+    // byte offset, inside the slice, of what this lane loads of row r (chunk 0 where the slice has no such chunk, which is
+    // not multiplied)
     static __device__ __forceinline__ unsigned src(int r, int n_blk) {
         const int c = ((int)(threadIdx.x & 63) % C) ^ key(r);
         return (unsigned)(c < 4 * n_blk ? c : 0) * 16u;
     }
 };
 // Product of the staged rows with all tiles, added into acc: rows are columns of the result, lane l holds row l % 16 and
-// columns (l / 16) * 4 + e of a tile.
+// columns (l / 16) * 4 + e of a tile.  zero: 16 bytes of zeros.
 template <int MODE, int MT, int NB>
-__device__ __forceinline__ void few_stage_product(const f32x4_t (&w)[MT * NB], const unsigned char* stage, int n_blk, f32x4_t (&acc)[MT]) {
+__device__ __forceinline__ void few_stage_product(const f32x4_t (&w)[MT * NB], const unsigned char* stage, const float* zero, int n_blk,
+                                                  f32x4_t (&acc)[MT]) {
     constexpr int GRP = NB < 8 ? NB : 8;   // operands in flight
     const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
     const unsigned char* row = stage + lr * (FewStage<NB>::C * 16);
     const int key = FewStage<NB>::key(lr);
 #pragma unroll
     for (int b0 = 0; b0 < NB; b0 += GRP) {
+        if (!few_always_whole<MODE, MT>() && GRP < NB && b0 >= n_blk) break;
         f32x4_t op[GRP];
 #pragma unroll
-        for (int b = 0; b < GRP; ++b) op[b] = *reinterpret_cast<const f32x4_t*>(row + ((min(lk * n_blk + b0 + b, 4 * n_blk - 1) ^ key) << 4));
+        for (int b = 0; b < GRP; ++b) {
+            const unsigned char* src = row + (((lk * n_blk + b0 + b) ^ key) << 4);
+            if (!few_always_whole<MODE, MT>() && GRP == NB && b0 + b >= NB / 2 && n_blk < NB) src = reinterpret_cast<const unsigned char*>(zero);
+            op[b] = *reinterpret_cast<const f32x4_t*>(src);
+        }
 #pragma unroll
         for (int b = 0; b < GRP; ++b)
 #pragma unroll
@@ -474,10 +490,10 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
 #pragma unroll
             for (int j = 0; j < MT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             if constexpr (STAGED) {
-                few_stage_product<MODE, MT, NB>(s.w, stage, s.n_blk, acc);
+                few_stage_product<MODE, MT, NB>(s.w, stage, s.part + 16 * MT, s.n_blk, acc);
                 few_stage_write<MT>(acc, bs, part + s.slice * (PP * ROW));
             } else {
-                few_product<MODE, MT, NB, P, L>(s.w, raw, bs, acc);
+                few_product<MODE, MT, NB, P, L>(s.w, raw, bs, s.n_blk, acc);
                 few_write<MODE, MT, P>(acc, bs, part + s.slice * (PP * ROW));
             }
         }
@@ -746,10 +762,10 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
 #pragma unroll
             for (int i = 0; i < MT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             if constexpr (STAGED) {
-                few_stage_product<MODE, MT, NB>(s.w, stage, s.n_blk, acc);
+                few_stage_product<MODE, MT, NB>(s.w, stage, s.part + 16 * MT, s.n_blk, acc);
                 few_stage_write<MT>(acc, bs, part + s.slice * (PP * ROW));
             } else {
-                few_product<MODE, MT, NB, P, L>(s.w, raw, bs, acc);
+                few_product<MODE, MT, NB, P, L>(s.w, raw, bs, s.n_blk, acc);
                 few_write<MODE, MT, P>(acc, bs, part + s.slice * (PP * ROW));
             }
         }

@@ -544,7 +544,7 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned 
                     f32x4_t acc[MT];
 #pragma unroll
                     for (int j = 0; j < MT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-                    few_stage_product<MODE, MT, NB>(wreg, stage, n_blk, acc);
+                    few_stage_product<MODE, MT, NB>(wreg, stage, part + COLS, n_blk, acc);
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the operands have been read)
                     if (r0 + 16 < n) work_request<NB>(rsA, stage, s_row + r0 + 16, (unsigned)(K * es), slice, n_blk);
                     few_stage_write<MT>(acc, rows, part + slice * (16 * ROW));

@@ -257,3 +257,66 @@ def test_workers_hold_the_weights_several_times(ver, compute, hidden):
                   minibatches=1, speed_sigma=0.6)
     _, meta = case(ver, w, seed=60 + hidden, compute=compute, x_bf16=bool(compute))
     assert meta["n_seq"] > 3 * 32
+
+
+def poisoned(ver, w, seed, compute, poison):
+    """Forward (and backward) runs with clean initial states and with `poison` applied to them; poison(h0, n_seq) changes
+    the states in place."""
+    ro = wl.make_rollout(w, seed=seed, bias_scale=0.2)
+    meta = opack.pack_minibatch(ro["dones"], ro["env_off"], ro["seq_key"][0], 1, 0, ro["env_started_episode"])
+    clean = opack.initial_states(ro["rnn_h"], meta["seq_first"], meta["seq_is_ep_start"])
+    c0 = opack.initial_states(ro["rnn_c"], meta["seq_first"], meta["seq_is_ep_start"])
+    h0 = np.array(clean, np.float32)
+    poison(h0, meta["n_seq"])
+    x = opack.gather_rows(ro["obs"], meta["gather_idx"])
+    runs = [LstmRun(ver, w, ro["weights"], x, meta, h, c0, compute) for h in (clean, h0)]
+    return ro, meta, h0, c0, runs
+
+
+@pytest.mark.parametrize("n_envs", [16, 72, 160])
+@pytest.mark.parametrize("compute,hidden", [(0, 320), (1, 320), (1, 576), (1, 704), (1, 832), (1, 960), (1, 1024)])
+def test_infinite_initial_state(ver, compute, hidden, n_envs):
+    """An infinite hidden state saturates the gates and leaves finite results, in the last 64 units above all: above 512
+    units they are a share of the contraction that is only partly filled at odd multiples of 64 (groups of 2, 9 and 20
+    pieces: both small forms and the form for many)."""
+    w = wl.scaled(wl.WORKLOADS["manip"], budget=3 * n_envs, n_envs=n_envs, n_layers=1, hidden=hidden, input_dim=8, p_done=0.0,
+                  minibatches=1, speed_sigma=0.0)
+
+    def poison(h0, n):
+        for j in range(n):
+            h0[0, j, hidden - 1 - (7 * j) % 64 if j % 4 else (31 * j) % hidden] = np.inf if j % 2 else -np.inf
+    ro, meta, h0, c0, (_, run) = poisoned(ver, w, 5, compute, poison)
+    u, v = run.forward()
+    with np.errstate(over="ignore"):
+        fwd = olstm.minibatch_forward(ro["obs"], meta["seq_first"], meta["seq_len"], olstm.weights_f64(ro["weights"]), h0, c0)
+    close = closer(compute)
+    close(u, olstm.to_packed([f[0] for f in fwd], meta["t_off"]), "head_out")
+    close(v, olstm.to_packed([f[1] for f in fwd], meta["t_off"]), "value")
+
+
+@pytest.mark.parametrize("n_layers,n_envs", [(1, 16), (1, 72), (1, 160), (2, 9), (2, 40), (2, 70)])
+@pytest.mark.parametrize("compute,hidden", [(0, 64), (0, 320), (1, 64), (1, 576), (1, 1024)])
+def test_nan_stays_in_its_piece(ver, compute, hidden, n_layers, n_envs):
+    """A piece whose state is NaN (in fp32 the one whose bits mark an empty word of the exchange ring) stays NaN to its end,
+    ends no wait and leaves every other piece as it was, bit by bit; the gradients it contributes to are NaN."""
+    w = wl.scaled(wl.WORKLOADS["manip"], budget=5 * n_envs, n_envs=n_envs, n_layers=n_layers, hidden=hidden, input_dim=8,
+                  p_done=0.0, minibatches=1, speed_sigma=0.4)
+    bits = np.array([0xffffffff if compute == 0 else 0x7fc00000], np.uint32).view(np.float32)[0]
+    bad = []
+
+    def poison(h0, n):
+        for j in range(0, n, 5):
+            bad.append(j)
+            h0[0, j, :] = bits
+    _, meta, _, _, runs = poisoned(ver, w, 6, compute, poison)
+    (u, v), (u_bad, v_bad) = [r.forward() for r in runs]
+    rows = np.concatenate([meta["t_off"][t] + np.array([j for j in bad if j < n], int) for t, n in enumerate(meta["batch_sizes"])])
+    hit = np.zeros(meta["M"], bool)
+    hit[rows] = True
+    assert np.isnan(u_bad[hit]).all() and np.isnan(v_bad[hit]).all()
+    assert np.array_equal(u_bad[~hit], u[~hit]) and np.array_equal(v_bad[~hit], v[~hit])
+    rng = np.random.default_rng(7)
+    d_u, d_v = rng.standard_normal(u.shape).astype(np.float32) / meta["M"], rng.standard_normal(v.shape).astype(np.float32) / meta["M"]
+    (_, dx), (grads_bad, dx_bad) = [r.backward(d_u, d_v) for r in runs]
+    assert np.isnan(dx_bad[hit]).all() and np.array_equal(dx_bad[~hit], dx[~hit])
+    assert np.isnan(grads_bad[1]).any()
