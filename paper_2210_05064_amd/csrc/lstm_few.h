@@ -240,10 +240,11 @@ template <int NB> struct FewStage {
     }
 };
 // Product of the staged rows with all tiles, added into acc: rows are columns of the result, lane l holds row l % 16 and
-// columns (l / 16) * 4 + e of a tile.  zero: 16 bytes of zeros.
-template <int MODE, int MT, int NB>
+// columns (l / 16) * 4 + e of a tile.  zero: 16 bytes of zeros.  Calls read() once no operand is left to be fetched, ahead of
+// the last (up to 8) blocks' MFMAs.  RAGGED: any number of blocks.
+template <int MODE, int MT, int NB, bool RAGGED, typename F>
 __device__ __forceinline__ void few_stage_product(const f32x4_t (&w)[MT * NB], const unsigned char* stage, const float* zero, int n_blk,
-                                                  f32x4_t (&acc)[MT]) {
+                                                  f32x4_t (&acc)[MT], F&& read) {
     constexpr int GRP = NB < 8 ? NB : 8;   // operands in flight
     const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
     const unsigned char* row = stage + lr * (FewStage<NB>::C * 16);
@@ -254,14 +255,16 @@ __device__ __forceinline__ void few_stage_product(const f32x4_t (&w)[MT * NB], c
         f32x4_t op[GRP];
 #pragma unroll
         for (int b = 0; b < GRP; ++b) {
-            const unsigned char* src = row + (((lk * n_blk + b0 + b) ^ key) << 4);
+            const unsigned char* src = row + (((RAGGED ? min(lk * n_blk + b0 + b, 4 * n_blk - 1) : lk * n_blk + b0 + b) ^ key) << 4);
             if (!few_always_whole<MODE, MT>() && GRP == NB && b0 + b >= NB / 2 && n_blk < NB) src = reinterpret_cast<const unsigned char*>(zero);
             op[b] = *reinterpret_cast<const f32x4_t*>(src);
         }
+        if (b0 + GRP >= NB || (!few_always_whole<MODE, MT>() && b0 + GRP >= n_blk)) read();
 #pragma unroll
         for (int b = 0; b < GRP; ++b)
+            if (!RAGGED || b0 + b < n_blk)
 #pragma unroll
-            for (int j = 0; j < MT; ++j) acc[j] = mfma_block<MODE>(w[j * NB + b0 + b], op[b], acc[j]);
+                for (int j = 0; j < MT; ++j) acc[j] = mfma_block<MODE>(w[j * NB + b0 + b], op[b], acc[j]);
     }
 }
 template <int MT>
@@ -490,7 +493,7 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
 #pragma unroll
             for (int j = 0; j < MT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             if constexpr (STAGED) {
-                few_stage_product<MODE, MT, NB>(s.w, stage, s.part + 16 * MT, s.n_blk, acc);
+                few_stage_product<MODE, MT, NB, false>(s.w, stage, s.part + 16 * MT, s.n_blk, acc, [] {});
                 few_stage_write<MT>(acc, bs, part + s.slice * (PP * ROW));
             } else {
                 few_product<MODE, MT, NB, P, L>(s.w, raw, bs, s.n_blk, acc);
@@ -762,7 +765,7 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
 #pragma unroll
             for (int i = 0; i < MT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             if constexpr (STAGED) {
-                few_stage_product<MODE, MT, NB>(s.w, stage, s.part + 16 * MT, s.n_blk, acc);
+                few_stage_product<MODE, MT, NB, false>(s.w, stage, s.part + 16 * MT, s.n_blk, acc, [] {});
                 few_stage_write<MT>(acc, bs, part + s.slice * (PP * ROW));
             } else {
                 few_product<MODE, MT, NB, P, L>(s.w, raw, bs, s.n_blk, acc);

@@ -405,16 +405,21 @@ __device__ __forceinline__ void work_load_lds(__amdgpu_buffer_rsrc_t rs, unsigne
 }
 // Requests this wave's slice of 16 rows (numbers in LDS) into its staging area; a lane's LDS address is the load's base + 16 * lane.
 template <int NB>
-__device__ __forceinline__ void work_request(__amdgpu_buffer_rsrc_t rs, unsigned char* stage, const int* rows, unsigned row_bytes, int slice, int n_blk) {
+__device__ __forceinline__ void work_request(__amdgpu_buffer_rsrc_t rs, unsigned char* stage, const int* rows, unsigned row_bytes, int b_lo, int n_blk) {
 #pragma unroll
     for (int j = 0; j < FewStage<NB>::LOADS; ++j) {
         const int r = FewStage<NB>::row(j);
-        work_load_lds(rs, stage + j * 1024, (unsigned)rows[r] * row_bytes + (unsigned)(slice * NB) * 64u + FewStage<NB>::src(r, n_blk));
+        work_load_lds(rs, stage + j * 1024, (unsigned)rows[r] * row_bytes + (unsigned)b_lo * 64u + FewStage<NB>::src(r, n_blk));
     }
 }
 
+// First block of slice s when the contraction is dealt evenly over the waves; slices s and s + 4 round to opposite sides.
+inline __host__ __device__ int work_even(int blocks, int s) { return (s * blocks + (s > REC_WAVES / 2 ? REC_WAVES - 1 : 0)) / REC_WAVES; }
+
 // FWD: 16 * MT columns per worker, four of them (a unit's gates) per thread; else one column per thread.
-template <int MODE, int MT, int NB, bool FWD>
+// EVEN: the contraction is dealt evenly over the waves (w and w + 4 share a SIMD) instead of NB blocks at a time.  For fp32 forward below H = 512, where the MFMAs set the pace: two layers of 384 on
+// 32768 rows in 256 pieces 2.9 ms instead of 4.0.
+template <int MODE, int MT, int NB, bool FWD, bool EVEN>
 __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned char* smem) {
     typedef typename RecGeom<MODE>::E E;
     constexpr int es = (int)sizeof(E), KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC;
@@ -429,14 +434,15 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     unsigned char* stage = smem + (size_t)few_part_floats(COLS) * sizeof(float) + wave * few_stage_bytes(NB);
     int* s_toff = reinterpret_cast<int*>(smem + (size_t)few_part_floats(COLS) * sizeof(float) + REC_WAVES * few_stage_bytes(NB));
-    const int K = w.K, N = w.N, blocks = K / KBLK, n_slices = (blocks + NB - 1) / NB;
+    const int K = w.K, N = w.N, blocks = K / KBLK, n_slices = EVEN ? REC_WAVES : (blocks + NB - 1) / NB;
     // (which slice a wave takes rotates with the rank: all workers read the same rows at the same moment)
     const int slice = n_slices == REC_WAVES ? (wave + rank) % REC_WAVES : wave;
-    const int n_blk = min(NB, blocks - slice * NB);
+    const int b_lo = EVEN ? work_even(blocks, slice) : slice * NB;
+    const int n_blk = EVEN ? work_even(blocks, slice + 1) - b_lo : min(NB, blocks - b_lo);
     f32x4_t wreg[MT * NB];
 #pragma unroll
     for (int j = 0; j < MT; ++j) {
-        const E* wrow = static_cast<const E*>(w.B) + ((size_t)rank * COLS + j * 16 + lr) * K + (slice * NB * 4 + lk * n_blk) * VEC;
+        const E* wrow = static_cast<const E*>(w.B) + ((size_t)rank * COLS + j * 16 + lr) * K + (b_lo * 4 + lk * n_blk) * VEC;
 #pragma unroll
         for (int b = 0; b < NB; ++b)
             wreg[j * NB + b] = b < n_blk ? *reinterpret_cast<const f32x4_t*>(wrow + b * VEC) : f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -526,15 +532,19 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned 
         };
         // 16 rows at a time, their numbers from a table of up to REC_THREADS rows.  A wave's slice of the rows goes from memory
         // straight into its staging area (few_stage_product says how it lies there); the next tile's is requested as
-        // soon as this one's operands have been read, and arrives behind the partial sums.  (Every store is issued, out of
+        // soon as this one's operands have been read, and arrives behind the last MFMAs and the partial sums.  (Every store is issued, out of
         // range for rows that a tile does not have: a store that may or may not be there makes the wait for the loads
         // before it a wait for the store.)
-        const bool works = slice < n_slices;
+        const bool works = n_blk > 0;
+        // Requested ahead of the MFMAs where they take long enough to be worth the separation from the reads: fp32 (2 x 512
+        // forward on 32768 rows in 1024 pieces 3.75 -> 3.60 ms) and wide bf16 (2 x 1024 on 4096 rows in 64 445 -> 437 us), not
+        // narrow bf16 (2 x 512 on 32768 rows in 256 1.59 -> 1.62 ms).
+        constexpr bool EARLY = MODE == MODE_F32 || MT == 8 || MT == 2;
         for (int b0 = s_lo; b0 < s_hi; b0 += REC_THREADS) {
             const int n = min(s_hi - b0, REC_THREADS);
             s_row[tid] = row_of(min(b0 + tid, total - 1));
             bar_lds();
-            if (works) work_request<NB>(rsA, stage, s_row, (unsigned)(K * es), slice, n_blk);
+            if (works) work_request<NB>(rsA, stage, s_row, (unsigned)(K * es), b_lo, n_blk);
             for (int r0 = 0; r0 < n; r0 += 16) {
                 const int rows = min(16, n - r0);
                 const int out_row = s_row[r0 + min(m, 15)];
@@ -544,9 +554,13 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned 
                     f32x4_t acc[MT];
 #pragma unroll
                     for (int j = 0; j < MT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-                    few_stage_product<MODE, MT, NB>(wreg, stage, part + COLS, n_blk, acc);
-                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the operands have been read)
-                    if (r0 + 16 < n) work_request<NB>(rsA, stage, s_row + r0 + 16, (unsigned)(K * es), slice, n_blk);
+                    auto next = [&] {
+                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the operands have been read)
+                        if (r0 + 16 < n) work_request<NB>(rsA, stage, s_row + r0 + 16, (unsigned)(K * es), b_lo, n_blk);
+                        __builtin_amdgcn_sched_barrier(0);
+                    };
+                    few_stage_product<MODE, MT, NB, EVEN>(wreg, stage, part + COLS, n_blk, acc, [&] { if (EARLY) next(); });
+                    if (!EARLY) next();
                     few_stage_write<MT>(acc, rows, part + slice * (16 * ROW));
                 }
                 bar_lds();
@@ -626,7 +640,7 @@ __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
         }
     } else if (xcc < PIPE_XCDS && rank < REC_MAX_GROUP) {
         constexpr int WMT = REC_WAVES / KS * TPW;
-        pipe_worker<MODE, WMT, FewBlocks<MODE, WMT == 8>::fwd, true>(p.work, (xcc - 2 * PIPE_GROUPS) * REC_MAX_GROUP + rank, smem);
+        pipe_worker<MODE, WMT, FewBlocks<MODE, WMT == 8>::fwd, true, MODE == MODE_F32 && !STATIC>(p.work, (xcc - 2 * PIPE_GROUPS) * REC_MAX_GROUP + rank, smem);
     }
 #ifdef VER_REC_PROF
     if (stamp) tl[1] = wall_clock64();
@@ -660,7 +674,7 @@ __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
                 rec_bwd_body<MODE, MT, KS, NI, PIPE_CONSUMER>(p.l0, rank, ps, link.T, p.l0.flags + xcc * REC_MAX_GROUP, link, smem);
         }
     } else if (xcc < PIPE_XCDS && rank < REC_MAX_GROUP) {
-        pipe_worker<MODE, MT, FewBlocks<MODE, MT == 2>::bwd, false>(p.work, (xcc - 2 * PIPE_GROUPS) * REC_MAX_GROUP + rank, smem);
+        pipe_worker<MODE, MT, FewBlocks<MODE, MT == 2>::bwd, false, false>(p.work, (xcc - 2 * PIPE_GROUPS) * REC_MAX_GROUP + rank, smem);
     }
 #ifdef VER_REC_PROF
     if (stamp) tl[1] = wall_clock64();

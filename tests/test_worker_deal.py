@@ -66,3 +66,21 @@ def test_shares_of_a_chunk(deal, G):
         tiles = (total + 15) // 16
         edge = [min(tiles * k // parts * 16, total) for k in range(parts + 1)]
         assert edge[0] == 0 and edge[-1] == total and edge == sorted(edge)
+
+
+def test_even_slices_of_the_contraction(tmp_path):
+    """work_even: eight slices that cover all blocks of every width below 512, at most four each, and the two waves of a
+    SIMD (slices s and s + 4) share the work as evenly as the SIMDs can."""
+    text = open(os.path.join(ROOT, "paper_2210_05064_amd", "csrc", "lstm_pipe.h")).read()
+    rule = re.search(r"inline __host__ __device__ int work_even.*?}\n", text, re.S).group(0)
+    (tmp_path / "even.cpp").write_text(
+        "#include <cstdio>\n#define __host__\n#define __device__\nconstexpr int REC_WAVES = 8;\n" + rule +
+        'int main() { for (int b = 4; b < 32; b += 4) for (int s = 0; s <= 8; ++s) printf("%d\\n", work_even(b, s)); }\n')
+    subprocess.check_call(["g++", "-o", str(tmp_path / "even"), str(tmp_path / "even.cpp")])
+    first = [int(v) for v in subprocess.check_output([str(tmp_path / "even")], text=True).split()]
+    for k, blocks in enumerate(range(4, 32, 4)):
+        at = first[9 * k:9 * k + 9]
+        n = [b - a for a, b in zip(at, at[1:])]
+        assert at[0] == 0 and at[8] == blocks and min(n) >= 0 and max(n) <= 4
+        simd = [n[s] + n[s + 4] for s in range(4)]
+        assert max(simd) - min(simd) <= (0 if blocks % 4 == 0 else 1)
