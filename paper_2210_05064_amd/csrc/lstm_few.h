@@ -410,7 +410,7 @@ template <int MODE, int MT, int NB, int P, int PIPE>
 __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const RecFwdArgs& a, const PieceSet& ps, int rank, int* flags,
                                               unsigned char* ring, const PipeLink& pl, int& t, int T, int down_to) {
     typedef typename RecGeom<MODE>::E E;
-    constexpr int es = (int)sizeof(E), KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC;
+    constexpr int es = (int)sizeof(E);
     constexpr int UH = 4 * MT, COLS = 16 * MT, ROW = few_row(COLS), PP = P > 4 ? 16 : 4;
     constexpr bool STAGED = P > 4;
     constexpr int BPL = 16 / P, L = STAGED ? 1 : (NB + BPL - 1) / BPL;
@@ -658,7 +658,7 @@ template <int MODE, int MT, int NB, int P, int PIPE>
 __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const RecBwdArgs& a, const PieceSet& ps, int rank, unsigned char* ring,
                                               const PipeLink& pl, int& t, int T, int t_stop, int up_to) {
     typedef typename RecGeom<MODE>::E E;
-    constexpr int es = (int)sizeof(E), KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC;
+    constexpr int es = (int)sizeof(E);
     constexpr int UH = 16 * MT, ROW = few_row(UH), PP = P > 4 ? 16 : 4;
     constexpr bool STAGED = P > 4;
     constexpr int BPL = 16 / P, L = STAGED ? 1 : (NB + BPL - 1) / BPL;

@@ -143,6 +143,15 @@ def test_long_and_short_pieces(ver):
     assert meta["T_max"] > 1024
 
 
+@pytest.mark.parametrize("compute", [0, 1])
+def test_more_timesteps_than_the_workers_keep_offsets_of(ver, compute):
+    """Two-layer launch with more than 2048 timesteps: the workers keep the row offsets of the first 2048 in LDS and read
+    the others from memory; one chunk of 8 timesteps has offsets of both."""
+    _, meta = case(ver, wl.scaled(wl.WORKLOADS["nav"], budget=4500, n_envs=2, hidden=64, input_dim=8, p_done=0.0,
+                                  minibatches=1, speed_sigma=0.05), seed=14, compute=compute)
+    assert meta["T_max"] > 2060 and meta["batch_sizes"][2060] == 2
+
+
 def test_wide_hidden_not_a_multiple_of_128(ver):
     """hidden = 576 (bf16 operands; fp32 keeps its share of W_hh in registers only up to hidden = 512): more than 32
     tiles of 16 units (workgroups of 32 units) and a contraction that does not split into whole operand blocks four
@@ -237,9 +246,9 @@ def test_grouped_weight_gradients(ver, input_dim, layer_by_layer):
 @pytest.mark.parametrize("compute,hidden", [(0, 64), (0, 320), (0, 512), (1, 64), (1, 320), (1, 512), (1, 704), (1, 1024)])
 @pytest.mark.parametrize("n_layers,n_envs", [(1, 150), (2, 60)])
 def test_forms_of_the_time_loops(ver, compute, hidden, n_layers, n_envs):
-    """A group's timesteps change form with its alive pieces (more than 16, 16 .. 5, 4 .. 1 forward; 8, 4 and 1 or 2
-    backward; 4 and 1 in fp32): groups that start with about 20 pieces and end with one pass through all of
-    them, at widths with whole, partly filled and empty shares of the contraction."""
+    """A group's timesteps change form with its alive pieces (forward: more than 16, 16 .. 5, 4 .. 1; backward: up to 1 or 2,
+    up to 4, up to 16, more): groups that start with about 20 pieces and end with one pass through all of them, at
+    widths with whole, partly filled and empty shares of the contraction."""
     w = wl.scaled(wl.WORKLOADS["manip"], budget=6 * n_envs, n_envs=n_envs, n_layers=n_layers, hidden=hidden, input_dim=20,
                   p_done=0.01, minibatches=1, speed_sigma=0.8)
     _, meta = case(ver, w, seed=17 + hidden, compute=compute, x_bf16=bool(compute))
