@@ -457,10 +457,10 @@ inline int device_fits_time_loops() {
 // sticky time-out word at the start of the workspace, and writes the plans of both launches of the minibatch (the
 // backward call runs on the packing of the forward call whose activations it finds in the workspace).  Before the
 // backward launch only the words are cleared.
-inline void pipe_prepare_fwd(LstmWs& ws, int mode, bool wide, int M, const int32_t* info, const int32_t* batch_sizes, hipStream_t s) {
+inline void pipe_prepare_fwd(LstmWs& ws, int mode, bool wide, int G, int M, const int32_t* info, const int32_t* batch_sizes, hipStream_t s) {
     int* last = ws.pipe + ws.pipe_words;
     hipLaunchKernelGGL(lstm_pipe_plan_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, info, batch_sizes, M, ws.plan[0], ws.plan[1],
-                       ws.plan_scratch, ws.err, (int)(last - ws.err), plan_cost(mode, wide, true), plan_cost(mode, wide, false));
+                       ws.plan_scratch, ws.err, (int)(last - ws.err), plan_cost(mode, wide, true, G), plan_cost(mode, wide, false, G));
 }
 inline void pipe_work(const LstmWs& ws, int dir, int M, const int32_t* t_off, PipeWork* pw) {
     pw->M = M;
@@ -495,7 +495,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     size_t lds = ntc * (tile + red_per_tile);
     const int few_nb = wide ? FewBlocks<MODE, true>::fwd : FewBlocks<MODE, false>::fwd;
     if (few_lds_bytes(16 * mt, few_nb) > lds) lds = few_lds_bytes(16 * mt, few_nb);
-    const size_t work_lds = work_lds_bytes(16 * mt, few_nb);
+    const size_t work_lds = work_lds_bytes(16 * mt, few_nb, work_bufs<MODE, true>());
     if (pipelined && work_lds > lds) lds = work_lds;
     const int nb = (H / ks) / RecGeom<MODE>::KBLK;
 
@@ -570,7 +570,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     prep_all();
     if (pipelined) {
         project(0);
-        pipe_prepare_fwd(ws, MODE, wide, M, info, batch_sizes, s);
+        pipe_prepare_fwd(ws, MODE, wide, H / (4 * mt), M, info, batch_sizes, s);
         PipeFwdArgs pa;
         pa.l0 = rec_args(0);
         pa.l1 = rec_args(1);
@@ -629,7 +629,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     size_t lds = ntc * (tile + red_per_tile);
     const int few_nb = wide ? FewBlocks<MODE, true>::bwd : FewBlocks<MODE, false>::bwd;
     if (few_lds_bytes(16 * mt, few_nb) > lds) lds = few_lds_bytes(16 * mt, few_nb);
-    const size_t work_lds = work_lds_bytes(16 * mt, few_nb);
+    const size_t work_lds = work_lds_bytes(16 * mt, few_nb, work_bufs<MODE, false>());
     if (pipelined && work_lds > lds) lds = work_lds;
     const int ni = (4 * H / ks) / RecGeom<MODE>::KBLK;
 

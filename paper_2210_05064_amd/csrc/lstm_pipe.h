@@ -55,20 +55,29 @@ inline __host__ __device__ int pipe_sync_words(int M) { return 16 + PIPE_GROUPS 
 // Predicted microseconds of a timestep: step + piece * b + tile * (ceil(b / 16) - 1) (b alive pieces of the group).
 struct PlanCost {
     float step, piece, tile;
+    int chunk_rows;   // rows per chunk that groups of more than 16 pieces aim at where the workers set the pace; 0: never
 };
 // Timesteps per chunk by the pieces of the group: a chunk is handed on when it is complete, so the consumer starts and
 // ends that much later than the producer; it costs a worker about 4 us beside the product of its rows.
-constexpr int PLAN_CT_FEW = 8, PLAN_CT_MID = 8, PLAN_CT_MANY = 2;   // up to 4, up to 16, more pieces
-// Fitted by hand to the time per timestep of launches over equally long pieces, 1 .. 64 per group (us):
+constexpr int PLAN_CT_FEW = 8, PLAN_CT_MANY = 2;   // up to 16, more pieces
+// fp32 forward from 384 units on, where only two teams of workers hold the weights and a tile costs them 1.8 to 2.5 us:
+// with PLAN_DENSE alive pieces per timestep (average over the launch) or more the workers are behind and long chunks pay,
+// with fewer the delay costs more.  us per timestep with 32 equally long pieces per group (96 alive), chunks of 2
+// timesteps -> of 256 rows: H = 384 9.0 -> 7.0, 512 10.7 -> 8.5; us per launch: 512 units, 32768 rows in 256 pieces (64
+// alive) 3750 -> 3080, 8192 in 256 (64) 1075 -> 962, 4096 in 128 (39) 557 -> 611, 4096 in 64 (23) 604 -> 680.
+constexpr int PLAN_DENSE = 48, PLAN_CHUNK_ROWS = 256;
+// us per timestep of launches over equally long pieces (two layers; time of a launch against its timesteps):
 //   pieces               1     2     4     8    16    32    64
-//   bf16 H=1024 fwd   1.43  1.35  1.40  1.86  2.04   5.1  12.5      bwd  1.65  1.83  2.2   2.26  3.0   9.1  18
-//   bf16 H=512  fwd   1.19  1.18  1.20  1.36  1.54   3.1            bwd  1.42  1.34  1.6   1.65  2.0   4.4
-//   fp32 H=512  fwd   1.52  1.62  2.26  3.9   3.75   6.6            bwd  1.7   2.05  3.05  4.5   5.35  9.6
-// (timesteps with up to 16 pieces, 4 in fp32, run in the form of lstm_few.h).
-inline PlanCost plan_cost(int mode, bool wide, bool fwd) {
-    if (mode == MODE_F32) return fwd ? PlanCost{1.45f, 0.19f, 1.f} : PlanCost{1.6f, 0.27f, 0.f};
-    if (wide) return fwd ? PlanCost{1.38f, 0.042f, 2.4f} : PlanCost{1.75f, 0.08f, 4.6f};
-    return fwd ? PlanCost{1.17f, 0.023f, 1.2f} : PlanCost{1.38f, 0.04f, 1.7f};
+//   bf16 H=1024 fwd   1.37  1.35  1.38  1.96  2.6    5.1  11.2      bwd  1.68  1.88  2.16  2.49  3.45  8.9  17.1
+//   bf16 H=512  fwd   1.12  1.12  1.12  1.29  1.63   3.4   5.3      bwd  1.38  1.39  1.60  1.66  2.15  4.2   8.1
+//   fp32 H=512  fwd   1.23  1.53  2.16  3.1   5.2   8.5   16        bwd  1.50  2.06  3.08  3.65  4.5   10.2  19
+// (timesteps with up to 16 pieces run in the form of lstm_few.h).  The constants were fitted by hand to such a table when
+// single timesteps took 0.1 to 0.3 us longer; the cuts between the groups depend on the ratios only.
+inline PlanCost plan_cost(int mode, bool wide, bool fwd, int G) {
+    if (mode == MODE_F32)
+        return fwd ? PlanCost{1.45f, 0.19f, 1.f, 2 * REC_MAX_GROUP / G < 3 ? PLAN_CHUNK_ROWS : 0} : PlanCost{1.6f, 0.27f, 0.f, 0};
+    if (wide) return fwd ? PlanCost{1.38f, 0.042f, 2.4f, 0} : PlanCost{1.75f, 0.08f, 4.6f, 0};
+    return fwd ? PlanCost{1.17f, 0.023f, 1.2f, 0} : PlanCost{1.38f, 0.04f, 1.7f, 0};
 }
 
 struct PipeWork {
@@ -207,7 +216,8 @@ __device__ __forceinline__ void plan_body(const int32_t* __restrict__ batch_size
         const int lo = s_kb[d][g], cap = s_kb[d][g + 1] - lo;
         int* plan = d == 0 ? plan_fwd : plan_bwd;
         plan[PLAN_T + g] = cap > 0 ? (int)len[lo] : 0;
-        plan[PLAN_CT + g] = cap <= 4 ? PLAN_CT_FEW : (cap <= 16 ? PLAN_CT_MID : PLAN_CT_MANY);
+        const int aim = M >= PLAN_DENSE * T ? (d == 0 ? pc_fwd : pc_bwd).chunk_rows : 0;
+        plan[PLAN_CT + g] = cap <= 16 ? PLAN_CT_FEW : min(max(aim / cap, PLAN_CT_MANY), PLAN_CT_FEW);
     }
 }
 
@@ -396,8 +406,8 @@ __device__ __forceinline__ PieceSet pipe_pieces_of(const int* plan, int g) {
 // A net of up to 320 units needs fewer than half of the 64 workers for its weights: the others hold them again (work_deal).
 // One team per XCD left 28 of 32 CUs idle at H = 64 and made the workers the bound of launches over hundreds of pieces.
 constexpr int WORK_LDS_T = 2047;   // timesteps whose row offsets are kept in LDS
-inline __host__ __device__ size_t work_lds_bytes(int cols, int nb) {
-    return (size_t)few_part_floats(cols) * sizeof(float) + (size_t)REC_WAVES * few_stage_bytes(nb) + (WORK_LDS_T + 1) * sizeof(int);
+inline __host__ __device__ size_t work_lds_bytes(int cols, int nb, int bufs) {
+    return (size_t)bufs * few_part_floats(cols) * sizeof(float) + (size_t)REC_WAVES * few_stage_bytes(nb) + (WORK_LDS_T + 1) * sizeof(int);
 }
 
 __device__ __forceinline__ void work_load_lds(__amdgpu_buffer_rsrc_t rs, unsigned char* lds, unsigned off) {
@@ -413,6 +423,8 @@ __device__ __forceinline__ void work_request(__amdgpu_buffer_rsrc_t rs, unsigned
     }
 }
 
+// The fp32 forward workers add up the partial sums of a tile behind the MFMAs of the next one: two buffers of them.
+template <int MODE, bool FWD> constexpr int work_bufs() { return FWD && MODE == MODE_F32 ? 2 : 1; }
 // First block of slice s when the contraction is dealt evenly over the waves; slices s and s + 4 round to opposite sides.
 inline __host__ __device__ int work_even(int blocks, int s) { return (s * blocks + (s > REC_WAVES / 2 ? REC_WAVES - 1 : 0)) / REC_WAVES; }
 
@@ -432,8 +444,10 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned 
     float* part = reinterpret_cast<float*>(smem);
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    unsigned char* stage = smem + (size_t)few_part_floats(COLS) * sizeof(float) + wave * few_stage_bytes(NB);
-    int* s_toff = reinterpret_cast<int*>(smem + (size_t)few_part_floats(COLS) * sizeof(float) + REC_WAVES * few_stage_bytes(NB));
+    constexpr int BUFS = work_bufs<MODE, FWD>();
+    unsigned char* stages = smem + (size_t)BUFS * few_part_floats(COLS) * sizeof(float);
+    unsigned char* stage = stages + wave * few_stage_bytes(NB);
+    int* s_toff = reinterpret_cast<int*>(stages + REC_WAVES * few_stage_bytes(NB));
     const int K = w.K, N = w.N, blocks = K / KBLK, n_slices = EVEN ? REC_WAVES : (blocks + NB - 1) / NB;
     // (which slice a wave takes rotates with the rank: all workers read the same rows at the same moment)
     const int slice = n_slices == REC_WAVES ? (wave + rank) % REC_WAVES : wave;
@@ -469,7 +483,8 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned 
         t_max = max(t_max, T[g]);
     }
     for (int t = tid; t <= min(t_max, WORK_LDS_T); t += REC_THREADS) s_toff[t] = w.t_off[t];
-    few_clear_part<COLS>(part);
+#pragma unroll
+    for (int i = 0; i < BUFS; ++i) few_clear_part<COLS>(part + i * few_part_floats(COLS));
     bar_lds();
     const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(w.A), 0, w.M * K * es, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(w.C, 0, w.M * N * 4, 0x00020000);
@@ -540,6 +555,31 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned 
         // forward on 32768 rows in 1024 pieces 3.75 -> 3.60 ms) and wide bf16 (2 x 1024 on 4096 rows in 64 445 -> 437 us), not
         // narrow bf16 (2 x 512 on 32768 rows in 256 1.59 -> 1.62 ms).
         constexpr bool EARLY = MODE == MODE_F32 || MT == 8 || MT == 2;
+        // this thread's columns of a tile: read its partial sums, add them, store them at `out`
+        constexpr unsigned NOWHERE = 0xFFFFFFF0u;
+        typedef typename std::conditional<FWD, f32x4_t, float>::type col_t;
+        const float* mine_part = part + min(m, 15) * ROW + (tid % TPR) * PER;
+        auto read_part = [&](const float* q, col_t (&o)[REC_WAVES]) {
+#pragma unroll
+            for (int k = 0; k < REC_WAVES; ++k) o[k] = *reinterpret_cast<const col_t*>(q + k * (16 * ROW));
+        };
+        auto add_store = [&](const col_t (&o)[REC_WAVES], unsigned out) {
+            if constexpr (FWD) {
+                f32x4_t v = bias;
+#pragma unroll
+                for (int k = 0; k < REC_WAVES; ++k) {
+                    v[0] += o[k][0]; v[1] += o[k][1]; v[2] += o[k][2]; v[3] += o[k][3];
+                }
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), rsC, out, 0, 17);
+            } else {
+                float v = 0.f;
+#pragma unroll
+                for (int k = 0; k < REC_WAVES; ++k) v += o[k];
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsC, out, 0, 17);
+            }
+        };
+        unsigned out_before = NOWHERE;   // two buffers: where the tile before goes, which is in buffer buf ^ 1
+        int buf = 0;
         for (int b0 = s_lo; b0 < s_hi; b0 += REC_THREADS) {
             const int n = min(s_hi - b0, REC_THREADS);
             s_row[tid] = row_of(min(b0 + tid, total - 1));
@@ -548,8 +588,10 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned 
             for (int r0 = 0; r0 < n; r0 += 16) {
                 const int rows = min(16, n - r0);
                 const int out_row = s_row[r0 + min(m, 15)];
+                const unsigned out = m < rows ? ((unsigned)out_row * (unsigned)N + col) * 4u : NOWHERE;
                 if (r0 == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 else asm volatile("s_waitcnt vmcnt(1)" ::: "memory");   // (the store of the tile before)
+                col_t o[REC_WAVES];
                 if (works) {
                     f32x4_t acc[MT];
 #pragma unroll
@@ -557,31 +599,32 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned 
                     auto next = [&] {
                         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the operands have been read)
                         if (r0 + 16 < n) work_request<NB>(rsA, stage, s_row + r0 + 16, (unsigned)(K * es), b_lo, n_blk);
+                        if (BUFS == 2) read_part(mine_part + (buf ^ 1) * few_part_floats(COLS), o);
                         __builtin_amdgcn_sched_barrier(0);
                     };
                     few_stage_product<MODE, MT, NB, EVEN>(wreg, stage, part + COLS, n_blk, acc, [&] { if (EARLY) next(); });
                     if (!EARLY) next();
-                    few_stage_write<MT>(acc, rows, part + slice * (16 * ROW));
+                    few_stage_write<MT>(acc, rows, part + buf * few_part_floats(COLS) + slice * (16 * ROW));
+                } else if (BUFS == 2) {
+                    read_part(mine_part + (buf ^ 1) * few_part_floats(COLS), o);
+                }
+                if (BUFS == 2) {
+                    add_store(o, out_before);
+                    out_before = out;
+                    buf ^= 1;
                 }
                 bar_lds();
-                const float* q = part + min(m, 15) * ROW + (tid % TPR) * PER;
-                const unsigned out = m < rows ? ((unsigned)out_row * (unsigned)N + col) * 4u : 0xFFFFFFF0u;
-                if constexpr (FWD) {
-                    f32x4_t v = bias;
-#pragma unroll
-                    for (int k = 0; k < REC_WAVES; ++k) {
-                        const f32x4_t o = *reinterpret_cast<const f32x4_t*>(q + k * (16 * ROW));
-                        v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3];
-                    }
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), rsC, out, 0, 17);
-                } else {
-                    float v = 0.f;
-#pragma unroll
-                    for (int k = 0; k < REC_WAVES; ++k) v += q[k * (16 * ROW)];
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsC, out, 0, 17);
+                if (BUFS == 1) {
+                    read_part(mine_part, o);
+                    add_store(o, out);
+                    bar_lds();   // (the partial sums have been read)
                 }
-                bar_lds();   // (the partial sums have been read)
             }
+        }
+        if (BUFS == 2) {
+            col_t o[REC_WAVES];
+            read_part(mine_part + (buf ^ 1) * few_part_floats(COLS), o);
+            add_store(o, out_before);
         }
         if (wave == 0) have = lane < PIPE_GROUPS ? ld_agent(w.sync + lane) : 0;   // (arrives while the stores complete)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

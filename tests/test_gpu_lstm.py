@@ -268,6 +268,16 @@ def test_workers_hold_the_weights_several_times(ver, compute, hidden):
     assert meta["n_seq"] > 3 * 32
 
 
+@pytest.mark.parametrize("hidden,n_envs,steps", [(384, 120, 10), (512, 60, 13), (384, 900, 2)])
+def test_fp32_chunks_of_many_pieces(ver, hidden, n_envs, steps):
+    """Two-layer launch in fp32 whose weights two teams of workers hold: chunks of about 256 rows (6 and 8 timesteps of 40
+    and 20 pieces per group), and chunks of more rows than a worker numbers at once (2 timesteps of 300 pieces)."""
+    w = wl.scaled(wl.WORKLOADS["manip"], budget=steps * n_envs, n_envs=n_envs, n_layers=2, hidden=hidden, input_dim=12, p_done=0.0,
+                  minibatches=1, speed_sigma=0.0)
+    _, meta = case(ver, w, seed=70 + hidden, compute=0)
+    assert meta["M"] >= 48 * meta["T_max"] and meta["n_seq"] > 3 * 16
+
+
 def poisoned(ver, w, seed, compute, poison):
     """Forward (and backward) runs with clean initial states and with `poison` applied to them; poison(h0, n_seq) changes
     the states in place."""
