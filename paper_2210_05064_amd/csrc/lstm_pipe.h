@@ -646,15 +646,6 @@ __device__ __forceinline__ int xcc_ticket(int* tickets, int& xcc) {
     return s_t;
 }
 
-// The kernels below run one of three roles per workgroup, each with its own set of arguments.  Taken by value, all
-// of them are loaded into scalar registers at the top of the kernel and stay there (or rather in spill lanes, from
-// where the time loops fetch them again and again); read in place from the kernel-argument segment (the struct is
-// the kernel's only parameter, so it sits at its start), a role loads what it uses where it uses it.
-template <typename A>
-__device__ __forceinline__ const A& pipe_args_in_place(const A&) {
-    return *(const A*)__builtin_amdgcn_kernarg_segment_ptr();   // (from the constant address space: only a C-style cast does that)
-}
-
 struct PipeFwdArgs {
     RecFwdArgs l0, l1;   // producer (layer 0) and consumer (layer 1)
     PipeWork work;

@@ -260,7 +260,8 @@ template <> __device__ __forceinline__ void st_row4<float>(float* p, float a, fl
 // points there): equal addresses are broadcast by the LDS, so with one or two alive pieces the LDS traffic
 // of the step drops sixteen-fold, and the reads stay unconditional so that they can be issued ahead.
 // NI > 0: exactly NI blocks, straight-line code (all LDS reads can be issued ahead of the MFMAs).
-// NI == 0: ni_rt blocks (<= REC_NI), guarded: the general, slower path.
+// NI == 0: ni_rt blocks (<= NW), guarded: the general, slower path.  (NW is what the widths of the arithmetic need: guards
+// for more blocks than that only cost scalar registers: 3.6 -> 2.8 us backward with 24 pieces at H = 64 in fp32.)
 template <int MODE, int NI, int NT, int NW>
 __device__ __forceinline__ void mma_tiles(const f32x4_t (&wreg)[NW], const typename RecGeom<MODE>::E* brow, int stride,
                                           int ni_rt, const typename RecGeom<MODE>::E* blast, f32x4_t (&acc)[REC_NTC]) {
@@ -307,15 +308,18 @@ __device__ __forceinline__ void mma_tiles(const f32x4_t (&wreg)[NW], const typen
     } else {
 #pragma unroll
         for (int q = 0; q < NT; ++q) acc[q] = zero;
+        constexpr int STEP = NW > 8 ? 2 : 1;   // (H / 32 blocks are an even number, H / 64 any)
 #pragma unroll
-        for (int i = 0; i < NW; ++i)
-            if (i < ni_rt) {
+        for (int i0 = 0; i0 < NW; i0 += STEP)
+            if (i0 < ni_rt) {
 #pragma unroll
-                for (int q = 0; q < NT; ++q) {
-                    const typename RecGeom<MODE>::E* src = (q + 1 < NT) ? brow : blast;
-                    const f32x4_t b = *reinterpret_cast<const f32x4_t*>(src + q * 16 * stride + i * KBLK);
-                    acc[q] = mfma_block<MODE>(wreg[i], b, acc[q]);
-                }
+                for (int i = i0; i < i0 + STEP; ++i)
+#pragma unroll
+                    for (int q = 0; q < NT; ++q) {
+                        const typename RecGeom<MODE>::E* src = (q + 1 < NT) ? brow : blast;
+                        const f32x4_t b = *reinterpret_cast<const f32x4_t*>(src + q * 16 * stride + i * KBLK);
+                        acc[q] = mfma_block<MODE>(wreg[i], b, acc[q]);
+                    }
             }
     }
 }
@@ -419,21 +423,12 @@ __device__ __forceinline__ void st_row4_buf(__amdgpu_buffer_rsrc_t rs, int off, 
 // instruction costs the same whether 4 or 64 of its lanes carry data.)
 constexpr int REC_PRE = 2;   // piece tiles whose per-step inputs are prefetched one timestep ahead
 
-// Register slot i of a wave holds operand block blk_of(i) of its share, for the weights and for the rows
-// alike: the rotation `rot` (different in every workgroup) keeps the workgroups of a group, which all read the
-// same rows at the same moment, from asking L2 for the same line at the same time.
-template <int NBW, bool STATIC>
-__device__ __forceinline__ int blk_of(int i, int rot, int nb) {
-    const int v = i + rot;
-    if (STATIC) return v % NBW;
-    return v >= nb ? v - nb : v;
-}
 // acc[tt] = sum over the wave's operand blocks of W(tile tt, block) * B(block): the B blocks (16 bytes per lane from
 // the staged rows at p) are fetched from LDS a few at a time, ahead of the MFMAs that consume them; with fewer than
 // four tiles the sum is split over independent accumulator chains so that consecutive MFMAs do not wait for each
 // other's result.
 template <int MODE, int TPW, int NBW, bool STATIC>
-__device__ __forceinline__ void mma_rows(const f32x4_t (&wreg)[TPW * NBW], const typename RecGeom<MODE>::E* p, int nb, int rot,
+__device__ __forceinline__ void mma_rows(const f32x4_t (&wreg)[TPW * NBW], const typename RecGeom<MODE>::E* p, int nb,
                                          f32x4_t (&acc)[TPW]) {
     constexpr int CH = TPW >= 4 ? 1 : (TPW == 2 ? (STATIC ? 2 : 1) : 4);
     constexpr int BCH = NBW < 8 ? NBW : 8;
@@ -448,7 +443,7 @@ __device__ __forceinline__ void mma_rows(const f32x4_t (&wreg)[TPW * NBW], const
 #pragma unroll
         for (int i = 0; i < BCH; ++i)
             if (c0 + i < NBW && (STATIC || c0 + i < nb))
-                b[i] = *reinterpret_cast<const f32x4_t*>(p + blk_of<NBW, STATIC>(c0 + i, rot, nb) * RecGeom<MODE>::KBLK);
+                b[i] = *reinterpret_cast<const f32x4_t*>(p + (c0 + i) * RecGeom<MODE>::KBLK);
 #pragma unroll
         for (int i = 0; i < BCH; ++i)
             if (c0 + i < NBW && (STATIC || c0 + i < nb)) {
@@ -521,6 +516,24 @@ struct RecBwdArgs {
 
 namespace ver {
 
+// The kernels below run one of three roles per workgroup, each with its own set of arguments.  Taken by value, all
+// of them are loaded into scalar registers at the top of the kernel and stay there (or rather in spill lanes, from
+// where the time loops fetch them again and again); read in place from the kernel-argument segment (the struct is
+// the kernel's only parameter, so it sits at its start), a role loads what it uses where it uses it.
+template <typename A>
+__device__ __forceinline__ const A& pipe_args_in_place(const A&) {
+    return *(const A*)__builtin_amdgcn_kernarg_segment_ptr();   // (from the constant address space: only a C-style cast does that)
+}
+// The same arguments, to be loaded again where they are used next: held in registers across a time loop that does not
+// need them, they push what it does need into spill lanes (143 v_readlane in a forward timestep at H = 1024, 13 without).
+template <typename A>
+__device__ __forceinline__ const A& args_again(const A& a) {
+    typedef const A __attribute__((address_space(4)))* P;
+    P p = (P)&a;
+    asm volatile("" : "+s"(p));
+    return *(const A*)p;
+}
+
 // Waves are (row group rg, contraction share ks): REC_WAVES = RG * KS; a wave multiplies TPW tiles of 16 gate
 // rows over 1/KS of the contraction; the workgroup owns MT = RG*TPW tiles = 4*MT hidden units.  In the
 // epilogue wave w adds the KS partial sums of tile w and updates the cells of its 4 units.
@@ -549,7 +562,6 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
     E* hprev = static_cast<E*>(a.hprev);
     const int k_lo = ((ks + rank) % KS) * (H / KS);   // which share a wave takes rotates with the rank, too
     const int nb = (H / KS) / KBLK;
-    const int rot = (rank / KS) % nb;
 
     // initial hidden state of every piece, this workgroup's columns
     for (int i = tid; i < n_seq * (UH / 4); i += REC_THREADS) {
@@ -560,8 +572,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
     }
     // From timestep t0 on at most FEW_MAX pieces of the group are alive: those timesteps run in the form of lstm_few.h.
     const int t0 = n_seq > FEW_MAX ? grp_steps(a.batch_sizes, T, FEW_MAX * X + x) : 0;
-    unsigned char* ring = static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, H);
-    few_clear_ring<MODE>(ring, H, j0, UH);
+    few_clear_ring<MODE>(static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, H), H, j0, UH);
     rec_publish(flags, rank, 1);
     REC_PROF_DECL
     REC_PROF_START();
@@ -575,7 +586,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
         const E* wrow = static_cast<const E*>(a.whh) + ((size_t)rank * ROWS + (rg * TPW + tt) * 16 + lr) * H + k_lo + lk * VEC;
 #pragma unroll
         for (int i = 0; i < NBW; ++i)
-            wreg[tt * NBW + i] = (STATIC || i < nb) ? *reinterpret_cast<const f32x4_t*>(wrow + blk_of<NBW, STATIC>(i, rot, nb) * KBLK)
+            wreg[tt * NBW + i] = (STATIC || i < nb) ? *reinterpret_cast<const f32x4_t*>(wrow + i * KBLK)
                                                     : f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
     // The weights have arrived before the time loop starts, and the compiler has to know: without a use of the
@@ -668,7 +679,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
                 // dead lanes of the last tile read its first row: equal addresses are broadcast by the LDS
                 const int r = q * 16 + ((q * 16 + lr < rows) ? lr : 0);
                 f32x4_t acc[TPW];
-                mma_rows<MODE, TPW, NBW, STATIC>(wreg, sB + r * stride + k_lo + lk * VEC, nb, rot, acc);
+                mma_rows<MODE, TPW, NBW, STATIC>(wreg, sB + r * stride + k_lo + lk * VEC, nb, acc);
 #pragma unroll
                 for (int tt = 0; tt < TPW; ++tt) sRed[((ks * MT + rg * TPW + tt) * ntc + q) * 64 + lane] = acc[tt];
             }
@@ -755,7 +766,10 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
         REC_PROF_STEP();
     }
     }
-    if (t0 < T && !few_fwd<MODE, MT, PIPE>(a, ps, rank, t0, T, flags, pl, c_wait, ring, smem)) return;
+    if (t0 < T) {
+        const RecFwdArgs f = args_again(a);
+        if (!few_fwd<MODE, MT, PIPE>(f, ps, rank, t0, T, flags, pl, c_wait, static_cast<unsigned char*>(f.ring) + ps.id * few_ring_bytes(MODE, f.H), smem)) return;
+    }
     if (PIPE == PIPE_PRODUCER && rank == 0) {   // the last timestep is complete once every flag says so
         if (T > 0 && !rec_wait(flags, G, T + 1, a.err)) return;
         if (tid == 0) st_agent(pl.progress, T);
@@ -763,7 +777,8 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
 }
 
 template <int MODE, int TPW, int KS, int NBW, bool STATIC>
-__global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_rec_fwd_kernel(RecFwdArgs a) {
+__global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_rec_fwd_kernel(RecFwdArgs by_value) {
+    const RecFwdArgs& a = pipe_args_in_place<RecFwdArgs>(by_value);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int grp;
     const int rank = rec_rank(a.ticket, a.G, grp);
@@ -801,7 +816,7 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& a, int rank, cons
     typedef typename RecGeom<MODE>::E E;
     constexpr int PAD = RecGeom<MODE>::PAD, KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC;
     constexpr int UH = 16 * MT;
-    constexpr int NW = NI > 0 ? NI : REC_NI;
+    constexpr int NW = NI > 0 ? NI : (MODE == MODE_F32 ? 16 : (MT == 2 ? REC_NI : 8));   // (H / 32 fp32, H / 64 and H / 32 bf16)
     const int G = a.G;
 
     const int H = a.H, K = 4 * H, stride = K + PAD, ntc = a.ntc;

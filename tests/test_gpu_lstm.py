@@ -268,6 +268,16 @@ def test_workers_hold_the_weights_several_times(ver, compute, hidden):
     assert meta["n_seq"] > 3 * 32
 
 
+@pytest.mark.parametrize("compute,hidden", [(0, 192), (0, 384), (0, 448), (1, 192), (1, 384), (1, 448), (1, 960)])
+def test_general_widths_with_many_pieces(ver, compute, hidden):
+    """One layer at widths without a loop of their own, up to the most operand blocks that the general form of each
+    arithmetic holds (14 of 16 in fp32, 7 of 8 and 30 of 32 in bf16), groups of 20 pieces throughout."""
+    w = wl.scaled(wl.WORKLOADS["manip"], budget=640, n_envs=160, n_layers=1, hidden=hidden, input_dim=12, p_done=0.0,
+                  minibatches=1, speed_sigma=0.0)
+    _, meta = case(ver, w, seed=80 + hidden, compute=compute, x_bf16=bool(compute))
+    assert meta["batch_sizes"][-1] > 8 * 16
+
+
 @pytest.mark.parametrize("hidden,n_envs,steps", [(384, 120, 10), (512, 60, 13), (384, 900, 2)])
 def test_fp32_chunks_of_many_pieces(ver, hidden, n_envs, steps):
     """Two-layer launch in fp32 whose weights two teams of workers hold: chunks of about 256 rows (6 and 8 timesteps of 40
