@@ -318,7 +318,7 @@ struct LstmWs {
     long long* prof;   // [128] phase counters of the recurrent kernels (forward 0..15, backward 16..31; +32: consumer layer), timeline, workers
     LayerWs layer[8];
     void* dz[2];       // [M, 4H] operand type; the second one only when two layers share a launch
-    int* pipe;         // hand-over words of a two-layer launch: progress[8], queues at [8], done[][] from [16]
+    int* pipe;         // hand-over words of a two-layer launch: progress[8], done[][] from [16]
     int pipe_words;
     int* plan[2];      // which pieces every group of a two-layer launch runs, and its chunks (lstm_pipe.h): forward, backward
     float* plan_scratch;
@@ -482,10 +482,11 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     // 8 waves = row groups x shares of the contraction (TPW tiles of 16 gate rows per wave): a workgroup owns
     // 8 tiles (32 units) when 32 workgroups need all of H/32 units each, else 4 tiles (16 units)
     const bool wide = H / 16 > REC_MAX_GROUP;
-    // Shares of the contraction: with 8 tiles per workgroup two (a wave then reads 16 operand blocks per piece tile
-    // and the cell update adds two partial sums; measured 2.7 % faster than four shares, which read less from LDS but
-    // reduce more: the group that bounds a launch has one or two alive pieces, whose reads are broadcasts; one share,
-    // without any reduction, is 9 % slower), with 4 tiles four (two was measured 0.4 % slower on H = 512).
+    // Shares of the contraction in timesteps with more than 16 alive pieces of a group: with 8 tiles per workgroup two (a
+    // wave then reads 16 operand blocks per piece tile and the cell update adds two partial sums; four read less from LDS
+    // but reduce more: H = 1024, one layer, 32 / 48 / 64 pieces 5.70 / 9.04 / 12.3 us per timestep with two, 5.83 / 9.41 / 12.5 with
+    // four, the same below 24), with 4 tiles four (H = 512, one layer, 17 / 32 / 64 pieces 3.28 / 3.53 / 5.9 us with four, 3.35 /
+    // 3.70 / 6.2 with two; H = 256 3.55 / 3.87 / 6.6 and 4.06 / 4.38 / 7.8).
     const bool quarter = MODE == MODE_F32 || (!wide && H % 128 == 0);   // a quarter of H is a whole number of operand blocks
     const int ks = quarter ? 4 : 2;
     const int mt = wide ? 8 : 4;

@@ -11,7 +11,7 @@
 //              into the consumer's input (forward: gates_1 = h_0 W_ih1^T + b; backward: dh_0 = dz_1 W_ih1)
 //
 // Which pieces a group runs.  A timestep of a time loop costs a fixed latency (one exchange between the group's
-// workgroups, ~3 us) plus a little per alive piece, and the launch lasts as long as its slowest group.  The
+// workgroups, 1.1 to 1.7 us) plus a little per alive piece, and the launch lasts as long as its slowest group.  The
 // pieces are sorted longest first, so they are cut into three blocks of consecutive pieces: group 0 gets the few
 // longest ones (its chain of T_max dependent steps is what bounds the launch, so its steps should be the
 // cheapest), the last group the many short ones (few steps, each with many pieces).  lstm_pipe_plan_kernel
@@ -22,13 +22,13 @@
 // than 16 k alive pieces are those of the block's piece number 16 k.  Producer and
 // consumer group g run the same block, and everything between them is per group: chunks of the group's own
 // timesteps, tiles over the group's own rows (gathered: a group's rows of a timestep are consecutive, those of
-// a chunk are not), a queue and completion counters of its own.  So a group never waits for another one: with
+// a chunk are not), completion counters of its own.  So a group never waits for another one: with
 // the pieces dealt round-robin all groups had to march in step, and every step paid for a third of all alive pieces.
 //
 // Hand-over (lstm_rec.h, PipeLink): producer rows are written through to memory and their completion is
-// published per group; the workers of one XCD, which hold all of W_ih1 in their registers, take the chunk, write
-// their columns of the result through, wait for the stores and count themselves in done[group][chunk]; the consumer
-// group waits until that count has reached the number of workers.  Waiting only ever points backwards along
+// published per group; every chunk belongs to a fixed set of workers that hold all of W_ih1 in their registers
+// (work_deal); they write their columns of the result through, wait for the stores and count themselves in
+// done[group][chunk]; the consumer group waits until that count has reached the number of the set's workers.  Waiting only ever points backwards along
 // producer -> worker -> consumer and every worker takes a group's chunks in the order its consumer needs them,
 // so the launch cannot deadlock; every wait is bounded and raises the shared error word on time-out.
 #pragma once
@@ -403,8 +403,9 @@ __device__ __forceinline__ PieceSet pipe_pieces_of(const int* plan, int g) {
 // and per chunk the round trips of progress word, rows and stores (about 4 us).  (128 x 256 tiles that streamed the
 // weights from L2 through LDS took 18 us forward and 54 us backward each, 14 and 38 us for a handful of rows: the
 // consumer started and ended that much later, and 32768 rows kept the two XCDs busy for 2.9 ms.)
-// A net of up to 320 units needs fewer than half of the 64 workers for its weights: the others hold them again (work_deal).
-// One team per XCD left 28 of 32 CUs idle at H = 64 and made the workers the bound of launches over hundreds of pieces.
+// Where a third of the 64 workers or fewer hold the weights (up to 320 units; 576 and 640), the others hold them again
+// (work_deal).  One team per XCD left 28 of 32 CUs idle at H = 64 and made the workers the bound of launches over hundreds
+// of pieces: fp32 forward on 32768 rows in 1024 pieces 2.40 ms, now 1.44 (H = 320 in 256 pieces 3.9 -> 2.6 ms).
 constexpr int WORK_LDS_T = 2047;   // timesteps whose row offsets are kept in LDS
 inline __host__ __device__ size_t work_lds_bytes(int cols, int nb, int bufs) {
     return (size_t)bufs * few_part_floats(cols) * sizeof(float) + (size_t)REC_WAVES * few_stage_bytes(nb) + (WORK_LDS_T + 1) * sizeof(int);

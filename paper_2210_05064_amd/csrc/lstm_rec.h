@@ -257,8 +257,8 @@ template <> __device__ __forceinline__ void st_row4<float>(float* p, float a, fl
 
 // acc[q] += W(16 x k-range) * B_q(k-range x 16) for NT staged tiles; W blocks come from registers, B from LDS.
 // In the last (possibly partly empty) tile, lanes whose piece does not exist read piece 0 instead (blast
-// points there): equal addresses are broadcast by the LDS, so with one or two alive pieces the LDS traffic
-// of the step drops sixteen-fold, and the reads stay unconditional so that they can be issued ahead.
+// points there): equal addresses are broadcast by the LDS, so that a tile of one piece costs little LDS traffic and
+// the reads stay unconditional and can be issued ahead.
 // NI > 0: exactly NI blocks, straight-line code (all LDS reads can be issued ahead of the MFMAs).
 // NI == 0: ni_rt blocks (<= NW), guarded: the general, slower path.  (NW is what the widths of the arithmetic need: guards
 // for more blocks than that only cost scalar registers: 3.6 -> 2.8 us backward with 24 pieces at H = 64 in fp32.)
@@ -417,10 +417,8 @@ __device__ __forceinline__ void st_row4_buf(__amdgpu_buffer_rsrc_t rs, int off, 
 // A wave holds TPW 16-row tiles of the weight matrix over its share of the contraction, NBW 16-byte operand
 // blocks per tile (wreg[tile * NBW + block]).  For one tile of 16 pieces it reads the matching blocks of the
 // staged rows from LDS once, multiplies them with all its tiles, and leaves its partial sums in LDS for the
-// wave that owns the tile in the epilogue.  Sharing the contraction between waves is what keeps the number of
-// LDS reads down: with one or two alive pieces the step is bound by LDS instructions, not by the MFMAs.
-// (Operand blocks loaded straight from the exchanged rows in L2 were measured slower than staging: a load
-// instruction costs the same whether 4 or 64 of its lanes carry data.)
+// wave that owns the tile in the epilogue.  Sharing the contraction between waves keeps the number of LDS reads down
+// (run_fwd has both sides of the choice of KS).
 constexpr int REC_PRE = 2;   // piece tiles whose per-step inputs are prefetched one timestep ahead
 
 // acc[tt] = sum over the wave's operand blocks of W(tile tt, block) * B(block): the B blocks (16 bytes per lane from
