@@ -55,17 +55,20 @@ inline __host__ __device__ int pipe_sync_words(int M) { return 16 + PIPE_GROUPS 
 // Predicted microseconds of a timestep: step + piece * b + tile * (ceil(b / 16) - 1) (b alive pieces of the group).
 struct PlanCost {
     float step, piece, tile;
-    int chunk_rows;   // rows per chunk that groups of more than 16 pieces aim at where the workers set the pace; 0: never
+    int chunk_rows, dense;   // rows per chunk that groups of more than 16 pieces aim at from `dense` alive pieces per timestep on
+                             // (average over the launch), where the workers set the pace; 0: never
 };
 // Timesteps per chunk by the pieces of the group: a chunk is handed on when it is complete, so the consumer starts and
 // ends that much later than the producer; it costs a worker about 4 us beside the product of its rows.
 constexpr int PLAN_CT_FEW = 8, PLAN_CT_MANY = 2;   // up to 16, more pieces
 // fp32 forward from 384 units on, where only two teams of workers hold the weights and a tile costs them 1.8 to 2.5 us:
-// with PLAN_DENSE alive pieces per timestep (average over the launch) or more the workers are behind and long chunks pay,
-// with fewer the delay costs more.  us per timestep with 32 equally long pieces per group (96 alive), chunks of 2
+// with 48 alive pieces per timestep or more the workers are behind and long chunks pay, with fewer the delay costs more.  us per timestep with 32 equally long pieces per group (96 alive), chunks of 2
 // timesteps -> of 256 rows: H = 384 9.0 -> 7.0, 512 10.7 -> 8.5; us per launch: 512 units, 32768 rows in 256 pieces (64
 // alive) 3750 -> 3080, 8192 in 256 (64) 1075 -> 962, 4096 in 128 (39) 557 -> 611, 4096 in 64 (23) 604 -> 680.
-constexpr int PLAN_DENSE = 48, PLAN_CHUNK_ROWS = 256;
+// bf16 forward at 512 units: the same from 90 alive pieces on, with shorter chunks.  us per launch over equally long pieces,
+// 2 timesteps -> 192 rows: 64 timesteps of 32 / 48 pieces per group 296 -> 256 / 359 -> 324, 128 timesteps 504 -> 529 / 702 -> 723, 24
+// pieces (72 alive) 223 -> 253; 8192 rows in 192 pieces of about equal length 354 -> 318.  (Narrower layers have workers to spare: 448
+// units, 32 timesteps of 48 pieces 222 -> 251.)
 // us per timestep of launches over equally long pieces (two layers; time of a launch against its timesteps):
 //   pieces               1     2     4     8    16    32    64
 //   bf16 H=1024 fwd   1.37  1.35  1.38  1.96  2.6    5.1  11.2      bwd  1.68  1.88  2.16  2.49  3.45  8.9  17.1
@@ -75,9 +78,9 @@ constexpr int PLAN_DENSE = 48, PLAN_CHUNK_ROWS = 256;
 // single timesteps took 0.1 to 0.3 us longer; the cuts between the groups depend on the ratios only.
 inline PlanCost plan_cost(int mode, bool wide, bool fwd, int G) {
     if (mode == MODE_F32)
-        return fwd ? PlanCost{1.45f, 0.19f, 1.f, 2 * REC_MAX_GROUP / G < 3 ? PLAN_CHUNK_ROWS : 0} : PlanCost{1.6f, 0.27f, 0.f, 0};
-    if (wide) return fwd ? PlanCost{1.38f, 0.042f, 2.4f, 0} : PlanCost{1.75f, 0.08f, 4.6f, 0};
-    return fwd ? PlanCost{1.17f, 0.023f, 1.2f, 0} : PlanCost{1.38f, 0.04f, 1.7f, 0};
+        return fwd ? PlanCost{1.45f, 0.19f, 1.f, 2 * REC_MAX_GROUP / G < 3 ? 256 : 0, 48} : PlanCost{1.6f, 0.27f, 0.f, 0, 0};
+    if (wide) return fwd ? PlanCost{1.38f, 0.042f, 2.4f, 0, 0} : PlanCost{1.75f, 0.08f, 4.6f, 0, 0};
+    return fwd ? PlanCost{1.17f, 0.023f, 1.2f, G == REC_MAX_GROUP ? 192 : 0, 90} : PlanCost{1.38f, 0.04f, 1.7f, 0, 0};
 }
 
 struct PipeWork {
@@ -216,7 +219,8 @@ __device__ __forceinline__ void plan_body(const int32_t* __restrict__ batch_size
         const int lo = s_kb[d][g], cap = s_kb[d][g + 1] - lo;
         int* plan = d == 0 ? plan_fwd : plan_bwd;
         plan[PLAN_T + g] = cap > 0 ? (int)len[lo] : 0;
-        const int aim = M >= PLAN_DENSE * T ? (d == 0 ? pc_fwd : pc_bwd).chunk_rows : 0;
+        const PlanCost& p = d == 0 ? pc_fwd : pc_bwd;
+        const int aim = M >= p.dense * T ? p.chunk_rows : 0;
         plan[PLAN_CT + g] = cap <= 16 ? PLAN_CT_FEW : min(max(aim / cap, PLAN_CT_MANY), PLAN_CT_FEW);
     }
 }

@@ -288,6 +288,16 @@ def test_fp32_chunks_of_many_pieces(ver, hidden, n_envs, steps):
     assert meta["M"] >= 48 * meta["T_max"] and meta["n_seq"] > 3 * 16
 
 
+@pytest.mark.parametrize("n_envs,steps", [(112, 13), (150, 9)])
+def test_bf16_chunks_of_many_pieces(ver, n_envs, steps):
+    """Two-layer launch in bf16 at 512 units with 90 alive pieces per timestep or more: chunks of about 192 rows (5 and 3
+    timesteps of 37 and 50 pieces per group, the last chunk shorter)."""
+    w = wl.scaled(wl.WORKLOADS["manip"], budget=steps * n_envs, n_envs=n_envs, n_layers=2, hidden=512, input_dim=12, p_done=0.0,
+                  minibatches=1, speed_sigma=0.0)
+    _, meta = case(ver, w, seed=90 + n_envs, compute=1, x_bf16=True)
+    assert meta["M"] >= 90 * meta["T_max"] and meta["n_seq"] > 3 * 16
+
+
 def poisoned(ver, w, seed, compute, poison):
     """Forward (and backward) runs with clean initial states and with `poison` applied to them; poison(h0, n_seq) changes
     the states in place."""
