@@ -414,21 +414,12 @@ __device__ __forceinline__ void gemm_tn_dma_body(
 
     for (int kt = 0; kt < TN_STAGES - 1 && kt < nk; ++kt) issue(kt);
     for (int kt = 0; kt < nk; ++kt) {
-        // this wave's NA + 2 loads of stage kt have landed; up to STAGES - 2 younger stages may be in flight
+        // this wave's loads of stage kt have landed; up to STAGES - 2 younger stages may be in flight
+        constexpr int LOADS = NA + 2 + (XTRA ? 1 : 0);   // per wave and stage, see issue()
         const int younger = min(nk - 1 - kt, TN_STAGES - 2);
-        if (WM == 8) {
-            if (younger >= 1 && XTRA) asm volatile("s_waitcnt vmcnt(7)" ::: "memory");
-            else if (younger >= 1) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        } else if (XTRA) {   // 7 loads per wave and stage
-            if (younger >= 2) asm volatile("s_waitcnt vmcnt(14)" ::: "memory");
-            else if (younger == 1) asm volatile("s_waitcnt vmcnt(7)" ::: "memory");
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        } else {
-            if (younger >= 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-            else if (younger == 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        }
+        if (TN_STAGES == 4 && younger >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LOADS) : "memory");
+        else if (younger >= 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         bar_lds();   // everyone's loads of stage kt have landed, and everyone is done reading stage kt-1
         if (kt + TN_STAGES - 1 < nk) issue(kt + TN_STAGES - 1);
         const unsigned char* st = smem + (kt % TN_STAGES) * TN_STAGE_BYTES;
