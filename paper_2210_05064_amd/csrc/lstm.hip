@@ -310,7 +310,7 @@ struct LayerWs {
     float* c;     // [M, H]
     float* hout;  // [M, H]
     void* hprev;  // [M, H] operand type
-    void* hcopy;  // [M, H] operand type: h_t, for the workers of a two-layer launch
+    void* hcopy;  // [M, H] operand type: h_t, for the workers of a two-layer launch (lower layer of a pair only)
 };
 struct LstmWs {
     int* err;          // word 0 of the workspace
@@ -378,10 +378,10 @@ inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws)
         L.c = cv.take<float>(Mz * H);
         L.hout = cv.take<float>(Mz * H);
         L.hprev = cv.take<char>(Mz * H * es);
-        L.hcopy = (c.n_layers == 2 && l == 0) ? cv.take<char>(Mz * H * es) : nullptr;
+        L.hcopy = (l % 2 == 0 && l + 1 < c.n_layers) ? cv.take<char>(Mz * H * es) : nullptr;
     }
     ws->dz[0] = cv.take<char>(Mz * 4 * H * es);
-    ws->dz[1] = c.n_layers == 2 ? cv.take<char>(Mz * 4 * H * es) : ws->dz[0];
+    ws->dz[1] = c.n_layers >= 2 ? cv.take<char>(Mz * 4 * H * es) : ws->dz[0];
     ws->dh[0] = cv.take<float>(Mz * H);
     ws->dh[1] = cv.take<float>(Mz * H);
     ws->dh_state = cv.take<float>(2 * Mz * H);
@@ -470,14 +470,22 @@ inline void pipe_work(const LstmWs& ws, int dir, int M, const int32_t* t_off, Pi
     pw->err = ws.err;
 }
 
+// Networks of several layers run two layers at a time in one launch each (lstm_pipe.h), the layers numbered 2i and 2i + 1;
+// the top layer of an odd number has a launch of its own.  A pair's time loops advance side by side on three XCDs each,
+// where one after the other would have all eight: us per forward and backward pass of two layers, a launch per layer
+// -> one for both: 300 rows (longest piece 98) at 512 units 632 -> 357, 8192 (473) at 1024 4204 -> 2417; closest where
+// hundreds of short pieces keep every XCD busy: 8192 rows in 538 pieces (86) at 320 units 1121 -> 1103.  Three layers of 320 on
+// 3001 rows in 36 pieces (bf16): 2430 -> 1843 us.
+inline bool pairs_of_layers(const ver_lstm_cfg& c) { return c.n_layers >= 2 && !c.layer_by_layer; }
+
 template <int MODE>
 int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, const int32_t* batch_sizes,
             const int32_t* t_off, const float* h0, const float* c0, int seq_cap, const float* const* w,
             float* head_out, float* value, LstmWs& ws, hipStream_t s) {
     typedef typename RecGeom<MODE>::E E;
     const int H = c.hidden, A = c.act_dim;
-    const bool pipelined = c.n_layers == 2 && !c.layer_by_layer;   // both time loops in one launch
-    if (!pipelined) fill_words(ws.err, 1, 0, s);
+    const bool pairs = pairs_of_layers(c);   // two layers' time loops in one launch
+    if (!pairs) fill_words(ws.err, 1, 0, s);
 
     // 8 waves = row groups x shares of the contraction (TPW tiles of 16 gate rows per wave): a workgroup owns
     // 8 tiles (32 units) when 32 workgroups need all of H/32 units each, else 4 tiles (16 units)
@@ -497,7 +505,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     const int few_nb = wide ? FewBlocks<MODE, true>::fwd : FewBlocks<MODE, false>::fwd;
     if (few_lds_bytes(16 * mt, few_nb) > lds) lds = few_lds_bytes(16 * mt, few_nb);
     const size_t work_lds = work_lds_bytes(16 * mt, few_nb, work_bufs<MODE, true>());
-    if (pipelined && work_lds > lds) lds = work_lds;
+    if (pairs && work_lds > lds) lds = work_lds;
     const int nb = (H / ks) / RecGeom<MODE>::KBLK;
 
     // operand-type copies of every layer's weights (and their transposes) and the summed biases: one launch
@@ -536,16 +544,16 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
                                                4 * H, M, 4 * H, H, L.bias, 0, ws.gemm_part, true, s);
         }
     };
-    auto rec_args = [&](int l) {
+    auto rec_args = [&](int l, bool consumer = false) {
         LayerWs& L = ws.layer[l];
         RecFwdArgs ra;
         ra.info = info; ra.batch_sizes = batch_sizes; ra.t_off = t_off;
         ra.gates = L.gates; ra.c = L.c; ra.hout = L.hout; ra.hprev = L.hprev; ra.hcopy = L.hcopy; ra.whh = L.whh;
-        ra.ring = ws.ring + (pipelined && l == 1 ? PIPE_GROUPS * few_ring_bytes(MODE, H) : 0);
+        ra.ring = ws.ring + (consumer ? PIPE_GROUPS * few_ring_bytes(MODE, H) : 0);
         ra.h0 = h0 ? h0 + (size_t)l * seq_cap * H : nullptr;
         ra.c0 = c0 ? c0 + (size_t)l * seq_cap * H : nullptr;
         ra.H = H; ra.seq_cap = seq_cap; ra.M = M; ra.flags = ws.flags; ra.ticket = ws.flags + 8 * REC_MAX_GROUP;
-        ra.err = ws.err; ra.prof = ws.prof + (pipelined && l == 1 ? 32 : 0); ra.prof_all = ws.prof;
+        ra.err = ws.err; ra.prof = ws.prof + (consumer ? 32 : 0); ra.prof_all = ws.prof;
         ra.G = H / (4 * mt); ra.ntc = ntc;
         return ra;
     };
@@ -569,28 +577,32 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         } } while (0)
 
     prep_all();
-    if (pipelined) {
-        project(0);
-        pipe_prepare_fwd(ws, MODE, wide, H / (4 * mt), M, info, batch_sizes, s);
-        PipeFwdArgs pa;
-        pa.l0 = rec_args(0);
-        pa.l1 = rec_args(1);
-        pa.work.A = ws.layer[0].hcopy; pa.work.B = ws.layer[1].wih; pa.work.C = ws.layer[1].gates;
-        pa.work.bias = ws.layer[1].bias; pa.work.K = H; pa.work.N = 4 * H;
-        pipe_work(ws, 0, M, t_off, &pa.work);
-        pa.work.G = pa.l0.G;
-        ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
-        VER_FWD_DISPATCH(lstm_pipe_fwd_kernel, pa);
-        if (!ok) return VER_EHIP;
-    } else {
-        for (int l = 0; l < c.n_layers; ++l) {
-            project(l);
+    bool planned = false;
+    for (int l = 0; l < c.n_layers;) {
+        project(l);
+        if (pairs && l + 1 < c.n_layers) {
+            // the plan (of the packing: the same for every pair) and the first pair's synchronisation words from one kernel
+            if (!planned) pipe_prepare_fwd(ws, MODE, wide, H / (4 * mt), M, info, batch_sizes, s);
+            else fill_words(ws.flags, (size_t)(ws.pipe + ws.pipe_words - ws.flags), 0, s);
+            planned = true;
+            PipeFwdArgs pa;
+            pa.l0 = rec_args(l);
+            pa.l1 = rec_args(l + 1, true);
+            pa.work.A = ws.layer[l].hcopy; pa.work.B = ws.layer[l + 1].wih; pa.work.C = ws.layer[l + 1].gates;
+            pa.work.bias = ws.layer[l + 1].bias; pa.work.K = H; pa.work.N = 4 * H;
+            pipe_work(ws, 0, M, t_off, &pa.work);
+            pa.work.G = pa.l0.G;
+            ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
+            VER_FWD_DISPATCH(lstm_pipe_fwd_kernel, pa);
+            l += 2;
+        } else {
             fill_words(ws.flags, REC_FLAG_WORDS, 0, s);
             RecFwdArgs ra = rec_args(l);
             ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
             VER_FWD_DISPATCH(lstm_rec_fwd_kernel, ra);
-            if (!ok) return VER_EHIP;
+            l += 1;
         }
+        if (!ok) return VER_EHIP;
     }
 #undef VER_FWD_DISPATCH
 #undef VER_FWD_LAUNCH
@@ -608,12 +620,12 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     typedef typename RecGeom<MODE>::E E;
     const int H = c.hidden, A = c.act_dim, nl = c.n_layers;
     const float* h_top = ws.layer[nl - 1].hout;
-    const bool pipelined = nl == 2 && !c.layer_by_layer;   // both time loops in one launch
+    const bool pairs = pairs_of_layers(c), top_pair = pairs && nl % 2 == 0;   // two layers' time loops in one launch
     // heads
     {
     ProfScope prof(VER_PROF_HEADS_BWD, s);
     hipLaunchKernelGGL(heads_bwd_dh_kernel, dim3((H / 4 + 255) / 256, (M + HB_ROWS - 1) / HB_ROWS), dim3(256), 0, s, d_u, d_v, M, H, A, w[4 * nl],
-                       w[4 * nl + 2], ws.dh[0], pipelined ? ws.flags : nullptr, pipelined ? (int)(ws.pipe + ws.pipe_words - ws.flags) : 0);
+                       w[4 * nl + 2], ws.dh[0], top_pair ? ws.flags : nullptr, top_pair ? (int)(ws.pipe + ws.pipe_words - ws.flags) : 0);
     const int rb_h = (M + HW_ROWS - 1) / HW_ROWS;
     hipLaunchKernelGGL(heads_wgrad_partial_kernel, dim3((H / 4 + 255) / 256, rb_h), dim3(256), 0, s, d_u, d_v, h_top, M, H,
                        A, ws.part, ws.part_b);
@@ -631,24 +643,25 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     const int few_nb = wide ? FewBlocks<MODE, true>::bwd : FewBlocks<MODE, false>::bwd;
     if (few_lds_bytes(16 * mt, few_nb) > lds) lds = few_lds_bytes(16 * mt, few_nb);
     const size_t work_lds = work_lds_bytes(16 * mt, few_nb, work_bufs<MODE, false>());
-    if (pipelined && work_lds > lds) lds = work_lds;
+    if (pairs && work_lds > lds) lds = work_lds;
     const int ni = (4 * H / ks) / RecGeom<MODE>::KBLK;
 
-    // ws.dh[l == nl-1 ? 0 : 1 ...]: gradient arriving at layer l's h; dz_of(l): its gate gradients
-    auto dz_of = [&](int l) { return pipelined ? ws.dz[l] : ws.dz[0]; };
-    auto rec_args = [&](int l, const float* dh_above) {
+    // dz_of(l): layer l's gate gradients.  The two layers of a pair (l & 1: the upper one, which is the producer here) carry
+    // their state in separate halves of the scratch; a top layer without a partner has an even number.
+    auto half = [&](int l) { return pairs ? l & 1 : 0; };
+    auto dz_of = [&](int l) { return ws.dz[half(l)]; };
+    auto rec_args = [&](int l, const float* dh_above, bool consumer = false) {
         LayerWs& L = ws.layer[l];
         RecBwdArgs ra;
         ra.info = info; ra.batch_sizes = batch_sizes; ra.t_off = t_off;
         ra.gates = L.gates; ra.c = L.c; ra.c0 = c0 ? c0 + (size_t)l * seq_cap * H : nullptr;
         ra.dh_above = dh_above; ra.dz = dz_of(l); ra.whhT = L.whhT;
-        ra.ring = ws.ring + (pipelined && l == 0 ? PIPE_GROUPS * few_ring_bytes(MODE, 4 * H) : 0);
-        // the two layers of a shared launch carry their state in separate halves of the scratch
-        ra.dh_state = ws.dh_state + (pipelined ? (size_t)l * M * H : 0);
-        ra.dc_state = ws.dc_state + (pipelined ? (size_t)l * M * H : 0);
-        ra.db_part = ws.db_part + (pipelined ? (size_t)l * REC_GROUPS * 4 * H : 0);
+        ra.ring = ws.ring + (consumer ? PIPE_GROUPS * few_ring_bytes(MODE, 4 * H) : 0);
+        ra.dh_state = ws.dh_state + (size_t)half(l) * M * H;
+        ra.dc_state = ws.dc_state + (size_t)half(l) * M * H;
+        ra.db_part = ws.db_part + (size_t)half(l) * REC_GROUPS * 4 * H;
         ra.H = H; ra.seq_cap = seq_cap; ra.flags = ws.flags; ra.ticket = ws.flags + 8 * REC_MAX_GROUP;
-        ra.err = ws.err; ra.prof = ws.prof + 16 + (pipelined && l == 0 ? 32 : 0); ra.prof_all = ws.prof;
+        ra.err = ws.err; ra.prof = ws.prof + 16 + (consumer ? 32 : 0); ra.prof_all = ws.prof;
         ra.G = H / (16 * mt); ra.ntc = ntc;
         return ra;
     };
@@ -666,9 +679,10 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             else if (ni == 4) VER_BWD_LAUNCH(KERNEL, ARGS, 1, 8, 4); \
             else VER_BWD_LAUNCH(KERNEL, ARGS, 1, 8, 0); \
         } } while (0)
-    // everything of layer l that is not the time loop: dx (optional), dW_ih, dW_hh, db
+    // Everything of layer l that is not the time loop: dx (optional), dW_ih, dW_hh, db.  A pair's upper layer comes first
+    // and leaves its weight gradients and bias sums to the launches of the lower one (last = false).
     TnGroup dw_group;
-    auto layer_grads = [&](int l, float* dx, bool flush_dw) {
+    auto layer_grads = [&](int l, float* dx, bool in_pair, bool last) {
         const int D = l == 0 ? c.input_dim : H;
         LayerWs& L = ws.layer[l];
         const E* dz = static_cast<const E*>(dz_of(l));
@@ -690,7 +704,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
                 return dw_group.add(reinterpret_cast<const bf16_t*>(dz), 4 * H, static_cast<const bf16_t*>(B), ldb, C, Nc, 4 * H, Nc, M, H);
             return false;
         };
-        if (l > 0 && pipelined && ws.layer[l - 1].hcopy) {   // the layer below left its h in operand type
+        if (l > 0 && in_pair && !last) {   // the layer below is the pair's lower one and left its h in operand type
             if (!grouped(ws.layer[l - 1].hcopy, H, gw[4 * l], D))
                 gemm_launch<MODE, E, E, true>(dz, 4 * H, static_cast<const E*>(ws.layer[l - 1].hcopy), H, gw[4 * l], D, 4 * H, D, M,
                                               nullptr, H, ws.gemm_part, true, s);
@@ -706,40 +720,39 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         if (!grouped(L.hprev, H, gw[4 * l + 1], H))
             gemm_launch<MODE, E, E, true>(dz, 4 * H, static_cast<const E*>(L.hprev), H, gw[4 * l + 1], H, 4 * H, H, M,
                                           nullptr, H, ws.gemm_part, true, s);
-        if (flush_dw) dw_group.launch(s);
+        if (last) dw_group.launch(s);
         }
-        // db_ih = db_hh = column sums of dz: the time loop left one partial sum per group (two-layer launch: both
-        // layers' sums in one launch, after the second call)
-        if (!pipelined || l == 0) {
+        // db_ih = db_hh = column sums of dz: the time loop left one partial sum per group (a pair: both layers' sums in
+        // one launch)
+        if (last) {
         ProfScope prof(VER_PROF_LSTM_DBIAS, s);
         const size_t stride = (size_t)REC_GROUPS * 4 * H;
-        if (pipelined)
-            hipLaunchKernelGGL(colsum_final_kernel, dim3((4 * H + 255) / 256, 2), dim3(256), 0, s, ws.db_part, PIPE_GROUPS, 4 * H, H,
-                               gw[2], gw[3], stride, gw[6], gw[7]);
-        else
-            hipLaunchKernelGGL(colsum_final_kernel, dim3((4 * H + 255) / 256, 1), dim3(256), 0, s, ws.db_part, REC_GROUPS, 4 * H, H,
-                               gw[4 * l + 2], gw[4 * l + 3], stride, static_cast<float*>(nullptr), static_cast<float*>(nullptr));
+        float* const* g = gw + 4 * l;
+        hipLaunchKernelGGL(colsum_final_kernel, dim3((4 * H + 255) / 256, in_pair ? 2 : 1), dim3(256), 0, s, ws.db_part,
+                           in_pair ? PIPE_GROUPS : REC_GROUPS, 4 * H, H, g[2], g[3], stride, in_pair ? g[6] : nullptr, in_pair ? g[7] : nullptr);
         }
     };
 
-    if (pipelined) {
-        PipeBwdArgs pa;   // (the launch's synchronisation words were cleared by heads_bwd_dh_kernel)
-        pa.l1 = rec_args(1, ws.dh[0]);
-        pa.l0 = rec_args(0, ws.dh[1]);
-        pa.work.A = ws.dz[1]; pa.work.B = ws.layer[1].wihT; pa.work.C = ws.dh[1]; pa.work.bias = nullptr;
-        pa.work.K = 4 * H; pa.work.N = H;
-        pipe_work(ws, 1, M, t_off, &pa.work);
-        pa.work.G = pa.l1.G;
-        {
-        ProfScope prof(VER_PROF_LSTM_REC_BWD, s);
-        VER_BWD_DISPATCH(lstm_pipe_bwd_kernel, pa);
-        if (!ok) return VER_EHIP;
-        }
-        layer_grads(1, nullptr, false);   // the weight gradients of both layers leave in one grouped launch
-        layer_grads(0, d_x, true);
-    } else {
-        int cur = 0;  // ws.dh[cur] holds the gradient arriving at the current layer's h
-        for (int l = nl - 1; l >= 0; --l) {
+    int cur = 0;  // ws.dh[cur] holds the gradient arriving at the current layer's h
+    for (int l = nl - 1; l >= 0;) {
+        if (pairs && l % 2 == 1) {
+            if (l != nl - 1) fill_words(ws.flags, (size_t)(ws.pipe + ws.pipe_words - ws.flags), 0, s);   // (the top pair's: heads_bwd_dh_kernel)
+            PipeBwdArgs pa;
+            pa.l1 = rec_args(l, ws.dh[cur]);
+            pa.l0 = rec_args(l - 1, ws.dh[cur ^ 1], true);
+            pa.work.A = ws.dz[1]; pa.work.B = ws.layer[l].wihT; pa.work.C = ws.dh[cur ^ 1]; pa.work.bias = nullptr;
+            pa.work.K = 4 * H; pa.work.N = H;
+            pipe_work(ws, 1, M, t_off, &pa.work);
+            pa.work.G = pa.l1.G;
+            {
+            ProfScope prof(VER_PROF_LSTM_REC_BWD, s);
+            VER_BWD_DISPATCH(lstm_pipe_bwd_kernel, pa);
+            if (!ok) return VER_EHIP;
+            }
+            layer_grads(l, nullptr, true, false);   // the weight gradients of both layers leave in one grouped launch
+            layer_grads(l - 1, l > 1 ? ws.dh[cur] : d_x, true, true);
+            l -= 2;
+        } else {
             fill_words(ws.flags, REC_FLAG_WORDS, 0, s);
             RecBwdArgs ra = rec_args(l, ws.dh[cur]);
             {
@@ -747,8 +760,9 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             VER_BWD_DISPATCH(lstm_rec_bwd_kernel, ra);
             if (!ok) return VER_EHIP;
             }
-            layer_grads(l, l > 0 ? ws.dh[cur ^ 1] : d_x, true);
+            layer_grads(l, l > 0 ? ws.dh[cur ^ 1] : d_x, false, true);
             cur ^= 1;
+            l -= 1;
         }
     }
 #undef VER_BWD_DISPATCH

@@ -66,8 +66,8 @@ def test_two_layers_ragged(ver, compute, b):
 
 @pytest.mark.parametrize("compute", [0, 1])
 def test_two_layers_one_launch_per_layer(ver, compute):
-    """Two-layer networks normally run both time loops in one launch; the layer-by-layer path (every other
-    depth) is checked against the oracle on the same case through the library's diagnostic switch."""
+    """Two-layer networks normally run both time loops in one launch; the layer-by-layer path (one layer, and the
+    top layer of an odd number) is checked against the oracle on the same case through the library's diagnostic switch."""
     case(ver, wl.scaled(wl.WORKLOADS["manip"], **SMALL), seed=21, b=1, compute=compute, layer_by_layer=True)
 
 
@@ -175,6 +175,15 @@ def test_two_layer_launch_random_packings(ver, seed):
 def test_three_layers_wide_input(ver):
     case(ver, wl.scaled(wl.WORKLOADS["manip"], budget=256, n_envs=6, hidden=192, input_dim=260, n_layers=3,
                         p_done=0.03, minibatches=1), seed=8)
+
+
+@pytest.mark.parametrize("layer_by_layer", [False, True])
+@pytest.mark.parametrize("n_layers,compute", [(3, 1), (4, 0), (5, 0)])
+def test_pairs_of_layers(ver, n_layers, compute, layer_by_layer):
+    """Deeper networks run two layers per launch, an odd top layer alone: one pair and a top layer, two pairs, two pairs
+    and a top layer; the launch per layer on the same case."""
+    case(ver, wl.scaled(wl.WORKLOADS["manip"], budget=700, n_envs=9, hidden=128, input_dim=36, n_layers=n_layers, p_done=0.03,
+                        minibatches=1), seed=9, compute=compute, layer_by_layer=layer_by_layer)
 
 
 def test_packing_order_invariance_on_device(ver):
