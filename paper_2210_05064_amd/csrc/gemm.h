@@ -17,31 +17,9 @@
 //              v_mfma_f32_16x16x32_bf16, fp32 accumulate.
 //   MODE_F32 : fp32 operands, v_mfma_f32_16x16x4_f32.
 #pragma once
-#include "common.h"
+#include "mfma.h"
 
 namespace ver {
-
-typedef unsigned short bf16_t;  // storage type of a bf16 value
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef unsigned short u16x8_t __attribute__((ext_vector_type(8)));
-typedef unsigned short u16x4_t __attribute__((ext_vector_type(4)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ bf16_t to_bf16(float f) {  // round to nearest even
-    unsigned int u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)((u >> 16) | 0x40);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (bf16_t)(u >> 16);
-}
-__device__ __forceinline__ float from_bf16(bf16_t h) { return __uint_as_float(((unsigned int)h) << 16); }
-
-__device__ __forceinline__ f32x4_t mfma_bf16_16x16x32(u16x8_t a, u16x8_t b, f32x4_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
-                                                   c, 0, 0, 0);
-}
-__device__ __forceinline__ f32x4_t mfma_f32_16x16x4(float a, float b, f32x4_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
 
 enum { MODE_F32 = 0, MODE_BF16 = 1 };
 
@@ -89,8 +67,6 @@ __device__ __forceinline__ void store_quad(bf16_t* dst, const Quad<bf16_t>& q) {
 __device__ __forceinline__ void store_quad(float* dst, const Quad<float>& q) {
     *reinterpret_cast<f32x4_t*>(dst) = f32x4_t{q.v[0], q.v[1], q.v[2], q.v[3]};
 }
-
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
 constexpr int GEMM_BM = 128, GEMM_BN = 128, GEMM_THREADS = 256;
 

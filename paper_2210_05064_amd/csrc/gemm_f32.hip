@@ -1,0 +1,249 @@
+// fp32 contractions of the LSTM on v_mfma_f32_16x16x4_f32: input projections and input gradients (K-major operands) and
+// weight gradients (K-minor operands: the contraction runs over the packed rows).  gfx950 only.
+//
+// Bound by the MFMAs (157 TFLOP/s at 2.4 GHz; these launches run at 2.0 to 2.1), so what matters is that every SIMD always has
+// one to issue:
+//  * K-tiles of 32 go from global memory straight into LDS (buffer_load ... lds), one barrier per K-tile.  Neither direction
+//    needs a transposition: the MFMA takes one value per lane and any assignment of contraction indices to lanes works as
+//    long as A and B agree, so K-major rows are read 16 bytes (4 k) at a time, and K-minor rows are read along the
+//    output index (with 64 x 64 tiles two adjacent outputs per lane, which go to two MFMAs: the tile's rows and columns
+//    are permuted, and the store puts them back);
+//  * two stages of LDS, so that four workgroups share a CU and one multiplies while another waits (three or four stages with
+//    fewer workgroups: 8 to 15 % slower);
+//  * square tiles of 64, or of 32 where those would leave CUs idle (launch rule below), without splitting the
+//    contraction: no partial tiles in memory and no pass that adds them.  A running sum is moved to a second set of
+//    registers every 128 k, so chains of additions stay as short as with a split;
+//  * all weight gradients of a minibatch share a launch, so the last, partly filled round of the chip is paid once.
+// us, the 128 x 128 register-staged tiles with a split contraction that ran here before -> now: the four weight gradients of 2 x
+// 512 units over 1024 rows (8.7 GFLOP) 235 -> 98, input projection 1024 x 2048 x 516 55 -> 26, input gradient 1024 x
+// 516 x 2048 55 -> 35.  Counters of the first: the CUs are busy 84 % of the launch (its last round is partly filled), the MFMAs 79 % of that.
+#include "gemm_f32.h"
+#include "mfma.h"
+
+namespace ver {
+namespace {
+
+constexpr int BK = 32;
+// T: rows and columns of a workgroup's tile (4 waves, 2 x 2)
+template <int T> struct Geom {
+    static constexpr int W = T / 2, WT = W / 16;       // a wave's square, in MFMA tiles
+    static constexpr int OPERAND = T * BK * 4, STAGE = 2 * OPERAND;
+    static constexpr int STAGES = 2;
+    static constexpr int NL = OPERAND / 1024 / 4;      // load instructions per wave, operand and stage
+    static constexpr int ACCS = T == 32 ? 2 : 1;       // running sums per MFMA tile (a wave with a single tile alternates)
+};
+
+// Chunk (16 bytes) position p of LDS row r holds chunk p ^ swz(r).
+template <int T, bool KMIN> __device__ __forceinline__ int swz(int r) {
+    if (!KMIN) return (r & 7) ^ ((r >> 3) & 1);        // rows of 8 chunks, read by 16 lanes of one chunk column
+    return T == 64 ? (r & 1) << 3 : ((r >> 1) & 1) << 2;   // 16 or 8 chunks, read by 16 lanes along each of 4 rows
+}
+
+template <int T, bool KMIN>
+__device__ __forceinline__ void tile(const F32Problem& q, int t, unsigned char* smem) {
+    typedef Geom<T> G;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lk = lane >> 4;
+    const int m0 = t / q.tiles_n * T, n0 = t % q.tiles_n * T;
+    const int wm = (wave >> 1) * G::W, wn = (wave & 1) * G::W;
+    const int nk = (q.K + BK - 1) / BK;
+    const int rowsA = KMIN ? q.K : q.Mr, rowsB = KMIN ? q.K : q.Nc;
+    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(q.A), 0, rowsA * q.lda * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(q.B), 0, rowsB * q.ldb * 4, 0x00020000);
+    // A load instruction fills 1 KB of LDS (8 rows K-major; 1024 / (4 T) rows K-minor); the swizzle is applied on the global side.
+    constexpr int CHUNKS = KMIN ? T / 4 : BK / 4;
+    unsigned offA[G::NL], offB[G::NL];
+    int kc[G::NL];   // K-major: this lane's first k in the K-tile
+#pragma unroll
+    for (int j = 0; j < G::NL; ++j) {
+        const int row = (wave * G::NL + j) * (64 / CHUNKS) + lane / CHUNKS, c = (lane % CHUNKS) ^ swz<T, KMIN>(row);
+        kc[j] = c * 4;
+        if (KMIN) {   // rows beyond K are beyond the buffer and read zero; columns beyond the matrix feed outputs that are not stored
+            offA[j] = ((unsigned)row * q.lda + m0 + c * 4) * 4;
+            offB[j] = ((unsigned)row * q.ldb + n0 + c * 4) * 4;
+        } else {      // rows beyond the matrix repeat its last one
+            offA[j] = ((unsigned)min(m0 + row, q.Mr - 1) * q.lda + c * 4) * 4;
+            offB[j] = ((unsigned)min(n0 + row, q.Nc - 1) * q.ldb + c * 4) * 4;
+        }
+    }
+    auto issue = [&](int kt) {
+        unsigned char* st = smem + kt % G::STAGES * G::STAGE + wave * G::NL * 1024;
+        const unsigned stepA = KMIN ? (unsigned)(kt * BK) * q.lda * 4 : kt * BK * 4, stepB = KMIN ? (unsigned)(kt * BK) * q.ldb * 4 : kt * BK * 4;
+#pragma unroll
+        for (int j = 0; j < G::NL; ++j) {
+            const bool in = KMIN || kt * BK + kc[j] < q.K;   // (K is a multiple of 4 when K-major; beyond it: read zero)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_ptr_t)(st + j * 1024), 16, in ? offA[j] + stepA : 0xFFFFFFF0u, 0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, (lds_ptr_t)(st + G::OPERAND + j * 1024), 16, in ? offB[j] + stepB : 0xFFFFFFF0u, 0, 0, 0);
+        }
+    };
+    f32x4_t acc[G::ACCS][G::WT][G::WT], sum[G::WT][G::WT];
+#pragma unroll
+    for (int i = 0; i < G::WT; ++i)
+#pragma unroll
+        for (int j = 0; j < G::WT; ++j) {
+            sum[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < G::ACCS; ++s) acc[s][i][j] = sum[i][j];
+        }
+    auto fold = [&] {
+#pragma unroll
+        for (int s = 0; s < G::ACCS; ++s)
+#pragma unroll
+            for (int i = 0; i < G::WT; ++i)
+#pragma unroll
+                for (int j = 0; j < G::WT; ++j) {
+                    sum[i][j] += acc[s][i][j];
+                    acc[s][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                }
+    };
+    // A wave's operands of one K-tile.  K-major: 16 bytes along k; K-minor: WT adjacent outputs for each of 8 k.
+    constexpr int STEPS = KMIN ? BK / 4 : BK / 16, VALS = KMIN ? 1 : G::WT;
+    typedef float op_t __attribute__((ext_vector_type(KMIN ? G::WT : 4)));
+    struct Operands { op_t a[STEPS][VALS], b[STEPS][VALS]; };
+    auto read = [&](int kt, Operands& o) {
+        const unsigned char* sA = smem + kt % G::STAGES * G::STAGE;
+        const unsigned char* sB = sA + G::OPERAND;
+#pragma unroll
+        for (int ks = 0; ks < STEPS; ++ks)
+#pragma unroll
+            for (int i = 0; i < VALS; ++i) {
+                if constexpr (KMIN) {
+                    const int k = ks * 4 + lk, ca = wm + lr * G::WT, cb = wn + lr * G::WT;
+                    o.a[ks][i] = *reinterpret_cast<const op_t*>(sA + k * (T * 4) + (((ca >> 2) ^ swz<T, KMIN>(k)) << 4) + (ca & 3) * 4);
+                    o.b[ks][i] = *reinterpret_cast<const op_t*>(sB + k * (T * 4) + (((cb >> 2) ^ swz<T, KMIN>(k)) << 4) + (cb & 3) * 4);
+                } else {
+                    const int ra = wm + i * 16 + lr, rb = wn + i * 16 + lr;
+                    o.a[ks][i] = *reinterpret_cast<const op_t*>(sA + ra * 128 + (((ks * 4 + lk) ^ swz<T, KMIN>(ra)) << 4));
+                    o.b[ks][i] = *reinterpret_cast<const op_t*>(sB + rb * 128 + (((ks * 4 + lk) ^ swz<T, KMIN>(rb)) << 4));
+                }
+            }
+    };
+    auto multiply = [&](const Operands& o) {
+#pragma unroll
+        for (int ks = 0; ks < STEPS; ++ks)
+#pragma unroll
+            for (int e = 0; e < (KMIN ? 1 : 4); ++e)
+#pragma unroll
+                for (int i = 0; i < G::WT; ++i)
+#pragma unroll
+                    for (int j = 0; j < G::WT; ++j) {
+                        f32x4_t& c = acc[(ks + e) % G::ACCS][i][j];
+                        c = KMIN ? mfma_f32_16x16x4(o.a[ks][0][KMIN ? i : 0], o.b[ks][0][KMIN ? j : 0], c)
+                                 : mfma_f32_16x16x4(o.a[ks][KMIN ? 0 : i][e], o.b[ks][KMIN ? 0 : j][e], c);
+                    }
+    };
+    // this wave's loads have landed, and after the barrier so have everyone's
+    auto arrived = [&] {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        bar_lds();
+    };
+    for (int kt = 0; kt < G::STAGES && kt < nk; ++kt) issue(kt);
+    if (nk >= G::STAGES) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((G::STAGES - 1) * 2 * G::NL) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    bar_lds();
+    // The operands of K-tile kt + 1 are read before the MFMAs of K-tile kt are issued.
+    Operands even, odd;
+    auto step = [&](int kt, const Operands& now, Operands& next) {
+        arrived();   // (and everyone has read the stage of kt, which is the one that is filled again)
+        if (kt + G::STAGES < nk) issue(kt + G::STAGES);
+        read(kt + 1, next);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(now);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    read(0, even);
+    int kt = 0;
+    for (; kt + 2 < nk; kt += 2) {
+        step(kt, even, odd);
+        step(kt + 1, odd, even);
+        if ((kt & 2) != 0) fold();   // every 4 K-tiles
+    }
+    if (kt + 1 < nk) {
+        step(kt, even, odd);
+        multiply(odd);
+    } else {
+        multiply(even);
+    }
+    fold();
+    // element r of lane l: row lk * 4 + r, column lr of the MFMA tile; what lies outside the matrix is stored out of the
+    // buffer's range, i.e. dropped
+    const __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(q.C, 0, q.Mr * q.ldc * 4, 0x00020000);
+    float bv[G::WT];
+#pragma unroll
+    for (int j = 0; j < G::WT; ++j) {
+        const int n = n0 + wn + (KMIN ? lr * G::WT + j : j * 16 + lr);
+        bv[j] = q.bias && n < q.Nc ? q.bias[n] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < G::WT; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = m0 + wm + (KMIN ? (lk * 4 + r) * G::WT + i : i * 16 + lk * 4 + r);
+            const int out = q.unperm_h > 0 ? (m & 3) * q.unperm_h + (m >> 2) : m;
+#pragma unroll
+            for (int j = 0; j < G::WT; ++j) {
+                const int n = n0 + wn + (KMIN ? lr * G::WT + j : j * 16 + lr);
+                const unsigned at = m < q.Mr && n < q.Nc ? ((unsigned)out * q.ldc + n) * 4 : 0xFFFFFFF0u;
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sum[i][j][r] + bv[j]), rsC, at, 0, 0);
+            }
+        }
+}
+
+// Workgroups go to the 8 XCDs round-robin: every XCD takes a stretch of consecutive tiles, so that the rows they share are
+// fetched into its L2 once.
+template <int T, bool KMIN>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(F32GroupArgs g) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int per = gridDim.x / 8, t = (blockIdx.x % 8) * per + blockIdx.x / 8;
+    if (t >= g.tiles) return;
+    F32Problem q = g.p[0];   // uniform selects (an indexed copy of a kernel argument would live in scratch memory)
+#pragma unroll
+    for (int i = 1; i < F32_GROUP_MAX; ++i)
+        if (i < g.n && t >= g.p[i].tile_first) q = g.p[i];
+    tile<T, KMIN>(q, t - q.tile_first, smem);
+}
+
+template <int T, bool KMIN>
+void start(F32GroupArgs& a, int tiles, hipStream_t s) {
+    constexpr int lds = Geom<T>::STAGES * Geom<T>::STAGE;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_f32_kernel<T, KMIN>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    a.tiles = tiles;
+    hipLaunchKernelGGL((gemm_f32_kernel<T, KMIN>), dim3((tiles + 7) / 8 * 8), dim3(256), lds, s, a);
+}
+int lay_out(F32GroupArgs& a, int T) {
+    int tiles = 0;
+    for (int i = 0; i < a.n; ++i) {
+        F32Problem& q = a.p[i];
+        q.tiles_n = (q.Nc + T - 1) / T;
+        q.tile_first = tiles;
+        tiles += q.tiles_n * ((q.Mr + T - 1) / T);
+    }
+    return tiles;
+}
+
+}  // namespace
+
+bool F32Gemm::add(const float* A, int lda, const float* B, int ldb, float* C, int ldc, int Mr, int Nc, int K, const float* bias, int unperm_h) {
+    const size_t rowsA = k_minor ? K : Mr, rowsB = k_minor ? K : Nc;
+    if (a.n >= F32_GROUP_MAX || (rowsA + BK) * lda * 4 >= 0x7fffffff || (rowsB + BK) * ldb * 4 >= 0x7fffffff ||
+        (size_t)Mr * ldc * 4 >= 0x7fffffff) return false;
+    a.p[a.n++] = F32Problem{A, B, C, bias, lda, ldb, ldc, Mr, Nc, K, unperm_h, 0, 0};
+    return true;
+}
+
+// From this many tiles of 64 on they fill the chip.  us with tiles of 64 / 32: 512 tiles 26.2 / 30.0, 4096 367 / 434, 1056 (K-minor)
+// 99.8 / 97.3, 256 48.7 / 47.9, 144 46.1 / 35.5, 80 6.2 / 4.5, 24 (K-minor, 2048 rows) 42 / 19.
+constexpr int T64_FROM = 384;
+void F32Gemm::launch(hipStream_t s) {
+    if (a.n == 0) return;
+    const int tiles64 = lay_out(a, 64);
+    if (tiles64 >= T64_FROM) {
+        k_minor ? start<64, true>(a, tiles64, s) : start<64, false>(a, tiles64, s);
+    } else {
+        const int tiles32 = lay_out(a, 32);
+        k_minor ? start<32, true>(a, tiles32, s) : start<32, false>(a, tiles32, s);
+    }
+    a.n = 0;
+}
+
+}  // namespace ver

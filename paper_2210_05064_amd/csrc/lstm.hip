@@ -14,6 +14,7 @@
 #include <cstring>
 #include <mutex>
 
+#include "gemm_f32.h"
 #include "lstm_pipe.h"
 
 namespace ver {
@@ -338,9 +339,10 @@ inline size_t part_floats(const ver_lstm_cfg& c, int M) {
     return rb_heads * (c.act_dim + 1) * c.hidden;   // the row-block partial sums of the heads' weight gradient
 }
 
-// Largest split-K scratch any GEMM of the forward or backward pass asks for.
+// Largest split-K scratch any GEMM of the forward or backward pass asks for (the fp32 contractions are not split).
 inline size_t gemm_part_max(const ver_lstm_cfg& c, int M) {
-    const int bk = c.compute ? GemmGeom<MODE_BF16>::BK : GemmGeom<MODE_F32>::BK;
+    if (!c.compute) return 0;
+    const int bk = GemmGeom<MODE_BF16>::BK;
     const int H = c.hidden;
     size_t m = 0;
     for (int l = 0; l < c.n_layers; ++l) {
@@ -528,6 +530,14 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         const int D = l == 0 ? c.input_dim : H;
         LayerWs& L = ws.layer[l];
         ProfScope prof(VER_PROF_LSTM_GEMM_FWD, s);
+        if constexpr (MODE == MODE_F32) {
+            F32Gemm g(false);
+            if (g.add(l == 0 ? static_cast<const float*>(x) : ws.layer[l - 1].hout, D, static_cast<const float*>(L.wih), D, L.gates, 4 * H, M,
+                      4 * H, D, L.bias, 0)) {
+                g.launch(s);
+                return;
+            }
+        }
         if (l == 0) {
             if constexpr (MODE == MODE_BF16) {
                 // bf16 rows on both sides: the LDS-direct tiles of the two-layer launch, as a launch of their own
@@ -535,13 +545,13 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             }
             if (c.x_bf16)
                 gemm_launch<MODE, bf16_t, E, false>(static_cast<const bf16_t*>(x), D, static_cast<const E*>(L.wih), D,
-                                                    L.gates, 4 * H, M, 4 * H, D, L.bias, 0, ws.gemm_part, true, s);
+                                                    L.gates, 4 * H, M, 4 * H, D, L.bias, 0, ws.gemm_part, MODE == MODE_BF16, s);
             else
                 gemm_launch<MODE, float, E, false>(static_cast<const float*>(x), D, static_cast<const E*>(L.wih), D,
-                                                   L.gates, 4 * H, M, 4 * H, D, L.bias, 0, ws.gemm_part, true, s);
+                                                   L.gates, 4 * H, M, 4 * H, D, L.bias, 0, ws.gemm_part, MODE == MODE_BF16, s);
         } else {
             gemm_launch<MODE, float, E, false>(ws.layer[l - 1].hout, H, static_cast<const E*>(L.wih), H, L.gates,
-                                               4 * H, M, 4 * H, H, L.bias, 0, ws.gemm_part, true, s);
+                                               4 * H, M, 4 * H, H, L.bias, 0, ws.gemm_part, MODE == MODE_BF16, s);
         }
     };
     auto rec_args = [&](int l, bool consumer = false) {
@@ -682,6 +692,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     // Everything of layer l that is not the time loop: dx (optional), dW_ih, dW_hh, db.  A pair's upper layer comes first
     // and leaves its weight gradients and bias sums to the launches of the lower one (last = false).
     TnGroup dw_group;
+    F32Gemm dw_f32(true);
     auto layer_grads = [&](int l, float* dx, bool in_pair, bool last) {
         const int D = l == 0 ? c.input_dim : H;
         LayerWs& L = ws.layer[l];
@@ -691,36 +702,41 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             ProfScope prof(VER_PROF_LSTM_GEMM_DX, s);
             bool done = false;
             if constexpr (MODE == MODE_BF16) done = launch_proj_dma(dz, L.wihT, dx, nullptr, M, D, 4 * H, s);
+            else {
+                F32Gemm g(false);
+                done = g.add(dz, 4 * H, static_cast<const float*>(L.wihT), 4 * H, dx, D, M, D, 4 * H, nullptr, 0);
+                g.launch(s);
+            }
             if (!done)
                 gemm_launch<MODE, E, E, false>(dz, 4 * H, static_cast<const E*>(L.wihT), 4 * H, dx, D, M, D, 4 * H,
-                                               nullptr, 0, ws.gemm_part, true, s);
+                                               nullptr, 0, ws.gemm_part, MODE == MODE_BF16, s);
         }
-        // dW_ih[4H, D] = dz^T x ; dW_hh[4H, H] = dz^T h_{t-1}; stored gate-major.  Contractions whose operands are both
-        // bf16 join the grouped launch (dw_group) when they fit it; the others are launched on the spot.
+        // dW_ih[4H, D] = dz^T x ; dW_hh[4H, H] = dz^T h_{t-1}; stored gate-major.  The contractions of a layer or pair leave in
+        // one launch where their operands are of one type; the others are launched on the spot.
         {
         ProfScope prof(VER_PROF_LSTM_GEMM_DW, s);
-        auto grouped = [&](const void* B, int ldb, float* C, int Nc) {
-            if constexpr (MODE == MODE_BF16)
-                return dw_group.add(reinterpret_cast<const bf16_t*>(dz), 4 * H, static_cast<const bf16_t*>(B), ldb, C, Nc, 4 * H, Nc, M, H);
-            return false;
+        auto contract = [&](const auto* B, float* C, int Nc) {
+            typedef typename std::remove_const<typename std::remove_pointer<decltype(B)>::type>::type TB;
+            if constexpr (MODE == MODE_F32) {
+                if (dw_f32.add(dz, 4 * H, B, Nc, C, Nc, 4 * H, Nc, M, nullptr, H)) return;
+            } else if constexpr (sizeof(TB) == 2) {
+                if (dw_group.add(dz, 4 * H, B, Nc, C, Nc, 4 * H, Nc, M, H)) return;
+            }
+            gemm_launch<MODE, E, TB, true>(dz, 4 * H, B, Nc, C, Nc, 4 * H, Nc, M, nullptr, H, ws.gemm_part, MODE == MODE_BF16, s);
         };
-        if (l > 0 && in_pair && !last) {   // the layer below is the pair's lower one and left its h in operand type
-            if (!grouped(ws.layer[l - 1].hcopy, H, gw[4 * l], D))
-                gemm_launch<MODE, E, E, true>(dz, 4 * H, static_cast<const E*>(ws.layer[l - 1].hcopy), H, gw[4 * l], D, 4 * H, D, M,
-                                              nullptr, H, ws.gemm_part, true, s);
-        } else if (l > 0)
-            gemm_launch<MODE, E, float, true>(dz, 4 * H, ws.layer[l - 1].hout, H, gw[4 * l], D, 4 * H, D, M, nullptr, H, ws.gemm_part, true, s);
-        else if (c.x_bf16) {
-            if (!grouped(x, D, gw[4 * l], D))
-                gemm_launch<MODE, E, bf16_t, true>(dz, 4 * H, static_cast<const bf16_t*>(x), D, gw[4 * l], D, 4 * H, D, M,
-                                                   nullptr, H, ws.gemm_part, true, s);
-        } else
-            gemm_launch<MODE, E, float, true>(dz, 4 * H, static_cast<const float*>(x), D, gw[4 * l], D, 4 * H, D, M,
-                                              nullptr, H, ws.gemm_part, true, s);
-        if (!grouped(L.hprev, H, gw[4 * l + 1], H))
-            gemm_launch<MODE, E, E, true>(dz, 4 * H, static_cast<const E*>(L.hprev), H, gw[4 * l + 1], H, 4 * H, H, M,
-                                          nullptr, H, ws.gemm_part, true, s);
-        if (last) dw_group.launch(s);
+        if (l > 0 && in_pair && !last)   // the layer below is the pair's lower one and left its h in operand type
+            contract(static_cast<const E*>(ws.layer[l - 1].hcopy), gw[4 * l], D);
+        else if (l > 0)
+            contract(ws.layer[l - 1].hout, gw[4 * l], D);
+        else if (MODE == MODE_BF16 && c.x_bf16)
+            contract(static_cast<const E*>(x), gw[4 * l], D);
+        else
+            contract(static_cast<const float*>(x), gw[4 * l], D);
+        contract(static_cast<const E*>(L.hprev), gw[4 * l + 1], H);
+        if (last) {
+            dw_group.launch(s);
+            dw_f32.launch(s);
+        }
         }
         // db_ih = db_hh = column sums of dz: the time loop left one partial sum per group (a pair: both layers' sums in
         // one launch)

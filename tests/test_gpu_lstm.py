@@ -186,6 +186,14 @@ def test_pairs_of_layers(ver, n_layers, compute, layer_by_layer):
                         minibatches=1), seed=9, compute=compute, layer_by_layer=layer_by_layer)
 
 
+@pytest.mark.parametrize("rows,hidden,input_dim", [(32, 64, 4), (33, 64, 32), (63, 128, 68), (127, 64, 132), (129, 320, 36), (1000, 512, 516)])
+def test_fp32_contractions(ver, rows, hidden, input_dim):
+    """Edges of the 32 x 32 (K-major: up to 127 rows) and 64 x 64 tiles of the fp32 contractions: one to 32 K-tiles, rows and
+    columns one short of and one beyond a tile, K-tiles with 4 valid k."""
+    case(ver, wl.scaled(wl.WORKLOADS["manip"], budget=rows, n_envs=max(2, rows // 25), hidden=hidden, input_dim=input_dim, p_done=0.05,
+                        minibatches=1), seed=rows)
+
+
 def test_packing_order_invariance_on_device(ver):
     """Another random order of the same sequences (B = 1): identical weight gradients up to rounding."""
     w = wl.scaled(wl.WORKLOADS["manip"], budget=400, n_envs=10, hidden=64, input_dim=16, p_done=0.03,
