@@ -1,22 +1,16 @@
-// LDS-tiled MFMA GEMM for the time-batched contractions of the LSTM
-// (input projections, input gradients, weight gradients).  gfx950 only.
+// MFMA contractions of the LSTM outside the time loops: the general kernel, and the grouped weight gradients of large
+// minibatches in bf16.  gfx950 only.
 //
 //   C[m][n] = sum_k A(m,k) * B(n,k)  (+ bias[n])
 //
-// Operands are "K-major" (A(m,k) = A[m*lda + k]: the contraction index is
-// contiguous) or, with TRANS, "K-minor" (A(m,k) = A[k*lda + m]: used for the
-// weight gradients, where the contraction runs over the packed rows).  Either
-// way a 128x128 tile of C is built by 4 waves (2x2, 64x64 each) from K-tiles
-// staged in LDS as [row][k] so that every MFMA operand is one aligned 16-byte
-// LDS read.  K-minor tiles are transposed in registers (4x4 blocks) on the way
-// into LDS.  The global loads of K-tile i+1 are issued before the MFMAs of tile
-// i (register double buffering), and the contraction can be split over
-// gridDim.z with the partial tiles summed in index order by a second kernel, so
-// that small outputs still fill the chip; both keep the result deterministic.
-//   MODE_BF16: operands rounded to bf16 on the way into LDS (or already bf16),
-//              v_mfma_f32_16x16x32_bf16, fp32 accumulate.
-//   MODE_F32 : fp32 operands, v_mfma_f32_16x16x4_f32.
+// Operands are "K-major" (A(m,k) = A[m*lda + k]: the contraction index is contiguous) or, with TRANS, "K-minor" (A(m,k) =
+// A[k*lda + m]: used for the weight gradients, where the contraction runs over the packed rows).
+// The general kernel addresses with 64 bits and takes what the LDS-direct kernels (gemm_f32.hip, gemm_bf16.hip, below) cannot:
+// arrays of 2 GB and more.  A 128x128 tile of C is built by 4 waves (2x2, 64x64 each) from K-tiles staged in LDS as [row][k]
+// so that every MFMA operand is one aligned 16-byte LDS read; K-minor tiles are transposed in registers (4x4 blocks) on the
+// way into LDS; the global loads of K-tile i+1 are issued before the MFMAs of tile i.
 #pragma once
+#include "gemm_group.h"
 #include "mfma.h"
 
 namespace ver {
@@ -27,31 +21,16 @@ template <int MODE> struct LdsElem;
 template <> struct LdsElem<MODE_F32> { typedef float type; };
 template <> struct LdsElem<MODE_BF16> { typedef bf16_t type; };
 
-template <typename TO> __device__ __forceinline__ TO cvt_elem(float v);
-template <> __device__ __forceinline__ float cvt_elem<float>(float v) { return v; }
-template <> __device__ __forceinline__ bf16_t cvt_elem<bf16_t>(float v) { return to_bf16(v); }
-template <typename TO> __device__ __forceinline__ TO cvt_elem(bf16_t v);
-template <> __device__ __forceinline__ float cvt_elem<float>(bf16_t v) { return from_bf16(v); }
-template <> __device__ __forceinline__ bf16_t cvt_elem<bf16_t>(bf16_t v) { return v; }
-
-// 4 consecutive elements (aligned to 4 elements) of a source row, converted to the LDS element type.
+// 4 consecutive elements (aligned to 4 elements) of a source row.
 template <typename E> struct Quad { E v[4]; };
-template <typename E, typename T> __device__ __forceinline__ Quad<E> load_quad(const T* p);
-template <> __device__ __forceinline__ Quad<float> load_quad<float, float>(const float* p) {
+template <typename E> __device__ __forceinline__ Quad<E> load_quad(const E* p);
+template <> __device__ __forceinline__ Quad<float> load_quad<float>(const float* p) {
     const f32x4_t t = *reinterpret_cast<const f32x4_t*>(p);
     return Quad<float>{{t[0], t[1], t[2], t[3]}};
 }
-template <> __device__ __forceinline__ Quad<bf16_t> load_quad<bf16_t, float>(const float* p) {
-    const f32x4_t t = *reinterpret_cast<const f32x4_t*>(p);
-    return Quad<bf16_t>{{to_bf16(t[0]), to_bf16(t[1]), to_bf16(t[2]), to_bf16(t[3])}};
-}
-template <> __device__ __forceinline__ Quad<bf16_t> load_quad<bf16_t, bf16_t>(const bf16_t* p) {
+template <> __device__ __forceinline__ Quad<bf16_t> load_quad<bf16_t>(const bf16_t* p) {
     const u16x4_t t = *reinterpret_cast<const u16x4_t*>(p);
     return Quad<bf16_t>{{t[0], t[1], t[2], t[3]}};
-}
-template <> __device__ __forceinline__ Quad<float> load_quad<float, bf16_t>(const bf16_t* p) {
-    const u16x4_t t = *reinterpret_cast<const u16x4_t*>(p);
-    return Quad<float>{{from_bf16(t[0]), from_bf16(t[1]), from_bf16(t[2]), from_bf16(t[3])}};
 }
 template <typename E> __device__ __forceinline__ Quad<E> zero_quad() {
     Quad<E> q;
@@ -70,29 +49,6 @@ __device__ __forceinline__ void store_quad(float* dst, const Quad<float>& q) {
 
 constexpr int GEMM_BM = 128, GEMM_BN = 128, GEMM_THREADS = 256;
 
-// Which tile a workgroup computes.  Workgroups are dealt to the 8 XCDs round-robin in launch order and every
-// XCD has its own 4 MB L2, so the workgroups of one XCD are given a band of row tiles (with all its column tiles
-// and K-splits), and inside the band the ~64 workgroups that are resident at a time form an 8 x 8 block of
-// tiles: the operand tiles they share are then fetched from HBM once per block instead of once per workgroup.
-// bx: column tile, by: row tile, bz: K-split.
-__device__ __forceinline__ void gemm_tile_of_block(int& bx, int& by, int& bz) {
-    const int gx = gridDim.x, gy = gridDim.y, gz = gridDim.z;
-    const int id = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-    if (gy % 8 != 0) {   // no even bands: launch order as it is
-        bx = blockIdx.x; by = blockIdx.y; bz = blockIdx.z;
-        return;
-    }
-    const int R = gy / 8;                       // row tiles of a band
-    const int xcd = id % 8, slot = id / 8;      // slot: 0 .. R*gx*gz - 1 in launch order on this XCD
-    bz = slot / (R * gx);
-    const int rem = slot - bz * (R * gx);
-    const int Rb = R % 8 == 0 ? 8 : R, Cb = gx % 8 == 0 ? 8 : gx;   // block of tiles that is resident together
-    const int blk = rem / (Rb * Cb), in = rem - blk * (Rb * Cb);
-    const int blocks_x = gx / Cb;
-    by = xcd * R + (blk / blocks_x) * Rb + in / Cb;
-    bx = (blk % blocks_x) * Cb + in % Cb;
-}
-
 template <int MODE> struct GemmGeom;
 template <> struct GemmGeom<MODE_BF16> { static constexpr int BK = 64, LDS_STRIDE = 72; };
 template <> struct GemmGeom<MODE_F32> { static constexpr int BK = 32, LDS_STRIDE = 36; };
@@ -107,8 +63,8 @@ template <int MODE> struct TileRegs {
 
 // K-major source: quad c (of BK/4) of row r; 16-byte (fp32) or 8-byte (bf16) coalesced loads.
 // K-minor source: each thread owns 4(k) x 4(rows) blocks, loaded as 4 row-quads and transposed.
-template <int MODE, typename T, bool TRANS>
-__device__ __forceinline__ void tile_load(const T* __restrict__ src, int ld, int row0, int n_rows, int k0, int k_end,
+template <int MODE, bool TRANS>
+__device__ __forceinline__ void tile_load(const typename LdsElem<MODE>::type* __restrict__ src, int ld, int row0, int n_rows, int k0, int k_end,
                                           TileRegs<MODE>& regs) {
     typedef typename LdsElem<MODE>::type E;
     constexpr int BK = GemmGeom<MODE>::BK, QUADS = TileRegs<MODE>::QUADS;
@@ -120,7 +76,7 @@ __device__ __forceinline__ void tile_load(const T* __restrict__ src, int ld, int
 #pragma unroll
         for (int i = 0; i < QUADS; ++i) {
             const int gr = row0 + r + i * RPP, gk = k0 + c * 4;
-            regs.q[i] = (gr < n_rows && gk < k_end) ? load_quad<E, T>(src + (size_t)gr * ld + gk) : zero_quad<E>();
+            regs.q[i] = (gr < n_rows && gk < k_end) ? load_quad<E>(src + (size_t)gr * ld + gk) : zero_quad<E>();
         }
     } else {
         constexpr int MB = 128 / 4;                      // 4-row blocks across the tile
@@ -132,7 +88,7 @@ __device__ __forceinline__ void tile_load(const T* __restrict__ src, int ld, int
             Quad<E> in[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                in[j] = (gk + j < k_end && gr < n_rows) ? load_quad<E, T>(src + (size_t)(gk + j) * ld + gr) : zero_quad<E>();
+                in[j] = (gk + j < k_end && gr < n_rows) ? load_quad<E>(src + (size_t)(gk + j) * ld + gr) : zero_quad<E>();
 #pragma unroll
             for (int m = 0; m < 4; ++m)                  // row gr+m gets k = gk .. gk+3
 #pragma unroll
@@ -162,25 +118,18 @@ __device__ __forceinline__ void tile_store(const TileRegs<MODE>& regs, typename 
 }
 
 // unperm_h > 0: output row m is stored at row (m % 4) * unperm_h + m / 4 (gate-interleaved -> gate-major).
-// gridDim.z > 1: block z contracts k in [z*k_chunk, (z+1)*k_chunk) and writes its partial tile to
-// C + z*split_stride without bias and without the row permutation (gemm_reduce_kernel applies both).
-template <int MODE, typename TA, typename TB, bool TRANS>
+template <int MODE, bool TRANS>
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(
-    const TA* __restrict__ A, int lda, const TB* __restrict__ B, int ldb, float* __restrict__ C, int ldc,
-    int Mr, int Nc, int K, const float* __restrict__ bias, int unperm_h, int k_chunk, size_t split_stride) {
+    const typename LdsElem<MODE>::type* __restrict__ A, int lda, const typename LdsElem<MODE>::type* __restrict__ B, int ldb,
+    float* __restrict__ C, int ldc, int Mr, int Nc, int K, const float* __restrict__ bias, int unperm_h) {
     typedef typename LdsElem<MODE>::type E;
     constexpr int BK = GemmGeom<MODE>::BK, STRIDE = GemmGeom<MODE>::LDS_STRIDE;
     __shared__ __attribute__((aligned(16))) E sA[GEMM_BM * STRIDE];
     __shared__ __attribute__((aligned(16))) E sB[GEMM_BN * STRIDE];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
-    int bx, by, bz;
-    gemm_tile_of_block(bx, by, bz);
-    const int m0 = by * GEMM_BM, n0 = bx * GEMM_BN;
+    const int m0 = blockIdx.y * GEMM_BM, n0 = blockIdx.x * GEMM_BN;
     const int lr = lane & 15, lk = lane >> 4;
-    const int k_begin = bz * k_chunk, k_end = min(K, k_begin + k_chunk);
-    const bool split = gridDim.z > 1;
-    if (split) C += (size_t)bz * split_stride;
 
     f32x4_t acc[4][4];
 #pragma unroll
@@ -189,15 +138,15 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(
         for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     TileRegs<MODE> ra, rb;
-    tile_load<MODE, TA, TRANS>(A, lda, m0, Mr, k_begin, k_end, ra);
-    tile_load<MODE, TB, TRANS>(B, ldb, n0, Nc, k_begin, k_end, rb);
-    for (int k0 = k_begin; k0 < k_end; k0 += BK) {
+    tile_load<MODE, TRANS>(A, lda, m0, Mr, 0, K, ra);
+    tile_load<MODE, TRANS>(B, ldb, n0, Nc, 0, K, rb);
+    for (int k0 = 0; k0 < K; k0 += BK) {
         tile_store<MODE, TRANS>(ra, sA);
         tile_store<MODE, TRANS>(rb, sB);
         __syncthreads();
-        if (k0 + BK < k_end) {   // next K-tile: in flight while this one is multiplied
-            tile_load<MODE, TA, TRANS>(A, lda, m0, Mr, k0 + BK, k_end, ra);
-            tile_load<MODE, TB, TRANS>(B, ldb, n0, Nc, k0 + BK, k_end, rb);
+        if (k0 + BK < K) {   // next K-tile: in flight while this one is multiplied
+            tile_load<MODE, TRANS>(A, lda, m0, Mr, k0 + BK, K, ra);
+            tile_load<MODE, TRANS>(B, ldb, n0, Nc, k0 + BK, K, rb);
         }
         if (MODE == MODE_BF16) {
 #pragma unroll
@@ -243,30 +192,15 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(
         for (int j = 0; j < 4; ++j) {
             const int n = n0 + wn + j * 16 + lr;
             if (n >= Nc) continue;
-            const float bv = (bias && !split) ? bias[n] : 0.f;
+            const float bv = bias ? bias[n] : 0.f;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int m = m0 + wm + i * 16 + lk * 4 + r;
                 if (m >= Mr) continue;
-                const int out_row = (unperm_h > 0 && !split) ? (m & 3) * unperm_h + (m >> 2) : m;
+                const int out_row = unperm_h > 0 ? (m & 3) * unperm_h + (m >> 2) : m;
                 C[(size_t)out_row * ldc + n] = acc[i][j][r] + bv;
             }
         }
-}
-
-// C[perm(m)][n] = sum_z part[z][m][n] (+ bias[n]), z ascending.
-__global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restrict__ part, int splits, size_t split_stride,
-                                                          int Mr, int Nc, float* __restrict__ C, int ldc,
-                                                          const float* __restrict__ bias, int unperm_h) {
-    const size_t total = (size_t)Mr * Nc;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        const int m = (int)(i / Nc), n = (int)(i % Nc);
-        float s = 0.f;
-        for (int z = 0; z < splits; ++z) s += part[(size_t)z * split_stride + i];
-        if (bias) s += bias[n];
-        const int out_row = unperm_h > 0 ? (m & 3) * unperm_h + (m >> 2) : m;
-        C[(size_t)out_row * ldc + n] = s;
-    }
 }
 
 // ---- K-minor bf16 operands through LDS-direct loads --------------------------------------------------------
@@ -288,10 +222,6 @@ template <int WM> struct TnGeom {
     static constexpr int NA = TN_BK * ROW_A / 1024 / 4;   // A load instructions per wave and stage
     static constexpr int LDS = STAGES * STAGE;
 };
-#ifndef VER_TN_TARGET_WGS
-#define VER_TN_TARGET_WGS 256
-#endif
-constexpr int TN_TARGET_WGS = VER_TN_TARGET_WGS;
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ int tn_swz(int k) { return ((k & 3) << 1) | (((k >> 3) & 1) << 3); }
 
@@ -303,17 +233,14 @@ constexpr int TN_X_STAGE = TN_BK * 64;   // bytes per stage: 32 k-rows of 32 col
 template <int WM, bool XTRA = false>
 __device__ __forceinline__ void gemm_tn_dma_body(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb, float* __restrict__ C, int ldc,
-    int Mr, int Nc, int K, int unperm_h, int k_chunk, size_t split_stride, unsigned char* smem, int bx, int by, int bz,
-    bool split, int x_cols = 0, int x_mt = 0) {
+    int Mr, int Nc, int K, int unperm_h, unsigned char* smem, int bx, int by, int x_cols = 0, int x_mt = 0) {
     typedef TnGeom<WM> G;
     constexpr int TN_STAGES = G::STAGES, TN_STAGE_BYTES = G::STAGE + (XTRA ? TN_X_STAGE : 0), ROW_A = G::ROW_A, NA = G::NA;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = (wave >> 1) * 16 * WM, wn = (wave & 1) * 64;
     const int m0 = by * G::BM, n0 = bx * GEMM_BN;
     const int lr = lane & 15, lk = lane >> 4;
-    const int k_begin = bz * k_chunk, k_end = min(K, k_begin + k_chunk);
-    const int nk = (k_end - k_begin + TN_BK - 1) / TN_BK;
-    if (split) C += (size_t)bz * split_stride;
+    const int nk = (K + TN_BK - 1) / TN_BK;
     // rows beyond K read zero (buffer bounds); columns beyond the matrix only feed outputs that are not stored
     __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(A), 0, (int)min((size_t)K * lda * 2, (size_t)0x7fffffff), 0x00020000);
     __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(B), 0, (int)min((size_t)K * ldb * 2, (size_t)0x7fffffff), 0x00020000);
@@ -339,7 +266,7 @@ __device__ __forceinline__ void gemm_tn_dma_body(
     const int voffX = (wave * 8 + ((lane & 31) >> 2)) * ldb * 2 + x_n0 * 2 + (lane & 3) * 16;
     auto issue = [&](int kt) {
         unsigned char* st = smem + (kt % TN_STAGES) * TN_STAGE_BYTES;
-        const int k0 = k_begin + kt * TN_BK;
+        const int k0 = kt * TN_BK;
         // the row goes into the per-lane offset: only that one is checked against the buffer bounds
 #pragma unroll
         for (int j = 0; j < NA; ++j)
@@ -464,28 +391,32 @@ __device__ __forceinline__ void gemm_tn_dma_body(
             for (int r = 0; r < 4; ++r) {
                 const int m = m0 + wm + i * 16 + lk * 4 + r;
                 if (m >= Mr) continue;
-                const int out_row = (unperm_h > 0 && !split) ? (m & 3) * unperm_h + (m >> 2) : m;
+                const int out_row = unperm_h > 0 ? (m & 3) * unperm_h + (m >> 2) : m;
                 C[(size_t)out_row * ldc + n] = acc[i][j][r];
             }
         }
 }
 
 // (plain kernels around the template body: the transposing-load builtin only exists in the device pass)
-__global__ __launch_bounds__(GEMM_THREADS) void gemm_tn_dma_kernel(
-    const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb, float* __restrict__ C, int ldc,
-    int Mr, int Nc, int K, int unperm_h, int k_chunk, size_t split_stride) {
+// Several such contractions in one launch, their tiles in the order of the list: widths whose rows make no even bands for
+// the grouped launch below.
+__global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_tn_dma_list_kernel(GemmGroupArgs g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    int bx, by, bz;
-    gemm_tile_of_block(bx, by, bz);
-    gemm_tn_dma_body<4>(A, lda, B, ldb, C, ldc, Mr, Nc, K, unperm_h, k_chunk, split_stride, smem, bx, by, bz, gridDim.z > 1);
+    const int t = group_tile(g.tiles);
+    if (t < 0) return;
+    const GemmProblem q = group_problem(g, t);
+    const int r = t - q.tile_first;
+    gemm_tn_dma_body<4>(static_cast<const bf16_t*>(q.A), q.lda, static_cast<const bf16_t*>(q.B), q.ldb, q.C, q.ldc, q.Mr, q.Nc, q.K, q.unperm_h,
+                        smem, r % q.tiles_n, r / q.tiles_n);
 }
-__global__ __launch_bounds__(GEMM_THREADS) void gemm_tn_dma_tall_kernel(
-    const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb, float* __restrict__ C, int ldc,
-    int Mr, int Nc, int K, int unperm_h, int k_chunk, size_t split_stride) {
+__global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_tn_dma_list_tall_kernel(GemmGroupArgs g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    int bx, by, bz;
-    gemm_tile_of_block(bx, by, bz);
-    gemm_tn_dma_body<8>(A, lda, B, ldb, C, ldc, Mr, Nc, K, unperm_h, k_chunk, split_stride, smem, bx, by, bz, gridDim.z > 1);
+    const int t = group_tile(g.tiles);
+    if (t < 0) return;
+    const GemmProblem q = group_problem(g, t);
+    const int r = t - q.tile_first;
+    gemm_tn_dma_body<8>(static_cast<const bf16_t*>(q.A), q.lda, static_cast<const bf16_t*>(q.B), q.ldb, q.C, q.ldc, q.Mr, q.Nc, q.K, q.unperm_h,
+                        smem, r % q.tiles_n, r / q.tiles_n);
 }
 
 // Several such contractions in one launch (the weight gradients of a minibatch: same row count, different
@@ -496,7 +427,10 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_tn_dma_tall_kernel(
 // of every set, a row tile's column tiles next to each other (counters: 79 % of the L2 requests hit).  Slots s and
 // s + 32 of an XCD (the two workgroups that end up on one CU when 64 are resident per XCD) take neighbouring column
 // tiles of one row tile: the second one finds the A rows in the CU's own cache (-4 %).
-constexpr int TN_GROUP_MAX = 4;
+constexpr int TN_GROUP_MAX = GEMM_GROUP_MAX;
+// From this many workgroups on the 256-row tiles fill two per CU; fewer 128-row tiles than the second number leave more than half of
+// the chip idle, and the 64 x 64 tiles take over.
+constexpr int TN_TALL_FROM = 448, TN_WGS_FROM = 128;
 struct TnProblem {
     const bf16_t* A; const bf16_t* B; float* C;
     int lda, ldb, ldc, Mr, Nc, K, unperm_h;
@@ -528,10 +462,9 @@ __device__ __forceinline__ void gemm_tn_dma_group_body(const TnGroupArgs g, unsi
     for (int i = 1; i < TN_GROUP_MAX; ++i)
         if (pi == i) q = g.p[i];
     if (q.x_cols > 0)
-        gemm_tn_dma_body<WM, true>(q.A, q.lda, q.B, q.ldb, q.C, q.ldc, q.Mr, q.Nc, q.K, q.unperm_h, q.K, 0, smem, bx, by, 0, false,
-                                   q.x_cols, q.x_mt);
+        gemm_tn_dma_body<WM, true>(q.A, q.lda, q.B, q.ldb, q.C, q.ldc, q.Mr, q.Nc, q.K, q.unperm_h, smem, bx, by, q.x_cols, q.x_mt);
     else
-        gemm_tn_dma_body<WM>(q.A, q.lda, q.B, q.ldb, q.C, q.ldc, q.Mr, q.Nc, q.K, q.unperm_h, q.K, 0, smem, bx, by, 0, false);
+        gemm_tn_dma_body<WM>(q.A, q.lda, q.B, q.ldb, q.C, q.ldc, q.Mr, q.Nc, q.K, q.unperm_h, smem, bx, by);
 #endif
 }
 __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_tn_dma_group_kernel(TnGroupArgs g) {
@@ -543,21 +476,15 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_tn_dma_group_tall_kernel
     gemm_tn_dma_group_body<8>(g, smem);
 }
 
-// Whether a K-minor bf16 contraction can join a grouped launch, and the launch itself.
-inline bool tn_group_fits(int lda, int ldb, int Mr, int K) {
-    return lda % 2 == 0 && ldb % 2 == 0 && Mr % (GEMM_BM * 8) == 0 && (size_t)K * lda * 2 < 0x7fffffff &&
-           (size_t)K * ldb * 2 < 0x7fffffff;
-}
-#ifndef VER_TN_TALL_FROM
-#define VER_TN_TALL_FROM 448
-#endif
 struct TnGroup {
     TnGroupArgs a{};
-    bool add(const bf16_t* A, int lda, const bf16_t* B, int ldb, float* C, int ldc, int Mr, int Nc, int K, int unperm_h) {
-        if (a.n >= TN_GROUP_MAX || !tn_group_fits(lda, ldb, Mr, K)) return false;
-        TnProblem& q = a.p[a.n++];
-        q.A = A; q.B = B; q.C = C; q.lda = lda; q.ldb = ldb; q.ldc = ldc; q.Mr = Mr; q.Nc = Nc; q.K = K; q.unperm_h = unperm_h;
-        return true;
+    explicit TnGroup(const GemmGroupArgs& g) {
+        for (; a.n < g.n; ++a.n) {
+            TnProblem& q = a.p[a.n];
+            const GemmProblem& p = g.p[a.n];
+            q.A = static_cast<const bf16_t*>(p.A); q.B = static_cast<const bf16_t*>(p.B); q.C = p.C;
+            q.lda = p.lda; q.ldb = p.ldb; q.ldc = p.ldc; q.Mr = p.Mr; q.Nc = p.Nc; q.K = p.K; q.unperm_h = p.unperm_h;
+        }
     }
     // Tiles of `bm` rows: column tiles and extra columns of every problem, sets, XCDs and slots; returns the number
     // of workgroups (0 if some problem has no even bands of such tiles).
@@ -600,94 +527,45 @@ struct TnGroup {
         a.slots = slots;
         return 8 * slots;
     }
-    void launch(hipStream_t s) {
-        if (a.n == 0) return;
+    bool launch(hipStream_t s) {
         // 256-row tiles (fewer LDS and L2 bytes per MFMA) when they fill two workgroups per CU, else 128-row tiles
         int wgs = lay_out(256);
-        if (wgs >= VER_TN_TALL_FROM) {
+        if (wgs >= TN_TALL_FROM) {
             constexpr int lds = TnGeom<8>::LDS + TnGeom<8>::STAGES * TN_X_STAGE;
             (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tn_dma_group_tall_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
             hipLaunchKernelGGL(gemm_tn_dma_group_tall_kernel, dim3(wgs), dim3(GEMM_THREADS), lds, s, a);
         } else {
             wgs = lay_out(128);
+            if (wgs < TN_WGS_FROM) return false;
             constexpr int lds = TnGeom<4>::LDS + TnGeom<4>::STAGES * TN_X_STAGE;
             (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tn_dma_group_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
             hipLaunchKernelGGL(gemm_tn_dma_group_kernel, dim3(wgs), dim3(GEMM_THREADS), lds, s, a);
         }
-        a.n = 0;
+        return true;
     }
 };
-
-// How many ways to split the contraction so that the grid has a few workgroups per CU.
-inline int gemm_splits(int Mr, int Nc, int K, int BK) {
-    const long tiles = (long)((Mr + GEMM_BM - 1) / GEMM_BM) * ((Nc + GEMM_BN - 1) / GEMM_BN);
-    int s = (int)((768 + tiles - 1) / tiles);
-    const int max_s = K / (4 * BK) > 0 ? K / (4 * BK) : 1;   // at least 4 K-tiles per split
-    if (s > max_s) s = max_s;
-    if (s > 8) s = 8;
-    return s < 1 ? 1 : s;
-}
-inline size_t gemm_part_floats(int Mr, int Nc, int K, int BK) {
-    const int s = gemm_splits(Mr, Nc, K, BK);
-    return s > 1 ? (size_t)s * Mr * Nc : 0;
-}
-
-// part: scratch of gemm_part_floats(...) floats (may be NULL when that is 0 or allow_split is false).
-template <int MODE, typename TA, typename TB, bool TRANS>
-inline void gemm_launch(const TA* A, int lda, const TB* B, int ldb, float* C, int ldc, int Mr, int Nc, int K,
-                        const float* bias, int unperm_h, float* part, bool allow_split, hipStream_t s) {
-    constexpr int BK = GemmGeom<MODE>::BK;
-    const int splits = (allow_split && part) ? gemm_splits(Mr, Nc, K, BK) : 1;
-    dim3 grid((Nc + GEMM_BN - 1) / GEMM_BN, (Mr + GEMM_BM - 1) / GEMM_BM, splits);
-    if constexpr (TRANS && MODE == MODE_BF16 && sizeof(TA) == 2 && sizeof(TB) == 2) {
-        // both operands bf16 and K-minor: the LDS-direct kernel (bias is never used with these shapes)
-        if (!bias && lda % 2 == 0 && ldb % 2 == 0 && (size_t)K * lda * 2 < 0x7fffffff && (size_t)K * ldb * 2 < 0x7fffffff) {
-            // Aim at one workgroup per CU, split as little as possible: measured on the weight gradients of the largest
-            // configuration (4096 x 1024 outputs over 8192 rows), 256 tiles of 128 x 128 without any split (5.9 ms per
-            // update) beat 128 tiles of 256 x 128 split 4 ways (6.7 ms, a quarter of it the pass that adds the partial
-            // tiles) and the same 128 x 128 tiles split 2 or 3 ways (6.5, 7.1 ms); 3 or 5 stages instead of 4: 7.2, 7.5 ms.
-            const bool tall = Mr % 256 == 0 && (long)(Mr / 256) * grid.x >= TN_TARGET_WGS;   // 256-row tiles when they alone fill the chip
-            if (tall) grid.y = Mr / 256;
-            const int tiles = grid.x * grid.y;
-            int sp = (allow_split && part) ? (TN_TARGET_WGS + tiles / 2) / tiles : 1;
-            const int max_sp = K / (8 * TN_BK) > 0 ? K / (8 * TN_BK) : 1;
-            sp = sp < 1 ? 1 : (sp > 8 ? 8 : sp);
-            if (sp > max_sp) sp = max_sp;
-            if (sp > gemm_splits(Mr, Nc, K, BK)) sp = gemm_splits(Mr, Nc, K, BK);   // the scratch is sized for that many
-            grid.z = sp;
-            const int splits = sp;
-            const int k_chunk = splits == 1 ? K : ((K + splits - 1) / splits + BK - 1) / BK * BK;
-            const size_t stride = (size_t)Mr * Nc;
-            if (tall) {
-                (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tn_dma_tall_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    TnGeom<8>::LDS);
-                hipLaunchKernelGGL(gemm_tn_dma_tall_kernel, grid, dim3(GEMM_THREADS), TnGeom<8>::LDS, s, reinterpret_cast<const bf16_t*>(A),
-                                   lda, reinterpret_cast<const bf16_t*>(B), ldb, splits == 1 ? C : part, splits == 1 ? ldc : Nc, Mr, Nc,
-                                   K, unperm_h, k_chunk, stride);
-            } else {
-                (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tn_dma_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    TnGeom<4>::LDS);
-                hipLaunchKernelGGL(gemm_tn_dma_kernel, grid, dim3(GEMM_THREADS), TnGeom<4>::LDS, s, reinterpret_cast<const bf16_t*>(A),
-                                   lda, reinterpret_cast<const bf16_t*>(B), ldb, splits == 1 ? C : part, splits == 1 ? ldc : Nc, Mr, Nc,
-                                   K, unperm_h, k_chunk, stride);
-            }
-            if (splits > 1)
-                hipLaunchKernelGGL(gemm_reduce_kernel, dim3(1024), dim3(256), 0, s, part, splits, stride, Mr, Nc, C, ldc, bias,
-                                   unperm_h);
-            return;
-        }
+// The contractions collected in g (K-minor, bf16) as one launch of 128- or 256-row tiles; false where those would be too few (the
+// caller then launches g itself, in 64 x 64 tiles).
+inline bool launch_tn_group(GemmGroup& g, hipStream_t s) {
+    if (g.a.n == 0) return true;
+    if (!TnGroup(g.a).launch(s)) {
+        auto list = [&](auto kernel, int lds) {
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            hipLaunchKernelGGL(kernel, dim3(group_grid(g.a.tiles)), dim3(GEMM_THREADS), lds, s, g.a);
+        };
+        if (g.lay_out(256, GEMM_BN) >= TN_TALL_FROM) list(gemm_tn_dma_list_tall_kernel, TnGeom<8>::LDS);
+        else if (g.lay_out(128, GEMM_BN) >= TN_WGS_FROM) list(gemm_tn_dma_list_kernel, TnGeom<4>::LDS);
+        else return false;
     }
-    if (splits == 1) {
-        hipLaunchKernelGGL((gemm_kernel<MODE, TA, TB, TRANS>), grid, dim3(GEMM_THREADS), 0, s, A, lda, B, ldb, C, ldc, Mr,
-                           Nc, K, bias, unperm_h, K, (size_t)0);
-        return;
-    }
-    const int k_chunk = ((K + splits - 1) / splits + BK - 1) / BK * BK;
-    const size_t stride = (size_t)Mr * Nc;
-    hipLaunchKernelGGL((gemm_kernel<MODE, TA, TB, TRANS>), grid, dim3(GEMM_THREADS), 0, s, A, lda, B, ldb, part, Nc, Mr,
-                       Nc, K, bias, unperm_h, k_chunk, stride);
-    hipLaunchKernelGGL(gemm_reduce_kernel, dim3(1024), dim3(256), 0, s, part, splits, stride, Mr, Nc, C, ldc, bias,
-                       unperm_h);
+    g.a.n = 0;
+    return true;
+}
+
+template <int MODE, bool TRANS>
+inline void gemm_launch(const typename LdsElem<MODE>::type* A, int lda, const typename LdsElem<MODE>::type* B, int ldb, float* C, int ldc, int Mr,
+                        int Nc, int K, const float* bias, int unperm_h, hipStream_t s) {
+    const dim3 grid((Nc + GEMM_BN - 1) / GEMM_BN, (Mr + GEMM_BM - 1) / GEMM_BM);
+    hipLaunchKernelGGL((gemm_kernel<MODE, TRANS>), grid, dim3(GEMM_THREADS), 0, s, A, lda, B, ldb, C, ldc, Mr, Nc, K, bias, unperm_h);
 }
 
 }  // namespace ver

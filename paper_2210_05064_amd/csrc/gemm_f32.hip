@@ -17,7 +17,7 @@
 // us, the 128 x 128 register-staged tiles with a split contraction that ran here before -> now: the four weight gradients of 2 x
 // 512 units over 1024 rows (8.7 GFLOP) 235 -> 98, input projection 1024 x 2048 x 516 55 -> 26, input gradient 1024 x
 // 516 x 2048 55 -> 35.  Counters of the first: the CUs are busy 84 % of the launch (its last round is partly filled), the MFMAs 79 % of that.
-#include "gemm_f32.h"
+#include "gemm_group.h"
 #include "mfma.h"
 
 namespace ver {
@@ -35,12 +35,12 @@ template <int T> struct Geom {
 
 // Chunk (16 bytes) position p of LDS row r holds chunk p ^ swz(r).
 template <int T, bool KMIN> __device__ __forceinline__ int swz(int r) {
-    if (!KMIN) return (r & 7) ^ ((r >> 3) & 1);        // rows of 8 chunks, read by 16 lanes of one chunk column
+    if (!KMIN) return (r >> 1) & 7;                    // rows of 8 chunks, read by 16 lanes of one chunk column
     return T == 64 ? (r & 1) << 3 : ((r >> 1) & 1) << 2;   // 16 or 8 chunks, read by 16 lanes along each of 4 rows
 }
 
 template <int T, bool KMIN>
-__device__ __forceinline__ void tile(const F32Problem& q, int t, unsigned char* smem) {
+__device__ __forceinline__ void tile(const GemmProblem& q, int t, unsigned char* smem) {
     typedef Geom<T> G;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lk = lane >> 4;
@@ -48,8 +48,8 @@ __device__ __forceinline__ void tile(const F32Problem& q, int t, unsigned char* 
     const int wm = (wave >> 1) * G::W, wn = (wave & 1) * G::W;
     const int nk = (q.K + BK - 1) / BK;
     const int rowsA = KMIN ? q.K : q.Mr, rowsB = KMIN ? q.K : q.Nc;
-    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(q.A), 0, rowsA * q.lda * 4, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(q.B), 0, rowsB * q.ldb * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(q.A), 0, rowsA * q.lda * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(q.B), 0, rowsB * q.ldb * 4, 0x00020000);
     // A load instruction fills 1 KB of LDS (8 rows K-major; 1024 / (4 T) rows K-minor); the swizzle is applied on the global side.
     constexpr int CHUNKS = KMIN ? T / 4 : BK / 4;
     unsigned offA[G::NL], offB[G::NL];
@@ -189,61 +189,33 @@ __device__ __forceinline__ void tile(const F32Problem& q, int t, unsigned char* 
         }
 }
 
-// Workgroups go to the 8 XCDs round-robin: every XCD takes a stretch of consecutive tiles, so that the rows they share are
-// fetched into its L2 once.
 template <int T, bool KMIN>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(F32GroupArgs g) {
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmGroupArgs g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int per = gridDim.x / 8, t = (blockIdx.x % 8) * per + blockIdx.x / 8;
-    if (t >= g.tiles) return;
-    F32Problem q = g.p[0];   // uniform selects (an indexed copy of a kernel argument would live in scratch memory)
-#pragma unroll
-    for (int i = 1; i < F32_GROUP_MAX; ++i)
-        if (i < g.n && t >= g.p[i].tile_first) q = g.p[i];
+    const int t = group_tile(g.tiles);
+    if (t < 0) return;
+    const GemmProblem q = group_problem(g, t);
     tile<T, KMIN>(q, t - q.tile_first, smem);
 }
 
 template <int T, bool KMIN>
-void start(F32GroupArgs& a, int tiles, hipStream_t s) {
-    constexpr int lds = Geom<T>::STAGES * Geom<T>::STAGE;
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_f32_kernel<T, KMIN>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    a.tiles = tiles;
-    hipLaunchKernelGGL((gemm_f32_kernel<T, KMIN>), dim3((tiles + 7) / 8 * 8), dim3(256), lds, s, a);
-}
-int lay_out(F32GroupArgs& a, int T) {
-    int tiles = 0;
-    for (int i = 0; i < a.n; ++i) {
-        F32Problem& q = a.p[i];
-        q.tiles_n = (q.Nc + T - 1) / T;
-        q.tile_first = tiles;
-        tiles += q.tiles_n * ((q.Mr + T - 1) / T);
-    }
-    return tiles;
-}
-
-}  // namespace
-
-bool F32Gemm::add(const float* A, int lda, const float* B, int ldb, float* C, int ldc, int Mr, int Nc, int K, const float* bias, int unperm_h) {
-    const size_t rowsA = k_minor ? K : Mr, rowsB = k_minor ? K : Nc;
-    if (a.n >= F32_GROUP_MAX || (rowsA + BK) * lda * 4 >= 0x7fffffff || (rowsB + BK) * ldb * 4 >= 0x7fffffff ||
-        (size_t)Mr * ldc * 4 >= 0x7fffffff) return false;
-    a.p[a.n++] = F32Problem{A, B, C, bias, lda, ldb, ldc, Mr, Nc, K, unperm_h, 0, 0};
-    return true;
+void start(const GemmGroupArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL((gemm_f32_kernel<T, KMIN>), dim3(group_grid(a.tiles)), dim3(256), Geom<T>::STAGES * Geom<T>::STAGE, s, a);
 }
 
 // From this many tiles of 64 on they fill the chip.  us with tiles of 64 / 32: 512 tiles 26.2 / 30.0, 4096 367 / 434, 1056 (K-minor)
 // 99.8 / 97.3, 256 48.7 / 47.9, 144 46.1 / 35.5, 80 6.2 / 4.5, 24 (K-minor, 2048 rows) 42 / 19.
 constexpr int T64_FROM = 384;
-void F32Gemm::launch(hipStream_t s) {
-    if (a.n == 0) return;
-    const int tiles64 = lay_out(a, 64);
-    if (tiles64 >= T64_FROM) {
-        k_minor ? start<64, true>(a, tiles64, s) : start<64, false>(a, tiles64, s);
+
+}  // namespace
+
+void GemmGroup::launch_f32(hipStream_t s) {
+    if (lay_out(64) >= T64_FROM) {
+        k_minor ? start<64, true>(a, s) : start<64, false>(a, s);
     } else {
-        const int tiles32 = lay_out(a, 32);
-        k_minor ? start<32, true>(a, tiles32, s) : start<32, false>(a, tiles32, s);
+        lay_out(32);
+        k_minor ? start<32, true>(a, s) : start<32, false>(a, s);
     }
-    a.n = 0;
 }
 
 }  // namespace ver

@@ -1,0 +1,67 @@
+// Contractions of the LSTM outside the time loops, several to a launch: host interface of gemm_f32.hip and gemm_bf16.hip.
+#pragma once
+#include "common.h"
+
+namespace ver {
+
+constexpr int GEMM_GROUP_MAX = 4;
+struct GemmProblem {
+    const void* A; const void* B; float* C; const float* bias;
+    int lda, ldb, ldc, Mr, Nc, K, unperm_h;
+    int tiles_n, tile_first;   // column tiles; first tile of the problem in the launch
+};
+struct GemmGroupArgs { GemmProblem p[GEMM_GROUP_MAX]; int n, tiles; };
+
+// Up to four contractions in one launch, all with the contraction index contiguous (K-major: C = A[Mr, K] B[Nc, K]^T + bias)
+// or all with it outermost (K-minor: C = A[K, Mr]^T B[K, Nc]); operands fp32 or bf16, C and bias fp32.  Leading dimensions,
+// Nc, K (K-major) and Mr (K-minor) are multiples of 4; unperm_h > 0 stores output row m at row (m % 4) * unperm_h + m / 4.
+struct GemmGroup {
+    GemmGroupArgs a{};
+    bool k_minor, bf16;
+    GemmGroup(bool k_minor_, bool bf16_) : k_minor(k_minor_), bf16(bf16_) {}
+    // False if an array is beyond the kernels' 32-bit byte offsets (or the launch is full): not added.
+    bool add(const void* A, int lda, const void* B, int ldb, float* C, int ldc, int Mr, int Nc, int K, const float* bias, int unperm_h) {
+        const size_t rowsA = k_minor ? K : Mr, rowsB = k_minor ? K : Nc, es = bf16 ? 2 : 4, lim = 0x7fffffff;
+        constexpr size_t over = 256;   // rows that a last tile may address beyond the arrays (they read zero)
+        if (a.n >= GEMM_GROUP_MAX || (rowsA + over) * lda * es >= lim || (rowsB + over) * ldb * es >= lim || (size_t)Mr * ldc * 4 >= lim) return false;
+        a.p[a.n++] = GemmProblem{A, B, C, bias, lda, ldb, ldc, Mr, Nc, K, unperm_h, 0, 0};
+        return true;
+    }
+    // Tiles of TM rows and TN columns: numbers the tiles of all problems and returns how many there are.
+    int lay_out(int T) { return lay_out(T, T); }
+    int lay_out(int TM, int TN) {
+        int tiles = 0;
+        for (int i = 0; i < a.n; ++i) {
+            GemmProblem& q = a.p[i];
+            q.tiles_n = (q.Nc + TN - 1) / TN;
+            q.tile_first = tiles;
+            tiles += q.tiles_n * ((q.Mr + TM - 1) / TM);
+        }
+        return a.tiles = tiles;
+    }
+    void launch(hipStream_t s) {
+        if (a.n > 0) bf16 ? launch_bf16(s) : launch_f32(s);
+        a.n = 0;
+    }
+
+private:
+    void launch_f32(hipStream_t s);
+    void launch_bf16(hipStream_t s);
+};
+
+// Which tile of a launch a workgroup computes (-1: none).  Workgroups go to the 8 XCDs round-robin: every XCD takes a stretch
+// of consecutive tiles, so that the rows they share are fetched into its L2 once.
+__device__ __forceinline__ int group_tile(int tiles) {
+    const int per = gridDim.x / 8, t = (blockIdx.x % 8) * per + blockIdx.x / 8;
+    return t < tiles ? t : -1;
+}
+inline int group_grid(int tiles) { return (tiles + 7) / 8 * 8; }
+__device__ __forceinline__ GemmProblem group_problem(const GemmGroupArgs& g, int t) {
+    GemmProblem q = g.p[0];   // uniform selects (an indexed copy of a kernel argument would live in scratch memory)
+#pragma unroll
+    for (int i = 1; i < GEMM_GROUP_MAX; ++i)
+        if (i < g.n && t >= g.p[i].tile_first) q = g.p[i];
+    return q;
+}
+
+}  // namespace ver

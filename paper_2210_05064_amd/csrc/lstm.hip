@@ -11,10 +11,11 @@
 //       (forward), dz_t and W_hh dz_t (backward) - see lstm_rec.h.
 // Internally the 4H gate rows are interleaved (row = unit*4 + gate); user-facing
 // weights and gradients keep the gate-major order i,f,g,o of the declaration.
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
-#include "gemm_f32.h"
+#include "gemm_group.h"
 #include "lstm_pipe.h"
 
 namespace ver {
@@ -34,20 +35,37 @@ __device__ __forceinline__ void st4(bf16_t* p, float a, float b, float c, float 
 // 16 lanes cover a tile row in either direction.
 // All matrices and bias vectors of a call in one launch (blockIdx.z: the job; a launch per matrix took ~10 us each,
 // most of it ramp and tail).
-constexpr int PREP_MAX_JOBS = 24;   // 2 matrices + 1 bias per layer, 8 layers
+constexpr int PREP_MAX_JOBS = 25;   // 2 matrices + 1 bias per layer, 8 layers; the fp32 rows of a bf16 call
+constexpr int PREP_BIAS = 0, PREP_ROWS = -1;
 struct PrepJob {
-    const float* W;      // matrix [4H, cols] gate-major, or b_ih when cols == 0
+    const float* W;      // matrix [4H, cols] gate-major, or b_ih (bias job), or rows
     const float* b_hh;   // (bias jobs)
     void* dst; void* dstT;
-    int cols;            // 0: bias job
+    int cols;            // > 0, PREP_BIAS or PREP_ROWS
+    unsigned quads;      // (rows: groups of four elements)
 };
 struct PrepArgs { PrepJob job[PREP_MAX_JOBS]; };
+// Rows converted to the operand type, four elements per thread and step.
+template <typename E>
+__device__ __forceinline__ void convert_rows(const float* __restrict__ src, E* __restrict__ dst, unsigned quads, unsigned first, unsigned stride) {
+    for (unsigned i = first; i < quads; i += stride) {
+        const f32x4_t v = *reinterpret_cast<const f32x4_t*>(src + (size_t)i * 4);
+        st4(dst + (size_t)i * 4, v[0], v[1], v[2], v[3]);
+    }
+}
+__global__ __launch_bounds__(256) void convert_rows_kernel(const float* __restrict__ src, bf16_t* __restrict__ dst, unsigned quads) {
+    convert_rows(src, dst, quads, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
+}
 template <typename E>
 __global__ __launch_bounds__(256) void prep_weights_kernel(PrepArgs a, int H) {
     __shared__ float tile[64][65];
     const PrepJob& jb = a.job[blockIdx.z];   // (uniform index into the kernel arguments: scalar loads)
     const int cols = jb.cols;
-    if (cols == 0) {   // bias: dst[q] = b_ih + b_hh, gate rows interleaved
+    if (cols == PREP_ROWS) {
+        convert_rows(jb.W, static_cast<E*>(jb.dst), jb.quads, (blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x, gridDim.x * gridDim.y * 256);
+        return;
+    }
+    if (cols == PREP_BIAS) {   // bias: dst[q] = b_ih + b_hh, gate rows interleaved
         const int q = (blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
         if (q < 4 * H) {
             const int src = (q & 3) * H + (q >> 2);
@@ -142,17 +160,24 @@ __global__ __launch_bounds__(256) void heads_fwd_kernel(const float* __restrict_
 // multiple of 64) for a block of HB_ROWS rows, so a head weight is read once per block instead of once per row
 // (the loss gradients are wave-uniform scalars).  Bound by writing dh once.
 constexpr int HB_ROWS = 8;
+// (also in this launch: a bf16 call's fp32 rows in the operand type, for the first layer's weight gradient)
+struct RowsToConvert { const float* src; bf16_t* dst; unsigned quads; };
 __global__ __launch_bounds__(256) void heads_bwd_dh_kernel(const float* __restrict__ d_u, const float* __restrict__ d_v,
                                                            int M, int H, int A, const float* __restrict__ W_a,
                                                            const float* __restrict__ w_v, float* __restrict__ dh,
-                                                           int32_t* __restrict__ clear, int n_clear) {
+                                                           int32_t* __restrict__ clear, int n_clear, RowsToConvert rows) {
     __shared__ float s_g[HB_ROWS][64];   // the block's loss gradients: heads 0..A-1, then the value head
+    const unsigned n_blocks = (M + HB_ROWS - 1) / HB_ROWS;
+    if (blockIdx.y >= n_blocks) {   // (the blocks beyond the rows')
+        convert_rows(rows.src, rows.dst, rows.quads, ((blockIdx.y - n_blocks) * gridDim.x + blockIdx.x) * 256 + threadIdx.x, (gridDim.y - n_blocks) * gridDim.x * 256);
+        return;
+    }
     const int j = (blockIdx.x * 256 + threadIdx.x) * 4;
     const int p0 = blockIdx.y * HB_ROWS;
     // (first kernel of the backward pass: it also clears the synchronisation words of the two-layer launch that
     // follows, which saves a launch of its own)
     if (blockIdx.x == 0)
-        for (int i = blockIdx.y * 256 + threadIdx.x; i < n_clear; i += gridDim.y * 256) clear[i] = 0;
+        for (int i = blockIdx.y * 256 + threadIdx.x; i < n_clear; i += n_blocks * 256) clear[i] = 0;
     for (int i = threadIdx.x; i < HB_ROWS * 64; i += 256) {
         const int r = i >> 6, a = i & 63, p = p0 + r;
         s_g[r][a] = (p < M) ? (a < A ? d_u[(size_t)p * A + a] : (a == A ? d_v[p] : 0.f)) : 0.f;
@@ -311,7 +336,7 @@ struct LayerWs {
     float* c;     // [M, H]
     float* hout;  // [M, H]
     void* hprev;  // [M, H] operand type
-    void* hcopy;  // [M, H] operand type: h_t, for the workers of a two-layer launch (lower layer of a pair only)
+    void* hcopy;  // [M, H] operand type: h_t, for what contracts it: the workers of a two-layer launch (lower layer of a pair), in bf16 also the layer above
 };
 struct LstmWs {
     int* err;          // word 0 of the workspace
@@ -328,7 +353,7 @@ struct LstmWs {
     float* dc_state;   // [M, H]
     float* part;       // partial sums of the two-stage reductions
     float* part_b;     // [row blocks][64]: the heads' bias gradients per row block
-    float* gemm_part;  // partial tiles of GEMMs whose contraction is split over workgroups
+    bf16_t* x_op;      // [M, input_dim]: fp32 input rows of a bf16 call in the operand type
     char* ring;        // [8 groups] exchange rings of the time loops (lstm_few.h)
     float* db_part;    // [2][8][4H]: per layer of a launch and group, the sum of the gate gradients over the group's rows
     size_t bytes;
@@ -337,21 +362,6 @@ struct LstmWs {
 inline size_t part_floats(const ver_lstm_cfg& c, int M) {
     const size_t rb_heads = (size_t)(M + HW_ROWS - 1) / HW_ROWS;
     return rb_heads * (c.act_dim + 1) * c.hidden;   // the row-block partial sums of the heads' weight gradient
-}
-
-// Largest split-K scratch any GEMM of the forward or backward pass asks for (the fp32 contractions are not split).
-inline size_t gemm_part_max(const ver_lstm_cfg& c, int M) {
-    if (!c.compute) return 0;
-    const int bk = GemmGeom<MODE_BF16>::BK;
-    const int H = c.hidden;
-    size_t m = 0;
-    for (int l = 0; l < c.n_layers; ++l) {
-        const int D = l == 0 ? c.input_dim : H;
-        const size_t v[4] = {gemm_part_floats(M, 4 * H, D, bk), gemm_part_floats(M, D, 4 * H, bk),
-                             gemm_part_floats(4 * H, D, M, bk), gemm_part_floats(4 * H, H, M, bk)};
-        for (size_t x : v) m = x > m ? x : m;
-    }
-    return m;
 }
 
 inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws) {
@@ -380,7 +390,7 @@ inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws)
         L.c = cv.take<float>(Mz * H);
         L.hout = cv.take<float>(Mz * H);
         L.hprev = cv.take<char>(Mz * H * es);
-        L.hcopy = (l % 2 == 0 && l + 1 < c.n_layers) ? cv.take<char>(Mz * H * es) : nullptr;
+        L.hcopy = (l + 1 < c.n_layers && (c.compute || l % 2 == 0)) ? cv.take<char>(Mz * H * es) : nullptr;
     }
     ws->dz[0] = cv.take<char>(Mz * 4 * H * es);
     ws->dz[1] = c.n_layers >= 2 ? cv.take<char>(Mz * 4 * H * es) : ws->dz[0];
@@ -390,7 +400,7 @@ inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws)
     ws->dc_state = cv.take<float>(2 * Mz * H);
     ws->part = cv.take<float>(part_floats(c, M));
     ws->part_b = cv.take<float>((size_t)(M + HW_ROWS - 1) / HW_ROWS * 64);
-    ws->gemm_part = cv.take<float>(gemm_part_max(c, M));
+    ws->x_op = c.compute && !c.x_bf16 ? cv.take<bf16_t>(Mz * c.input_dim) : nullptr;
     ws->db_part = cv.take<float>((size_t)2 * REC_GROUPS * 4 * H);
     ws->ring = cv.take<char>(REC_GROUPS * few_ring_bytes(c.compute ? MODE_BF16 : MODE_F32, 4 * c.hidden));
     ws->bytes = cv.used;
@@ -422,17 +432,27 @@ inline bool set_lds(K kernel, size_t bytes) {
                                (int)bytes) == hipSuccess;
 }
 
-// C[M, N] = A[M, K] B[N, K]^T (+ bias), all three row-major, A and B bf16: the LDS-direct 128 x 256 tiles, one
-// workgroup per tile.  False if the shape does not fit the kernel's 32-bit byte offsets (the caller then uses
-// the general GEMM).
-inline bool launch_proj_dma(const void* A, const void* B, float* C, const float* bias, int M, int N, int K, hipStream_t s) {
-    if ((size_t)M * K * 2 >= 0x7fffffff || (size_t)N * K * 2 >= 0x7fffffff || (size_t)M * N * 4 >= 0x7fffffff) return false;
-    if (!set_lds(lstm_proj_dma_kernel, (size_t)PIPE_STAGES * PIPE_STAGE_BYTES)) return false;
-    const ProjWork pw = {A, B, C, bias, K, N, M};
-    const int tiles_n = (N + PIPE_BN - 1) / PIPE_BN, tiles_m = (M + PIPE_BM - 1) / PIPE_BM;
-    hipLaunchKernelGGL(lstm_proj_dma_kernel, dim3(tiles_m * tiles_n), dim3(REC_THREADS), (size_t)PIPE_STAGES * PIPE_STAGE_BYTES, s,
-                       pw, tiles_n);
-    return true;
+// C[M, N] = A[M, K] B[N, K]^T (+ bias), all three row-major, A and B in the operand type.  bf16 in 64 x 64 tiles while those
+// are at most four per CU, else in 128 x 256 tiles (us: 1024 tiles, 1000 x 4096 x 1044 28 with either, 2048 x 2048 x 516 15.4 and
+// 16.5; 940, 3001 x 1280 x 320 9.0 and 12; 235, 3001 x 320 x 1280 8.8 and 21; 4096, 8192 x 4096 x 1044 210 and 114).  What lies beyond
+// the 32-bit byte offsets of these kernels (only rows of the caller's can) goes to the general kernel.
+template <int MODE>
+inline int contract_rows(const typename RecGeom<MODE>::E* A, const typename RecGeom<MODE>::E* B, float* C, const float* bias, int M, int N, int K, hipStream_t s) {
+    GemmGroup g(false, MODE == MODE_BF16);
+    if (!g.add(A, K, B, K, C, N, M, N, K, bias, 0)) {
+        gemm_launch<MODE, false>(A, K, B, K, C, N, M, N, K, bias, 0, s);
+        return VER_OK;
+    }
+    if (MODE == MODE_BF16 && g.lay_out(64) > 4 * REC_GRID) {
+        if (!set_lds(lstm_proj_dma_kernel, (size_t)PIPE_STAGES * PIPE_STAGE_BYTES)) return VER_EHIP;
+        const ProjWork pw = {A, B, C, bias, K, N, M};
+        const int tiles_n = (N + PIPE_BN - 1) / PIPE_BN, tiles_m = (M + PIPE_BM - 1) / PIPE_BM;
+        hipLaunchKernelGGL(lstm_proj_dma_kernel, dim3(tiles_m * tiles_n), dim3(REC_THREADS), (size_t)PIPE_STAGES * PIPE_STAGE_BYTES, s,
+                           pw, tiles_n);
+        return VER_OK;
+    }
+    g.launch(s);
+    return VER_OK;
 }
 
 // The persistent time-loop kernels are written for the whole of one MI355X: a grid of one workgroup per CU that
@@ -480,6 +500,15 @@ inline void pipe_work(const LstmWs& ws, int dir, int M, const int32_t* t_off, Pi
 // 3001 rows in 36 pieces (bf16): 2430 -> 1843 us.
 inline bool pairs_of_layers(const ver_lstm_cfg& c) { return c.n_layers >= 2 && !c.layer_by_layer; }
 
+// The rows that layer l contracts, in the operand type.  (fp32: the lower layer of a pair leaves its h in hcopy only.)
+template <int MODE>
+inline const typename RecGeom<MODE>::E* layer_input(const ver_lstm_cfg& c, const LstmWs& ws, const void* x, int l) {
+    typedef const typename RecGeom<MODE>::E* rows_t;
+    if (l == 0) return ws.x_op ? reinterpret_cast<rows_t>(ws.x_op) : static_cast<rows_t>(x);
+    const bool copied = MODE == MODE_BF16 || (l % 2 == 1 && pairs_of_layers(c));
+    return copied ? static_cast<rows_t>(ws.layer[l - 1].hcopy) : reinterpret_cast<rows_t>(ws.layer[l - 1].hout);
+}
+
 template <int MODE>
 int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, const int32_t* batch_sizes,
             const int32_t* t_off, const float* h0, const float* c0, int seq_cap, const float* const* w,
@@ -519,10 +548,11 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             const int D = l == 0 ? c.input_dim : H;
             LayerWs& L = ws.layer[l];
             max_cols = D > max_cols ? D : max_cols;
-            pa.job[n++] = PrepJob{w[4 * l], nullptr, L.wih, L.wihT, D};
-            pa.job[n++] = PrepJob{w[4 * l + 1], nullptr, L.whh, L.whhT, H};
-            pa.job[n++] = PrepJob{w[4 * l + 2], w[4 * l + 3], L.bias, nullptr, 0};
+            pa.job[n++] = PrepJob{w[4 * l], nullptr, L.wih, L.wihT, D, 0};
+            pa.job[n++] = PrepJob{w[4 * l + 1], nullptr, L.whh, L.whhT, H, 0};
+            pa.job[n++] = PrepJob{w[4 * l + 2], w[4 * l + 3], L.bias, nullptr, PREP_BIAS, 0};
         }
+        if (ws.x_op) pa.job[n++] = PrepJob{static_cast<const float*>(x), nullptr, ws.x_op, nullptr, PREP_ROWS, (unsigned)((size_t)M * c.input_dim / 4)};
         hipLaunchKernelGGL(prep_weights_kernel<E>, dim3((max_cols + 63) / 64, 4 * H / 64, n), dim3(256), 0, s, pa, H);
     };
     // time-batched input projection: gates[M, 4H] = x W_ih^T + (b_ih + b_hh), interleaved columns
@@ -530,29 +560,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         const int D = l == 0 ? c.input_dim : H;
         LayerWs& L = ws.layer[l];
         ProfScope prof(VER_PROF_LSTM_GEMM_FWD, s);
-        if constexpr (MODE == MODE_F32) {
-            F32Gemm g(false);
-            if (g.add(l == 0 ? static_cast<const float*>(x) : ws.layer[l - 1].hout, D, static_cast<const float*>(L.wih), D, L.gates, 4 * H, M,
-                      4 * H, D, L.bias, 0)) {
-                g.launch(s);
-                return;
-            }
-        }
-        if (l == 0) {
-            if constexpr (MODE == MODE_BF16) {
-                // bf16 rows on both sides: the LDS-direct tiles of the two-layer launch, as a launch of their own
-                if (c.x_bf16 && launch_proj_dma(x, L.wih, L.gates, L.bias, M, 4 * H, D, s)) return;
-            }
-            if (c.x_bf16)
-                gemm_launch<MODE, bf16_t, E, false>(static_cast<const bf16_t*>(x), D, static_cast<const E*>(L.wih), D,
-                                                    L.gates, 4 * H, M, 4 * H, D, L.bias, 0, ws.gemm_part, MODE == MODE_BF16, s);
-            else
-                gemm_launch<MODE, float, E, false>(static_cast<const float*>(x), D, static_cast<const E*>(L.wih), D,
-                                                   L.gates, 4 * H, M, 4 * H, D, L.bias, 0, ws.gemm_part, MODE == MODE_BF16, s);
-        } else {
-            gemm_launch<MODE, float, E, false>(ws.layer[l - 1].hout, H, static_cast<const E*>(L.wih), H, L.gates,
-                                               4 * H, M, 4 * H, H, L.bias, 0, ws.gemm_part, MODE == MODE_BF16, s);
-        }
+        return contract_rows<MODE>(layer_input<MODE>(c, ws, x, l), static_cast<const E*>(L.wih), L.gates, L.bias, M, 4 * H, D, s) == VER_OK;
     };
     auto rec_args = [&](int l, bool consumer = false) {
         LayerWs& L = ws.layer[l];
@@ -589,7 +597,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     prep_all();
     bool planned = false;
     for (int l = 0; l < c.n_layers;) {
-        project(l);
+        if (!project(l)) return VER_EHIP;
         if (pairs && l + 1 < c.n_layers) {
             // the plan (of the packing: the same for every pair) and the first pair's synchronisation words from one kernel
             if (!planned) pipe_prepare_fwd(ws, MODE, wide, H / (4 * mt), M, info, batch_sizes, s);
@@ -613,6 +621,12 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             l += 1;
         }
         if (!ok) return VER_EHIP;
+        if constexpr (MODE == MODE_BF16)   // the layer above contracts this layer's h
+            if (l < c.n_layers) {
+                const unsigned quads = (unsigned)((size_t)M * H / 4);
+                hipLaunchKernelGGL(convert_rows_kernel, dim3((quads + 1023) / 1024), dim3(256), 0, s, ws.layer[l - 1].hout,
+                                   static_cast<bf16_t*>(ws.layer[l - 1].hcopy), quads);
+            }
     }
 #undef VER_FWD_DISPATCH
 #undef VER_FWD_LAUNCH
@@ -634,8 +648,10 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     // heads
     {
     ProfScope prof(VER_PROF_HEADS_BWD, s);
-    hipLaunchKernelGGL(heads_bwd_dh_kernel, dim3((H / 4 + 255) / 256, (M + HB_ROWS - 1) / HB_ROWS), dim3(256), 0, s, d_u, d_v, M, H, A, w[4 * nl],
-                       w[4 * nl + 2], ws.dh[0], top_pair ? ws.flags : nullptr, top_pair ? (int)(ws.pipe + ws.pipe_words - ws.flags) : 0);
+    const RowsToConvert rows = {static_cast<const float*>(x), ws.x_op, ws.x_op ? (unsigned)((size_t)M * c.input_dim / 4) : 0u};
+    hipLaunchKernelGGL(heads_bwd_dh_kernel, dim3((H / 4 + 255) / 256, (M + HB_ROWS - 1) / HB_ROWS + std::min(1024u, (rows.quads + 1023) / 1024)), dim3(256), 0, s,
+                       d_u, d_v, M, H, A, w[4 * nl], w[4 * nl + 2], ws.dh[0], top_pair ? ws.flags : nullptr,
+                       top_pair ? (int)(ws.pipe + ws.pipe_words - ws.flags) : 0, rows);
     const int rb_h = (M + HW_ROWS - 1) / HW_ROWS;
     hipLaunchKernelGGL(heads_wgrad_partial_kernel, dim3((H / 4 + 255) / 256, rb_h), dim3(256), 0, s, d_u, d_v, h_top, M, H,
                        A, ws.part, ws.part_b);
@@ -691,8 +707,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         } } while (0)
     // Everything of layer l that is not the time loop: dx (optional), dW_ih, dW_hh, db.  A pair's upper layer comes first
     // and leaves its weight gradients and bias sums to the launches of the lower one (last = false).
-    TnGroup dw_group;
-    F32Gemm dw_f32(true);
+    GemmGroup dw(true, MODE == MODE_BF16);
     auto layer_grads = [&](int l, float* dx, bool in_pair, bool last) {
         const int D = l == 0 ? c.input_dim : H;
         LayerWs& L = ws.layer[l];
@@ -700,43 +715,19 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         // gradient w.r.t. the layer input: dx[M, D] = dz[M, 4H] . W_ih[4H, D]
         if (dx) {
             ProfScope prof(VER_PROF_LSTM_GEMM_DX, s);
-            bool done = false;
-            if constexpr (MODE == MODE_BF16) done = launch_proj_dma(dz, L.wihT, dx, nullptr, M, D, 4 * H, s);
-            else {
-                F32Gemm g(false);
-                done = g.add(dz, 4 * H, static_cast<const float*>(L.wihT), 4 * H, dx, D, M, D, 4 * H, nullptr, 0);
-                g.launch(s);
-            }
-            if (!done)
-                gemm_launch<MODE, E, E, false>(dz, 4 * H, static_cast<const E*>(L.wihT), 4 * H, dx, D, M, D, 4 * H,
-                                               nullptr, 0, ws.gemm_part, MODE == MODE_BF16, s);
+            ok = contract_rows<MODE>(dz, static_cast<const E*>(L.wihT), dx, nullptr, M, D, 4 * H, s) == VER_OK;
         }
         // dW_ih[4H, D] = dz^T x ; dW_hh[4H, H] = dz^T h_{t-1}; stored gate-major.  The contractions of a layer or pair leave in
-        // one launch where their operands are of one type; the others are launched on the spot.
+        // one launch.
         {
         ProfScope prof(VER_PROF_LSTM_GEMM_DW, s);
-        auto contract = [&](const auto* B, float* C, int Nc) {
-            typedef typename std::remove_const<typename std::remove_pointer<decltype(B)>::type>::type TB;
-            if constexpr (MODE == MODE_F32) {
-                if (dw_f32.add(dz, 4 * H, B, Nc, C, Nc, 4 * H, Nc, M, nullptr, H)) return;
-            } else if constexpr (sizeof(TB) == 2) {
-                if (dw_group.add(dz, 4 * H, B, Nc, C, Nc, 4 * H, Nc, M, H)) return;
-            }
-            gemm_launch<MODE, E, TB, true>(dz, 4 * H, B, Nc, C, Nc, 4 * H, Nc, M, nullptr, H, ws.gemm_part, MODE == MODE_BF16, s);
+        auto contract = [&](const E* B, float* C, int Nc) {
+            if (!dw.add(dz, 4 * H, B, Nc, C, Nc, 4 * H, Nc, M, nullptr, H))
+                gemm_launch<MODE, true>(dz, 4 * H, B, Nc, C, Nc, 4 * H, Nc, M, nullptr, H, s);
         };
-        if (l > 0 && in_pair && !last)   // the layer below is the pair's lower one and left its h in operand type
-            contract(static_cast<const E*>(ws.layer[l - 1].hcopy), gw[4 * l], D);
-        else if (l > 0)
-            contract(ws.layer[l - 1].hout, gw[4 * l], D);
-        else if (MODE == MODE_BF16 && c.x_bf16)
-            contract(static_cast<const E*>(x), gw[4 * l], D);
-        else
-            contract(static_cast<const float*>(x), gw[4 * l], D);
+        contract(layer_input<MODE>(c, ws, x, l), gw[4 * l], D);
         contract(static_cast<const E*>(L.hprev), gw[4 * l + 1], H);
-        if (last) {
-            dw_group.launch(s);
-            dw_f32.launch(s);
-        }
+        if (last && (MODE == MODE_F32 || !launch_tn_group(dw, s))) dw.launch(s);
         }
         // db_ih = db_hh = column sums of dz: the time loop left one partial sum per group (a pair: both layers' sums in
         // one launch)
@@ -767,6 +758,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             }
             layer_grads(l, nullptr, true, false);   // the weight gradients of both layers leave in one grouped launch
             layer_grads(l - 1, l > 1 ? ws.dh[cur] : d_x, true, true);
+            if (!ok) return VER_EHIP;
             l -= 2;
         } else {
             fill_words(ws.flags, REC_FLAG_WORDS, 0, s);
@@ -777,6 +769,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             if (!ok) return VER_EHIP;
             }
             layer_grads(l, l > 0 ? ws.dh[cur ^ 1] : d_x, false, true);
+            if (!ok) return VER_EHIP;
             cur ^= 1;
             l -= 1;
         }

@@ -194,6 +194,18 @@ def test_fp32_contractions(ver, rows, hidden, input_dim):
                         minibatches=1), seed=rows)
 
 
+@pytest.mark.parametrize("rows,hidden,input_dim,layers,x_bf16", [
+    (63, 64, 4, 1, False), (65, 64, 36, 1, True), (128, 128, 68, 2, False), (129, 192, 132, 3, True),   # 64 x 64 tiles and their edges
+    (1100, 1024, 260, 1, True),    # projection in 128 x 256 tiles
+    (200, 320, 644, 2, False),     # 128-row tiles in list order
+    (150, 960, 932, 2, True)])     # 256-row tiles in list order
+def test_bf16_contractions(ver, rows, hidden, input_dim, layers, x_bf16):
+    """Tiles of the bf16 contractions at their edges; input widths that are not a multiple of 8 (the 16-byte chunk that
+    straddles the end of a row); fp32 input rows, converted on the way."""
+    case(ver, wl.scaled(wl.WORKLOADS["manip"], budget=rows, n_envs=max(2, rows // 25), hidden=hidden, input_dim=input_dim, n_layers=layers,
+                        p_done=0.05, minibatches=1), seed=rows, compute=1, x_bf16=x_bf16)
+
+
 def test_packing_order_invariance_on_device(ver):
     """Another random order of the same sequences (B = 1): identical weight gradients up to rounding."""
     w = wl.scaled(wl.WORKLOADS["manip"], budget=400, n_envs=10, hidden=64, input_dim=16, p_done=0.03,
