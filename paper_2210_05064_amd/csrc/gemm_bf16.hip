@@ -177,12 +177,144 @@ __global__ __launch_bounds__(256) void gemm_bf16_k_minor_kernel(GemmGroupArgs g)
     tile<true>(q, t - q.tile_first, smem);
 }
 
+// ---- large K-major contractions: 256 x 256 tiles, 8 waves (2 x 4 of 128 x 64), one workgroup per CU ------------------------
+// K-tiles of 64 in two stages of 64 KB, one barrier per K-tile (2048 MFMA cycles per SIMD).  A K-tile is multiplied in two halves
+// of 32; the operands of a half are read between the MFMAs of the half before it, one read after two MFMAs: read in one go
+// they hold the wave's MFMAs up while the LDS serves all eight waves at once (2 to 5 % slower).  1169 TFLOP/s on 8192 x 8192 x
+// 8192 (the library 1132).  The projections have short contractions and write 4 bytes per 2 K flops: 8192 x 4096 x 1044 bf16 takes 91
+// us, of which 27 are the 134 MB of results (after each round of tiles, with no MFMAs beside them), and rows of 1044 are not
+// aligned to cache lines (83 us with 1088); 114 us with 128 x 256 tiles, 424 against 475 on 32768 rows.  Tried: K-tiles of 32 in four stages
+// (64-byte row pieces: 101 us), 16-byte stores of a transposed product (97).
+constexpr int LT = 256, L_THREADS = 512, L_OPERAND = LT * BK * 2, L_STAGE = 2 * L_OPERAND, L_NL = L_OPERAND / 1024 / 8, L_STAGES = 2;
+__global__ __launch_bounds__(L_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_large_kernel(GemmGroupArgs g) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_l[];
+    const int t = group_tile(g.tiles);
+    if (t < 0) return;
+    const GemmProblem& q = g.p[0];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lk = lane >> 4;
+    // tiles in bands of 4 rows of tiles, column by column: the 32 workgroups of an XCD that run at a time share 4 rows and 8 columns
+    const int band = t / (4 * q.tiles_n), rows_m = (q.Mr + LT - 1) / LT, in_band = min(4, rows_m - band * 4), rem = t - band * 4 * q.tiles_n;
+    const int m0 = (band * 4 + rem % in_band) * LT, n0 = rem / in_band * LT;
+    const int wm = (wave >> 2) * 128, wn = (wave & 3) * 64;
+    const int nk = (q.K + BK - 1) / BK;
+    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(q.A), 0, q.Mr * q.lda * 2, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(q.B), 0, q.Nc * q.ldb * 2, 0x00020000);
+    // a load instruction fills 8 rows (lane -> row lane / 8, position lane % 8); rows beyond the matrix repeat its last one
+    unsigned offA[L_NL], offB[L_NL];
+    const int kc0 = ((lane & 7) ^ ((lane >> 4) & 3)) * 8;   // this lane's first k in the K-tile for even j; odd j: ^ 32 (the swizzle (row >> 1) & 7)
+#pragma unroll
+    for (int j = 0; j < L_NL; ++j) {
+        const int row = (wave * L_NL + j) * 8 + (lane >> 3), kc = (j & 1) ? kc0 ^ 32 : kc0;
+        offA[j] = ((unsigned)min(m0 + row, q.Mr - 1) * q.lda + kc) * 2;
+        offB[j] = ((unsigned)min(n0 + row, q.Nc - 1) * q.ldb + kc) * 2;
+    }
+    auto issue = [&](int kt) {
+        unsigned char* st = smem_l + (kt & 1) * L_STAGE + wave * L_NL * 1024;
+        const bool in[2] = {kt * BK + kc0 < q.K, kt * BK + (kc0 ^ 32) < q.K};
+#pragma unroll
+        for (int j = 0; j < L_NL; ++j) {
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_ptr_t)(st + j * 1024), 16, in[j & 1] ? offA[j] + kt * (BK * 2) : 0xFFFFFFF0u, 0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, (lds_ptr_t)(st + L_OPERAND + j * 1024), 16, in[j & 1] ? offB[j] + kt * (BK * 2) : 0xFFFFFFF0u, 0, 0, 0);
+        }
+    };
+    f32x4_t acc[8][4];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    struct Operands { u16x8_t a[8], b[4]; };
+    // row wm + i * 16 + lr: (row >> 1) & 7 = lr >> 1, the same for every i
+    const int sw = lr >> 1, rowA = (wm + lr) * 128, rowB = L_OPERAND + (wn + lr) * 128;
+    auto read = [&](int kt, int half, Operands& o) {
+        const unsigned char* st = smem_l + (kt & 1) * L_STAGE + (((half * 4 + lk) ^ sw) << 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o.b[j] = *reinterpret_cast<const u16x8_t*>(st + rowB + j * 2048);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o.a[i] = *reinterpret_cast<const u16x8_t*>(st + rowA + i * 2048);
+    };
+    auto multiply = [&](const Operands& o) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = mfma_bf16_16x16x32(o.a[i], o.b[j], acc[i][j]);
+    };
+    auto trim = [&] {   // (as above)
+        if (q.K % 8 == 0) return;
+        const int row = tid & (LT - 1), c = (q.K % BK) >> 3;
+        *reinterpret_cast<u64_t*>(smem_l + (nk - 1) % L_STAGES * L_STAGE + (tid / LT) * L_OPERAND + row * 128 + ((c ^ ((row >> 1) & 7)) << 4) + 8) = 0;
+        bar_lds();
+    };
+    issue(0);
+    if (nk > 1) {
+        issue(1);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * L_NL) : "memory");
+    } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    bar_lds();
+    if (nk == 1) trim();
+    Operands lo, hi;
+    read(0, 0, lo);
+    for (int kt = 0; kt < nk - 1; ++kt) {
+        read(kt, 1, hi);
+        multiply(lo);
+#pragma unroll
+        for (int x = 0; x < 12; ++x) {   // two MFMAs, one LDS read
+            __builtin_amdgcn_sched_group_barrier(0x8, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x8, 8, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's loads of K-tile kt + 1 have landed,
+        bar_lds();                                         // everyone's have, and everyone has read K-tile kt
+        if (kt + 2 < nk) issue(kt + 2);
+        if (kt + 2 == nk) trim();
+        __builtin_amdgcn_sched_barrier(0);
+        read(kt + 1, 0, lo);
+        multiply(hi);
+#pragma unroll
+        for (int x = 0; x < 12; ++x) {
+            __builtin_amdgcn_sched_group_barrier(0x8, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x8, 8, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    read(nk - 1, 1, hi);
+    multiply(lo);
+    multiply(hi);
+    const __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(q.C, 0, q.Mr * q.ldc * 4, 0x00020000);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int n = n0 + wn + j * 16 + lr;
+        const float bv = q.bias && n < q.Nc ? q.bias[n] : 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                // (rows beyond the matrix are beyond the buffer: dropped)
+                const unsigned at = n < q.Nc ? ((unsigned)(m0 + wm + i * 16 + lk * 4 + r) * q.ldc + n) * 4 : 0xFFFFFFF0u;
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][r] + bv), rsC, at, 0, 0);
+            }
+    }
+}
+
 }  // namespace
 
 void GemmGroup::launch_bf16(hipStream_t s) {
     lay_out(T);
     if (k_minor) hipLaunchKernelGGL(gemm_bf16_k_minor_kernel, dim3(group_grid(a.tiles)), dim3(256), 0, s, a);
     else hipLaunchKernelGGL(gemm_bf16_kernel, dim3(group_grid(a.tiles)), dim3(256), 0, s, a);
+}
+
+bool GemmGroup::launch_large(hipStream_t s) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_large_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            L_STAGES * L_STAGE) != hipSuccess) return false;
+    lay_out(LT);
+    hipLaunchKernelGGL(gemm_bf16_large_kernel, dim3(group_grid(a.tiles)), dim3(L_THREADS), L_STAGES * L_STAGE, s, a);
+    a.n = 0;
+    return true;
 }
 
 }  // namespace ver

@@ -43,6 +43,9 @@ struct GemmGroup {
         if (a.n > 0) bf16 ? launch_bf16(s) : launch_f32(s);
         a.n = 0;
     }
+    // One K-major bf16 contraction in 256 x 256 tiles (false: not launched).
+    static constexpr int LARGE_TILE = 256;
+    bool launch_large(hipStream_t s);
 
 private:
     void launch_f32(hipStream_t s);

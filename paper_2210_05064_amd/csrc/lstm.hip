@@ -433,9 +433,11 @@ inline bool set_lds(K kernel, size_t bytes) {
 }
 
 // C[M, N] = A[M, K] B[N, K]^T (+ bias), all three row-major, A and B in the operand type.  bf16 in 64 x 64 tiles while those
-// are at most four per CU, else in 128 x 256 tiles (us: 1024 tiles, 1000 x 4096 x 1044 28 with either, 2048 x 2048 x 516 15.4 and
-// 16.5; 940, 3001 x 1280 x 320 9.0 and 12; 235, 3001 x 320 x 1280 8.8 and 21; 4096, 8192 x 4096 x 1044 210 and 114).  What lies beyond
-// the 32-bit byte offsets of these kernels (only rows of the caller's can) goes to the general kernel.
+// are at most four per CU (us, 64 x 64 and 128 x 256 tiles: 1024 tiles, 1000 x 4096 x 1044 28 and 28, 2048 x 2048 x 516 15.4 and
+// 16.5; 940, 3001 x 1280 x 320 9.0 and 12; 235, 3001 x 320 x 1280 8.8 and 21; 4096, 8192 x 4096 x 1044 210 and 114).  Beyond that one
+// tile per CU at a time: 256 x 256 or 128 x 256, whichever's rounds take less; a round of the larger ones takes 1.6 times as long
+// (45 and 28 us at K = 1044).  What lies beyond the 32-bit byte offsets of these kernels (only rows of the caller's can) goes
+// to the general kernel.
 template <int MODE>
 inline int contract_rows(const typename RecGeom<MODE>::E* A, const typename RecGeom<MODE>::E* B, float* C, const float* bias, int M, int N, int K, hipStream_t s) {
     GemmGroup g(false, MODE == MODE_BF16);
@@ -444,6 +446,8 @@ inline int contract_rows(const typename RecGeom<MODE>::E* A, const typename RecG
         return VER_OK;
     }
     if (MODE == MODE_BF16 && g.lay_out(64) > 4 * REC_GRID) {
+        auto rounds = [](int tiles) { return (tiles + REC_GRID - 1) / REC_GRID; };
+        if (8 * rounds(g.lay_out(GemmGroup::LARGE_TILE)) <= 5 * rounds(g.lay_out(PIPE_BM, PIPE_BN))) return g.launch_large(s) ? VER_OK : VER_EHIP;
         if (!set_lds(lstm_proj_dma_kernel, (size_t)PIPE_STAGES * PIPE_STAGE_BYTES)) return VER_EHIP;
         const ProjWork pw = {A, B, C, bias, K, N, M};
         const int tiles_n = (N + PIPE_BN - 1) / PIPE_BN, tiles_m = (M + PIPE_BM - 1) / PIPE_BM;

@@ -197,6 +197,7 @@ def test_fp32_contractions(ver, rows, hidden, input_dim):
 @pytest.mark.parametrize("rows,hidden,input_dim,layers,x_bf16", [
     (63, 64, 4, 1, False), (65, 64, 36, 1, True), (128, 128, 68, 2, False), (129, 192, 132, 3, True),   # 64 x 64 tiles and their edges
     (1100, 1024, 260, 1, True),    # projection in 128 x 256 tiles
+    (4100, 512, 132, 1, True),     # projection in 256 x 256 tiles, last rows of tiles partly filled
     (200, 320, 644, 2, False),     # 128-row tiles in list order
     (150, 960, 932, 2, True)])     # 256-row tiles in list order
 def test_bf16_contractions(ver, rows, hidden, input_dim, layers, x_bf16):
