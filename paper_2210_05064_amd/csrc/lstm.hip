@@ -35,14 +35,14 @@ __device__ __forceinline__ void st4(bf16_t* p, float a, float b, float c, float 
 // 16 lanes cover a tile row in either direction.
 // All matrices and bias vectors of a call in one launch (blockIdx.z: the job; a launch per matrix took ~10 us each,
 // most of it ramp and tail).
-constexpr int PREP_MAX_JOBS = 25;   // 2 matrices + 1 bias per layer, 8 layers; the fp32 rows of a bf16 call
-constexpr int PREP_BIAS = 0, PREP_ROWS = -1;
+constexpr int PREP_MAX_JOBS = 26;   // 2 matrices + 1 bias per layer, 8 layers; the fp32 rows of a bf16 call; words to clear
+constexpr int PREP_BIAS = 0, PREP_ROWS = -1, PREP_CLEAR = -2;
 struct PrepJob {
     const float* W;      // matrix [4H, cols] gate-major, or b_ih (bias job), or rows
     const float* b_hh;   // (bias jobs)
     void* dst; void* dstT;
-    int cols;            // > 0, PREP_BIAS or PREP_ROWS
-    unsigned quads;      // (rows: groups of four elements)
+    int cols;            // > 0, PREP_BIAS, PREP_ROWS or PREP_CLEAR
+    unsigned quads;      // rows: groups of four elements; clear: words
 };
 struct PrepArgs { PrepJob job[PREP_MAX_JOBS]; };
 // Rows converted to the operand type, four elements per thread and step.
@@ -63,6 +63,11 @@ __global__ __launch_bounds__(256) void prep_weights_kernel(PrepArgs a, int H) {
     const int cols = jb.cols;
     if (cols == PREP_ROWS) {
         convert_rows(jb.W, static_cast<E*>(jb.dst), jb.quads, (blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x, gridDim.x * gridDim.y * 256);
+        return;
+    }
+    if (cols == PREP_CLEAR) {
+        for (unsigned i = (blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < jb.quads; i += gridDim.x * gridDim.y * 256)
+            static_cast<int32_t*>(jb.dst)[i] = 0;
         return;
     }
     if (cols == PREP_BIAS) {   // bias: dst[q] = b_ih + b_hh, gate rows interleaved
@@ -98,12 +103,6 @@ __global__ __launch_bounds__(256) void prep_weights_kernel(PrepArgs a, int H) {
 }
 
 // ---------------------------------------------------------------- heads
-__device__ __forceinline__ float wave_sum_all(float v) {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, VER_WAVE);
-    return v;
-}
-
 // head_out[p][a] = W_a[a] . h[p] + b_a[a];  value[p] = w_v . h[p] + b_v: a skinny fp32 GEMM (at most 64 columns)
 // bound by reading h once.  One workgroup per 16 rows, fp32 MFMA 16x16x4 with the heads (action outputs, then the
 // value) on the N dimension, 16 at a time; its four waves take a quarter of the contraction each (H is a multiple
@@ -156,127 +155,125 @@ __global__ __launch_bounds__(256) void heads_fwd_kernel(const float* __restrict_
     }
 }
 
-// dh[p][j] = sum_a d_u[p][a] W_a[a][j] + d_v[p] w_v[j].  A thread owns 4 adjacent columns (16-byte stores; H is a
-// multiple of 64) for a block of HB_ROWS rows, so a head weight is read once per block instead of once per row
-// (the loss gradients are wave-uniform scalars).  Bound by writing dh once.
-constexpr int HB_ROWS = 8;
-// (also in this launch: a bf16 call's fp32 rows in the operand type, for the first layer's weight gradient)
-struct RowsToConvert { const float* src; bf16_t* dst; unsigned quads; };
-__global__ __launch_bounds__(256) void heads_bwd_dh_kernel(const float* __restrict__ d_u, const float* __restrict__ d_v,
-                                                           int M, int H, int A, const float* __restrict__ W_a,
-                                                           const float* __restrict__ w_v, float* __restrict__ dh,
-                                                           int32_t* __restrict__ clear, int n_clear, RowsToConvert rows) {
+// The heads' part of the backward pass, one launch (nothing in it depends on anything else in it); blockIdx.y says which:
+//  * dh[p][j] = sum_a d_u[p][a] W_a[a][j] + d_v[p] w_v[j].  A thread owns 4 adjacent columns (16-byte stores; H is a
+//    multiple of 64) for a block of HB_ROWS rows, so a head weight is read once per block instead of once per row.  Bound by
+//    writing dh once.  These blocks also clear the synchronisation words of the time loop that follows.
+//  * The weight gradients' partial sums over blocks of HW_ROWS rows: part[rb][a][j] = sum_{p in block rb} du(p,a) h[p][j], a =
+//    0..A (A = value head), and the same of the bias gradients.  A wave takes 64 columns and the block's rows on fp32 MFMAs,
+//    heads on M (16 at a time), rows on K: 4 rows and 64 columns (16 bytes per lane) per load of h, all loads of a wave in
+//    flight at once.  Bound by reading h once.  (A thread per 4 columns walking over the rows four at a time, eight
+//    dependent rounds: 11 us where this takes 4, on 59 rows as on 1000.)
+//  * a bf16 call's fp32 rows in the operand type, for the first layer's weight gradient.
+constexpr int HB_ROWS = 8, HW_ROWS = 32;
+struct HeadsBwdArgs {
+    const float* d_u; const float* d_v; const float* W_a; const float* w_v; const float* h;
+    float* dh; float* part; float* part_b;
+    int32_t* clear;
+    const float* rows; bf16_t* rows_op;
+    int M, H, A, n_clear;
+    unsigned quads;          // (rows)
+    int dh_blocks, w_blocks; // blockIdx.y below dh_blocks: dh; then w_blocks of weight-gradient blocks; then rows
+};
+__device__ __forceinline__ void heads_dh_block(const HeadsBwdArgs& a, int block) {
     __shared__ float s_g[HB_ROWS][64];   // the block's loss gradients: heads 0..A-1, then the value head
-    const unsigned n_blocks = (M + HB_ROWS - 1) / HB_ROWS;
-    if (blockIdx.y >= n_blocks) {   // (the blocks beyond the rows')
-        convert_rows(rows.src, rows.dst, rows.quads, ((blockIdx.y - n_blocks) * gridDim.x + blockIdx.x) * 256 + threadIdx.x, (gridDim.y - n_blocks) * gridDim.x * 256);
-        return;
-    }
+    const int M = a.M, H = a.H, A = a.A;
     const int j = (blockIdx.x * 256 + threadIdx.x) * 4;
-    const int p0 = blockIdx.y * HB_ROWS;
-    // (first kernel of the backward pass: it also clears the synchronisation words of the two-layer launch that
-    // follows, which saves a launch of its own)
+    const int p0 = block * HB_ROWS;
     if (blockIdx.x == 0)
-        for (int i = blockIdx.y * 256 + threadIdx.x; i < n_clear; i += n_blocks * 256) clear[i] = 0;
+        for (int i = block * 256 + threadIdx.x; i < a.n_clear; i += a.dh_blocks * 256) a.clear[i] = 0;
     for (int i = threadIdx.x; i < HB_ROWS * 64; i += 256) {
-        const int r = i >> 6, a = i & 63, p = p0 + r;
-        s_g[r][a] = (p < M) ? (a < A ? d_u[(size_t)p * A + a] : (a == A ? d_v[p] : 0.f)) : 0.f;
+        const int r = i >> 6, e = i & 63, p = p0 + r;
+        s_g[r][e] = (p < M) ? (e < A ? a.d_u[(size_t)p * A + e] : (e == A ? a.d_v[p] : 0.f)) : 0.f;
     }
     __syncthreads();
     if (j >= H) return;
     f32x4_t s[HB_ROWS];
-    const f32x4_t wv = *reinterpret_cast<const f32x4_t*>(w_v + j);
+    const f32x4_t wv = *reinterpret_cast<const f32x4_t*>(a.w_v + j);
 #pragma unroll
     for (int r = 0; r < HB_ROWS; ++r) {
         const float g = s_g[r][A];
         s[r] = f32x4_t{g * wv[0], g * wv[1], g * wv[2], g * wv[3]};
     }
-    for (int a = 0; a < A; ++a) {
-        const f32x4_t w = *reinterpret_cast<const f32x4_t*>(W_a + (size_t)a * H + j);
+#pragma unroll 4
+    for (int e = 0; e < A; ++e) {
+        const f32x4_t w = *reinterpret_cast<const f32x4_t*>(a.W_a + (size_t)e * H + j);
 #pragma unroll
         for (int r = 0; r < HB_ROWS; ++r) {
-            const float g = s_g[r][a];   // same address in every lane: a broadcast read
+            const float g = s_g[r][e];   // same address in every lane: a broadcast read
             s[r][0] += g * w[0]; s[r][1] += g * w[1]; s[r][2] += g * w[2]; s[r][3] += g * w[3];
         }
     }
 #pragma unroll
     for (int r = 0; r < HB_ROWS; ++r)
-        if (p0 + r < M) *reinterpret_cast<f32x4_t*>(dh + (size_t)(p0 + r) * H + j) = s[r];
+        if (p0 + r < M) *reinterpret_cast<f32x4_t*>(a.dh + (size_t)(p0 + r) * H + j) = s[r];
 }
-
-// Partial sums over a block of rows: part[rb][a][j] = sum_{p in block rb} du(p,a) * h[p][j], a = 0..A (A = value head).
-// A thread owns 4 adjacent columns (16-byte loads of h; H is a multiple of 64) and reads h once per 8 heads, four
-// rows in flight; the loss gradients are wave-uniform scalars.  Bound by reading h once.
-constexpr int HW_ROWS = 32;  // rows per row block
-__global__ __launch_bounds__(256) void heads_wgrad_partial_kernel(const float* __restrict__ d_u,
-                                                                  const float* __restrict__ d_v,
-                                                                  const float* __restrict__ h, int M, int H, int A,
-                                                                  float* __restrict__ part, float* __restrict__ part_b) {
-    __shared__ float s_g[HW_ROWS][64];   // the block's loss gradients: heads 0..A-1, then the value head, then zeros
-    const int j = (blockIdx.x * 256 + threadIdx.x) * 4;
-    const int rb = blockIdx.y;
-    const int p_lo = rb * HW_ROWS, p_hi = min(M, p_lo + HW_ROWS);
-    for (int i = threadIdx.x; i < HW_ROWS * 64; i += 256) {
-        const int r = i >> 6, a = i & 63, p = p_lo + r;
-        s_g[r][a] = (p < p_hi) ? (a < A ? d_u[(size_t)p * A + a] : (a == A ? d_v[p] : 0.f)) : 0.f;
-    }
-    __syncthreads();
-    // bias gradients: the block's sum of every head's loss gradient (first column block only), rows in order
-    if (blockIdx.x == 0 && (int)threadIdx.x <= A) {
-        float sb = 0.f;
-        for (int r = 0; r < HW_ROWS; ++r) sb += s_g[r][threadIdx.x];
-        part_b[(size_t)rb * 64 + threadIdx.x] = sb;
-    }
-    if (j >= H) return;
-    // 16 heads per pass over the block's rows (one pass for every policy of the paper: 4 or 11 outputs + the value)
+__device__ __forceinline__ void heads_wgrad_block(const HeadsBwdArgs& a, int block) {
+    const int M = a.M, H = a.H, A = a.A, groups = H / 64;   // groups of 64 columns
+    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+    const int unit = block * 4 + (threadIdx.x >> 6), rb = unit / groups, j = unit % groups * 64 + lr * 4;
+    const int p0 = rb * HW_ROWS + lk;   // this lane's rows: p0 + 4 s
+    if (rb * HW_ROWS >= M) return;
+    constexpr int STEPS = HW_ROWS / 4;
+    f32x4_t hv[STEPS];
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) hv[k] = *reinterpret_cast<const f32x4_t*>(a.h + (size_t)min(p0 + 4 * k, M - 1) * H + j);
     for (int a0 = 0; a0 <= A; a0 += 16) {
-        f32x4_t acc[16];
+        const int e = a0 + lr;   // this lane's head
+        float g[STEPS], sum = 0.f;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        for (int p = p_lo; p < p_hi; p += 4) {
-            f32x4_t hv[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                hv[u] = (p + u < p_hi) ? *reinterpret_cast<const f32x4_t*>(h + (size_t)(p + u) * H + j) : f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (p + u >= p_hi) continue;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const float g = s_g[p + u - p_lo][a0 + e];   // same address in every lane: a broadcast read
-                    acc[e][0] += g * hv[u][0]; acc[e][1] += g * hv[u][1]; acc[e][2] += g * hv[u][2]; acc[e][3] += g * hv[u][3];
-                }
-            }
+        for (int k = 0; k < STEPS; ++k) {
+            const int p = min(p0 + 4 * k, M - 1);
+            const float* src = e < A ? a.d_u + (size_t)p * A + e : a.d_v + p;
+            g[k] = *src;
         }
+        f32x4_t acc[4];
 #pragma unroll
-        for (int e = 0; e < 16; ++e)
-            if (a0 + e <= A) *reinterpret_cast<f32x4_t*>(part + ((size_t)rb * (A + 1) + a0 + e) * H + j) = acc[e];
+        for (int t = 0; t < 4; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < STEPS; ++k) {
+            const bool in = e <= A && p0 + 4 * k < M;
+            const float gk = in ? g[k] : 0.f;
+            sum += gk;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[t] = mfma_f32_16x16x4(gk, p0 + 4 * k < M ? hv[k][t] : 0.f, acc[t]);
+        }
+        // element r of lane l: head a0 + lk * 4 + r, columns j .. j + 3 (one of each of the four products)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int o = a0 + lk * 4 + r;
+            if (o <= A) *reinterpret_cast<f32x4_t*>(a.part + ((size_t)rb * (A + 1) + o) * H + j) = f32x4_t{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+        }
+        if (unit % groups == 0) {   // bias gradients: the four lanes of a head together
+            sum += __shfl_xor(sum, 16, VER_WAVE);
+            sum += __shfl_xor(sum, 32, VER_WAVE);
+            if (lk == 0 && e <= A) a.part_b[(size_t)rb * 64 + e] = sum;
+        }
+    }
+}
+__global__ __launch_bounds__(256) void heads_bwd_kernel(HeadsBwdArgs a) {
+    const int y = blockIdx.y;
+    if (y < a.dh_blocks) {
+        heads_dh_block(a, y);
+    } else if (y < a.dh_blocks + a.w_blocks) {
+        heads_wgrad_block(a, (y - a.dh_blocks) * gridDim.x + blockIdx.x);
+    } else {
+        const unsigned first = (y - a.dh_blocks - a.w_blocks) * gridDim.x + blockIdx.x;
+        convert_rows(a.rows, a.rows_op, a.quads, first * 256 + threadIdx.x, (gridDim.y - a.dh_blocks - a.w_blocks) * gridDim.x * 256);
     }
 }
 // One workgroup adds the row blocks' partial sums for 64 columns of one head: its four waves take a quarter of the
 // row blocks each (in index order, 8 loads in flight), and the four shares are added in wave order.
 constexpr int HF_COLS = 64;
-__global__ __launch_bounds__(256) void heads_wgrad_final_kernel(const float* __restrict__ part, const float* __restrict__ part_b, int n_rb,
-                                                                int H, int A, float* __restrict__ dW_a, float* __restrict__ dw_v,
-                                                                float* __restrict__ db_a, float* __restrict__ db_v) {
+struct HeadsFinalArgs {
+    const float* part; const float* part_b;
+    float* dW_a; float* dw_v; float* db_a; float* db_v;
+    int n_rb, H, A;
+};
+__device__ __forceinline__ void heads_final_block(const HeadsFinalArgs& q, int bx, int a) {
     __shared__ float red[256];
-    const int lane = threadIdx.x & 63, share = threadIdx.x >> 6;
-    const int j = blockIdx.x * HF_COLS + lane;
-    const int a = blockIdx.y;
-    if (blockIdx.x == 0) {
-        float sb = 0.f;
-        for (int rb = threadIdx.x; rb < n_rb; rb += 256) sb += part_b[(size_t)rb * 64 + a];
-        red[threadIdx.x] = sb;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            if (a < A) db_a[a] = red[0]; else db_v[0] = red[0];
-        }
-        __syncthreads();
-    }
+    const int lane = threadIdx.x & 63, share = threadIdx.x >> 6, n_rb = q.n_rb, H = q.H, A = q.A;
+    const int j = bx * HF_COLS + lane;
     const int per = (n_rb + 3) / 4, rb_end = min(n_rb, (share + 1) * per);
     float s = 0.f;
     int rb = share * per;
@@ -284,43 +281,62 @@ __global__ __launch_bounds__(256) void heads_wgrad_final_kernel(const float* __r
         for (; rb + 8 <= rb_end; rb += 8) {   // 8 loads in flight, added in index order
             float v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = part[((size_t)(rb + u) * (A + 1) + a) * H + j];
+            for (int u = 0; u < 8; ++u) v[u] = q.part[((size_t)(rb + u) * (A + 1) + a) * H + j];
 #pragma unroll
             for (int u = 0; u < 8; ++u) s += v[u];
         }
-        for (; rb < rb_end; ++rb) s += part[((size_t)rb * (A + 1) + a) * H + j];
+        for (; rb < rb_end; ++rb) s += q.part[((size_t)rb * (A + 1) + a) * H + j];
     }
     red[threadIdx.x] = s;
     __syncthreads();
     if (share == 0 && j < H) {
         s = ((red[lane] + red[64 + lane]) + red[128 + lane]) + red[192 + lane];
-        if (a < A) dW_a[(size_t)a * H + j] = s; else dw_v[j] = s;
+        if (a < A) q.dW_a[(size_t)a * H + j] = s; else q.dw_v[j] = s;
+    }
+    if (bx != 0) return;
+    float sb = 0.f;
+    for (int i = threadIdx.x; i < n_rb; i += 256) sb += q.part_b[(size_t)i * 64 + a];
+    __syncthreads();
+    red[threadIdx.x] = sb;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        if (a < A) q.db_a[a] = red[0]; else q.db_v[0] = red[0];
     }
 }
 
-// out[perm(c)] (and out2) = sum over the n_rb rows of part[n_rb][cols], in row order (deterministic);
-// unperm_h > 0 maps interleaved column c to (c%4)*H + c/4.
-// blockIdx.y = 1: the second set (the other layer of a two-layer launch), whose partial sums follow at part_stride.
-__global__ __launch_bounds__(256) void colsum_final_kernel(const float* __restrict__ part, int n_rb, int cols,
-                                                           int unperm_h, float* __restrict__ out,
-                                                           float* __restrict__ out2, size_t part_stride,
-                                                           float* __restrict__ out_b, float* __restrict__ out2_b) {
-    const int c = blockIdx.x * 256 + threadIdx.x;
+// The bias gradients of a layer (sets = 1) or a pair of layers (2): out[(c % 4) * H + c / 4] (and out2) = sum over the n_rb
+// rows of part[n_rb][4H], in row order (deterministic); the second set's sums follow at part_stride.
+struct BiasFinalArgs {
+    const float* part; size_t part_stride;
+    float* out[2]; float* out2[2];
+    int n_rb, H, sets;
+};
+__device__ __forceinline__ void bias_final_block(const BiasFinalArgs& q, int bx, int set) {
+    const int c = bx * 256 + threadIdx.x, cols = 4 * q.H;
     if (c >= cols) return;
-    if (blockIdx.y == 1) { part += part_stride; out = out_b; out2 = out2_b; }
+    const float* part = q.part + (set == 1 ? q.part_stride : 0);
     float s = 0.f;
     int rb = 0;
-    for (; rb + 8 <= n_rb; rb += 8) {   // 8 loads in flight, added in index order
+    for (; rb + 8 <= q.n_rb; rb += 8) {   // 8 loads in flight, added in index order
         float v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = part[(size_t)(rb + u) * cols + c];
 #pragma unroll
         for (int u = 0; u < 8; ++u) s += v[u];
     }
-    for (; rb < n_rb; ++rb) s += part[(size_t)rb * cols + c];
-    const int dst = unperm_h > 0 ? (c & 3) * unperm_h + (c >> 2) : c;
-    out[dst] = s;
-    if (out2) out2[dst] = s;
+    for (; rb < q.n_rb; ++rb) s += part[(size_t)rb * cols + c];
+    const int dst = (c & 3) * q.H + (c >> 2);
+    (set == 1 ? q.out[1] : q.out[0])[dst] = s;
+    (set == 1 ? q.out2[1] : q.out2[0])[dst] = s;
+}
+// Both in one launch behind the first time loop of the backward pass (blockIdx.y: the bias sets, then the heads).
+__global__ __launch_bounds__(256) void grads_final_kernel(BiasFinalArgs b, HeadsFinalArgs h) {
+    if ((int)blockIdx.y < b.sets) bias_final_block(b, blockIdx.x, blockIdx.y);
+    else if ((int)blockIdx.x * HF_COLS < h.H) heads_final_block(h, blockIdx.x, blockIdx.y - b.sets);
 }
 
 // ---------------------------------------------------------------- workspace
@@ -520,7 +536,6 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     typedef typename RecGeom<MODE>::E E;
     const int H = c.hidden, A = c.act_dim;
     const bool pairs = pairs_of_layers(c);   // two layers' time loops in one launch
-    if (!pairs) fill_words(ws.err, 1, 0, s);
 
     // 8 waves = row groups x shares of the contraction (TPW tiles of 16 gate rows per wave): a workgroup owns
     // 8 tiles (32 units) when 32 workgroups need all of H/32 units each, else 4 tiles (16 units)
@@ -557,6 +572,8 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             pa.job[n++] = PrepJob{w[4 * l + 2], w[4 * l + 3], L.bias, nullptr, PREP_BIAS, 0};
         }
         if (ws.x_op) pa.job[n++] = PrepJob{static_cast<const float*>(x), nullptr, ws.x_op, nullptr, PREP_ROWS, (unsigned)((size_t)M * c.input_dim / 4)};
+        // without a pair, also the time-out word and the flags of the first time loop (else: pipe_prepare_fwd)
+        if (!pairs) pa.job[n++] = PrepJob{nullptr, nullptr, ws.err, nullptr, PREP_CLEAR, (unsigned)(ws.flags + REC_FLAG_WORDS - ws.err)};
         hipLaunchKernelGGL(prep_weights_kernel<E>, dim3((max_cols + 63) / 64, 4 * H / 64, n), dim3(256), 0, s, pa, H);
     };
     // time-batched input projection: gates[M, 4H] = x W_ih^T + (b_ih + b_hh), interleaved columns
@@ -618,7 +635,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             VER_FWD_DISPATCH(lstm_pipe_fwd_kernel, pa);
             l += 2;
         } else {
-            fill_words(ws.flags, REC_FLAG_WORDS, 0, s);
+            if (l > 0) fill_words(ws.flags, REC_FLAG_WORDS, 0, s);
             RecFwdArgs ra = rec_args(l);
             ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
             VER_FWD_DISPATCH(lstm_rec_fwd_kernel, ra);
@@ -652,16 +669,19 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     // heads
     {
     ProfScope prof(VER_PROF_HEADS_BWD, s);
-    const RowsToConvert rows = {static_cast<const float*>(x), ws.x_op, ws.x_op ? (unsigned)((size_t)M * c.input_dim / 4) : 0u};
-    hipLaunchKernelGGL(heads_bwd_dh_kernel, dim3((H / 4 + 255) / 256, (M + HB_ROWS - 1) / HB_ROWS + std::min(1024u, (rows.quads + 1023) / 1024)), dim3(256), 0, s,
-                       d_u, d_v, M, H, A, w[4 * nl], w[4 * nl + 2], ws.dh[0], top_pair ? ws.flags : nullptr,
-                       top_pair ? (int)(ws.pipe + ws.pipe_words - ws.flags) : 0, rows);
     const int rb_h = (M + HW_ROWS - 1) / HW_ROWS;
-    hipLaunchKernelGGL(heads_wgrad_partial_kernel, dim3((H / 4 + 255) / 256, rb_h), dim3(256), 0, s, d_u, d_v, h_top, M, H,
-                       A, ws.part, ws.part_b);
-    hipLaunchKernelGGL(heads_wgrad_final_kernel, dim3((H + HF_COLS - 1) / HF_COLS, A + 1), dim3(256), 0, s, ws.part, ws.part_b, rb_h, H, A,
-                       gw[4 * nl], gw[4 * nl + 2], gw[4 * nl + 1], gw[4 * nl + 3]);
+    HeadsBwdArgs ha;
+    ha.d_u = d_u; ha.d_v = d_v; ha.W_a = w[4 * nl]; ha.w_v = w[4 * nl + 2]; ha.h = h_top;
+    ha.dh = ws.dh[0]; ha.part = ws.part; ha.part_b = ws.part_b;
+    ha.M = M; ha.H = H; ha.A = A;
+    ha.clear = ws.flags; ha.n_clear = top_pair ? (int)(ws.pipe + ws.pipe_words - ws.flags) : REC_FLAG_WORDS;
+    ha.rows = static_cast<const float*>(x); ha.rows_op = ws.x_op; ha.quads = ws.x_op ? (unsigned)((size_t)M * c.input_dim / 4) : 0;
+    const int gx = (H / 4 + 255) / 256;
+    ha.dh_blocks = (M + HB_ROWS - 1) / HB_ROWS;
+    ha.w_blocks = ((rb_h * (H / 64) + 3) / 4 + gx - 1) / gx;
+    hipLaunchKernelGGL(heads_bwd_kernel, dim3(gx, ha.dh_blocks + ha.w_blocks + std::min(1024u, (ha.quads + 1023) / 1024)), dim3(256), 0, s, ha);
     }
+    HeadsFinalArgs hf{ws.part, ws.part_b, gw[4 * nl], gw[4 * nl + 2], gw[4 * nl + 1], gw[4 * nl + 3], (M + HW_ROWS - 1) / HW_ROWS, H, A};
 
     // one wave per (16 units, share of the 4H contraction): 2 tiles x 4 when H/16 > 32 workgroups, else 1 x 8
     const bool wide = H / 16 > REC_MAX_GROUP;
@@ -734,20 +754,22 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         if (last && (MODE == MODE_F32 || !launch_tn_group(dw, s))) dw.launch(s);
         }
         // db_ih = db_hh = column sums of dz: the time loop left one partial sum per group (a pair: both layers' sums in
-        // one launch)
+        // one launch; the heads' gradients join the first)
         if (last) {
         ProfScope prof(VER_PROF_LSTM_DBIAS, s);
-        const size_t stride = (size_t)REC_GROUPS * 4 * H;
         float* const* g = gw + 4 * l;
-        hipLaunchKernelGGL(colsum_final_kernel, dim3((4 * H + 255) / 256, in_pair ? 2 : 1), dim3(256), 0, s, ws.db_part,
-                           in_pair ? PIPE_GROUPS : REC_GROUPS, 4 * H, H, g[2], g[3], stride, in_pair ? g[6] : nullptr, in_pair ? g[7] : nullptr);
+        const BiasFinalArgs bf{ws.db_part, (size_t)REC_GROUPS * 4 * H, {g[2], in_pair ? g[6] : nullptr}, {g[3], in_pair ? g[7] : nullptr},
+                               in_pair ? PIPE_GROUPS : REC_GROUPS, H, in_pair ? 2 : 1};
+        const bool heads = l + (in_pair ? 2 : 1) == nl;
+        hipLaunchKernelGGL(grads_final_kernel, dim3(std::max((4 * H + 255) / 256, (H + HF_COLS - 1) / HF_COLS), bf.sets + (heads ? A + 1 : 0)),
+                           dim3(256), 0, s, bf, hf);
         }
     };
 
     int cur = 0;  // ws.dh[cur] holds the gradient arriving at the current layer's h
     for (int l = nl - 1; l >= 0;) {
         if (pairs && l % 2 == 1) {
-            if (l != nl - 1) fill_words(ws.flags, (size_t)(ws.pipe + ws.pipe_words - ws.flags), 0, s);   // (the top pair's: heads_bwd_dh_kernel)
+            if (l != nl - 1) fill_words(ws.flags, (size_t)(ws.pipe + ws.pipe_words - ws.flags), 0, s);   // (the top layers': heads_bwd_kernel)
             PipeBwdArgs pa;
             pa.l1 = rec_args(l, ws.dh[cur]);
             pa.l0 = rec_args(l - 1, ws.dh[cur ^ 1], true);
@@ -765,7 +787,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             if (!ok) return VER_EHIP;
             l -= 2;
         } else {
-            fill_words(ws.flags, REC_FLAG_WORDS, 0, s);
+            if (l != nl - 1) fill_words(ws.flags, REC_FLAG_WORDS, 0, s);
             RecBwdArgs ra = rec_args(l, ws.dh[cur]);
             {
             ProfScope prof(VER_PROF_LSTM_REC_BWD, s);

@@ -207,6 +207,13 @@ def test_bf16_contractions(ver, rows, hidden, input_dim, layers, x_bf16):
                         p_done=0.05, minibatches=1), seed=rows, compute=1, x_bf16=x_bf16)
 
 
+@pytest.mark.parametrize("rows,hidden,act_dim", [(31, 64, 1), (32, 64, 15), (33, 128, 16), (65, 320, 47), (130, 64, 63)])
+def test_head_gradients(ver, rows, hidden, act_dim):
+    """Row blocks of the heads' weight gradients at their edges; head counts at the edges of the 16-row products."""
+    case(ver, wl.scaled(wl.WORKLOADS["manip"], budget=rows, n_envs=3, hidden=hidden, input_dim=8, act_dim=act_dim, n_layers=1, p_done=0.05,
+                        minibatches=1), seed=rows)
+
+
 def test_packing_order_invariance_on_device(ver):
     """Another random order of the same sequences (B = 1): identical weight gradients up to rounding."""
     w = wl.scaled(wl.WORKLOADS["manip"], budget=400, n_envs=10, hidden=64, input_dim=16, p_done=0.03,
