@@ -1,6 +1,6 @@
 // ver_ppo_loss: PPO clipped surrogate + value + entropy loss over the packed
 // rows of a minibatch, its six scalars and the gradient w.r.t. the heads'
-// outputs, in ONE kernel (plus a tiny counter reset).
+// outputs, in one kernel (plus a small one that adds the workgroups' sums).
 //
 // Paper: section 2.2 "Learning method" (PPO), appendix hyper-parameter table
 // (clip 0.2, value coefficient 0.5, no clipped value loss, no advantage
@@ -11,11 +11,11 @@
 //
 // One thread owns a row: the row's head outputs, action, old log-probability,
 // advantage and return are read once, its gradients written once (56 B/row
-// categorical-4, 156 B/row Gaussian-11: HBM bound); rows of up to 16 head
+// categorical-4, 156 B/row Gaussian-11: HBM bound); rows of up to 24 head
 // outputs travel through LDS so that memory sees whole contiguous blocks.
 // Sums are reduced wave -> workgroup -> per-workgroup partials in the
-// workspace; the workgroup that finishes last adds the partials in index
-// order, so the result does not depend on scheduling.
+// workspace, which a second launch adds in index order, so the result does
+// not depend on scheduling.
 #include "common.h"
 
 namespace ver {
@@ -32,121 +32,110 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;  // valid in lane 0
 }
 
-// Sum over the workgroup, valid in thread 0.  s_red has one slot per wave.
-__device__ __forceinline__ float block_sum(float v, float* s_red) {
-    v = wave_sum(v);
-    const int lane = threadIdx.x & (VER_WAVE - 1), wave = threadIdx.x / VER_WAVE;
-    __syncthreads();  // s_red may still be read from the previous call
-    if (lane == 0) s_red[wave] = v;
-    __syncthreads();
-    float t = 0.f;
-    if (threadIdx.x == 0)
-        for (int w = 0; w < LOSS_THREADS / VER_WAVE; ++w) t += s_red[w];
-    return t;
-}
-
-// What every loss kernel ends with: the workgroup's sums (acc: policy, value, entropy, kl, clipped count; s_lsacc:
-// per wave, the log-std gradient per dimension) go to the workgroup's slot of `partials`; the workgroup that
-// finishes last adds all slots in index order (a fixed order, whatever the schedule was) and writes the scalars.
-template <int DIST>
-__device__ __forceinline__ void loss_finish(const ver_ppo_cfg& cfg, int M, const float (&acc)[LOSS_SCALARS],
-                                            float (*s_lsacc)[64], float* __restrict__ scalars,
-                                            float* __restrict__ d_log_std, float* __restrict__ partials,
-                                            int* __restrict__ counter, const float* __restrict__ alpha,
-                                            float target_entropy, float alpha_sign, float* __restrict__ d_alpha,
-                                            float ent_coef) {
-    __shared__ float s_red[LOSS_THREADS / VER_WAVE];
-    __shared__ int s_last;
+// The sums over the workgroups' partials (width each), means, totals and alpha's gradient, by one workgroup of THREADS.
+struct LossOut {
+    float* scalars; float* d_log_std; float* d_alpha;
+    const float* alpha;
+    float target_entropy, alpha_sign;
+};
+template <int THREADS>
+__device__ __forceinline__ void loss_total(const ver_ppo_cfg& cfg, int M, int width, const float* __restrict__ partials, int G, const LossOut& out) {
+    __shared__ float s_slot[THREADS];
     __shared__ float s_out[LOSS_SCALARS];
-    __shared__ float s_slot[LOSS_THREADS];
-    const int A = cfg.act_dim;
-    const int width = LOSS_SCALARS + (DIST == 1 ? A : 0);  // partial sums per workgroup
-    const float inv_m = 1.f / (float)M;
-    float* my_partial = partials + (size_t)blockIdx.x * width;
-    for (int q = 0; q < LOSS_SCALARS; ++q) {
-        const float t = block_sum(acc[q], s_red);
-        if (threadIdx.x == 0) st_agent(&my_partial[q], t);
-    }
-    if (DIST == 1) {
-        __syncthreads();
-        if (threadIdx.x < A) {
-            float t = 0.f;
-            for (int w = 0; w < LOSS_THREADS / VER_WAVE; ++w) t += s_lsacc[w][threadIdx.x];
-            st_agent(&my_partial[LOSS_SCALARS + threadIdx.x], t);
-        }
-    }
-
-    // Last workgroup to arrive adds the partials in index order.  The partials are written through to memory with
-    // device-scope stores whose completion every thread awaits before the workgroup counts itself in, and are read
-    // with device-scope loads: no fence.  (A device-scope fence here writes back the whole L2 of the XCD, dirty
-    // with megabytes of gradient rows, once per workgroup: a fifth of the kernel's time on 2^24 rows.)
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0)
-        s_last = (__hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1);
-    __syncthreads();
-    if (!s_last) return;
-    // Column c of the partials is added by T / width threads ("slots"): slot k adds the workgroups k, k + slots, ...
+    // Column c of the partials is added by THREADS / width threads ("slots"): slot k adds the workgroups k, k + slots, ...
     // with 8 loads in flight, then one thread per column adds the slots in order: a fixed order, whatever the
-    // schedule was, and every thread of the workgroup has work (with one thread per column, 16 of 256 had).
-    {
-        const int G = gridDim.x, slots = LOSS_THREADS / width;   // width <= 69: at least 3 slots
-        const int c = threadIdx.x % width, slot = threadIdx.x / width;
-        if (slot < slots) {
-            float t = 0.f;
-            int g = slot;
-            for (; g + 7 * slots < G; g += 8 * slots) {
-                float x[8];
+    // schedule was.
+    const int slots = THREADS / width;   // width <= 69: at least 3 slots
+    const int c = threadIdx.x % width, slot = threadIdx.x / width;
+    if (slot < slots) {
+        float t = 0.f;
+        int g = slot;
+        for (; g + 7 * slots < G; g += 8 * slots) {
+            float x[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) x[k] = ld_agent(&partials[(size_t)(g + k * slots) * width + c]);
+            for (int k = 0; k < 8; ++k) x[k] = partials[(size_t)(g + k * slots) * width + c];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) t += x[k];
-            }
-            for (; g < G; g += slots) t += ld_agent(&partials[(size_t)g * width + c]);
-            s_slot[slot * width + c] = t;
+            for (int k = 0; k < 8; ++k) t += x[k];
         }
-        __syncthreads();
-        if (threadIdx.x < width) {
-            float t = 0.f;
-            for (int k = 0; k < slots; ++k) t += s_slot[k * width + threadIdx.x];
-            if (threadIdx.x < LOSS_SCALARS) s_out[threadIdx.x] = t * inv_m;  // means
-            else d_log_std[threadIdx.x - LOSS_SCALARS] = t;
-        }
+        for (; g < G; g += slots) t += partials[(size_t)g * width + c];
+        s_slot[slot * width + c] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < width) {
+        float t = 0.f;
+        for (int k = 0; k < slots; ++k) t += s_slot[k * width + threadIdx.x];
+        if (threadIdx.x < LOSS_SCALARS) s_out[threadIdx.x] = t * (1.f / (float)M);  // means
+        else out.d_log_std[threadIdx.x - LOSS_SCALARS] = t;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         const float pol = s_out[0], val = s_out[1], ent = s_out[2];
+        const float ent_coef = out.alpha ? out.alpha[0] : cfg.entropy_coef;
         float total = pol + cfg.value_coef * val - ent_coef * ent;
-        if (alpha) {
-            total += ent_coef * (target_entropy - ent);
-            d_alpha[0] = alpha_sign * (target_entropy - ent);
+        if (out.alpha) {
+            total += ent_coef * (out.target_entropy - ent);
+            out.d_alpha[0] = out.alpha_sign * (out.target_entropy - ent);
         }
-        scalars[0] = total;
-        scalars[1] = pol;
-        scalars[2] = val;
-        scalars[3] = ent;
-        scalars[4] = s_out[3];
-        scalars[5] = s_out[4];
-        *counter = 0;
+        out.scalars[0] = total;
+        out.scalars[1] = pol;
+        out.scalars[2] = val;
+        out.scalars[3] = ent;
+        out.scalars[4] = s_out[3];
+        out.scalars[5] = s_out[4];
+    }
+}
+// The launch behind a loss kernel of several workgroups.  (One launch instead of two, the workgroup that counts itself in last
+// adding the partials: the counter has to be cleared by a launch of its own, and 768 atomics on one address as all workgroups
+// end together take longer than this one.  us per call, one launch and the
+// clearing -> two launches: 300001 rows of 11 25.9 -> 17.4, 150001 20.1 -> 14, 1000000 39.4 -> 33.3, 390000 of 4 18.9 -> 13.)
+constexpr int LOSS_TOTAL_THREADS = 1024;
+__global__ __launch_bounds__(LOSS_TOTAL_THREADS) void loss_total_kernel(ver_ppo_cfg cfg, int M, int width, const float* __restrict__ partials, int G, LossOut out) {
+    loss_total<LOSS_TOTAL_THREADS>(cfg, M, width, partials, G, out);
+}
+
+// What every loss kernel ends with: the workgroup's sums (acc: policy, value, entropy, kl, clipped count; s_lsacc:
+// per wave, the log-std gradient per dimension) go to the workgroup's slot of `partials`; a workgroup on its own also
+// writes the scalars.
+template <int DIST>
+__device__ __forceinline__ void loss_finish(const ver_ppo_cfg& cfg, int M, const float (&acc)[LOSS_SCALARS], float (*s_lsacc)[64],
+                                            float* __restrict__ partials, const LossOut& out) {
+    __shared__ float s_red[LOSS_THREADS / VER_WAVE][LOSS_SCALARS];
+    const int A = cfg.act_dim, lane = threadIdx.x & (VER_WAVE - 1), wave = threadIdx.x / VER_WAVE;
+    const int width = LOSS_SCALARS + (DIST == 1 ? A : 0);  // partial sums per workgroup
+    float* my_partial = partials + (size_t)blockIdx.x * width;
+#pragma unroll
+    for (int q = 0; q < LOSS_SCALARS; ++q) {
+        const float t = wave_sum(acc[q]);
+        if (lane == 0) s_red[wave][q] = t;
+    }
+    __syncthreads();   // (also s_lsacc)
+    if (threadIdx.x < width) {
+        float t = 0.f;
+        for (int w = 0; w < LOSS_THREADS / VER_WAVE; ++w)
+            t += threadIdx.x < LOSS_SCALARS ? s_red[w][threadIdx.x] : s_lsacc[w][threadIdx.x - LOSS_SCALARS];
+        my_partial[threadIdx.x] = t;
+    }
+    if (gridDim.x == 1) {
+        __syncthreads();
+        loss_total<LOSS_THREADS>(cfg, M, width, partials, 1, out);
     }
 }
 
-constexpr int LOSS_STAGE_MAX_A = 16;   // widest row that is staged through LDS
+constexpr int LOSS_STAGE_MAX_A = 24;   // widest row that is staged through LDS: two times 24 KB, three workgroups per CU as launched
 
-// STAGED (1: word by word, 2: 16 bytes at a time for 16-byte aligned arrays): the workgroup's 256 rows of head outputs (and Gaussian actions) are contiguous in memory: they are
+// Rows that the fixed-width kernel below does not take (wider ones, arrays that are not 16-byte aligned).
+// STAGED: the workgroup's 256 rows of head outputs (and Gaussian actions) are contiguous in memory: they are
 // copied into LDS with consecutive lanes on consecutive words, every thread then works on its own row there
 // (row pitch A words), writes the row's gradient over the head outputs it has consumed, and the block is
 // copied out the same way.  Read row by row straight from memory, a wave instruction would touch 64 rows
 // A*4 bytes apart.
-template <int DIST, int STAGED>
+template <int DIST, bool STAGED>
 __global__ __launch_bounds__(LOSS_THREADS) void ppo_loss_kernel(
     ver_ppo_cfg cfg, int M, const float* __restrict__ u, const float* __restrict__ value,
     const float* __restrict__ log_std, const void* __restrict__ actions,
     const float* __restrict__ logp_old, const float* __restrict__ adv, const float* __restrict__ ret,
-    const float* __restrict__ is_weight, float* __restrict__ scalars, float* __restrict__ d_u,
-    float* __restrict__ d_value, float* __restrict__ d_log_std, float* __restrict__ partials,
-    int* __restrict__ counter, const float* __restrict__ alpha, float target_entropy, float alpha_sign,
-    float* __restrict__ d_alpha) {
+    const float* __restrict__ is_weight, float* __restrict__ d_u, float* __restrict__ d_value, float* __restrict__ partials,
+    LossOut out) {
     __shared__ float s_ls[64], s_inv_sigma[64];
     __shared__ float s_lsacc[LOSS_THREADS / VER_WAVE][64];   // per wave: running sums of the log-std gradient
     // staged rows: [256][A] head outputs, then (Gaussian) [256][A] actions; sized by the launch
@@ -157,7 +146,7 @@ __global__ __launch_bounds__(LOSS_THREADS) void ppo_loss_kernel(
     const float inv_m = 1.f / (float)M;
     const int lane = threadIdx.x & (VER_WAVE - 1), wave = threadIdx.x / VER_WAVE;
     // entropy coefficient: the fixed one, or the current value of the learned one (a constant for the policy)
-    const float ent_coef = alpha ? alpha[0] : cfg.entropy_coef;
+    const float ent_coef = out.alpha ? out.alpha[0] : cfg.entropy_coef;
     if (DIST == 1) {
         if (threadIdx.x < A) {
             s_ls[threadIdx.x] = log_std[threadIdx.x];
@@ -182,12 +171,7 @@ __global__ __launch_bounds__(LOSS_THREADS) void ppo_loss_kernel(
             if (round > 0) bar_lds();   // the previous block has been copied out
             const float* gu = u + (size_t)p0 * A;
             const float* ga = static_cast<const float*>(actions) + (size_t)p0 * A;
-            const int vec_words = STAGED == 2 ? words & ~3 : 0;
-            for (int i = threadIdx.x * 4; i < vec_words; i += LOSS_THREADS * 4) {
-                *reinterpret_cast<float4*>(s_u + i) = *reinterpret_cast<const float4*>(gu + i);
-                if (DIST == 1) *reinterpret_cast<float4*>(s_a + i) = *reinterpret_cast<const float4*>(ga + i);
-            }
-            for (int i = vec_words + threadIdx.x; i < words; i += LOSS_THREADS) {
+            for (int i = threadIdx.x; i < words; i += LOSS_THREADS) {
                 s_u[i] = gu[i];
                 if (DIST == 1) s_a[i] = ga[i];
             }
@@ -285,10 +269,7 @@ __global__ __launch_bounds__(LOSS_THREADS) void ppo_loss_kernel(
         if (STAGED) {
             bar_lds();
             float* gd = d_u + (size_t)p0 * A;
-            const int vec_words = STAGED == 2 ? words & ~3 : 0;
-            for (int i = threadIdx.x * 4; i < vec_words; i += LOSS_THREADS * 4)
-                *reinterpret_cast<float4*>(gd + i) = *reinterpret_cast<const float4*>(s_u + i);
-            for (int i = vec_words + threadIdx.x; i < words; i += LOSS_THREADS) gd[i] = s_u[i];
+            for (int i = threadIdx.x; i < words; i += LOSS_THREADS) gd[i] = s_u[i];
         }
     }
     if (DIST == 1 && STAGED) {
@@ -300,7 +281,7 @@ __global__ __launch_bounds__(LOSS_THREADS) void ppo_loss_kernel(
             }
         }
     }
-    loss_finish<DIST>(cfg, M, acc, s_lsacc, scalars, d_log_std, partials, counter, alpha, target_entropy, alpha_sign, d_alpha, ent_coef);
+    loss_finish<DIST>(cfg, M, acc, s_lsacc, partials, out);
 }
 
 // Lanes of one wave hand data to each other through LDS without a barrier (the hardware executes a wave's LDS
@@ -311,22 +292,22 @@ __device__ __forceinline__ void wave_lds_fence() {
     asm volatile("" ::: "memory");
 }
 
-// The same loss for rows of a width A known at compile time (1..16; 16-byte aligned arrays, M * A a multiple of 4):
+// The same loss for rows of a width A known at compile time (1..24; 16-byte aligned arrays):
 // loops over the action dimensions unroll (232 vector instructions per 64 rows instead of ~800 and a dozen
 // branches), a row lives in registers between its LDS read and its LDS write, log-std terms are per-kernel
 // constants.  A wave's 64 rows are contiguous in memory: it copies them into its own part of LDS with consecutive
 // lanes on consecutive 16-byte chunks, every lane works on its own row, the gradient goes back through the same LDS
-// words and out as chunks.  LDS instructions of one wave execute in order, so the loop has no barrier and the
-// waves of a workgroup drift apart freely.
+// words and out as chunks (the up to three words beyond the last whole chunk of the buffer one by one, in the wave that has
+// them).  LDS instructions of one wave execute in order, so the loop has no barrier and the waves of a workgroup drift
+// apart freely.  us per call, the general kernel -> this one: 1000003 rows of 11 (Gaussian)
+// 46.5 -> 41.4 (cold arrays), 700001 of 18 (categorical) 209 -> 33.
 template <int DIST, int A>
 __global__ __launch_bounds__(LOSS_THREADS) void ppo_loss_fixed_kernel(
     ver_ppo_cfg cfg, int M, const float* __restrict__ u, const float* __restrict__ value,
     const float* __restrict__ log_std, const void* __restrict__ actions,
     const float* __restrict__ logp_old, const float* __restrict__ adv, const float* __restrict__ ret,
-    const float* __restrict__ is_weight, float* __restrict__ scalars, float* __restrict__ d_u,
-    float* __restrict__ d_value, float* __restrict__ d_log_std, float* __restrict__ partials,
-    int* __restrict__ counter, const float* __restrict__ alpha, float target_entropy, float alpha_sign,
-    float* __restrict__ d_alpha) {
+    const float* __restrict__ is_weight, float* __restrict__ d_u, float* __restrict__ d_value, float* __restrict__ partials,
+    LossOut out) {
     static_assert(A >= 1 && A <= LOSS_STAGE_MAX_A, "row width");
     constexpr int WWORDS = VER_WAVE * A;                       // words of a wave's 64 rows
     constexpr int NCH = (WWORDS / 4 + VER_WAVE - 1) / VER_WAVE; // 16-byte chunks per lane
@@ -336,9 +317,9 @@ __global__ __launch_bounds__(LOSS_THREADS) void ppo_loss_fixed_kernel(
     __shared__ __attribute__((aligned(16))) float s_a[DIST == 1 ? LOSS_THREADS * A : 4];
     const float inv_m = 1.f / (float)M;
     const int lane = threadIdx.x & (VER_WAVE - 1), wave = threadIdx.x / VER_WAVE;
-    const float ent_coef = alpha ? alpha[0] : cfg.entropy_coef;
+    const float ent_coef = out.alpha ? out.alpha[0] : cfg.entropy_coef;
     float inv_sigma[A], ls_own[A];
-    float ls_sum = 0.f;
+    double ls_sum = 0.0;
 #pragma unroll
     for (int d = 0; d < A; ++d) {
         ls_own[d] = 0.f;
@@ -349,20 +330,25 @@ __global__ __launch_bounds__(LOSS_THREADS) void ppo_loss_fixed_kernel(
             ls_sum += ls;
         }
     }
-    const float gauss_ent = ls_sum + (float)A * (0.5f + HALF_LOG_2PI);   // the same for every row
+    const float gauss_ent = (float)ls_sum + (float)A * (0.5f + HALF_LOG_2PI);   // the same for every row
+    // what every row's log-probability has in common, in two parts: rounded to one, its error would be the same in all rows and
+    // stay in their mean (approximate KL), the more so the wider the rows
+    const double log_norm = ls_sum + (double)A * (double)HALF_LOG_2PI;
+    const float norm_hi = (float)log_norm, norm_lo = (float)(log_norm - (double)norm_hi);
     float acc[LOSS_SCALARS] = {0.f, 0.f, 0.f, 0.f, 0.f};
     const int stride = gridDim.x * LOSS_THREADS;
     const int rounds = (M + stride - 1) / stride;
     float* su = s_u + wave * WWORDS;
     float* sa = s_a + (DIST == 1 ? wave * WWORDS : 0);
 
-    static_assert(NCH <= 4, "chunks per lane");
+    static_assert(NCH <= 6, "chunks per lane");
     for (int round = 0; round < rounds; ++round) {
         const int p0 = round * stride + (int)blockIdx.x * LOSS_THREADS + wave * VER_WAVE;   // the wave's first row
         const int p = p0 + lane;
         const bool live = p < M;
         const int rows = max(0, min(VER_WAVE, M - p0));
-        const int vec_words = rows * A;   // a multiple of 4: the host only launches this kernel when M * A is
+        // whole chunks, and what follows them in the wave that holds the buffer's last rows (a whole wave's 64 rows are whole chunks)
+        const int vec_words = (rows * A) & ~3, tail = (rows * A) & 3;
         // Every load of the round is issued up front and unconditionally (rows and chunks beyond the buffer's end
         // re-read valid words that are never used): with loads under conditions the compiler cannot count what is
         // in flight and waits for everything at once.  (Fetching a round or two ahead into spare registers was
@@ -373,7 +359,7 @@ __global__ __launch_bounds__(LOSS_THREADS) void ppo_loss_fixed_kernel(
         const float w = is_weight ? is_weight[pl] : 1.f;
         const float lp_old = logp_old[pl], adv_p = adv[pl], val_p = value[pl], ret_p = ret[pl];
         {
-            const size_t row0 = vec_words > 0 ? (size_t)p0 * A : 0;   // a wave without rows re-reads the start of the buffer
+            const size_t row0 = vec_words > 0 ? (size_t)p0 * A : 0;   // a wave without a whole chunk re-reads the start of the buffer
             const int last = vec_words > 0 ? vec_words - 4 : 0;       // last whole chunk of the wave's rows (M * A >= 4)
             const float* gu = u + row0;
             const float* ga = static_cast<const float*>(actions) + row0;
@@ -391,6 +377,11 @@ __global__ __launch_bounds__(LOSS_THREADS) void ppo_loss_fixed_kernel(
                     *reinterpret_cast<float4*>(su + i) = cu[k];
                     if (DIST == 1) *reinterpret_cast<float4*>(sa + i) = ca[k];
                 }
+            }
+            if (lane < tail) {
+                const size_t at = (size_t)p0 * A + vec_words + lane;
+                su[vec_words + lane] = u[at];
+                if (DIST == 1) sa[vec_words + lane] = static_cast<const float*>(actions)[at];
             }
         }
         wave_lds_fence();   // the row below was written by other lanes
@@ -457,7 +448,7 @@ __global__ __launch_bounds__(LOSS_THREADS) void ppo_loss_fixed_kernel(
                     zed[d] = diff[d] * inv_sigma[d];
                     logp += -0.5f * zed[d] * zed[d];
                 }
-                logp -= ls_sum + (float)A * HALF_LOG_2PI;
+                logp = (logp - norm_hi) - norm_lo;
                 ent = gauss_ent;
                 const float rho = expf(logp - lp_old);
                 const float s1 = rho * adv_p;
@@ -494,6 +485,7 @@ __global__ __launch_bounds__(LOSS_THREADS) void ppo_loss_fixed_kernel(
             const int i = (lane + k * VER_WAVE) * 4;
             if (i < vec_words) *reinterpret_cast<float4*>(gd + i) = *reinterpret_cast<const float4*>(su + i);
         }
+        if (lane < tail) gd[vec_words + lane] = su[vec_words + lane];
         wave_lds_fence();   // the next round overwrites what other lanes have just read
     }
     if (DIST == 1) {
@@ -503,7 +495,7 @@ __global__ __launch_bounds__(LOSS_THREADS) void ppo_loss_fixed_kernel(
             if (lane == 0) s_lsacc[wave][d] = t;
         }
     }
-    loss_finish<DIST>(cfg, M, acc, s_lsacc, scalars, d_log_std, partials, counter, alpha, target_entropy, alpha_sign, d_alpha, ent_coef);
+    loss_finish<DIST>(cfg, M, acc, s_lsacc, partials, out);
 }
 
 inline int loss_blocks(int M) {
@@ -535,28 +527,26 @@ int ppo_loss_launch(const ver_ppo_cfg* cfg, int32_t M, const float* head_out, co
     if (!workspace || workspace_bytes < ver_ppo_loss_workspace_bytes(M, cfg->act_dim)) return VER_EWORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     Carver cv(workspace);
-    int* counter = cv.take<int>(64);
+    (void)cv.take<int>(64);
     float* partials = cv.take<float>((size_t)loss_blocks(M) * (LOSS_SCALARS + cfg->act_dim));
-    fill_words(counter, 1, 0, s);
     const int blocks = loss_blocks(M);
+    const LossOut out{scalars, d_log_std, d_alpha, alpha, target_entropy, alpha_sign};
     ProfScope prof(VER_PROF_LOSS, s);
-    // 0: rows read from memory one by one; 1: staged through LDS; 2: staged with 16-byte accesses
-    int staged = cfg->act_dim <= LOSS_STAGE_MAX_A ? 1 : 0;
+    const bool staged = cfg->act_dim <= LOSS_STAGE_MAX_A;
     const uintptr_t bits = reinterpret_cast<uintptr_t>(head_out) | reinterpret_cast<uintptr_t>(d_head_out) |
                            (cfg->dist == 1 ? reinterpret_cast<uintptr_t>(actions_packed) : 0);
-    if (staged && (bits & 15) == 0) staged = 2;
-    // the fixed-width kernel moves whole 16-byte chunks only
-    const bool fixed_width = staged == 2 && ((long long)M * cfg->act_dim) % 4 == 0;
+    // the fixed-width kernel moves 16-byte chunks (and reads one even where the buffer is shorter)
+    const bool fixed_width = staged && (bits & 15) == 0 && (long long)M * cfg->act_dim >= 4;
     const size_t lds = staged ? (size_t)LOSS_THREADS * cfg->act_dim * 4 * (cfg->dist == 1 ? 2 : 1) : 0;
 #define VER_LOSS_LAUNCH(DIST, STAGED)                                                                                  \
     hipLaunchKernelGGL((ppo_loss_kernel<DIST, STAGED>), dim3(blocks), dim3(LOSS_THREADS), lds, s, *cfg, M, head_out,    \
-                       value, log_std, actions_packed, logp_old, adv, ret, is_weight, scalars, d_head_out, d_value,    \
-                       d_log_std, partials, counter, alpha, target_entropy, alpha_sign, d_alpha)
+                       value, log_std, actions_packed, logp_old, adv, ret, is_weight, d_head_out, d_value,             \
+                       partials, out)
 #define VER_LOSS_FIXED(DIST, A_)                                                                                        \
     case A_:                                                                                                            \
         hipLaunchKernelGGL((ppo_loss_fixed_kernel<DIST, A_>), dim3(blocks), dim3(LOSS_THREADS), 0, s, *cfg, M, head_out, \
-                           value, log_std, actions_packed, logp_old, adv, ret, is_weight, scalars, d_head_out, d_value, \
-                           d_log_std, partials, counter, alpha, target_entropy, alpha_sign, d_alpha);                   \
+                           value, log_std, actions_packed, logp_old, adv, ret, is_weight, d_head_out, d_value,          \
+                           partials, out);                                                                              \
         break;
 #define VER_LOSS_FIXED_ALL(DIST)                                                                                        \
     switch (cfg->act_dim) {                                                                                             \
@@ -564,13 +554,18 @@ int ppo_loss_launch(const ver_ppo_cfg* cfg, int32_t M, const float* head_out, co
         VER_LOSS_FIXED(DIST, 5) VER_LOSS_FIXED(DIST, 6) VER_LOSS_FIXED(DIST, 7) VER_LOSS_FIXED(DIST, 8)                  \
         VER_LOSS_FIXED(DIST, 9) VER_LOSS_FIXED(DIST, 10) VER_LOSS_FIXED(DIST, 11) VER_LOSS_FIXED(DIST, 12)               \
         VER_LOSS_FIXED(DIST, 13) VER_LOSS_FIXED(DIST, 14) VER_LOSS_FIXED(DIST, 15) VER_LOSS_FIXED(DIST, 16)              \
+        VER_LOSS_FIXED(DIST, 17) VER_LOSS_FIXED(DIST, 18) VER_LOSS_FIXED(DIST, 19) VER_LOSS_FIXED(DIST, 20)              \
+        VER_LOSS_FIXED(DIST, 21) VER_LOSS_FIXED(DIST, 22) VER_LOSS_FIXED(DIST, 23) VER_LOSS_FIXED(DIST, 24)              \
         default: return VER_EUNSUPPORTED;                                                                               \
     }
     if (cfg->dist == 0) {
-        if (fixed_width) VER_LOSS_FIXED_ALL(0) else if (staged == 2) VER_LOSS_LAUNCH(0, 2); else if (staged) VER_LOSS_LAUNCH(0, 1); else VER_LOSS_LAUNCH(0, 0);
+        if (fixed_width) VER_LOSS_FIXED_ALL(0) else if (staged) VER_LOSS_LAUNCH(0, true); else VER_LOSS_LAUNCH(0, false);
     } else {
-        if (fixed_width) VER_LOSS_FIXED_ALL(1) else if (staged == 2) VER_LOSS_LAUNCH(1, 2); else if (staged) VER_LOSS_LAUNCH(1, 1); else VER_LOSS_LAUNCH(1, 0);
+        if (fixed_width) VER_LOSS_FIXED_ALL(1) else if (staged) VER_LOSS_LAUNCH(1, true); else VER_LOSS_LAUNCH(1, false);
     }
+    if (blocks > 1)
+        hipLaunchKernelGGL(loss_total_kernel, dim3(1), dim3(LOSS_TOTAL_THREADS), 0, s, *cfg, M, LOSS_SCALARS + (cfg->dist == 1 ? cfg->act_dim : 0),
+                           partials, blocks, out);
 #undef VER_LOSS_FIXED_ALL
 #undef VER_LOSS_FIXED
 #undef VER_LOSS_LAUNCH

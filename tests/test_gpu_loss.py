@@ -81,6 +81,14 @@ def test_against_oracle(ver, dist, A, M):
     check(ver, dist, make(rng, dist, M, A))
 
 
+@pytest.mark.parametrize("dist,A,M", [(0, 1, 3), (0, 1, 5), (1, 3, 3), (0, 5, 63), (1, 11, 65), (1, 7, 191), (0, 13, 255), (1, 11, 257), (0, 3, 1021),
+                                      (1, 13, 2050), (1, 16, 129), (0, 15, 193), (0, 17, 67), (1, 18, 301), (0, 24, 130), (1, 24, 63), (0, 25, 70), (1, 31, 300)])
+def test_rows_beyond_whole_chunks(ver, dist, A, M):
+    """One to three words of the rows beyond the last whole 16-byte chunk, in the first wave or a later one, in a first or a
+    second workgroup; buffers shorter than a chunk."""
+    check(ver, dist, make(np.random.default_rng(M + A), dist, M, A))
+
+
 @pytest.mark.parametrize("dist,A", [(0, 4), (1, 11)])
 def test_row_weights(ver, dist, A):
     rng = np.random.default_rng(3)
