@@ -17,6 +17,7 @@ if not os.path.exists(LIB_PATH):
     raise ImportError(f"{LIB_PATH} is missing: run `python -m paper_2210_05064_amd.build` "
                       "(or __graft_entry__.build()) first; there is no CPU fallback")
 lib = C.CDLL(LIB_PATH)
+from . import _marshal  # noqa: E402  (built with the library; after torch, whose symbols it uses)
 
 VER_OK = 0
 _vp, _i32, _sz, _f = C.c_void_p, C.c_int32, C.c_size_t, C.c_float
@@ -124,15 +125,20 @@ def _check(status: int) -> None:
         raise VerError(status)
 
 
-def _ptr(t) -> int | None:
+def _ptr_any(t) -> int | None:
+    """What _marshal does for a tensor, for any object (and the place its errors come from)."""
     if t is None:
         return None
     assert t.is_cuda and t.is_contiguous(), "device, contiguous tensors only"
     return t.data_ptr()
 
 
+_marshal.init(_ptr_any)
+_ptr = _marshal.ptr
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ws(ws):
@@ -180,9 +186,8 @@ def ver_ingest_gather(order, S, src, dst):
 def ver_ingest_gather_batch(order, S, pairs):
     """dst[k] = src[order[k]] for every (src, dst) pair of contiguous tensors, in one launch."""
     n = len(pairs)
-    srcs = (C.c_void_p * n)(*[_ptr(a) for a, _ in pairs])
-    dsts = (C.c_void_p * n)(*[_ptr(b) for _, b in pairs])
-    rows = (C.c_int32 * n)(*[a.element_size() * (a[0].numel() if S > 0 else 1) for a, _ in pairs])
+    srcs, dsts = _ptr_array([a for a, _ in pairs]), _ptr_array([b for _, b in pairs])
+    rows = (C.c_int32 * n)(*[a.element_size() * (a.numel() // a.shape[0] if S > 0 else 1) for a, _ in pairs])
     _check(lib.ver_ingest_gather_batch(_ptr(order), S, n, srcs, rows, dsts, _stream()))
 
 
@@ -197,10 +202,10 @@ def ver_pack_workspace_bytes(N: int, S: int, B: int) -> int:
 def pack_args(**kw) -> PackArgs:
     """ver_pack_args from keyword arguments (its fields; tensors or ints)."""
     a = PackArgs()
-    names = {f[0] for f in PackArgs._fields_}
-    for k, v in kw.items():
-        if k not in names:
+    for k in _marshal.pointers(a, _PACK_POINTERS, kw):   # what is not a tensor for a pointer field
+        if k not in _PACK_NAMES:
             raise TypeError(f"unknown ver_pack_args field {k}")
+        v = kw[k]
         if k == "workspace":
             a.workspace, a.workspace_bytes = _ws(v)
         elif isinstance(v, torch.Tensor):
@@ -208,6 +213,10 @@ def pack_args(**kw) -> PackArgs:
         elif v is not None:
             setattr(a, k, v)
     return a
+
+
+_PACK_NAMES = frozenset(f[0] for f in PackArgs._fields_)
+_PACK_POINTERS = {f[0]: getattr(PackArgs, f[0]).offset for f in PackArgs._fields_ if f[1] is _vp and f[0] != "workspace"}
 
 
 def ver_pack_minibatch(**kw):
@@ -224,8 +233,7 @@ def ver_pack_index_batch(arg_blocks):
 
 def _ptr_array(tensors):
     arr = (_vp * len(tensors))()
-    for i, t in enumerate(tensors):
-        arr[i] = _ptr(t)
+    _marshal.fill(arr, tensors)
     return arr
 
 

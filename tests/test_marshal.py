@@ -1,0 +1,55 @@
+"""Addresses of tensors for the C entry points (csrc/marshal.cpp): the Python rule holds for whatever is not plainly a device
+tensor, errors included.  CPU only (device tensors go through it in every GPU test)."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2210_05064_amd import binding as ver
+
+
+class Like:
+    def __init__(self, p, cuda=True, contiguous=True):
+        self.p, self.is_cuda, self.c = p, cuda, contiguous
+
+    def is_contiguous(self):
+        return self.c
+
+    def data_ptr(self):
+        return self.p
+
+
+class Sub(torch.Tensor):
+    is_cuda = True
+
+    def data_ptr(self):
+        return 2 ** 63 + 5
+
+
+@pytest.mark.parametrize("take", [ver._ptr, lambda t: ver._ptr_array([t])[0], lambda t: ver.pack_args(obs=t).obs])
+def test_addresses(take):
+    assert take(None) is None
+    assert take(Sub()) == 2 ** 63 + 5
+    for bad in (torch.zeros(4), torch.zeros(4, 4).t()):
+        with pytest.raises(AssertionError, match="device, contiguous tensors only"):
+            take(bad)
+
+
+def test_look_alikes_and_other_objects():
+    assert ver._ptr(Like(77)) == 77
+    assert list(ver._ptr_array((Like(1), None, Like(2 ** 64 - 1)))) == [1, None, 2 ** 64 - 1]
+    for bad in (Like(1, cuda=False), Like(1, contiguous=False)):
+        with pytest.raises(AssertionError):
+            ver._ptr(bad)
+    with pytest.raises(AttributeError):
+        ver._ptr(3)
+
+
+def test_pack_args_fields():
+    a = ver.pack_args(N=3, S=7, obs=None, h0=Sub(), D=4, workspace=None)
+    assert (a.N, a.S, a.D, a.obs, a.h0, a.workspace, a.workspace_bytes) == (3, 7, 4, None, 2 ** 63 + 5, None, 0)
+    assert ver.pack_args(obs=1234).obs == 1234
+    with pytest.raises(TypeError, match="unknown ver_pack_args field nonsense"):
+        ver.pack_args(N=1, nonsense=Sub())
+    with pytest.raises(ValueError):
+        ver._marshal.fill((C.c_void_p * 1)(), [None, None])
