@@ -31,7 +31,7 @@ constexpr int GAE_ITEMS = 8;
 constexpr int GAE_TILE = GAE_THREADS * GAE_ITEMS;
 constexpr long long GAE_SPIN_LIMIT = 1LL << 24;  // polls before a wait gives up
 constexpr int GAE_MAX_BATCH = 64;      // tiles per ticket at most (measured on 65536 tiles: 16 -> 0.516 ms, 32 -> 0.506, 64 -> 0.499)
-constexpr int GAE_BATCH_FROM = 1024;   // one more tile per ticket for every so many tiles
+constexpr int GAE_RESIDENT = 1024;     // workgroups that the chip holds at a time (four per CU)
 
 // A map's offset b is kept in fp64 everywhere: advantages are sums of TD errors that cancel heavily (with
 // lambda = 1 they telescope to a discounted reward sum minus a value), so an fp32 sum of a thousand terms of size 1
@@ -127,7 +127,14 @@ __global__ __launch_bounds__(GAE_THREADS) void gae_kernel(
 
     const int tid = threadIdx.x;
     const int lane = tid & (VER_WAVE - 1), wave = tid / VER_WAVE;
-    if (tid == 0) s_ticket = atomicAdd(ws.ticket, 1);
+    if (tid == 0) {
+        if (ntiles == 1) {   // alone: nothing to take turns with, and no launch has cleared the words
+            s_ticket = 0;
+            *ws.error = 0;
+        } else {
+            s_ticket = atomicAdd(ws.ticket, 1);
+        }
+    }
     *reinterpret_cast<unsigned long long*>(s_last + tid * 8) = 0ull;   // (every reader clears what it has read)
     if (tid == 0) *reinterpret_cast<unsigned long long*>(s_last + GAE_TILE) = 0ull;
     __syncthreads();
@@ -377,9 +384,14 @@ __global__ __launch_bounds__(GAE_THREADS) void gae_kernel(
 }
 
 inline int gae_tiles(int S) { return (S + GAE_TILE - 1) / GAE_TILE; }
+// Tiles per ticket: as many as let all workgroups run at once (with one fewer, a handful of workgroups started when the others
+// were done and the scan took twice their time), three at least, since every batch reads one tile twice.  us per scan with the
+// former floor(tiles / 1024) -> now: 1075 tiles 31.7 -> 22.7, 1465 40.3 -> 25.0, 2198 44.1 -> 31.6, 2930 50.8 -> 41.6, 4395 67.8 ->
+// 53.1, 6554 87.9 -> 70.0 (fill of the words included).  733 tiles one by one 20.6, in threes 19.8: not worth a second rule.
 inline int gae_batch(int tiles) {
-    const int b = tiles / GAE_BATCH_FROM;
-    return b < 1 ? 1 : (b > GAE_MAX_BATCH ? GAE_MAX_BATCH : b);
+    if (tiles <= GAE_RESIDENT) return 1;
+    const int b = (tiles + GAE_RESIDENT - 1) / GAE_RESIDENT;
+    return b < 3 ? 3 : (b > GAE_MAX_BATCH ? GAE_MAX_BATCH : b);
 }
 
 }  // namespace
@@ -406,14 +418,13 @@ int gae_launch(const float* rewards, const float* values, const uint8_t* dones, 
     ws.inc = cv.take<unsigned long long>(tiles);
     ws.agg_a = cv.take<unsigned long long>(tiles);
     ws.agg_b = cv.take<unsigned long long>(tiles);
-    // ticket, error and every published word must start at zero (the blocks are adjacent)
-    fill_words(reinterpret_cast<int32_t*>(head), cv.used / 4, 0, s);
+    // ticket, error and every published word must start at zero (the blocks are adjacent); a single tile needs the error word only
+    if (tiles > 1) fill_words(reinterpret_cast<int32_t*>(head), cv.used / 4, 0, s);
     ProfScope prof(VER_PROF_GAE, s);
     // 16-byte accesses need 16-byte aligned arrays (tiles start at multiples of the tile size)
     const uintptr_t bits = reinterpret_cast<uintptr_t>(rewards) | reinterpret_cast<uintptr_t>(values) |
                            reinterpret_cast<uintptr_t>(adv) | reinterpret_cast<uintptr_t>(ret) |
                            (reinterpret_cast<uintptr_t>(dones) << 2);
-    // tiles per ticket: 1 while tickets are few, up to GAE_MAX_BATCH for buffers of many thousands of tiles
     const int batch = gae_batch(tiles), groups = (tiles + batch - 1) / batch;
     if ((bits & 15) == 0)
         hipLaunchKernelGGL(gae_kernel<true>, dim3(groups), dim3(GAE_THREADS), 0, s, rewards, values, dones,
