@@ -57,10 +57,15 @@ struct PlanCost {
     float step, piece, tile;
     int chunk_rows, dense;   // rows per chunk that groups of more than 16 pieces aim at from `dense` alive pieces per timestep on
                              // (average over the launch), where the workers set the pace; 0: never
+    int few;                 // timesteps per chunk of groups of up to 16 pieces
 };
 // Timesteps per chunk by the pieces of the group: a chunk is handed on when it is complete, so the consumer starts and
 // ends that much later than the producer; it costs a worker about 4 us beside the product of its rows.
-constexpr int PLAN_CT_FEW = 8, PLAN_CT_MANY = 2;   // up to 16, more pieces
+// Up to 16 pieces: 8, or 4 where the workers keep up with that: bf16 with three or more teams of workers (work_deal) or the long
+// timesteps of the widths above 512.  us per forward and backward pass, 8 -> 4 timesteps, 200 rows in few pieces: 64 units 260 -> 250, 320
+// 280 -> 271, 1024 389 -> 385; 800 rows in 12: 1024 449 -> 432; 3000 rows in 46: 192 421 -> 406; but 512 486 -> 500, and fp32 2 x 512 on
+// 1024 rows 1062 -> 1099.
+constexpr int PLAN_CT_FEW = 8, PLAN_CT_FEW_FAST = 4, PLAN_CT_MANY = 2;   // up to 16 pieces, more pieces
 // fp32 forward from 384 units on, where only two teams of workers hold the weights and a tile costs them 1.8 to 2.5 us:
 // with 48 alive pieces per timestep or more the workers are behind and long chunks pay, with fewer the delay costs more.  us per timestep with 32 equally long pieces per group (96 alive), chunks of 2
 // timesteps -> of 256 rows: H = 384 9.0 -> 7.0, 512 10.7 -> 8.5; us per launch: 512 units, 32768 rows in 256 pieces (64
@@ -77,10 +82,12 @@ constexpr int PLAN_CT_FEW = 8, PLAN_CT_MANY = 2;   // up to 16, more pieces
 // (timesteps with up to 16 pieces run in the form of lstm_few.h).  The constants were fitted by hand to such a table when
 // single timesteps took 0.1 to 0.3 us longer; the cuts between the groups depend on the ratios only.
 inline PlanCost plan_cost(int mode, bool wide, bool fwd, int G) {
+    const int teams = 2 * REC_MAX_GROUP / G;
     if (mode == MODE_F32)
-        return fwd ? PlanCost{1.45f, 0.19f, 1.f, 2 * REC_MAX_GROUP / G < 3 ? 256 : 0, 48} : PlanCost{1.6f, 0.27f, 0.f, 0, 0};
-    if (wide) return fwd ? PlanCost{1.38f, 0.042f, 2.4f, 0, 0} : PlanCost{1.75f, 0.08f, 4.6f, 0, 0};
-    return fwd ? PlanCost{1.17f, 0.023f, 1.2f, G == REC_MAX_GROUP ? 192 : 0, 90} : PlanCost{1.38f, 0.04f, 1.7f, 0, 0};
+        return fwd ? PlanCost{1.45f, 0.19f, 1.f, teams < 3 ? 256 : 0, 48, PLAN_CT_FEW} : PlanCost{1.6f, 0.27f, 0.f, 0, 0, PLAN_CT_FEW};
+    if (wide) return fwd ? PlanCost{1.38f, 0.042f, 2.4f, 0, 0, PLAN_CT_FEW_FAST} : PlanCost{1.75f, 0.08f, 4.6f, 0, 0, PLAN_CT_FEW_FAST};
+    const int few = teams < 3 ? PLAN_CT_FEW : PLAN_CT_FEW_FAST;
+    return fwd ? PlanCost{1.17f, 0.023f, 1.2f, G == REC_MAX_GROUP ? 192 : 0, 90, few} : PlanCost{1.38f, 0.04f, 1.7f, 0, 0, few};
 }
 
 struct PipeWork {
@@ -221,7 +228,7 @@ __device__ __forceinline__ void plan_body(const int32_t* __restrict__ batch_size
         plan[PLAN_T + g] = cap > 0 ? (int)len[lo] : 0;
         const PlanCost& p = d == 0 ? pc_fwd : pc_bwd;
         const int aim = M >= p.dense * T ? p.chunk_rows : 0;
-        plan[PLAN_CT + g] = cap <= 16 ? PLAN_CT_FEW : min(max(aim / cap, PLAN_CT_MANY), PLAN_CT_FEW);
+        plan[PLAN_CT + g] = cap <= 16 ? p.few : min(max(aim / cap, PLAN_CT_MANY), PLAN_CT_FEW);
     }
 }
 
