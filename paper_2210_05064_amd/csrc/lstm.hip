@@ -34,7 +34,9 @@ __device__ __forceinline__ void st4(bf16_t* p, float a, float b, float c, float 
 // A thread moves 4 adjacent elements at a time (16-byte loads, 8- or 16-byte stores; cols is a multiple of 4):
 // 16 lanes cover a tile row in either direction.
 // All matrices and bias vectors of a call in one launch (blockIdx.z: the job; a launch per matrix took ~10 us each,
-// most of it ramp and tail).
+// most of it ramp and tail).  Workgroups of 1024 threads, a tile per 256, so that the plan of the two-layer launches
+// (lstm_pipe.h) can be one of them, the first to start: as a launch of its own it took 7 to 30 us in front of the time loops.
+constexpr int PREP_THREADS = PLAN_THREADS, PREP_TILES = PREP_THREADS / 256;
 constexpr int PREP_MAX_JOBS = 26;   // 2 matrices + 1 bias per layer, 8 layers; the fp32 rows of a bf16 call; words to clear
 constexpr int PREP_BIAS = 0, PREP_ROWS = -1, PREP_CLEAR = -2;
 struct PrepJob {
@@ -56,34 +58,43 @@ __device__ __forceinline__ void convert_rows(const float* __restrict__ src, E* _
 __global__ __launch_bounds__(256) void convert_rows_kernel(const float* __restrict__ src, bf16_t* __restrict__ dst, unsigned quads) {
     convert_rows(src, dst, quads, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
 }
+constexpr size_t PREP_TILE_FLOATS = 64 * 65;
+inline size_t prep_lds_bytes() { return std::max(PREP_TILES * PREP_TILE_FLOATS * sizeof(float), sizeof(PlanLds)); }
+// blockIdx.z = 0 is the plan where there is one (plan.plan_fwd != NULL), then the jobs.
 template <typename E>
-__global__ __launch_bounds__(256) void prep_weights_kernel(PrepArgs a, int H) {
-    __shared__ float tile[64][65];
-    const PrepJob& jb = a.job[blockIdx.z];   // (uniform index into the kernel arguments: scalar loads)
+__global__ __launch_bounds__(PREP_THREADS) void prep_weights_kernel(PrepArgs a, int H, PlanArgs plan) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char prep_smem[];
+    const int planned = plan.plan_fwd != nullptr ? 1 : 0;
+    if ((int)blockIdx.z < planned) {
+        if (blockIdx.x == 0 && blockIdx.y == 0) plan_launches(plan, *reinterpret_cast<PlanLds*>(prep_smem));
+        return;
+    }
+    const PrepJob& jb = a.job[blockIdx.z - planned];   // (uniform index into the kernel arguments: scalar loads)
     const int cols = jb.cols;
+    const unsigned first = (blockIdx.y * gridDim.x + blockIdx.x) * PREP_THREADS + threadIdx.x, stride = gridDim.x * gridDim.y * PREP_THREADS;
     if (cols == PREP_ROWS) {
-        convert_rows(jb.W, static_cast<E*>(jb.dst), jb.quads, (blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x, gridDim.x * gridDim.y * 256);
+        convert_rows(jb.W, static_cast<E*>(jb.dst), jb.quads, first, stride);
         return;
     }
     if (cols == PREP_CLEAR) {
-        for (unsigned i = (blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < jb.quads; i += gridDim.x * gridDim.y * 256)
-            static_cast<int32_t*>(jb.dst)[i] = 0;
+        for (unsigned i = first; i < jb.quads; i += stride) static_cast<int32_t*>(jb.dst)[i] = 0;
         return;
     }
     if (cols == PREP_BIAS) {   // bias: dst[q] = b_ih + b_hh, gate rows interleaved
-        const int q = (blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
-        if (q < 4 * H) {
+        for (unsigned q = first; q < 4u * H; q += stride) {
             const int src = (q & 3) * H + (q >> 2);
             static_cast<float*>(jb.dst)[q] = jb.W[src] + jb.b_hh[src];
         }
         return;
     }
-    const int q0 = blockIdx.y * 64, d0 = blockIdx.x * 64;
-    if (d0 >= cols) return;
+    const int tid = threadIdx.x & 255, sub = threadIdx.x >> 8;
+    float (*tile)[65] = reinterpret_cast<float (*)[65]>(prep_smem) + sub * 64;
+    const int q0 = blockIdx.y * 64, d0 = (blockIdx.x * PREP_TILES + sub) * 64;
+    if ((int)blockIdx.x * PREP_TILES * 64 >= cols) return;   // (the whole workgroup)
     const float* __restrict__ W = jb.W;
     E* __restrict__ dst = static_cast<E*>(jb.dst);
     E* __restrict__ dstT = static_cast<E*>(jb.dstT);
-    const int c4 = (threadIdx.x & 15) * 4, r0 = threadIdx.x >> 4;
+    const int c4 = (tid & 15) * 4, r0 = tid >> 4;
 #pragma unroll
     for (int r = r0; r < 64; r += 16) {
         const int q = q0 + r, d = d0 + c4;   // 4H is a multiple of 64: q is always a valid row
@@ -495,14 +506,12 @@ inline int device_fits_time_loops() {
     return known[dev] > 0 ? VER_OK : VER_EUNSUPPORTED;
 }
 
-// Before the forward two-layer launch: one small kernel zeroes the flags, ticket counters, hand-over words and the
-// sticky time-out word at the start of the workspace, and writes the plans of both launches of the minibatch (the
-// backward call runs on the packing of the forward call whose activations it finds in the workspace).  Before the
-// backward launch only the words are cleared.
-inline void pipe_prepare_fwd(LstmWs& ws, int mode, bool wide, int G, int M, const int32_t* info, const int32_t* batch_sizes, hipStream_t s) {
-    int* last = ws.pipe + ws.pipe_words;
-    hipLaunchKernelGGL(lstm_pipe_plan_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, info, batch_sizes, M, ws.plan[0], ws.plan[1],
-                       ws.plan_scratch, ws.err, (int)(last - ws.err), plan_cost(mode, wide, true, G), plan_cost(mode, wide, false, G));
+// What the first launch of the forward pass does for the two-layer launches: zeroes the flags, ticket counters, hand-over words
+// and the sticky time-out word at the start of the workspace, and writes the plans of both launches of the minibatch (the
+// backward call runs on the packing of the forward call whose activations it finds in the workspace).
+inline PlanArgs pipe_plan(const LstmWs& ws, int mode, bool wide, int G, int M, const int32_t* info, const int32_t* batch_sizes) {
+    return PlanArgs{info, batch_sizes, M, ws.plan[0], ws.plan[1], ws.plan_scratch, ws.err, (int)(ws.pipe + ws.pipe_words - ws.err),
+                    plan_cost(mode, wide, true, G), plan_cost(mode, wide, false, G)};
 }
 inline void pipe_work(const LstmWs& ws, int dir, int M, const int32_t* t_off, PipeWork* pw) {
     pw->M = M;
@@ -572,9 +581,13 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             pa.job[n++] = PrepJob{w[4 * l + 2], w[4 * l + 3], L.bias, nullptr, PREP_BIAS, 0};
         }
         if (ws.x_op) pa.job[n++] = PrepJob{static_cast<const float*>(x), nullptr, ws.x_op, nullptr, PREP_ROWS, (unsigned)((size_t)M * c.input_dim / 4)};
-        // without a pair, also the time-out word and the flags of the first time loop (else: pipe_prepare_fwd)
+        // without a pair, also the time-out word and the flags of the first time loop (else: the plan clears them)
         if (!pairs) pa.job[n++] = PrepJob{nullptr, nullptr, ws.err, nullptr, PREP_CLEAR, (unsigned)(ws.flags + REC_FLAG_WORDS - ws.err)};
-        hipLaunchKernelGGL(prep_weights_kernel<E>, dim3((max_cols + 63) / 64, 4 * H / 64, n), dim3(256), 0, s, pa, H);
+        const PlanArgs plan = pairs ? pipe_plan(ws, MODE, wide, H / (4 * mt), M, info, batch_sizes) : PlanArgs{};
+        if (!set_lds(prep_weights_kernel<E>, prep_lds_bytes())) return false;
+        hipLaunchKernelGGL(prep_weights_kernel<E>, dim3((max_cols + 64 * PREP_TILES - 1) / (64 * PREP_TILES), 4 * H / 64, n + (pairs ? 1 : 0)),
+                           dim3(PREP_THREADS), prep_lds_bytes(), s, pa, H, plan);
+        return true;
     };
     // time-batched input projection: gates[M, 4H] = x W_ih^T + (b_ih + b_hh), interleaved columns
     auto project = [&](int l) {
@@ -615,15 +628,12 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             else VER_FWD_LAUNCH(KERNEL, ARGS, 2, 4, 8, false); \
         } } while (0)
 
-    prep_all();
-    bool planned = false;
+    if (!prep_all()) return VER_EHIP;
     for (int l = 0; l < c.n_layers;) {
         if (!project(l)) return VER_EHIP;
         if (pairs && l + 1 < c.n_layers) {
-            // the plan (of the packing: the same for every pair) and the first pair's synchronisation words from one kernel
-            if (!planned) pipe_prepare_fwd(ws, MODE, wide, H / (4 * mt), M, info, batch_sizes, s);
-            else fill_words(ws.flags, (size_t)(ws.pipe + ws.pipe_words - ws.flags), 0, s);
-            planned = true;
+            // (the plan, of the packing, is the same for every pair)
+            if (l > 0) fill_words(ws.flags, (size_t)(ws.pipe + ws.pipe_words - ws.flags), 0, s);
             PipeFwdArgs pa;
             pa.l0 = rec_args(l);
             pa.l1 = rec_args(l + 1, true);

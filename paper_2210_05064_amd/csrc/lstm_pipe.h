@@ -14,7 +14,7 @@
 // workgroups, 1.1 to 1.7 us) plus a little per alive piece, and the launch lasts as long as its slowest group.  The
 // pieces are sorted longest first, so they are cut into three blocks of consecutive pieces: group 0 gets the few
 // longest ones (its chain of T_max dependent steps is what bounds the launch, so its steps should be the
-// cheapest), the last group the many short ones (few steps, each with many pieces).  lstm_pipe_plan_kernel
+// cheapest), the last group the many short ones (few steps, each with many pieces).  the plan
 // picks the two cuts that minimise the largest predicted group time
 //     sum over the group's timesteps of (step + piece * b_t + tile * (ceil(b_t / 16) - 1)),   b_t = alive pieces of the group
 // (a time loop works through the alive pieces 16 at a time: the MFMA's columns), which it evaluates per candidate
@@ -40,7 +40,7 @@ constexpr int PIPE_GROUPS = 3;       // groups (XCDs) per layer
 constexpr int PIPE_XCDS = 8;         // XCDs of the chip: those beyond the two layers' groups are workers
 static_assert(PIPE_XCDS - 2 * PIPE_GROUPS == 2, "two worker XCDs");
 
-// The plan of a launch (ints in global memory, written by lstm_pipe_plan_kernel):
+// The plan of a launch (ints in global memory, written by plan_launches):
 constexpr int PLAN_KB = 0;           // [PIPE_GROUPS + 1] first piece of every group's block, then the number of pieces
 constexpr int PLAN_T = 8;            // [PIPE_GROUPS] timesteps of the group (those of its first piece; 0 if it has none)
 constexpr int PLAN_CT = 12;          // [PIPE_GROUPS] timesteps per chunk
@@ -232,20 +232,26 @@ __device__ __forceinline__ void plan_body(const int32_t* __restrict__ batch_size
     }
 }
 
-// One workgroup, in front of the forward launch: clears that launch's synchronisation words and writes the plans of
-// the forward and of the backward launch (see the top of this file).  scratch: plan_scratch_floats(M) floats.
-__global__ __launch_bounds__(PLAN_THREADS) void lstm_pipe_plan_kernel(const int32_t* __restrict__ info, const int32_t* __restrict__ batch_sizes,
-                                                                      int M, int* __restrict__ plan_fwd, int* __restrict__ plan_bwd,
-                                                                      float* __restrict__ scratch, int* __restrict__ clear_first, int n_clear,
-                                                                      PlanCost pc_fwd, PlanCost pc_bwd) {
-    __shared__ int s_bs[PLAN_LDS_N];
-    __shared__ float s_len[PLAN_LDS_N], s_S1[PLAN_LDS_N + 1];
-    const int n_seq = min(max(info[0], 0), M), T = min(max(info[1], 0), M);
-    for (int i = threadIdx.x; i < n_clear; i += PLAN_THREADS) clear_first[i] = 0;
+// By one workgroup in front of the forward launch: clears that launch's synchronisation words and writes the plans of the
+// forward and of the backward launch (see the top of this file).  scratch: plan_scratch_floats(M) floats.
+struct PlanArgs {
+    const int32_t* info; const int32_t* batch_sizes;
+    int M;
+    int* plan_fwd; int* plan_bwd; float* scratch;
+    int* clear; int n_clear;
+    PlanCost fwd, bwd;
+};
+struct PlanLds {
+    int bs[PLAN_LDS_N];
+    float len[PLAN_LDS_N], S1[PLAN_LDS_N + 1];
+};
+__device__ __forceinline__ void plan_launches(const PlanArgs& a, PlanLds& lds) {
+    const int M = a.M, n_seq = min(max(a.info[0], 0), M), T = min(max(a.info[1], 0), M);
+    for (int i = threadIdx.x; i < a.n_clear; i += PLAN_THREADS) a.clear[i] = 0;
     if (n_seq <= PLAN_LDS_N && T <= PLAN_LDS_N)
-        plan_body<true>(batch_sizes, M, n_seq, T, plan_fwd, plan_bwd, scratch, s_bs, s_len, s_S1, pc_fwd, pc_bwd);
+        plan_body<true>(a.batch_sizes, M, n_seq, T, a.plan_fwd, a.plan_bwd, a.scratch, lds.bs, lds.len, lds.S1, a.fwd, a.bwd);
     else
-        plan_body<false>(batch_sizes, M, n_seq, T, plan_fwd, plan_bwd, scratch, s_bs, s_len, s_S1, pc_fwd, pc_bwd);
+        plan_body<false>(a.batch_sizes, M, n_seq, T, a.plan_fwd, a.plan_bwd, a.scratch, lds.bs, lds.len, lds.S1, a.fwd, a.bwd);
 }
 
 // One 128 x 256 tile of C[M, N] = A[M, K] B[N, K]^T + bias for bf16 operands, by 8 waves (2 x 4 of 64 x 64) of a workgroup
