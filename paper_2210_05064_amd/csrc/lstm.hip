@@ -166,7 +166,7 @@ __global__ __launch_bounds__(256) void heads_fwd_kernel(const float* __restrict_
     }
 }
 
-// The heads' part of the backward pass, one launch (nothing in it depends on anything else in it); blockIdx.y says which:
+// The heads' part of the backward pass, one launch (nothing in it depends on anything else in it); blockIdx.x says which:
 //  * dh[p][j] = sum_a d_u[p][a] W_a[a][j] + d_v[p] w_v[j].  A thread owns 4 adjacent columns (16-byte stores; H is a
 //    multiple of 64) for a block of HB_ROWS rows, so a head weight is read once per block instead of once per row.  Bound by
 //    writing dh once.  These blocks also clear the synchronisation words of the time loop that follows.
@@ -184,15 +184,14 @@ struct HeadsBwdArgs {
     const float* rows; bf16_t* rows_op;
     int M, H, A, n_clear;
     unsigned quads;          // (rows)
-    int dh_blocks, w_blocks; // blockIdx.y below dh_blocks: dh; then w_blocks of weight-gradient blocks; then rows
+    int dh_blocks, w_blocks; // blockIdx.x below dh_blocks: dh; then w_blocks of weight-gradient blocks; then rows
 };
 __device__ __forceinline__ void heads_dh_block(const HeadsBwdArgs& a, int block) {
     __shared__ float s_g[HB_ROWS][64];   // the block's loss gradients: heads 0..A-1, then the value head
     const int M = a.M, H = a.H, A = a.A;
-    const int j = (blockIdx.x * 256 + threadIdx.x) * 4;
+    const int j = threadIdx.x * 4;   // (H <= 1024)
     const int p0 = block * HB_ROWS;
-    if (blockIdx.x == 0)
-        for (int i = block * 256 + threadIdx.x; i < a.n_clear; i += a.dh_blocks * 256) a.clear[i] = 0;
+    for (int i = block * 256 + threadIdx.x; i < a.n_clear; i += a.dh_blocks * 256) a.clear[i] = 0;
     for (int i = threadIdx.x; i < HB_ROWS * 64; i += 256) {
         const int r = i >> 6, e = i & 63, p = p0 + r;
         s_g[r][e] = (p < M) ? (e < A ? a.d_u[(size_t)p * A + e] : (e == A ? a.d_v[p] : 0.f)) : 0.f;
@@ -263,15 +262,10 @@ __device__ __forceinline__ void heads_wgrad_block(const HeadsBwdArgs& a, int blo
     }
 }
 __global__ __launch_bounds__(256) void heads_bwd_kernel(HeadsBwdArgs a) {
-    const int y = blockIdx.y;
-    if (y < a.dh_blocks) {
-        heads_dh_block(a, y);
-    } else if (y < a.dh_blocks + a.w_blocks) {
-        heads_wgrad_block(a, (y - a.dh_blocks) * gridDim.x + blockIdx.x);
-    } else {
-        const unsigned first = (y - a.dh_blocks - a.w_blocks) * gridDim.x + blockIdx.x;
-        convert_rows(a.rows, a.rows_op, a.quads, first * 256 + threadIdx.x, (gridDim.y - a.dh_blocks - a.w_blocks) * gridDim.x * 256);
-    }
+    const int b = blockIdx.x, rows0 = a.dh_blocks + a.w_blocks;
+    if (b < a.dh_blocks) heads_dh_block(a, b);
+    else if (b < rows0) heads_wgrad_block(a, b - a.dh_blocks);
+    else convert_rows(a.rows, a.rows_op, a.quads, (b - rows0) * 256 + threadIdx.x, (gridDim.x - rows0) * 256);
 }
 // One workgroup adds the row blocks' partial sums for 64 columns of one head: its four waves take a quarter of the
 // row blocks each (in index order, 8 loads in flight), and the four shares are added in wave order.
@@ -686,10 +680,9 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     ha.M = M; ha.H = H; ha.A = A;
     ha.clear = ws.flags; ha.n_clear = top_pair ? (int)(ws.pipe + ws.pipe_words - ws.flags) : REC_FLAG_WORDS;
     ha.rows = static_cast<const float*>(x); ha.rows_op = ws.x_op; ha.quads = ws.x_op ? (unsigned)((size_t)M * c.input_dim / 4) : 0;
-    const int gx = (H / 4 + 255) / 256;
     ha.dh_blocks = (M + HB_ROWS - 1) / HB_ROWS;
-    ha.w_blocks = ((rb_h * (H / 64) + 3) / 4 + gx - 1) / gx;
-    hipLaunchKernelGGL(heads_bwd_kernel, dim3(gx, ha.dh_blocks + ha.w_blocks + std::min(1024u, (ha.quads + 1023) / 1024)), dim3(256), 0, s, ha);
+    ha.w_blocks = (rb_h * (H / 64) + 3) / 4;
+    hipLaunchKernelGGL(heads_bwd_kernel, dim3(ha.dh_blocks + ha.w_blocks + std::min(1024u, (ha.quads + 1023) / 1024)), dim3(256), 0, s, ha);
     }
     HeadsFinalArgs hf{ws.part, ws.part_b, gw[4 * nl], gw[4 * nl + 2], gw[4 * nl + 1], gw[4 * nl + 3], (M + HW_ROWS - 1) / HW_ROWS, H, A};
 

@@ -5,6 +5,7 @@ tensors that come out of back-propagation through time, which have a bar of
 their own (tests/util.py: assert_close_bf16_bptt)."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import lstm as olstm, pack as opack
 from paper_2210_05064_amd import workloads as wl
@@ -212,6 +213,29 @@ def test_head_gradients(ver, rows, hidden, act_dim):
     """Row blocks of the heads' weight gradients at their edges; head counts at the edges of the 16-row products."""
     case(ver, wl.scaled(wl.WORKLOADS["manip"], budget=rows, n_envs=3, hidden=hidden, input_dim=8, act_dim=act_dim, n_layers=1, p_done=0.05,
                         minibatches=1), seed=rows)
+
+
+@pytest.mark.parametrize("compute", [0, 1])
+def test_fp32_rows_at_any_word(ver, compute):
+    """Input rows and the input gradient that begin 4, 8 and 12 bytes behind a 16-byte boundary: bit for bit the result of
+    aligned ones."""
+    w = wl.scaled(wl.WORKLOADS["manip"], budget=150, n_envs=5, hidden=64, input_dim=36, n_layers=2, p_done=0.05, minibatches=1)
+    ro = wl.make_rollout(w, seed=4, bias_scale=0.2)
+    meta = opack.pack_minibatch(ro["dones"], ro["env_off"], ro["seq_key"][0], 1, 0, ro["env_started_episode"])
+    x = opack.gather_rows(ro["obs"], meta["gather_idx"])
+    d_u = np.full((meta["M"], w.act_dim), 1.0 / meta["M"], np.float32)
+    d_v = np.full(meta["M"], 1.0 / meta["M"], np.float32)
+    res = []
+    for words in range(4):
+        run = LstmRun(ver, w, ro["weights"], x, meta, compute=compute)
+        at = torch.zeros(x.size + words, device="cuda")[words:].view(x.shape)
+        at.copy_(run.x)
+        run.x = at
+        u, v = run.forward()
+        grads, dx = run.backward(d_u, d_v)
+        res.append([u, v, dx] + grads)
+    for other in res[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(res[0], other))
 
 
 def test_packing_order_invariance_on_device(ver):
