@@ -15,8 +15,8 @@
 //    registers every 128 k, so chains of additions stay as short as with a split;
 //  * all weight gradients of a minibatch share a launch, so the last, partly filled round of the chip is paid once.
 // us, the 128 x 128 register-staged tiles with a split contraction that ran here before -> now: the four weight gradients of 2 x
-// 512 units over 1024 rows (8.7 GFLOP) 235 -> 98, input projection 1024 x 2048 x 516 55 -> 26, input gradient 1024 x
-// 516 x 2048 55 -> 35.  Counters of the first: the CUs are busy 84 % of the launch (its last round is partly filled), the MFMAs 79 % of that.
+// 512 units over 1024 rows (8.7 GFLOP) 235 -> 88, input projection 1024 x 2048 x 516 55 -> 26, input gradient 1024 x
+// 516 x 2048 55 -> 35.  Counters of the first (tiles of 64): the CUs are busy 84 % of the launch (its last round is partly filled), the MFMAs 79 % of that.
 #include "gemm_group.h"
 #include "mfma.h"
 
@@ -141,14 +141,26 @@ __device__ __forceinline__ void tile(const GemmProblem& q, int t, unsigned char*
     if (nk >= G::STAGES) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((G::STAGES - 1) * 2 * G::NL) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     bar_lds();
-    // The operands of K-tile kt + 1 are read before the MFMAs of K-tile kt are issued.
+    // The operands of K-tile kt + 1 are read before the MFMAs of K-tile kt are issued; K-minor, whose 8 paired reads keep a small
+    // tile's 8 MFMAs waiting for longest, between them (two layers of 64 units, 2048 rows 18.0 -> 14.8 us, of 512, 1024 rows in
+    // tiles of 32 92.7 -> 87.5; K-major in tiles of 32 3 % slower).
     Operands even, odd;
     auto step = [&](int kt, const Operands& now, Operands& next) {
         arrived();   // (and everyone has read the stage of kt, which is the one that is filled again)
         if (kt + G::STAGES < nk) issue(kt + G::STAGES);
-        read(kt + 1, next);
         __builtin_amdgcn_sched_barrier(0);
+        read(kt + 1, next);
+        if (!KMIN) __builtin_amdgcn_sched_barrier(0);
         multiply(now);
+        if constexpr (KMIN) {
+            constexpr int MFMAS = 8 * G::WT * G::WT, READS = 8, PER = MFMAS / READS / 2 > 0 ? MFMAS / READS / 2 : 1;
+#pragma unroll
+            for (int x = 0; x < READS; ++x) {   // PER MFMAs, one (paired) LDS read
+                __builtin_amdgcn_sched_group_barrier(0x8, PER, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x8, MFMAS - READS * PER, 0);
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
     read(0, even);
@@ -203,14 +215,15 @@ void start(const GemmGroupArgs& a, hipStream_t s) {
     hipLaunchKernelGGL((gemm_f32_kernel<T, KMIN>), dim3(group_grid(a.tiles)), dim3(256), Geom<T>::STAGES * Geom<T>::STAGE, s, a);
 }
 
-// From this many tiles of 64 on they fill the chip.  us with tiles of 64 / 32: 512 tiles 26.2 / 30.0, 4096 367 / 434, 1056 (K-minor)
-// 99.8 / 97.3, 256 48.7 / 47.9, 144 46.1 / 35.5, 80 6.2 / 4.5, 24 (K-minor, 2048 rows) 42 / 19.
-constexpr int T64_FROM = 384;
+// From this many tiles of 64 on they fill the chip.  us with tiles of 64 / 32: 512 tiles 26.2 / 30.0, 4096 367 / 434, 256 48.7 / 47.9,
+// 144 46.1 / 35.5, 80 6.2 / 4.5; K-minor 1056 92.7 / 87.5 (in tiles of 64 a few more than the chip holds at a time), 544 408 / 414, 24
+// (2048 rows) 36.4 / 14.8.
+constexpr int T64_FROM = 384, T64_FROM_K_MINOR = 1280;
 
 }  // namespace
 
 void GemmGroup::launch_f32(hipStream_t s) {
-    if (lay_out(64) >= T64_FROM) {
+    if (lay_out(64) >= (k_minor ? T64_FROM_K_MINOR : T64_FROM)) {
         k_minor ? start<64, true>(a, s) : start<64, false>(a, s);
     } else {
         lay_out(32);
