@@ -332,9 +332,9 @@ __global__ __launch_bounds__(LOSS_THREADS) void ppo_loss_fixed_kernel(
     }
     const float gauss_ent = (float)ls_sum + (float)A * (0.5f + HALF_LOG_2PI);   // the same for every row
     // what every row's log-probability has in common, in two parts: rounded to one, its error would be the same in all rows and
-    // stay in their mean (approximate KL), the more so the wider the rows
+    // stay in their mean (approximate KL), the more so the wider the rows.  (An infinite sum has no second part: inf - inf.)
     const double log_norm = ls_sum + (double)A * (double)HALF_LOG_2PI;
-    const float norm_hi = (float)log_norm, norm_lo = (float)(log_norm - (double)norm_hi);
+    const float norm_hi = (float)log_norm, norm_lo = isinf(norm_hi) ? 0.f : (float)(log_norm - (double)norm_hi);
     float acc[LOSS_SCALARS] = {0.f, 0.f, 0.f, 0.f, 0.f};
     const int stride = gridDim.x * LOSS_THREADS;
     const int rounds = (M + stride - 1) / stride;

@@ -89,6 +89,20 @@ def test_rows_beyond_whole_chunks(ver, dist, A, M):
     check(ver, dist, make(np.random.default_rng(M + A), dist, M, A))
 
 
+@pytest.mark.parametrize("A", [1, 11, 24, 25])
+def test_infinite_deviation(ver, A):
+    """A log-std of +inf: probability 0, so no gradient but the entropy's; infinite entropy and approximate KL, nothing NaN."""
+    x = make(np.random.default_rng(A), 1, 300, A)
+    x["ls"][A // 2] = np.inf
+    scal, d_u, d_v, d_ls = run(ver, 1, x)
+    ref, r_u, r_v, r_ls = opl.ppo_loss(1, x["u"], x["v"], x["ls"], x["act"], x["logp_old"], x["adv"], x["ret"],
+                                       float(np.float32(0.2)), 0.5, float(np.float32(1e-2)))
+    np.testing.assert_allclose(scal, [ref[n] for n in NAMES], rtol=TOL)
+    np.testing.assert_array_equal(d_u, r_u)
+    np.testing.assert_allclose(d_v, r_v, rtol=TOL)
+    np.testing.assert_allclose(d_ls, r_ls, rtol=TOL)
+
+
 @pytest.mark.parametrize("dist,A", [(0, 4), (1, 11)])
 def test_row_weights(ver, dist, A):
     rng = np.random.default_rng(3)
