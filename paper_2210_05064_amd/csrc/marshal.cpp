@@ -56,18 +56,18 @@ PyObject* ptr(PyObject*, PyObject* o) {
 // fill(buffer, tensors): the addresses of a list or tuple of tensors, 8 bytes each, into a writable buffer
 PyObject* fill(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (n != 2) return PyErr_Format(PyExc_TypeError, "fill(buffer, tensors)");
-    PyObject* seq = PySequence_Fast(args[1], "a sequence of tensors");
+    PyObject* seq = PySequence_Tuple(args[1]);   // (a copy: an object's own address function could change the list)
     if (!seq) return nullptr;
     Py_buffer b;
     if (PyObject_GetBuffer(args[0], &b, PyBUF_WRITABLE) != 0) {
         Py_DECREF(seq);
         return nullptr;
     }
-    bool ok = PySequence_Fast_GET_SIZE(seq) * 8 <= b.len;
+    bool ok = PyTuple_GET_SIZE(seq) * 8 <= b.len;
     if (!ok) PyErr_SetString(PyExc_ValueError, "buffer too short");
-    for (Py_ssize_t i = 0; ok && i < PySequence_Fast_GET_SIZE(seq); ++i) {
+    for (Py_ssize_t i = 0; ok && i < PyTuple_GET_SIZE(seq); ++i) {
         unsigned long long p;
-        ok = address_of(PySequence_Fast_GET_ITEM(seq, i), &p);
+        ok = address_of(PyTuple_GET_ITEM(seq, i), &p);
         if (ok) std::memcpy(static_cast<char*>(b.buf) + i * 8, &p, 8);
     }
     PyBuffer_Release(&b);

@@ -45,6 +45,18 @@ def test_look_alikes_and_other_objects():
         ver._ptr(3)
 
 
+def test_a_list_that_changes_meanwhile():
+    """The addresses are those of the list as it was handed over: an object that lengthens it adds nothing to the buffer."""
+    class Grows(Like):
+        def data_ptr(self):
+            tensors.append(Like(99))
+            return self.p
+    tensors = [Grows(5)]
+    buf = (C.c_void_p * 8)()
+    ver._marshal.fill(buf, tensors)
+    assert list(buf) == [5] + [None] * 7
+
+
 def test_pack_args_fields():
     a = ver.pack_args(N=3, S=7, obs=None, h0=Sub(), D=4, workspace=None)
     assert (a.N, a.S, a.D, a.obs, a.h0, a.workspace, a.workspace_bytes) == (3, 7, 4, None, 2 ** 63 + 5, None, 0)
