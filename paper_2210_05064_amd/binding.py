@@ -13,11 +13,12 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("VER_LIB", os.path.join(_HERE, "libver.so"))
-if not os.path.exists(LIB_PATH):
-    raise ImportError(f"{LIB_PATH} is missing: run `python -m paper_2210_05064_amd.build` "
-                      "(or __graft_entry__.build()) first; there is no CPU fallback")
+_NATIVE = os.path.exists(os.path.join(_HERE, "_marshal.so"))   # built with the library; one built elsewhere (VER_LIB) does without
+for _path in [LIB_PATH] + ([] if _NATIVE or "VER_LIB" in os.environ else [os.path.join(_HERE, "_marshal.so")]):
+    if not os.path.exists(_path):
+        raise ImportError(f"{_path} is missing: run `python -m paper_2210_05064_amd.build` "
+                          "(or __graft_entry__.build()) first; there is no CPU fallback")
 lib = C.CDLL(LIB_PATH)
-from . import _marshal  # noqa: E402  (built with the library; after torch, whose symbols it uses)
 
 VER_OK = 0
 _vp, _i32, _sz, _f = C.c_void_p, C.c_int32, C.c_size_t, C.c_float
@@ -133,7 +134,22 @@ def _ptr_any(t) -> int | None:
     return t.data_ptr()
 
 
-_marshal.init(_ptr_any)
+if _NATIVE:
+    from . import _marshal   # (after torch, whose symbols it uses)
+    _marshal.init(_ptr_any)
+else:
+    class _marshal:
+        """The same in Python."""
+        ptr = staticmethod(_ptr_any)
+
+        @staticmethod
+        def fill(arr, tensors):
+            for i, t in enumerate(tensors):
+                arr[i] = _ptr_any(t)
+
+        @staticmethod
+        def pointers(block, offsets, values):
+            return list(values)   # (pack_args takes every field)
 _ptr = _marshal.ptr
 
 

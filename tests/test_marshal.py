@@ -1,6 +1,10 @@
 """Addresses of tensors for the C entry points (csrc/marshal.cpp): the Python rule holds for whatever is not plainly a device
 tensor, errors included.  CPU only (device tensors go through it in every GPU test)."""
 import ctypes as C
+import os
+import shutil
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -65,3 +69,31 @@ def test_pack_args_fields():
         ver.pack_args(N=1, nonsense=Sub())
     with pytest.raises(ValueError):
         ver._marshal.fill((C.c_void_p * 1)(), [None, None])
+
+
+@pytest.mark.parametrize("elsewhere", [True, False])
+def test_sources_that_were_not_built(tmp_path, elsewhere):
+    """Without _marshal.so: a library built elsewhere (VER_LIB) is enough; else the error says what to run."""
+    package = tmp_path / "paper_2210_05064_amd"
+    package.mkdir()
+    for f in ("__init__.py", "binding.py"):
+        shutil.copy(os.path.join(os.path.dirname(ver.__file__), f), package)
+    if not elsewhere:
+        os.symlink(ver.LIB_PATH, package / "libver.so")
+    env = {k: v for k, v in os.environ.items() if k != "VER_LIB"}
+    if elsewhere:
+        env["VER_LIB"] = ver.LIB_PATH
+    code = """if True:
+        from paper_2210_05064_amd import binding as ver
+        class T:
+            is_cuda = True
+            is_contiguous = lambda self: True
+            data_ptr = lambda self: 77
+        a = ver.pack_args(N=3, rnn_h=None, workspace=None)
+        assert ver._ptr(T()) == 77 and list(ver._ptr_array([T(), None])) == [77, None] and (a.N, a.rnn_h, a.workspace) == (3, None, None)
+    """
+    run = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, env=env, capture_output=True, text=True)
+    if elsewhere:
+        assert run.returncode == 0, run.stderr
+    else:
+        assert "ImportError" in run.stderr and "_marshal.so is missing: run `python -m" in run.stderr, run.stderr
