@@ -19,11 +19,15 @@ struct GemmGroup {
     GemmGroupArgs a{};
     bool k_minor, bf16;
     GemmGroup(bool k_minor_, bool bf16_) : k_minor(k_minor_), bf16(bf16_) {}
-    // False if an array is beyond the kernels' 32-bit byte offsets (or the launch is full): not added.
-    bool add(const void* A, int lda, const void* B, int ldb, float* C, int ldc, int Mr, int Nc, int K, const float* bias, int unperm_h) {
+    // Whether all arrays are within the kernels' 32-bit byte offsets.
+    bool fits(int lda, int ldb, int ldc, int Mr, int Nc, int K) const {
         const size_t rowsA = k_minor ? K : Mr, rowsB = k_minor ? K : Nc, es = bf16 ? 2 : 4, lim = 0x7fffffff;
         constexpr size_t over = 256;   // rows that a last tile may address beyond the arrays (they read zero)
-        if (a.n >= GEMM_GROUP_MAX || (rowsA + over) * lda * es >= lim || (rowsB + over) * ldb * es >= lim || (size_t)Mr * ldc * 4 >= lim) return false;
+        return (rowsA + over) * lda * es < lim && (rowsB + over) * ldb * es < lim && (size_t)Mr * ldc * 4 < lim;
+    }
+    // False if they are not (or the launch is full): not added.
+    bool add(const void* A, int lda, const void* B, int ldb, float* C, int ldc, int Mr, int Nc, int K, const float* bias, int unperm_h) {
+        if (a.n >= GEMM_GROUP_MAX || !fits(lda, ldb, ldc, Mr, Nc, K)) return false;
         a.p[a.n++] = GemmProblem{A, B, C, bias, lda, ldb, ldc, Mr, Nc, K, unperm_h, 0, 0};
         return true;
     }

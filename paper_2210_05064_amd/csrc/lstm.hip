@@ -374,6 +374,7 @@ struct LstmWs {
     float* dc_state;   // [M, H]
     float* part;       // partial sums of the two-stage reductions
     float* part_b;     // [row blocks][64]: the heads' bias gradients per row block
+    float* gemm_part;  // partial tiles of the general contraction kernel (gemm.h), where a call's arrays need it
     bf16_t* x_op;      // [M, input_dim]: fp32 input rows of a bf16 call in the operand type
     char* ring;        // [8 groups] exchange rings of the time loops (lstm_few.h)
     float* db_part;    // [2][8][4H]: per layer of a launch and group, the sum of the gate gradients over the group's rows
@@ -383,6 +384,21 @@ struct LstmWs {
 inline size_t part_floats(const ver_lstm_cfg& c, int M) {
     const size_t rb_heads = (size_t)(M + HW_ROWS - 1) / HW_ROWS;
     return rb_heads * (c.act_dim + 1) * c.hidden;   // the row-block partial sums of the heads' weight gradient
+}
+
+// Largest scratch that the general kernel asks for in any contraction of the forward or backward pass.
+inline size_t gemm_part_max(const ver_lstm_cfg& c, int M) {
+    const int bk = c.compute ? GemmGeom<MODE_BF16>::BK : GemmGeom<MODE_F32>::BK, H4 = 4 * c.hidden;
+    const GemmGroup rows(false, c.compute != 0), dw(true, c.compute != 0);
+    size_t m = 0;
+    for (int l = 0; l < c.n_layers; ++l) {
+        const int D = l == 0 ? c.input_dim : c.hidden;
+        if (!rows.fits(D, D, H4, M, H4, D)) m = std::max(m, gemm_part_floats(M, H4, D, bk));
+        if (!rows.fits(H4, H4, D, M, D, H4)) m = std::max(m, gemm_part_floats(M, D, H4, bk));
+        for (int n : {D, c.hidden})
+            if (!dw.fits(H4, n, n, H4, n, M)) m = std::max(m, gemm_part_floats(H4, n, M, bk));
+    }
+    return m;
 }
 
 inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws) {
@@ -421,6 +437,7 @@ inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws)
     ws->dc_state = cv.take<float>(2 * Mz * H);
     ws->part = cv.take<float>(part_floats(c, M));
     ws->part_b = cv.take<float>((size_t)(M + HW_ROWS - 1) / HW_ROWS * 64);
+    ws->gemm_part = cv.take<float>(gemm_part_max(c, M));
     ws->x_op = c.compute && !c.x_bf16 ? cv.take<bf16_t>(Mz * c.input_dim) : nullptr;
     ws->db_part = cv.take<float>((size_t)2 * REC_GROUPS * 4 * H);
     ws->ring = cv.take<char>(REC_GROUPS * few_ring_bytes(c.compute ? MODE_BF16 : MODE_F32, 4 * c.hidden));
@@ -460,10 +477,10 @@ inline bool set_lds(K kernel, size_t bytes) {
 // (45 and 28 us at K = 1044).  What lies beyond the 32-bit byte offsets of these kernels (only rows of the caller's can) goes
 // to the general kernel.
 template <int MODE>
-inline int contract_rows(const typename RecGeom<MODE>::E* A, const typename RecGeom<MODE>::E* B, float* C, const float* bias, int M, int N, int K, hipStream_t s) {
+inline int contract_rows(const typename RecGeom<MODE>::E* A, const typename RecGeom<MODE>::E* B, float* C, const float* bias, int M, int N, int K, float* part, hipStream_t s) {
     GemmGroup g(false, MODE == MODE_BF16);
     if (!g.add(A, K, B, K, C, N, M, N, K, bias, 0)) {
-        gemm_launch<MODE, false>(A, K, B, K, C, N, M, N, K, bias, 0, s);
+        gemm_launch<MODE, false>(A, K, B, K, C, N, M, N, K, bias, 0, part, s);
         return VER_OK;
     }
     if (MODE == MODE_BF16 && g.lay_out(64) > 4 * REC_GRID) {
@@ -588,7 +605,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         const int D = l == 0 ? c.input_dim : H;
         LayerWs& L = ws.layer[l];
         ProfScope prof(VER_PROF_LSTM_GEMM_FWD, s);
-        return contract_rows<MODE>(layer_input<MODE>(c, ws, x, l), static_cast<const E*>(L.wih), L.gates, L.bias, M, 4 * H, D, s) == VER_OK;
+        return contract_rows<MODE>(layer_input<MODE>(c, ws, x, l), static_cast<const E*>(L.wih), L.gates, L.bias, M, 4 * H, D, ws.gemm_part, s) == VER_OK;
     };
     auto rec_args = [&](int l, bool consumer = false) {
         LayerWs& L = ws.layer[l];
@@ -742,7 +759,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         // gradient w.r.t. the layer input: dx[M, D] = dz[M, 4H] . W_ih[4H, D]
         if (dx) {
             ProfScope prof(VER_PROF_LSTM_GEMM_DX, s);
-            ok = contract_rows<MODE>(dz, static_cast<const E*>(L.wihT), dx, nullptr, M, D, 4 * H, s) == VER_OK;
+            ok = contract_rows<MODE>(dz, static_cast<const E*>(L.wihT), dx, nullptr, M, D, 4 * H, ws.gemm_part, s) == VER_OK;
         }
         // dW_ih[4H, D] = dz^T x ; dW_hh[4H, H] = dz^T h_{t-1}; stored gate-major.  The contractions of a layer or pair leave in
         // one launch.
@@ -750,7 +767,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         ProfScope prof(VER_PROF_LSTM_GEMM_DW, s);
         auto contract = [&](const E* B, float* C, int Nc) {
             if (!dw.add(dz, 4 * H, B, Nc, C, Nc, 4 * H, Nc, M, nullptr, H))
-                gemm_launch<MODE, true>(dz, 4 * H, B, Nc, C, Nc, 4 * H, Nc, M, nullptr, H, s);
+                gemm_launch<MODE, true>(dz, 4 * H, B, Nc, C, Nc, 4 * H, Nc, M, nullptr, H, ws.gemm_part, s);
         };
         contract(layer_input<MODE>(c, ws, x, l), gw[4 * l], D);
         contract(static_cast<const E*>(L.hprev), gw[4 * l + 1], H);

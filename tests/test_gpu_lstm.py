@@ -420,3 +420,45 @@ def test_nan_stays_in_its_piece(ver, compute, hidden, n_layers, n_envs):
     (_, dx), (grads_bad, dx_bad) = [r.backward(d_u, d_v) for r in runs]
     assert np.isnan(dx_bad[hit]).all() and np.array_equal(dx_bad[~hit], dx[~hit])
     assert np.isnan(grads_bad[1]).any()
+
+
+@pytest.mark.parametrize("rows,input_dim,compute", [(520000, 1044, 0), (2000, 270000, 0), (1040000, 1044, 1), (4000, 270000, 1)])
+def test_arrays_beyond_2_gigabytes(ver, rows, input_dim, compute):
+    """Input rows and their gradient of 2 GB and more (the general contraction kernel): few tiles and a long contraction in the
+    weight gradient (many rows) or in the projection (wide rows).  One timestep of `rows` pieces, so that plain torch in 64 bits
+    is the reference.  fp32: a sum of n terms as P partial sums of chains of n / (4 P) additions is off by about
+    2^-24 sqrt(n / (8 P)) of its size; P = 8, and half as much again.  bf16: gate gradients rounded to 8 bits."""
+    H, A = 64, 4
+    M, D, g = rows, input_dim, torch.Generator(device="cuda").manual_seed(rows)
+    normal = lambda *shape, scale=1.0: torch.randn(*shape, generator=g, device="cuda").mul_(scale)
+    x = normal(M, D)
+    x = x.bfloat16() if compute else x
+    w = [normal(4 * H, D, scale=D ** -0.5), normal(4 * H, H, scale=H ** -0.5), normal(4 * H, scale=0.1), normal(4 * H, scale=0.1),
+         normal(A, H, scale=H ** -0.5), normal(A, scale=0.1), normal(H, scale=H ** -0.5), normal(1, scale=0.1)]
+    if compute:
+        w[0] = w[0].bfloat16().float()   # (exact in the operand type: the rounding of the weights is not what is tested)
+    d_u, d_v = normal(M, A, scale=1.0 / M), normal(M, scale=1.0 / M)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    info, bs, t_off = torch.tensor([M, 1, M, 0], **i32), torch.zeros(M, **i32), torch.full((M + 1,), M, **i32)
+    bs[0], t_off[0] = M, 0
+    cfg = ver.lstm_cfg(1, D, H, A, compute, compute)
+    ws = ver.workspace(ver.ver_lstm_workspace_bytes(cfg, M))
+    nan = lambda t: torch.full_like(t, float("nan"))
+    u, v, grads, dx = nan(d_u), nan(d_v), [nan(t) for t in w], torch.full((M, D), float("nan"), device="cuda")
+    ver.ver_lstm_fwd(cfg, x, M, info, bs, t_off, None, None, 0, w, u, v, ws)
+    ver.ver_lstm_bwd(cfg, x, M, info, bs, t_off, None, None, 0, w, d_u, d_v, grads, dx, ws)
+    torch.cuda.synchronize()
+    assert ws[0].item() == 0
+    W = [t.double().requires_grad_() for t in w]
+    x64 = x.double().requires_grad_()
+    gate_i, _, gate_g, gate_o = (x64 @ W[0].t() + (W[2] + W[3])).chunk(4, 1)
+    h = torch.sigmoid(gate_o) * torch.tanh(torch.sigmoid(gate_i) * torch.tanh(gate_g))
+    u64, v64 = h @ W[4].t() + W[5], h @ W[6] + W[7]
+    ((u64 * d_u.double()).sum() + (v64 * d_v.double()).sum()).backward()
+    off = lambda got, ref: ((got.double() - ref).norm() / ref.norm()).item()
+    chain = lambda n: 1.5 * 2.0 ** -24 * (n / 64) ** 0.5
+    tight, rounded = max(chain(D), 2e-6), 2.0 ** -8
+    assert off(u, u64.detach()) <= tight and off(v, v64.detach()) <= tight
+    assert off(grads[0], W[0].grad) <= (rounded if compute else max(chain(M), tight))
+    assert off(dx, x64.grad) <= (rounded if compute else tight)
+    assert off(grads[2], W[2].grad) <= (rounded if compute else 1e-5) and not grads[1].any()
