@@ -4,7 +4,8 @@
 // Same frame as gemm_f32.hip: K-tiles of 64 straight from global memory into LDS, two stages, one barrier per K-tile, the operands
 // of the next K-tile read before the MFMAs of this one, several workgroups per CU.  A wave's 32 x 32 needs 4 KB of LDS reads for 64
 // MFMA cycles, so a full chip is bound by LDS at half the MFMA rate; these launches are bound by the latency of their few
-// K-tiles instead.  K-minor operands are read with the transposing LDS load (its lane layout: gemm.h).
+// K-tiles instead (K-minor ones, whose contraction runs over the rows of a minibatch, are split to that end: gemm_group.h).
+// K-minor operands are read with the transposing LDS load (its lane layout: gemm.h).
 #include "gemm_group.h"
 #include "mfma.h"
 
@@ -171,10 +172,39 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmGroupArgs g) {
 }
 __global__ __launch_bounds__(256) void gemm_bf16_k_minor_kernel(GemmGroupArgs g) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[STAGES * STAGE];
-    const int t = group_tile(g.tiles);
-    if (t < 0) return;
-    const GemmProblem q = group_problem(g, t);
+    const int all = group_tile(g.tiles * g.parts);
+    if (all < 0) return;
+    const int part = all / g.tiles, t = all - part * g.tiles;
+    GemmProblem q = group_problem(g, t);
+    if (g.parts > 1) {   // rows [part * k_part, ...) of both operands, into the part's own results
+        const int k0 = part * g.k_part;
+        q.A = static_cast<const bf16_t*>(q.A) + (size_t)k0 * q.lda;
+        q.B = static_cast<const bf16_t*>(q.B) + (size_t)k0 * q.ldb;
+        q.K = min(q.K - k0, g.k_part);
+        q.C = q.part + (size_t)part * q.Mr * q.Nc;
+        q.ldc = q.Nc;
+        q.unperm_h = 0;
+    }
     tile<true>(q, t - q.tile_first, smem);
+}
+// C = sum of the parts in index order, 8 loads in flight; blockIdx.y: the problem.
+__global__ __launch_bounds__(256) void gemm_add_parts_kernel(GemmGroupArgs g) {
+    const GemmProblem& q = g.p[blockIdx.y];   // (uniform index into the kernel arguments: scalar loads)
+    const unsigned total = (unsigned)q.Mr * q.Nc;
+    for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
+        float s = 0.f;
+        int z = 0;
+        for (; z + 8 <= g.parts; z += 8) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = q.part[(size_t)(z + u) * total + i];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+        for (; z < g.parts; ++z) s += q.part[(size_t)z * total + i];
+        const unsigned m = i / q.Nc, n = i - m * q.Nc, out = q.unperm_h > 0 ? (m & 3) * q.unperm_h + (m >> 2) : m;
+        q.C[(size_t)out * q.ldc + n] = s;
+    }
 }
 
 // ---- large K-major contractions: 256 x 256 tiles, 8 waves (2 x 4 of 128 x 64), one workgroup per CU ------------------------
@@ -303,9 +333,25 @@ __global__ __launch_bounds__(L_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)
 }  // namespace
 
 void GemmGroup::launch_bf16(hipStream_t s) {
-    lay_out(T);
-    if (k_minor) hipLaunchKernelGGL(gemm_bf16_k_minor_kernel, dim3(group_grid(a.tiles)), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(gemm_bf16_kernel, dim3(group_grid(a.tiles)), dim3(256), 0, s, a);
+    const int tiles = lay_out(T);
+    if (!k_minor) {
+        hipLaunchKernelGGL(gemm_bf16_kernel, dim3(group_grid(tiles)), dim3(256), 0, s, a);
+        return;
+    }
+    const int K = a.p[0].K;   // (the same in all of them: the rows of a minibatch)
+    a.parts = part ? std::max(1, std::min(K / PART_ROWS, PART_TILES / tiles)) : 1;
+    a.k_part = ((K + a.parts - 1) / a.parts + BK - 1) / BK * BK;
+    a.parts = (K + a.k_part - 1) / a.k_part;   // (none of them empty)
+    unsigned most = 0;
+    float* to = part;
+    for (int i = 0; a.parts > 1 && i < a.n; ++i) {
+        const unsigned results = (unsigned)a.p[i].Mr * a.p[i].Nc;
+        a.p[i].part = to;
+        to += (size_t)a.parts * results;
+        most = std::max(most, results);
+    }
+    hipLaunchKernelGGL(gemm_bf16_k_minor_kernel, dim3(group_grid(tiles * a.parts)), dim3(256), 0, s, a);
+    if (a.parts > 1) hipLaunchKernelGGL(gemm_add_parts_kernel, dim3(std::min(1024u, (most + 255) / 256), a.n), dim3(256), 0, s, a);
 }
 
 bool GemmGroup::launch_large(hipStream_t s) {

@@ -1,5 +1,7 @@
 // Contractions of the LSTM outside the time loops, several to a launch: host interface of gemm_f32.hip and gemm_bf16.hip.
 #pragma once
+#include <algorithm>
+
 #include "common.h"
 
 namespace ver {
@@ -9,8 +11,10 @@ struct GemmProblem {
     const void* A; const void* B; float* C; const float* bias;
     int lda, ldb, ldc, Mr, Nc, K, unperm_h;
     int tiles_n, tile_first;   // column tiles; first tile of the problem in the launch
+    float* part;               // parts > 1: [parts][Mr][Nc]
 };
-struct GemmGroupArgs { GemmProblem p[GEMM_GROUP_MAX]; int n, tiles; };
+// parts > 1: that many workgroups per tile take k_part of the contraction each.
+struct GemmGroupArgs { GemmProblem p[GEMM_GROUP_MAX]; int n, tiles, parts, k_part; };
 
 // Up to four contractions in one launch, all with the contraction index contiguous (K-major: C = A[Mr, K] B[Nc, K]^T + bias)
 // or all with it outermost (K-minor: C = A[K, Mr]^T B[K, Nc]); operands fp32 or bf16, C and bias fp32.  Leading dimensions,
@@ -18,7 +22,19 @@ struct GemmGroupArgs { GemmProblem p[GEMM_GROUP_MAX]; int n, tiles; };
 struct GemmGroup {
     GemmGroupArgs a{};
     bool k_minor, bf16;
-    GemmGroup(bool k_minor_, bool bf16_) : k_minor(k_minor_), bf16(bf16_) {}
+    float* part;   // scratch of part_floats (bf16, K-minor), or NULL
+    GemmGroup(bool k_minor_, bool bf16_, float* part_ = nullptr) : k_minor(k_minor_), bf16(bf16_), part(part_) {}
+    // K-minor bf16 contractions in 64 x 64 tiles are split into parts of at least PART_ROWS rows (a part takes a few us whatever its
+    // length, and one more pass adds the parts) while all parts' tiles are at most PART_TILES, what the chip holds at a time.
+    // us per launch (bf16), one part -> several: 32 inputs, 64 units, 2048 rows 23 -> 12, 8192 75 -> 13, 131072 1501 -> 34; 256 units, 8192
+    // rows 76 -> 21, 131072 1560 -> 166; 1044 inputs, 320 units, 1500 rows 21 -> 25, 8192 81 -> 67.  At least 256 / 512 / 1024 rows: 64
+    // units, 8192 rows 11.3 / 12.6 / 16.3; 320 units, 1000 rows 22 / 16 / 16.  At most 512 / 1024 / 2048 tiles: 256 units, 32768 rows 78 /
+    // 50 / 55; 320 units, 32768 rows 400 / 248 / 269.
+    static constexpr int PART_ROWS = 512, PART_TILES = 1024;
+    // Bound of the scratch for contractions over K rows of up to `outputs` results per launch.
+    static size_t part_floats(size_t outputs, int K) {
+        return K < 2 * PART_ROWS ? 0 : std::min((size_t)PART_TILES * 64 * 64, outputs * (K / PART_ROWS));
+    }
     // Whether all arrays are within the kernels' 32-bit byte offsets.
     bool fits(int lda, int ldb, int ldc, int Mr, int Nc, int K) const {
         const size_t rowsA = k_minor ? K : Mr, rowsB = k_minor ? K : Nc, es = bf16 ? 2 : 4, lim = 0x7fffffff;
@@ -28,7 +44,7 @@ struct GemmGroup {
     // False if they are not (or the launch is full): not added.
     bool add(const void* A, int lda, const void* B, int ldb, float* C, int ldc, int Mr, int Nc, int K, const float* bias, int unperm_h) {
         if (a.n >= GEMM_GROUP_MAX || !fits(lda, ldb, ldc, Mr, Nc, K)) return false;
-        a.p[a.n++] = GemmProblem{A, B, C, bias, lda, ldb, ldc, Mr, Nc, K, unperm_h, 0, 0};
+        a.p[a.n++] = GemmProblem{A, B, C, bias, lda, ldb, ldc, Mr, Nc, K, unperm_h, 0, 0, nullptr};
         return true;
     }
     // Tiles of TM rows and TN columns: numbers the tiles of all problems and returns how many there are.

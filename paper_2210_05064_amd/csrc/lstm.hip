@@ -374,7 +374,7 @@ struct LstmWs {
     float* dc_state;   // [M, H]
     float* part;       // partial sums of the two-stage reductions
     float* part_b;     // [row blocks][64]: the heads' bias gradients per row block
-    float* gemm_part;  // partial tiles of the general contraction kernel (gemm.h), where a call's arrays need it
+    float* gemm_part;  // partial results of split contractions
     bf16_t* x_op;      // [M, input_dim]: fp32 input rows of a bf16 call in the operand type
     char* ring;        // [8 groups] exchange rings of the time loops (lstm_few.h)
     float* db_part;    // [2][8][4H]: per layer of a launch and group, the sum of the gate gradients over the group's rows
@@ -386,7 +386,7 @@ inline size_t part_floats(const ver_lstm_cfg& c, int M) {
     return rb_heads * (c.act_dim + 1) * c.hidden;   // the row-block partial sums of the heads' weight gradient
 }
 
-// Largest scratch that the general kernel asks for in any contraction of the forward or backward pass.
+// Largest scratch that any contraction of the forward or backward pass asks for: partial results of a contraction that is split.
 inline size_t gemm_part_max(const ver_lstm_cfg& c, int M) {
     const int bk = c.compute ? GemmGeom<MODE_BF16>::BK : GemmGeom<MODE_F32>::BK, H4 = 4 * c.hidden;
     const GemmGroup rows(false, c.compute != 0), dw(true, c.compute != 0);
@@ -398,6 +398,7 @@ inline size_t gemm_part_max(const ver_lstm_cfg& c, int M) {
         for (int n : {D, c.hidden})
             if (!dw.fits(H4, n, n, H4, n, M)) m = std::max(m, gemm_part_floats(H4, n, M, bk));
     }
+    if (c.compute) m = std::max(m, GemmGroup::part_floats((size_t)H4 * (std::max(c.input_dim, c.hidden) + (size_t)c.hidden * (c.n_layers >= 2 ? 3 : 1)), M));
     return m;
 }
 
@@ -751,7 +752,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         } } while (0)
     // Everything of layer l that is not the time loop: dx (optional), dW_ih, dW_hh, db.  A pair's upper layer comes first
     // and leaves its weight gradients and bias sums to the launches of the lower one (last = false).
-    GemmGroup dw(true, MODE == MODE_BF16);
+    GemmGroup dw(true, MODE == MODE_BF16, ws.gemm_part);
     auto layer_grads = [&](int l, float* dx, bool in_pair, bool last) {
         const int D = l == 0 ? c.input_dim : H;
         LayerWs& L = ws.layer[l];

@@ -208,6 +208,13 @@ def test_bf16_contractions(ver, rows, hidden, input_dim, layers, x_bf16):
                         p_done=0.05, minibatches=1), seed=rows, compute=1, x_bf16=x_bf16)
 
 
+@pytest.mark.parametrize("rows,hidden,input_dim,layers", [(1023, 64, 36, 1), (1024, 64, 4, 1), (1025, 64, 36, 2), (1600, 128, 132, 1), (2100, 64, 260, 3)])
+def test_bf16_weight_gradients_in_parts(ver, rows, hidden, input_dim, layers):
+    """Weight gradients of few tiles are split over the rows from 1024 rows on: one part, two and more, the last one shorter."""
+    case(ver, wl.scaled(wl.WORKLOADS["manip"], budget=rows, n_envs=rows // 20, hidden=hidden, input_dim=input_dim, n_layers=layers,
+                        p_done=0.05, minibatches=1), seed=rows, compute=1, x_bf16=True)
+
+
 @pytest.mark.parametrize("rows,hidden,act_dim", [(31, 64, 1), (32, 64, 15), (33, 128, 16), (65, 320, 47), (130, 64, 63)])
 def test_head_gradients(ver, rows, hidden, act_dim):
     """Row blocks of the heads' weight gradients at their edges; head counts at the edges of the 16-row products."""
