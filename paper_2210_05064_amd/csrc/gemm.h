@@ -148,7 +148,8 @@ __device__ __forceinline__ void tile_store(const TileRegs<MODE>& regs, typename 
 template <int MODE, bool TRANS>
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(
     const typename LdsElem<MODE>::type* __restrict__ A, int lda, const typename LdsElem<MODE>::type* __restrict__ B, int ldb,
-    float* __restrict__ C, int ldc, int Mr, int Nc, int K, const float* __restrict__ bias, int unperm_h, int k_chunk, size_t split_stride) {
+    float* __restrict__ C, int ldc, int Mr, int Nc, int K, const float* __restrict__ bias, int unperm_h, int k_chunk, size_t split_stride, const int* __restrict__ alone) {
+    if (alone && *alone == 0) return;   // (gemm_group.h)
     typedef typename LdsElem<MODE>::type E;
     constexpr int BK = GemmGeom<MODE>::BK, STRIDE = GemmGeom<MODE>::LDS_STRIDE;
     __shared__ __attribute__((aligned(16))) E sA[GEMM_BM * STRIDE];
@@ -238,7 +239,8 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(
 // C[perm(m)][n] = sum_z part[z][m][n] (+ bias[n]), z ascending.
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restrict__ part, int splits, size_t split_stride,
                                                           int Mr, int Nc, float* __restrict__ C, int ldc,
-                                                          const float* __restrict__ bias, int unperm_h) {
+                                                          const float* __restrict__ bias, int unperm_h, const int* __restrict__ alone) {
+    if (alone && *alone == 0) return;
     const size_t total = (size_t)Mr * Nc;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
         const int m = (int)(i / Nc), n = (int)(i % Nc);
@@ -625,18 +627,18 @@ inline size_t gemm_part_floats(int Mr, int Nc, int K, int BK) {
 // part: scratch of gemm_part_floats(...) floats.
 template <int MODE, bool TRANS>
 inline void gemm_launch(const typename LdsElem<MODE>::type* A, int lda, const typename LdsElem<MODE>::type* B, int ldb, float* C, int ldc, int Mr,
-                        int Nc, int K, const float* bias, int unperm_h, float* part, hipStream_t s) {
+                        int Nc, int K, const float* bias, int unperm_h, float* part, const int* alone, hipStream_t s) {
     constexpr int BK = GemmGeom<MODE>::BK;
     const int splits = gemm_splits(Mr, Nc, K, BK);
     const dim3 grid((Nc + GEMM_BN - 1) / GEMM_BN, (Mr + GEMM_BM - 1) / GEMM_BM, splits);
     if (splits == 1) {
-        hipLaunchKernelGGL((gemm_kernel<MODE, TRANS>), grid, dim3(GEMM_THREADS), 0, s, A, lda, B, ldb, C, ldc, Mr, Nc, K, bias, unperm_h, K, (size_t)0);
+        hipLaunchKernelGGL((gemm_kernel<MODE, TRANS>), grid, dim3(GEMM_THREADS), 0, s, A, lda, B, ldb, C, ldc, Mr, Nc, K, bias, unperm_h, K, (size_t)0, alone);
         return;
     }
     const int k_chunk = ((K + splits - 1) / splits + BK - 1) / BK * BK;
     const size_t stride = (size_t)Mr * Nc;
-    hipLaunchKernelGGL((gemm_kernel<MODE, TRANS>), grid, dim3(GEMM_THREADS), 0, s, A, lda, B, ldb, part, Nc, Mr, Nc, K, bias, unperm_h, k_chunk, stride);
-    hipLaunchKernelGGL(gemm_reduce_kernel, dim3(1024), dim3(256), 0, s, part, splits, stride, Mr, Nc, C, ldc, bias, unperm_h);
+    hipLaunchKernelGGL((gemm_kernel<MODE, TRANS>), grid, dim3(GEMM_THREADS), 0, s, A, lda, B, ldb, part, Nc, Mr, Nc, K, bias, unperm_h, k_chunk, stride, alone);
+    hipLaunchKernelGGL(gemm_reduce_kernel, dim3(1024), dim3(256), 0, s, part, splits, stride, Mr, Nc, C, ldc, bias, unperm_h, alone);
 }
 
 }  // namespace ver

@@ -166,7 +166,7 @@ __device__ __forceinline__ void tile(const GemmProblem& q, int t, unsigned char*
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmGroupArgs g) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[STAGES * STAGE];
     const int t = group_tile(g.tiles);
-    if (t < 0) return;
+    if (t < 0 || (g.alone && *g.alone == 0)) return;
     const GemmProblem q = group_problem(g, t);
     tile<false>(q, t - q.tile_first, smem);
 }
@@ -219,7 +219,7 @@ constexpr int LT = 256, L_THREADS = 512, L_OPERAND = LT * BK * 2, L_STAGE = 2 * 
 __global__ __launch_bounds__(L_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_large_kernel(GemmGroupArgs g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_l[];
     const int t = group_tile(g.tiles);
-    if (t < 0) return;
+    if (t < 0 || (g.alone && *g.alone == 0)) return;
     const GemmProblem& q = g.p[0];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lk = lane >> 4;

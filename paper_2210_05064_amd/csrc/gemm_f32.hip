@@ -205,7 +205,7 @@ template <int T, bool KMIN>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmGroupArgs g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int t = group_tile(g.tiles);
-    if (t < 0) return;
+    if (t < 0 || (g.alone && *g.alone == 0)) return;
     const GemmProblem q = group_problem(g, t);
     tile<T, KMIN>(q, t - q.tile_first, smem);
 }

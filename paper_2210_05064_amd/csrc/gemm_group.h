@@ -14,7 +14,8 @@ struct GemmProblem {
     float* part;               // parts > 1: [parts][Mr][Nc]
 };
 // parts > 1: that many workgroups per tile take k_part of the contraction each.
-struct GemmGroupArgs { GemmProblem p[GEMM_GROUP_MAX]; int n, tiles, parts, k_part; };
+// alone: the launch does nothing if it points to a zero (lstm_pipe.h: PLAN_ALONE); NULL: it always runs.
+struct GemmGroupArgs { GemmProblem p[GEMM_GROUP_MAX]; int n, tiles, parts, k_part; const int* alone; };
 
 // Up to four contractions in one launch, all with the contraction index contiguous (K-major: C = A[Mr, K] B[Nc, K]^T + bias)
 // or all with it outermost (K-minor: C = A[K, Mr]^T B[K, Nc]); operands fp32 or bf16, C and bias fp32.  Leading dimensions,

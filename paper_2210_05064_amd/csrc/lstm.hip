@@ -55,7 +55,8 @@ __device__ __forceinline__ void convert_rows(const float* __restrict__ src, E* _
         st4(dst + (size_t)i * 4, v[0], v[1], v[2], v[3]);
     }
 }
-__global__ __launch_bounds__(256) void convert_rows_kernel(const float* __restrict__ src, bf16_t* __restrict__ dst, unsigned quads) {
+__global__ __launch_bounds__(256) void convert_rows_kernel(const float* __restrict__ src, bf16_t* __restrict__ dst, unsigned quads, const int* __restrict__ alone) {
+    if (alone && *alone == 0) return;   // (lstm_pipe.h: PLAN_ALONE)
     convert_rows(src, dst, quads, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
 }
 constexpr size_t PREP_TILE_FLOATS = 64 * 65;
@@ -319,21 +320,23 @@ struct BiasFinalArgs {
     const float* part; size_t part_stride;
     float* out[2]; float* out2[2];
     int n_rb, H, sets;
+    const int* alone;   // points to anything but a zero: the time loops had all groups, n_rb is REC_GROUPS (NULL: as given)
 };
 __device__ __forceinline__ void bias_final_block(const BiasFinalArgs& q, int bx, int set) {
+    const int n_rb = q.alone && *q.alone != 0 ? REC_GROUPS : q.n_rb;
     const int c = bx * 256 + threadIdx.x, cols = 4 * q.H;
     if (c >= cols) return;
     const float* part = q.part + (set == 1 ? q.part_stride : 0);
     float s = 0.f;
     int rb = 0;
-    for (; rb + 8 <= q.n_rb; rb += 8) {   // 8 loads in flight, added in index order
+    for (; rb + 8 <= n_rb; rb += 8) {   // 8 loads in flight, added in index order
         float v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = part[(size_t)(rb + u) * cols + c];
 #pragma unroll
         for (int u = 0; u < 8; ++u) s += v[u];
     }
-    for (; rb < q.n_rb; ++rb) s += part[(size_t)rb * cols + c];
+    for (; rb < n_rb; ++rb) s += part[(size_t)rb * cols + c];
     const int dst = (c & 3) * q.H + (c >> 2);
     (set == 1 ? q.out[1] : q.out[0])[dst] = s;
     (set == 1 ? q.out2[1] : q.out2[0])[dst] = s;
@@ -357,11 +360,12 @@ struct LayerWs {
     float* c;     // [M, H]
     float* hout;  // [M, H]
     void* hprev;  // [M, H] operand type
-    void* hcopy;  // [M, H] operand type: h_t, for what contracts it: the workers of a two-layer launch (lower layer of a pair), in bf16 also the layer above
+    void* hcopy;  // [M, H] operand type: h_t, for what contracts it: the layer above, in a two-layer launch its workers (fp32: hout itself)
 };
 struct LstmWs {
     int* err;          // word 0 of the workspace
     int* flags;        // [REC_FLAG_WORDS]: per-workgroup flags of a recurrent launch, then its ticket counters
+    int* flags_alone;  // [REC_FLAG_WORDS]: the same for a second launch behind the same clearing (may_run_alone)
     long long* prof;   // [128] phase counters of the recurrent kernels (forward 0..15, backward 16..31; +32: consumer layer), timeline, workers
     LayerWs layer[8];
     void* dz[2];       // [M, 4H] operand type; the second one only when two layers share a launch
@@ -409,6 +413,7 @@ inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws)
     int* head = cv.take<int>(64);
     ws->err = head;
     ws->flags = cv.take<int>(REC_FLAG_WORDS);
+    ws->flags_alone = cv.take<int>(REC_FLAG_WORDS);
     ws->prof = cv.take<long long>(128);
     // the hand-over words sit right behind, so that one fill clears everything a launch needs cleared
     ws->pipe_words = pipe_sync_words(M);
@@ -428,7 +433,7 @@ inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws)
         L.c = cv.take<float>(Mz * H);
         L.hout = cv.take<float>(Mz * H);
         L.hprev = cv.take<char>(Mz * H * es);
-        L.hcopy = (l + 1 < c.n_layers && (c.compute || l % 2 == 0)) ? cv.take<char>(Mz * H * es) : nullptr;
+        L.hcopy = l + 1 == c.n_layers ? nullptr : (c.compute ? static_cast<void*>(cv.take<char>(Mz * H * es)) : L.hout);
     }
     ws->dz[0] = cv.take<char>(Mz * 4 * H * es);
     ws->dz[1] = c.n_layers >= 2 ? cv.take<char>(Mz * 4 * H * es) : ws->dz[0];
@@ -478,17 +483,18 @@ inline bool set_lds(K kernel, size_t bytes) {
 // (45 and 28 us at K = 1044).  What lies beyond the 32-bit byte offsets of these kernels (only rows of the caller's can) goes
 // to the general kernel.
 template <int MODE>
-inline int contract_rows(const typename RecGeom<MODE>::E* A, const typename RecGeom<MODE>::E* B, float* C, const float* bias, int M, int N, int K, float* part, hipStream_t s) {
+inline int contract_rows(const typename RecGeom<MODE>::E* A, const typename RecGeom<MODE>::E* B, float* C, const float* bias, int M, int N, int K, float* part, hipStream_t s, const int* alone = nullptr) {
     GemmGroup g(false, MODE == MODE_BF16);
+    g.a.alone = alone;
     if (!g.add(A, K, B, K, C, N, M, N, K, bias, 0)) {
-        gemm_launch<MODE, false>(A, K, B, K, C, N, M, N, K, bias, 0, part, s);
+        gemm_launch<MODE, false>(A, K, B, K, C, N, M, N, K, bias, 0, part, alone, s);
         return VER_OK;
     }
     if (MODE == MODE_BF16 && g.lay_out(64) > 4 * REC_GRID) {
         auto rounds = [](int tiles) { return (tiles + REC_GRID - 1) / REC_GRID; };
         if (8 * rounds(g.lay_out(GemmGroup::LARGE_TILE)) <= 5 * rounds(g.lay_out(PIPE_BM, PIPE_BN))) return g.launch_large(s) ? VER_OK : VER_EHIP;
         if (!set_lds(lstm_proj_dma_kernel, (size_t)PIPE_STAGES * PIPE_STAGE_BYTES)) return VER_EHIP;
-        const ProjWork pw = {A, B, C, bias, K, N, M};
+        const ProjWork pw = {A, B, C, bias, K, N, M, alone};
         const int tiles_n = (N + PIPE_BN - 1) / PIPE_BN, tiles_m = (M + PIPE_BM - 1) / PIPE_BM;
         hipLaunchKernelGGL(lstm_proj_dma_kernel, dim3(tiles_m * tiles_n), dim3(REC_THREADS), (size_t)PIPE_STAGES * PIPE_STAGE_BYTES, s,
                            pw, tiles_n);
@@ -518,19 +524,13 @@ inline int device_fits_time_loops() {
     return known[dev] > 0 ? VER_OK : VER_EUNSUPPORTED;
 }
 
-// What the first launch of the forward pass does for the two-layer launches: zeroes the flags, ticket counters, hand-over words
-// and the sticky time-out word at the start of the workspace, and writes the plans of both launches of the minibatch (the
-// backward call runs on the packing of the forward call whose activations it finds in the workspace).
-inline PlanArgs pipe_plan(const LstmWs& ws, int mode, bool wide, int G, int M, const int32_t* info, const int32_t* batch_sizes) {
-    return PlanArgs{info, batch_sizes, M, ws.plan[0], ws.plan[1], ws.plan_scratch, ws.err, (int)(ws.pipe + ws.pipe_words - ws.err),
-                    plan_cost(mode, wide, true, G), plan_cost(mode, wide, false, G)};
-}
-inline void pipe_work(const LstmWs& ws, int dir, int M, const int32_t* t_off, PipeWork* pw) {
+inline void pipe_work(const LstmWs& ws, int dir, int M, const int32_t* t_off, const int* alone, PipeWork* pw) {
     pw->M = M;
     pw->t_off = t_off;
     pw->plan = ws.plan[dir];
     pw->sync = ws.pipe;
     pw->err = ws.err;
+    pw->alone = alone;
 }
 
 // Networks of several layers run two layers at a time in one launch each (lstm_pipe.h), the layers numbered 2i and 2i + 1;
@@ -540,14 +540,39 @@ inline void pipe_work(const LstmWs& ws, int dir, int M, const int32_t* t_off, Pi
 // hundreds of short pieces keep every XCD busy: 8192 rows in 538 pieces (86) at 320 units 1121 -> 1103.  Three layers of 320 on
 // 3001 rows in 36 pieces (bf16): 2430 -> 1843 us.
 inline bool pairs_of_layers(const ver_lstm_cfg& c) { return c.n_layers >= 2 && !c.layer_by_layer; }
+// From three layers on a pair's launch is for minibatches of few alive pieces per timestep (rows / timesteps): many are bound by
+// throughput, of which three XCDs per layer have less than eight for one layer after the other (and finding the cuts for
+// thousands of pieces takes milliseconds).  Only the device knows the timesteps: both forms are launched, and what the plan has
+// not chosen does nothing (15 us in all; up to PAIRS_ROWS rows the pairs are launched alone, which then take less in any
+// packing than a launch per layer did before the contractions were made faster).
+constexpr int PAIRS_ROWS = 768;
+inline bool may_run_alone(const ver_lstm_cfg& c, int M) { return c.n_layers > 2 && pairs_of_layers(c) && M > PAIRS_ROWS; }
+// The lines, by alive pieces (timesteps): us per forward and backward pass of three layers, pairs / a launch per layer: bf16, 320 units
+// 35 (29) 423 / 440, 51 (59) 782 / 787, 70 (117) 1675 / 1642, 76 (27) 562 / 512, 104 (29) 763 / 607, 910 (36) 8807 / 3677; fp32, 256
+// units 44 (68) 1027 / 1106, 70 (117) 2197 / 2263, 76 (27) 733 / 651; from 384 units on, where the workers hold the weights twice at
+// most, 512 units 20 (51) 866 / 931, 24 (21) 533 / 514, 28 (36) 791 / 792, 35 (29) 847 / 766, 44 (68) 1808 / 1805, 51 (59) 1818 / 1693, 70 (117)
+// 4177 / 3976.
+inline void pair_lines(const ver_lstm_cfg& c, int M, PlanArgs* p) {
+    const bool low = !c.compute && c.hidden > 320;
+    p->base = low ? 12 : 45; p->per = low ? 2 : 4; p->most = may_run_alone(c, M) ? (low ? 60 : 80) : 0;
+}
 
-// The rows that layer l contracts, in the operand type.  (fp32: the lower layer of a pair leaves its h in hcopy only.)
+// What the first launch of the forward pass does for the two-layer launches: zeroes the flags, ticket counters, hand-over words
+// and the sticky time-out word at the start of the workspace, and writes the plans of both launches of the minibatch (the
+// backward call runs on the packing of the forward call whose activations it finds in the workspace).
+inline PlanArgs pipe_plan(const LstmWs& ws, int mode, bool wide, int G, int M, const int32_t* info, const int32_t* batch_sizes, const ver_lstm_cfg& c) {
+    PlanArgs p{info, batch_sizes, M, ws.plan[0], ws.plan[1], ws.plan_scratch, ws.err, (int)(ws.pipe + ws.pipe_words - ws.err),
+                    plan_cost(mode, wide, true, G), plan_cost(mode, wide, false, G), 0, 0, 0};
+    pair_lines(c, M, &p);
+    return p;
+}
+
+// The rows that layer l contracts, in the operand type.
 template <int MODE>
 inline const typename RecGeom<MODE>::E* layer_input(const ver_lstm_cfg& c, const LstmWs& ws, const void* x, int l) {
     typedef const typename RecGeom<MODE>::E* rows_t;
     if (l == 0) return ws.x_op ? reinterpret_cast<rows_t>(ws.x_op) : static_cast<rows_t>(x);
-    const bool copied = MODE == MODE_BF16 || (l % 2 == 1 && pairs_of_layers(c));
-    return copied ? static_cast<rows_t>(ws.layer[l - 1].hcopy) : reinterpret_cast<rows_t>(ws.layer[l - 1].hout);
+    return static_cast<rows_t>(ws.layer[l - 1].hcopy);
 }
 
 template <int MODE>
@@ -595,18 +620,18 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         if (ws.x_op) pa.job[n++] = PrepJob{static_cast<const float*>(x), nullptr, ws.x_op, nullptr, PREP_ROWS, (unsigned)((size_t)M * c.input_dim / 4)};
         // without a pair, also the time-out word and the flags of the first time loop (else: the plan clears them)
         if (!pairs) pa.job[n++] = PrepJob{nullptr, nullptr, ws.err, nullptr, PREP_CLEAR, (unsigned)(ws.flags + REC_FLAG_WORDS - ws.err)};
-        const PlanArgs plan = pairs ? pipe_plan(ws, MODE, wide, H / (4 * mt), M, info, batch_sizes) : PlanArgs{};
+        const PlanArgs plan = pairs ? pipe_plan(ws, MODE, wide, H / (4 * mt), M, info, batch_sizes, c) : PlanArgs{};
         if (!set_lds(prep_weights_kernel<E>, prep_lds_bytes())) return false;
         hipLaunchKernelGGL(prep_weights_kernel<E>, dim3((max_cols + 64 * PREP_TILES - 1) / (64 * PREP_TILES), 4 * H / 64, n + (pairs ? 1 : 0)),
                            dim3(PREP_THREADS), prep_lds_bytes(), s, pa, H, plan);
         return true;
     };
     // time-batched input projection: gates[M, 4H] = x W_ih^T + (b_ih + b_hh), interleaved columns
-    auto project = [&](int l) {
+    auto project = [&](int l, const int* alone = nullptr) {
         const int D = l == 0 ? c.input_dim : H;
         LayerWs& L = ws.layer[l];
         ProfScope prof(VER_PROF_LSTM_GEMM_FWD, s);
-        return contract_rows<MODE>(layer_input<MODE>(c, ws, x, l), static_cast<const E*>(L.wih), L.gates, L.bias, M, 4 * H, D, ws.gemm_part, s) == VER_OK;
+        return contract_rows<MODE>(layer_input<MODE>(c, ws, x, l), static_cast<const E*>(L.wih), L.gates, L.bias, M, 4 * H, D, ws.gemm_part, s, alone) == VER_OK;
     };
     auto rec_args = [&](int l, bool consumer = false) {
         LayerWs& L = ws.layer[l];
@@ -618,7 +643,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         ra.c0 = c0 ? c0 + (size_t)l * seq_cap * H : nullptr;
         ra.H = H; ra.seq_cap = seq_cap; ra.M = M; ra.flags = ws.flags; ra.ticket = ws.flags + 8 * REC_MAX_GROUP;
         ra.err = ws.err; ra.prof = ws.prof + (consumer ? 32 : 0); ra.prof_all = ws.prof;
-        ra.G = H / (4 * mt); ra.ntc = ntc;
+        ra.G = H / (4 * mt); ra.ntc = ntc; ra.alone = nullptr;
         return ra;
     };
     bool ok = true;
@@ -640,36 +665,51 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             else VER_FWD_LAUNCH(KERNEL, ARGS, 2, 4, 8, false); \
         } } while (0)
 
+    // The time loop of one layer in a launch of its own.
+    auto loop_alone = [&](int l, int* flags, const int* alone) {
+        RecFwdArgs ra = rec_args(l);
+        ra.flags = flags; ra.ticket = flags + 8 * REC_MAX_GROUP; ra.alone = alone;
+        ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
+        VER_FWD_DISPATCH(lstm_rec_fwd_kernel, ra);
+        return ok;
+    };
+    // bf16: what the layer above layer l contracts (a two-layer launch writes that of its lower layer itself)
+    auto copy_h = [&](int l, const int* alone) {
+        if constexpr (MODE == MODE_BF16) {
+            const unsigned quads = (unsigned)((size_t)M * H / 4);
+            hipLaunchKernelGGL(convert_rows_kernel, dim3((quads + 1023) / 1024), dim3(256), 0, s, ws.layer[l].hout,
+                               static_cast<bf16_t*>(ws.layer[l].hcopy), quads, alone);
+        }
+    };
     if (!prep_all()) return VER_EHIP;
+    const int* alone = may_run_alone(c, M) ? ws.plan[0] + PLAN_ALONE : nullptr;
     for (int l = 0; l < c.n_layers;) {
         if (!project(l)) return VER_EHIP;
         if (pairs && l + 1 < c.n_layers) {
             // (the plan, of the packing, is the same for every pair)
             if (l > 0) fill_words(ws.flags, (size_t)(ws.pipe + ws.pipe_words - ws.flags), 0, s);
+            if (alone) {   // the same two layers one after the other; where they do nothing they leave the words as they are
+                if (!loop_alone(l, ws.flags, alone)) return VER_EHIP;
+                copy_h(l, alone);
+                if (!project(l + 1, alone) || !loop_alone(l + 1, ws.flags_alone, alone)) return VER_EHIP;
+            }
             PipeFwdArgs pa;
             pa.l0 = rec_args(l);
             pa.l1 = rec_args(l + 1, true);
             pa.work.A = ws.layer[l].hcopy; pa.work.B = ws.layer[l + 1].wih; pa.work.C = ws.layer[l + 1].gates;
             pa.work.bias = ws.layer[l + 1].bias; pa.work.K = H; pa.work.N = 4 * H;
-            pipe_work(ws, 0, M, t_off, &pa.work);
+            pipe_work(ws, 0, M, t_off, alone, &pa.work);
             pa.work.G = pa.l0.G;
             ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
             VER_FWD_DISPATCH(lstm_pipe_fwd_kernel, pa);
+            if (!ok) return VER_EHIP;
             l += 2;
         } else {
             if (l > 0) fill_words(ws.flags, REC_FLAG_WORDS, 0, s);
-            RecFwdArgs ra = rec_args(l);
-            ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
-            VER_FWD_DISPATCH(lstm_rec_fwd_kernel, ra);
+            if (!loop_alone(l, ws.flags, nullptr)) return VER_EHIP;
             l += 1;
         }
-        if (!ok) return VER_EHIP;
-        if constexpr (MODE == MODE_BF16)   // the layer above contracts this layer's h
-            if (l < c.n_layers) {
-                const unsigned quads = (unsigned)((size_t)M * H / 4);
-                hipLaunchKernelGGL(convert_rows_kernel, dim3((quads + 1023) / 1024), dim3(256), 0, s, ws.layer[l - 1].hout,
-                                   static_cast<bf16_t*>(ws.layer[l - 1].hcopy), quads);
-            }
+        if (l < c.n_layers) copy_h(l - 1, nullptr);
     }
 #undef VER_FWD_DISPATCH
 #undef VER_FWD_LAUNCH
@@ -733,7 +773,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         ra.db_part = ws.db_part + (size_t)half(l) * REC_GROUPS * 4 * H;
         ra.H = H; ra.seq_cap = seq_cap; ra.flags = ws.flags; ra.ticket = ws.flags + 8 * REC_MAX_GROUP;
         ra.err = ws.err; ra.prof = ws.prof + 16 + (consumer ? 32 : 0); ra.prof_all = ws.prof;
-        ra.G = H / (16 * mt); ra.ntc = ntc;
+        ra.G = H / (16 * mt); ra.ntc = ntc; ra.alone = nullptr;
         return ra;
     };
     bool ok = true;
@@ -750,6 +790,20 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             else if (ni == 4) VER_BWD_LAUNCH(KERNEL, ARGS, 1, 8, 4); \
             else VER_BWD_LAUNCH(KERNEL, ARGS, 1, 8, 0); \
         } } while (0)
+    auto loop_alone = [&](int l, const float* dh_above, int* flags, const int* alone) {
+        RecBwdArgs ra = rec_args(l, dh_above);
+        ra.flags = flags; ra.ticket = flags + 8 * REC_MAX_GROUP; ra.alone = alone;
+        ProfScope prof(VER_PROF_LSTM_REC_BWD, s);
+        VER_BWD_DISPATCH(lstm_rec_bwd_kernel, ra);
+        return ok;
+    };
+    // gradient w.r.t. the layer input: dx[M, D] = dz[M, 4H] . W_ih[4H, D]
+    auto input_grad = [&](int l, float* dx, const int* alone) {
+        ProfScope prof(VER_PROF_LSTM_GEMM_DX, s);
+        ok = contract_rows<MODE>(static_cast<const E*>(dz_of(l)), static_cast<const E*>(ws.layer[l].wihT), dx, nullptr, M, l == 0 ? c.input_dim : H, 4 * H,
+                                 ws.gemm_part, s, alone) == VER_OK;
+    };
+    const int* alone = may_run_alone(c, M) ? ws.plan[1] + PLAN_ALONE : nullptr;
     // Everything of layer l that is not the time loop: dx (optional), dW_ih, dW_hh, db.  A pair's upper layer comes first
     // and leaves its weight gradients and bias sums to the launches of the lower one (last = false).
     GemmGroup dw(true, MODE == MODE_BF16, ws.gemm_part);
@@ -757,18 +811,14 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         const int D = l == 0 ? c.input_dim : H;
         LayerWs& L = ws.layer[l];
         const E* dz = static_cast<const E*>(dz_of(l));
-        // gradient w.r.t. the layer input: dx[M, D] = dz[M, 4H] . W_ih[4H, D]
-        if (dx) {
-            ProfScope prof(VER_PROF_LSTM_GEMM_DX, s);
-            ok = contract_rows<MODE>(dz, static_cast<const E*>(L.wihT), dx, nullptr, M, D, 4 * H, ws.gemm_part, s) == VER_OK;
-        }
+        if (dx) input_grad(l, dx, nullptr);
         // dW_ih[4H, D] = dz^T x ; dW_hh[4H, H] = dz^T h_{t-1}; stored gate-major.  The contractions of a layer or pair leave in
         // one launch.
         {
         ProfScope prof(VER_PROF_LSTM_GEMM_DW, s);
         auto contract = [&](const E* B, float* C, int Nc) {
             if (!dw.add(dz, 4 * H, B, Nc, C, Nc, 4 * H, Nc, M, nullptr, H))
-                gemm_launch<MODE, true>(dz, 4 * H, B, Nc, C, Nc, 4 * H, Nc, M, nullptr, H, ws.gemm_part, s);
+                gemm_launch<MODE, true>(dz, 4 * H, B, Nc, C, Nc, 4 * H, Nc, M, nullptr, H, ws.gemm_part, nullptr, s);
         };
         contract(layer_input<MODE>(c, ws, x, l), gw[4 * l], D);
         contract(static_cast<const E*>(L.hprev), gw[4 * l + 1], H);
@@ -780,7 +830,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         ProfScope prof(VER_PROF_LSTM_DBIAS, s);
         float* const* g = gw + 4 * l;
         const BiasFinalArgs bf{ws.db_part, (size_t)REC_GROUPS * 4 * H, {g[2], in_pair ? g[6] : nullptr}, {g[3], in_pair ? g[7] : nullptr},
-                               in_pair ? PIPE_GROUPS : REC_GROUPS, H, in_pair ? 2 : 1};
+                               in_pair ? PIPE_GROUPS : REC_GROUPS, H, in_pair ? 2 : 1, in_pair ? alone : nullptr};
         const bool heads = l + (in_pair ? 2 : 1) == nl;
         hipLaunchKernelGGL(grads_final_kernel, dim3(std::max((4 * H + 255) / 256, (H + HF_COLS - 1) / HF_COLS), bf.sets + (heads ? A + 1 : 0)),
                            dim3(256), 0, s, bf, hf);
@@ -791,12 +841,17 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     for (int l = nl - 1; l >= 0;) {
         if (pairs && l % 2 == 1) {
             if (l != nl - 1) fill_words(ws.flags, (size_t)(ws.pipe + ws.pipe_words - ws.flags), 0, s);   // (the top layers': heads_bwd_kernel)
+            if (alone) {   // (as in the forward pass)
+                if (!loop_alone(l, ws.dh[cur], ws.flags, alone)) return VER_EHIP;
+                input_grad(l, ws.dh[cur ^ 1], alone);
+                if (!ok || !loop_alone(l - 1, ws.dh[cur ^ 1], ws.flags_alone, alone)) return VER_EHIP;
+            }
             PipeBwdArgs pa;
             pa.l1 = rec_args(l, ws.dh[cur]);
             pa.l0 = rec_args(l - 1, ws.dh[cur ^ 1], true);
             pa.work.A = ws.dz[1]; pa.work.B = ws.layer[l].wihT; pa.work.C = ws.dh[cur ^ 1]; pa.work.bias = nullptr;
             pa.work.K = 4 * H; pa.work.N = H;
-            pipe_work(ws, 1, M, t_off, &pa.work);
+            pipe_work(ws, 1, M, t_off, alone, &pa.work);
             pa.work.G = pa.l1.G;
             {
             ProfScope prof(VER_PROF_LSTM_REC_BWD, s);
@@ -809,12 +864,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             l -= 2;
         } else {
             if (l != nl - 1) fill_words(ws.flags, REC_FLAG_WORDS, 0, s);
-            RecBwdArgs ra = rec_args(l, ws.dh[cur]);
-            {
-            ProfScope prof(VER_PROF_LSTM_REC_BWD, s);
-            VER_BWD_DISPATCH(lstm_rec_bwd_kernel, ra);
-            if (!ok) return VER_EHIP;
-            }
+            if (!loop_alone(l, ws.dh[cur], ws.flags, nullptr)) return VER_EHIP;
             layer_grads(l, l > 0 ? ws.dh[cur ^ 1] : d_x, false, true);
             if (!ok) return VER_EHIP;
             cur ^= 1;

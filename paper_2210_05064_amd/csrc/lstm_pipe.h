@@ -42,6 +42,7 @@ static_assert(PIPE_XCDS - 2 * PIPE_GROUPS == 2, "two worker XCDs");
 
 // The plan of a launch (ints in global memory, written by plan_launches):
 constexpr int PLAN_KB = 0;           // [PIPE_GROUPS + 1] first piece of every group's block, then the number of pieces
+constexpr int PLAN_ALONE = 6;        // not 0: too many alive pieces per timestep, the layers run alone (see plan_launches)
 constexpr int PLAN_T = 8;            // [PIPE_GROUPS] timesteps of the group (those of its first piece; 0 if it has none)
 constexpr int PLAN_CT = 12;          // [PIPE_GROUPS] timesteps per chunk
 constexpr int PLAN_WORDS = 16;
@@ -101,6 +102,7 @@ struct PipeWork {
     int* sync;          // progress, done counters (see above)
     int* err;
     int G;              // workers per XCD; each owns N / G columns
+    const int* alone;   // the launch does nothing if it points to anything but a zero (NULL: it always runs)
 };
 
 constexpr int PLAN_THREADS = 1024;
@@ -240,6 +242,9 @@ struct PlanArgs {
     int* plan_fwd; int* plan_bwd; float* scratch;
     int* clear; int n_clear;
     PlanCost fwd, bwd;
+    // Two layers share a launch up to min(most, base + T / per) alive pieces per timestep (average over the T timesteps); most = 0:
+    // always.
+    int base, per, most;
 };
 struct PlanLds {
     int bs[PLAN_LDS_N];
@@ -248,6 +253,9 @@ struct PlanLds {
 __device__ __forceinline__ void plan_launches(const PlanArgs& a, PlanLds& lds) {
     const int M = a.M, n_seq = min(max(a.info[0], 0), M), T = min(max(a.info[1], 0), M);
     for (int i = threadIdx.x; i < a.n_clear; i += PLAN_THREADS) a.clear[i] = 0;
+    const bool alone = a.most > 0 && M > min(a.most, a.base + T / a.per) * T;
+    if (threadIdx.x == 0) a.plan_fwd[PLAN_ALONE] = a.plan_bwd[PLAN_ALONE] = alone ? 1 : 0;
+    if (alone) return;
     if (n_seq <= PLAN_LDS_N && T <= PLAN_LDS_N)
         plan_body<true>(a.batch_sizes, M, n_seq, T, a.plan_fwd, a.plan_bwd, a.scratch, lds.bs, lds.len, lds.S1, a.fwd, a.bwd);
     else
@@ -273,6 +281,7 @@ struct ProjWork {
     float* C;           // [M, N]
     const float* bias;  // [N] or NULL
     int K, N, M;
+    const int* alone;   // (gemm_group.h)
 };
 __device__ __forceinline__ void proj_tile_dma(const ProjWork& w, int row0, int row_end, int col0, unsigned char* smem) {
     constexpr int BK = 64;
@@ -379,6 +388,7 @@ __device__ __forceinline__ void proj_tile_dma(const ProjWork& w, int row0, int r
 // from memory by one round of workgroups.
 __global__ __launch_bounds__(REC_THREADS) void lstm_proj_dma_kernel(ProjWork w, int tiles_n) {
     extern __shared__ __attribute__((aligned(16))) unsigned char proj_smem[];
+    if (w.alone && *w.alone == 0) return;
     const int rt = blockIdx.x / tiles_n, ct = blockIdx.x % tiles_n;
     proj_tile_dma(w, rt * PIPE_BM, min(w.M, (rt + 1) * PIPE_BM), ct * PIPE_BN, proj_smem);
 }
@@ -672,6 +682,7 @@ template <int MODE, int TPW, int KS, int NBW, bool STATIC>
 __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_pipe_fwd_kernel(PipeFwdArgs p_by_value) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const PipeFwdArgs& p = pipe_args_in_place<PipeFwdArgs>(p_by_value);
+    if (p.work.alone && *p.work.alone != 0) return;
     int xcc;
     const int rank = xcc_ticket(p.l0.ticket, xcc);
     const int g = xcc < PIPE_GROUPS ? xcc : xcc - PIPE_GROUPS;
@@ -707,6 +718,7 @@ template <int MODE, int MT, int KS, int NI>
 __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_pipe_bwd_kernel(PipeBwdArgs p_by_value) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const PipeBwdArgs& p = pipe_args_in_place<PipeBwdArgs>(p_by_value);
+    if (p.work.alone && *p.work.alone != 0) return;
     int xcc;
     const int rank = xcc_ticket(p.l1.ticket, xcc);
     const int g = xcc < PIPE_GROUPS ? xcc : xcc - PIPE_GROUPS;

@@ -483,6 +483,7 @@ struct RecFwdArgs {
     int* err;
     long long* prof;    // [16] phase cycle counters (only touched by builds with VER_REC_PROF)
     long long* prof_all;   // start of the profiling words
+    const int* alone;   // a launch of its own does nothing if this points to a zero (lstm_pipe.h: PLAN_ALONE); NULL: it always runs
 };
 struct RecBwdArgs {
     const int32_t* info;
@@ -506,6 +507,7 @@ struct RecBwdArgs {
     int* err;
     long long* prof;
     long long* prof_all;
+    const int* alone;
 };
 
 }  // namespace ver
@@ -778,6 +780,7 @@ template <int MODE, int TPW, int KS, int NBW, bool STATIC>
 __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_rec_fwd_kernel(RecFwdArgs by_value) {
     const RecFwdArgs& a = pipe_args_in_place<RecFwdArgs>(by_value);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    if (a.alone && *a.alone == 0) return;   // (before a ticket is taken)
     int grp;
     const int rank = rec_rank(a.ticket, a.G, grp);
     if (rank < 0) return;
@@ -1034,6 +1037,7 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& a, int rank, cons
 template <int MODE, int MT, int KS, int NI>
 __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_rec_bwd_kernel(RecBwdArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    if (a.alone && *a.alone == 0) return;   // (before a ticket is taken)
     int grp;
     const int rank = rec_rank(a.ticket, a.G, grp);
     if (rank < 0) return;

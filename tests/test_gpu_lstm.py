@@ -469,3 +469,42 @@ def test_arrays_beyond_2_gigabytes(ver, rows, input_dim, compute):
     assert off(grads[0], W[0].grad) <= (rounded if compute else max(chain(M), tight))
     assert off(dx, x64.grad) <= (rounded if compute else tight)
     assert off(grads[2], W[2].grad) <= (rounded if compute else 1e-5) and not grads[1].any()
+
+
+def even(ver, pieces, steps, layers, compute, hidden, **kw):
+    """`pieces` pieces of `steps` timesteps each."""
+    return case(ver, wl.scaled(wl.WORKLOADS["manip"], budget=pieces * steps, n_envs=pieces, speed_sigma=0.0, hidden=hidden, input_dim=36,
+                               n_layers=layers, p_done=0.0, minibatches=1), seed=pieces + layers, compute=compute, **kw)
+
+
+@pytest.mark.parametrize("pieces,steps,layers,compute,hidden", [
+    (49, 17, 3, 1, 64), (50, 17, 3, 1, 64), (256, 3, 3, 1, 64), (257, 3, 3, 1, 64), (300, 3, 4, 1, 320), (900, 1, 5, 1, 128),
+    (50, 20, 3, 0, 256), (51, 20, 3, 0, 256), (32, 40, 3, 0, 384), (33, 40, 3, 0, 384), (400, 2, 4, 0, 64), (300, 3, 5, 0, 128)])
+def test_many_pieces_and_layers(ver, pieces, steps, layers, compute, hidden):
+    """Three layers and more share launches in pairs up to 45 + T / 4 alive pieces per timestep (fp32 beyond 320 units: 12 + T / 2) and
+    up to 768 rows; beyond, every layer runs alone: both sides of the lines, a single timestep, a pair above a pair."""
+    run, meta = even(ver, pieces, steps, layers, compute, hidden)
+    assert meta["n_seq"] == pieces and meta["T_max"] == steps
+
+
+@pytest.mark.parametrize("compute", [0, 1])
+def test_pairs_and_single_layers_in_one_workspace(ver, compute):
+    """Minibatches of few and of many pieces in turn, in the same workspace: what either form leaves there is not taken for the
+    other's.  Each as in a workspace of its own, bit for bit."""
+    runs = []
+    for pieces, steps in ((10, 80), (400, 2)):
+        w = wl.scaled(wl.WORKLOADS["manip"], budget=800, n_envs=pieces, speed_sigma=0.0, hidden=64, input_dim=36, n_layers=3, p_done=0.0, minibatches=1)
+        ro = wl.make_rollout(w, seed=5, bias_scale=0.2)
+        meta = opack.pack_minibatch(ro["dones"], ro["env_off"], ro["seq_key"][0], 1, 0, ro["env_started_episode"])
+        runs.append(LstmRun(ver, w, ro["weights"], opack.gather_rows(ro["obs"], meta["gather_idx"]), meta, compute=compute))
+    d_u, d_v = np.full((800, w.act_dim), 1.0 / 800, np.float32), np.full(800, 1.0 / 800, np.float32)
+
+    def step(run):
+        u, v = run.forward()
+        grads, dx = run.backward(d_u, d_v)
+        return [u, v, dx] + grads
+    alone = [step(run) for run in runs]
+    runs[1].ws = runs[0].ws
+    for _ in range(2):
+        for run, ref in zip(runs, alone):
+            assert all(np.array_equal(a, b) for a, b in zip(step(run), ref))
