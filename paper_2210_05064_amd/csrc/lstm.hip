@@ -44,24 +44,27 @@ struct PrepJob {
     const float* b_hh;   // (bias jobs)
     void* dst; void* dstT;
     int cols;            // > 0, PREP_BIAS, PREP_ROWS or PREP_CLEAR
-    unsigned quads;      // rows: groups of four elements; clear: words
+    size_t quads;        // rows: groups of four elements; clear: words
 };
-struct PrepArgs { PrepJob job[PREP_MAX_JOBS]; };
+struct PrepArgs { PrepJob job[PREP_MAX_JOBS]; int n; };
 // Rows converted to the operand type, four elements per thread and step.
 template <typename E>
-__device__ __forceinline__ void convert_rows(const float* __restrict__ src, E* __restrict__ dst, unsigned quads, unsigned first, unsigned stride) {
-    for (unsigned i = first; i < quads; i += stride) {
-        const f32x4_t v = *reinterpret_cast<const f32x4_t*>(src + (size_t)i * 4);
-        st4(dst + (size_t)i * 4, v[0], v[1], v[2], v[3]);
+__device__ __forceinline__ void convert_rows(const float* __restrict__ src, E* __restrict__ dst, size_t quads, size_t first, unsigned stride) {
+    for (size_t i = first; i < quads; i += stride) {
+        const f32x4_t v = *reinterpret_cast<const f32x4_t*>(src + i * 4);
+        st4(dst + i * 4, v[0], v[1], v[2], v[3]);
     }
 }
-__global__ __launch_bounds__(256) void convert_rows_kernel(const float* __restrict__ src, bf16_t* __restrict__ dst, unsigned quads, const int* __restrict__ alone) {
+__global__ __launch_bounds__(256) void convert_rows_kernel(const float* __restrict__ src, bf16_t* __restrict__ dst, size_t quads, const int* __restrict__ alone) {
     if (alone && *alone == 0) return;   // (lstm_pipe.h: PLAN_ALONE)
     convert_rows(src, dst, quads, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
 }
 constexpr size_t PREP_TILE_FLOATS = 64 * 65;
 inline size_t prep_lds_bytes() { return std::max(PREP_TILES * PREP_TILE_FLOATS * sizeof(float), sizeof(PlanLds)); }
-// blockIdx.z = 0 is the plan where there is one (plan.plan_fwd != NULL), then the jobs.
+// blockIdx.z = 0 is the plan where there is one (plan.plan_fwd != NULL), then the jobs; what is left belongs to the last job, the
+// rows where there are any: x and y are as many as the widest matrix has tiles, 20 workgroups for 64 units and 1044 inputs (us
+// per launch with those / with a workgroup per 4096 groups: 8192 rows of 1044 53 / 13, 32768 274 / 43, 400000 3500 / 590).
+constexpr size_t PREP_ROWS_QUADS = 4 * PREP_THREADS, PREP_ROWS_WGS = 512;
 template <typename E>
 __global__ __launch_bounds__(PREP_THREADS) void prep_weights_kernel(PrepArgs a, int H, PlanArgs plan) {
     extern __shared__ __attribute__((aligned(16))) unsigned char prep_smem[];
@@ -70,13 +73,16 @@ __global__ __launch_bounds__(PREP_THREADS) void prep_weights_kernel(PrepArgs a, 
         if (blockIdx.x == 0 && blockIdx.y == 0) plan_launches(plan, *reinterpret_cast<PlanLds*>(prep_smem));
         return;
     }
-    const PrepJob& jb = a.job[blockIdx.z - planned];   // (uniform index into the kernel arguments: scalar loads)
+    const int z = blockIdx.z - planned, job = min(z, a.n - 1);
+    const PrepJob& jb = a.job[job];   // (uniform index into the kernel arguments: scalar loads)
     const int cols = jb.cols;
-    const unsigned first = (blockIdx.y * gridDim.x + blockIdx.x) * PREP_THREADS + threadIdx.x, stride = gridDim.x * gridDim.y * PREP_THREADS;
+    const unsigned wgs = gridDim.x * gridDim.y, wg = blockIdx.y * gridDim.x + blockIdx.x;
     if (cols == PREP_ROWS) {
-        convert_rows(jb.W, static_cast<E*>(jb.dst), jb.quads, first, stride);
+        const unsigned layers = gridDim.z - planned - job;   // of the grid
+        convert_rows(jb.W, static_cast<E*>(jb.dst), jb.quads, ((size_t)(z - job) * wgs + wg) * PREP_THREADS + threadIdx.x, layers * wgs * PREP_THREADS);
         return;
     }
+    const unsigned first = wg * PREP_THREADS + threadIdx.x, stride = wgs * PREP_THREADS;
     if (cols == PREP_CLEAR) {
         for (unsigned i = first; i < jb.quads; i += stride) static_cast<int32_t*>(jb.dst)[i] = 0;
         return;
@@ -184,7 +190,7 @@ struct HeadsBwdArgs {
     int32_t* clear;
     const float* rows; bf16_t* rows_op;
     int M, H, A, n_clear;
-    unsigned quads;          // (rows)
+    size_t quads;            // (rows)
     int dh_blocks, w_blocks; // blockIdx.x below dh_blocks: dh; then w_blocks of weight-gradient blocks; then rows
 };
 __device__ __forceinline__ void heads_dh_block(const HeadsBwdArgs& a, int block) {
@@ -266,7 +272,7 @@ __global__ __launch_bounds__(256) void heads_bwd_kernel(HeadsBwdArgs a) {
     const int b = blockIdx.x, rows0 = a.dh_blocks + a.w_blocks;
     if (b < a.dh_blocks) heads_dh_block(a, b);
     else if (b < rows0) heads_wgrad_block(a, b - a.dh_blocks);
-    else convert_rows(a.rows, a.rows_op, a.quads, (b - rows0) * 256 + threadIdx.x, (gridDim.x - rows0) * 256);
+    else convert_rows(a.rows, a.rows_op, a.quads, (size_t)(b - rows0) * 256 + threadIdx.x, (gridDim.x - rows0) * 256);
 }
 // One workgroup adds the row blocks' partial sums for 64 columns of one head: its four waves take a quarter of the
 // row blocks each (in index order, 8 loads in flight), and the four shares are added in wave order.
@@ -617,12 +623,19 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             pa.job[n++] = PrepJob{w[4 * l + 1], nullptr, L.whh, L.whhT, H, 0};
             pa.job[n++] = PrepJob{w[4 * l + 2], w[4 * l + 3], L.bias, nullptr, PREP_BIAS, 0};
         }
-        if (ws.x_op) pa.job[n++] = PrepJob{static_cast<const float*>(x), nullptr, ws.x_op, nullptr, PREP_ROWS, (unsigned)((size_t)M * c.input_dim / 4)};
         // without a pair, also the time-out word and the flags of the first time loop (else: the plan clears them)
-        if (!pairs) pa.job[n++] = PrepJob{nullptr, nullptr, ws.err, nullptr, PREP_CLEAR, (unsigned)(ws.flags + REC_FLAG_WORDS - ws.err)};
+        if (!pairs) pa.job[n++] = PrepJob{nullptr, nullptr, ws.err, nullptr, PREP_CLEAR, (size_t)(ws.flags + REC_FLAG_WORDS - ws.err)};
+        const unsigned gx = (max_cols + 64 * PREP_TILES - 1) / (64 * PREP_TILES), gy = 4 * H / 64;
+        size_t layers = 1;   // of the grid, for the last job
+        if (ws.x_op) {
+            const size_t quads = (size_t)M * c.input_dim / 4;
+            pa.job[n++] = PrepJob{static_cast<const float*>(x), nullptr, ws.x_op, nullptr, PREP_ROWS, quads};
+            layers = (std::min(PREP_ROWS_WGS, (quads + PREP_ROWS_QUADS - 1) / PREP_ROWS_QUADS) + gx * gy - 1) / (gx * gy);
+        }
+        pa.n = n;
         const PlanArgs plan = pairs ? pipe_plan(ws, MODE, wide, H / (4 * mt), M, info, batch_sizes, c) : PlanArgs{};
         if (!set_lds(prep_weights_kernel<E>, prep_lds_bytes())) return false;
-        hipLaunchKernelGGL(prep_weights_kernel<E>, dim3((max_cols + 64 * PREP_TILES - 1) / (64 * PREP_TILES), 4 * H / 64, n + (pairs ? 1 : 0)),
+        hipLaunchKernelGGL(prep_weights_kernel<E>, dim3(gx, gy, n - 1 + (unsigned)layers + (pairs ? 1 : 0)),
                            dim3(PREP_THREADS), prep_lds_bytes(), s, pa, H, plan);
         return true;
     };
@@ -676,8 +689,8 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     // bf16: what the layer above layer l contracts (a two-layer launch writes that of its lower layer itself)
     auto copy_h = [&](int l, const int* alone) {
         if constexpr (MODE == MODE_BF16) {
-            const unsigned quads = (unsigned)((size_t)M * H / 4);
-            hipLaunchKernelGGL(convert_rows_kernel, dim3((quads + 1023) / 1024), dim3(256), 0, s, ws.layer[l].hout,
+            const size_t quads = (size_t)M * H / 4;
+            hipLaunchKernelGGL(convert_rows_kernel, dim3((unsigned)((quads + 1023) / 1024)), dim3(256), 0, s, ws.layer[l].hout,
                                static_cast<bf16_t*>(ws.layer[l].hcopy), quads, alone);
         }
     };
@@ -737,10 +750,10 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     ha.dh = ws.dh[0]; ha.part = ws.part; ha.part_b = ws.part_b;
     ha.M = M; ha.H = H; ha.A = A;
     ha.clear = ws.flags; ha.n_clear = top_pair ? (int)(ws.pipe + ws.pipe_words - ws.flags) : REC_FLAG_WORDS;
-    ha.rows = static_cast<const float*>(x); ha.rows_op = ws.x_op; ha.quads = ws.x_op ? (unsigned)((size_t)M * c.input_dim / 4) : 0;
+    ha.rows = static_cast<const float*>(x); ha.rows_op = ws.x_op; ha.quads = ws.x_op ? (size_t)M * c.input_dim / 4 : 0;
     ha.dh_blocks = (M + HB_ROWS - 1) / HB_ROWS;
     ha.w_blocks = (rb_h * (H / 64) + 3) / 4;
-    hipLaunchKernelGGL(heads_bwd_kernel, dim3(ha.dh_blocks + ha.w_blocks + std::min(1024u, (ha.quads + 1023) / 1024)), dim3(256), 0, s, ha);
+    hipLaunchKernelGGL(heads_bwd_kernel, dim3(ha.dh_blocks + ha.w_blocks + (unsigned)std::min((size_t)1024, (ha.quads + 1023) / 1024)), dim3(256), 0, s, ha);
     }
     HeadsFinalArgs hf{ws.part, ws.part_b, gw[4 * nl], gw[4 * nl + 2], gw[4 * nl + 1], gw[4 * nl + 3], (M + HW_ROWS - 1) / HW_ROWS, H, A};
 

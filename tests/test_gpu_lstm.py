@@ -508,3 +508,36 @@ def test_pairs_and_single_layers_in_one_workspace(ver, compute):
     for _ in range(2):
         for run, ref in zip(runs, alone):
             assert all(np.array_equal(a, b) for a, b in zip(step(run), ref))
+
+
+def test_conversion_of_16_giga_elements(ver):
+    """fp32 input rows of a bf16 call, 2^34 elements and a few more: every row converted (equal rows, equal outputs)."""
+    M, D, H, A = 2000000, 8592, 64, 2
+    assert M * D > 2 ** 34
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 160 << 30:
+        pytest.skip("needs 160 GB")
+    row, w = torch.linspace(-1, 1, D, device="cuda"), [torch.full((4 * H, D), 2.0 ** -13, device="cuda"), torch.zeros(4 * H, H, device="cuda")]
+    w[0][:, D // 2:] = 2.0 ** -10
+    w += [torch.zeros(4 * H, device="cuda"), torch.zeros(4 * H, device="cuda"), torch.full((A, H), 0.5, device="cuda"),
+          torch.zeros(A, device="cuda"), torch.full((H,), 0.25, device="cuda"), torch.zeros(1, device="cuda")]
+    cfg = ver.lstm_cfg(1, D, H, A, 1, 0)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    outs = []
+    for rows in (16, M):
+        x = row.expand(rows, D).contiguous()
+        info, bs, t_off = torch.tensor([rows, 1, rows, 0], **i32), torch.zeros(rows, **i32), torch.full((rows + 1,), rows, **i32)
+        bs[0], t_off[0] = rows, 0
+        ws = ver.workspace(ver.ver_lstm_workspace_bytes(cfg, rows))
+        ws.fill_(-1)
+        u, v = torch.full((rows, A), float("nan"), device="cuda"), torch.full((rows,), float("nan"), device="cuda")
+        ver.ver_lstm_fwd(cfg, x, rows, info, bs, t_off, None, None, 0, w, u, v, ws)
+        torch.cuda.synchronize()
+        assert ws[0].item() == 0
+        outs.append((u, v))
+        del x, ws
+    torch.cuda.empty_cache()
+    (u16, v16), (u, v) = outs
+    assert u16.abs().min() > 1e-3
+    # (another contraction kernel: sums in another order)
+    assert ((u - u16[0]).abs() <= 1e-5 * u16[0].abs()).all() and ((v - v16[0]).abs() <= 1e-5 * v16[0].abs()).all()
