@@ -187,8 +187,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_k_minor_kernel(GemmGroupArgs g)
     }
     tile<true>(q, t - q.tile_first, smem);
 }
-// C = sum of the parts in index order, 8 loads in flight; blockIdx.y: the problem.
+// C = sum of the parts in index order (+ bias), 8 loads in flight; blockIdx.y: the problem.
 __global__ __launch_bounds__(256) void gemm_add_parts_kernel(GemmGroupArgs g) {
+    if (g.alone && *g.alone == 0) return;
     const GemmProblem& q = g.p[blockIdx.y];   // (uniform index into the kernel arguments: scalar loads)
     const unsigned total = (unsigned)q.Mr * q.Nc;
     for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(256) void gemm_add_parts_kernel(GemmGroupArgs g) {
         }
         for (; z < g.parts; ++z) s += q.part[(size_t)z * total + i];
         const unsigned m = i / q.Nc, n = i - m * q.Nc, out = q.unperm_h > 0 ? (m & 3) * q.unperm_h + (m >> 2) : m;
-        q.C[(size_t)out * q.ldc + n] = s;
+        q.C[(size_t)out * q.ldc + n] = q.bias ? s + q.bias[n] : s;
     }
 }
 
@@ -338,20 +339,16 @@ void GemmGroup::launch_bf16(hipStream_t s) {
         hipLaunchKernelGGL(gemm_bf16_kernel, dim3(group_grid(tiles)), dim3(256), 0, s, a);
         return;
     }
-    const int K = a.p[0].K;   // (the same in all of them: the rows of a minibatch)
-    a.parts = part ? std::max(1, std::min(K / PART_ROWS, PART_TILES / tiles)) : 1;
-    a.k_part = ((K + a.parts - 1) / a.parts + BK - 1) / BK * BK;
-    a.parts = (K + a.k_part - 1) / a.k_part;   // (none of them empty)
-    unsigned most = 0;
-    float* to = part;
-    for (int i = 0; a.parts > 1 && i < a.n; ++i) {
-        const unsigned results = (unsigned)a.p[i].Mr * a.p[i].Nc;
-        a.p[i].part = to;
-        to += (size_t)a.parts * results;
-        most = std::max(most, results);
-    }
+    split(tiles, PART_ROWS, BK);
     hipLaunchKernelGGL(gemm_bf16_k_minor_kernel, dim3(group_grid(tiles * a.parts)), dim3(256), 0, s, a);
-    if (a.parts > 1) hipLaunchKernelGGL(gemm_add_parts_kernel, dim3(std::min(1024u, (most + 255) / 256), a.n), dim3(256), 0, s, a);
+    add_parts(s);
+}
+
+void GemmGroup::add_parts(hipStream_t s) {
+    if (a.parts <= 1) return;
+    unsigned most = 0;
+    for (int i = 0; i < a.n; ++i) most = std::max(most, (unsigned)a.p[i].Mr * a.p[i].Nc);
+    hipLaunchKernelGGL(gemm_add_parts_kernel, dim3(std::min(1024u, (most + 255) / 256), a.n), dim3(256), 0, s, a);
 }
 
 bool GemmGroup::launch_large(hipStream_t s) {

@@ -11,8 +11,8 @@
 //  * two stages of LDS, so that four workgroups share a CU and one multiplies while another waits (three or four stages with
 //    fewer workgroups: 8 to 15 % slower);
 //  * square tiles of 64, or of 32 where those would leave CUs idle (launch rule below), without splitting the
-//    contraction: no partial tiles in memory and no pass that adds them.  A running sum is moved to a second set of
-//    registers every 128 k, so chains of additions stay as short as with a split;
+//    contraction (but for few rows of very wide inputs: gemm_group.h): no partial tiles in memory and no pass that adds
+//    them.  A running sum is moved to a second set of registers every 128 k, so chains of additions stay as short as with a split;
 //  * all weight gradients of a minibatch share a launch, so the last, partly filled round of the chip is paid once.
 // us, the 128 x 128 register-staged tiles with a split contraction that ran here before -> now: the four weight gradients of 2 x
 // 512 units over 1024 rows (8.7 GFLOP) 235 -> 88, input projection 1024 x 2048 x 516 55 -> 26, input gradient 1024 x
@@ -204,31 +204,46 @@ __device__ __forceinline__ void tile(const GemmProblem& q, int t, unsigned char*
 template <int T, bool KMIN>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmGroupArgs g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int t = group_tile(g.tiles);
-    if (t < 0 || (g.alone && *g.alone == 0)) return;
-    const GemmProblem q = group_problem(g, t);
+    const int all = group_tile(g.tiles * g.parts);
+    if (all < 0 || (g.alone && *g.alone == 0)) return;
+    const int part = g.parts > 1 ? all / g.tiles : 0, t = all - part * g.tiles;
+    GemmProblem q = group_problem(g, t);
+    if (!KMIN && g.parts > 1) {   // columns [part * k_part, ...) of both operands, into the part's own results
+        const int k0 = part * g.k_part;
+        q.A = static_cast<const float*>(q.A) + k0;
+        q.B = static_cast<const float*>(q.B) + k0;
+        q.K = min(q.K - k0, g.k_part);
+        q.C = q.part + (size_t)part * q.Mr * q.Nc;
+        q.ldc = q.Nc;
+        q.bias = nullptr;
+    }
     tile<T, KMIN>(q, t - q.tile_first, smem);
 }
 
 template <int T, bool KMIN>
 void start(const GemmGroupArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL((gemm_f32_kernel<T, KMIN>), dim3(group_grid(a.tiles)), dim3(256), Geom<T>::STAGES * Geom<T>::STAGE, s, a);
+    hipLaunchKernelGGL((gemm_f32_kernel<T, KMIN>), dim3(group_grid(a.tiles * a.parts)), dim3(256), Geom<T>::STAGES * Geom<T>::STAGE, s, a);
 }
 
 // From this many tiles of 64 on they fill the chip.  us with tiles of 64 / 32: 512 tiles 26.2 / 30.0, 4096 367 / 434, 256 48.7 / 47.9,
 // 144 46.1 / 35.5, 80 6.2 / 4.5; K-minor 1056 92.7 / 87.5 (in tiles of 64 a few more than the chip holds at a time), 544 408 / 414, 24
 // (2048 rows) 36.4 / 14.8.
 constexpr int T64_FROM = 384, T64_FROM_K_MINOR = 1280;
+// Of a split contraction: tiles of 64 where all parts' tiles are as many as the chip holds (us with 64 / 32: 256 rows, 512 units, 16384
+// inputs, 8 parts of 128 tiles 149 / 192; 1024 rows, 256 units, 4 parts of 256 tiles 282 / 309).
 
 }  // namespace
 
 void GemmGroup::launch_f32(hipStream_t s) {
-    if (lay_out(64) >= (k_minor ? T64_FROM_K_MINOR : T64_FROM)) {
-        k_minor ? start<64, true>(a, s) : start<64, false>(a, s);
-    } else {
-        lay_out(32);
-        k_minor ? start<32, true>(a, s) : start<32, false>(a, s);
-    }
+    a.parts = 1;
+    int tiles = lay_out(64);
+    const bool whole = k_minor || tiles >= T64_FROM;
+    const bool of_64 = tiles >= (k_minor ? T64_FROM_K_MINOR : T64_FROM) || (!whole && tiles * parts(tiles, PART_COLS) >= PART_TILES);
+    if (!of_64) tiles = lay_out(32);
+    if (!whole) split(tiles, PART_COLS, BK);
+    if (of_64) k_minor ? start<64, true>(a, s) : start<64, false>(a, s);
+    else k_minor ? start<32, true>(a, s) : start<32, false>(a, s);
+    add_parts(s);
 }
 
 }  // namespace ver

@@ -23,7 +23,7 @@ struct GemmGroupArgs { GemmProblem p[GEMM_GROUP_MAX]; int n, tiles, parts, k_par
 struct GemmGroup {
     GemmGroupArgs a{};
     bool k_minor, bf16;
-    float* part;   // scratch of part_floats (bf16, K-minor), or NULL
+    float* part;   // scratch of part_floats (bf16, K-minor) or row_part_floats (fp32, K-major), or NULL
     GemmGroup(bool k_minor_, bool bf16_, float* part_ = nullptr) : k_minor(k_minor_), bf16(bf16_), part(part_) {}
     // K-minor bf16 contractions in 64 x 64 tiles are split into parts of at least PART_ROWS rows (a part takes a few us whatever its
     // length, and one more pass adds the parts) while all parts' tiles are at most PART_TILES, what the chip holds at a time.
@@ -35,6 +35,13 @@ struct GemmGroup {
     // Bound of the scratch for contractions over K rows of up to `outputs` results per launch.
     static size_t part_floats(size_t outputs, int K) {
         return K < 2 * PART_ROWS ? 0 : std::min((size_t)PART_TILES * 64 * 64, outputs * (K / PART_ROWS));
+    }
+    // K-major fp32 contractions of few tiles over wide inputs are split in the same way, into parts of at least PART_COLS.  us per
+    // projection, one part -> several (128 x 128 tiles split up to eight ways, before: in brackets): 59 rows, 64 units, 4096
+    // inputs 46 -> 30 (54), 16384 183 -> 31 (166); 59 rows, 512 units, 16384 inputs 294 -> 72 (168); 256 rows, 512 units 301 -> 149 (178).
+    static constexpr int PART_COLS = 2048;
+    static size_t row_part_floats(int Mr, int Nc, int K) {
+        return K < 2 * PART_COLS ? 0 : std::min((size_t)PART_TILES * 64 * 64, (size_t)Mr * Nc * (K / PART_COLS));
     }
     // Whether all arrays are within the kernels' 32-bit byte offsets.
     bool fits(int lda, int ldb, int ldc, int Mr, int Nc, int K) const {
@@ -69,6 +76,21 @@ struct GemmGroup {
     bool launch_large(hipStream_t s);
 
 private:
+    // Parts of at least `least` of the contraction (the same in all problems) for launches of `tiles` tiles, and where their
+    // results go; add_parts, behind the launch, adds those.
+    int parts(int tiles, int least) const { return part ? std::max(1, std::min(a.p[0].K / least, PART_TILES / tiles)) : 1; }
+    void split(int tiles, int least, int BK) {
+        const int K = a.p[0].K;
+        a.parts = parts(tiles, least);
+        a.k_part = ((K + a.parts - 1) / a.parts + BK - 1) / BK * BK;
+        a.parts = (K + a.k_part - 1) / a.k_part;   // (none of them empty)
+        float* to = part;
+        for (int i = 0; a.parts > 1 && i < a.n; ++i) {
+            a.p[i].part = to;
+            to += (size_t)a.parts * a.p[i].Mr * a.p[i].Nc;
+        }
+    }
+    void add_parts(hipStream_t s);
     void launch_f32(hipStream_t s);
     void launch_bf16(hipStream_t s);
 };

@@ -403,6 +403,7 @@ inline size_t gemm_part_max(const ver_lstm_cfg& c, int M) {
     size_t m = 0;
     for (int l = 0; l < c.n_layers; ++l) {
         const int D = l == 0 ? c.input_dim : c.hidden;
+        if (!c.compute) m = std::max({m, GemmGroup::row_part_floats(M, H4, D), GemmGroup::row_part_floats(M, D, H4)});
         if (!rows.fits(D, D, H4, M, H4, D)) m = std::max(m, gemm_part_floats(M, H4, D, bk));
         if (!rows.fits(H4, H4, D, M, D, H4)) m = std::max(m, gemm_part_floats(M, D, H4, bk));
         for (int n : {D, c.hidden})
@@ -490,7 +491,7 @@ inline bool set_lds(K kernel, size_t bytes) {
 // to the general kernel.
 template <int MODE>
 inline int contract_rows(const typename RecGeom<MODE>::E* A, const typename RecGeom<MODE>::E* B, float* C, const float* bias, int M, int N, int K, float* part, hipStream_t s, const int* alone = nullptr) {
-    GemmGroup g(false, MODE == MODE_BF16);
+    GemmGroup g(false, MODE == MODE_BF16, part);
     g.a.alone = alone;
     if (!g.add(A, K, B, K, C, N, M, N, K, bias, 0)) {
         gemm_launch<MODE, false>(A, K, B, K, C, N, M, N, K, bias, 0, part, alone, s);

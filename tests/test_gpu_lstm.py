@@ -215,6 +215,14 @@ def test_bf16_weight_gradients_in_parts(ver, rows, hidden, input_dim, layers):
                         p_done=0.05, minibatches=1), seed=rows, compute=1, x_bf16=True)
 
 
+@pytest.mark.parametrize("rows,hidden,input_dim,layers", [(59, 64, 4092, 1), (59, 64, 4096, 1), (31, 64, 4100, 2), (33, 128, 6148, 1), (70, 320, 8196, 1), (450, 512, 8200, 1)])
+def test_wide_inputs(ver, rows, hidden, input_dim, layers):
+    """fp32 projections of few rows are split over the inputs from 4096 on: one part, two and more, the last one shorter; the last
+    case in tiles of 64."""
+    case(ver, wl.scaled(wl.WORKLOADS["manip"], budget=rows, n_envs=max(2, rows // 20), hidden=hidden, input_dim=input_dim, n_layers=layers,
+                        p_done=0.05, minibatches=1), seed=rows + input_dim)
+
+
 @pytest.mark.parametrize("rows,hidden,act_dim", [(31, 64, 1), (32, 64, 15), (33, 128, 16), (65, 320, 47), (130, 64, 63)])
 def test_head_gradients(ver, rows, hidden, act_dim):
     """Row blocks of the heads' weight gradients at their edges; head counts at the edges of the 16-row products."""
