@@ -10,7 +10,7 @@
 //    are permuted, and the store puts them back);
 //  * two stages of LDS, so that four workgroups share a CU and one multiplies while another waits (three or four stages with
 //    fewer workgroups: 8 to 15 % slower);
-//  * square tiles of 64, or of 32 where those would leave CUs idle (launch rule below), without splitting the
+//  * square tiles of 64, or of 32 where their rounds of the chip take less (launch rule below), without splitting the
 //    contraction (but for few rows of very wide inputs: gemm_group.h): no partial tiles in memory and no pass that adds
 //    them.  A running sum is moved to a second set of registers every 128 k, so chains of additions stay as short as with a split;
 //  * all weight gradients of a minibatch share a launch, so the last, partly filled round of the chip is paid once.
@@ -225,10 +225,14 @@ void start(const GemmGroupArgs& a, hipStream_t s) {
     hipLaunchKernelGGL((gemm_f32_kernel<T, KMIN>), dim3(group_grid(a.tiles * a.parts)), dim3(256), Geom<T>::STAGES * Geom<T>::STAGE, s, a);
 }
 
-// From this many tiles of 64 on they fill the chip.  us with tiles of 64 / 32: 512 tiles 26.2 / 30.0, 4096 367 / 434, 256 48.7 / 47.9,
-// 144 46.1 / 35.5, 80 6.2 / 4.5; K-minor 1056 92.7 / 87.5 (in tiles of 64 a few more than the chip holds at a time), 544 408 / 414, 24
-// (2048 rows) 36.4 / 14.8.
-constexpr int T64_FROM = 384, T64_FROM_K_MINOR = 1280;
+// A round of 256 tiles of 64, one per CU, lasts as long as ROUND_OF_32 tiles of 32 (a CU's workgroups share its MFMAs: it is the
+// count per CU that matters, not how many workgroups are resident), and tiles of 64 need two rounds, so that a CU has another
+// workgroup while one waits.  us with tiles of 64 / 32, by tiles of 64 (of 32).  K-minor, 4096 rows: 336 (1188) 132 / 110, 544 (2112) 191 / 168, 800
+// (3200) 262 / 234, 928 (3648) 261 / 267, 960 (3800) 262 / 301, 1056 (4160) 326 / 306, 1224 (4848) 327 / 369, 1440 (5696) 387 / 444, 2080 (8320) 567 /
+// 634; 1024 rows: 544 54 / 48, 992 (3904) 76 / 80, 1056 91 / 85, 1312 (5184) 106 / 99.  K-major, K = 516: 256 (1024) 17.4 / 17.7, 384 (1536) 25 / 22, 448
+// (1792) 26 / 24, 576 (2304) 34 / 32, 768 (3072) 35 / 39, 2048 (8192) 80 / 90; K = 2048 and 2052: 252 (952) 44 / 41, 384 74 / 65, 462 (1820) 74 / 77, 576
+// (2176) 103 / 91, 640 (2560) 106 / 114, 1056 (4160) 167 / 160, 2048 269 / 335.
+constexpr int ROUND = 256, ROUND_OF_32 = 850;
 // Of a split contraction: tiles of 64 where all parts' tiles are as many as the chip holds (us with 64 / 32: 256 rows, 512 units, 16384
 // inputs, 8 parts of 128 tiles 149 / 192; 1024 rows, 256 units, 4 parts of 256 tiles 282 / 309).
 
@@ -236,9 +240,12 @@ constexpr int T64_FROM = 384, T64_FROM_K_MINOR = 1280;
 
 void GemmGroup::launch_f32(hipStream_t s) {
     a.parts = 1;
+    const int tiles_32 = lay_out(32);
     int tiles = lay_out(64);
-    const bool whole = k_minor || tiles >= T64_FROM;
-    const bool of_64 = tiles >= (k_minor ? T64_FROM_K_MINOR : T64_FROM) || (!whole && tiles * parts(tiles, PART_COLS) >= PART_TILES);
+    const int rounds = (tiles + ROUND - 1) / ROUND;
+    bool of_64 = rounds >= 2 && ROUND_OF_32 * rounds <= tiles_32;
+    const bool whole = k_minor || of_64;
+    if (!whole) of_64 = tiles * parts(tiles, PART_COLS) >= PART_TILES;
     if (!of_64) tiles = lay_out(32);
     if (!whole) split(tiles, PART_COLS, BK);
     if (of_64) k_minor ? start<64, true>(a, s) : start<64, false>(a, s);

@@ -187,9 +187,9 @@ def test_pairs_of_layers(ver, n_layers, compute, layer_by_layer):
                         minibatches=1), seed=9, compute=compute, layer_by_layer=layer_by_layer)
 
 
-@pytest.mark.parametrize("rows,hidden,input_dim", [(32, 64, 4), (33, 64, 32), (63, 128, 68), (127, 64, 132), (129, 320, 36), (1000, 512, 516), (130, 512, 1028)])
+@pytest.mark.parametrize("rows,hidden,input_dim", [(32, 64, 4), (33, 64, 32), (63, 128, 68), (127, 64, 132), (129, 320, 36), (1000, 512, 516), (130, 512, 1028), (700, 512, 388)])
 def test_fp32_contractions(ver, rows, hidden, input_dim):
-    """Edges of the 32 x 32 and 64 x 64 tiles of the fp32 contractions (64 x 64: K-major at 1000 rows, K-minor at 1028 inputs): one to 32 K-tiles, rows and
+    """Edges of the 32 x 32 and 64 x 64 tiles of the fp32 contractions (64 x 64: K-major at 1000 rows, K-minor at 388 and 1028 inputs): one to 32 K-tiles, rows and
     columns one short of and one beyond a tile, K-tiles with 4 valid k."""
     case(ver, wl.scaled(wl.WORKLOADS["manip"], budget=rows, n_envs=max(2, rows // 25), hidden=hidden, input_dim=input_dim, p_done=0.05,
                         minibatches=1), seed=rows)
