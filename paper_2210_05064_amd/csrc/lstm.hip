@@ -485,10 +485,14 @@ inline bool set_lds(K kernel, size_t bytes) {
 
 // C[M, N] = A[M, K] B[N, K]^T (+ bias), all three row-major, A and B in the operand type.  bf16 in 64 x 64 tiles while those
 // are at most four per CU (us, 64 x 64 and 128 x 256 tiles: 1024 tiles, 1000 x 4096 x 1044 28 and 28, 2048 x 2048 x 516 15.4 and
-// 16.5; 940, 3001 x 1280 x 320 9.0 and 12; 235, 3001 x 320 x 1280 8.8 and 21; 4096, 8192 x 4096 x 1044 210 and 114).  Beyond that one
+// 16.5; 940, 3001 x 1280 x 320 9.0 and 12; 235, 3001 x 320 x 1280 8.8 and 21; 4096, 8192 x 4096 x 1044 210 and 114); where one column of
+// 128 x 256 tiles covers the matrix, and so reads the rows once, at most TILES_64_NARROW of them (768 tiles, 12288 x 256 x 4096 57 and 62; 876, 14000 x
+// 224 x 4096 65 and 61; 1024, 16384 x 256 x 4096 75 and 62, 32768 x 128 x 2048 47 and 37).  Beyond that one
 // tile per CU at a time: 256 x 256 or 128 x 256, whichever's rounds take less; a round of the larger ones takes 1.6 times as long
-// (45 and 28 us at K = 1044).  What lies beyond the 32-bit byte offsets of these kernels (only rows of the caller's can) goes
+// (45 and 28 us at K = 1044), and more where the contraction is short and the time that of the stores, with nothing beside them in
+// a CU (8192 x 4096: K = 36 35 and 30, 192 41 and 36, 256 44 and 44; 32768 x 4096: 36 121 and 111, 260 194 and 218).  What lies beyond the 32-bit byte offsets of these kernels (only rows of the caller's can) goes
 // to the general kernel.
+constexpr int LARGE_FROM_K = 256, TILES_64_NARROW = 832;
 template <int MODE>
 inline int contract_rows(const typename RecGeom<MODE>::E* A, const typename RecGeom<MODE>::E* B, float* C, const float* bias, int M, int N, int K, float* part, hipStream_t s, const int* alone = nullptr) {
     GemmGroup g(false, MODE == MODE_BF16, part);
@@ -497,9 +501,9 @@ inline int contract_rows(const typename RecGeom<MODE>::E* A, const typename RecG
         gemm_launch<MODE, false>(A, K, B, K, C, N, M, N, K, bias, 0, part, alone, s);
         return VER_OK;
     }
-    if (MODE == MODE_BF16 && g.lay_out(64) > 4 * REC_GRID) {
+    if (MODE == MODE_BF16 && g.lay_out(64) > (N <= PIPE_BN ? TILES_64_NARROW : 4 * REC_GRID)) {
         auto rounds = [](int tiles) { return (tiles + REC_GRID - 1) / REC_GRID; };
-        if (8 * rounds(g.lay_out(GemmGroup::LARGE_TILE)) <= 5 * rounds(g.lay_out(PIPE_BM, PIPE_BN))) return g.launch_large(s) ? VER_OK : VER_EHIP;
+        if (K >= LARGE_FROM_K && 8 * rounds(g.lay_out(GemmGroup::LARGE_TILE)) <= 5 * rounds(g.lay_out(PIPE_BM, PIPE_BN))) return g.launch_large(s) ? VER_OK : VER_EHIP;
         if (!set_lds(lstm_proj_dma_kernel, (size_t)PIPE_STAGES * PIPE_STAGE_BYTES)) return VER_EHIP;
         const ProjWork pw = {A, B, C, bias, K, N, M, alone};
         const int tiles_n = (N + PIPE_BN - 1) / PIPE_BN, tiles_m = (M + PIPE_BM - 1) / PIPE_BM;

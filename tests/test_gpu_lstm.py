@@ -437,13 +437,11 @@ def test_nan_stays_in_its_piece(ver, compute, hidden, n_layers, n_envs):
     assert np.isnan(grads_bad[1]).any()
 
 
-@pytest.mark.parametrize("rows,input_dim,compute", [(520000, 1044, 0), (2000, 270000, 0), (1040000, 1044, 1), (4000, 270000, 1)])
-def test_arrays_beyond_2_gigabytes(ver, rows, input_dim, compute):
-    """Input rows and their gradient of 2 GB and more (the general contraction kernel): few tiles and a long contraction in the
-    weight gradient (many rows) or in the projection (wide rows).  One timestep of `rows` pieces, so that plain torch in 64 bits
-    is the reference.  fp32: a sum of n terms as P partial sums of chains of n / (4 P) additions is off by about
-    2^-24 sqrt(n / (8 P)) of its size; P = 8, and half as much again.  bf16: gate gradients rounded to 8 bits."""
-    H, A = 64, 4
+def one_timestep(ver, rows, input_dim, compute, H=64):
+    """One timestep of `rows` pieces, with plain torch in 64 bits as the reference.  fp32: a sum of n terms as P partial sums of chains of
+    n / (4 P) additions is off by about 2^-24 sqrt(n / (8 P)) of its size; P = 8, and half as much again.  bf16: gate gradients
+    rounded to 8 bits."""
+    A = 4
     M, D, g = rows, input_dim, torch.Generator(device="cuda").manual_seed(rows)
     normal = lambda *shape, scale=1.0: torch.randn(*shape, generator=g, device="cuda").mul_(scale)
     x = normal(M, D)
@@ -477,6 +475,20 @@ def test_arrays_beyond_2_gigabytes(ver, rows, input_dim, compute):
     assert off(grads[0], W[0].grad) <= (rounded if compute else max(chain(M), tight))
     assert off(dx, x64.grad) <= (rounded if compute else tight)
     assert off(grads[2], W[2].grad) <= (rounded if compute else 1e-5) and not grads[1].any()
+
+
+@pytest.mark.parametrize("rows,input_dim,compute", [(520000, 1044, 0), (2000, 270000, 0), (1040000, 1044, 1), (4000, 270000, 1)])
+def test_arrays_beyond_2_gigabytes(ver, rows, input_dim, compute):
+    """Input rows and their gradient of 2 GB and more (the general contraction kernel): few tiles and a long contraction in the
+    weight gradient (many rows) or in the projection (wide rows)."""
+    one_timestep(ver, rows, input_dim, compute)
+
+
+@pytest.mark.parametrize("rows,input_dim,hidden", [(53184, 60, 64), (53249, 60, 64), (14000, 252, 128), (3000, 252, 1024), (3000, 256, 1024), (3000, 36, 1024)])
+def test_bf16_tiles_of_contractions(ver, rows, input_dim, hidden):
+    """Narrow input gradients on either side of 832 tiles of 64 x 64; projections of many tiles whose contraction is shorter than
+    256 and not."""
+    one_timestep(ver, rows, input_dim, 1, hidden)
 
 
 def even(ver, pieces, steps, layers, compute, hidden, **kw):
