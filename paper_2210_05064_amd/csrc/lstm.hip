@@ -34,9 +34,10 @@ __device__ __forceinline__ void st4(bf16_t* p, float a, float b, float c, float 
 // A thread moves 4 adjacent elements at a time (16-byte loads, 8- or 16-byte stores; cols is a multiple of 4):
 // 16 lanes cover a tile row in either direction.
 // All matrices and bias vectors of a call in one launch (blockIdx.z: the job; a launch per matrix took ~10 us each,
-// most of it ramp and tail).  Workgroups of 1024 threads, a tile per 256, so that the plan of the two-layer launches
-// (lstm_pipe.h) can be one of them, the first to start: as a launch of its own it took 7 to 30 us in front of the time loops.
-constexpr int PREP_THREADS = PLAN_THREADS, PREP_TILES = PREP_THREADS / 256;
+// most of it ramp and tail).  A tile per 256 threads: workgroups of that size for a single layer, for several workgroups of
+// PLAN_THREADS, so that the plan of the two-layer launches (lstm_pipe.h) can be one of them, the first to start: as a launch of its own
+// it took 7 to 30 us in front of the time loops.  (A single layer in workgroups of 1024, whose four tiles wait
+// for each other: 1024 units and 36 inputs 13.0 us instead of 11.3, 512 units and 16384 inputs 79 instead of 58.)
 constexpr int PREP_MAX_JOBS = 26;   // 2 matrices + 1 bias per layer, 8 layers; the fp32 rows of a bf16 call; words to clear
 constexpr int PREP_BIAS = 0, PREP_ROWS = -1, PREP_CLEAR = -2;
 struct PrepJob {
@@ -60,19 +61,24 @@ __global__ __launch_bounds__(256) void convert_rows_kernel(const float* __restri
     convert_rows(src, dst, quads, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
 }
 constexpr size_t PREP_TILE_FLOATS = 64 * 65;
-inline size_t prep_lds_bytes() { return std::max(PREP_TILES * PREP_TILE_FLOATS * sizeof(float), sizeof(PlanLds)); }
+inline size_t prep_lds_bytes(int threads) {
+    const size_t tiles = threads / 256 * PREP_TILE_FLOATS * sizeof(float);
+    return threads == PLAN_THREADS ? std::max(tiles, sizeof(PlanLds)) : tiles;
+}
 // blockIdx.z = 0 is the plan where there is one (plan.plan_fwd != NULL), then the jobs; what is left belongs to the last job, the
-// rows where there are any: x and y are as many as the widest matrix has tiles, 20 workgroups for 64 units and 1044 inputs (us
-// per launch with those / with a workgroup per 4096 groups: 8192 rows of 1044 53 / 13, 32768 274 / 43, 400000 3500 / 590).
-constexpr size_t PREP_ROWS_QUADS = 4 * PREP_THREADS, PREP_ROWS_WGS = 512;
-template <typename E>
+// rows where there are any: x and y are as many as the widest matrix has tiles, 20 workgroups of 1024 for 64 units and 1044 inputs
+// (us per launch with those / with a thread per four groups: 8192 rows of 1044 53 / 13, 32768 315 / 50; at most a quarter as many threads: 58).
+constexpr size_t PREP_ROWS_QUADS = 4, PREP_ROWS_THREADS = 2048 * 1024;   // per thread; at most
+template <typename E, int PREP_THREADS>
 __global__ __launch_bounds__(PREP_THREADS) void prep_weights_kernel(PrepArgs a, int H, PlanArgs plan) {
     extern __shared__ __attribute__((aligned(16))) unsigned char prep_smem[];
-    const int planned = plan.plan_fwd != nullptr ? 1 : 0;
-    if ((int)blockIdx.z < planned) {
-        if (blockIdx.x == 0 && blockIdx.y == 0) plan_launches(plan, *reinterpret_cast<PlanLds*>(prep_smem));
-        return;
-    }
+    constexpr int PREP_TILES = PREP_THREADS / 256;
+    const int planned = PREP_THREADS == PLAN_THREADS && plan.plan_fwd != nullptr ? 1 : 0;
+    if constexpr (PREP_THREADS == PLAN_THREADS)
+        if ((int)blockIdx.z < planned) {
+            if (blockIdx.x == 0 && blockIdx.y == 0) plan_launches(plan, *reinterpret_cast<PlanLds*>(prep_smem));
+            return;
+        }
     const int z = blockIdx.z - planned, job = min(z, a.n - 1);
     const PrepJob& jb = a.job[job];   // (uniform index into the kernel arguments: scalar loads)
     const int cols = jb.cols;
@@ -630,19 +636,23 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         }
         // without a pair, also the time-out word and the flags of the first time loop (else: the plan clears them)
         if (!pairs) pa.job[n++] = PrepJob{nullptr, nullptr, ws.err, nullptr, PREP_CLEAR, (size_t)(ws.flags + REC_FLAG_WORDS - ws.err)};
-        const unsigned gx = (max_cols + 64 * PREP_TILES - 1) / (64 * PREP_TILES), gy = 4 * H / 64;
+        const unsigned threads = pairs ? PLAN_THREADS : 256, cols = threads / 4;   // columns of a workgroup's tiles
+        const unsigned gx = (max_cols + cols - 1) / cols, gy = 4 * H / 64;
         size_t layers = 1;   // of the grid, for the last job
         if (ws.x_op) {
             const size_t quads = (size_t)M * c.input_dim / 4;
             pa.job[n++] = PrepJob{static_cast<const float*>(x), nullptr, ws.x_op, nullptr, PREP_ROWS, quads};
-            layers = (std::min(PREP_ROWS_WGS, (quads + PREP_ROWS_QUADS - 1) / PREP_ROWS_QUADS) + gx * gy - 1) / (gx * gy);
+            const size_t wgs = std::min(PREP_ROWS_THREADS / threads, (quads + PREP_ROWS_QUADS * threads - 1) / (PREP_ROWS_QUADS * threads));
+            layers = (wgs + gx * gy - 1) / (gx * gy);
         }
         pa.n = n;
         const PlanArgs plan = pairs ? pipe_plan(ws, MODE, wide, H / (4 * mt), M, info, batch_sizes, c) : PlanArgs{};
-        if (!set_lds(prep_weights_kernel<E>, prep_lds_bytes())) return false;
-        hipLaunchKernelGGL(prep_weights_kernel<E>, dim3(gx, gy, n - 1 + (unsigned)layers + (pairs ? 1 : 0)),
-                           dim3(PREP_THREADS), prep_lds_bytes(), s, pa, H, plan);
-        return true;
+        auto launch = [&](auto kernel) {
+            if (!set_lds(kernel, prep_lds_bytes(threads))) return false;
+            hipLaunchKernelGGL(kernel, dim3(gx, gy, n - 1 + (unsigned)layers + (pairs ? 1 : 0)), dim3(threads), prep_lds_bytes(threads), s, pa, H, plan);
+            return true;
+        };
+        return pairs ? launch(prep_weights_kernel<E, PLAN_THREADS>) : launch(prep_weights_kernel<E, 256>);
     };
     // time-batched input projection: gates[M, 4H] = x W_ih^T + (b_ih + b_hh), interleaved columns
     auto project = [&](int l, const int* alone = nullptr) {
