@@ -496,9 +496,9 @@ inline bool set_lds(K kernel, size_t bytes) {
 // 224 x 4096 65 and 61; 1024, 16384 x 256 x 4096 75 and 62, 32768 x 128 x 2048 47 and 37).  Beyond that one
 // tile per CU at a time: 256 x 256 or 128 x 256, whichever's rounds take less; a round of the larger ones takes 1.6 times as long
 // (45 and 28 us at K = 1044), and more where the contraction is short and the time that of the stores, with nothing beside them in
-// a CU (8192 x 4096: K = 36 35 and 30, 192 41 and 36, 256 44 and 44; 32768 x 4096: 36 121 and 111, 260 194 and 218).  What lies beyond the 32-bit byte offsets of these kernels (only rows of the caller's can) goes
+// a CU (8192 x 4096: K = 36 35 and 30, 192 41 and 36, 256 44 and 44; 32768 x 4096: 36 121 and 111, 260 194 and 218; 32768 x 1044: 256 72 and 50).  What lies beyond the 32-bit byte offsets of these kernels (only rows of the caller's can) goes
 // to the general kernel.
-constexpr int LARGE_FROM_K = 256, TILES_64_NARROW = 832;
+constexpr int LARGE_FROM_K = 260, TILES_64_NARROW = 832;
 template <int MODE>
 inline int contract_rows(const typename RecGeom<MODE>::E* A, const typename RecGeom<MODE>::E* B, float* C, const float* bias, int M, int N, int K, float* part, hipStream_t s, const int* alone = nullptr) {
     GemmGroup g(false, MODE == MODE_BF16, part);
