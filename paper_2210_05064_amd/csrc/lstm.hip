@@ -188,16 +188,15 @@ __global__ __launch_bounds__(256) void heads_fwd_kernel(const float* __restrict_
 //    heads on M (16 at a time), rows on K: 4 rows and 64 columns (16 bytes per lane) per load of h, all loads of a wave in
 //    flight at once.  Bound by reading h once.  (A thread per 4 columns walking over the rows four at a time, eight
 //    dependent rounds: 11 us where this takes 4, on 59 rows as on 1000.)
-//  * a bf16 call's fp32 rows in the operand type, for the first layer's weight gradient.
+// (The fp32 rows of a bf16 call, which the first layer's weight gradient reads, are still there in the operand type from the
+// forward call: converted here again they took 34 us for 32768 rows of 1044, and 35 more in the time loop behind, 64 units.)
 constexpr int HB_ROWS = 8, HW_ROWS = 32;
 struct HeadsBwdArgs {
     const float* d_u; const float* d_v; const float* W_a; const float* w_v; const float* h;
     float* dh; float* part; float* part_b;
     int32_t* clear;
-    const float* rows; bf16_t* rows_op;
     int M, H, A, n_clear;
-    size_t quads;            // (rows)
-    int dh_blocks, w_blocks; // blockIdx.x below dh_blocks: dh; then w_blocks of weight-gradient blocks; then rows
+    int dh_blocks;           // blockIdx.x below dh_blocks: dh; then weight-gradient blocks
 };
 __device__ __forceinline__ void heads_dh_block(const HeadsBwdArgs& a, int block) {
     __shared__ float s_g[HB_ROWS][64];   // the block's loss gradients: heads 0..A-1, then the value head
@@ -275,10 +274,8 @@ __device__ __forceinline__ void heads_wgrad_block(const HeadsBwdArgs& a, int blo
     }
 }
 __global__ __launch_bounds__(256) void heads_bwd_kernel(HeadsBwdArgs a) {
-    const int b = blockIdx.x, rows0 = a.dh_blocks + a.w_blocks;
-    if (b < a.dh_blocks) heads_dh_block(a, b);
-    else if (b < rows0) heads_wgrad_block(a, b - a.dh_blocks);
-    else convert_rows(a.rows, a.rows_op, a.quads, (size_t)(b - rows0) * 256 + threadIdx.x, (gridDim.x - rows0) * 256);
+    if ((int)blockIdx.x < a.dh_blocks) heads_dh_block(a, blockIdx.x);
+    else heads_wgrad_block(a, blockIdx.x - a.dh_blocks);
 }
 // One workgroup adds the row blocks' partial sums for 64 columns of one head: its four waves take a quarter of the
 // row blocks each (in index order, 8 loads in flight), and the four shares are added in wave order.
@@ -765,10 +762,8 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     ha.dh = ws.dh[0]; ha.part = ws.part; ha.part_b = ws.part_b;
     ha.M = M; ha.H = H; ha.A = A;
     ha.clear = ws.flags; ha.n_clear = top_pair ? (int)(ws.pipe + ws.pipe_words - ws.flags) : REC_FLAG_WORDS;
-    ha.rows = static_cast<const float*>(x); ha.rows_op = ws.x_op; ha.quads = ws.x_op ? (size_t)M * c.input_dim / 4 : 0;
     ha.dh_blocks = (M + HB_ROWS - 1) / HB_ROWS;
-    ha.w_blocks = (rb_h * (H / 64) + 3) / 4;
-    hipLaunchKernelGGL(heads_bwd_kernel, dim3(ha.dh_blocks + ha.w_blocks + (unsigned)std::min((size_t)1024, (ha.quads + 1023) / 1024)), dim3(256), 0, s, ha);
+    hipLaunchKernelGGL(heads_bwd_kernel, dim3(ha.dh_blocks + (rb_h * (H / 64) + 3) / 4), dim3(256), 0, s, ha);
     }
     HeadsFinalArgs hf{ws.part, ws.part_b, gw[4 * nl], gw[4 * nl + 2], gw[4 * nl + 1], gw[4 * nl + 3], (M + HW_ROWS - 1) / HW_ROWS, H, A};
 
