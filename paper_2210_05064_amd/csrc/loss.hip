@@ -508,7 +508,7 @@ inline int loss_blocks(int M) {
 
 extern "C" size_t ver_ppo_loss_workspace_bytes(int32_t M, int32_t act_dim) {
     if (M <= 0 || act_dim <= 0) return 0;
-    return 256 + ver::align_up((size_t)ver::loss_blocks(M) * (ver::LOSS_SCALARS + act_dim) * 4, 256);
+    return ver::align_up((size_t)ver::loss_blocks(M) * (ver::LOSS_SCALARS + act_dim) * 4, 256);
 }
 
 namespace ver {
@@ -527,7 +527,6 @@ int ppo_loss_launch(const ver_ppo_cfg* cfg, int32_t M, const float* head_out, co
     if (!workspace || workspace_bytes < ver_ppo_loss_workspace_bytes(M, cfg->act_dim)) return VER_EWORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     Carver cv(workspace);
-    (void)cv.take<int>(64);
     float* partials = cv.take<float>((size_t)loss_blocks(M) * (LOSS_SCALARS + cfg->act_dim));
     const int blocks = loss_blocks(M);
     const LossOut out{scalars, d_log_std, d_alpha, alpha, target_entropy, alpha_sign};
