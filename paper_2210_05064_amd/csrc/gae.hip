@@ -30,7 +30,6 @@ constexpr int GAE_THREADS = 256;
 constexpr int GAE_ITEMS = 8;
 constexpr int GAE_TILE = GAE_THREADS * GAE_ITEMS;
 constexpr long long GAE_SPIN_LIMIT = 1LL << 24;  // polls before a wait gives up
-constexpr int GAE_MAX_BATCH = 64;      // tiles per ticket at most (measured on 65536 tiles: 16 -> 0.516 ms, 32 -> 0.506, 64 -> 0.499)
 constexpr int GAE_RESIDENT = 1024;     // workgroups that the chip holds at a time (four per CU)
 
 // A map's offset b is kept in fp64 everywhere: advantages are sums of TD errors that cancel heavily (with
@@ -387,11 +386,11 @@ inline int gae_tiles(int S) { return (S + GAE_TILE - 1) / GAE_TILE; }
 // Tiles per ticket: as many as let all workgroups run at once (with one fewer, a handful of workgroups started when the others
 // were done and the scan took twice their time), three at least, since every batch reads one tile twice.  us per scan with the
 // former floor(tiles / 1024) -> now: 1075 tiles 31.7 -> 22.7, 1465 40.3 -> 25.0, 2198 44.1 -> 31.6, 2930 50.8 -> 41.6, 4395 67.8 ->
-// 53.1, 6554 87.9 -> 70.0 (fill of the words included).  733 tiles one by one 20.6, in threes 19.8: not worth a second rule.
+// 53.1, 6554 87.9 -> 70.0 (fill of the words included); 66560 636 -> 485, 80000 784 -> 583, 131072 939 -> 931 (at most 64 -> now).  733 tiles one by one 20.6, in threes 19.8: not worth a second rule.
 inline int gae_batch(int tiles) {
     if (tiles <= GAE_RESIDENT) return 1;
     const int b = (tiles + GAE_RESIDENT - 1) / GAE_RESIDENT;
-    return b < 3 ? 3 : (b > GAE_MAX_BATCH ? GAE_MAX_BATCH : b);
+    return b < 3 ? 3 : b;
 }
 
 }  // namespace

@@ -14,7 +14,7 @@
 // workgroups, 1.1 to 1.7 us) plus a little per alive piece, and the launch lasts as long as its slowest group.  The
 // pieces are sorted longest first, so they are cut into three blocks of consecutive pieces: group 0 gets the few
 // longest ones (its chain of T_max dependent steps is what bounds the launch, so its steps should be the
-// cheapest), the last group the many short ones (few steps, each with many pieces).  the plan
+// cheapest), the last group the many short ones (few steps, each with many pieces).  The plan
 // picks the two cuts that minimise the largest predicted group time
 //     sum over the group's timesteps of (step + piece * b_t + tile * (ceil(b_t / 16) - 1)),   b_t = alive pieces of the group
 // (a time loop works through the alive pieces 16 at a time: the MFMA's columns), which it evaluates per candidate

@@ -10,7 +10,7 @@ import torch
 from oracle import lstm as olstm, pack as opack
 from paper_2210_05064_amd import workloads as wl
 from tests.gpu_util import LstmRun, grads_to_list, GRAD_NAMES
-from tests.util import closer, rel_err
+from tests.util import closer, l2_rel_err, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -499,12 +499,33 @@ def even(ver, pieces, steps, layers, compute, hidden, **kw):
 
 @pytest.mark.parametrize("pieces,steps,layers,compute,hidden", [
     (49, 17, 3, 1, 64), (50, 17, 3, 1, 64), (256, 3, 3, 1, 64), (257, 3, 3, 1, 64), (300, 3, 4, 1, 320), (900, 1, 5, 1, 128),
+    (20, 30, 4, 1, 320), (16, 50, 4, 1, 1024),   # pairs above pairs
     (50, 20, 3, 0, 256), (51, 20, 3, 0, 256), (32, 40, 3, 0, 384), (33, 40, 3, 0, 384), (400, 2, 4, 0, 64), (300, 3, 5, 0, 128)])
 def test_many_pieces_and_layers(ver, pieces, steps, layers, compute, hidden):
     """Three layers and more share launches in pairs up to 45 + T / 4 alive pieces per timestep (fp32 beyond 320 units: 12 + T / 2) and
-    up to 768 rows; beyond, every layer runs alone: both sides of the lines, a single timestep, a pair above a pair."""
+    up to 768 rows; beyond, every layer runs alone: both sides of the lines, a single timestep, pairs above pairs in either form."""
     run, meta = even(ver, pieces, steps, layers, compute, hidden)
     assert meta["n_seq"] == pieces and meta["T_max"] == steps
+
+
+@pytest.mark.parametrize("pieces,steps,layers,hidden", [(40, 20, 5, 128), (12, 60, 7, 64), (10, 70, 8, 192)])
+def test_pairs_above_pairs_bf16(ver, pieces, steps, layers, hidden):
+    """Two and more pairs, in launches of pairs and layer by layer.  Either form is up to 7e-3 from the exact gradients in the 2-norm
+    (five layers 5.4e-3, seven 7.1e-3, the same in both), so that they are up to twice that from each other; from five layers on the
+    largest element is beyond the oracle tests' 7e-2 in both (8.6e-2)."""
+    w = wl.scaled(wl.WORKLOADS["manip"], budget=pieces * steps, n_envs=pieces, speed_sigma=0.0, hidden=hidden, input_dim=36, n_layers=layers,
+                  p_done=0.0, minibatches=1)
+    ro = wl.make_rollout(w, seed=layers, bias_scale=0.2)
+    meta = opack.pack_minibatch(ro["dones"], ro["env_off"], ro["seq_key"][0], 1, 0, ro["env_started_episode"])
+    d_u, d_v = np.full((meta["M"], w.act_dim), 1.0 / meta["M"], np.float32), np.full(meta["M"], 1.0 / meta["M"], np.float32)
+    res = []
+    for layer_by_layer in (False, True):
+        run = LstmRun(ver, w, ro["weights"], opack.gather_rows(ro["obs"], meta["gather_idx"]), meta, compute=1, layer_by_layer=layer_by_layer)
+        u, v = run.forward()
+        grads, dx = run.backward(d_u, d_v)
+        res.append([u, v, dx] + grads)
+    for a, b in zip(*res):
+        assert l2_rel_err(a, b) <= 1.4e-2
 
 
 @pytest.mark.parametrize("compute", [0, 1])
