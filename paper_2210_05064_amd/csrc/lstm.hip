@@ -726,7 +726,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             pipe_work(ws, 0, M, t_off, alone, &pa.work);
             pa.work.G = pa.l0.G;
             ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
-            VER_FWD_DISPATCH(lstm_pipe_fwd_kernel, pa);
+            if (alone) VER_FWD_DISPATCH(lstm_pipe_fwd_planned_kernel, pa); else VER_FWD_DISPATCH(lstm_pipe_fwd_kernel, pa);
             if (!ok) return VER_EHIP;
             l += 2;
         } else {
@@ -878,7 +878,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             pa.work.G = pa.l1.G;
             {
             ProfScope prof(VER_PROF_LSTM_REC_BWD, s);
-            VER_BWD_DISPATCH(lstm_pipe_bwd_kernel, pa);
+            if (alone) VER_BWD_DISPATCH(lstm_pipe_bwd_planned_kernel, pa); else VER_BWD_DISPATCH(lstm_pipe_bwd_kernel, pa);
             if (!ok) return VER_EHIP;
             }
             layer_grads(l, nullptr, true, false);   // the weight gradients of both layers leave in one grouped launch
