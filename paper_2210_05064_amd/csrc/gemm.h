@@ -146,7 +146,7 @@ __device__ __forceinline__ void tile_store(const TileRegs<MODE>& regs, typename 
 // gridDim.z > 1: block z contracts k in [z*k_chunk, (z+1)*k_chunk) and writes its partial tile to
 // C + z*split_stride without bias and without the row permutation (gemm_reduce_kernel applies both).
 template <int MODE, bool TRANS>
-__global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(
+static __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(
     const typename LdsElem<MODE>::type* __restrict__ A, int lda, const typename LdsElem<MODE>::type* __restrict__ B, int ldb,
     float* __restrict__ C, int ldc, int Mr, int Nc, int K, const float* __restrict__ bias, int unperm_h, int k_chunk, size_t split_stride, const int* __restrict__ alone) {
     if (alone && *alone == 0) return;   // (gemm_group.h)
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(
 }
 
 // C[perm(m)][n] = sum_z part[z][m][n] (+ bias[n]), z ascending.
-__global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restrict__ part, int splits, size_t split_stride,
+static __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restrict__ part, int splits, size_t split_stride,
                                                           int Mr, int Nc, float* __restrict__ C, int ldc,
                                                           const float* __restrict__ bias, int unperm_h, const int* __restrict__ alone) {
     if (alone && *alone == 0) return;
@@ -449,7 +449,7 @@ __device__ __forceinline__ void gemm_tn_dma_body(
 // (plain kernels around the template body: the transposing-load builtin only exists in the device pass)
 // Several such contractions in one launch, their tiles in the order of the list: widths whose rows make no even bands for
 // the grouped launch below.
-__global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_tn_dma_list_kernel(GemmGroupArgs g) {
+static __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_tn_dma_list_kernel(GemmGroupArgs g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int t = group_tile(g.tiles);
     if (t < 0) return;
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_tn_dma_list_kernel(GemmG
     gemm_tn_dma_body<4>(static_cast<const bf16_t*>(q.A), q.lda, static_cast<const bf16_t*>(q.B), q.ldb, q.C, q.ldc, q.Mr, q.Nc, q.K, q.unperm_h,
                         smem, r % q.tiles_n, r / q.tiles_n);
 }
-__global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_tn_dma_list_tall_kernel(GemmGroupArgs g) {
+static __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_tn_dma_list_tall_kernel(GemmGroupArgs g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int t = group_tile(g.tiles);
     if (t < 0) return;
@@ -516,11 +516,11 @@ __device__ __forceinline__ void gemm_tn_dma_group_body(const TnGroupArgs g, unsi
         gemm_tn_dma_body<WM>(q.A, q.lda, q.B, q.ldb, q.C, q.ldc, q.Mr, q.Nc, q.K, q.unperm_h, smem, bx, by);
 #endif
 }
-__global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_tn_dma_group_kernel(TnGroupArgs g) {
+static __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_tn_dma_group_kernel(TnGroupArgs g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     gemm_tn_dma_group_body<4>(g, smem);
 }
-__global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_tn_dma_group_tall_kernel(TnGroupArgs g) {
+static __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_tn_dma_group_tall_kernel(TnGroupArgs g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     gemm_tn_dma_group_body<8>(g, smem);
 }

@@ -16,7 +16,7 @@
 #include <mutex>
 
 #include "gemm_group.h"
-#include "lstm_pipe.h"
+#include "lstm_launch.h"
 
 namespace ver {
 namespace {
@@ -480,12 +480,6 @@ inline int rec_tiles(size_t tile_bytes, size_t red_bytes_per_tile) {
     return n < 1 ? 1 : (n > REC_NTC ? REC_NTC : n);
 }
 
-template <typename K>
-inline bool set_lds(K kernel, size_t bytes) {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)bytes) == hipSuccess;
-}
-
 // C[M, N] = A[M, K] B[N, K]^T (+ bias), all three row-major, A and B in the operand type.  bf16 in 64 x 64 tiles while those
 // are at most four per CU (us, 64 x 64 and 128 x 256 tiles: 1024 tiles, 1000 x 4096 x 1044 28 and 28, 2048 x 2048 x 516 15.4 and
 // 16.5; 940, 3001 x 1280 x 320 9.0 and 12; 235, 3001 x 320 x 1280 8.8 and 21; 4096, 8192 x 4096 x 1044 210 and 114); where one column of
@@ -671,32 +665,13 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         ra.G = H / (4 * mt); ra.ntc = ntc; ra.alone = nullptr;
         return ra;
     };
-    bool ok = true;
-#define VER_FWD_LAUNCH(KERNEL, ARGS, TPW_, KS_, NBW_, ST_) do { ok = set_lds(KERNEL<MODE, TPW_, KS_, NBW_, ST_>, lds); \
-        if (ok) hipLaunchKernelGGL((KERNEL<MODE, TPW_, KS_, NBW_, ST_>), dim3(REC_GRID), dim3(REC_THREADS), lds, s, ARGS); } while (0)
-#define VER_FWD_DISPATCH(KERNEL, ARGS) do { \
-        if constexpr (MODE == MODE_BF16) { \
-            if (wide) { \
-                if (!quarter && nb == 16) VER_FWD_LAUNCH(KERNEL, ARGS, 2, 2, 16, true); \
-                else VER_FWD_LAUNCH(KERNEL, ARGS, 2, 2, 16, false); \
-            } else { \
-                if (!quarter && nb == 8) VER_FWD_LAUNCH(KERNEL, ARGS, 1, 2, 8, true); \
-                else if (!quarter) VER_FWD_LAUNCH(KERNEL, ARGS, 1, 2, 8, false); \
-                else if (nb == 4) VER_FWD_LAUNCH(KERNEL, ARGS, 2, 4, 4, true); \
-                else VER_FWD_LAUNCH(KERNEL, ARGS, 2, 4, 4, false); \
-            } \
-        } else { \
-            if (nb == 8) VER_FWD_LAUNCH(KERNEL, ARGS, 2, 4, 8, true); \
-            else VER_FWD_LAUNCH(KERNEL, ARGS, 2, 4, 8, false); \
-        } } while (0)
-
+    const FwdForm form{wide, quarter, nb, lds};
     // The time loop of one layer in a launch of its own.
     auto loop_alone = [&](int l, int* flags, const int* alone) {
         RecFwdArgs ra = rec_args(l);
         ra.flags = flags; ra.ticket = flags + 8 * REC_MAX_GROUP; ra.alone = alone;
         ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
-        VER_FWD_DISPATCH(lstm_rec_fwd_kernel, ra);
-        return ok;
+        return launch_fwd_loop<MODE>(form, ra, s);
     };
     // bf16: what the layer above layer l contracts (a two-layer launch writes that of its lower layer itself)
     auto copy_h = [&](int l, const int* alone) {
@@ -726,8 +701,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             pipe_work(ws, 0, M, t_off, alone, &pa.work);
             pa.work.G = pa.l0.G;
             ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
-            if (alone) VER_FWD_DISPATCH(lstm_pipe_fwd_planned_kernel, pa); else VER_FWD_DISPATCH(lstm_pipe_fwd_kernel, pa);
-            if (!ok) return VER_EHIP;
+            if (!launch_fwd_pair<MODE>(form, pa, alone != nullptr, s)) return VER_EHIP;
             l += 2;
         } else {
             if (l > 0) fill_words(ws.flags, REC_FLAG_WORDS, 0, s);
@@ -736,8 +710,6 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         }
         if (l < c.n_layers) copy_h(l - 1, nullptr);
     }
-#undef VER_FWD_DISPATCH
-#undef VER_FWD_LAUNCH
     ProfScope prof(VER_PROF_HEADS_FWD, s);
     hipLaunchKernelGGL(heads_fwd_kernel, dim3((M + 15) / 16), dim3(256), 0, s, ws.layer[c.n_layers - 1].hout, M, H, A,
                        w[4 * c.n_layers], w[4 * c.n_layers + 1], w[4 * c.n_layers + 2], w[4 * c.n_layers + 3],
@@ -800,25 +772,12 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         return ra;
     };
     bool ok = true;
-#define VER_BWD_LAUNCH(KERNEL, ARGS, MT_, KS_, N_) do { ok = set_lds(KERNEL<MODE, MT_, KS_, N_>, lds); \
-        if (ok) hipLaunchKernelGGL((KERNEL<MODE, MT_, KS_, N_>), dim3(REC_GRID), dim3(REC_THREADS), lds, s, ARGS); } while (0)
-#define VER_BWD_DISPATCH(KERNEL, ARGS) do { \
-        if (wide) { \
-            if constexpr (MODE == MODE_BF16) {   /* (fp32: hidden <= 512) */ \
-                if (ni == 32) VER_BWD_LAUNCH(KERNEL, ARGS, 2, 4, 32); else VER_BWD_LAUNCH(KERNEL, ARGS, 2, 4, 0); \
-            } \
-        } else { \
-            if (ni == 16) VER_BWD_LAUNCH(KERNEL, ARGS, 1, 8, 16); \
-            else if (ni == 8) VER_BWD_LAUNCH(KERNEL, ARGS, 1, 8, 8); \
-            else if (ni == 4) VER_BWD_LAUNCH(KERNEL, ARGS, 1, 8, 4); \
-            else VER_BWD_LAUNCH(KERNEL, ARGS, 1, 8, 0); \
-        } } while (0)
+    const BwdForm form{wide, ni, lds};
     auto loop_alone = [&](int l, const float* dh_above, int* flags, const int* alone) {
         RecBwdArgs ra = rec_args(l, dh_above);
         ra.flags = flags; ra.ticket = flags + 8 * REC_MAX_GROUP; ra.alone = alone;
         ProfScope prof(VER_PROF_LSTM_REC_BWD, s);
-        VER_BWD_DISPATCH(lstm_rec_bwd_kernel, ra);
-        return ok;
+        return launch_bwd_loop<MODE>(form, ra, s);
     };
     // gradient w.r.t. the layer input: dx[M, D] = dz[M, 4H] . W_ih[4H, D]
     auto input_grad = [&](int l, float* dx, const int* alone) {
@@ -878,8 +837,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             pa.work.G = pa.l1.G;
             {
             ProfScope prof(VER_PROF_LSTM_REC_BWD, s);
-            if (alone) VER_BWD_DISPATCH(lstm_pipe_bwd_planned_kernel, pa); else VER_BWD_DISPATCH(lstm_pipe_bwd_kernel, pa);
-            if (!ok) return VER_EHIP;
+            if (!launch_bwd_pair<MODE>(form, pa, alone != nullptr, s)) return VER_EHIP;
             }
             layer_grads(l, nullptr, true, false);   // the weight gradients of both layers leave in one grouped launch
             layer_grads(l - 1, l > 1 ? ws.dh[cur] : d_x, true, true);
@@ -894,8 +852,6 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             l -= 1;
         }
     }
-#undef VER_BWD_DISPATCH
-#undef VER_BWD_LAUNCH
     return launch_status();
 }
 

@@ -1,0 +1,6 @@
+// One layer per launch, backward, bf16: see lstm_launch.h.
+#include "lstm_launch_bwd.h"
+
+namespace ver {
+template bool launch_bwd_loop<MODE_BF16>(const BwdForm&, const RecBwdArgs&, hipStream_t);
+}  // namespace ver

@@ -1,0 +1,6 @@
+// One layer per launch, backward, fp32: see lstm_launch.h.
+#include "lstm_launch_bwd.h"
+
+namespace ver {
+template bool launch_bwd_loop<MODE_F32>(const BwdForm&, const RecBwdArgs&, hipStream_t);
+}  // namespace ver

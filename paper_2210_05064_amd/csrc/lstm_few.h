@@ -8,14 +8,14 @@
 //    of a slot holds FEW_EMPTY, which no published word equals (see few_word), so a reader polls the values it needs
 //    and has them when the poll succeeds: no flag, no wait for a store's acknowledgement, no barrier, no copy.
 //  * Each of the 8 waves owns an eighth of the contraction (all gate rows of the workgroup) and polls just that
-//    slice of the rows.  Up to 4 pieces: straight into the operand registers of the product.  The 16 rows of an
+//    slice of the rows.  Up to 4 pieces (lstm_quad.h): straight into the operand registers of the product.  The 16 rows of an
 //    operand hold P pieces x 16/P operand blocks, so that a load instruction is full and four neighbouring lanes
 //    read 64 contiguous bytes (lanes of a quad that read different lines cost a cycle each); a block is brought to
 //    its piece's first row by rotating the lanes of a row (DPP), the other rows of the operand are whatever they are (a
 //    row of A only reaches the same row of the result).  fp32 reads its values as DPP broadcasts.  More pieces: in
 //    the order of memory into registers, and through a piece of LDS of the wave's own into operand order.
-//  * The partial sums of the waves meet in LDS (two buffers, one barrier per timestep); a thread then owns one
-//    (piece, unit) and keeps its cell state (backward: both carried gradients) in registers.
+//  * The partial sums of the waves meet in LDS; a thread (up to 4 pieces: four lanes, two buffers, one barrier per
+//    timestep) then owns one (piece, unit) and keeps its cell state (backward: both carried gradients) in registers.
 //  * Everything that is not on the way from one exchange to the next (saved activations, copies for other XCDs,
 //    prefetches) is issued right after a poll has succeeded, so that it completes behind the product: memory
 //    operations of a wave complete in order, and what is queued before a poll delays it.
@@ -25,12 +25,16 @@
 //
 // Bound by the latency of its phases: about 0.6 us for the exchange alone (a kernel that does nothing else), 0.43 us for
 // the MFMAs of one 16-row tile at H = 1024 (1.7 us in fp32 at H = 512), then the partial sums through LDS and the cell
-// update.  Microseconds per timestep (one layer), flag protocol -> this form:
-//     alive pieces                     1             2             4             8             16
-//     bf16, H = 1024   forward    2.36 -> 1.31  2.36 -> 1.28  2.44 -> 1.32  2.69 -> 1.91  3.31 -> 2.04
-//                      backward   2.23 -> 1.56  3.11 -> 1.85  3.26 -> 2.05  3.79 -> 2.32  4.80 -> 3.09
-//     fp32, H = 512    forward    2.20 -> 1.16  2.73 -> 1.47  3.75 -> 2.23  3.86 -> 3.00  4.38 -> 3.26
-//                      backward   2.78 -> 1.37  3.65 -> 2.03  4.30 -> 3.31  4.69 -> 3.73  5.70 -> 4.58
+// update.  Microseconds per timestep (two layers in one launch, time of a launch against its timesteps), a thread per (piece,
+// unit) throughout -> four lanes up to 4 pieces:
+//     alive pieces                     1             2             4             8      16
+//     bf16, H = 1024   forward    1.34 -> 1.23  1.35 -> 1.29  1.40 -> 1.47     1.9    3.2
+//                      backward   1.58 -> 1.64  1.84 -> 1.73  2.21 -> 2.18     2.4    3.3
+//     bf16, H = 512    forward    1.05 -> 0.87  1.06 -> 0.90  1.05 -> 0.95     1.3    1.8
+//                      backward   1.37 -> 1.15  1.38 -> 1.17  1.55 -> 1.38     1.5    2.1
+//     fp32, H = 512    forward    1.21 -> 1.15  1.51 -> 1.43  2.14 -> 2.08     3.0    4.9
+//                      backward   1.46 -> 1.28  2.05 -> 1.83  3.07 -> 2.77     3.6    4.5
+// (the flag protocol took 2.2 to 2.4 us with one piece and 3.3 to 5.7 with 16.)
 // What mattered after the exchange itself: four neighbouring lanes on contiguous memory (16 pieces forward 2.74 -> 2.04 us,
 // backward 5.25 -> 2.99), reading the eight partial sums without a branch per share (0.2 us per timestep), and no wait
 // for a prefetch before the next poll (0.1 us).
@@ -106,13 +110,17 @@ __device__ __forceinline__ void few_touch(int& v) { asm volatile("" : "+v"(v)); 
 // A word to publish: never FEW_EMPTY (only a pair of NaNs, or an fp32 NaN, has these bits; it stays NaN).
 __device__ __forceinline__ unsigned few_word(unsigned v) { return v == FEW_EMPTY ? FEW_EMPTY - 1 : v; }
 
-// Reads L x 16 bytes per lane at base + off[j]; with `check` again and again until no word is empty.  The loads
+// Reads L x 16 bytes per lane at from + off[j]; with `check` again and again until no word is empty.  The loads
 // bypass the CU's L1 (sc0 sc1) and are written out because the compiler waits for every volatile load by itself.
 // Lanes that do not `take` part keep what raw holds.  False: the wait was abandoned (time-out here or in another
 // workgroup).
 template <int L>
-__device__ __forceinline__ bool few_read(const unsigned char* base, const unsigned (&off)[L], bool take, bool check, u32x4_t (&raw)[L], int* err) {
+__device__ __forceinline__ bool few_read(const unsigned char* from, const unsigned (&off)[L], bool take, bool check, u32x4_t (&raw)[L], int* err) {
     static_assert(L == 1 || L == 2 || L == 4 || L == 8, "loads per poll");
+    // (the same for all lanes, which the asm needs and the compiler does not always see)
+    const unsigned long long at = reinterpret_cast<unsigned long long>(from);
+    const unsigned char* base = reinterpret_cast<const unsigned char*>(
+        (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)at) | (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32);
     long long spins = 0;
     for (;;) {
         unsigned m = 0;
@@ -140,7 +148,7 @@ __device__ __forceinline__ bool few_read(const unsigned char* base, const unsign
         }
         if (!check || __all(m != FEW_EMPTY)) return true;
         ++spins;
-        if ((spins & 1023) == 0 && (spins > REC_SPIN_LIMIT || ld_agent(err) != 0)) {
+        if ((spins & 1023) == 0 && (spins > REC_SPIN_LIMIT || __builtin_amdgcn_readfirstlane(ld_agent(err)) != 0)) {
             st_agent(err, 1);
             return false;
         }
@@ -355,6 +363,17 @@ __device__ __forceinline__ void few_clear_ring(unsigned char* ring, int row_elem
         reinterpret_cast<unsigned*>(ring)[(size_t)(i / words) * (row_elems * es / 4) + j0 * es / 4 + i % words] = FEW_EMPTY;
 }
 
+// Up to QUAD_MAX pieces: lstm_quad.h.
+constexpr int QUAD_MAX = 4;
+template <int MODE, int MT, int NB> struct FewFwd;
+template <int MODE, int MT, int NB> struct FewBwd;
+template <int MODE, int MT, int NB, int PIPE>
+__device__ __forceinline__ bool quad_fwd(FewFwd<MODE, MT, NB>& s, const RecFwdArgs& a, const PieceSet& ps, int rank, int* flags, unsigned char* ring, const PipeLink& pl, int& t,
+                         int T);
+template <int MODE, int MT, int NB, int PIPE>
+__device__ __forceinline__ bool quad_bwd(FewBwd<MODE, MT, NB>& s, const RecBwdArgs& a, const PieceSet& ps, int rank, unsigned char* ring, const PipeLink& pl, int& t, int T,
+                         int t_stop);
+
 // ---- forward ------------------------------------------------------------------------------------------------
 // What a group's workgroup carries through its timesteps with few pieces.
 template <int MODE, int MT, int NB>
@@ -405,30 +424,21 @@ __device__ __forceinline__ void few_fwd_store(const FewFwd<MODE, MT, NB>& s, con
     }
 }
 
-// Runs timesteps while more than `down_to` (and at most P) pieces are alive.  False: a wait was abandoned.
-template <int MODE, int MT, int NB, int P, int PIPE>
+// Runs timesteps while more than QUAD_MAX (and at most FEW_MAX) pieces are alive.  False: a wait was abandoned.
+template <int MODE, int MT, int NB, int PIPE>
 __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const RecFwdArgs& a, const PieceSet& ps, int rank, int* flags,
-                                              unsigned char* ring, const PipeLink& pl, int& t, int T, int down_to) {
+                                              unsigned char* ring, const PipeLink& pl, int& t, int T) {
     typedef typename RecGeom<MODE>::E E;
     constexpr int es = (int)sizeof(E);
-    constexpr int UH = 4 * MT, COLS = 16 * MT, ROW = few_row(COLS), PP = P > 4 ? 16 : 4;
-    constexpr bool STAGED = P > 4;
-    constexpr int BPL = 16 / P, L = STAGED ? 1 : (NB + BPL - 1) / BPL;
+    constexpr int UH = 4 * MT, COLS = 16 * MT, ROW = few_row(COLS);
     const int X = ps.X, x = ps.x, H = a.H;
-    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
+    const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = tid / UH, u = tid % UH, j0 = rank * UH;
-    const int piece = lr / BPL, blk = lr % BPL;
     const unsigned slice_off = (unsigned)(s.slice * NB) * 64u;                          // bytes: an operand block is 64
-    const unsigned k_off = slice_off + (unsigned)(lk * s.n_blk + blk) * 16u;   // this lane's first 16 bytes inside a row
     const unsigned slot = (unsigned)few_slot_bytes(MODE, H);
     const unsigned w_off = (unsigned)(m * H + j0 + u) * es;   // where this thread's value goes inside a slot
     const bool polls = s.slice < s.n_slices;
-    unsigned off[L];
-    few_offsets<L, BPL>(off, (unsigned)(piece * H) * es + k_off, blk, s.n_blk);
-    u32x4_t raw[L];
-#pragma unroll
-    for (int j = 0; j < L; ++j) raw[j] = u32x4_t{0u, 0u, 0u, 0u};
     unsigned char* stage = reinterpret_cast<unsigned char*>(s.part + few_part_floats(COLS)) + wave * few_stage_bytes(NB);
     bar_lds();   // (the partial sums of the phase before have been read)
     few_clear_part<COLS>(s.part);
@@ -437,7 +447,7 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
     const __amdgpu_buffer_rsrc_t rs_g = __builtin_amdgcn_make_buffer_rsrc(a.gates, 0, WHOLE, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_ring = __builtin_amdgcn_make_buffer_rsrc(ring, 0, (int)(FEW_RING * slot), 0x00020000);
 
-    auto step = [&](f32x4_t& z, f32x4_t& z_next) -> bool {
+    auto step = [&](f32x4_t& z, f32x4_t& z_next) __attribute__((always_inline)) -> bool {
         const int bs = grp_count(s.bs_a, ps), bs_next = t + 1 < T ? grp_count(s.bs_b, ps) : 0;
         const int base_next = s.base + s.bs_a;
         s.win.advance(t + 2);
@@ -453,18 +463,11 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
             if (PIPE == PIPE_PRODUCER && rank == 0 && tid == 0 && t > 0) st_agent(pl.progress, t);
             if (polls) {
                 const unsigned char* rows = reinterpret_cast<const unsigned char*>(static_cast<const E*>(a.hprev) + (size_t)(s.base + x) * H);
-                if constexpr (STAGED) {
-                    few_stage_read<NB>(rows, (unsigned)(X * H) * es, slice_off, s.n_blk, bs, false, stage, a.err);
-                } else {
-                    unsigned first[L];
-                    few_offsets<L, BPL>(first, (unsigned)(piece * X * H) * es + k_off, blk, s.n_blk);
-                    few_read<L>(rows, first, piece < bs && blk < s.n_blk, false, raw, a.err);
-                }
+                few_stage_read<NB>(rows, (unsigned)(X * H) * es, slice_off, s.n_blk, bs, false, stage, a.err);
             }
         } else if (polls) {
             const unsigned char* rows = ring + (unsigned)((t - 1) & (FEW_RING - 1)) * slot;
-            if constexpr (STAGED) ok = few_stage_read<NB>(rows, (unsigned)H * es, slice_off, s.n_blk, bs, true, stage, a.err);
-            else ok = few_read<L>(rows, off, piece < bs && blk < s.n_blk, true, raw, a.err);
+            ok = few_stage_read<NB>(rows, (unsigned)H * es, slice_off, s.n_blk, bs, true, stage, a.err);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (also: this wave's stores of two timesteps ago have completed)
         few_touch(z);
@@ -487,22 +490,17 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
             if (t + 3 < T && t + 3 == s.c_wait * pl.ct && tid == REC_THREADS - 1) s.have = ld_agent(&pl.done[s.c_wait]);
         }
         if (t > s.t0) few_fwd_store<MODE, MT, NB, PIPE>(s, a, ps, j0, grp_count(s.base - s.base_prev, ps), s.base, bs);
-        float* part = s.part + (STAGED ? 0 : (t & 1) * (REC_WAVES * PP * ROW));
+        float* part = s.part;
         if (polls) {
             f32x4_t acc[MT];
 #pragma unroll
             for (int j = 0; j < MT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            if constexpr (STAGED) {
-                few_stage_product<MODE, MT, NB, false>(s.w, stage, s.part + 16 * MT, s.n_blk, acc, [] {});
-                few_stage_write<MT>(acc, bs, part + s.slice * (PP * ROW));
-            } else {
-                few_product<MODE, MT, NB, P, L>(s.w, raw, bs, s.n_blk, acc);
-                few_write<MODE, MT, P>(acc, bs, part + s.slice * (PP * ROW));
-            }
+            few_stage_product<MODE, MT, NB, false>(s.w, stage, s.part + 16 * MT, s.n_blk, acc, [] {});
+            few_stage_write<MT>(acc, bs, part + s.slice * (16 * ROW));
         }
         bar_lds();
         const int failed = *s.fail;   // (looked at after the publication: its read is not waited for by itself)
-        if (look) s.ready = s.fail[1] >= pl.need;
+        if (look) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= pl.need;
         // Every workgroup has published the rows of timestep t-1, which it did after its stores for timestep t-3 had
         // completed (they are issued in timestep t-2 and waited for in timestep t-1).
         if (PIPE == PIPE_PRODUCER && rank == 0 && tid == REC_THREADS - 1 && t - 2 > s.t0) st_agent(pl.progress, t - 2);
@@ -510,7 +508,7 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
             f32x4_t q = z, o[REC_WAVES];
             const float* p = part + m * ROW + u * 4;
 #pragma unroll
-            for (int k = 0; k < REC_WAVES; ++k) o[k] = *reinterpret_cast<const f32x4_t*>(p + k * (PP * ROW));
+            for (int k = 0; k < REC_WAVES; ++k) o[k] = *reinterpret_cast<const f32x4_t*>(p + k * (16 * ROW));
 #pragma unroll
             for (int k = 0; k < REC_WAVES; ++k) {
                 q[0] += o[k][0]; q[1] += o[k][1]; q[2] += o[k][2]; q[3] += o[k][3];
@@ -532,8 +530,8 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
                 __builtin_amdgcn_raw_buffer_store_b32(FEW_EMPTY, rs_ring, w_off, (unsigned)((t + 2) & (FEW_RING - 1)) * slot, 0);
             }
         }
-        if (failed) return false;
-        if (STAGED) bar_lds();   // (one buffer of partial sums: it has been read)
+        if (__builtin_amdgcn_readfirstlane(failed)) return false;
+        bar_lds();   // (one buffer of partial sums: it has been read)
         s.base_prev = s.base;
         s.base = base_next;
         s.bs_a = s.bs_b;
@@ -543,9 +541,9 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
     };
     // (two steps per iteration: a prefetched value is used where it was loaded, a move would wait for the load)
     f32x4_t z2 = s.z;
-    while (t < T && grp_count(s.bs_a, ps) > down_to) {
+    while (t < T && grp_count(s.bs_a, ps) > QUAD_MAX) {
         if (!step(s.z, z2)) return false;
-        if (!(t < T && grp_count(s.bs_a, ps) > down_to)) {
+        if (!(t < T && grp_count(s.bs_a, ps) > QUAD_MAX)) {
             s.z = z2;
             break;
         }
@@ -554,11 +552,61 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
     return true;
 }
 
+// few_fwd and few_bwd take the address of the kernel's arguments and load them once more, and take everything else as values that
+// are made scalar here: their time loops shared the scalar registers with what the kernel keeps for its other forms and roles, and
+// fetched their own constants from spill lanes (64 to 88 v_readlane per backward timestep of a consumer, now 2 to 18).  (As calls, with
+// registers of their own, they save and restore a hundred vector registers per lane: 16 us per launch at H = 1024.)
+template <typename T> __device__ __forceinline__ T few_scalar(T v) {
+    if constexpr (sizeof(T) == 8) {
+        const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+        const unsigned long long u = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)b) |
+                                     (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(b >> 32)) << 32;
+        return __builtin_bit_cast(T, u);
+    } else {
+        return __builtin_bit_cast(T, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+    }
+}
+// A pointer that the compiler knows to be global (of one read from memory it does not, and a generic access also counts
+// as one to LDS).
+template <typename T> __device__ __forceinline__ void few_global(T*& p) { p = (T*)(__attribute__((address_space(1))) T*)p; }
+template <typename A> using few_args_t = const A __attribute__((address_space(4)))*;
+struct FewLink { PieceSet ps; PipeLink pl; };
+template <int PIPE>
+__device__ __forceinline__ FewLink few_link(int x, int cap, int id, int* progress, int* done, int need, int ct) {
+    FewLink l;
+    l.ps.x = few_scalar(x);
+    l.ps.X = PIPE == PIPE_NONE ? REC_GROUPS : 1;   // (PieceSet: dealt round-robin, or a block)
+    l.ps.cap = few_scalar(cap);
+    l.ps.id = few_scalar(id);
+    l.pl.progress = few_scalar(progress);
+    l.pl.done = few_scalar(done);
+    few_global(l.pl.progress);
+    few_global(l.pl.done);
+    l.pl.need = few_scalar(need);
+    l.pl.ct = few_scalar(ct);
+    l.pl.T = 0;
+    return l;
+}
+
 // Timesteps [t0, T): at most FEW_MAX pieces of the group are alive.  The rows of h_{t0-1} are in hprev, announced by
-// flag value t0 + 1.  False: a wait was abandoned.
+// flag value t0 + 1.  lds: where the dynamic LDS begins.  False: a wait was abandoned.
 template <int MODE, int MT, int PIPE>
-__device__ __forceinline__ bool few_fwd(const RecFwdArgs& a, const PieceSet& ps, int rank, int t0, int T, int* flags, const PipeLink& pl,
-                                        int c_wait, unsigned char* ring, unsigned char* smem) {
+__device__ __forceinline__ bool few_fwd(few_args_t<RecFwdArgs> args, int x_, int cap_, int id_, int rank_, int t0_, int T_, int* flags_, int* progress_,
+                                                  int* done_, int need_, int ct_, int c_wait_, unsigned lds_) {
+    const FewLink link = few_link<PIPE>(x_, cap_, id_, progress_, done_, need_, ct_);
+    const PieceSet& ps = link.ps;
+    const PipeLink& pl = link.pl;
+    const int rank = few_scalar(rank_), t0 = few_scalar(t0_), T = few_scalar(T_), c_wait = few_scalar(c_wait_);
+    int* flags = few_scalar(flags_);
+    few_global(flags);
+    RecFwdArgs a = *(const RecFwdArgs*)few_scalar(args);
+    few_global(a.batch_sizes); few_global(a.t_off); few_global(a.gates); few_global(a.c); few_global(a.hout);
+    few_global(a.c0); few_global(a.err);
+    a.hprev = (void*)(__attribute__((address_space(1))) void*)a.hprev;
+    a.whh = (const void*)(__attribute__((address_space(1))) const void*)a.whh;
+    a.ring = (void*)(__attribute__((address_space(1))) void*)a.ring;
+    unsigned char* ring = static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, a.H);
+    unsigned char* smem = (unsigned char*)(__attribute__((address_space(3))) unsigned char*)few_scalar(lds_);
     typedef typename RecGeom<MODE>::E E;
     constexpr int KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC, UH = 4 * MT;
     constexpr int NB = FewBlocks<MODE, MT == 8>::fwd;
@@ -607,9 +655,9 @@ __device__ __forceinline__ bool few_fwd(const RecFwdArgs& a, const PieceSet& ps,
         else if (a.c0 && n < a.seq_cap) s.c = a.c0[(size_t)n * H + j0 + u];
     }
     int t = t0;
-    if (!few_fwd_phase<MODE, MT, NB, 16, PIPE>(s, a, ps, rank, flags, ring, pl, t, T, 4)) return false;
-    if (!few_fwd_phase<MODE, MT, NB, 4, PIPE>(s, a, ps, rank, flags, ring, pl, t, T, 0)) return false;
-    few_fwd_store<MODE, MT, NB, PIPE>(s, a, ps, j0, grp_count(s.base - s.base_prev, ps), s.base, 0);
+    if (!few_fwd_phase<MODE, MT, NB, PIPE>(s, a, ps, rank, flags, ring, pl, t, T)) return false;
+    if (t > t0) few_fwd_store<MODE, MT, NB, PIPE>(s, a, ps, j0, grp_count(s.base - s.base_prev, ps), s.base, t < T ? grp_count(s.bs_a, ps) : 0);
+    if (t < T && !quad_fwd<MODE, MT, NB, PIPE>(s, a, ps, rank, flags, ring, pl, t, T)) return false;
     if (PIPE == PIPE_PRODUCER) rec_publish(flags, rank, T + 1);
     return true;
 }
@@ -653,30 +701,21 @@ __device__ __forceinline__ void few_load_saved(FewSaved& sv, const RecBwdArgs& a
     if (bs_q > bs_q_up && m >= bs_q_up) sv.c = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_c, col * 4u, so * 4u, 0));
 }
 
-// Runs timesteps t, t-1, ... >= t_stop while at most `up_to` (<= P) pieces are alive.  False: a wait was abandoned.
-template <int MODE, int MT, int NB, int P, int PIPE>
+// Runs timesteps t, t-1, ... >= t_stop while at most FEW_MAX pieces are alive.  False: a wait was abandoned.
+template <int MODE, int MT, int NB, int PIPE>
 __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const RecBwdArgs& a, const PieceSet& ps, int rank, unsigned char* ring,
-                                              const PipeLink& pl, int& t, int T, int t_stop, int up_to) {
+                                              const PipeLink& pl, int& t, int T, int t_stop) {
     typedef typename RecGeom<MODE>::E E;
     constexpr int es = (int)sizeof(E);
-    constexpr int UH = 16 * MT, ROW = few_row(UH), PP = P > 4 ? 16 : 4;
-    constexpr bool STAGED = P > 4;
-    constexpr int BPL = 16 / P, L = STAGED ? 1 : (NB + BPL - 1) / BPL;
+    constexpr int UH = 16 * MT, ROW = few_row(UH);
     const int X = ps.X, x = ps.x, H = a.H, K = 4 * H;
-    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
+    const int tid = threadIdx.x;
     const int m = tid / UH, u = tid % UH, j0 = rank * UH, n = m * X + x, j = j0 + u;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int piece = lr / BPL, blk = lr % BPL;
     const unsigned slice_off = (unsigned)(s.slice * NB) * 64u;
-    const unsigned k_off = slice_off + (unsigned)(lk * s.n_blk + blk) * 16u;
     const unsigned slot = (unsigned)few_slot_bytes(MODE, K);
     const unsigned w_off = (unsigned)(m * K + j * 4) * es;
     const bool polls = s.slice < s.n_slices;
-    unsigned off[L];
-    few_offsets<L, BPL>(off, (unsigned)(piece * K) * es + k_off, blk, s.n_blk);
-    u32x4_t raw[L];
-#pragma unroll
-    for (int i = 0; i < L; ++i) raw[i] = u32x4_t{0u, 0u, 0u, 0u};
     unsigned char* stage = reinterpret_cast<unsigned char*>(s.part + few_part_floats(UH)) + wave * few_stage_bytes(NB);
     bar_lds();   // (the partial sums of the phase before have been read)
     few_clear_part<UH>(s.part);
@@ -691,7 +730,7 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
     };
 
     // sv: what the forward pass saved for timestep t; other: for timestep t - 1, requested a timestep ago
-    auto step = [&](FewSaved& sv, FewSaved& other) -> bool {
+    auto step = [&](FewSaved& sv, FewSaved& other) __attribute__((always_inline)) -> bool {
         s.win.advance(t - 3);
         const int bs = grp_count(s.bs_t, ps), bs_up = t + 1 < T ? grp_count(s.bs_up, ps) : 0;
         wv_t word;
@@ -732,10 +771,7 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
         // B. dh carried to t-1: dh[piece][k] = sum_q dz[piece][q] * W_hh[q][k] for this workgroup's columns k
         const unsigned char* src = ring + (unsigned)(t & (FEW_RING - 1)) * slot;
         bool ok = true;
-        if (polls) {
-            if constexpr (STAGED) ok = few_stage_read<NB>(src, (unsigned)K * es, slice_off, s.n_blk, bs, true, stage, a.err);
-            else ok = few_read<L>(src, off, piece < bs && blk < s.n_blk, true, raw, a.err);
-        }
+        if (polls) ok = few_stage_read<NB>(src, (unsigned)K * es, slice_off, s.n_blk, bs, true, stage, a.err);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (also: this wave's dz rows of timestep t+1 have completed)
         few_touch(other.g);
         few_touch(other.c_prev);
@@ -759,22 +795,17 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
             if (look) s.have = 0;
             if (t >= 4 && t - 4 == s.c_wait * pl.ct - 1 && tid == REC_THREADS - 1) s.have = ld_agent(&pl.done[s.c_wait - 1]);
         }
-        float* part = s.part + (STAGED ? 0 : (t & 1) * (REC_WAVES * PP * ROW));
+        float* part = s.part;
         if (polls) {
             f32x4_t acc[MT];
 #pragma unroll
             for (int i = 0; i < MT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            if constexpr (STAGED) {
-                few_stage_product<MODE, MT, NB, false>(s.w, stage, s.part + 16 * MT, s.n_blk, acc, [] {});
-                few_stage_write<MT>(acc, bs, part + s.slice * (PP * ROW));
-            } else {
-                few_product<MODE, MT, NB, P, L>(s.w, raw, bs, s.n_blk, acc);
-                few_write<MODE, MT, P>(acc, bs, part + s.slice * (PP * ROW));
-            }
+            few_stage_product<MODE, MT, NB, false>(s.w, stage, s.part + 16 * MT, s.n_blk, acc, [] {});
+            few_stage_write<MT>(acc, bs, part + s.slice * (16 * ROW));
         }
         bar_lds();
         const int failed = *s.fail;
-        if (look) s.ready = s.fail[1] >= pl.need;
+        if (look) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= pl.need;
         // Every workgroup has published the rows of timestep t, which it did after its dz rows of timestep t+2 had
         // completed (they are stored in that timestep and waited for in timestep t+1).
         if (PIPE == PIPE_PRODUCER && rank == 0 && tid == REC_THREADS - 1 && t + 2 < T) st_agent(pl.progress, T - (t + 2));
@@ -782,14 +813,14 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
             float q = 0.f, o[REC_WAVES];
             const float* p = part + m * ROW + u;
 #pragma unroll
-            for (int k = 0; k < REC_WAVES; ++k) o[k] = p[k * (PP * ROW)];
+            for (int k = 0; k < REC_WAVES; ++k) o[k] = p[k * (16 * ROW)];
 #pragma unroll
             for (int k = 0; k < REC_WAVES; ++k) q += o[k];
             s.dh = q;
             store(wv_t(FEW_EMPTY), rs_ring, w_off, (unsigned)((t + 1) & (FEW_RING - 1)) * slot, FewIdx<0>{});
         }
-        if (failed) return false;
-        if (STAGED) bar_lds();   // (one buffer of partial sums: it has been read)
+        if (__builtin_amdgcn_readfirstlane(failed)) return false;
+        bar_lds();   // (one buffer of partial sums: it has been read)
         s.base -= s.bs_m1;
         s.bs_up = s.bs_t;
         s.bs_t = s.bs_m1;
@@ -798,24 +829,38 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
         --t;
         return true;
     };
-    while (t >= t_stop && grp_count(s.bs_t, ps) <= up_to) {
+    while (t >= t_stop) {
         if (!step(s.sv, s.sv2)) return false;
-        if (!(t >= t_stop && grp_count(s.bs_t, ps) <= up_to)) {
-            const FewSaved o = s.sv;
-            s.sv = s.sv2;
-            s.sv2 = o;
-            break;
-        }
+        if (t < t_stop) break;
         if (!step(s.sv2, s.sv)) return false;
     }
     return true;
 }
 
-// Timesteps T-1 .. t_stop: at most FEW_MAX pieces of the group are alive.  Leaves the carried gradients of this
-// thread's (piece, unit), the sums of its gate gradients and the lowest chunk waited for.  False: a wait was abandoned.
+// What the few-pieces form leaves of a thread's (piece, unit): the carried gradients, the sums of its gate gradients; and the
+// lowest chunk waited for.
+struct FewBwdOut {
+    float dh, dc, db[4];
+    int c_wait;
+    bool ok;   // false: a wait was abandoned
+};
+// Timesteps T-1 .. t_stop: at most FEW_MAX pieces of the group are alive.
 template <int MODE, int MT, int PIPE>
-__device__ __forceinline__ bool few_bwd(const RecBwdArgs& a, const PieceSet& ps, int rank, int t_stop, int T, const PipeLink& pl, int& c_wait,
-                                        unsigned char* ring, unsigned char* smem, float& dh, float& dc, float (&db)[4]) {
+__device__ __forceinline__ FewBwdOut few_bwd(few_args_t<RecBwdArgs> args, int x_, int cap_, int id_, int rank_, int t_stop_, int T_, int* progress_,
+                                                       int* done_, int need_, int ct_, int c_wait_, unsigned lds_) {
+    const FewLink link = few_link<PIPE>(x_, cap_, id_, progress_, done_, need_, ct_);
+    const PieceSet& ps = link.ps;
+    const PipeLink& pl = link.pl;
+    const int rank = few_scalar(rank_), t_stop = few_scalar(t_stop_), T = few_scalar(T_), c_wait = few_scalar(c_wait_);
+    RecBwdArgs a = *(const RecBwdArgs*)few_scalar(args);
+    few_global(a.batch_sizes); few_global(a.t_off); few_global(a.gates); few_global(a.c); few_global(a.dh_above);
+    few_global(a.c0); few_global(a.err);
+    a.dz = (void*)(__attribute__((address_space(1))) void*)a.dz;
+    a.whhT = (const void*)(__attribute__((address_space(1))) const void*)a.whhT;
+    a.ring = (void*)(__attribute__((address_space(1))) void*)a.ring;
+    unsigned char* ring = static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, 4 * a.H);
+    unsigned char* smem = (unsigned char*)(__attribute__((address_space(3))) unsigned char*)few_scalar(lds_);
+    const FewBwdOut gave_up = {};
     typedef typename RecGeom<MODE>::E E;
     constexpr int KBLK = RecGeom<MODE>::KBLK, VEC = RecGeom<MODE>::VEC, UH = 16 * MT;
     constexpr int NB = FewBlocks<MODE, MT == 2>::bwd, LOW = 16 / NB;
@@ -855,26 +900,26 @@ __device__ __forceinline__ bool few_bwd(const RecBwdArgs& a, const PieceSet& ps,
     s.sv.g = s.sv2.g = f32x4_t{0.f, 0.f, 0.f, 0.f};
     s.sv.c_prev = s.sv.dh_above = s.sv.c = s.sv2.c_prev = s.sv2.dh_above = s.sv2.c = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s.db[i] = db[i];
-    few_load_saved(s.sv, a, m, n, j, T - 1, grp_count(s.bs_t, ps), 0, s.base, s.base - s.bs_m1);
-    if (T > 1) {
-        if (PIPE == PIPE_CONSUMER && T - 2 < s.c_wait * pl.ct) {
-            --s.c_wait;
-            if (!pipe_wait_chunk(pl, s.c_wait, a.err)) return false;
-        }
-        const int base_1 = s.base - s.bs_m1;
-        few_load_saved(s.sv2, a, m, n, j, T - 2, grp_count(s.bs_m1, ps), grp_count(s.bs_t, ps), base_1, base_1 - s.bs_m2);
-    }
+    for (int i = 0; i < 4; ++i) s.db[i] = 0.f;
     int t = T - 1;
-    if (!few_bwd_phase<MODE, MT, NB, LOW, PIPE>(s, a, ps, rank, ring, pl, t, T, t_stop, LOW)) return false;
-    if (!few_bwd_phase<MODE, MT, NB, 4, PIPE>(s, a, ps, rank, ring, pl, t, T, t_stop, 4)) return false;
-    if (!few_bwd_phase<MODE, MT, NB, 16, PIPE>(s, a, ps, rank, ring, pl, t, T, t_stop, 16)) return false;
-    c_wait = s.c_wait;
-    dh = s.dh;
-    dc = s.dc;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) db[i] = s.db[i];
-    return true;
+    if (!quad_bwd<MODE, MT, NB, PIPE>(s, a, ps, rank, ring, pl, t, T, t_stop)) return gave_up;
+    if (t >= t_stop) {
+        if (PIPE == PIPE_CONSUMER)
+            while (s.c_wait > 0 && t - 1 < s.c_wait * pl.ct) {
+                --s.c_wait;
+                if (!pipe_wait_chunk(pl, s.c_wait, a.err)) return gave_up;
+                s.ready = false;
+            }
+        const int base_1 = s.base - s.bs_m1;
+        few_load_saved(s.sv, a, m, n, j, t, grp_count(s.bs_t, ps), t + 1 < T ? grp_count(s.bs_up, ps) : 0, s.base, base_1);
+        if (t > 0) few_load_saved(s.sv2, a, m, n, j, t - 1, grp_count(s.bs_m1, ps), grp_count(s.bs_t, ps), base_1, base_1 - s.bs_m2);
+        few_touch(s.sv.g); few_touch(s.sv.c_prev); few_touch(s.sv.dh_above); few_touch(s.sv.c);   // (the loads are complete before the loop)
+        few_touch(s.sv2.g); few_touch(s.sv2.c_prev); few_touch(s.sv2.dh_above); few_touch(s.sv2.c);
+        if (!few_bwd_phase<MODE, MT, NB, PIPE>(s, a, ps, rank, ring, pl, t, T, t_stop)) return gave_up;
+    }
+    return FewBwdOut{s.dh, s.dc, {s.db[0], s.db[1], s.db[2], s.db[3]}, s.c_wait, true};
 }
 
 }  // namespace ver
+
+#include "lstm_quad.h"

@@ -1,0 +1,6 @@
+// One layer per launch, forward, fp32: see lstm_launch.h.
+#include "lstm_launch_fwd.h"
+
+namespace ver {
+template bool launch_fwd_loop<MODE_F32>(const FwdForm&, const RecFwdArgs&, hipStream_t);
+}  // namespace ver

@@ -386,7 +386,7 @@ __device__ __forceinline__ void proj_tile_dma(const ProjWork& w, int row0, int r
 // C[M, N] = A[M, K] B[N, K]^T + bias (the input projection of the first layer).  One workgroup per tile; consecutive
 // workgroups (dealt round-robin to the XCDs) take the column tiles of one row tile, so that a row tile of A is fetched
 // from memory by one round of workgroups.
-__global__ __launch_bounds__(REC_THREADS) void lstm_proj_dma_kernel(ProjWork w, int tiles_n) {
+static __global__ __launch_bounds__(REC_THREADS) void lstm_proj_dma_kernel(ProjWork w, int tiles_n) {
     extern __shared__ __attribute__((aligned(16))) unsigned char proj_smem[];
     if (w.alone && *w.alone == 0) return;
     const int rt = blockIdx.x / tiles_n, ct = blockIdx.x % tiles_n;
@@ -670,8 +670,8 @@ __device__ __forceinline__ int xcc_ticket(int* tickets, int& xcc) {
         s_t = id < PIPE_XCDS ? __hip_atomic_fetch_add(&tickets[id], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : REC_MAX_GROUP;
     }
     __syncthreads();
-    xcc = s_x;
-    return s_t;
+    xcc = __builtin_amdgcn_readfirstlane(s_x);   // (see rec_rank)
+    return __builtin_amdgcn_readfirstlane(s_t);
 }
 
 struct PipeFwdArgs {

@@ -133,8 +133,9 @@ __device__ __forceinline__ int rec_rank(int* tickets, int G, int& grp) {
         s_grp = xcc;
     }
     __syncthreads();
-    grp = s_grp;
-    return s_rank;
+    // (uniform, which the compiler cannot know of a value read from LDS: branches on it and addresses formed with it stay scalar)
+    grp = __builtin_amdgcn_readfirstlane(s_grp);
+    return __builtin_amdgcn_readfirstlane(s_rank);
 }
 // Which pieces a group runs: n = x + m * X for m = 0 .. cap-1.  Dealt round-robin to X groups (x = group, cap
 // unbounded) or a block of consecutive pieces (x = first piece, X = 1, cap = pieces in the block).
@@ -156,7 +157,7 @@ __device__ __forceinline__ int grp_steps(const int32_t* batch_sizes, int T, int 
     for (int t = threadIdx.x; t < T; t += blockDim.x) cnt += batch_sizes[t] > x ? 1 : 0;
     if (cnt) atomicAdd(&s_T, cnt);
     __syncthreads();
-    const int steps = s_T;
+    const int steps = __builtin_amdgcn_readfirstlane(s_T);
     __syncthreads();
     return steps;
 }
@@ -180,7 +181,7 @@ __device__ __forceinline__ bool rec_wait(const int* flags, int G, int target, in
             const bool ok = pl >= G || ld_l2(&flags[pl]) >= target;
             if (__all(ok)) break;
             ++spins;
-            if ((spins & 1023) == 0 && (spins > REC_SPIN_LIMIT || ld_agent(err) != 0)) {
+            if ((spins & 1023) == 0 && (spins > REC_SPIN_LIMIT || __builtin_amdgcn_readfirstlane(ld_agent(err)) != 0)) {
                 if (pl == 0) st_agent(err, 1);
                 alive = false;
                 break;
@@ -189,7 +190,7 @@ __device__ __forceinline__ bool rec_wait(const int* flags, int G, int target, in
         if (pl == 0) s_ok = alive ? 1 : 0;
     }
     bar_lds();
-    return s_ok != 0;
+    return __builtin_amdgcn_readfirstlane(s_ok) != 0;   // (uniform, see rec_rank)
 }
 
 // Call after the exchanged rows were written: waits until this wave's stores have reached L2, then (after
@@ -366,7 +367,7 @@ __device__ __forceinline__ bool pipe_wait_chunk(const PipeLink& pl, int c, int* 
         while (have < pl.need) {
             have = ld_agent(&pl.done[c]);
             ++spins;
-            if ((spins & 255) == 0 && (spins > REC_SPIN_LIMIT || ld_agent(err) != 0)) {
+            if ((spins & 255) == 0 && (spins > REC_SPIN_LIMIT || __builtin_amdgcn_readfirstlane(ld_agent(err)) != 0)) {
                 st_agent(err, 1);
                 alive = false;
                 break;
@@ -378,7 +379,7 @@ __device__ __forceinline__ bool pipe_wait_chunk(const PipeLink& pl, int c, int* 
 #endif
     }
     bar_lds();
-    return s_ok2 != 0;
+    return __builtin_amdgcn_readfirstlane(s_ok2) != 0;
 }
 #ifdef VER_REC_PROF
 #define REC_PROF_CHUNK_ACC(a, rank, ps) ((rank) == 0 ? (a).prof_all + 88 + (ps).id : nullptr)
@@ -767,8 +768,9 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
     }
     }
     if (t0 < T) {
-        const RecFwdArgs f = args_again(a);
-        if (!few_fwd<MODE, MT, PIPE>(f, ps, rank, t0, T, flags, pl, c_wait, static_cast<unsigned char*>(f.ring) + ps.id * few_ring_bytes(MODE, f.H), smem)) return;
+        unsigned lds = (unsigned)(unsigned long long)(lds_ptr_t)smem;
+        asm volatile("" : "+v"(lds));   // (known to be the start of the dynamic LDS, it would be read from a table wherever it is used)
+        if (!few_fwd<MODE, MT, PIPE>((few_args_t<RecFwdArgs>)&a, ps.x, ps.cap, ps.id, rank, t0, T, flags, pl.progress, pl.done, pl.need, pl.ct, c_wait, lds)) return;
     }
     if (PIPE == PIPE_PRODUCER && rank == 0) {   // the last timestep is complete once every flag says so
         if (T > 0 && !rec_wait(flags, G, T + 1, a.err)) return;
@@ -809,8 +811,9 @@ __device__ __forceinline__ BwdSaved load_saved(const RecBwdArgs& a, int t, int b
 
 // MT 16-unit tiles per workgroup, KS waves per tile split the contraction over the 4H gate rows.
 template <int MODE, int MT, int KS, int NI, int PIPE>
-__device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& a, int rank, const PieceSet ps, int T, int* flags,
+__device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& by_ref, int rank, const PieceSet ps, int T, int* flags,
                                              const PipeLink& pl, unsigned char* smem) {
+    const RecBwdArgs& a = by_ref;   // (the two forms load what they use again, see args_again)
     const int x = ps.x, X = ps.X;
     static_assert(MT * KS == REC_WAVES, "one wave per (tile, k-split)");
     static_assert(MT * REC_NTC <= REC_WAVES, "one wave per tile sum");
@@ -828,20 +831,9 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& a, int rank, cons
     const int mt = wave / KS, ks = wave % KS;
     const int lr = lane & 15, lk = lane >> 4;
     const int j0 = rank * UH;
-    E* dzw = static_cast<E*>(a.dz);
     const int k_lo = ks * (K / KS);
     const int ni = (K / KS) / KBLK;
 
-    // The arrays as buffers that never change during the loop (host code guarantees that each is shorter than
-    // 2^31 bytes); where a timestep's rows begin is the scalar offset of an access, and this thread's first
-    // (piece, unit) sits at the same place inside every timestep's rows.
-    constexpr int WHOLE = (int)0x80000000u;
-    const __amdgpu_buffer_rsrc_t rs_dzall = __builtin_amdgcn_make_buffer_rsrc(dzw, 0, WHOLE, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rs_gates = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.gates), 0, WHOLE, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rs_cell = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.c), 0, WHOLE, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rs_above = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.dh_above), 0, WHOLE, 0x00020000);
-    const unsigned poff = (unsigned)(((tid / UH) * X + x) * H + j0 + (tid % UH)) * 4u;   // bytes inside an [rows, H] fp32 array
-    const unsigned row_h = 4u * (unsigned)H;
     float dcreg = 0.f;   // cell-state gradient of this thread's first (piece, unit), carried from timestep to timestep
     // Bias gradient: a thread always works on the same unit (the stride of its items is a multiple of UH), so it
     // adds up that unit's four gate gradients over all its items in registers; summed over threads after the loop.
@@ -859,7 +851,15 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& a, int rank, cons
         few_clear_ring<MODE>(ring, K, j0 * 4, UH * 4);
         rec_publish(flags, rank, 1);
         if (!rec_wait(flags, G, 1, a.err)) return;
-        if (!few_bwd<MODE, MT, PIPE>(a, ps, rank, t_few, T, pl, c_wait, ring, smem, dh_few, dcreg, db)) return;
+        unsigned lds = (unsigned)(unsigned long long)(lds_ptr_t)smem;
+        asm volatile("" : "+v"(lds));   // (known to be the start of the dynamic LDS, it would be read from a table wherever it is used)
+        const FewBwdOut out = few_bwd<MODE, MT, PIPE>((few_args_t<RecBwdArgs>)&by_ref, ps.x, ps.cap, ps.id, rank, t_few, T, pl.progress, pl.done, pl.need, pl.ct, c_wait, lds);
+        if (!__builtin_amdgcn_readfirstlane((int)out.ok)) return;
+        c_wait = __builtin_amdgcn_readfirstlane(out.c_wait);
+        dh_few = out.dh;
+        dcreg = out.dc;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) db[i] = out.db[i];
         if (t_few == 0 && PIPE == PIPE_PRODUCER) {   // the last rows are complete once every flag says so
             rec_publish(flags, rank, T + 1);
             if (rank == 0) {
@@ -869,6 +869,18 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& a, int rank, cons
         }
     }
     if (t_few > 0) {
+    const RecBwdArgs a = args_again(by_ref);
+    E* dzw = static_cast<E*>(a.dz);
+    // The arrays as buffers that never change during the loop (host code guarantees that each is shorter than
+    // 2^31 bytes); where a timestep's rows begin is the scalar offset of an access, and this thread's first
+    // (piece, unit) sits at the same place inside every timestep's rows.
+    constexpr int WHOLE = (int)0x80000000u;
+    const __amdgpu_buffer_rsrc_t rs_dzall = __builtin_amdgcn_make_buffer_rsrc(dzw, 0, WHOLE, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_gates = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.gates), 0, WHOLE, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_cell = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.c), 0, WHOLE, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_above = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.dh_above), 0, WHOLE, 0x00020000);
+    const unsigned poff = (unsigned)(((tid / UH) * X + x) * H + j0 + (tid % UH)) * 4u;   // bytes inside an [rows, H] fp32 array
+    const unsigned row_h = 4u * (unsigned)H;
     f32x4_t wreg[NW];
     {
         const E* wrow = static_cast<const E*>(a.whhT) + ((size_t)j0 + mt * 16 + lr) * K + k_lo + lk * VEC;
@@ -1035,7 +1047,8 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& a, int rank, cons
 }
 
 template <int MODE, int MT, int KS, int NI>
-__global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_rec_bwd_kernel(RecBwdArgs a) {
+__global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_rec_bwd_kernel(RecBwdArgs by_value) {
+    const RecBwdArgs& a = pipe_args_in_place<RecBwdArgs>(by_value);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     if (a.alone && *a.alone == 0) return;   // (before a ticket is taken)
     int grp;

@@ -582,3 +582,13 @@ def test_conversion_of_16_giga_elements(ver):
     assert u16.abs().min() > 1e-3
     # (another contraction kernel: sums in another order)
     assert ((u - u16[0]).abs() <= 1e-5 * u16[0].abs()).all() and ((v - v16[0]).abs() <= 1e-5 * v16[0].abs()).all()
+
+
+@pytest.mark.parametrize("n_envs,layers", [(1, 1), (2, 2), (5, 2), (9, 2), (14, 2), (40, 1)])
+@pytest.mark.parametrize("compute,hidden", [(0, 64), (0, 512), (1, 64), (1, 320), (1, 576)])
+def test_one_to_five_pieces_per_group(ver, compute, hidden, n_envs, layers):
+    """Groups that come from and go to one, two, four and five alive pieces: four lanes own a (piece, unit) up to four.
+    576 units: the last slice of the contraction has half of its operand blocks (1024 units: test_forms_of_the_time_loops; over so few
+    rows the largest of 4 million elements is at 7e-2 in any form)."""
+    w = wl.Workload("quad", n_envs, 24 * n_envs, 0, 0, 0.9, 20, layers, hidden, 1, 3, 0.01, 1, 1, bool(compute))
+    case(ver, w, seed=70 + n_envs, compute=compute, x_bf16=bool(compute))
