@@ -16,10 +16,10 @@
 // longest ones (its chain of T_max dependent steps is what bounds the launch, so its steps should be the
 // cheapest), the last group the many short ones (few steps, each with many pieces).  The plan
 // picks the two cuts that minimise the largest predicted group time
-//     sum over the group's timesteps of (step + piece * b_t + tile * (ceil(b_t / 16) - 1)),   b_t = alive pieces of the group
-// (a time loop works through the alive pieces 16 at a time: the MFMA's columns), which it evaluates per candidate
-// from the pieces' lengths: sum_t b_t = sum of the block's lengths (a prefix sum), and the timesteps with more
-// than 16 k alive pieces are those of the block's piece number 16 k.  Producer and
+//     sum over the group's timesteps of (step + low * min(b_t, 4) + over (b_t > 4) + piece * b_t + tile * (ceil(b_t / 16) - 1)),   b_t = alive pieces
+// (a time loop works through the alive pieces 16 at a time: the MFMA's columns; up to four have a form of their own), which it
+// evaluates per candidate from the pieces' lengths: sum_t b_t = sum of the block's lengths (a prefix sum), and the timesteps
+// with more than k alive pieces are those of the block's piece number k.  Producer and
 // consumer group g run the same block, and everything between them is per group: chunks of the group's own
 // timesteps, tiles over the group's own rows (gathered: a group's rows of a timestep are consecutive, those of
 // a chunk are not), completion counters of its own.  So a group never waits for another one: with
@@ -53,9 +53,10 @@ constexpr int PIPE_CT_MIN = 2, PIPE_CT_MAX = 8;
 inline __host__ __device__ int pipe_done_stride(int M) { return M / PIPE_CT_MIN + 2; }
 inline __host__ __device__ int pipe_sync_words(int M) { return 16 + PIPE_GROUPS * pipe_done_stride(M); }
 
-// Predicted microseconds of a timestep: step + piece * b + tile * (ceil(b / 16) - 1) (b alive pieces of the group).
+// Predicted microseconds of a timestep with b alive pieces of the group: step + low * min(b, 4) + over (more than four) + piece * b +
+// tile * (ceil(b / 16) - 1): up to four pieces, up to 16 and more run in forms of their own.
 struct PlanCost {
-    float step, piece, tile;
+    float step, low, over, piece, tile;
     int chunk_rows, dense;   // rows per chunk that groups of more than 16 pieces aim at from `dense` alive pieces per timestep on
                              // (average over the launch), where the workers set the pace; 0: never
     int few;                 // timesteps per chunk of groups of up to 16 pieces
@@ -76,19 +77,19 @@ constexpr int PLAN_CT_FEW = 8, PLAN_CT_FEW_FAST = 4, PLAN_CT_MANY = 2;   // up t
 // pieces (72 alive) 223 -> 253; 8192 rows in 192 pieces of about equal length 354 -> 318.  (Narrower layers have workers to spare: 448
 // units, 32 timesteps of 48 pieces 222 -> 251.)
 // us per timestep of launches over equally long pieces (two layers; time of a launch against its timesteps):
-//   pieces               1     2     4     8    16    32    64
-//   bf16 H=1024 fwd   1.37  1.35  1.38  1.96  2.6    5.1  11.2      bwd  1.68  1.88  2.16  2.49  3.45  8.9  17.1
-//   bf16 H=512  fwd   1.12  1.12  1.12  1.29  1.63   3.4   5.3      bwd  1.38  1.39  1.60  1.66  2.15  4.2   8.1
-//   fp32 H=512  fwd   1.23  1.53  2.16  3.1   5.2   8.5   16        bwd  1.50  2.06  3.08  3.65  4.5   10.2  19
-// (timesteps with up to 16 pieces run in the form of lstm_few.h).  The constants were fitted by hand to such a table when
-// single timesteps took 0.1 to 0.3 us longer; the cuts between the groups depend on the ratios only.
+//   pieces               1     2     4     5     8    16    17    32    64
+//   bf16 H=1024 fwd   1.23  1.29  1.47  1.93  1.97  3.1   4.6   5.2  11.2      bwd  1.64  1.73  2.18  2.47  2.45  3.2   6.9   9.0  17.1
+//   bf16 H=512  fwd   0.87  0.90  0.95  1.30  1.30  1.8   3.0   4.0   5.3      bwd  1.15  1.17  1.38  1.51  1.50  2.1   3.3   4.5   8.1
+//   fp32 H=512  fwd   1.15  1.43  2.08  3.00  3.0   4.9   6.6   8.1  16        bwd  1.28  1.83  2.77  3.56  3.5   4.5   8.4  10.2  19
+// The constants are fitted by hand to it (without the step from four to five pieces, two short groups of fp32 got five and more
+// pieces each and ended 50 us after the long one: 2 x 512 on 1024 rows in 8).
 inline PlanCost plan_cost(int mode, bool wide, bool fwd, int G) {
     const int teams = 2 * REC_MAX_GROUP / G;
     if (mode == MODE_F32)
-        return fwd ? PlanCost{1.45f, 0.19f, 1.f, teams < 3 ? 256 : 0, 48, PLAN_CT_FEW} : PlanCost{1.6f, 0.27f, 0.f, 0, 0, PLAN_CT_FEW};
-    if (wide) return fwd ? PlanCost{1.38f, 0.042f, 2.4f, 0, 0, PLAN_CT_FEW_FAST} : PlanCost{1.75f, 0.08f, 4.6f, 0, 0, PLAN_CT_FEW_FAST};
+        return fwd ? PlanCost{0.85f, 0.25f, 0.7f, 0.06f, 2.2f, teams < 3 ? 256 : 0, 48, PLAN_CT_FEW} : PlanCost{0.85f, 0.42f, 0.45f, 0.06f, 3.f, 0, 0, PLAN_CT_FEW};
+    if (wide) return fwd ? PlanCost{1.13f, 0.03f, 0.45f, 0.042f, 2.4f, 0, 0, PLAN_CT_FEW_FAST} : PlanCost{1.45f, 0.08f, 0.2f, 0.08f, 3.8f, 0, 0, PLAN_CT_FEW_FAST};
     const int few = teams < 3 ? PLAN_CT_FEW : PLAN_CT_FEW_FAST;
-    return fwd ? PlanCost{1.17f, 0.023f, 1.2f, G == REC_MAX_GROUP ? 192 : 0, 90, few} : PlanCost{1.38f, 0.04f, 1.7f, 0, 0, few};
+    return fwd ? PlanCost{0.84f, 0.f, 0.25f, 0.03f, 1.1f, G == REC_MAX_GROUP ? 192 : 0, 90, few} : PlanCost{1.09f, 0.01f, 0.05f, 0.05f, 1.2f, 0, 0, few};
 }
 
 struct PipeWork {
@@ -188,7 +189,8 @@ __device__ __forceinline__ void plan_body(const int32_t* __restrict__ batch_size
         int k = lo + 16;
         for (int i = 0; i < 64 && k < hi; ++i, k += 16) P += len[k];
         if (k < hi) P += (S1[hi] - S1[k - 8]) * (1.f / 16.f);
-        return pc.step * len[lo] + pc.piece * (S1[hi] - S1[lo]) + pc.tile * P;
+        const float over = lo + QUAD_MAX < hi ? len[lo + QUAD_MAX] : 0.f;
+        return pc.step * len[lo] + pc.low * (S1[min(lo + QUAD_MAX, hi)] - S1[lo]) + pc.over * over + pc.piece * (S1[hi] - S1[lo]) + pc.tile * P;
     };
     // every first cut k1 with the second cut that balances the two remaining groups; ties go to the smaller cuts
     float best = 3.0e38f;
