@@ -157,7 +157,7 @@ __device__ __forceinline__ int grp_steps(const int32_t* batch_sizes, int T, int 
     for (int t = threadIdx.x; t < T; t += blockDim.x) cnt += batch_sizes[t] > x ? 1 : 0;
     if (cnt) atomicAdd(&s_T, cnt);
     __syncthreads();
-    const int steps = __builtin_amdgcn_readfirstlane(s_T);
+    const int steps = s_T;
     __syncthreads();
     return steps;
 }
@@ -572,7 +572,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
         st_row4<E>(hprev + (size_t)n * H + j0 + u, v[0], v[1], v[2], v[3]);
     }
     // From timestep t0 on at most FEW_MAX pieces of the group are alive: those timesteps run in the form of lstm_few.h.
-    const int t0 = n_seq > FEW_MAX ? grp_steps(a.batch_sizes, T, FEW_MAX * X + x) : 0;
+    const int t0 = n_seq > FEW_MAX ? __builtin_amdgcn_readfirstlane(grp_steps(a.batch_sizes, T, FEW_MAX * X + x)) : 0;
     few_clear_ring<MODE>(static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, H), H, j0, UH);
     rec_publish(flags, rank, 1);
     REC_PROF_DECL
@@ -788,7 +788,7 @@ __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     if (rank < 0) return;
     PipeLink none = {};
     const PieceSet ps = {grp, REC_GROUPS, 0x7fffffff, grp};
-    const int T = grp_steps(a.batch_sizes, a.info[1], grp);
+    const int T = __builtin_amdgcn_readfirstlane(grp_steps(a.batch_sizes, a.info[1], grp));
     rec_fwd_body<MODE, TPW, KS, NBW, STATIC, PIPE_NONE>(a, rank, ps, T, a.flags + grp * REC_MAX_GROUP, none, smem);
 }
 
@@ -844,7 +844,7 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& by_ref, int rank,
     // Timesteps >= t_few have at most FEW_MAX alive pieces and run in the form of lstm_few.h (flag value 1: the
     // workgroup has emptied its words of the exchange ring).
     const int n_seq = grp_count(a.info[0], ps);
-    const int t_few = n_seq > FEW_MAX ? grp_steps(a.batch_sizes, T, FEW_MAX * X + x) : 0;
+    const int t_few = n_seq > FEW_MAX ? __builtin_amdgcn_readfirstlane(grp_steps(a.batch_sizes, T, FEW_MAX * X + x)) : 0;
     unsigned char* ring = static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, K);
     float dh_few = 0.f;
     if (t_few < T) {
@@ -1056,7 +1056,7 @@ __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     if (rank < 0) return;
     PipeLink none = {};
     const PieceSet ps = {grp, REC_GROUPS, 0x7fffffff, grp};
-    const int T = grp_steps(a.batch_sizes, a.info[1], grp);
+    const int T = __builtin_amdgcn_readfirstlane(grp_steps(a.batch_sizes, a.info[1], grp));
     rec_bwd_body<MODE, MT, KS, NI, PIPE_NONE>(a, rank, ps, T, a.flags + grp * REC_MAX_GROUP, none, smem);
 }
 
