@@ -323,11 +323,11 @@ __device__ __forceinline__ void heads_final_block(const HeadsFinalArgs& q, int b
     }
 }
 
-// The bias gradients of a layer (sets = 1) or a pair of layers (2): out[(c % 4) * H + c / 4] (and out2) = sum over the n_rb
-// rows of part[n_rb][4H], in row order (deterministic); the second set's sums follow at part_stride.
+// The bias gradients of a layer (sets = 1) or of the two or three layers of a launch: out[(c % 4) * H + c / 4] (and out2) = sum over the n_rb
+// rows of part[n_rb][4H], in row order (deterministic); the next set's sums follow at part_stride.
 struct BiasFinalArgs {
     const float* part; size_t part_stride;
-    float* out[2]; float* out2[2];
+    float* out[3]; float* out2[3];
     int n_rb, H, sets;
     const int* alone;   // points to anything but a zero: the time loops had all groups, n_rb is REC_GROUPS (NULL: as given)
 };
@@ -335,7 +335,7 @@ __device__ __forceinline__ void bias_final_block(const BiasFinalArgs& q, int bx,
     const int n_rb = q.alone && *q.alone != 0 ? REC_GROUPS : q.n_rb;
     const int c = bx * 256 + threadIdx.x, cols = 4 * q.H;
     if (c >= cols) return;
-    const float* part = q.part + (set == 1 ? q.part_stride : 0);
+    const float* part = q.part + set * q.part_stride;
     float s = 0.f;
     int rb = 0;
     for (; rb + 8 <= n_rb; rb += 8) {   // 8 loads in flight, added in index order
@@ -347,8 +347,8 @@ __device__ __forceinline__ void bias_final_block(const BiasFinalArgs& q, int bx,
     }
     for (; rb < n_rb; ++rb) s += part[(size_t)rb * cols + c];
     const int dst = (c & 3) * q.H + (c >> 2);
-    (set == 1 ? q.out[1] : q.out[0])[dst] = s;
-    (set == 1 ? q.out2[1] : q.out2[0])[dst] = s;
+    (set == 2 ? q.out[2] : set == 1 ? q.out[1] : q.out[0])[dst] = s;
+    (set == 2 ? q.out2[2] : set == 1 ? q.out2[1] : q.out2[0])[dst] = s;
 }
 // Both in one launch behind the first time loop of the backward pass (blockIdx.y: the bias sets, then the heads).
 __global__ __launch_bounds__(256) void grads_final_kernel(BiasFinalArgs b, HeadsFinalArgs h) {
@@ -374,15 +374,15 @@ struct LayerWs {
 struct LstmWs {
     int* err;          // word 0 of the workspace
     int* flags;        // [REC_FLAG_WORDS]: per-workgroup flags of a recurrent launch, then its ticket counters
-    int* flags_alone;  // [REC_FLAG_WORDS]: the same for a second launch behind the same clearing (may_run_alone)
+    int* flags_alone[2];   // [REC_FLAG_WORDS]: the same for a second and third launch behind the same clearing (may_run_alone)
     long long* prof;   // [128] phase counters of the recurrent kernels (forward 0..15, backward 16..31; +32: consumer layer), timeline, workers
     LayerWs layer[8];
-    void* dz[2];       // [M, 4H] operand type; the second one only when two layers share a launch
-    int* pipe;         // hand-over words of a two-layer launch: progress[8], done[][] from [16]
+    void* dz[3];       // [M, 4H] operand type; as many as layers share a launch
+    int* pipe;         // hand-over words of a launch of several layers: progress[8], done[][] from [16]; three layers: twice
     int pipe_words;
-    int* plan[2];      // which pieces every group of a two-layer launch runs, and its chunks (lstm_pipe.h): forward, backward
+    int* plan[2];      // which pieces every group of such a launch runs, and its chunks (lstm_pipe.h): forward, backward
     float* plan_scratch;
-    float* dh[2];      // [M, H] ping-pong: gradient arriving at a layer's h
+    float* dh[3];      // [M, H] in turn: gradient arriving at a layer's h (the third with three layers only)
     float* dh_state;   // [M, H]
     float* dc_state;   // [M, H]
     float* part;       // partial sums of the two-stage reductions
@@ -390,7 +390,7 @@ struct LstmWs {
     float* gemm_part;  // partial results of split contractions
     bf16_t* x_op;      // [M, input_dim]: fp32 input rows of a bf16 call in the operand type
     char* ring;        // [8 groups] exchange rings of the time loops (lstm_few.h)
-    float* db_part;    // [2][8][4H]: per layer of a launch and group, the sum of the gate gradients over the group's rows
+    float* db_part;    // [2 or 3][8][4H]: per layer of a launch and group, the sum of the gate gradients over the group's rows
     size_t bytes;
 };
 
@@ -412,7 +412,7 @@ inline size_t gemm_part_max(const ver_lstm_cfg& c, int M) {
         for (int n : {D, c.hidden})
             if (!dw.fits(H4, n, n, H4, n, M)) m = std::max(m, gemm_part_floats(H4, n, M, bk));
     }
-    if (c.compute) m = std::max(m, GemmGroup::part_floats((size_t)H4 * (std::max(c.input_dim, c.hidden) + (size_t)c.hidden * (c.n_layers >= 2 ? 3 : 1)), M));
+    if (c.compute) m = std::max(m, GemmGroup::part_floats((size_t)H4 * (std::max(c.input_dim, c.hidden) + (size_t)c.hidden * (c.n_layers >= 2 ? 3 : 1)), M));   // (a launch takes up to two layers' weight gradients)
     return m;
 }
 
@@ -423,10 +423,11 @@ inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws)
     int* head = cv.take<int>(64);
     ws->err = head;
     ws->flags = cv.take<int>(REC_FLAG_WORDS);
-    ws->flags_alone = cv.take<int>(REC_FLAG_WORDS);
+    for (int*& f : ws->flags_alone) f = cv.take<int>(REC_FLAG_WORDS);
+    const bool three = c.n_layers == 3;   // (three_layers, which may be switched off between the calls)
     ws->prof = cv.take<long long>(128);
     // the hand-over words sit right behind, so that one fill clears everything a launch needs cleared
-    ws->pipe_words = pipe_sync_words(M);
+    ws->pipe_words = pipe_sync_words(M) * (three ? 2 : 1);
     ws->pipe = cv.take<int>(ws->pipe_words);
     ws->plan[0] = cv.take<int>(PLAN_WORDS);
     ws->plan[1] = cv.take<int>(PLAN_WORDS);
@@ -447,15 +448,17 @@ inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws)
     }
     ws->dz[0] = cv.take<char>(Mz * 4 * H * es);
     ws->dz[1] = c.n_layers >= 2 ? cv.take<char>(Mz * 4 * H * es) : ws->dz[0];
+    ws->dz[2] = three ? cv.take<char>(Mz * 4 * H * es) : ws->dz[0];
     ws->dh[0] = cv.take<float>(Mz * H);
     ws->dh[1] = cv.take<float>(Mz * H);
-    ws->dh_state = cv.take<float>(2 * Mz * H);
-    ws->dc_state = cv.take<float>(2 * Mz * H);
+    ws->dh[2] = three ? cv.take<float>(Mz * H) : nullptr;
+    ws->dh_state = cv.take<float>((three ? 3 : 2) * Mz * H);
+    ws->dc_state = cv.take<float>((three ? 3 : 2) * Mz * H);
     ws->part = cv.take<float>(part_floats(c, M));
     ws->part_b = cv.take<float>((size_t)(M + HW_ROWS - 1) / HW_ROWS * 64);
     ws->gemm_part = cv.take<float>(gemm_part_max(c, M));
     ws->x_op = c.compute && !c.x_bf16 ? cv.take<bf16_t>(Mz * c.input_dim) : nullptr;
-    ws->db_part = cv.take<float>((size_t)2 * REC_GROUPS * 4 * H);
+    ws->db_part = cv.take<float>((size_t)(three ? 3 : 2) * REC_GROUPS * 4 * H);
     ws->ring = cv.take<char>(REC_GROUPS * few_ring_bytes(c.compute ? MODE_BF16 : MODE_F32, 4 * c.hidden));
     ws->bytes = cv.used;
 }
@@ -532,37 +535,51 @@ inline int device_fits_time_loops() {
     return known[dev] > 0 ? VER_OK : VER_EUNSUPPORTED;
 }
 
-inline void pipe_work(const LstmWs& ws, int dir, int M, const int32_t* t_off, const int* alone, PipeWork* pw) {
+// stage: 1 for the second of the two products of a three-layer launch.
+inline void pipe_work(const LstmWs& ws, int dir, int M, const int32_t* t_off, const int* alone, PipeWork* pw, int count = WORK_COUNT, int stage = 0) {
     pw->M = M;
+    pw->count = count;
     pw->t_off = t_off;
     pw->plan = ws.plan[dir];
-    pw->sync = ws.pipe;
+    pw->sync = ws.pipe + stage * pipe_sync_words(M);
     pw->err = ws.err;
     pw->alone = alone;
 }
 
 // Networks of several layers run two layers at a time in one launch each (lstm_pipe.h), the layers numbered 2i and 2i + 1;
-// the top layer of an odd number has a launch of its own.  A pair's time loops advance side by side on three XCDs each,
+// the top layer of an odd number from five on has a launch of its own.  A pair's time loops advance side by side on three XCDs each,
 // where one after the other would have all eight: us per forward and backward pass of two layers, a launch per layer
 // -> one for both: 300 rows (longest piece 98) at 512 units 632 -> 357, 8192 (473) at 1024 4204 -> 2417; closest where
-// hundreds of short pieces keep every XCD busy: 8192 rows in 538 pieces (86) at 320 units 1121 -> 1103.  Three layers of 320 on
-// 3001 rows in 36 pieces (bf16): 2430 -> 1843 us.
+// hundreds of short pieces keep every XCD busy: 8192 rows in 538 pieces (86) at 320 units 1121 -> 1103.
 inline bool pairs_of_layers(const ver_lstm_cfg& c) { return c.n_layers >= 2 && !c.layer_by_layer; }
-// From three layers on a pair's launch is for minibatches of few alive pieces per timestep (rows / timesteps): many are bound by
-// throughput, of which three XCDs per layer have less than eight for one layer after the other (and finding the cuts for
+// Three layers run in one launch, on two XCDs each and an XCD for each of the two products: one walk over the dependent timesteps instead of
+// two.  us per forward and backward pass of 3001 rows in 30 to 36 pieces at 320 units (bf16), a pair and a top layer -> three: 1523 -> 1196
+// (and 1680 to 2080 where timesteps of few pieces took longer).
+inline bool three_layers(const ver_lstm_cfg& c) { return c.n_layers == 3 && !c.layer_by_layer; }
+// From three layers on a shared launch is for minibatches of few alive pieces per timestep (rows / timesteps): many are bound by
+// throughput, of which two or three XCDs per layer have less than eight for one layer after the other (and finding the cuts for
 // thousands of pieces takes milliseconds).  Only the device knows the timesteps: both forms are launched, and what the plan has
-// not chosen does nothing (15 us in all; up to PAIRS_ROWS rows the pairs are launched alone, which then take less in any
-// packing than a launch per layer did before the contractions were made faster).
+// not chosen does nothing (15 us in all for pairs, 25 for three layers); up to this many rows the shared form is launched alone.
+// Three layers, pieces x timesteps, us of a launch per layer / three in a launch / before (pairs without a choice): bf16, 320 units 50 x 7 206 /
+// 195 / 206, 100 x 7 224 / 278 / 253; fp32, 256 units 25 x 7 222 / 240 / 236, 100 x 7 271 / 411 / 317; 512 units 12 x 7 280 / 312 / 297, 50 x 15 582 / 738 / 671.
 constexpr int PAIRS_ROWS = 768;
-inline bool may_run_alone(const ver_lstm_cfg& c, int M) { return c.n_layers > 2 && pairs_of_layers(c) && M > PAIRS_ROWS; }
-// The lines, by alive pieces (timesteps): us per forward and backward pass of three layers, pairs / a launch per layer: bf16, 320 units
+inline int shared_rows(const ver_lstm_cfg& c) { return !three_layers(c) ? PAIRS_ROWS : c.compute ? 512 : c.hidden > 320 ? 64 : 256; }
+inline bool may_run_alone(const ver_lstm_cfg& c, int M) { return c.n_layers > 2 && pairs_of_layers(c) && M > shared_rows(c); }
+// The lines, by alive pieces (timesteps), us per forward and backward pass of three layers of equally long pieces, three in a launch / a launch
+// per layer (pieces of different length favour the former, whose time follows the longest): bf16, 320 units 32 (50) 448 / 488, 40 (50) 584 /
+// 580, 50 (50) 628 / 582, 64 units 64 (120) 1009 / 1034, 80 (120) 1237 / 1084, 1024 units 40 (50) 993 / 1082, 50 (50) 1146 / 1132; fp32, 256 units
+// 32 (20) 380 / 397, 50 (20) 487 / 446, 50 (50) 830 / 923, 64 (120) 1845 / 2115, 80 (120) 2496 / 2412; from 384 units on, where one team of
+// workers holds the weights, 512 units 8 (20) 364 / 362, 24 (50) 970 / 969, 32 (50) 1191 / 1142, 40 (120) 3101 / 3280, 50 (120) 3654 / 3427.
+// Pairs (of three layers, before): bf16, 320 units
 // 35 (29) 423 / 440, 51 (59) 782 / 787, 70 (117) 1675 / 1642, 76 (27) 562 / 512, 104 (29) 763 / 607, 910 (36) 8807 / 3677; fp32, 256
 // units 44 (68) 1027 / 1106, 70 (117) 2197 / 2263, 76 (27) 733 / 651; from 384 units on, where the workers hold the weights twice at
 // most, 512 units 20 (51) 866 / 931, 24 (21) 533 / 514, 28 (36) 791 / 792, 35 (29) 847 / 766, 44 (68) 1808 / 1805, 51 (59) 1818 / 1693, 70 (117)
 // 4177 / 3976.
 inline void pair_lines(const ver_lstm_cfg& c, int M, PlanArgs* p) {
-    const bool low = !c.compute && c.hidden > 320;
-    p->base = low ? 12 : 45; p->per = low ? 2 : 4; p->most = may_run_alone(c, M) ? (low ? 60 : 80) : 0;
+    const bool low = !c.compute && c.hidden > 320, three = three_layers(c);
+    p->base = three ? (low ? 0 : c.compute ? 46 : 30) : low ? 12 : 45;
+    p->per = three ? 2 : low ? 2 : 4;
+    p->most = !may_run_alone(c, M) ? 0 : three ? (low ? 44 : c.compute ? 46 : 70) : low ? 60 : 80;
 }
 
 // What the first launch of the forward pass does for the two-layer launches: zeroes the flags, ticket counters, hand-over words
@@ -570,7 +587,9 @@ inline void pair_lines(const ver_lstm_cfg& c, int M, PlanArgs* p) {
 // backward call runs on the packing of the forward call whose activations it finds in the workspace).
 inline PlanArgs pipe_plan(const LstmWs& ws, int mode, bool wide, int G, int M, const int32_t* info, const int32_t* batch_sizes, const ver_lstm_cfg& c) {
     PlanArgs p{info, batch_sizes, M, ws.plan[0], ws.plan[1], ws.plan_scratch, ws.err, (int)(ws.pipe + ws.pipe_words - ws.err),
-                    plan_cost(mode, wide, true, G), plan_cost(mode, wide, false, G), 0, 0, 0};
+                    plan_cost(mode, wide, true, G, three_layers(c) ? TRIPLE_WORK_COUNT : WORK_COUNT),
+                    plan_cost(mode, wide, false, G, three_layers(c) ? TRIPLE_WORK_COUNT : WORK_COUNT), 0, 0, 0,
+                    three_layers(c) ? TRIPLE_GROUPS : PIPE_GROUPS};
     pair_lines(c, M, &p);
     return p;
 }
@@ -652,16 +671,16 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         ProfScope prof(VER_PROF_LSTM_GEMM_FWD, s);
         return contract_rows<MODE>(layer_input<MODE>(c, ws, x, l), static_cast<const E*>(L.wih), L.gates, L.bias, M, 4 * H, D, ws.gemm_part, s, alone) == VER_OK;
     };
-    auto rec_args = [&](int l, bool consumer = false) {
+    auto rec_args = [&](int l, int groups_before = 0) {   // (of the layers before in the same launch)
         LayerWs& L = ws.layer[l];
         RecFwdArgs ra;
         ra.info = info; ra.batch_sizes = batch_sizes; ra.t_off = t_off;
         ra.gates = L.gates; ra.c = L.c; ra.hout = L.hout; ra.hprev = L.hprev; ra.hcopy = L.hcopy; ra.whh = L.whh;
-        ra.ring = ws.ring + (consumer ? PIPE_GROUPS * few_ring_bytes(MODE, H) : 0);
+        ra.ring = ws.ring + groups_before * few_ring_bytes(MODE, H);
         ra.h0 = h0 ? h0 + (size_t)l * seq_cap * H : nullptr;
         ra.c0 = c0 ? c0 + (size_t)l * seq_cap * H : nullptr;
         ra.H = H; ra.seq_cap = seq_cap; ra.M = M; ra.flags = ws.flags; ra.ticket = ws.flags + 8 * REC_MAX_GROUP;
-        ra.err = ws.err; ra.prof = ws.prof + (consumer ? 32 : 0); ra.prof_all = ws.prof;
+        ra.err = ws.err; ra.prof = ws.prof + (groups_before ? 32 : 0); ra.prof_all = ws.prof;
         ra.G = H / (4 * mt); ra.ntc = ntc; ra.alone = nullptr;
         return ra;
     };
@@ -685,17 +704,34 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     const int* alone = may_run_alone(c, M) ? ws.plan[0] + PLAN_ALONE : nullptr;
     for (int l = 0; l < c.n_layers;) {
         if (!project(l)) return VER_EHIP;
-        if (pairs && l + 1 < c.n_layers) {
+        if (three_layers(c)) {
+            for (int k = 0; alone && k < 3; ++k) {   // the same layers one after the other; where they do nothing they leave the words as they are
+                if (k > 0 && !project(k, alone)) return VER_EHIP;
+                if (!loop_alone(k, k == 0 ? ws.flags : ws.flags_alone[k - 1], alone)) return VER_EHIP;
+                if (k < 2) copy_h(k, alone);
+            }
+            TripleFwdArgs ta;
+            for (int k = 0; k < 3; ++k) ta.l[k] = rec_args(k, k * TRIPLE_GROUPS);
+            for (int k = 0; k < 2; ++k) {
+                ta.work[k].A = ws.layer[k].hcopy; ta.work[k].B = ws.layer[k + 1].wih; ta.work[k].C = ws.layer[k + 1].gates;
+                ta.work[k].bias = ws.layer[k + 1].bias; ta.work[k].K = H; ta.work[k].N = 4 * H;
+                pipe_work(ws, 0, M, t_off, ws.plan[0] + PLAN_ALONE, &ta.work[k], TRIPLE_WORK_COUNT, k);
+                ta.work[k].G = ta.l[0].G;
+            }
+            ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
+            if (!launch_fwd_triple<MODE>(form, ta, s)) return VER_EHIP;
+            l = 3;
+        } else if (pairs && l + 1 < c.n_layers) {
             // (the plan, of the packing, is the same for every pair)
             if (l > 0) fill_words(ws.flags, (size_t)(ws.pipe + ws.pipe_words - ws.flags), 0, s);
             if (alone) {   // the same two layers one after the other; where they do nothing they leave the words as they are
                 if (!loop_alone(l, ws.flags, alone)) return VER_EHIP;
                 copy_h(l, alone);
-                if (!project(l + 1, alone) || !loop_alone(l + 1, ws.flags_alone, alone)) return VER_EHIP;
+                if (!project(l + 1, alone) || !loop_alone(l + 1, ws.flags_alone[0], alone)) return VER_EHIP;
             }
             PipeFwdArgs pa;
             pa.l0 = rec_args(l);
-            pa.l1 = rec_args(l + 1, true);
+            pa.l1 = rec_args(l + 1, PIPE_GROUPS);
             pa.work.A = ws.layer[l].hcopy; pa.work.B = ws.layer[l + 1].wih; pa.work.C = ws.layer[l + 1].gates;
             pa.work.bias = ws.layer[l + 1].bias; pa.work.K = H; pa.work.N = 4 * H;
             pipe_work(ws, 0, M, t_off, alone, &pa.work);
@@ -724,7 +760,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     typedef typename RecGeom<MODE>::E E;
     const int H = c.hidden, A = c.act_dim, nl = c.n_layers;
     const float* h_top = ws.layer[nl - 1].hout;
-    const bool pairs = pairs_of_layers(c), top_pair = pairs && nl % 2 == 0;   // two layers' time loops in one launch
+    const bool pairs = pairs_of_layers(c), three = three_layers(c), top_pair = three || (pairs && nl % 2 == 0);   // several layers' time loops in one launch
     // heads
     {
     ProfScope prof(VER_PROF_HEADS_BWD, s);
@@ -753,21 +789,21 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     const int ni = (4 * H / ks) / RecGeom<MODE>::KBLK;
 
     // dz_of(l): layer l's gate gradients.  The two layers of a pair (l & 1: the upper one, which is the producer here) carry
-    // their state in separate halves of the scratch; a top layer without a partner has an even number.
-    auto half = [&](int l) { return pairs ? l & 1 : 0; };
+    // their state in separate halves of the scratch, three layers in thirds; a top layer without a partner has an even number.
+    auto half = [&](int l) { return three ? l : pairs ? l & 1 : 0; };
     auto dz_of = [&](int l) { return ws.dz[half(l)]; };
-    auto rec_args = [&](int l, const float* dh_above, bool consumer = false) {
+    auto rec_args = [&](int l, const float* dh_above, int groups_before = 0) {
         LayerWs& L = ws.layer[l];
         RecBwdArgs ra;
         ra.info = info; ra.batch_sizes = batch_sizes; ra.t_off = t_off;
         ra.gates = L.gates; ra.c = L.c; ra.c0 = c0 ? c0 + (size_t)l * seq_cap * H : nullptr;
         ra.dh_above = dh_above; ra.dz = dz_of(l); ra.whhT = L.whhT;
-        ra.ring = ws.ring + (consumer ? PIPE_GROUPS * few_ring_bytes(MODE, 4 * H) : 0);
+        ra.ring = ws.ring + groups_before * few_ring_bytes(MODE, 4 * H);
         ra.dh_state = ws.dh_state + (size_t)half(l) * M * H;
         ra.dc_state = ws.dc_state + (size_t)half(l) * M * H;
         ra.db_part = ws.db_part + (size_t)half(l) * REC_GROUPS * 4 * H;
         ra.H = H; ra.seq_cap = seq_cap; ra.flags = ws.flags; ra.ticket = ws.flags + 8 * REC_MAX_GROUP;
-        ra.err = ws.err; ra.prof = ws.prof + 16 + (consumer ? 32 : 0); ra.prof_all = ws.prof;
+        ra.err = ws.err; ra.prof = ws.prof + 16 + (groups_before ? 32 : 0); ra.prof_all = ws.prof;
         ra.G = H / (16 * mt); ra.ntc = ntc; ra.alone = nullptr;
         return ra;
     };
@@ -786,10 +822,10 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
                                  ws.gemm_part, s, alone) == VER_OK;
     };
     const int* alone = may_run_alone(c, M) ? ws.plan[1] + PLAN_ALONE : nullptr;
-    // Everything of layer l that is not the time loop: dx (optional), dW_ih, dW_hh, db.  A pair's upper layer comes first
-    // and leaves its weight gradients and bias sums to the launches of the lower one (last = false).
+    // Everything of layer l that is not the time loop: dx (optional), dW_ih, dW_hh, db.  The upper layers of a launch of `with` layers come
+    // first and leave their weight gradients and bias sums to the launches of the lowest one (last).
     GemmGroup dw(true, MODE == MODE_BF16, ws.gemm_part);
-    auto layer_grads = [&](int l, float* dx, bool in_pair, bool last) {
+    auto layer_grads = [&](int l, float* dx, int with, bool last) {
         const int D = l == 0 ? c.input_dim : H;
         LayerWs& L = ws.layer[l];
         const E* dz = static_cast<const E*>(dz_of(l));
@@ -804,16 +840,16 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         };
         contract(layer_input<MODE>(c, ws, x, l), gw[4 * l], D);
         contract(static_cast<const E*>(L.hprev), gw[4 * l + 1], H);
-        if (last && (MODE == MODE_F32 || !launch_tn_group(dw, s))) dw.launch(s);
+        if ((last || dw.a.n == GEMM_GROUP_MAX) && (MODE == MODE_F32 || !launch_tn_group(dw, s))) dw.launch(s);
         }
         // db_ih = db_hh = column sums of dz: the time loop left one partial sum per group (a pair: both layers' sums in
         // one launch; the heads' gradients join the first)
         if (last) {
         ProfScope prof(VER_PROF_LSTM_DBIAS, s);
         float* const* g = gw + 4 * l;
-        const BiasFinalArgs bf{ws.db_part, (size_t)REC_GROUPS * 4 * H, {g[2], in_pair ? g[6] : nullptr}, {g[3], in_pair ? g[7] : nullptr},
-                               in_pair ? PIPE_GROUPS : REC_GROUPS, H, in_pair ? 2 : 1, in_pair ? alone : nullptr};
-        const bool heads = l + (in_pair ? 2 : 1) == nl;
+        BiasFinalArgs bf{ws.db_part, (size_t)REC_GROUPS * 4 * H, {}, {}, with == 1 ? REC_GROUPS : with == 2 ? PIPE_GROUPS : TRIPLE_GROUPS, H, with, with > 1 ? alone : nullptr};
+        for (int k = 0; k < with; ++k) { bf.out[k] = g[4 * k + 2]; bf.out2[k] = g[4 * k + 3]; }
+        const bool heads = l + with == nl;
         hipLaunchKernelGGL(grads_final_kernel, dim3(std::max((4 * H + 255) / 256, (H + HF_COLS - 1) / HF_COLS), bf.sets + (heads ? A + 1 : 0)),
                            dim3(256), 0, s, bf, hf);
         }
@@ -821,16 +857,39 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
 
     int cur = 0;  // ws.dh[cur] holds the gradient arriving at the current layer's h
     for (int l = nl - 1; l >= 0;) {
-        if (pairs && l % 2 == 1) {
+        if (three) {
+            for (int k = 2; alone && k >= 0; --k) {   // (as in the forward pass)
+                if (!loop_alone(k, ws.dh[2 - k], k == 2 ? ws.flags : ws.flags_alone[1 - k], alone)) return VER_EHIP;
+                if (k > 0) input_grad(k, ws.dh[3 - k], alone);
+                if (!ok) return VER_EHIP;
+            }
+            TripleBwdArgs ta;
+            for (int k = 0; k < 3; ++k) ta.l[k] = rec_args(2 - k, ws.dh[k], k * TRIPLE_GROUPS);
+            for (int k = 0; k < 2; ++k) {
+                ta.work[k].A = ws.dz[2 - k]; ta.work[k].B = ws.layer[2 - k].wihT; ta.work[k].C = ws.dh[k + 1]; ta.work[k].bias = nullptr;
+                ta.work[k].K = 4 * H; ta.work[k].N = H;
+                pipe_work(ws, 1, M, t_off, ws.plan[1] + PLAN_ALONE, &ta.work[k], TRIPLE_WORK_COUNT, k);
+                ta.work[k].G = ta.l[0].G;
+            }
+            {
+            ProfScope prof(VER_PROF_LSTM_REC_BWD, s);
+            if (!launch_bwd_triple<MODE>(form, ta, s)) return VER_EHIP;
+            }
+            layer_grads(2, nullptr, 3, false);
+            layer_grads(1, nullptr, 3, false);
+            layer_grads(0, d_x, 3, true);
+            if (!ok) return VER_EHIP;
+            l = -1;
+        } else if (pairs && l % 2 == 1) {
             if (l != nl - 1) fill_words(ws.flags, (size_t)(ws.pipe + ws.pipe_words - ws.flags), 0, s);   // (the top layers': heads_bwd_kernel)
             if (alone) {   // (as in the forward pass)
                 if (!loop_alone(l, ws.dh[cur], ws.flags, alone)) return VER_EHIP;
                 input_grad(l, ws.dh[cur ^ 1], alone);
-                if (!ok || !loop_alone(l - 1, ws.dh[cur ^ 1], ws.flags_alone, alone)) return VER_EHIP;
+                if (!ok || !loop_alone(l - 1, ws.dh[cur ^ 1], ws.flags_alone[0], alone)) return VER_EHIP;
             }
             PipeBwdArgs pa;
             pa.l1 = rec_args(l, ws.dh[cur]);
-            pa.l0 = rec_args(l - 1, ws.dh[cur ^ 1], true);
+            pa.l0 = rec_args(l - 1, ws.dh[cur ^ 1], PIPE_GROUPS);
             pa.work.A = ws.dz[1]; pa.work.B = ws.layer[l].wihT; pa.work.C = ws.dh[cur ^ 1]; pa.work.bias = nullptr;
             pa.work.K = 4 * H; pa.work.N = H;
             pipe_work(ws, 1, M, t_off, alone, &pa.work);
@@ -839,14 +898,14 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
             ProfScope prof(VER_PROF_LSTM_REC_BWD, s);
             if (!launch_bwd_pair<MODE>(form, pa, alone != nullptr, s)) return VER_EHIP;
             }
-            layer_grads(l, nullptr, true, false);   // the weight gradients of both layers leave in one grouped launch
-            layer_grads(l - 1, l > 1 ? ws.dh[cur] : d_x, true, true);
+            layer_grads(l, nullptr, 2, false);   // the weight gradients of both layers leave in one grouped launch
+            layer_grads(l - 1, l > 1 ? ws.dh[cur] : d_x, 2, true);
             if (!ok) return VER_EHIP;
             l -= 2;
         } else {
             if (l != nl - 1) fill_words(ws.flags, REC_FLAG_WORDS, 0, s);
             if (!loop_alone(l, ws.dh[cur], ws.flags, nullptr)) return VER_EHIP;
-            layer_grads(l, l > 0 ? ws.dh[cur ^ 1] : d_x, false, true);
+            layer_grads(l, l > 0 ? ws.dh[cur ^ 1] : d_x, 1, true);
             if (!ok) return VER_EHIP;
             cur ^= 1;
             l -= 1;

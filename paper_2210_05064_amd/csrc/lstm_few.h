@@ -408,7 +408,7 @@ __device__ __forceinline__ void few_fwd_store(const FewFwd<MODE, MT, NB>& s, con
     const __amdgpu_buffer_rsrc_t rs_c = __builtin_amdgcn_make_buffer_rsrc(a.c, 0, WHOLE, 0x00020000);
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, s.s_g), rs_g, col * 16u, so * 16u, 0);
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s.s_c), rs_c, col * 4u, so * 4u, 0);
-    if (PIPE != PIPE_PRODUCER) {
+    if (!(PIPE & PIPE_PRODUCER)) {
         const __amdgpu_buffer_rsrc_t rs_h = __builtin_amdgcn_make_buffer_rsrc(a.hout, 0, WHOLE, 0x00020000);
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s.s_h), rs_h, col * 4u, so * 4u, 0);
     }
@@ -417,7 +417,7 @@ __device__ __forceinline__ void few_fwd_store(const FewFwd<MODE, MT, NB>& s, con
             const __amdgpu_buffer_rsrc_t rs_hp = __builtin_amdgcn_make_buffer_rsrc(a.hprev, 0, WHOLE, 0x00020000);
             __builtin_amdgcn_raw_buffer_store_b32(s.s_w, rs_hp, col * es, (unsigned)base * (unsigned)(H * es), 0);
         }
-        if (PIPE == PIPE_PRODUCER) {   // written through: input of the workers' GEMM
+        if (PIPE & PIPE_PRODUCER) {   // written through: input of the workers' GEMM
             const __amdgpu_buffer_rsrc_t rs_hc = __builtin_amdgcn_make_buffer_rsrc(a.hcopy, 0, WHOLE, 0x00020000);
             __builtin_amdgcn_raw_buffer_store_b32(s.s_w, rs_hc, col * es, so * es, 17);
         }
@@ -451,7 +451,7 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
         const int bs = grp_count(s.bs_a, ps), bs_next = t + 1 < T ? grp_count(s.bs_b, ps) : 0;
         const int base_next = s.base + s.bs_a;
         s.win.advance(t + 2);
-        if (PIPE == PIPE_CONSUMER && t + 1 < T && t + 1 == s.c_wait * pl.ct) {
+        if ((PIPE & PIPE_CONSUMER) && t + 1 < T && t + 1 == s.c_wait * pl.ct) {
             if (!s.ready && !pipe_wait_chunk(pl, s.c_wait, a.err)) return false;
             ++s.c_wait;
             s.ready = false;
@@ -460,7 +460,7 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
         if (t == s.t0) {
             // the rows were written under the flag protocol (initial states, or the timestep before with more pieces)
             if (!rec_wait(flags, a.G, t + 1, a.err)) return false;
-            if (PIPE == PIPE_PRODUCER && rank == 0 && tid == 0 && t > 0) st_agent(pl.progress, t);
+            if ((PIPE & PIPE_PRODUCER) && rank == 0 && tid == 0 && t > 0) st_agent(pl.progress, t);
             if (polls) {
                 const unsigned char* rows = reinterpret_cast<const unsigned char*>(static_cast<const E*>(a.hprev) + (size_t)(s.base + x) * H);
                 few_stage_read<NB>(rows, (unsigned)(X * H) * es, slice_off, s.n_blk, bs, false, stage, a.err);
@@ -473,7 +473,7 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
         few_touch(z);
         few_touch(s.win.cur);
         few_touch(s.win.other);
-        if (PIPE == PIPE_CONSUMER) few_touch(s.have);
+        if (PIPE & PIPE_CONSUMER) few_touch(s.have);
         if (!ok) *s.fail = 1;
         const int bs_c = s.win.at(t + 2);
         // off the critical path: results of the timestep before, the input projection of the next one
@@ -483,8 +483,8 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
         // A look at the chunk that the next timestep asks for: usually finished, which saves that wait its round trip.  Its
         // counter was requested a timestep earlier (a load waited for in the timestep that requests it, under a condition,
         // makes the compiler wait in every timestep).
-        const bool look = PIPE == PIPE_CONSUMER && t + 2 < T && t + 2 == s.c_wait * pl.ct;
-        if (PIPE == PIPE_CONSUMER) {
+        const bool look = (PIPE & PIPE_CONSUMER) && t + 2 < T && t + 2 == s.c_wait * pl.ct;
+        if (PIPE & PIPE_CONSUMER) {
             if (look && tid == REC_THREADS - 1) s.fail[1] = s.have;
             if (look) s.have = 0;
             if (t + 3 < T && t + 3 == s.c_wait * pl.ct && tid == REC_THREADS - 1) s.have = ld_agent(&pl.done[s.c_wait]);
@@ -503,7 +503,7 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
         if (look) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= pl.need;
         // Every workgroup has published the rows of timestep t-1, which it did after its stores for timestep t-3 had
         // completed (they are issued in timestep t-2 and waited for in timestep t-1).
-        if (PIPE == PIPE_PRODUCER && rank == 0 && tid == REC_THREADS - 1 && t - 2 > s.t0) st_agent(pl.progress, t - 2);
+        if ((PIPE & PIPE_PRODUCER) && rank == 0 && tid == REC_THREADS - 1 && t - 2 > s.t0) st_agent(pl.progress, t - 2);
         if (m < bs) {
             f32x4_t q = z, o[REC_WAVES];
             const float* p = part + m * ROW + u * 4;
@@ -658,7 +658,7 @@ __device__ __forceinline__ bool few_fwd(few_args_t<RecFwdArgs> args, int x_, int
     if (!few_fwd_phase<MODE, MT, NB, PIPE>(s, a, ps, rank, flags, ring, pl, t, T)) return false;
     if (t > t0) few_fwd_store<MODE, MT, NB, PIPE>(s, a, ps, j0, grp_count(s.base - s.base_prev, ps), s.base, t < T ? grp_count(s.bs_a, ps) : 0);
     if (t < T && !quad_fwd<MODE, MT, NB, PIPE>(s, a, ps, rank, flags, ring, pl, t, T)) return false;
-    if (PIPE == PIPE_PRODUCER) rec_publish(flags, rank, T + 1);
+    if (PIPE & PIPE_PRODUCER) rec_publish(flags, rank, T + 1);
     return true;
 }
 
@@ -759,11 +759,11 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
         }
         const unsigned so_dz = (unsigned)s.base * (unsigned)(K * es);
         if (t == 0) {   // nothing is carried before the first timestep
-            if (m < bs) store(word, rs_dz, (unsigned)(n * K + j * 4) * es, so_dz, FewIdx<PIPE == PIPE_PRODUCER ? 17 : 0>{});
+            if (m < bs) store(word, rs_dz, (unsigned)(n * K + j * 4) * es, so_dz, FewIdx<(PIPE & PIPE_PRODUCER) ? 17 : 0>{});
             --t;
             return true;
         }
-        if (PIPE == PIPE_CONSUMER && t >= 2 && t - 2 < s.c_wait * pl.ct) {
+        if ((PIPE & PIPE_CONSUMER) && t >= 2 && t - 2 < s.c_wait * pl.ct) {
             --s.c_wait;
             if (!s.ready && !pipe_wait_chunk(pl, s.c_wait, a.err)) return false;
             s.ready = false;
@@ -779,18 +779,18 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
         few_touch(other.c);
         few_touch(s.win.cur);
         few_touch(s.win.other);
-        if (PIPE == PIPE_CONSUMER) few_touch(s.have);
+        if (PIPE & PIPE_CONSUMER) few_touch(s.have);
         if (!ok) *s.fail = 1;
         const int bs_m3 = s.win.at(t - 3);
         // off the critical path: the dz rows of this timestep, the saved activations of timestep t-2
-        if (m < bs) store(word, rs_dz, (unsigned)(n * K + j * 4) * es, so_dz, FewIdx<PIPE == PIPE_PRODUCER ? 17 : 0>{});
+        if (m < bs) store(word, rs_dz, (unsigned)(n * K + j * 4) * es, so_dz, FewIdx<(PIPE & PIPE_PRODUCER) ? 17 : 0>{});
         if (t >= 2) {
             const int base_2 = s.base - s.bs_m1 - s.bs_m2;
             few_load_saved(sv, a, m, n, j, t - 2, grp_count(s.bs_m2, ps), grp_count(s.bs_m1, ps), base_2, base_2 - bs_m3);
         }
         // a look at the chunk that the next timestep asks for, see the forward loop
-        const bool look = PIPE == PIPE_CONSUMER && t >= 3 && t - 3 == s.c_wait * pl.ct - 1;
-        if (PIPE == PIPE_CONSUMER) {
+        const bool look = (PIPE & PIPE_CONSUMER) && t >= 3 && t - 3 == s.c_wait * pl.ct - 1;
+        if (PIPE & PIPE_CONSUMER) {
             if (look && tid == REC_THREADS - 1) s.fail[1] = s.have;
             if (look) s.have = 0;
             if (t >= 4 && t - 4 == s.c_wait * pl.ct - 1 && tid == REC_THREADS - 1) s.have = ld_agent(&pl.done[s.c_wait - 1]);
@@ -808,7 +808,7 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
         if (look) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= pl.need;
         // Every workgroup has published the rows of timestep t, which it did after its dz rows of timestep t+2 had
         // completed (they are stored in that timestep and waited for in timestep t+1).
-        if (PIPE == PIPE_PRODUCER && rank == 0 && tid == REC_THREADS - 1 && t + 2 < T) st_agent(pl.progress, T - (t + 2));
+        if ((PIPE & PIPE_PRODUCER) && rank == 0 && tid == REC_THREADS - 1 && t + 2 < T) st_agent(pl.progress, T - (t + 2));
         if (m < bs) {
             float q = 0.f, o[REC_WAVES];
             const float* p = part + m * ROW + u;
@@ -904,7 +904,7 @@ __device__ __forceinline__ FewBwdOut few_bwd(few_args_t<RecBwdArgs> args, int x_
     int t = T - 1;
     if (!quad_bwd<MODE, MT, NB, PIPE>(s, a, ps, rank, ring, pl, t, T, t_stop)) return gave_up;
     if (t >= t_stop) {
-        if (PIPE == PIPE_CONSUMER)
+        if (PIPE & PIPE_CONSUMER)
             while (s.c_wait > 0 && t - 1 < s.c_wait * pl.ct) {
                 --s.c_wait;
                 if (!pipe_wait_chunk(pl, s.c_wait, a.err)) return gave_up;

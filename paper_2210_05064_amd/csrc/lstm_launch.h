@@ -22,9 +22,11 @@ struct BwdForm {
     int ni;               // operand blocks of a wave's share
     size_t lds;
 };
-// One layer; two layers (planned: the kernels that ask the plan whether they run).
+// One layer; two layers (planned: the kernels that ask the plan whether they run); three layers (always planned).
 template <int MODE> bool launch_fwd_loop(const FwdForm& f, const RecFwdArgs& a, hipStream_t s);
 template <int MODE> bool launch_fwd_pair(const FwdForm& f, const PipeFwdArgs& a, bool planned, hipStream_t s);
+template <int MODE> bool launch_fwd_triple(const FwdForm& f, const TripleFwdArgs& a, hipStream_t s);
+template <int MODE> bool launch_bwd_triple(const BwdForm& f, const TripleBwdArgs& a, hipStream_t s);
 template <int MODE> bool launch_bwd_loop(const BwdForm& f, const RecBwdArgs& a, hipStream_t s);
 template <int MODE> bool launch_bwd_pair(const BwdForm& f, const PipeBwdArgs& a, bool planned, hipStream_t s);
 

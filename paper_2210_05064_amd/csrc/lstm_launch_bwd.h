@@ -22,6 +22,7 @@ template <int MODE> bool launch_bwd_pair(const BwdForm& f, const PipeBwdArgs& a,
     if (planned) VER_BWD_DISPATCH(lstm_pipe_bwd_planned_kernel);
     else VER_BWD_DISPATCH(lstm_pipe_bwd_kernel);
 }
+template <int MODE> bool launch_bwd_triple(const BwdForm& f, const TripleBwdArgs& a, hipStream_t s) { VER_BWD_DISPATCH(lstm_triple_bwd_kernel); }
 #undef VER_BWD_DISPATCH
 #undef VER_BWD_LAUNCH
 

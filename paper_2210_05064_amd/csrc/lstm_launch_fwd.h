@@ -27,6 +27,7 @@ template <int MODE> bool launch_fwd_pair(const FwdForm& f, const PipeFwdArgs& a,
     if (planned) VER_FWD_DISPATCH(lstm_pipe_fwd_planned_kernel);
     else VER_FWD_DISPATCH(lstm_pipe_fwd_kernel);
 }
+template <int MODE> bool launch_fwd_triple(const FwdForm& f, const TripleFwdArgs& a, hipStream_t s) { VER_FWD_DISPATCH(lstm_triple_fwd_kernel); }
 #undef VER_FWD_DISPATCH
 #undef VER_FWD_LAUNCH
 

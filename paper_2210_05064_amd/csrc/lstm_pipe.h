@@ -1,4 +1,4 @@
-// Two LSTM layers in one launch.  gfx950 only.
+// Two LSTM layers in one launch, or three (at the end of this file).  gfx950 only.
 //
 // Paper: the policy is a multi-layer LSTM (section 4 "Architecture") evaluated over packed minibatches
 // (section 2.2).  The time loop of a layer is a chain of hundreds of dependent steps that leaves most of the
@@ -37,6 +37,7 @@
 namespace ver {
 
 constexpr int PIPE_GROUPS = 3;       // groups (XCDs) per layer
+constexpr int TRIPLE_GROUPS = 2;     // the same with three layers in a launch
 constexpr int PIPE_XCDS = 8;         // XCDs of the chip: those beyond the two layers' groups are workers
 static_assert(PIPE_XCDS - 2 * PIPE_GROUPS == 2, "two worker XCDs");
 
@@ -83,8 +84,8 @@ constexpr int PLAN_CT_FEW = 8, PLAN_CT_FEW_FAST = 4, PLAN_CT_MANY = 2;   // up t
 //   fp32 H=512  fwd   1.15  1.43  2.08  3.00  3.0   4.9   6.6   8.1  16        bwd  1.28  1.83  2.77  3.56  3.5   4.5   8.4  10.2  19
 // The constants are fitted by hand to it (without the step from four to five pieces, two short groups of fp32 got five and more
 // pieces each and ended 50 us after the long one: 2 x 512 on 1024 rows in 8).
-inline PlanCost plan_cost(int mode, bool wide, bool fwd, int G) {
-    const int teams = 2 * REC_MAX_GROUP / G;
+inline PlanCost plan_cost(int mode, bool wide, bool fwd, int G, int workers) {
+    const int teams = workers / G;
     if (mode == MODE_F32)
         return fwd ? PlanCost{0.85f, 0.25f, 0.7f, 0.06f, 2.2f, teams < 3 ? 256 : 0, 48, PLAN_CT_FEW} : PlanCost{0.85f, 0.42f, 0.45f, 0.06f, 3.f, 0, 0, PLAN_CT_FEW};
     if (wide) return fwd ? PlanCost{1.13f, 0.03f, 0.45f, 0.042f, 2.4f, 0, 0, PLAN_CT_FEW_FAST} : PlanCost{1.45f, 0.08f, 0.2f, 0.08f, 3.8f, 0, 0, PLAN_CT_FEW_FAST};
@@ -102,7 +103,8 @@ struct PipeWork {
     const int* plan;
     int* sync;          // progress, done counters (see above)
     int* err;
-    int G;              // workers per XCD; each owns N / G columns
+    int G;              // workers of a team; each owns N / G columns
+    int count;          // workers in all
     const int* alone;   // the planned kernels do nothing if it points to anything but a zero
 };
 
@@ -148,7 +150,7 @@ constexpr int PLAN_DIRS = 2;
 template <bool IN_LDS>
 __device__ __forceinline__ void plan_body(const int32_t* __restrict__ batch_sizes, int M, int n_seq, int T, int* __restrict__ plan_fwd,
                                           int* __restrict__ plan_bwd, float* __restrict__ scratch, int* s_bs, float* s_len, float* s_S1,
-                                          const PlanCost& pc_fwd, const PlanCost& pc_bwd) {
+                                          const PlanCost& pc_fwd, const PlanCost& pc_bwd, int groups) {
     constexpr int WAVES = PLAN_THREADS / 64;
     __shared__ float s_wf[WAVES];
     __shared__ float s_obj[WAVES];
@@ -197,12 +199,13 @@ __device__ __forceinline__ void plan_body(const int32_t* __restrict__ batch_size
     int bk1 = n_seq, bk2 = n_seq;
     for (int k1 = 1 + rank; k1 <= n_seq; k1 += PLAN_THREADS / PLAN_DIRS) {
         int lo = k1, hi = n_seq;
-        while (lo < hi) {
+        while (lo < hi && groups != TRIPLE_GROUPS) {
             const int mid = (lo + hi) >> 1;
             if (cost(k1, mid) >= cost(mid, n_seq)) hi = mid; else lo = mid + 1;
         }
         const float c0 = cost(0, k1);
-        for (int k2 = max(lo - 1, k1); k2 <= lo; ++k2) {
+        if (groups == TRIPLE_GROUPS) lo = n_seq;   // (the third block stays empty)
+        for (int k2 = groups == TRIPLE_GROUPS ? lo : max(lo - 1, k1); k2 <= lo; ++k2) {
             const float obj = fmaxf(c0, fmaxf(cost(k1, k2), cost(k2, n_seq)));
             if (obj < best) { best = obj; bk1 = k1; bk2 = k2; }
         }
@@ -247,6 +250,7 @@ struct PlanArgs {
     // Two layers share a launch up to min(most, base + T / per) alive pieces per timestep (average over the T timesteps); most = 0:
     // always.
     int base, per, most;
+    int groups;   // per layer
 };
 struct PlanLds {
     int bs[PLAN_LDS_N];
@@ -259,9 +263,9 @@ __device__ __forceinline__ void plan_launches(const PlanArgs& a, PlanLds& lds) {
     if (threadIdx.x == 0) a.plan_fwd[PLAN_ALONE] = a.plan_bwd[PLAN_ALONE] = alone ? 1 : 0;
     if (alone) return;
     if (n_seq <= PLAN_LDS_N && T <= PLAN_LDS_N)
-        plan_body<true>(a.batch_sizes, M, n_seq, T, a.plan_fwd, a.plan_bwd, a.scratch, lds.bs, lds.len, lds.S1, a.fwd, a.bwd);
+        plan_body<true>(a.batch_sizes, M, n_seq, T, a.plan_fwd, a.plan_bwd, a.scratch, lds.bs, lds.len, lds.S1, a.fwd, a.bwd, a.groups);
     else
-        plan_body<false>(a.batch_sizes, M, n_seq, T, a.plan_fwd, a.plan_bwd, a.scratch, lds.bs, lds.len, lds.S1, a.fwd, a.bwd);
+        plan_body<false>(a.batch_sizes, M, n_seq, T, a.plan_fwd, a.plan_bwd, a.scratch, lds.bs, lds.len, lds.S1, a.fwd, a.bwd, a.groups);
 }
 
 // One 128 x 256 tile of C[M, N] = A[M, K] B[N, K]^T + bias for bf16 operands, by 8 waves (2 x 4 of 64 x 64) of a workgroup
@@ -400,21 +404,25 @@ static __global__ __launch_bounds__(REC_THREADS) void lstm_proj_dma_kernel(ProjW
 // rows of a chunk.  Up to 16 pieces a chunk is a handful of tiles of 16 rows and every team is a set of its own; with
 // more, 16, 8 and 4 teams are two sets, so that a chunk of hundreds of rows does not wait for a single team.
 constexpr int WORK_COUNT = (PIPE_XCDS - 2 * PIPE_GROUPS) * REC_MAX_GROUP;
+constexpr int TRIPLE_WORK_COUNT = REC_MAX_GROUP;   // (three layers: an XCD for each of the two products)
+static_assert(PIPE_XCDS - 3 * TRIPLE_GROUPS == 2, "an XCD of workers per product");
 struct WorkDeal {
     int sets, share;   // a set is 1 << share teams
 };
-inline __host__ __device__ WorkDeal work_deal(int G, int cap) {
-    const int teams = WORK_COUNT / G;
+inline __host__ __device__ WorkDeal work_deal(int G, int cap, int count = WORK_COUNT) {
+    const int teams = count / G;
     const int share = cap > 16 && teams % 2 == 0 ? __builtin_ctz(teams) - 1 : 0;
     return WorkDeal{teams >> share, share};
 }
 
 // One group's view of the hand-over words, from the plan.
-__device__ __forceinline__ PipeLink pipe_link_of(const int* plan, int* sync, int M, int G, int g) {
+// out: the product that takes this layer's rows, in: the one that makes its input (with two layers the same for both).
+__device__ __forceinline__ PipeLink pipe_link_of(const PipeWork& out, const PipeWork& in, int g) {
+    const int* plan = in.plan;
     PipeLink pl;
-    pl.progress = sync + g;
-    pl.done = sync + 16 + g * pipe_done_stride(M);
-    pl.need = G << work_deal(G, plan[PLAN_KB + g + 1] - plan[PLAN_KB + g]).share;
+    pl.progress = out.sync + g;
+    pl.done = in.sync + 16 + g * pipe_done_stride(in.M);
+    pl.need = in.G << work_deal(in.G, plan[PLAN_KB + g + 1] - plan[PLAN_KB + g], in.count).share;
     pl.ct = plan[PLAN_CT + g];
     pl.T = plan[PLAN_T + g];
     return pl;
@@ -505,7 +513,7 @@ __device__ __forceinline__ void pipe_worker(const PipeWork& w, int id, unsigned 
         ct[g] = w.plan[PLAN_CT + g];
         const int n = (T[g] + ct[g] - 1) / ct[g];
         // this team's first chunk of the group in the consumer's order (none: behind the last)
-        const WorkDeal d = work_deal(w.G, cap[g]);
+        const WorkDeal d = work_deal(w.G, cap[g], w.count);
         const int first = team < d.sets << d.share ? ((team >> d.share) + g) % d.sets : n;
         at[g] = DESCEND ? n - 1 - first : first;
         step[g] = DESCEND ? -d.sets : d.sets;
@@ -691,7 +699,7 @@ __device__ __forceinline__ void pipe_fwd_body(const PipeFwdArgs& p, unsigned cha
     if (stamp) tl[0] = wall_clock64();
 #endif
     if (xcc < 2 * PIPE_GROUPS) {
-        const PipeLink link = pipe_link_of(p.work.plan, p.work.sync, p.work.M, p.work.G, g);
+        const PipeLink link = pipe_link_of(p.work, p.work, g);
         const PieceSet ps = pipe_pieces_of(p.work.plan, g);
         if (xcc < PIPE_GROUPS) {
             if (rank < p.l0.G)
@@ -738,7 +746,7 @@ __device__ __forceinline__ void pipe_bwd_body(const PipeBwdArgs& p, unsigned cha
     if (stamp) tl[0] = wall_clock64();
 #endif
     if (xcc < 2 * PIPE_GROUPS) {
-        const PipeLink link = pipe_link_of(p.work.plan, p.work.sync, p.work.M, p.work.G, g);
+        const PipeLink link = pipe_link_of(p.work, p.work, g);
         const PieceSet ps = pipe_pieces_of(p.work.plan, g);
         if (xcc < PIPE_GROUPS) {
             if (rank < p.l1.G)
@@ -765,6 +773,66 @@ __global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     const PipeBwdArgs& p = pipe_args_in_place<PipeBwdArgs>(p_by_value);
     if (*p.work.alone != 0) return;
     pipe_bwd_body<MODE, MT, KS, NI>(p, smem);
+}
+
+// ---- three layers -------------------------------------------------------------------------------------------------
+// The same with two XCDs per layer and one for each of the two products between them; the middle layer is consumer of one
+// and producer of the other.  A pair and then a top layer alone walk T_max dependent timesteps twice; here the third layer ends two
+// chunks after the first.  (Planned: run_fwd in lstm.hip says when it runs.)
+struct TripleFwdArgs {
+    RecFwdArgs l[3];     // producer, middle, consumer
+    PipeWork work[2];
+};
+struct TripleBwdArgs {
+    RecBwdArgs l[3];     // producer (the top layer), middle, consumer
+    PipeWork work[2];
+};
+template <typename F0, typename F1, typename F2, typename W>
+__device__ __forceinline__ void triple_roles(int xcc, int rank, int G, F0&& producer, F1&& middle, F2&& consumer, W&& worker) {
+    const int g = xcc % TRIPLE_GROUPS;
+    if (xcc < 3 * TRIPLE_GROUPS) {
+        if (rank >= G) return;
+        if (xcc < TRIPLE_GROUPS) producer(g);
+        else if (xcc < 2 * TRIPLE_GROUPS) middle(g);
+        else consumer(g);
+    } else if (xcc < PIPE_XCDS && rank < TRIPLE_WORK_COUNT) {
+        worker(xcc - 3 * TRIPLE_GROUPS);
+    }
+}
+template <int MODE, int TPW, int KS, int NBW, bool STATIC>
+__global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_triple_fwd_kernel(TripleFwdArgs p_by_value) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const TripleFwdArgs& p = pipe_args_in_place<TripleFwdArgs>(p_by_value);
+    if (*p.work[0].alone != 0) return;
+    int xcc;
+    const int rank = xcc_ticket(p.l[0].ticket, xcc);
+    triple_roles(xcc, rank, p.l[0].G,
+        [&](int g) { rec_fwd_body<MODE, TPW, KS, NBW, STATIC, PIPE_PRODUCER>(p.l[0], rank, pipe_pieces_of(p.work[0].plan, g), p.work[0].plan[PLAN_T + g],
+                         p.l[0].flags + xcc * REC_MAX_GROUP, pipe_link_of(p.work[0], p.work[0], g), smem); },
+        [&](int g) { rec_fwd_body<MODE, TPW, KS, NBW, STATIC, PIPE_MIDDLE>(p.l[1], rank, pipe_pieces_of(p.work[0].plan, g), p.work[0].plan[PLAN_T + g],
+                         p.l[1].flags + xcc * REC_MAX_GROUP, pipe_link_of(p.work[1], p.work[0], g), smem); },
+        [&](int g) { rec_fwd_body<MODE, TPW, KS, NBW, STATIC, PIPE_CONSUMER>(p.l[2], rank, pipe_pieces_of(p.work[0].plan, g), p.work[0].plan[PLAN_T + g],
+                         p.l[2].flags + xcc * REC_MAX_GROUP, pipe_link_of(p.work[1], p.work[1], g), smem); },
+        [&](int stage) {
+            constexpr int WMT = REC_WAVES / KS * TPW;
+            pipe_worker<MODE, WMT, FewBlocks<MODE, WMT == 8>::fwd, true, MODE == MODE_F32 && !STATIC>(p.work[stage], rank, smem);
+        });
+}
+template <int MODE, int MT, int KS, int NI>
+__global__ __launch_bounds__(REC_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_triple_bwd_kernel(TripleBwdArgs p_by_value) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const TripleBwdArgs& p = pipe_args_in_place<TripleBwdArgs>(p_by_value);
+    if (*p.work[0].alone != 0) return;
+    int xcc;
+    const int rank = xcc_ticket(p.l[0].ticket, xcc);
+    triple_roles(xcc, rank, p.l[0].G,
+        [&](int g) { rec_bwd_body<MODE, MT, KS, NI, PIPE_PRODUCER>(p.l[0], rank, pipe_pieces_of(p.work[0].plan, g), p.work[0].plan[PLAN_T + g],
+                         p.l[0].flags + xcc * REC_MAX_GROUP, pipe_link_of(p.work[0], p.work[0], g), smem); },
+        [&](int g) { rec_bwd_body<MODE, MT, KS, NI, PIPE_MIDDLE>(p.l[1], rank, pipe_pieces_of(p.work[0].plan, g), p.work[0].plan[PLAN_T + g],
+                         p.l[1].flags + xcc * REC_MAX_GROUP, pipe_link_of(p.work[1], p.work[0], g), smem); },
+        [&](int g) { rec_bwd_body<MODE, MT, KS, NI, PIPE_CONSUMER>(p.l[2], rank, pipe_pieces_of(p.work[0].plan, g), p.work[0].plan[PLAN_T + g],
+                         p.l[2].flags + xcc * REC_MAX_GROUP, pipe_link_of(p.work[1], p.work[1], g), smem); },
+        [&](int stage) { pipe_worker<MODE, MT, FewBlocks<MODE, MT == 2>::bwd, false, false>(p.work[stage], rank, smem); });
 }
 
 }  // namespace ver

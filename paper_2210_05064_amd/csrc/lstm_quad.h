@@ -116,7 +116,7 @@ __device__ __forceinline__ bool quad_fwd(FewFwd<MODE, MT, NB>& s, const RecFwdAr
     bar_lds();
     constexpr int WHOLE = (int)0x80000000u;
     const __amdgpu_buffer_rsrc_t rs_g = __builtin_amdgcn_make_buffer_rsrc(a.gates, 0, WHOLE, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rs_hc = __builtin_amdgcn_make_buffer_rsrc(a.hcopy, 0, PIPE == PIPE_PRODUCER ? WHOLE : 0, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_hc = __builtin_amdgcn_make_buffer_rsrc(a.hcopy, 0, (PIPE & PIPE_PRODUCER) ? WHOLE : 0, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_ring = __builtin_amdgcn_make_buffer_rsrc(ring, 0, (int)(FEW_RING * slot), 0x00020000);
     const unsigned g_off = (unsigned)(n * 4 * H + j0 * 4 + col) * 4u;   // bytes inside a timestep's gates rows
     const unsigned h_off = (unsigned)(n * H + j0 + u);                  // elements inside those of an [M, H] array
@@ -125,13 +125,13 @@ __device__ __forceinline__ bool quad_fwd(FewFwd<MODE, MT, NB>& s, const RecFwdAr
     // lane 0 of a quad stores the cell state, 1 h, 2 the words of hprev: one instruction
     unsigned char* const to_c = reinterpret_cast<unsigned char*>(a.c), * const to_h = reinterpret_cast<unsigned char*>(a.hout), * const to_hp = static_cast<unsigned char*>(a.hprev);
     unsigned char* const side = (q == 0 ? to_c : q == 1 ? to_h : to_hp) + h_off * (q == 2 ? (unsigned)es : 4u);
-    const bool side_ch = q == 0 || (q == 1 && PIPE != PIPE_PRODUCER), side_hp = q == 2 && (MODE == MODE_F32 || (u & 1) == 0);
+    const bool side_ch = q == 0 || (q == 1 && !(PIPE & PIPE_PRODUCER)), side_hp = q == 2 && (MODE == MODE_F32 || (u & 1) == 0);
     // the non-linearity of this lane's gate: e = 2^(k x), value = ga / (1 + e) + gb (sigmoid, or tanh for gate 2)
     const float k_exp = q == 2 ? 2.8853900817779268f : -1.4426950408889634f, ga = q == 2 ? -2.f : 1.f, gb = q == 2 ? 1.f : 0.f;
     float s_g = 0.f, s_h = 0.f;               // with s_c: results of the timestep before, not yet stored
     unsigned s_w = 0;
     int bs_prev = 0;                          // pieces they belong to
-    int edge = PIPE == PIPE_CONSUMER && s.c_wait * pl.ct < T ? s.c_wait * pl.ct : 0x7fffffff;   // first timestep of the chunk to wait for
+    int edge = (PIPE & PIPE_CONSUMER) && s.c_wait * pl.ct < T ? s.c_wait * pl.ct : 0x7fffffff;   // first timestep of the chunk to wait for
     int off_bs = grp_count(s.bs_a, ps);
     unsigned off[L];
     quad_offsets<L, BPL>(off, (unsigned)(piece * H) * es + k_off, piece < off_bs, blk, s.n_blk);
@@ -146,7 +146,7 @@ __device__ __forceinline__ bool quad_fwd(FewFwd<MODE, MT, NB>& s, const RecFwdAr
         if (side_ch || (side_hp && m < bs)) {
             *reinterpret_cast<unsigned*>(side + (q == 2 ? so_hp : so_c)) = q == 0 ? vc : q == 1 ? vh : vw;
         }
-        if (PIPE == PIPE_PRODUCER && word_lane)   // written through: input of the workers' product
+        if ((PIPE & PIPE_PRODUCER) && word_lane)   // written through: input of the workers' product
             __builtin_amdgcn_raw_buffer_store_b32(s_w, rs_hc, h_off * es, so_hc, 17);
     };
 
@@ -160,7 +160,7 @@ __device__ __forceinline__ bool quad_fwd(FewFwd<MODE, MT, NB>& s, const RecFwdAr
         const int base_next = s.base + s.bs_a;
         s.win.advance(t + 2);
         int to_edge = 0x7fffffff;   // consumer: timesteps until the next chunk has to be there
-        if (PIPE == PIPE_CONSUMER) {
+        if (PIPE & PIPE_CONSUMER) {
             if (t + 1 == edge) {
                 if (!s.ready && !pipe_wait_chunk(pl, s.c_wait, a.err)) {
                     alive = false;
@@ -182,7 +182,7 @@ __device__ __forceinline__ bool quad_fwd(FewFwd<MODE, MT, NB>& s, const RecFwdAr
                 alive = false;
                 break;
             }
-            if (PIPE == PIPE_PRODUCER && rank == 0 && tid == 0 && t > 0) st_agent(pl.progress, t);
+            if ((PIPE & PIPE_PRODUCER) && rank == 0 && tid == 0 && t > 0) st_agent(pl.progress, t);
             if (polls) {
                 const unsigned char* rows = reinterpret_cast<const unsigned char*>(static_cast<const E*>(a.hprev) + (size_t)(s.base + x) * H);
                 unsigned first[L];
@@ -196,7 +196,7 @@ __device__ __forceinline__ bool quad_fwd(FewFwd<MODE, MT, NB>& s, const RecFwdAr
         few_touch(z2);
         few_touch(s.win.cur);
         few_touch(s.win.other);
-        if (PIPE == PIPE_CONSUMER) few_touch(s.have);
+        if (PIPE & PIPE_CONSUMER) few_touch(s.have);
         if (!ok) *s.fail = 1;
         const float z = z2;
         float* part = s.part + (t & 1) * (REC_WAVES * PART);
@@ -207,7 +207,7 @@ __device__ __forceinline__ bool quad_fwd(FewFwd<MODE, MT, NB>& s, const RecFwdAr
         });
         // A look at the chunk that the next timestep asks for: usually finished, which saves that wait its round trip.  Its
         // counter is requested a timestep earlier.
-        if (PIPE == PIPE_CONSUMER && to_edge <= 2) {
+        if ((PIPE & PIPE_CONSUMER) && to_edge <= 2) {
             if (to_edge == 1) {
                 if (tid == REC_THREADS - 1) s.fail[1] = s.have;
                 s.have = 0;
@@ -219,7 +219,7 @@ __device__ __forceinline__ bool quad_fwd(FewFwd<MODE, MT, NB>& s, const RecFwdAr
         const int failed = *s.fail;   // (looked at after the publication: its read is not waited for by itself)
         // Every workgroup has published the rows of timestep t-1, which it did after its stores for timestep t-3 had
         // completed (they are issued in timestep t-2 and waited for in timestep t-1).
-        if (PIPE == PIPE_PRODUCER && rank == 0 && tid == REC_THREADS - 1 && t - 2 > s.t0) st_agent(pl.progress, t - 2);
+        if ((PIPE & PIPE_PRODUCER) && rank == 0 && tid == REC_THREADS - 1 && t - 2 > s.t0) st_agent(pl.progress, t - 2);
         if (m < bs) {
             float o[REC_WAVES];
             const float* p = part + m * ROW + col;
@@ -246,7 +246,7 @@ __device__ __forceinline__ bool quad_fwd(FewFwd<MODE, MT, NB>& s, const RecFwdAr
         }
         if (polls) quad_request<L>(rs_ring, off, so_w, raw);   // (after the last timestep: nothing, from beyond the buffer)
         __builtin_amdgcn_sched_barrier(0);
-        if (PIPE == PIPE_CONSUMER && to_edge == 1) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= pl.need;
+        if ((PIPE & PIPE_CONSUMER) && to_edge == 1) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= pl.need;
         if (__builtin_amdgcn_readfirstlane(failed)) {
             alive = false;
             break;
@@ -386,14 +386,14 @@ __device__ __forceinline__ bool quad_bwd_loop(QuadBwd<MODE, MT, NB, PIPE>& d, Fe
         __builtin_amdgcn_sched_barrier(0);
         unsigned so_dz = (unsigned)s.base * (unsigned)(K * es);
         if (t == 0) {   // nothing is carried before the first timestep
-            if (m < bs && (MODE == MODE_F32 || (q & 1) == 0)) __builtin_amdgcn_raw_buffer_store_b32(word, rs_dz, dz_off, so_dz, PIPE == PIPE_PRODUCER ? 17 : 0);
+            if (m < bs && (MODE == MODE_F32 || (q & 1) == 0)) __builtin_amdgcn_raw_buffer_store_b32(word, rs_dz, dz_off, so_dz, (PIPE & PIPE_PRODUCER) ? 17 : 0);
             --t;
             break;
         }
         const int bs_3 = grp_count(d.bs_m3, ps);
         s.win.advance(t - 4);
         int to_edge = 0x7fffffff;   // consumer: timesteps until the chunk below has to be there
-        if (PIPE == PIPE_CONSUMER) {
+        if (PIPE & PIPE_CONSUMER) {
             if (t - 3 < edge && t >= 3) {
                 --s.c_wait;
                 if (!s.ready && !pipe_wait_chunk(pl, s.c_wait, a.err)) {
@@ -421,7 +421,7 @@ __device__ __forceinline__ bool quad_bwd_loop(QuadBwd<MODE, MT, NB, PIPE>& d, Fe
         quad_touch(d.r1);
         few_touch(s.win.cur);
         few_touch(s.win.other);
-        if (PIPE == PIPE_CONSUMER) few_touch(s.have);
+        if (PIPE & PIPE_CONSUMER) few_touch(s.have);
         if (!ok) *s.fail = 1;
         const int bs_m4 = s.win.at(t - 4);
         d.r0 = d.r1;
@@ -429,10 +429,10 @@ __device__ __forceinline__ bool quad_bwd_loop(QuadBwd<MODE, MT, NB, PIPE>& d, Fe
         quad_product<MODE, MT, NB, P, L>(s.w, raw, bs, s.n_blk, part + s.slice * PART, polls, [&]() __attribute__((always_inline)) {
             // the dz rows of this timestep, the saved activations of timestep t-3
             if (m < bs_3 && m < QUAD_MAX) quad_load_saved(d.r1, a, m, n, g_col, h_col, t - 3, bs_2, (int)base_3, (int)base_3 - bs_m4);
-            if (m < bs && (MODE == MODE_F32 || (q & 1) == 0)) __builtin_amdgcn_raw_buffer_store_b32(word, rs_dz, dz_off, so_dz, PIPE == PIPE_PRODUCER ? 17 : 0);
+            if (m < bs && (MODE == MODE_F32 || (q & 1) == 0)) __builtin_amdgcn_raw_buffer_store_b32(word, rs_dz, dz_off, so_dz, (PIPE & PIPE_PRODUCER) ? 17 : 0);
         });
         // a look at the chunk that the next timestep asks for, see the forward loop
-        if (PIPE == PIPE_CONSUMER && to_edge <= 2) {
+        if ((PIPE & PIPE_CONSUMER) && to_edge <= 2) {
             if (to_edge == 1) {
                 if (tid == REC_THREADS - 1) s.fail[1] = s.have;
                 s.have = 0;
@@ -444,13 +444,13 @@ __device__ __forceinline__ bool quad_bwd_loop(QuadBwd<MODE, MT, NB, PIPE>& d, Fe
         const int failed = *s.fail;
         // Every workgroup has published the rows of timestep t, which it did after its dz rows of timestep t+2 had
         // completed (they are stored in that timestep and waited for in timestep t+1).
-        if (PIPE == PIPE_PRODUCER && rank == 0 && tid == REC_THREADS - 1 && t + 2 < T) st_agent(pl.progress, T - (t + 2));
+        if ((PIPE & PIPE_PRODUCER) && rank == 0 && tid == REC_THREADS - 1 && t + 2 < T) st_agent(pl.progress, T - (t + 2));
         if (m < bs) {
             const float* p = part + m * ROW + u + 2 * q * PART;   // (a lane adds two of the eight)
             d.dh = quad_sum(p[0] + p[PART]);
             if (MODE == MODE_F32 || (q & 1) == 0) __builtin_amdgcn_raw_buffer_store_b32(FEW_EMPTY, rs_ring, w_off, so_e, 0);
         }
-        if (PIPE == PIPE_CONSUMER && to_edge == 1) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= pl.need;
+        if ((PIPE & PIPE_CONSUMER) && to_edge == 1) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= pl.need;
         if (__builtin_amdgcn_readfirstlane(failed)) {
             alive = false;
             break;
@@ -486,7 +486,7 @@ __device__ __forceinline__ bool quad_bwd(FewBwd<MODE, MT, NB>& s, const RecBwdAr
     d.r0.g = d.r0.c_prev = d.r0.dh_above = d.r0.c = 0.f;
     d.r1 = d.r0;
     d.bs_m3 = s.win.at(t - 3);
-    if (PIPE == PIPE_CONSUMER)   // saved gradients of timesteps down to t-2 are read here
+    if (PIPE & PIPE_CONSUMER)   // saved gradients of timesteps down to t-2 are read here
         while (s.c_wait > 0 && t - 2 < s.c_wait * pl.ct) {
             --s.c_wait;
             if (!pipe_wait_chunk(pl, s.c_wait, a.err)) return false;

@@ -49,7 +49,7 @@ namespace ver {
 #define VER_REC_PROF_GROUP 0
 #endif
 #define REC_PROF_DECL long long prof_t = 0; long long* prof_out = a.prof; const bool prof_on = threadIdx.x == 0 && rank == 0 && ps.id == VER_REC_PROF_GROUP;
-#define REC_PROF_START() do { if (prof_on) prof_t = clock64(); if (threadIdx.x == 0 && rank == 0 && PIPE != PIPE_NONE) a.prof_all[112 + ps.id + (PIPE == PIPE_CONSUMER ? 3 : 0)] = wall_clock64(); } while (0)
+#define REC_PROF_START() do { if (prof_on) prof_t = clock64(); if (threadIdx.x == 0 && rank == 0 && PIPE != PIPE_NONE) a.prof_all[112 + ps.id + ((PIPE & PIPE_CONSUMER) ? 3 : 0)] = wall_clock64(); } while (0)
 #define REC_PROF_MARK(i) do { if (prof_on) { long long now_ = clock64(); prof_out[i] += now_ - prof_t; prof_t = now_; } } while (0)
 #define REC_PROF_STEP() do { if (prof_on) prof_out[15] += 1; } while (0)
 #else
@@ -345,7 +345,7 @@ __device__ __forceinline__ void mma_dispatch(const f32x4_t (&wreg)[NW], const ty
 // (16 rows at a time); a consumer group waits for the chunk that holds its next timestep.  Groups never wait
 // for each other.  Everything that crosses XCDs is written through to memory (the L2s of different XCDs are not
 // coherent), completed (s_waitcnt) before it is announced, and announced/read with agent-scope atomics.
-enum { PIPE_NONE = 0, PIPE_PRODUCER = 1, PIPE_CONSUMER = 2 };
+enum { PIPE_NONE = 0, PIPE_PRODUCER = 1, PIPE_CONSUMER = 2, PIPE_MIDDLE = 3 };   // (bits: the middle layer of three is both)
 // One group's view of the hand-over (producer and consumer groups with the same index run the same pieces).
 struct PipeLink {
     int* progress;   // the group's word: timesteps whose producer rows are complete in memory
@@ -577,7 +577,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
     rec_publish(flags, rank, 1);
     REC_PROF_DECL
     REC_PROF_START();
-    if (PIPE == PIPE_CONSUMER && T > 0 && !pipe_wait_chunk(pl, 0, a.err, REC_PROF_CHUNK_ACC(a, rank, ps))) return;
+    if ((PIPE & PIPE_CONSUMER) && T > 0 && !pipe_wait_chunk(pl, 0, a.err, REC_PROF_CHUNK_ACC(a, rank, ps))) return;
     int c_wait = 1;   // consumer: the chunk it has to wait for next
     if (t0 > 0) {
     // this wave's rows of W_hh (its share of the contraction) -> registers, in MFMA operand layout
@@ -635,7 +635,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
     const __amdgpu_buffer_rsrc_t rs_c = __builtin_amdgcn_make_buffer_rsrc(a.c, 0, WHOLE, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_h = __builtin_amdgcn_make_buffer_rsrc(a.hout, 0, WHOLE, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_hp = __builtin_amdgcn_make_buffer_rsrc(hprev, 0, WHOLE, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rs_hcopy = __builtin_amdgcn_make_buffer_rsrc(a.hcopy, 0, PIPE == PIPE_PRODUCER ? WHOLE : 0, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_hcopy = __builtin_amdgcn_make_buffer_rsrc(a.hcopy, 0, (PIPE & PIPE_PRODUCER) ? WHOLE : 0, 0x00020000);
     for (int t = 0; t < t0; ++t) {
         // (the compiler reads it with a vector load, since it cannot prove the array constant; left alone it would
         // wait for that load, and for every store in flight before it, right here at the top of the step: the
@@ -644,7 +644,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
         // bs, bs_next: this group's alive pieces; its piece m sits in packed row base + m * X + x
         const int bs_all = bs_a, bs = grp_count(bs_all, ps);
         const int bs_next = (t + 1 < T) ? grp_count(bs_b, ps) : 0, base_next = base + bs_all;
-        if (PIPE == PIPE_CONSUMER && t + 1 < T && t + 1 == c_wait * pl.ct) {
+        if ((PIPE & PIPE_CONSUMER) && t + 1 < T && t + 1 == c_wait * pl.ct) {
             if (!pipe_wait_chunk(pl, c_wait, a.err, REC_PROF_CHUNK_ACC(a, rank, ps))) return;
             ++c_wait;
         }
@@ -656,7 +656,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
         const unsigned so_gnext = (unsigned)base_next * row_g, so_hnext = (unsigned)base_next * (unsigned)(H * (int)sizeof(E));
         if (!rec_wait(flags, G, t + 1, a.err)) return;
         // every workgroup of the group has raised its flag for timestep t-1, i.e. completed that step's stores
-        if (PIPE == PIPE_PRODUCER && rank == 0 && tid == 0 && t > 0) st_agent(pl.progress, t);
+        if ((PIPE & PIPE_PRODUCER) && rank == 0 && tid == 0 && t > 0) st_agent(pl.progress, t);
         REC_PROF_MARK(0);
         for (int c0 = 0; c0 < bs; c0 += 16 * ntc) {
             const int rows = min(bs - c0, 16 * ntc), nt = (rows + 15) >> 4;
@@ -719,11 +719,11 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
                             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, f32x4_t{gi, gf, gg, go}), rs_g, go_, so_g, 0);
                             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(cn), rs_c, go_ >> 2, so_c, 0);
                             // (the producer layer of a two-layer launch hands h on in operand type only: hcopy below)
-                            if (PIPE != PIPE_PRODUCER) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(hn), rs_h, go_ >> 2, so_c, 0);
+                            if (!(PIPE & PIPE_PRODUCER)) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(hn), rs_h, go_ >> 2, so_c, 0);
                         } else {
                             *gp = f32x4_t{gi, gf, gg, go};
                             a.c[p * H + je] = cn;
-                            if (PIPE != PIPE_PRODUCER) a.hout[p * H + je] = hn;
+                            if (!(PIPE & PIPE_PRODUCER)) a.hout[p * H + je] = hn;
                         }
                     }
                     // h_t goes to the exchange row of the next timestep through LDS (below)
@@ -743,7 +743,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
                     const u32x4_t v = *reinterpret_cast<const u32x4_t*>(sH + r * UH + pc * VEC);
                     __builtin_amdgcn_raw_buffer_store_b128(v, rs_hp, (((c0 + r) * X + x) * H + j0 + pc * VEC) * (int)sizeof(E), so_hnext, 0);
                 }
-                if (PIPE == PIPE_PRODUCER) {
+                if (PIPE & PIPE_PRODUCER) {
                     // h_t of every row of the chunk in operand type, written through: input of the workers' GEMM
                     for (int i = tid; i < min(rows, bs - c0) * PIECES; i += REC_THREADS) {
                         const int r = i / PIECES, pc = i % PIECES;
@@ -754,7 +754,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
             }
         }
         REC_PROF_MARK(3);
-        if (t + 1 < T || PIPE == PIPE_PRODUCER) rec_publish(flags, rank, t + 2);
+        if (t + 1 < T || (PIPE & PIPE_PRODUCER)) rec_publish(flags, rank, t + 2);
         asm volatile("" : "+v"(bs_c_v));
         const int bs_c = __builtin_amdgcn_readfirstlane(bs_c_v);
 #pragma unroll
@@ -772,7 +772,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
         asm volatile("" : "+v"(lds));   // (known to be the start of the dynamic LDS, it would be read from a table wherever it is used)
         if (!few_fwd<MODE, MT, PIPE>((few_args_t<RecFwdArgs>)&a, ps.x, ps.cap, ps.id, rank, t0, T, flags, pl.progress, pl.done, pl.need, pl.ct, c_wait, lds)) return;
     }
-    if (PIPE == PIPE_PRODUCER && rank == 0) {   // the last timestep is complete once every flag says so
+    if ((PIPE & PIPE_PRODUCER) && rank == 0) {   // the last timestep is complete once every flag says so
         if (T > 0 && !rec_wait(flags, G, T + 1, a.err)) return;
         if (tid == 0) st_agent(pl.progress, T);
     }
@@ -840,7 +840,7 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& by_ref, int rank,
     static_assert(REC_THREADS % UH == 0, "a thread keeps its unit");
     float db[4] = {0.f, 0.f, 0.f, 0.f};
     int c_wait = T > 0 ? (T - 1) / pl.ct : 0;   // consumer: the chunk of the timestep it runs next
-    if (PIPE == PIPE_CONSUMER && T > 0 && !pipe_wait_chunk(pl, c_wait, a.err, REC_PROF_CHUNK_ACC(a, rank, ps))) return;
+    if ((PIPE & PIPE_CONSUMER) && T > 0 && !pipe_wait_chunk(pl, c_wait, a.err, REC_PROF_CHUNK_ACC(a, rank, ps))) return;
     // Timesteps >= t_few have at most FEW_MAX alive pieces and run in the form of lstm_few.h (flag value 1: the
     // workgroup has emptied its words of the exchange ring).
     const int n_seq = grp_count(a.info[0], ps);
@@ -860,7 +860,7 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& by_ref, int rank,
         dcreg = out.dc;
 #pragma unroll
         for (int i = 0; i < 4; ++i) db[i] = out.db[i];
-        if (t_few == 0 && PIPE == PIPE_PRODUCER) {   // the last rows are complete once every flag says so
+        if (t_few == 0 && (PIPE & PIPE_PRODUCER)) {   // the last rows are complete once every flag says so
             rec_publish(flags, rank, T + 1);
             if (rank == 0) {
                 if (!rec_wait(flags, G, T + 1, a.err)) return;
@@ -947,18 +947,18 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& by_ref, int rank,
             // (written through in a two-layer launch: the rows are also read by the workers on other XCDs)
                         const float dzi = dc * gg * gi * (1.f - gi), dzf = dc * sv.c_prev * gf * (1.f - gf), dzg = dc * gi * (1.f - gg * gg),
                         dzo = dh * tc * go * (1.f - go);
-            st_row4_buf<E, PIPE == PIPE_PRODUCER ? 17 : 0>(rs_dzall, (n * K + j * 4) * (int)sizeof(E), so_dz, dzi, dzf, dzg, dzo);
+            st_row4_buf<E, (PIPE & PIPE_PRODUCER) ? 17 : 0>(rs_dzall, (n * K + j * 4) * (int)sizeof(E), so_dz, dzi, dzf, dzg, dzo);
             db[0] += dzi; db[1] += dzf; db[2] += dzg; db[3] += dzo;
             if (first) dcreg = dc * gf;
             else a.dc_state[(size_t)n * H + j] = dc * gf;
         }
-        if (t == 0 && PIPE != PIPE_PRODUCER) break;  // nothing is carried before the first timestep
+        if (t == 0 && !(PIPE & PIPE_PRODUCER)) break;  // nothing is carried before the first timestep
         REC_PROF_MARK(8);
         rec_publish(flags, rank, T - t + 1);
         REC_PROF_MARK(9);
         if (t == 0 && rank != 0) break;
         if (t > 0) {
-            if (PIPE == PIPE_CONSUMER && t == c_wait * pl.ct) {   // timestep t-1 opens the chunk below
+            if ((PIPE & PIPE_CONSUMER) && t == c_wait * pl.ct) {   // timestep t-1 opens the chunk below
                 --c_wait;
                 if (!pipe_wait_chunk(pl, c_wait, a.err, REC_PROF_CHUNK_ACC(a, rank, ps))) return;
             }
@@ -983,7 +983,7 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& by_ref, int rank,
         }
         if (!rec_wait(flags, G, T - t + 1, a.err, REC_WAVES - 1)) return;
         // every workgroup of the group has completed the dz rows of timesteps >= t
-        if (PIPE == PIPE_PRODUCER && rank == 0 && tid == 0) st_agent(pl.progress, T - t);
+        if ((PIPE & PIPE_PRODUCER) && rank == 0 && tid == 0) st_agent(pl.progress, T - t);
         if (t == 0) break;
         REC_PROF_MARK(10);
         // B. dh carried to t-1: dh[n][k] = sum_q dz[n][q] * W_hh[q][k] for this workgroup's columns k

@@ -592,3 +592,36 @@ def test_one_to_five_pieces_per_group(ver, compute, hidden, n_envs, layers):
     rows the largest of 4 million elements is at 7e-2 in any form)."""
     w = wl.Workload("quad", n_envs, 24 * n_envs, 0, 0, 0.9, 20, layers, hidden, 1, 3, 0.01, 1, 1, bool(compute))
     case(ver, w, seed=70 + n_envs, compute=compute, x_bf16=bool(compute))
+
+
+@pytest.mark.parametrize("n_envs,steps,hidden,compute", [
+    (1, 30, 64, 1), (3, 40, 320, 0), (9, 60, 64, 0), (9, 60, 512, 0), (24, 50, 320, 1), (40, 30, 128, 1)])
+def test_three_layers_in_a_launch(ver, n_envs, steps, hidden, compute):
+    """Ragged pieces, with and without the choice of a launch per layer, workers that hold the weights one to eight times, groups without pieces."""
+    w = wl.Workload("three", n_envs, steps * n_envs, 0, 0, 0.9, 36, 3, hidden, 1, 3, 0.01, 1, 1, bool(compute))
+    case(ver, w, seed=90 + n_envs, compute=compute, x_bf16=bool(compute))
+
+
+@pytest.mark.parametrize("pieces,steps,compute,hidden", [(46, 12, 1, 64), (47, 12, 1, 64), (35, 10, 0, 128), (36, 10, 0, 128), (10, 20, 0, 384), (11, 20, 0, 384)])
+def test_three_layers_lines(ver, pieces, steps, compute, hidden):
+    """Three layers share a launch up to 46 alive pieces per timestep, fp32 30 + T / 2, from 384 units on T / 2: both sides."""
+    even(ver, pieces, steps, 3, compute, hidden)
+
+
+@pytest.mark.parametrize("n_envs,steps,hidden", [(5, 40, 576), (24, 50, 1024)])
+def test_three_wide_layers(ver, n_envs, steps, hidden):
+    """In a launch and layer by layer: either is up to 7e-3 from the exact gradients in the 2-norm (tests/util.py), so up to twice that from the other."""
+    w = wl.Workload("three", n_envs, steps * n_envs, 0, 0, 0.9, 36, 3, hidden, 1, 3, 0.01, 1, 1, True)
+    ro = wl.make_rollout(w, seed=n_envs, bias_scale=0.2)
+    meta = opack.pack_minibatch(ro["dones"], ro["env_off"], ro["seq_key"][0], 1, 0, ro["env_started_episode"])
+    rng = np.random.default_rng(n_envs)
+    M = meta["M"]
+    d_u, d_v = (rng.standard_normal((M, w.act_dim)) / M).astype(np.float32), (rng.standard_normal(M) / M).astype(np.float32)
+    res = []
+    for layer_by_layer in (False, True):
+        run = LstmRun(ver, w, ro["weights"], opack.gather_rows(ro["obs"], meta["gather_idx"]), meta, compute=1, layer_by_layer=layer_by_layer)
+        u, v = run.forward()
+        grads, dx = run.backward(d_u, d_v)
+        res.append([u, v, dx] + grads)
+    for a, b in zip(*res):
+        assert l2_rel_err(a, b) <= 1.4e-2
