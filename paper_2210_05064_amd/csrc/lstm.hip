@@ -390,6 +390,7 @@ struct LstmWs {
     float* gemm_part;  // partial results of split contractions
     bf16_t* x_op;      // [M, input_dim]: fp32 input rows of a bf16 call in the operand type
     char* ring;        // [8 groups] exchange rings of the time loops (lstm_few.h)
+    char* ring_many;   // [8 groups] the same for more than 16 pieces (lstm_many.h)
     float* db_part;    // [2 or 3][8][4H]: per layer of a launch and group, the sum of the gate gradients over the group's rows
     size_t bytes;
 };
@@ -460,6 +461,7 @@ inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws)
     ws->x_op = c.compute && !c.x_bf16 ? cv.take<bf16_t>(Mz * c.input_dim) : nullptr;
     ws->db_part = cv.take<float>((size_t)(three ? 3 : 2) * REC_GROUPS * 4 * H);
     ws->ring = cv.take<char>(REC_GROUPS * few_ring_bytes(c.compute ? MODE_BF16 : MODE_F32, 4 * c.hidden));
+    ws->ring_many = cv.take<char>(REC_GROUPS * many_ring_bytes(c.compute ? MODE_BF16 : MODE_F32, c.hidden, many_rows(M)));
     ws->bytes = cv.used;
 }
 
@@ -627,6 +629,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     size_t lds = ntc * (tile + red_per_tile);
     const int few_nb = wide ? FewBlocks<MODE, true>::fwd : FewBlocks<MODE, false>::fwd;
     if (few_lds_bytes(16 * mt, few_nb) > lds) lds = few_lds_bytes(16 * mt, few_nb);
+    if (many_lds_bytes(16 * mt, few_nb) > lds) lds = many_lds_bytes(16 * mt, few_nb);
     const size_t work_lds = work_lds_bytes(16 * mt, few_nb, work_bufs<MODE, true>());
     if (pairs && work_lds > lds) lds = work_lds;
     const int nb = (H / ks) / RecGeom<MODE>::KBLK;
@@ -677,6 +680,8 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         ra.info = info; ra.batch_sizes = batch_sizes; ra.t_off = t_off;
         ra.gates = L.gates; ra.c = L.c; ra.hout = L.hout; ra.hprev = L.hprev; ra.hcopy = L.hcopy; ra.whh = L.whh;
         ra.ring = ws.ring + groups_before * few_ring_bytes(MODE, H);
+        ra.many_rows = many_rows(M);
+        ra.ring_many = ws.ring_many + groups_before * many_ring_bytes(MODE, H, many_rows(M));
         ra.h0 = h0 ? h0 + (size_t)l * seq_cap * H : nullptr;
         ra.c0 = c0 ? c0 + (size_t)l * seq_cap * H : nullptr;
         ra.H = H; ra.seq_cap = seq_cap; ra.M = M; ra.flags = ws.flags; ra.ticket = ws.flags + 8 * REC_MAX_GROUP;

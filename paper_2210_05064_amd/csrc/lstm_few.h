@@ -923,3 +923,4 @@ __device__ __forceinline__ FewBwdOut few_bwd(few_args_t<RecBwdArgs> args, int x_
 }  // namespace ver
 
 #include "lstm_quad.h"
+#include "lstm_many.h"

@@ -474,6 +474,8 @@ struct RecFwdArgs {
     void* hcopy;        // [M, H] operand type: row p = h_t, written through for the workers (producer layer only)
     const void* whh;    // [4H, H] operand type, interleaved rows
     void* ring;         // exchange ring of the layer's groups (lstm_few.h)
+    void* ring_many;    // the same for more than 16 pieces, many_rows rows per slot (lstm_many.h)
+    int many_rows;
     const float* h0;    // [seq_cap, H] of this layer, or NULL
     const float* c0;
     int H, seq_cap, M;
@@ -574,12 +576,23 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
     // From timestep t0 on at most FEW_MAX pieces of the group are alive: those timesteps run in the form of lstm_few.h.
     const int t0 = n_seq > FEW_MAX ? __builtin_amdgcn_readfirstlane(grp_steps(a.batch_sizes, T, FEW_MAX * X + x)) : 0;
     few_clear_ring<MODE>(static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, H), H, j0, UH);
+    // From timestep t_many on at most MANY_MAX are: lstm_many.h, which has both sides of the line.
+    const int t_many = !many_pays<MODE>(H) ? t0 : n_seq > MANY_MAX ? __builtin_amdgcn_readfirstlane(grp_steps(a.batch_sizes, T, MANY_MAX * X + x)) : 0;
+    if (t_many < t0) {   // empties this workgroup's words of that form's ring
+        constexpr int words = UH * (int)sizeof(E) / 4;
+        const int rows = a.many_rows, used = min(n_seq, rows);
+        unsigned* ring = reinterpret_cast<unsigned*>(static_cast<unsigned char*>(a.ring_many) + ps.id * many_ring_bytes(MODE, H, rows));
+        for (int i = tid; i < FEW_RING * used * words; i += REC_THREADS) {
+            const int r = i / words, k = r / used;
+            ring[((size_t)k * rows + r % used) * (H * (int)sizeof(E) / 4) + j0 * (int)sizeof(E) / 4 + i % words] = FEW_EMPTY;
+        }
+    }
     rec_publish(flags, rank, 1);
     REC_PROF_DECL
     REC_PROF_START();
     if ((PIPE & PIPE_CONSUMER) && T > 0 && !pipe_wait_chunk(pl, 0, a.err, REC_PROF_CHUNK_ACC(a, rank, ps))) return;
     int c_wait = 1;   // consumer: the chunk it has to wait for next
-    if (t0 > 0) {
+    if (t_many > 0) {
     // this wave's rows of W_hh (its share of the contraction) -> registers, in MFMA operand layout
     f32x4_t wreg[TPW * NBW];
 #pragma unroll
@@ -636,7 +649,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
     const __amdgpu_buffer_rsrc_t rs_h = __builtin_amdgcn_make_buffer_rsrc(a.hout, 0, WHOLE, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_hp = __builtin_amdgcn_make_buffer_rsrc(hprev, 0, WHOLE, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_hcopy = __builtin_amdgcn_make_buffer_rsrc(a.hcopy, 0, (PIPE & PIPE_PRODUCER) ? WHOLE : 0, 0x00020000);
-    for (int t = 0; t < t0; ++t) {
+    for (int t = 0; t < t_many; ++t) {
         // (the compiler reads it with a vector load, since it cannot prove the array constant; left alone it would
         // wait for that load, and for every store in flight before it, right here at the top of the step: the
         // value is kept in a vector register and made uniform only where the step waits for its stores anyway)
@@ -767,6 +780,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
         REC_PROF_STEP();
     }
     }
+    if (t_many < t0 && !many_fwd<MODE, MT, PIPE>((few_args_t<RecFwdArgs>)&a, ps, rank, t_many, t0, T, flags, pl, c_wait, smem)) return;
     if (t0 < T) {
         unsigned lds = (unsigned)(unsigned long long)(lds_ptr_t)smem;
         asm volatile("" : "+v"(lds));   // (known to be the start of the dynamic LDS, it would be read from a table wherever it is used)

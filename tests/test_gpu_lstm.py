@@ -625,3 +625,10 @@ def test_three_wide_layers(ver, n_envs, steps, hidden):
         res.append([u, v, dx] + grads)
     for a, b in zip(*res):
         assert l2_rel_err(a, b) <= 1.4e-2
+
+
+@pytest.mark.parametrize("pieces,steps,layers", [(136, 5, 1), (267, 4, 1), (53, 12, 2), (100, 2, 2)])
+@pytest.mark.parametrize("compute,hidden", [(0, 192), (0, 512), (1, 64), (1, 576)])
+def test_tiles_of_16_pieces(ver, pieces, steps, layers, compute, hidden):
+    """17, 33, 34 alive pieces in a group until its last timestep: two tiles and three, the last with one or two pieces."""
+    even(ver, pieces, steps, layers, compute, hidden)
