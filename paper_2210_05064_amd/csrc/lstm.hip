@@ -461,7 +461,8 @@ inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws)
     ws->x_op = c.compute && !c.x_bf16 ? cv.take<bf16_t>(Mz * c.input_dim) : nullptr;
     ws->db_part = cv.take<float>((size_t)(three ? 3 : 2) * REC_GROUPS * 4 * H);
     ws->ring = cv.take<char>(REC_GROUPS * few_ring_bytes(c.compute ? MODE_BF16 : MODE_F32, 4 * c.hidden));
-    ws->ring_many = cv.take<char>(REC_GROUPS * many_ring_bytes(c.compute ? MODE_BF16 : MODE_F32, c.hidden, many_rows(M)));
+    ws->ring_many = cv.take<char>(REC_GROUPS * std::max(many_ring_bytes(c.compute ? MODE_BF16 : MODE_F32, c.hidden, many_rows(M)),
+                                                        many_ring_bytes(c.compute ? MODE_BF16 : MODE_F32, 4 * c.hidden, many_rows_bwd(M))));
     ws->bytes = cv.used;
 }
 
@@ -804,6 +805,8 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         ra.gates = L.gates; ra.c = L.c; ra.c0 = c0 ? c0 + (size_t)l * seq_cap * H : nullptr;
         ra.dh_above = dh_above; ra.dz = dz_of(l); ra.whhT = L.whhT;
         ra.ring = ws.ring + groups_before * few_ring_bytes(MODE, 4 * H);
+        ra.many_rows = many_rows_bwd(M);
+        ra.ring_many = ws.ring_many + groups_before * many_ring_bytes(MODE, 4 * H, many_rows_bwd(M));
         ra.dh_state = ws.dh_state + (size_t)half(l) * M * H;
         ra.dc_state = ws.dc_state + (size_t)half(l) * M * H;
         ra.db_part = ws.db_part + (size_t)half(l) * REC_GROUPS * 4 * H;

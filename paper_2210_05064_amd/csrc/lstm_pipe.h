@@ -79,19 +79,20 @@ constexpr int PLAN_CT_FEW = 8, PLAN_CT_FEW_FAST = 4, PLAN_CT_MANY = 2;   // up t
 // units, 32 timesteps of 48 pieces 222 -> 251.)
 // us per timestep of launches over equally long pieces (two layers; time of a launch against its timesteps):
 //   pieces               1     2     4     5     8    16    17    32    64
-//   bf16 H=1024 fwd   1.23  1.29  1.47  1.93  1.97  2.3   3.5   4.4   8.2      bwd  1.64  1.73  2.18  2.47  2.45  3.2   6.9   9.0  17.1
-//   bf16 H=512  fwd   0.87  0.90  0.95  1.30  1.30  1.6   2.6   3.0   5.7      bwd  1.15  1.17  1.38  1.51  1.50  2.1   3.3   4.5   8.1
-//   fp32 H=512  fwd   1.15  1.43  2.08  3.00  3.0   3.0   5.9   6.2  12.7      bwd  1.28  1.83  2.77  3.56  3.5   4.5   8.4  10.2  19
-// (forward with 16 pieces and more: one layer, since with as many in all three groups the workers set the pace, 1.7 us per 16 rows at
-// H = 1024: with 1.5 us per tile instead of 2.4 the cuts of 32768 rows in 400 pieces cost 5 %).  The constants are fitted by hand to it (without the step from four to five pieces, two short groups of fp32 got five and more
-// pieces each and ended 50 us after the long one: 2 x 512 on 1024 rows in 8).
+//   bf16 H=1024 fwd   1.23  1.29  1.47  1.93  1.97  2.3   3.5   4.4   8.2      bwd  1.64  1.73  2.18  2.47  2.45  3.2   5.1   6.1  12.2
+//   bf16 H=512  fwd   0.87  0.90  0.95  1.30  1.30  1.6   2.6   3.0   5.7      bwd  1.15  1.17  1.38  1.51  1.50  2.1   3.3   3.7   7.3
+//   fp32 H=512  fwd   1.15  1.43  2.08  3.00  3.0   3.0   5.9   6.2  12.7      bwd  1.28  1.83  2.77  3.56  3.5   4.5   7.3   7.9  15.8
+// (from 16 pieces on: one layer, since with as many in all three groups the workers set the pace, 1.7 us per 16 rows at H = 1024).  The constants
+// are fitted by hand to it (without the step from four to five pieces, two short groups of fp32 got five and more pieces each and ended 50 us
+// after the long one: 2 x 512 on 1024 rows in 8; with 2.4 and 3.8 us per tile, what the wide layers took before, 8192 rows in about 100 pieces of 2 x
+// 1024 units took 2.55 ms forward and backward, now 2.38).
 inline PlanCost plan_cost(int mode, bool wide, bool fwd, int G, int workers) {
     const int teams = workers / G;
     if (mode == MODE_F32)
         return fwd ? PlanCost{0.85f, 0.25f, 0.7f, 0.06f, 2.2f, teams < 3 ? 256 : 0, 48, PLAN_CT_FEW} : PlanCost{0.85f, 0.42f, 0.45f, 0.06f, 3.f, 0, 0, PLAN_CT_FEW};
-    if (wide) return fwd ? PlanCost{1.13f, 0.03f, 0.45f, 0.042f, 2.4f, 0, 0, PLAN_CT_FEW_FAST} : PlanCost{1.45f, 0.08f, 0.2f, 0.08f, 3.8f, 0, 0, PLAN_CT_FEW_FAST};
+    if (wide) return fwd ? PlanCost{1.13f, 0.03f, 0.45f, 0.042f, 1.4f, 0, 0, PLAN_CT_FEW_FAST} : PlanCost{1.45f, 0.08f, 0.2f, 0.08f, 1.8f, 0, 0, PLAN_CT_FEW_FAST};
     const int few = teams < 3 ? PLAN_CT_FEW : PLAN_CT_FEW_FAST;
-    return fwd ? PlanCost{0.84f, 0.f, 0.25f, 0.03f, 1.1f, G == REC_MAX_GROUP ? 192 : 0, 90, few} : PlanCost{1.09f, 0.01f, 0.05f, 0.05f, 1.2f, 0, 0, few};
+    return fwd ? PlanCost{0.84f, 0.f, 0.25f, 0.03f, 1.1f, G == REC_MAX_GROUP ? 192 : 0, 90, few} : PlanCost{1.09f, 0.01f, 0.05f, 0.05f, 1.f, 0, 0, few};
 }
 
 struct PipeWork {

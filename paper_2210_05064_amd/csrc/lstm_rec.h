@@ -34,7 +34,8 @@
 //  * 4H (forward) or H (backward) sits on the MFMA M dimension and the alive
 //    pieces on N, so a ragged tail of one or two pieces wastes only N padding;
 //  * timesteps with few alive pieces, which are most of the timesteps that bound a launch, run in another form with
-//    another exchange (lstm_few.h); what follows here is the form for many pieces;
+//    another exchange (lstm_few.h), and most of the others in a third (lstm_many.h); what follows here is the form for
+//    more pieces than that has room for, and for the widths and short launches where it is the faster one;
 //  * every wait is bounded and sticky: on time-out the error word is set, every
 //    workgroup that sees it leaves the kernel, so the grid always drains.
 #pragma once
@@ -501,6 +502,8 @@ struct RecBwdArgs {
     float* dh_state;        // [n_cap, H] recurrent gradient carried to the previous timestep
     float* dc_state;        // [n_cap, H]
     void* ring;             // exchange ring of the layer's groups (lstm_few.h)
+    void* ring_many;        // the same for more than 16 pieces, many_rows rows per slot (lstm_many.h)
+    int many_rows;
     float* db_part;         // [groups, 4H] (out): every group's sum of dz over its rows, interleaved columns
     int H, seq_cap;
     int G;                  // participating workgroups; each owns 16*MT hidden units
@@ -578,15 +581,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
     few_clear_ring<MODE>(static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, H), H, j0, UH);
     // From timestep t_many on at most MANY_MAX are: lstm_many.h, which has both sides of the line.
     const int t_many = !many_pays<MODE>(H) ? t0 : n_seq > MANY_MAX ? __builtin_amdgcn_readfirstlane(grp_steps(a.batch_sizes, T, MANY_MAX * X + x)) : 0;
-    if (t_many < t0) {   // empties this workgroup's words of that form's ring
-        constexpr int words = UH * (int)sizeof(E) / 4;
-        const int rows = a.many_rows, used = min(n_seq, rows);
-        unsigned* ring = reinterpret_cast<unsigned*>(static_cast<unsigned char*>(a.ring_many) + ps.id * many_ring_bytes(MODE, H, rows));
-        for (int i = tid; i < FEW_RING * used * words; i += REC_THREADS) {
-            const int r = i / words, k = r / used;
-            ring[((size_t)k * rows + r % used) * (H * (int)sizeof(E) / 4) + j0 * (int)sizeof(E) / 4 + i % words] = FEW_EMPTY;
-        }
-    }
+    if (t_many < t0) many_clear_ring<MODE>(a.ring_many, ps.id, H, a.many_rows, min(n_seq, a.many_rows), j0, UH);
     rec_publish(flags, rank, 1);
     REC_PROF_DECL
     REC_PROF_START();
@@ -823,11 +818,15 @@ __device__ __forceinline__ BwdSaved load_saved(const RecBwdArgs& a, int t, int b
     return s;
 }
 
-// MT 16-unit tiles per workgroup, KS waves per tile split the contraction over the 4H gate rows.
+struct BwdKept {
+    int *flags, *progress, *done;
+    int x, cap, id, rank, t_few, T, need, ct, many;
+};
+// The timesteps below t_few and the end of the layer.  dh_few, dcreg, db: from the timesteps behind.
 template <int MODE, int MT, int KS, int NI, int PIPE>
-__device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& by_ref, int rank, const PieceSet ps, int T, int* flags,
-                                             const PipeLink& pl, unsigned char* smem) {
-    const RecBwdArgs& a = by_ref;   // (the two forms load what they use again, see args_again)
+__device__ __forceinline__ void rec_bwd_rest(const RecBwdArgs& by_ref, int rank, const PieceSet ps, int T, int* flags, const PipeLink& pl, unsigned char* smem,
+                                             int t_few, bool many, int c_wait, float dh_few, float dcreg, float (&db)[4]) {
+    const RecBwdArgs& a = args_again(by_ref);
     const int x = ps.x, X = ps.X;
     static_assert(MT * KS == REC_WAVES, "one wave per (tile, k-split)");
     static_assert(MT * REC_NTC <= REC_WAVES, "one wave per tile sum");
@@ -841,48 +840,25 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& by_ref, int rank,
     E* sB = reinterpret_cast<E*>(smem);                                                        // staged dz rows
     f32x4_t* sRed = reinterpret_cast<f32x4_t*>(smem + (size_t)ntc * 16 * stride * sizeof(E));  // [KS][MT][ntc][64]
     float* sDh = reinterpret_cast<float*>(sRed + (size_t)KS * MT * ntc * 64);   // [ntc*16][UH] dh carried to the previous timestep
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // (what the front part has derived from it is not kept for here)
+    const int lane = tid & 63, wave = tid >> 6;
     const int mt = wave / KS, ks = wave % KS;
     const int lr = lane & 15, lk = lane >> 4;
     const int j0 = rank * UH;
     const int k_lo = ks * (K / KS);
     const int ni = (K / KS) / KBLK;
 
-    float dcreg = 0.f;   // cell-state gradient of this thread's first (piece, unit), carried from timestep to timestep
-    // Bias gradient: a thread always works on the same unit (the stride of its items is a multiple of UH), so it
-    // adds up that unit's four gate gradients over all its items in registers; summed over threads after the loop.
-    static_assert(REC_THREADS % UH == 0, "a thread keeps its unit");
-    float db[4] = {0.f, 0.f, 0.f, 0.f};
-    int c_wait = T > 0 ? (T - 1) / pl.ct : 0;   // consumer: the chunk of the timestep it runs next
-    if ((PIPE & PIPE_CONSUMER) && T > 0 && !pipe_wait_chunk(pl, c_wait, a.err, REC_PROF_CHUNK_ACC(a, rank, ps))) return;
-    // Timesteps >= t_few have at most FEW_MAX alive pieces and run in the form of lstm_few.h (flag value 1: the
-    // workgroup has emptied its words of the exchange ring).
-    const int n_seq = grp_count(a.info[0], ps);
-    const int t_few = n_seq > FEW_MAX ? __builtin_amdgcn_readfirstlane(grp_steps(a.batch_sizes, T, FEW_MAX * X + x)) : 0;
-    unsigned char* ring = static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, K);
-    float dh_few = 0.f;
-    if (t_few < T) {
-        few_clear_ring<MODE>(ring, K, j0 * 4, UH * 4);
-        rec_publish(flags, rank, 1);
-        if (!rec_wait(flags, G, 1, a.err)) return;
-        unsigned lds = (unsigned)(unsigned long long)(lds_ptr_t)smem;
-        asm volatile("" : "+v"(lds));   // (known to be the start of the dynamic LDS, it would be read from a table wherever it is used)
-        const FewBwdOut out = few_bwd<MODE, MT, PIPE>((few_args_t<RecBwdArgs>)&by_ref, ps.x, ps.cap, ps.id, rank, t_few, T, pl.progress, pl.done, pl.need, pl.ct, c_wait, lds);
-        if (!__builtin_amdgcn_readfirstlane((int)out.ok)) return;
-        c_wait = __builtin_amdgcn_readfirstlane(out.c_wait);
-        dh_few = out.dh;
-        dcreg = out.dc;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) db[i] = out.db[i];
-        if (t_few == 0 && (PIPE & PIPE_PRODUCER)) {   // the last rows are complete once every flag says so
-            rec_publish(flags, rank, T + 1);
-            if (rank == 0) {
-                if (!rec_wait(flags, G, T + 1, a.err)) return;
-                if (tid == 0) st_agent(pl.progress, T);
-            }
+    if (t_few == 0 && T > 0 && (PIPE & PIPE_PRODUCER)) {   // the last rows are complete once every flag says so
+        rec_publish(flags, rank, T + 1);
+        if (rank == 0) {
+            if (!rec_wait(flags, G, T + 1, a.err)) return;
+            if (tid == 0) st_agent(pl.progress, T);
         }
     }
-    if (t_few > 0) {
+    if constexpr (MANY_BWD<MODE, MT, NI>)
+        if (many && !many_bwd<MODE, MT, PIPE>((few_args_t<RecBwdArgs>)&a, ps, rank, t_few, T, flags, pl, c_wait, smem, dh_few, dcreg, db)) return;
+    if (!many && t_few > 0) {
     const RecBwdArgs a = args_again(by_ref);
     E* dzw = static_cast<E*>(a.dz);
     // The arrays as buffers that never change during the loop (host code guarantees that each is shorter than
@@ -1057,6 +1033,66 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& by_ref, int rank,
             sum[0] += o[0]; sum[1] += o[1]; sum[2] += o[2]; sum[3] += o[3];
         }
         *reinterpret_cast<f32x4_t*>(a.db_part + (size_t)ps.id * K + (size_t)(j0 + tid) * 4) = sum;
+    }
+}
+
+// MT 16-unit tiles per workgroup, KS waves per tile split the contraction over the 4H gate rows.
+template <int MODE, int MT, int KS, int NI, int PIPE>
+__device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& by_ref, int rank, const PieceSet ps, int T, int* flags,
+                                             const PipeLink& pl, unsigned char* smem) {
+    const RecBwdArgs& a = by_ref;   // (the two forms load what they use again, see args_again)
+    const int x = ps.x, X = ps.X;
+    constexpr int UH = 16 * MT;
+    const int G = a.G, H = a.H, K = 4 * H, tid = threadIdx.x, j0 = rank * UH;
+
+    float dcreg = 0.f;   // cell-state gradient of this thread's first (piece, unit), carried from timestep to timestep
+    // Bias gradient: a thread always works on the same unit (the stride of its items is a multiple of UH), so it
+    // adds up that unit's four gate gradients over all its items in registers; summed over threads after the loop.
+    static_assert(REC_THREADS % UH == 0, "a thread keeps its unit");
+    float db[4] = {0.f, 0.f, 0.f, 0.f};
+    int c_wait = T > 0 ? (T - 1) / pl.ct : 0;   // consumer: the chunk of the timestep it runs next
+    if ((PIPE & PIPE_CONSUMER) && T > 0 && !pipe_wait_chunk(pl, c_wait, a.err, REC_PROF_CHUNK_ACC(a, rank, ps))) return;
+    // Timesteps >= t_few have at most FEW_MAX alive pieces and run in the form of lstm_few.h (flag value 1: the
+    // workgroup has emptied its words of the exchange ring).
+    const int n_seq = grp_count(a.info[0], ps);
+    const int t_few = n_seq > FEW_MAX ? __builtin_amdgcn_readfirstlane(grp_steps(a.batch_sizes, T, FEW_MAX * X + x)) : 0;
+    unsigned char* ring = static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, K);
+    float dh_few = 0.f;
+    bool many = false;   // lstm_many.h, which has both sides of the lines
+    if constexpr (MANY_BWD<MODE, MT, NI>) {
+        many = t_few >= MANY_STEPS_BWD && n_seq <= a.many_rows && many_pays_bwd<MODE, MT>(H, n_seq);
+        if (many) many_clear_ring<MODE>(a.ring_many, ps.id, K, a.many_rows, n_seq, j0 * 4, UH * 4);
+    }
+    if (t_few < T) few_clear_ring<MODE>(ring, K, j0 * 4, UH * 4);
+    // What the other forms need, put away: held in registers across the loop of few pieces, it pushes what that loop needs into spill lanes
+    // (31 v_readlane per timestep of a consumer at 512 units, 19 with it put away; update of 2 x 512 units 7.13 -> 7.03 ms).
+    __shared__ BwdKept s_kept;
+    if (MANY_BWD<MODE, MT, NI> && tid == 0) s_kept = BwdKept{flags, pl.progress, pl.done, ps.x, ps.cap, ps.id, rank, t_few, T, pl.need, pl.ct, many ? 1 : 0};
+    if (many || t_few < T) {
+        rec_publish(flags, rank, 1);
+        if (!rec_wait(flags, G, 1, a.err)) return;
+    } else if (MANY_BWD<MODE, MT, NI>) {
+        bar_lds();
+    }
+    if (t_few < T) {
+        unsigned lds = (unsigned)(unsigned long long)(lds_ptr_t)smem;
+        asm volatile("" : "+v"(lds));   // (known to be the start of the dynamic LDS, it would be read from a table wherever it is used)
+        const FewBwdOut out = few_bwd<MODE, MT, PIPE>((few_args_t<RecBwdArgs>)&by_ref, ps.x, ps.cap, ps.id, rank, t_few, T, pl.progress, pl.done, pl.need, pl.ct, c_wait, lds);
+        if (!__builtin_amdgcn_readfirstlane((int)out.ok)) return;
+        c_wait = __builtin_amdgcn_readfirstlane(out.c_wait);
+        dh_few = out.dh;
+        dcreg = out.dc;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) db[i] = out.db[i];
+    }
+    if constexpr (MANY_BWD<MODE, MT, NI>) {
+        const BwdKept k = s_kept;
+        const PieceSet ps_kept = {few_scalar(k.x), ps.X, few_scalar(k.cap), few_scalar(k.id)};
+        const PipeLink pl_kept = {few_scalar(k.progress), few_scalar(k.done), few_scalar(k.need), few_scalar(k.ct), 0};
+        rec_bwd_rest<MODE, MT, KS, NI, PIPE>(by_ref, few_scalar(k.rank), ps_kept, few_scalar(k.T), few_scalar(k.flags), pl_kept, smem, few_scalar(k.t_few),
+                                             few_scalar(k.many) != 0, c_wait, dh_few, dcreg, db);
+    } else {
+        rec_bwd_rest<MODE, MT, KS, NI, PIPE>(by_ref, rank, ps, T, flags, pl, smem, t_few, false, c_wait, dh_few, dcreg, db);
     }
 }
 

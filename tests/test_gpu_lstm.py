@@ -632,3 +632,24 @@ def test_three_wide_layers(ver, n_envs, steps, hidden):
 def test_tiles_of_16_pieces(ver, pieces, steps, layers, compute, hidden):
     """17, 33, 34 alive pieces in a group until its last timestep: two tiles and three, the last with one or two pieces."""
     even(ver, pieces, steps, layers, compute, hidden)
+
+
+@pytest.mark.parametrize("pieces,steps,layers", [(136, 24, 1), (267, 25, 1), (76, 26, 2), (150, 24, 2)])
+@pytest.mark.parametrize("compute,hidden", [(0, 320), (0, 512), (1, 64), (1, 192), (1, 512), (1, 576)])
+def test_tiles_of_16_pieces_backward(ver, pieces, steps, layers, compute, hidden):
+    """The same from the 24 timesteps on that the backward loop asks for: 17, 25, 33, 34, 50 alive pieces in a group."""
+    even(ver, pieces, steps, layers, compute, hidden)
+
+
+def test_tiles_of_16_pieces_of_256(ver):
+    """257 pieces in four of the groups and 256 in the others, the most that the backward loop takes 16 at a time."""
+    even(ver, 2052, 24, 1, 1, 192)
+
+
+@pytest.mark.parametrize("layers", [1, 2])
+@pytest.mark.parametrize("compute,hidden", [(0, 512), (1, 64), (1, 320), (1, 576)])
+def test_tiles_of_16_pieces_ragged(ver, layers, compute, hidden):
+    """Groups with more than 16 pieces in their first timesteps and few in their last, pieces that end in between."""
+    n_envs = 260 // (layers * layers)
+    w = wl.Workload("tiles", n_envs, 40 * n_envs, 0, 0, 0.9, 60, layers, hidden, 1, 3, 0.02, 1, 1, bool(compute))
+    case(ver, w, seed=120 + layers, compute=compute, x_bf16=bool(compute))
