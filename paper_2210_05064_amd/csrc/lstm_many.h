@@ -4,9 +4,8 @@
 // of the timestep before, which is at least one unit back, so that no unit has to wait for the exchange: a unit's rows, its
 // input projections and its cell states are requested while the unit before is worked on.  The rows go from the ring straight into
 // LDS (forward two areas per wave in turn); an operand that is still empty when it is read (lstm_few.h) is requested again.
-// Memory operations of a wave complete in order, and a unit issues the same number of them whatever its pieces (those without
-// one go beyond the buffers), so that the wait for a unit's rows leaves the stores of the unit before and the next unit's loads in
-// flight.
+// Memory operations of a wave complete in order, and a unit issues the same number of stores behind the next unit's loads whatever its
+// pieces (those without one go beyond the buffers), so that the wait for a unit's loads leaves the stores of the unit before in flight.
 // What is published in a unit is published after the stores of the unit before the last one have completed.  So whoever has the rows of a timestep
 // knows that the rows of the timestep before are complete in memory, and that the words that were emptied two units earlier are.
 // Bound by LDS (192 KB per unit at H = 1024, 0.64 us), the MFMAs (0.43 us) and the gates, one after the other in a wave.
@@ -436,6 +435,7 @@ __device__ __forceinline__ bool many_bwd(few_args_t<RecBwdArgs> args, const Piec
     if (t > 0) {
         if (polls) request(t, 0, bs);
         fetch(s0, t - 1, 0, bs_1, bs, base_1, base_1 - all_2);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (no stores behind these: the count below holds from the second unit on)
     }
     // false: that was the last unit, or a wait was abandoned
     auto unit = [&](ManySaved& s, ManySaved& s_next) __attribute__((always_inline)) -> bool {
