@@ -569,6 +569,17 @@ template <typename T> __device__ __forceinline__ T few_scalar(T v) {
 // A pointer that the compiler knows to be global (of one read from memory it does not, and a generic access also counts
 // as one to LDS).
 template <typename T> __device__ __forceinline__ void few_global(T*& p) { p = (T*)(__attribute__((address_space(1))) T*)p; }
+// Kept in vector registers: what a timestep rarely asks for, or asks for with a lane's address.
+template <typename T> __device__ __forceinline__ void few_away(T& v) {
+    if constexpr (std::is_pointer<T>::value) {
+        unsigned long long b = reinterpret_cast<unsigned long long>(v);
+        asm volatile("" : "+v"(b));
+        typedef typename std::remove_pointer<T>::type V;
+        v = (T)(__attribute__((address_space(1))) V*)b;
+    } else {
+        asm volatile("" : "+v"(v));
+    }
+}
 template <typename A> using few_args_t = const A __attribute__((address_space(4)))*;
 struct FewLink { PieceSet ps; PipeLink pl; };
 template <int PIPE>
@@ -580,8 +591,8 @@ __device__ __forceinline__ FewLink few_link(int x, int cap, int id, int* progres
     l.ps.id = few_scalar(id);
     l.pl.progress = few_scalar(progress);
     l.pl.done = few_scalar(done);
-    few_global(l.pl.progress);
-    few_global(l.pl.done);
+    few_away(l.pl.progress);
+    few_away(l.pl.done);
     l.pl.need = few_scalar(need);
     l.pl.ct = few_scalar(ct);
     l.pl.T = 0;
@@ -601,7 +612,7 @@ __device__ __forceinline__ bool few_fwd(few_args_t<RecFwdArgs> args, int x_, int
     few_global(flags);
     RecFwdArgs a = *(const RecFwdArgs*)few_scalar(args);
     few_global(a.batch_sizes); few_global(a.t_off); few_global(a.gates); few_global(a.c); few_global(a.hout);
-    few_global(a.c0); few_global(a.err);
+    few_away(a.c0); few_away(a.err); few_away(a.batch_sizes); few_away(a.seq_cap);
     a.hprev = (void*)(__attribute__((address_space(1))) void*)a.hprev;
     a.whh = (const void*)(__attribute__((address_space(1))) const void*)a.whh;
     a.ring = (void*)(__attribute__((address_space(1))) void*)a.ring;
@@ -854,7 +865,7 @@ __device__ __forceinline__ FewBwdOut few_bwd(few_args_t<RecBwdArgs> args, int x_
     const int rank = few_scalar(rank_), t_stop = few_scalar(t_stop_), T = few_scalar(T_), c_wait = few_scalar(c_wait_);
     RecBwdArgs a = *(const RecBwdArgs*)few_scalar(args);
     few_global(a.batch_sizes); few_global(a.t_off); few_global(a.gates); few_global(a.c); few_global(a.dh_above);
-    few_global(a.c0); few_global(a.err);
+    few_away(a.c0); few_away(a.err); few_away(a.batch_sizes); few_away(a.seq_cap);
     a.dz = (void*)(__attribute__((address_space(1))) void*)a.dz;
     a.whhT = (const void*)(__attribute__((address_space(1))) const void*)a.whhT;
     a.ring = (void*)(__attribute__((address_space(1))) void*)a.ring;

@@ -72,7 +72,7 @@ __device__ __forceinline__ bool many_fwd(few_args_t<RecFwdArgs> args, const Piec
     constexpr int STORES = 6;   // per unit and wave, behind the loads of the next unit
     __shared__ int s_fail_many;
     RecFwdArgs a = *(const RecFwdArgs*)few_scalar(args);
-    few_global(a.batch_sizes); few_global(a.t_off); few_global(a.gates); few_global(a.c); few_global(a.hout); few_global(a.c0); few_global(a.err);
+    few_global(a.batch_sizes); few_global(a.t_off); few_global(a.gates); few_global(a.c); few_global(a.hout); few_global(a.c0); few_away(a.err);
     a.whh = (const void*)(__attribute__((address_space(1))) const void*)a.whh;
     const int H = a.H, X = ps.X, x = ps.x;
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
@@ -306,7 +306,7 @@ __device__ __forceinline__ bool many_bwd(few_args_t<RecBwdArgs> args, const Piec
     constexpr int STORES = 4;   // per unit and wave, behind the loads of the next unit
     __shared__ int s_fail_many;
     RecBwdArgs a = *(const RecBwdArgs*)few_scalar(args);
-    few_global(a.batch_sizes); few_global(a.t_off); few_global(a.gates); few_global(a.c); few_global(a.dh_above); few_global(a.c0); few_global(a.err);
+    few_global(a.batch_sizes); few_global(a.t_off); few_global(a.gates); few_global(a.c); few_global(a.dh_above); few_global(a.c0); few_away(a.err);
     few_global(a.dc_state);
     a.whhT = (const void*)(__attribute__((address_space(1))) const void*)a.whhT;
     const int H = a.H, K = 4 * H, X = ps.X, x = ps.x;

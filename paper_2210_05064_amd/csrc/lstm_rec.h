@@ -859,7 +859,8 @@ __device__ __forceinline__ void rec_bwd_rest(const RecBwdArgs& by_ref, int rank,
     if constexpr (MANY_BWD<MODE, MT, NI>)
         if (many && !many_bwd<MODE, MT, PIPE>((few_args_t<RecBwdArgs>)&a, ps, rank, t_few, T, flags, pl, c_wait, smem, dh_few, dcreg, db)) return;
     if (!many && t_few > 0) {
-    const RecBwdArgs a = args_again(by_ref);
+    RecBwdArgs a = args_again(by_ref);
+    few_away(a.err); few_away(a.c0); few_away(a.batch_sizes); few_away(a.seq_cap); few_away(a.dh_state); few_away(a.dc_state);
     E* dzw = static_cast<E*>(a.dz);
     // The arrays as buffers that never change during the loop (host code guarantees that each is shorter than
     // 2^31 bytes); where a timestep's rows begin is the scalar offset of an access, and this thread's first
@@ -887,8 +888,8 @@ __device__ __forceinline__ void rec_bwd_rest(const RecBwdArgs& by_ref, int rank,
     // batch sizes of timesteps t+1, t, t-1, t-2 (t-3 is fetched a step ahead, see the forward kernel); row offsets
     // follow by subtraction
     const int t1 = t_few - 1;
-    int bs_up = t1 + 1 < T ? a.batch_sizes[t1 + 1] : 0, bs_t = a.batch_sizes[t1], bs_m1 = t1 > 0 ? a.batch_sizes[t1 - 1] : 0,
-        bs_m2 = t1 > 1 ? a.batch_sizes[t1 - 2] : 0;
+    int bs_up = few_scalar(t1 + 1 < T ? a.batch_sizes[t1 + 1] : 0), bs_t = few_scalar(a.batch_sizes[t1]), bs_m1 = few_scalar(t1 > 0 ? a.batch_sizes[t1 - 1] : 0),
+        bs_m2 = few_scalar(t1 > 1 ? a.batch_sizes[t1 - 2] : 0);
     int base = a.t_off[t1];
     {
         const int bs_l = grp_count(bs_t, ps);
