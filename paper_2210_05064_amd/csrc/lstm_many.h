@@ -41,7 +41,9 @@ inline __host__ __device__ size_t many_lds_bytes(int cols, int nb) { return (siz
 constexpr int MANY_MAX_BWD = 256;
 inline __host__ __device__ int many_rows_bwd(int M) { return M < MANY_MAX_BWD ? (M + 15) / 16 * 16 : MANY_MAX_BWD; }
 constexpr int MANY_STEPS_BWD = 24;
-template <int MODE, int MT, int NI> constexpr bool MANY_BWD = MODE == MODE_F32 || MT == 2 || NI == 0;   // kernels that have the form
+// Kernels that have the form: MT tiles per workgroup, loops for NI operand blocks (0: the general ones).
+constexpr bool many_bwd_form(int mode, int mt, int ni) { return mt == 2 || (ni != 4 && ni != 8 && (ni != 16 || mode == MODE_F32)); }
+template <int MODE, int MT, int NI> constexpr bool MANY_BWD = many_bwd_form(MODE, MT, NI);
 template <int MODE, int MT> __host__ __device__ constexpr bool many_pays_bwd(int H, int pieces) {
     if (MODE == MODE_F32) return H > 256;
     return MT == 2 || H > 128 || (pieces > 24 && pieces <= 48);

@@ -114,3 +114,10 @@ def test_no_load_is_left_in_flight(tmp_path):
         body = re.search(rf"^_ZN3ver\d+{name}\w*:[^\n]*\n(.*?)^\.Lfunc_end", asm, re.S | re.M).group(1)
         short, seen = short_waits(body, stores[kernel.split("_")[2]])
         assert seen and not short, (kernel, seen, short)
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_only_kernels_that_run_the_form_have_it(tmp_path):
+    """fp32 backward up to 256 units never runs it (many_pays_bwd): the kernels of 128 and 256 units, which have loops of their own, leave it out."""
+    for kernel, asm in assembly([f"lstm_rec_bwd_kernel<MODE_F32, 1, 8, {ni}>(RecBwdArgs)" for ni in (4, 8)], tmp_path).items():
+        assert short_waits(re.search(r"^_ZN3ver\d+lstm_rec_bwd\w*:[^\n]*\n(.*?)^\.Lfunc_end", asm, re.S | re.M).group(1), 4) == ([], 0), kernel
