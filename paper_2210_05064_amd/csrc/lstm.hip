@@ -417,6 +417,22 @@ inline size_t gemm_part_max(const ver_lstm_cfg& c, int M) {
     return m;
 }
 
+// How the backward time loops split a width over a workgroup's waves: one wave per (16 units, share of the 4H contraction): 2 tiles x 4
+// when H / 16 > 32 workgroups, else 1 x 8.
+struct BwdSplit {
+    bool wide;
+    int mt, ks, ni;   // tiles, shares, operand blocks of a share
+};
+inline BwdSplit bwd_split(int mode, int H) {
+    const bool wide = H / 16 > REC_MAX_GROUP;
+    const int ks = wide ? 4 : 8, kblk = mode == MODE_BF16 ? RecGeom<MODE_BF16>::KBLK : RecGeom<MODE_F32>::KBLK;
+    return BwdSplit{wide, wide ? 2 : 1, ks, 4 * H / ks / kblk};
+}
+inline int many_rows_bwd_of(int mode, int H, int M) {
+    const BwdSplit b = bwd_split(mode, H);
+    return many_rows_bwd(mode, H, b.mt, b.ni, M);
+}
+
 inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws) {
     const size_t es = c.compute ? 2 : 4;
     const size_t H = c.hidden, Mz = (size_t)M;
@@ -460,9 +476,10 @@ inline void lstm_ws_layout(const ver_lstm_cfg& c, int M, void* base, LstmWs* ws)
     ws->gemm_part = cv.take<float>(gemm_part_max(c, M));
     ws->x_op = c.compute && !c.x_bf16 ? cv.take<bf16_t>(Mz * c.input_dim) : nullptr;
     ws->db_part = cv.take<float>((size_t)(three ? 3 : 2) * REC_GROUPS * 4 * H);
-    ws->ring = cv.take<char>(REC_GROUPS * few_ring_bytes(c.compute ? MODE_BF16 : MODE_F32, 4 * c.hidden));
-    ws->ring_many = cv.take<char>(REC_GROUPS * std::max(many_ring_bytes(c.compute ? MODE_BF16 : MODE_F32, c.hidden, many_rows(M)),
-                                                        many_ring_bytes(c.compute ? MODE_BF16 : MODE_F32, 4 * c.hidden, many_rows_bwd(M))));
+    const int mode = c.compute ? MODE_BF16 : MODE_F32;
+    ws->ring = cv.take<char>(REC_GROUPS * few_ring_bytes(mode, 4 * c.hidden));
+    ws->ring_many = cv.take<char>(REC_GROUPS * std::max(many_ring_bytes(mode, c.hidden, many_rows(mode, c.hidden, M)),
+                                                        many_ring_bytes(mode, 4 * c.hidden, many_rows_bwd_of(mode, c.hidden, M))));
     ws->bytes = cv.used;
 }
 
@@ -681,8 +698,8 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         ra.info = info; ra.batch_sizes = batch_sizes; ra.t_off = t_off;
         ra.gates = L.gates; ra.c = L.c; ra.hout = L.hout; ra.hprev = L.hprev; ra.hcopy = L.hcopy; ra.whh = L.whh;
         ra.ring = ws.ring + groups_before * few_ring_bytes(MODE, H);
-        ra.many_rows = many_rows(M);
-        ra.ring_many = ws.ring_many + groups_before * many_ring_bytes(MODE, H, many_rows(M));
+        ra.many_rows = many_rows(MODE, H, M);
+        ra.ring_many = ws.ring_many + groups_before * many_ring_bytes(MODE, H, ra.many_rows);
         ra.h0 = h0 ? h0 + (size_t)l * seq_cap * H : nullptr;
         ra.c0 = c0 ? c0 + (size_t)l * seq_cap * H : nullptr;
         ra.H = H; ra.seq_cap = seq_cap; ra.M = M; ra.flags = ws.flags; ra.ticket = ws.flags + 8 * REC_MAX_GROUP;
@@ -781,9 +798,9 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     }
     HeadsFinalArgs hf{ws.part, ws.part_b, gw[4 * nl], gw[4 * nl + 2], gw[4 * nl + 1], gw[4 * nl + 3], (M + HW_ROWS - 1) / HW_ROWS, H, A};
 
-    // one wave per (16 units, share of the 4H contraction): 2 tiles x 4 when H/16 > 32 workgroups, else 1 x 8
-    const bool wide = H / 16 > REC_MAX_GROUP;
-    const int mt = wide ? 2 : 1, ks = wide ? 4 : 8;
+    const BwdSplit split = bwd_split(MODE, H);
+    const bool wide = split.wide;
+    const int mt = split.mt, ks = split.ks, ni = split.ni;
     const size_t tile = (size_t)16 * (4 * H + RecGeom<MODE>::PAD) * sizeof(E);
     const size_t red_per_tile = (size_t)ks * mt * 64 * 16 + (size_t)16 * 16 * mt * sizeof(float);   // partial sums + carried dh
     const int ntc = rec_tiles(tile, red_per_tile);
@@ -792,7 +809,6 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
     if (few_lds_bytes(16 * mt, few_nb) > lds) lds = few_lds_bytes(16 * mt, few_nb);
     const size_t work_lds = work_lds_bytes(16 * mt, few_nb, work_bufs<MODE, false>());
     if (pairs && work_lds > lds) lds = work_lds;
-    const int ni = (4 * H / ks) / RecGeom<MODE>::KBLK;
 
     // dz_of(l): layer l's gate gradients.  The two layers of a pair (l & 1: the upper one, which is the producer here) carry
     // their state in separate halves of the scratch, three layers in thirds; a top layer without a partner has an even number.
@@ -805,8 +821,8 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         ra.gates = L.gates; ra.c = L.c; ra.c0 = c0 ? c0 + (size_t)l * seq_cap * H : nullptr;
         ra.dh_above = dh_above; ra.dz = dz_of(l); ra.whhT = L.whhT;
         ra.ring = ws.ring + groups_before * few_ring_bytes(MODE, 4 * H);
-        ra.many_rows = many_rows_bwd(M);
-        ra.ring_many = ws.ring_many + groups_before * many_ring_bytes(MODE, 4 * H, many_rows_bwd(M));
+        ra.many_rows = many_rows_bwd_of(MODE, H, M);
+        ra.ring_many = ws.ring_many + groups_before * many_ring_bytes(MODE, 4 * H, ra.many_rows);
         ra.dh_state = ws.dh_state + (size_t)half(l) * M * H;
         ra.dc_state = ws.dc_state + (size_t)half(l) * M * H;
         ra.db_part = ws.db_part + (size_t)half(l) * REC_GROUPS * 4 * H;

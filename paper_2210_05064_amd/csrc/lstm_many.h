@@ -22,7 +22,11 @@ constexpr int MANY_MAX = 512;   // rows of a slot; more alive pieces than that: 
 // Not fp32 up to 128 units, where one or two waves hold all of the contraction, 2 us of MFMAs per unit (the flag form shares them): 64 units 3.5 /
 // 3.6 / 6.8 -> 3.9 / 3.9 / 7.6, 128 3.8 / 3.9 / 7.6 -> 3.9 / 3.9 / 7.8.
 template <int MODE> __host__ __device__ constexpr bool many_pays(int H) { return MODE == MODE_BF16 || H > 128; }
-inline __host__ __device__ int many_rows(int M) { return M < MANY_MAX ? (M + 15) / 16 * 16 : MANY_MAX; }
+// Rows of a slot for minibatches of M rows; 0 where no launch of this width runs the form.
+inline int many_rows(int mode, int H, int M) {
+    if (!(mode == MODE_BF16 ? many_pays<MODE_BF16>(H) : many_pays<MODE_F32>(H)) || M <= FEW_MAX) return 0;
+    return M < MANY_MAX ? (M + 15) / 16 * 16 : MANY_MAX;
+}
 inline __host__ __device__ size_t many_ring_bytes(int mode, int row_elems, int rows) { return (size_t)FEW_RING * rows * row_elems * (mode == MODE_BF16 ? 2 : 4); }
 inline __host__ __device__ size_t many_lds_bytes(int cols, int nb) { return (size_t)few_part_floats(cols) * sizeof(float) + (size_t)2 * REC_WAVES * few_stage_bytes(nb); }
 
@@ -39,7 +43,6 @@ inline __host__ __device__ size_t many_lds_bytes(int cols, int nb) { return (siz
 // units from 25 to 48 pieces.  Not bf16 at 128, 256 and 512 units, although long launches of 25 pieces and more gain there: with the form in the kernel
 // the compiler spills more scalars in the loops of few pieces, which an update of 2 x 512 units consists of (6.89 -> 7.03 ms).
 constexpr int MANY_MAX_BWD = 256;
-inline __host__ __device__ int many_rows_bwd(int M) { return M < MANY_MAX_BWD ? (M + 15) / 16 * 16 : MANY_MAX_BWD; }
 constexpr int MANY_STEPS_BWD = 24;
 // Kernels that have the form: MT tiles per workgroup, loops for NI operand blocks (0: the general ones).
 constexpr bool many_bwd_form(int mode, int mt, int ni) { return mt == 2 || (ni != 4 && ni != 8 && (ni != 16 || mode == MODE_F32)); }
@@ -47,6 +50,13 @@ template <int MODE, int MT, int NI> constexpr bool MANY_BWD = many_bwd_form(MODE
 template <int MODE, int MT> __host__ __device__ constexpr bool many_pays_bwd(int H, int pieces) {
     if (MODE == MODE_F32) return H > 256;
     return MT == 2 || H > 128 || (pieces > 24 && pieces <= 48);
+}
+// Rows of a slot of the backward ring for minibatches of M rows; ni: operand blocks per wave (run_bwd).  0 where no launch runs the form.
+inline int many_rows_bwd(int mode, int H, int mt, int ni, int M) {
+    const int most = mode == MODE_F32 || mt == 2 || H > 128 ? MANY_MAX_BWD : 48;
+    const bool pays = mode == MODE_F32 ? many_pays_bwd<MODE_F32, 1>(H, most) : mt == 2 ? many_pays_bwd<MODE_BF16, 2>(H, most) : many_pays_bwd<MODE_BF16, 1>(H, most);
+    if (!many_bwd_form(mode, mt, ni) || !pays || M < (FEW_MAX + 1) * MANY_STEPS_BWD) return 0;
+    return M < most ? (M + 15) / 16 * 16 : most;
 }
 
 // Empties this workgroup's words (cols elements from column j0) of the first `used` rows of every slot of group id's ring.
