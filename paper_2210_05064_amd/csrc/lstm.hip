@@ -329,10 +329,10 @@ struct BiasFinalArgs {
     const float* part; size_t part_stride;
     float* out[3]; float* out2[3];
     int n_rb, H, sets;
-    const int* alone;   // points to anything but a zero: the time loops had all groups, n_rb is REC_GROUPS (NULL: as given)
+    const int* groups;   // groups of the time loops: of the first two sets, of the third (NULL: n_rb)
 };
 __device__ __forceinline__ void bias_final_block(const BiasFinalArgs& q, int bx, int set) {
-    const int n_rb = q.alone && *q.alone != 0 ? REC_GROUPS : q.n_rb;
+    const int n_rb = q.groups ? q.groups[set / 2] : q.n_rb;
     const int c = bx * 256 + threadIdx.x, cols = 4 * q.H;
     if (c >= cols) return;
     const float* part = q.part + set * q.part_stride;
@@ -578,38 +578,67 @@ inline bool pairs_of_layers(const ver_lstm_cfg& c) { return c.n_layers >= 2 && !
 inline bool three_layers(const ver_lstm_cfg& c) { return c.n_layers == 3 && !c.layer_by_layer; }
 // From three layers on a shared launch is for minibatches of few alive pieces per timestep (rows / timesteps): many are bound by
 // throughput, of which two or three XCDs per layer have less than eight for one layer after the other (and finding the cuts for
-// thousands of pieces takes milliseconds).  Only the device knows the timesteps: both forms are launched, and what the plan has
-// not chosen does nothing (15 us in all for pairs, 25 for three layers); up to this many rows the shared form is launched alone.
-// Three layers, pieces x timesteps, us of a launch per layer / three in a launch / before (pairs without a choice): bf16, 320 units 50 x 7 206 /
-// 195 / 206, 100 x 7 224 / 278 / 253; fp32, 256 units 25 x 7 222 / 240 / 236, 100 x 7 271 / 411 / 317; 512 units 12 x 7 280 / 312 / 297, 50 x 15 582 / 738 / 671.
+// thousands of pieces takes milliseconds).  Only the device knows the timesteps: the forms are launched one behind the other, and what the
+// plan has not chosen does nothing (15 us in all for pairs); up to THREE_ROWS rows three layers are launched in the form of one launch alone, up
+// to PAIRS_ROWS rows without the form of a launch per layer.
 constexpr int PAIRS_ROWS = 768;
-inline int shared_rows(const ver_lstm_cfg& c) { return !three_layers(c) ? PAIRS_ROWS : c.compute ? 512 : c.hidden > 320 ? 64 : 256; }
-inline bool may_run_alone(const ver_lstm_cfg& c, int M) { return c.n_layers > 2 && pairs_of_layers(c) && M > shared_rows(c); }
-// The lines, by alive pieces (timesteps), us per forward and backward pass of three layers of equally long pieces, three in a launch / a launch
-// per layer (pieces of different length favour the former, whose time follows the longest): bf16, 320 units 32 (50) 448 / 488, 40 (50) 584 /
-// 580, 50 (50) 628 / 582, 64 units 64 (120) 1009 / 1034, 80 (120) 1237 / 1084, 1024 units 40 (50) 993 / 1082, 50 (50) 1146 / 1132; fp32, 256 units
-// 32 (20) 380 / 397, 50 (20) 487 / 446, 50 (50) 830 / 923, 64 (120) 1845 / 2115, 80 (120) 2496 / 2412; from 384 units on, where one team of
-// workers holds the weights, 512 units 8 (20) 364 / 362, 24 (50) 970 / 969, 32 (50) 1191 / 1142, 40 (120) 3101 / 3280, 50 (120) 3654 / 3427.
-// Pairs (of three layers, before): bf16, 320 units
-// 35 (29) 423 / 440, 51 (59) 782 / 787, 70 (117) 1675 / 1642, 76 (27) 562 / 512, 104 (29) 763 / 607, 910 (36) 8807 / 3677; fp32, 256
-// units 44 (68) 1027 / 1106, 70 (117) 2197 / 2263, 76 (27) 733 / 651; from 384 units on, where the workers hold the weights twice at
-// most, 512 units 20 (51) 866 / 931, 24 (21) 533 / 514, 28 (36) 791 / 792, 35 (29) 847 / 766, 44 (68) 1808 / 1805, 51 (59) 1818 / 1693, 70 (117)
-// 4177 / 3976.
+// The lines.  Three layers in a launch instead of a pair and a top layer, times of the one over the other, forward and backward pass of equally long
+// pieces (those of different length favour the former, whose time follows the longest):
+//   pieces (timesteps)     16 (8) 16 (96)  24 (16) 24 (32)  32 (16) 32 (96)  36 (8) 36 (32) 36 (96)  48 (32) 48 (96)  64 (8) 64 (96)
+//   bf16, 64 units           0.84    0.67     0.84    0.80     0.83    0.69    0.84    0.86    0.92     0.87    0.92    0.81    0.64
+//         256                0.94    0.70     0.99    0.88     0.99    0.74    0.85    0.89    0.94     0.89    0.93    0.84    0.71
+//         320                0.98    0.71     1.05    0.92     1.08    0.81   (40:) 0.95    1.09    1.13
+//         384                0.91    0.68     0.95    0.89     0.98    0.82    0.88    1.00    1.14     0.96    1.09    0.96    0.91
+//         576                0.89    0.68     0.91    0.85     0.94    0.85    0.98    1.06    1.10     0.99    1.02    0.98    0.76
+//         1024               0.88    0.68     0.87    0.82     0.90    0.84    0.85    1.03    1.07     0.93    0.96    0.93    0.88
+//   fp32, 64 units           1.02    0.74     1.01    0.91     0.99    0.73    0.69    0.70    0.75     0.71    0.74    0.83    0.74
+//         256                0.99    0.73     1.00    0.90     0.99    0.73    0.84    0.86    0.91     0.98    0.94    1.17    0.79
+//         384                1.06    0.77     1.11    0.97     1.14    0.89    0.94    0.95    1.11     1.06    1.04    1.15    1.04
+// What decides: whether the products' workers keep up, which are half as many as a pair's (above 256 units one team instead of two, at 320
+// instead of three), and from 33 alive pieces on whether 16 pieces at a time, two groups' worth instead of a pair's three, cost more than the
+// second walk.  (With what is launched and does nothing: 1.03 to 1.05 at fp32, 64 to 256 units, 24 and 32 pieces over 16 timesteps, and 0.97 to
+// 0.98 as pairs.)
+// Pairs instead of a launch per layer (of three layers): bf16, 320 units 35 (29) 423 / 440, 51 (59) 782 / 787, 70 (117) 1675 / 1642, 76 (27) 562 /
+// 512, 104 (29) 763 / 607, 910 (36) 8807 / 3677; fp32, 256 units 44 (68) 1027 / 1106, 70 (117) 2197 / 2263, 76 (27) 733 / 651; from 384 units on,
+// where the workers hold the weights twice at most, 512 units 20 (51) 866 / 931, 24 (21) 533 / 514, 28 (36) 791 / 792, 35 (29) 847 / 766, 44
+// (68) 1808 / 1805, 51 (59) 1818 / 1693, 70 (117) 4177 / 3976.
+inline int three_rows(const ver_lstm_cfg& c) { return c.hidden > 256 && (!c.compute || c.hidden == 320) ? (c.compute ? 128 : 64) : c.compute ? 512 : 128; }
+inline bool may_run_alone(const ver_lstm_cfg& c, int M) { return c.n_layers > 2 && pairs_of_layers(c) && M > PAIRS_ROWS; }
+// Three layers: whether other forms than that of one launch are launched.
+inline bool may_be_pairs(const ver_lstm_cfg& c, int M) { return three_layers(c) && M > three_rows(c); }
 inline void pair_lines(const ver_lstm_cfg& c, int M, PlanArgs* p) {
-    const bool low = !c.compute && c.hidden > 320, three = three_layers(c);
-    p->base = three ? (low ? 0 : c.compute ? 46 : 30) : low ? 12 : 45;
-    p->per = three ? 2 : low ? 2 : 4;
-    p->most = !may_run_alone(c, M) ? 0 : three ? (low ? 44 : c.compute ? 46 : 70) : low ? 60 : 80;
+    const bool low = !c.compute && c.hidden > 320;
+    p->base = low ? 12 : 45;
+    p->per = low ? 2 : 4;
+    p->most = !may_run_alone(c, M) ? 0 : low ? 60 : 80;
+    p->three = !three_layers(c) ? 0 : may_be_pairs(c, M) ? 1 : 2;
+    p->n2 = p->n3 = p->t2 = p->s2 = p->t3 = 0;
+    if (c.hidden <= 256) {   // two teams of workers for each product, or more
+        if (c.compute) {
+            p->n1 = 64;
+        } else {
+            p->n1 = 16; p->n2 = 40; p->t2 = 40; p->n3 = 64; p->t3 = c.hidden <= 128 ? 20 : 40;
+        }
+    } else if (c.compute) {
+        p->n1 = c.hidden == 320 ? 16 : 32; p->n2 = 32; p->t2 = 48;
+    } else {
+        p->n1 = 0; p->n2 = 32; p->t2 = 16; p->s2 = 3;
+    }
 }
 
-// What the first launch of the forward pass does for the two-layer launches: zeroes the flags, ticket counters, hand-over words
-// and the sticky time-out word at the start of the workspace, and writes the plans of both launches of the minibatch (the
+// What the first launch of the forward pass does for the launches of several layers: zeroes the flags, ticket counters, hand-over words
+// and the sticky time-out word at the start of the workspace, and writes the plans of both directions of the minibatch (the
 // backward call runs on the packing of the forward call whose activations it finds in the workspace).
 inline PlanArgs pipe_plan(const LstmWs& ws, int mode, bool wide, int G, int M, const int32_t* info, const int32_t* batch_sizes, const ver_lstm_cfg& c) {
-    PlanArgs p{info, batch_sizes, M, ws.plan[0], ws.plan[1], ws.plan_scratch, ws.err, (int)(ws.pipe + ws.pipe_words - ws.err),
-                    plan_cost(mode, wide, true, G, three_layers(c) ? TRIPLE_WORK_COUNT : WORK_COUNT),
-                    plan_cost(mode, wide, false, G, three_layers(c) ? TRIPLE_WORK_COUNT : WORK_COUNT), 0, 0, 0,
-                    three_layers(c) ? TRIPLE_GROUPS : PIPE_GROUPS};
+    PlanArgs p{};
+    p.info = info; p.batch_sizes = batch_sizes; p.M = M;
+    p.plan_fwd = ws.plan[0]; p.plan_bwd = ws.plan[1]; p.scratch = ws.plan_scratch;
+    p.clear = ws.err; p.n_clear = (int)(ws.pipe + ws.pipe_words - ws.err);
+    p.fwd = plan_cost(mode, wide, true, G, WORK_COUNT);
+    p.bwd = plan_cost(mode, wide, false, G, WORK_COUNT);
+    p.fwd_three = plan_cost(mode, wide, true, G, TRIPLE_WORK_COUNT);
+    p.bwd_three = plan_cost(mode, wide, false, G, TRIPLE_WORK_COUNT);
+    p.rows = PAIRS_ROWS;
     pair_lines(c, M, &p);
     return p;
 }
@@ -723,22 +752,40 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
                                static_cast<bf16_t*>(ws.layer[l].hcopy), quads, alone);
         }
     };
+    // Layers l and l + 1 in a launch; not_chosen: points to anything but a zero if the plan has chosen another form (NULL: it always runs).
+    auto pair = [&](int l, const int* not_chosen) {
+        PipeFwdArgs pa;
+        pa.l0 = rec_args(l);
+        pa.l1 = rec_args(l + 1, PIPE_GROUPS);
+        pa.work.A = ws.layer[l].hcopy; pa.work.B = ws.layer[l + 1].wih; pa.work.C = ws.layer[l + 1].gates;
+        pa.work.bias = ws.layer[l + 1].bias; pa.work.K = H; pa.work.N = 4 * H;
+        pipe_work(ws, 0, M, t_off, not_chosen, &pa.work);
+        pa.work.G = pa.l0.G;
+        ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
+        return launch_fwd_pair<MODE>(form, pa, not_chosen != nullptr, s);
+    };
     if (!prep_all()) return VER_EHIP;
     const int* alone = may_run_alone(c, M) ? ws.plan[0] + PLAN_ALONE : nullptr;
     for (int l = 0; l < c.n_layers;) {
         if (!project(l)) return VER_EHIP;
         if (three_layers(c)) {
-            for (int k = 0; alone && k < 3; ++k) {   // the same layers one after the other; where they do nothing they leave the words as they are
-                if (k > 0 && !project(k, alone)) return VER_EHIP;
-                if (!loop_alone(k, k == 0 ? ws.flags : ws.flags_alone[k - 1], alone)) return VER_EHIP;
-                if (k < 2) copy_h(k, alone);
+            if (may_be_pairs(c, M)) {   // the two lower layers one after the other or in a launch, then the top one; what does nothing leaves the words as they are
+                const int* top = ws.plan[0] + PLAN_TOP;
+                if (alone) {
+                    if (!loop_alone(0, ws.flags, alone)) return VER_EHIP;
+                    copy_h(0, alone);
+                    if (!project(1, alone) || !loop_alone(1, ws.flags_alone[0], alone)) return VER_EHIP;
+                }
+                if (!pair(0, ws.plan[0] + PLAN_NO_PAIR)) return VER_EHIP;
+                copy_h(1, top);
+                if (!project(2, top) || !loop_alone(2, ws.flags_alone[1], top)) return VER_EHIP;
             }
             TripleFwdArgs ta;
             for (int k = 0; k < 3; ++k) ta.l[k] = rec_args(k, k * TRIPLE_GROUPS);
             for (int k = 0; k < 2; ++k) {
                 ta.work[k].A = ws.layer[k].hcopy; ta.work[k].B = ws.layer[k + 1].wih; ta.work[k].C = ws.layer[k + 1].gates;
                 ta.work[k].bias = ws.layer[k + 1].bias; ta.work[k].K = H; ta.work[k].N = 4 * H;
-                pipe_work(ws, 0, M, t_off, ws.plan[0] + PLAN_ALONE, &ta.work[k], TRIPLE_WORK_COUNT, k);
+                pipe_work(ws, 0, M, t_off, ws.plan[0] + PLAN_NO_TRIPLE, &ta.work[k], TRIPLE_WORK_COUNT, k);
                 ta.work[k].G = ta.l[0].G;
             }
             ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
@@ -752,15 +799,7 @@ int run_fwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
                 copy_h(l, alone);
                 if (!project(l + 1, alone) || !loop_alone(l + 1, ws.flags_alone[0], alone)) return VER_EHIP;
             }
-            PipeFwdArgs pa;
-            pa.l0 = rec_args(l);
-            pa.l1 = rec_args(l + 1, PIPE_GROUPS);
-            pa.work.A = ws.layer[l].hcopy; pa.work.B = ws.layer[l + 1].wih; pa.work.C = ws.layer[l + 1].gates;
-            pa.work.bias = ws.layer[l + 1].bias; pa.work.K = H; pa.work.N = 4 * H;
-            pipe_work(ws, 0, M, t_off, alone, &pa.work);
-            pa.work.G = pa.l0.G;
-            ProfScope prof(VER_PROF_LSTM_REC_FWD, s);
-            if (!launch_fwd_pair<MODE>(form, pa, alone != nullptr, s)) return VER_EHIP;
+            if (!pair(l, alone)) return VER_EHIP;
             l += 2;
         } else {
             if (l > 0) fill_words(ws.flags, REC_FLAG_WORDS, 0, s);
@@ -871,7 +910,8 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         if (last) {
         ProfScope prof(VER_PROF_LSTM_DBIAS, s);
         float* const* g = gw + 4 * l;
-        BiasFinalArgs bf{ws.db_part, (size_t)REC_GROUPS * 4 * H, {}, {}, with == 1 ? REC_GROUPS : with == 2 ? PIPE_GROUPS : TRIPLE_GROUPS, H, with, with > 1 ? alone : nullptr};
+        const int* groups = with > 1 && (alone || may_be_pairs(c, M)) ? ws.plan[1] + PLAN_GROUPS : nullptr;
+        BiasFinalArgs bf{ws.db_part, (size_t)REC_GROUPS * 4 * H, {}, {}, with == 1 ? REC_GROUPS : with == 2 ? PIPE_GROUPS : TRIPLE_GROUPS, H, with, groups};
         for (int k = 0; k < with; ++k) { bf.out[k] = g[4 * k + 2]; bf.out2[k] = g[4 * k + 3]; }
         const bool heads = l + with == nl;
         hipLaunchKernelGGL(grads_final_kernel, dim3(std::max((4 * H + 255) / 256, (H + HF_COLS - 1) / HF_COLS), bf.sets + (heads ? A + 1 : 0)),
@@ -879,20 +919,40 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
         }
     };
 
+    // Layers l and l - 1 in a launch, with the gradients that arrive at their h (see the forward pass)
+    auto pair = [&](int l, float* dh_above, float* dh_below, const int* not_chosen) {
+        PipeBwdArgs pa;
+        pa.l1 = rec_args(l, dh_above);
+        pa.l0 = rec_args(l - 1, dh_below, PIPE_GROUPS);
+        pa.work.A = dz_of(l); pa.work.B = ws.layer[l].wihT; pa.work.C = dh_below; pa.work.bias = nullptr;
+        pa.work.K = 4 * H; pa.work.N = H;
+        pipe_work(ws, 1, M, t_off, not_chosen, &pa.work);
+        pa.work.G = pa.l1.G;
+        ProfScope prof(VER_PROF_LSTM_REC_BWD, s);
+        return launch_bwd_pair<MODE>(form, pa, not_chosen != nullptr, s);
+    };
+
     int cur = 0;  // ws.dh[cur] holds the gradient arriving at the current layer's h
     for (int l = nl - 1; l >= 0;) {
         if (three) {
-            for (int k = 2; alone && k >= 0; --k) {   // (as in the forward pass)
-                if (!loop_alone(k, ws.dh[2 - k], k == 2 ? ws.flags : ws.flags_alone[1 - k], alone)) return VER_EHIP;
-                if (k > 0) input_grad(k, ws.dh[3 - k], alone);
+            if (may_be_pairs(c, M)) {   // (as in the forward pass)
+                const int* top = ws.plan[1] + PLAN_TOP;
+                if (!loop_alone(2, ws.dh[0], ws.flags_alone[1], top)) return VER_EHIP;
+                input_grad(2, ws.dh[1], top);
                 if (!ok) return VER_EHIP;
+                if (alone) {
+                    if (!loop_alone(1, ws.dh[1], ws.flags_alone[0], alone)) return VER_EHIP;
+                    input_grad(1, ws.dh[2], alone);
+                    if (!ok || !loop_alone(0, ws.dh[2], ws.flags, alone)) return VER_EHIP;
+                }
+                if (!pair(1, ws.dh[1], ws.dh[2], ws.plan[1] + PLAN_NO_PAIR)) return VER_EHIP;
             }
             TripleBwdArgs ta;
             for (int k = 0; k < 3; ++k) ta.l[k] = rec_args(2 - k, ws.dh[k], k * TRIPLE_GROUPS);
             for (int k = 0; k < 2; ++k) {
                 ta.work[k].A = ws.dz[2 - k]; ta.work[k].B = ws.layer[2 - k].wihT; ta.work[k].C = ws.dh[k + 1]; ta.work[k].bias = nullptr;
                 ta.work[k].K = 4 * H; ta.work[k].N = H;
-                pipe_work(ws, 1, M, t_off, ws.plan[1] + PLAN_ALONE, &ta.work[k], TRIPLE_WORK_COUNT, k);
+                pipe_work(ws, 1, M, t_off, ws.plan[1] + PLAN_NO_TRIPLE, &ta.work[k], TRIPLE_WORK_COUNT, k);
                 ta.work[k].G = ta.l[0].G;
             }
             {
@@ -911,17 +971,7 @@ int run_bwd(const ver_lstm_cfg& c, const void* x, int M, const int32_t* info, co
                 input_grad(l, ws.dh[cur ^ 1], alone);
                 if (!ok || !loop_alone(l - 1, ws.dh[cur ^ 1], ws.flags_alone[0], alone)) return VER_EHIP;
             }
-            PipeBwdArgs pa;
-            pa.l1 = rec_args(l, ws.dh[cur]);
-            pa.l0 = rec_args(l - 1, ws.dh[cur ^ 1], PIPE_GROUPS);
-            pa.work.A = ws.dz[1]; pa.work.B = ws.layer[l].wihT; pa.work.C = ws.dh[cur ^ 1]; pa.work.bias = nullptr;
-            pa.work.K = 4 * H; pa.work.N = H;
-            pipe_work(ws, 1, M, t_off, alone, &pa.work);
-            pa.work.G = pa.l1.G;
-            {
-            ProfScope prof(VER_PROF_LSTM_REC_BWD, s);
-            if (!launch_bwd_pair<MODE>(form, pa, alone != nullptr, s)) return VER_EHIP;
-            }
+            if (!pair(l, ws.dh[cur], ws.dh[cur ^ 1], alone)) return VER_EHIP;
             layer_grads(l, nullptr, 2, false);   // the weight gradients of both layers leave in one grouped launch
             layer_grads(l - 1, l > 1 ? ws.dh[cur] : d_x, 2, true);
             if (!ok) return VER_EHIP;

@@ -43,9 +43,13 @@ static_assert(PIPE_XCDS - 2 * PIPE_GROUPS == 2, "two worker XCDs");
 
 // The plan of a launch (ints in global memory, written by plan_launches):
 constexpr int PLAN_KB = 0;           // [PIPE_GROUPS + 1] first piece of every group's block, then the number of pieces
+constexpr int PLAN_GROUPS = 4;       // [2] groups of a layer's time loop: the lower layers, the top one of three
 constexpr int PLAN_ALONE = 6;        // not 0: too many alive pieces per timestep, the layers run alone (see plan_launches)
+constexpr int PLAN_NO_PAIR = 7;      // three layers: 0 if the two lower ones share a launch
 constexpr int PLAN_T = 8;            // [PIPE_GROUPS] timesteps of the group (those of its first piece; 0 if it has none)
+constexpr int PLAN_NO_TRIPLE = 11;   // three layers: 0 if all share a launch
 constexpr int PLAN_CT = 12;          // [PIPE_GROUPS] timesteps per chunk
+constexpr int PLAN_TOP = 15;         // three layers: not 0 if the top one has a launch of its own
 constexpr int PLAN_WORDS = 16;
 inline __host__ __device__ size_t plan_scratch_floats(int M) { return 2 * ((size_t)M + 1); }
 // The words a launch synchronises through (zero at launch): progress[g] at g, then done[g][chunk] from 16 with
@@ -248,12 +252,21 @@ struct PlanArgs {
     int M;
     int* plan_fwd; int* plan_bwd; float* scratch;
     int* clear; int n_clear;
-    PlanCost fwd, bwd;
-    // Two layers share a launch up to min(most, base + T / per) alive pieces per timestep (average over the T timesteps); most = 0:
-    // always.
-    int base, per, most;
-    int groups;   // per layer
+    PlanCost fwd, bwd;                // of the launches of two layers
+    // Two layers share a launch up to min(most, base + T / per) alive pieces per timestep (average over the T timesteps) and up to `rows` rows;
+    // most = 0: always.
+    int base, per, most, rows;
+    // Three layers do up to n1 alive pieces, up to n2 where 2 T >= t2 + s2 times their number, and up to n3 from t3 timesteps on; else
+    // the two lower ones do by the rule above.
+    PlanCost fwd_three, bwd_three;
+    int three;                        // 0: not three layers, 1: by the rule, 2: always
+    int n1, n2, t2, s2, n3, t3;
 };
+// Whether all of three layers share a launch (M rows over T timesteps).
+inline __host__ __device__ bool plan_three(const PlanArgs& a, int M, int T) {
+    const long long m = M, t = T;
+    return a.three == 2 || m <= a.n1 * t || (m <= a.n2 * t && 2 * t * t >= a.t2 * t + a.s2 * m) || (m <= a.n3 * t && T >= a.t3);
+}
 struct PlanLds {
     int bs[PLAN_LDS_N];
     float len[PLAN_LDS_N], S1[PLAN_LDS_N + 1];
@@ -261,13 +274,25 @@ struct PlanLds {
 __device__ __forceinline__ void plan_launches(const PlanArgs& a, PlanLds& lds) {
     const int M = a.M, n_seq = min(max(a.info[0], 0), M), T = min(max(a.info[1], 0), M);
     for (int i = threadIdx.x; i < a.n_clear; i += PLAN_THREADS) a.clear[i] = 0;
-    const bool alone = a.most > 0 && M > min(a.most, a.base + T / a.per) * T;
-    if (threadIdx.x == 0) a.plan_fwd[PLAN_ALONE] = a.plan_bwd[PLAN_ALONE] = alone ? 1 : 0;
+    const bool triple = a.three != 0 && plan_three(a, M, T);
+    const bool alone = !triple && a.most > 0 && M > a.rows && M > min(a.most, a.base + T / a.per) * T;
+    if (threadIdx.x < PLAN_DIRS) {
+        int* plan = threadIdx.x == 0 ? a.plan_fwd : a.plan_bwd;
+        plan[PLAN_ALONE] = alone ? 1 : 0;
+        plan[PLAN_NO_PAIR] = triple || alone ? 1 : 0;
+        plan[PLAN_NO_TRIPLE] = triple ? 0 : 1;
+        plan[PLAN_TOP] = triple ? 0 : 1;
+        plan[PLAN_GROUPS] = triple ? TRIPLE_GROUPS : alone ? REC_GROUPS : PIPE_GROUPS;
+        plan[PLAN_GROUPS + 1] = triple ? TRIPLE_GROUPS : REC_GROUPS;
+    }
     if (alone) return;
+    const PlanCost& fwd = triple ? a.fwd_three : a.fwd;
+    const PlanCost& bwd = triple ? a.bwd_three : a.bwd;
+    const int groups = triple ? TRIPLE_GROUPS : PIPE_GROUPS;
     if (n_seq <= PLAN_LDS_N && T <= PLAN_LDS_N)
-        plan_body<true>(a.batch_sizes, M, n_seq, T, a.plan_fwd, a.plan_bwd, a.scratch, lds.bs, lds.len, lds.S1, a.fwd, a.bwd, a.groups);
+        plan_body<true>(a.batch_sizes, M, n_seq, T, a.plan_fwd, a.plan_bwd, a.scratch, lds.bs, lds.len, lds.S1, fwd, bwd, groups);
     else
-        plan_body<false>(a.batch_sizes, M, n_seq, T, a.plan_fwd, a.plan_bwd, a.scratch, lds.bs, lds.len, lds.S1, a.fwd, a.bwd, a.groups);
+        plan_body<false>(a.batch_sizes, M, n_seq, T, a.plan_fwd, a.plan_bwd, a.scratch, lds.bs, lds.len, lds.S1, fwd, bwd, groups);
 }
 
 // One 128 x 256 tile of C[M, N] = A[M, K] B[N, K]^T + bias for bf16 operands, by 8 waves (2 x 4 of 64 x 64) of a workgroup
