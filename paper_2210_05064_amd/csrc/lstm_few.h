@@ -110,6 +110,35 @@ __device__ __forceinline__ void few_touch(int& v) { asm volatile("" : "+v"(v)); 
 // A word to publish: never FEW_EMPTY (only a pair of NaNs, or an fp32 NaN, has these bits; it stays NaN).
 __device__ __forceinline__ unsigned few_word(unsigned v) { return v == FEW_EMPTY ? FEW_EMPTY - 1 : v; }
 
+// few_fwd and few_bwd take the address of the kernel's arguments and load them once more, and take everything else as values that
+// are made scalar here: their time loops shared the scalar registers with what the kernel keeps for its other forms and roles, and
+// fetched their own constants from spill lanes (64 to 88 v_readlane per backward timestep of a consumer, now 2 to 18).  (As calls, with
+// registers of their own, they save and restore a hundred vector registers per lane: 16 us per launch at H = 1024.)
+template <typename T> __device__ __forceinline__ T few_scalar(T v) {
+    if constexpr (sizeof(T) == 8) {
+        const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+        const unsigned long long u = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)b) |
+                                     (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(b >> 32)) << 32;
+        return __builtin_bit_cast(T, u);
+    } else {
+        return __builtin_bit_cast(T, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+    }
+}
+// A pointer that the compiler knows to be global (of one read from memory it does not, and a generic access also counts
+// as one to LDS).
+template <typename T> __device__ __forceinline__ void few_global(T*& p) { p = (T*)(__attribute__((address_space(1))) T*)p; }
+// Kept in vector registers: what a timestep rarely asks for, or asks for with a lane's address.
+template <typename T> __device__ __forceinline__ void few_away(T& v) {
+    if constexpr (std::is_pointer<T>::value) {
+        unsigned long long b = reinterpret_cast<unsigned long long>(v);
+        asm volatile("" : "+v"(b));
+        typedef typename std::remove_pointer<T>::type V;
+        v = (T)(__attribute__((address_space(1))) V*)b;
+    } else {
+        asm volatile("" : "+v"(v));
+    }
+}
+
 // Reads L x 16 bytes per lane at from + off[j]; with `check` again and again until no word is empty.  The loads
 // bypass the CU's L1 (sc0 sc1) and are written out because the compiler waits for every volatile load by itself.
 // Lanes that do not `take` part keep what raw holds.  False: the wait was abandoned (time-out here or in another
@@ -394,6 +423,18 @@ struct FewFwd {
     float* part;                 // LDS
 };
 
+// A word at `rows` + `off` bytes of an array (`rows`: the same for all lanes).  Consumers, which run out of scalar registers, store through a
+// pointer: two of them instead of a buffer's four (40 -> 16 v_readlane in two timesteps at 256 units; us per forward pass of two layers of
+// 256 units over 256 timesteps of 8 pieces per group 363 -> 347); one layer alone is faster with buffers (512 units 366 -> 360).
+template <int PIPE>
+__device__ __forceinline__ void few_store(void* array, unsigned rows, unsigned off, unsigned v) {
+    if constexpr ((PIPE & PIPE_CONSUMER) != 0) {
+        __attribute__((address_space(1))) unsigned char* at = (__attribute__((address_space(1))) unsigned char*)array + rows;
+        *(__attribute__((address_space(1))) unsigned*)(at + off) = v;
+    } else {
+        __builtin_amdgcn_raw_buffer_store_b32(v, __builtin_amdgcn_make_buffer_rsrc(array, 0, (int)0x80000000u, 0x00020000), off, rows, 0);
+    }
+}
 template <int MODE, int MT, int NB, int PIPE>
 __device__ __forceinline__ void few_fwd_store(const FewFwd<MODE, MT, NB>& s, const RecFwdArgs& a, const PieceSet& ps, int j0, int bs_prev,
                                               int base, int bs) {
@@ -405,18 +446,11 @@ __device__ __forceinline__ void few_fwd_store(const FewFwd<MODE, MT, NB>& s, con
     const unsigned col = (unsigned)(n * H + j0 + u);
     const unsigned so = (unsigned)s.base_prev * (unsigned)H;   // elements of an [M, H] array
     const __amdgpu_buffer_rsrc_t rs_g = __builtin_amdgcn_make_buffer_rsrc(a.gates, 0, WHOLE, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rs_c = __builtin_amdgcn_make_buffer_rsrc(a.c, 0, WHOLE, 0x00020000);
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, s.s_g), rs_g, col * 16u, so * 16u, 0);
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s.s_c), rs_c, col * 4u, so * 4u, 0);
-    if (!(PIPE & PIPE_PRODUCER)) {
-        const __amdgpu_buffer_rsrc_t rs_h = __builtin_amdgcn_make_buffer_rsrc(a.hout, 0, WHOLE, 0x00020000);
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s.s_h), rs_h, col * 4u, so * 4u, 0);
-    }
+    few_store<PIPE>(a.c, so * 4u, col * 4u, __float_as_uint(s.s_c));
+    if (!(PIPE & PIPE_PRODUCER)) few_store<PIPE>(a.hout, so * 4u, col * 4u, __float_as_uint(s.s_h));
     if (MODE == MODE_F32 || (u & 1) == 0) {   // operand type: a bf16 pair per even lane
-        if (m < bs) {
-            const __amdgpu_buffer_rsrc_t rs_hp = __builtin_amdgcn_make_buffer_rsrc(a.hprev, 0, WHOLE, 0x00020000);
-            __builtin_amdgcn_raw_buffer_store_b32(s.s_w, rs_hp, col * es, (unsigned)base * (unsigned)(H * es), 0);
-        }
+        if (m < bs) few_store<PIPE>(a.hprev, (unsigned)base * (unsigned)(H * es), col * es, s.s_w);
         if (PIPE & PIPE_PRODUCER) {   // written through: input of the workers' GEMM
             const __amdgpu_buffer_rsrc_t rs_hc = __builtin_amdgcn_make_buffer_rsrc(a.hcopy, 0, WHOLE, 0x00020000);
             __builtin_amdgcn_raw_buffer_store_b32(s.s_w, rs_hc, col * es, so * es, 17);
@@ -500,7 +534,7 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
         }
         bar_lds();
         const int failed = *s.fail;   // (looked at after the publication: its read is not waited for by itself)
-        if (look) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= pl.need;
+        if (look) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= few_scalar(pl.need);
         // Every workgroup has published the rows of timestep t-1, which it did after its stores for timestep t-3 had
         // completed (they are issued in timestep t-2 and waited for in timestep t-1).
         if ((PIPE & PIPE_PRODUCER) && rank == 0 && tid == REC_THREADS - 1 && t - 2 > s.t0) st_agent(pl.progress, t - 2);
@@ -552,34 +586,6 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
     return true;
 }
 
-// few_fwd and few_bwd take the address of the kernel's arguments and load them once more, and take everything else as values that
-// are made scalar here: their time loops shared the scalar registers with what the kernel keeps for its other forms and roles, and
-// fetched their own constants from spill lanes (64 to 88 v_readlane per backward timestep of a consumer, now 2 to 18).  (As calls, with
-// registers of their own, they save and restore a hundred vector registers per lane: 16 us per launch at H = 1024.)
-template <typename T> __device__ __forceinline__ T few_scalar(T v) {
-    if constexpr (sizeof(T) == 8) {
-        const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-        const unsigned long long u = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)b) |
-                                     (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(b >> 32)) << 32;
-        return __builtin_bit_cast(T, u);
-    } else {
-        return __builtin_bit_cast(T, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
-    }
-}
-// A pointer that the compiler knows to be global (of one read from memory it does not, and a generic access also counts
-// as one to LDS).
-template <typename T> __device__ __forceinline__ void few_global(T*& p) { p = (T*)(__attribute__((address_space(1))) T*)p; }
-// Kept in vector registers: what a timestep rarely asks for, or asks for with a lane's address.
-template <typename T> __device__ __forceinline__ void few_away(T& v) {
-    if constexpr (std::is_pointer<T>::value) {
-        unsigned long long b = reinterpret_cast<unsigned long long>(v);
-        asm volatile("" : "+v"(b));
-        typedef typename std::remove_pointer<T>::type V;
-        v = (T)(__attribute__((address_space(1))) V*)b;
-    } else {
-        asm volatile("" : "+v"(v));
-    }
-}
 template <typename A> using few_args_t = const A __attribute__((address_space(4)))*;
 struct FewLink { PieceSet ps; PipeLink pl; };
 template <int PIPE>
@@ -594,6 +600,7 @@ __device__ __forceinline__ FewLink few_link(int x, int cap, int id, int* progres
     few_away(l.pl.progress);
     few_away(l.pl.done);
     l.pl.need = few_scalar(need);
+    few_away(l.pl.need);
     l.pl.ct = few_scalar(ct);
     l.pl.T = 0;
     return l;
@@ -609,7 +616,7 @@ __device__ __forceinline__ bool few_fwd(few_args_t<RecFwdArgs> args, int x_, int
     const PipeLink& pl = link.pl;
     const int rank = few_scalar(rank_), t0 = few_scalar(t0_), T = few_scalar(T_), c_wait = few_scalar(c_wait_);
     int* flags = few_scalar(flags_);
-    few_global(flags);
+    few_away(flags);
     RecFwdArgs a = *(const RecFwdArgs*)few_scalar(args);
     few_global(a.batch_sizes); few_global(a.t_off); few_global(a.gates); few_global(a.c); few_global(a.hout);
     few_away(a.c0); few_away(a.err); few_away(a.batch_sizes); few_away(a.seq_cap);
@@ -669,7 +676,7 @@ __device__ __forceinline__ bool few_fwd(few_args_t<RecFwdArgs> args, int x_, int
     if (!few_fwd_phase<MODE, MT, NB, PIPE>(s, a, ps, rank, flags, ring, pl, t, T)) return false;
     if (t > t0) few_fwd_store<MODE, MT, NB, PIPE>(s, a, ps, j0, grp_count(s.base - s.base_prev, ps), s.base, t < T ? grp_count(s.bs_a, ps) : 0);
     if (t < T && !quad_fwd<MODE, MT, NB, PIPE>(s, a, ps, rank, flags, ring, pl, t, T)) return false;
-    if (PIPE & PIPE_PRODUCER) rec_publish(flags, rank, T + 1);
+    if (PIPE & PIPE_PRODUCER) rec_publish(few_scalar(flags), rank, T + 1);
     return true;
 }
 
@@ -816,7 +823,7 @@ __device__ __forceinline__ bool few_bwd_phase(FewBwd<MODE, MT, NB>& s, const Rec
         }
         bar_lds();
         const int failed = *s.fail;
-        if (look) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= pl.need;
+        if (look) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= few_scalar(pl.need);
         // Every workgroup has published the rows of timestep t, which it did after its dz rows of timestep t+2 had
         // completed (they are stored in that timestep and waited for in timestep t+1).
         if ((PIPE & PIPE_PRODUCER) && rank == 0 && tid == REC_THREADS - 1 && t + 2 < T) st_agent(pl.progress, T - (t + 2));

@@ -246,7 +246,7 @@ __device__ __forceinline__ bool quad_fwd(FewFwd<MODE, MT, NB>& s, const RecFwdAr
         }
         if (polls) quad_request<L>(rs_ring, off, so_w, raw);   // (after the last timestep: nothing, from beyond the buffer)
         __builtin_amdgcn_sched_barrier(0);
-        if ((PIPE & PIPE_CONSUMER) && to_edge == 1) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= pl.need;
+        if ((PIPE & PIPE_CONSUMER) && to_edge == 1) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= few_scalar(pl.need);
         if (__builtin_amdgcn_readfirstlane(failed)) {
             alive = false;
             break;
@@ -450,7 +450,7 @@ __device__ __forceinline__ bool quad_bwd_loop(QuadBwd<MODE, MT, NB, PIPE>& d, Fe
             d.dh = quad_sum(p[0] + p[PART]);
             if (MODE == MODE_F32 || (q & 1) == 0) __builtin_amdgcn_raw_buffer_store_b32(FEW_EMPTY, rs_ring, w_off, so_e, 0);
         }
-        if ((PIPE & PIPE_CONSUMER) && to_edge == 1) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= pl.need;
+        if ((PIPE & PIPE_CONSUMER) && to_edge == 1) s.ready = __builtin_amdgcn_readfirstlane(s.fail[1]) >= few_scalar(pl.need);
         if (__builtin_amdgcn_readfirstlane(failed)) {
             alive = false;
             break;

@@ -587,7 +587,16 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
     REC_PROF_START();
     if ((PIPE & PIPE_CONSUMER) && T > 0 && !pipe_wait_chunk(pl, 0, a.err, REC_PROF_CHUNK_ACC(a, rank, ps))) return;
     int c_wait = 1;   // consumer: the chunk it has to wait for next
+    const RecFwdArgs& by_ref = a;
     if (t_many > 0) {
+    // One layer alone: as in rec_bwd_rest (fp32, 17 pieces per group, 64 and 128 units 3.67 -> 3.60 and 4.03 -> 3.98 us per timestep; in launches of
+    // several layers it is the loops of few pieces that get slower, 512 units, fp32, 8 pieces per group 3.48 -> 3.53)
+    RecFwdArgs again;
+    if constexpr (PIPE == PIPE_NONE) {
+        again = args_again(by_ref);
+        few_away(again.err); few_away(again.c0); few_away(again.batch_sizes); few_away(again.seq_cap);
+    }
+    const RecFwdArgs& a = PIPE == PIPE_NONE ? again : by_ref;
     // this wave's rows of W_hh (its share of the contraction) -> registers, in MFMA operand layout
     f32x4_t wreg[TPW * NBW];
 #pragma unroll
@@ -619,7 +628,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
         goff[q] = ((unsigned)((q * 16 + lr) * X + x) * 4u * (unsigned)H + (unsigned)je * 4u) * 4u;
     }
     if (has_tile) {
-        const int bs0 = grp_count(a.batch_sizes[0], ps);
+        const int bs0 = grp_count(few_scalar(a.batch_sizes[0]), ps);
 #pragma unroll
         for (int q = 0; q < REC_PRE; ++q)
             if (q * 16 + lr < bs0) {
@@ -631,7 +640,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
 
     // batch sizes of timesteps t, t+1 (and t+2, fetched a step ahead: a scalar load that misses costs about half
     // a microsecond, which would otherwise sit at the top of every step); row offsets follow by addition
-    int bs_a = T > 0 ? a.batch_sizes[0] : 0, bs_b = T > 1 ? a.batch_sizes[1] : 0;
+    int bs_a = T > 0 ? few_scalar(a.batch_sizes[0]) : 0, bs_b = T > 1 ? few_scalar(a.batch_sizes[1]) : 0;
     int base = 0, base_prev = 0;
     // The activation arrays as buffers that never change during the loop (host code guarantees that every
     // array is shorter than 2^31 bytes); a lane without a piece gets an offset beyond the range, which a load

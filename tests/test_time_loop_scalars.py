@@ -41,3 +41,14 @@ def test_scalars_of_the_loops_of_few_pieces(tmp_path):
         # up to four pieces: a product, no LDS-direct loads, one timestep of four stores per pass
         reads = [count(l, r"v_readlane") for l in loops(body) if count(l, r"v_mfma|v_fmac\w*_dpp") and not count(l, r"offen lds") and count(l, r"buffer_store") == 4]
         assert len(reads) == 4 and max(reads) <= MOST, (kernel, reads)   # producer and consumer, two sizes each
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_scalars_of_the_consumers_loop_of_five_to_sixteen_pieces(tmp_path):
+    """Forward, two timesteps per pass: 15 to 24 before, 32 to 40 with the loops of many pieces in place."""
+    for kernel, asm in assembly(["lstm_pipe_fwd_kernel<MODE_BF16, 2, 4, 4, true>(PipeFwdArgs)", "lstm_pipe_fwd_kernel<MODE_BF16, 2, 2, 16, true>(PipeFwdArgs)"], tmp_path).items():
+        body = re.search(r"^_ZN3ver\d+lstm_pipe_fwd_kernel\w*:[^\n]*\n(.*?)^\.Lfunc_end", asm, re.S | re.M).group(1)
+        count = lambda loop, what: sum(bool(re.search(what, line)) for line in loop)
+        # four barriers per timestep: of the wait for a chunk, of that for the flags, behind the partial sums and behind their last read
+        reads = [count(l, r"v_readlane") for l in loops(body) if count(l, r"v_mfma") and not count(l, r"offen lds") and count(l, r"s_barrier") == 8]
+        assert len(reads) == 1 and reads[0] <= 24, (kernel, reads)
