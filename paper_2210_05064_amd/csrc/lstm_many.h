@@ -19,9 +19,18 @@
 namespace ver {
 
 constexpr int MANY_MAX = 512;   // rows of a slot; more alive pieces than that: the flag form of lstm_rec.h
-// Not fp32 up to 128 units, where one or two waves hold all of the contraction, 2 us of MFMAs per unit (the flag form shares them): 64 units 3.5 /
-// 3.6 / 6.8 -> 3.9 / 3.9 / 7.6, 128 3.8 / 3.9 / 7.6 -> 3.9 / 3.9 / 7.8.
-template <int MODE> __host__ __device__ constexpr bool many_pays(int H) { return MODE == MODE_BF16 || H > 128; }
+// fp32 holds the contraction in H / 64 waves, which all take 2 us of MFMAs per unit (the flag form shares them evenly), the first four of them on
+// SIMDs of their own: so 256 units and from 448 on.  us per forward pass of two layers with 17 / 32 / 64 pieces per group, 48 timesteps, flag form -> this one
+// in hundredths: 192 units 97 / 96 / 104 (12 timesteps 105 / 104 / 108), 256 91 / 90 / 96, 320 109 / 105 / 111, 384 102 / 99 / 100, 448 97 / 98 /
+// 96, 512 98 / 92 / 94; one layer of 64 units 3.5 / 3.6 / 6.8 -> 3.9 / 3.9 / 7.6 us per timestep.
+template <int MODE> __host__ __device__ constexpr bool many_pays(int H) { return MODE == MODE_BF16 || H == 256 || H > 384; }
+// In a launch of several layers it hands rows on about two timesteps later, and pays from this many timesteps on: forward passes of two layers with 17
+// pieces per group over 4 / 8 / 12 / 16 / 24 timesteps, as above: bf16, 512 units 111 / 106 / 102 / 101 / 99, 1024 105 / 103 / 102 / 101 / 99, 64 98 / 90 /
+// 87 / 84 / 81, 256 (6:) 100 / 98 / 96 / 93 / 90, 576 104 / 97 / 93 / 91 / 86; fp32, 256 units 109 / 103 / 100 / 98 / 96, 448 (12:) 103, 512 104 / 101 / 104 / 102 / 101.
+// One layer 101 / 97 / 97 / 95 / 94 at 1024 units.
+template <int MODE> __host__ __device__ constexpr int many_steps_fwd(int H, bool shared) {
+    return !shared ? 1 : MODE == MODE_F32 || H == 512 ? 24 : H == 1024 ? 16 : 8;
+}
 // Rows of a slot for minibatches of M rows; 0 where no launch of this width runs the form.
 inline int many_rows(int mode, int H, int M) {
     if (!(mode == MODE_BF16 ? many_pays<MODE_BF16>(H) : many_pays<MODE_F32>(H)) || M <= FEW_MAX) return 0;
@@ -31,31 +40,41 @@ inline __host__ __device__ size_t many_ring_bytes(int mode, int row_elems, int r
 inline __host__ __device__ size_t many_lds_bytes(int cols, int nb) { return (size_t)few_part_floats(cols) * sizeof(float) + (size_t)2 * REC_WAVES * few_stage_bytes(nb); }
 
 // The backward loop runs the timesteps of more than 16 pieces of a group in one form: this one for up to MANY_MAX_BWD (rows of a slot; dz has
-// four times the columns of h), from MANY_STEPS_BWD such timesteps on, where the lines below say so; else that of lstm_rec.h.
-// In a shared launch it hands rows on about two timesteps later, 10 to 20 us in all: us per backward launch of two layers with 17 / 32 / 64 equally
-// long pieces per group, flag form -> this one, 512 units (bf16) 16 timesteps 75 / 99 / 166 -> 96 / 107 / 175, 32 132 / 167 / 290 -> 154 / 175 / 289, 128
-// 491 / 589 / 1106 -> 487 / 544 / 1049; fp32, 512 units, 16 172 / 208 / 377 -> 188 / 212 / 372, 128 1080 / 1330 / 2559 -> 1034 / 1235 / 2309; 1024 units, 8
-// 95 / 113 / 193 -> 113 / 113 / 178, 32 253 / 316 / 601 -> 233 / 257 / 474, 128 922 / 1176 / 2254 -> 746 / 858 / 1627.
-// us per timestep of one layer, 17 / 32 / 64 pieces: bf16, 1024 units 6.7 / 8.7 / 16.5 -> 5.1 / 6.1 / 12.2, 576 7.5 / 9.2 / 17.4 -> 3.5 / 4.2 / 8.5, 512 3.4 /
-// 4.3 / 8.1 -> 3.3 / 3.7 / 7.3, 256 2.6 / 3.4 / 6.5 -> 2.5 / 2.8 / 5.7, 192 2.6 / 3.6 / 5.9 -> 2.4 / 2.7 / 5.6, 128 2.4 / 2.8 / 4.8 -> 2.4 / 2.4 / 5.1, 64 2.4 / 2.7 /
-// 4.0 -> 2.3 / 2.4 / 4.6; fp32, 512 8.2 / 9.8 / 19.1 -> 7.3 / 7.9 / 15.8, 320 7.5 / 9.4 / 17.7 -> 6.7 / 6.7 / 13.4, 256 4.7 / 5.7 / 10.9 -> 5.1 / 5.3 / 10.7, 128 3.2 /
-// 3.9 / 8.2 -> 4.6 / 4.7 / 9.5.  So: fp32 above 256 units; bf16 where the flag form's loop has no width of its own (NI = 0, and MT = 2), up to 128
-// units from 25 to 48 pieces.  Not bf16 at 128, 256 and 512 units, although long launches of 25 pieces and more gain there: with the form in the kernel
-// the compiler spills more scalars in the loops of few pieces, which an update of 2 x 512 units consists of (6.89 -> 7.03 ms).
+// four times the columns of h) where the lines of many_pays_bwd say so; else that of lstm_rec.h.
+// In a shared launch it hands rows on about two timesteps later, 10 to 20 us in all.  Backward passes of two layers over 24 / 48 / 96 timesteps, flag form ->
+// this one in hundredths (before its other lines):
+//   pieces per group           17                24                32                48                64
+//   bf16, 128 units            flags             flags       105 / 100 /  98   112 / 109 / 107         flags
+//         192            107 / 102 / 101   104 /  99 /  96    98 /  93 /  89   102 /  98 /  95   111 / 108 / 106
+//         320            102 /  97 /  93    93 /  89 /  85    87 /  80 /  76    87 /  81 /  77    83 /  79 /  77
+//         448            108 / 103 /  99   100 /  95 /  93    94 /  92 /  88    89 /  86 /  79    94 /  90 /  87
+//         576             82 /  75 /  71    76 /  70 /  66    72 /  65 /  61    69 /  65 /  62    69 /  65 /  63
+//        1024            103 /  97 /  92    94 /  88 /  84    88 /  86 /  83    89 /  84 /  82    88 /  84 /  81
+//   fp32, 320            104 / 101 / 100    98 /  94 /  92    92 /  87 /  84    91 /  89 /  85    92 /  88 /  86
+//         512            104 / 100 /  98    99 /  95 /  95   100 /  98 /  95    99 /  96 /  93    98 /  95 /  95
+// One layer alone: bf16, 128 units 32 pieces 96 / 92 / 91, 48 103 / 102 / 102; 192 97 / 95 / 93 to 100 / 98 / 97; 512, fp32, 97 to 87; 1024 90 to 81.
+// us per timestep of one layer, 17 / 32 / 64 pieces: bf16, 1024 units 6.7 / 8.7 / 16.5 -> 5.1 / 6.1 / 12.2, 576 7.5 / 9.2 / 17.4 -> 3.5 / 4.2 / 8.5, 192 2.6 / 3.6 /
+// 5.9 -> 2.4 / 2.7 / 5.6, 128 2.4 / 2.8 / 4.8 -> 2.4 / 2.4 / 5.1; fp32, 512 8.2 / 9.8 / 19.1 -> 7.3 / 7.9 / 15.8, 256 4.7 / 5.7 / 10.9 -> 5.1 / 5.3 / 10.7, 128 3.2 /
+// 3.9 / 8.2 -> 4.6 / 4.7 / 9.5.  Not bf16 at 256 and 512 units, whose flag form has a loop of its own width: 512 units 3.4 / 4.3 / 8.1 -> 3.3 / 3.7 / 7.3, 256 2.6 / 3.4 /
+// 6.5 -> 2.5 / 2.8 / 5.7; long launches of 25 pieces and more gain there, but with the form in the kernel the compiler spills more scalars in the loops of
+// few pieces, which an update of 2 x 512 units consists of (6.89 -> 7.03 ms).
 constexpr int MANY_MAX_BWD = 256;
 constexpr int MANY_STEPS_BWD = 24;
 // Kernels that have the form: MT tiles per workgroup, loops for NI operand blocks (0: the general ones).
 constexpr bool many_bwd_form(int mode, int mt, int ni) { return mt == 2 || (ni != 4 && ni != 8 && (ni != 16 || mode == MODE_F32)); }
 template <int MODE, int MT, int NI> constexpr bool MANY_BWD = many_bwd_form(MODE, MT, NI);
-template <int MODE, int MT> __host__ __device__ constexpr bool many_pays_bwd(int H, int pieces) {
+// pieces of a group, timesteps with more than 16 of them; shared: a launch of several layers.
+template <int MODE, int MT> __host__ __device__ constexpr bool many_pays_bwd(int H, int pieces, int steps, bool shared) {
+    if (steps < MANY_STEPS_BWD || pieces > MANY_MAX_BWD) return false;
+    if (shared && pieces <= 24 && steps < 2 * MANY_STEPS_BWD && (MT == 1 || H == 1024)) return false;
     if (MODE == MODE_F32) return H > 256;
-    return MT == 2 || H > 128 || (pieces > 24 && pieces <= 48);
+    if (MT == 1 && H <= 128) return pieces > 24 && pieces <= 32 && (!shared || steps >= 2 * MANY_STEPS_BWD);
+    return MT == 2 || H != 192 || !shared || (pieces > 24 && pieces <= 48);
 }
 // Rows of a slot of the backward ring for minibatches of M rows; ni: operand blocks per wave (run_bwd).  0 where no launch runs the form.
 inline int many_rows_bwd(int mode, int H, int mt, int ni, int M) {
-    const int most = mode == MODE_F32 || mt == 2 || H > 128 ? MANY_MAX_BWD : 48;
-    const bool pays = mode == MODE_F32 ? many_pays_bwd<MODE_F32, 1>(H, most) : mt == 2 ? many_pays_bwd<MODE_BF16, 2>(H, most) : many_pays_bwd<MODE_BF16, 1>(H, most);
-    if (!many_bwd_form(mode, mt, ni) || !pays || M < (FEW_MAX + 1) * MANY_STEPS_BWD) return 0;
+    const int most = mode == MODE_BF16 && H <= 128 ? 32 : MANY_MAX_BWD;
+    if (!many_bwd_form(mode, mt, ni) || (mode == MODE_F32 && H <= 256) || M < (FEW_MAX + 1) * MANY_STEPS_BWD) return 0;
     return M < most ? (M + 15) / 16 * 16 : most;
 }
 

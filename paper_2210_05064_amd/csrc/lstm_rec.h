@@ -199,9 +199,10 @@ __device__ __forceinline__ bool rec_wait(const int* flags, int G, int target, in
 __device__ __forceinline__ void rec_publish(int* flags, int rank, int value) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     bar_lds();
-    if (threadIdx.x == 0) {
-        __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(&flags[rank], 0, 4, 0x00020000);
-        __builtin_amdgcn_raw_buffer_store_b32(value, r, 0, 0, 0);
+    if (threadIdx.x == 0) {   // (through a pointer in vector registers: a buffer would be kept in four scalar ones)
+        unsigned long long at = reinterpret_cast<unsigned long long>(flags + rank);
+        asm volatile("" : "+v"(at));
+        *(__attribute__((address_space(1))) int*)at = value;
     }
 }
 
@@ -580,7 +581,8 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
     const int t0 = n_seq > FEW_MAX ? __builtin_amdgcn_readfirstlane(grp_steps(a.batch_sizes, T, FEW_MAX * X + x)) : 0;
     few_clear_ring<MODE>(static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, H), H, j0, UH);
     // From timestep t_many on at most MANY_MAX are: lstm_many.h, which has both sides of the line.
-    const int t_many = !many_pays<MODE>(H) ? t0 : n_seq > MANY_MAX ? __builtin_amdgcn_readfirstlane(grp_steps(a.batch_sizes, T, MANY_MAX * X + x)) : 0;
+    const int t_first = !many_pays<MODE>(H) ? t0 : n_seq > MANY_MAX ? __builtin_amdgcn_readfirstlane(grp_steps(a.batch_sizes, T, MANY_MAX * X + x)) : 0;
+    const int t_many = t0 - t_first < many_steps_fwd<MODE>(H, PIPE != PIPE_NONE) ? t0 : t_first;
     if (t_many < t0) many_clear_ring<MODE>(a.ring_many, ps.id, H, a.many_rows, min(n_seq, a.many_rows), j0, UH);
     rec_publish(flags, rank, 1);
     REC_PROF_DECL
@@ -1070,7 +1072,7 @@ __device__ __forceinline__ void rec_bwd_body(const RecBwdArgs& by_ref, int rank,
     float dh_few = 0.f;
     bool many = false;   // lstm_many.h, which has both sides of the lines
     if constexpr (MANY_BWD<MODE, MT, NI>) {
-        many = t_few >= MANY_STEPS_BWD && n_seq <= a.many_rows && many_pays_bwd<MODE, MT>(H, n_seq);
+        many = n_seq <= a.many_rows && many_pays_bwd<MODE, MT>(H, n_seq, t_few, PIPE != PIPE_NONE);
         if (many) many_clear_ring<MODE>(a.ring_many, ps.id, K, a.many_rows, n_seq, j0 * 4, UH * 4);
     }
     if (t_few < T) few_clear_ring<MODE>(ring, K, j0 * 4, UH * 4);
