@@ -25,15 +25,16 @@
 //
 // Bound by the latency of its phases: about 0.6 us for the exchange alone (a kernel that does nothing else), 0.43 us for
 // the MFMAs of one 16-row tile at H = 1024 (1.7 us in fp32 at H = 512), then the partial sums through LDS and the cell
-// update.  Microseconds per timestep (two layers in one launch, time of a launch against its timesteps), a thread per (piece,
-// unit) throughout -> four lanes up to 4 pieces:
+// update.  Microseconds per timestep (time of a launch against its timesteps; two layers, with 16 pieces one), a thread per (piece, unit)
+// throughout -> four lanes up to 4 pieces:
 //     alive pieces                     1             2             4             8      16
-//     bf16, H = 1024   forward    1.34 -> 1.23  1.35 -> 1.29  1.40 -> 1.47     1.9    3.2
-//                      backward   1.58 -> 1.64  1.84 -> 1.73  2.21 -> 2.18     2.4    3.3
-//     bf16, H = 512    forward    1.05 -> 0.87  1.06 -> 0.90  1.05 -> 0.95     1.3    1.8
-//                      backward   1.37 -> 1.15  1.38 -> 1.17  1.55 -> 1.38     1.5    2.1
-//     fp32, H = 512    forward    1.21 -> 1.15  1.51 -> 1.43  2.14 -> 2.08     3.0    4.9
-//                      backward   1.46 -> 1.28  2.05 -> 1.83  3.07 -> 2.77     3.6    4.5
+//     bf16, H = 1024   forward    1.37 -> 1.25  1.34 -> 1.24          1.37     1.9    2.1
+//                      backward   1.63 -> 1.58  1.81 -> 1.72  2.14 -> 2.24     2.4    2.9
+//     bf16, H = 512    forward    1.04 -> 0.90  1.04 -> 0.88  1.05 -> 0.94     1.3    1.3
+//                      backward   1.36 -> 1.16  1.36 -> 1.16  1.58 -> 1.34     1.5    2.0
+//     fp32, H = 512    forward    1.23 -> 1.12  1.51 -> 1.42  2.13 -> 2.05     3.0    3.0
+//                      backward   1.49 -> 1.28  2.05 -> 1.82  3.06 -> 2.74     3.5    4.2
+// (Backward 4 pieces at H = 1024 are slower: all eight waves of a workgroup, two per SIMD, then own a share of the cell update, where two did.)
 // (the flag protocol took 2.2 to 2.4 us with one piece and 3.3 to 5.7 with 16.)
 // What mattered after the exchange itself: four neighbouring lanes on contiguous memory (16 pieces forward 2.74 -> 2.04 us,
 // backward 5.25 -> 2.99), reading the eight partial sums without a branch per share (0.2 us per timestep), and no wait
@@ -394,6 +395,11 @@ __device__ __forceinline__ void few_clear_ring(unsigned char* ring, int row_elem
 
 // Up to QUAD_MAX pieces: lstm_quad.h.
 constexpr int QUAD_MAX = 4;
+// Forward the widths above 512 units, with 32 units per workgroup, run it up to 2 pieces, 3 and 4 with a thread per (piece, unit): with four lanes all
+// eight waves own a share of the cell update, two per SIMD, where two waves do with a thread.  us per forward pass of two layers over 256 timesteps of 4
+// pieces per group, four lanes -> a thread: 576 units 409 -> 403, 768 429 -> 424, 1024 458 -> 442; one layer of 576 378 -> 367.  (Backward the same
+// made the consumer's timesteps longer: 1024 units 746 -> 922.)
+template <int MT> constexpr int QUAD_FWD = MT == 8 ? 2 : QUAD_MAX;
 template <int MODE, int MT, int NB> struct FewFwd;
 template <int MODE, int MT, int NB> struct FewBwd;
 template <int MODE, int MT, int NB, int PIPE>
@@ -458,15 +464,19 @@ __device__ __forceinline__ void few_fwd_store(const FewFwd<MODE, MT, NB>& s, con
     }
 }
 
-// Runs timesteps while more than QUAD_MAX (and at most FEW_MAX) pieces are alive.  False: a wait was abandoned.
-template <int MODE, int MT, int NB, int PIPE>
+// Runs timesteps while more than down_to (and at most P) pieces are alive.  P = 16: rows through LDS; P = 4: polled into operand registers, two
+// buffers of partial sums, sums and gates in the order of lstm_quad.h.  False: a wait was abandoned.
+template <int MODE, int MT, int NB, int P, int PIPE>
 __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const RecFwdArgs& a, const PieceSet& ps, int rank, int* flags,
-                                              unsigned char* ring, const PipeLink& pl, int& t, int T) {
+                                              unsigned char* ring, const PipeLink& pl, int& t, int T, int down_to) {
     typedef typename RecGeom<MODE>::E E;
     constexpr int es = (int)sizeof(E);
     constexpr int UH = 4 * MT, COLS = 16 * MT, ROW = few_row(COLS);
+    constexpr bool STAGED = P > 4;
+    constexpr int BPL = STAGED ? 1 : 16 / P, L = STAGED ? 1 : (NB + BPL - 1) / BPL;
     const int X = ps.X, x = ps.x, H = a.H;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lr = tid & 15, lk = (tid & 63) >> 4;
+    const int piece = lr / BPL, blk = lr % BPL;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = tid / UH, u = tid % UH, j0 = rank * UH;
     const unsigned slice_off = (unsigned)(s.slice * NB) * 64u;                          // bytes: an operand block is 64
@@ -474,6 +484,12 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
     const unsigned w_off = (unsigned)(m * H + j0 + u) * es;   // where this thread's value goes inside a slot
     const bool polls = s.slice < s.n_slices;
     unsigned char* stage = reinterpret_cast<unsigned char*>(s.part + few_part_floats(COLS)) + wave * few_stage_bytes(NB);
+    const unsigned k_off = slice_off + (unsigned)(lk * s.n_blk + blk) * 16u;   // this lane's first 16 bytes inside a row
+    unsigned off[L];
+    few_offsets<L, BPL>(off, (unsigned)(piece * H) * es + k_off, blk, s.n_blk);
+    u32x4_t raw[L];
+#pragma unroll
+    for (int j = 0; j < L; ++j) raw[j] = u32x4_t{0u, 0u, 0u, 0u};
     bar_lds();   // (the partial sums of the phase before have been read)
     few_clear_part<COLS>(s.part);
     bar_lds();
@@ -497,11 +513,18 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
             if ((PIPE & PIPE_PRODUCER) && rank == 0 && tid == 0 && t > 0) st_agent(pl.progress, t);
             if (polls) {
                 const unsigned char* rows = reinterpret_cast<const unsigned char*>(static_cast<const E*>(a.hprev) + (size_t)(s.base + x) * H);
-                few_stage_read<NB>(rows, (unsigned)(X * H) * es, slice_off, s.n_blk, bs, false, stage, a.err);
+                if constexpr (STAGED) {
+                    few_stage_read<NB>(rows, (unsigned)(X * H) * es, slice_off, s.n_blk, bs, false, stage, a.err);
+                } else {
+                    unsigned first[L];
+                    few_offsets<L, BPL>(first, (unsigned)(piece * X * H) * es + k_off, blk, s.n_blk);
+                    few_read<L>(rows, first, piece < bs && blk < s.n_blk, false, raw, a.err);
+                }
             }
         } else if (polls) {
             const unsigned char* rows = ring + (unsigned)((t - 1) & (FEW_RING - 1)) * slot;
-            ok = few_stage_read<NB>(rows, (unsigned)H * es, slice_off, s.n_blk, bs, true, stage, a.err);
+            if constexpr (STAGED) ok = few_stage_read<NB>(rows, (unsigned)H * es, slice_off, s.n_blk, bs, true, stage, a.err);
+            else ok = few_read<L>(rows, off, piece < bs && blk < s.n_blk, true, raw, a.err);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (also: this wave's stores of two timesteps ago have completed)
         few_touch(z);
@@ -524,13 +547,18 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
             if (t + 3 < T && t + 3 == s.c_wait * pl.ct && tid == REC_THREADS - 1) s.have = ld_agent(&pl.done[s.c_wait]);
         }
         if (t > s.t0) few_fwd_store<MODE, MT, NB, PIPE>(s, a, ps, j0, grp_count(s.base - s.base_prev, ps), s.base, bs);
-        float* part = s.part;
+        float* part = s.part + (STAGED ? 0 : (t & 1) * (REC_WAVES * P * ROW));
         if (polls) {
             f32x4_t acc[MT];
 #pragma unroll
             for (int j = 0; j < MT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            few_stage_product<MODE, MT, NB, false>(s.w, stage, s.part + 16 * MT, s.n_blk, acc, [] {});
-            few_stage_write<MT>(acc, bs, part + s.slice * (16 * ROW));
+            if constexpr (STAGED) {
+                few_stage_product<MODE, MT, NB, false>(s.w, stage, s.part + 16 * MT, s.n_blk, acc, [] {});
+                few_stage_write<MT>(acc, bs, part + s.slice * (P * ROW));
+            } else {
+                few_product<MODE, MT, NB, P, L>(s.w, raw, bs, s.n_blk, acc);
+                few_write<MODE, MT, P>(acc, bs, part + s.slice * (P * ROW));
+            }
         }
         bar_lds();
         const int failed = *s.fail;   // (looked at after the publication: its read is not waited for by itself)
@@ -542,10 +570,15 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
             f32x4_t q = z, o[REC_WAVES];
             const float* p = part + m * ROW + u * 4;
 #pragma unroll
-            for (int k = 0; k < REC_WAVES; ++k) o[k] = *reinterpret_cast<const f32x4_t*>(p + k * (16 * ROW));
+            for (int k = 0; k < REC_WAVES; ++k) o[k] = *reinterpret_cast<const f32x4_t*>(p + k * (P * ROW));
+            if constexpr (STAGED) {
 #pragma unroll
-            for (int k = 0; k < REC_WAVES; ++k) {
-                q[0] += o[k][0]; q[1] += o[k][1]; q[2] += o[k][2]; q[3] += o[k][3];
+                for (int k = 0; k < REC_WAVES; ++k) {
+                    q[0] += o[k][0]; q[1] += o[k][1]; q[2] += o[k][2]; q[3] += o[k][3];
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) q[i] += ((o[0][i] + o[1][i]) + (o[2][i] + o[3][i])) + ((o[4][i] + o[5][i]) + (o[6][i] + o[7][i]));
             }
             const float gi = sigmoidf_(q[0]), gf = sigmoidf_(q[1]), gg = tanhf_(q[2]), go = sigmoidf_(q[3]);
             s.c = gf * s.c + gi * gg;
@@ -565,7 +598,7 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
             }
         }
         if (__builtin_amdgcn_readfirstlane(failed)) return false;
-        bar_lds();   // (one buffer of partial sums: it has been read)
+        if (STAGED) bar_lds();   // (one buffer of partial sums: it has been read)
         s.base_prev = s.base;
         s.base = base_next;
         s.bs_a = s.bs_b;
@@ -575,9 +608,9 @@ __device__ __forceinline__ bool few_fwd_phase(FewFwd<MODE, MT, NB>& s, const Rec
     };
     // (two steps per iteration: a prefetched value is used where it was loaded, a move would wait for the load)
     f32x4_t z2 = s.z;
-    while (t < T && grp_count(s.bs_a, ps) > QUAD_MAX) {
+    while (t < T && grp_count(s.bs_a, ps) > down_to) {
         if (!step(s.z, z2)) return false;
-        if (!(t < T && grp_count(s.bs_a, ps) > QUAD_MAX)) {
+        if (!(t < T && grp_count(s.bs_a, ps) > down_to)) {
             s.z = z2;
             break;
         }
@@ -673,7 +706,10 @@ __device__ __forceinline__ bool few_fwd(few_args_t<RecFwdArgs> args, int x_, int
         else if (a.c0 && n < a.seq_cap) s.c = a.c0[(size_t)n * H + j0 + u];
     }
     int t = t0;
-    if (!few_fwd_phase<MODE, MT, NB, PIPE>(s, a, ps, rank, flags, ring, pl, t, T)) return false;
+    if (!few_fwd_phase<MODE, MT, NB, 16, PIPE>(s, a, ps, rank, flags, ring, pl, t, T, QUAD_MAX)) return false;
+    constexpr int QUAD = QUAD_FWD<MT>;
+    if constexpr (QUAD < QUAD_MAX)
+        if (t < T && grp_count(s.bs_a, ps) > QUAD && !few_fwd_phase<MODE, MT, NB, QUAD_MAX, PIPE>(s, a, ps, rank, flags, ring, pl, t, T, QUAD)) return false;
     if (t > t0) few_fwd_store<MODE, MT, NB, PIPE>(s, a, ps, j0, grp_count(s.base - s.base_prev, ps), s.base, t < T ? grp_count(s.bs_a, ps) : 0);
     if (t < T && !quad_fwd<MODE, MT, NB, PIPE>(s, a, ps, rank, flags, ring, pl, t, T)) return false;
     if (PIPE & PIPE_PRODUCER) rec_publish(few_scalar(flags), rank, T + 1);

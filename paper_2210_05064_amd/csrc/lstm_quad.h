@@ -80,12 +80,12 @@ __device__ __forceinline__ void quad_product(const f32x4_t (&w)[MT * NB], const 
 }
 
 // ---- forward ------------------------------------------------------------------------------------------------
-// Timesteps [t, T), at most QUAD_MAX alive pieces.  False: a wait was abandoned.
+// Timesteps [t, T), at most QUAD_FWD alive pieces.  False: a wait was abandoned.
 template <int MODE, int MT, int NB, int PIPE>
 __device__ __forceinline__ bool quad_fwd(FewFwd<MODE, MT, NB>& s, const RecFwdArgs& a, const PieceSet& ps, int rank, int* flags,
                                          unsigned char* ring, const PipeLink& pl, int& t, int T) {
     typedef typename RecGeom<MODE>::E E;
-    constexpr int es = (int)sizeof(E), P = QUAD_MAX;
+    constexpr int es = (int)sizeof(E), P = QUAD_FWD<MT>;
     constexpr int UH = 4 * MT, COLS = 16 * MT, ROW = few_row(COLS), PART = P * ROW;
     constexpr int BPL = 16 / P, L = (NB + BPL - 1) / BPL;
     const int X = ps.X, x = ps.x, H = a.H;
