@@ -81,15 +81,17 @@ constexpr int PLAN_CT_FEW = 8, PLAN_CT_FEW_FAST = 4, PLAN_CT_MANY = 2;   // up t
 // 2 timesteps -> 192 rows: 64 timesteps of 32 / 48 pieces per group 296 -> 256 / 359 -> 324, 128 timesteps 504 -> 529 / 702 -> 723, 24
 // pieces (72 alive) 223 -> 253; 8192 rows in 192 pieces of about equal length 354 -> 318.  (Narrower layers have workers to spare: 448
 // units, 32 timesteps of 48 pieces 222 -> 251.)
-// us per timestep of launches over equally long pieces (two layers; time of a launch against its timesteps):
+// us per timestep of launches over equally long pieces (time of a launch against its timesteps; up to 8 per group two layers, from 16 on one, since with
+// as many in all three groups the workers set the pace, 1.7 us per 16 rows at H = 1024):
 //   pieces               1     2     4     5     8    16    17    32    64
-//   bf16 H=1024 fwd   1.23  1.29  1.47  1.93  1.97  2.3   3.5   4.4   8.2      bwd  1.64  1.73  2.18  2.47  2.45  3.2   5.1   6.1  12.2
-//   bf16 H=512  fwd   0.87  0.90  0.95  1.30  1.30  1.6   2.6   3.0   5.7      bwd  1.15  1.17  1.38  1.51  1.50  2.1   3.3   3.7   7.3
-//   fp32 H=512  fwd   1.15  1.43  2.08  3.00  3.0   3.0   5.9   6.2  12.7      bwd  1.28  1.83  2.77  3.56  3.5   4.5   7.3   7.9  15.8
-// (from 16 pieces on: one layer, since with as many in all three groups the workers set the pace, 1.7 us per 16 rows at H = 1024).  The constants
-// are fitted by hand to it (without the step from four to five pieces, two short groups of fp32 got five and more pieces each and ended 50 us
-// after the long one: 2 x 512 on 1024 rows in 8; with 2.4 and 3.8 us per tile, what the wide layers took before, 8192 rows in about 100 pieces of 2 x
-// 1024 units took 2.55 ms forward and backward, now 2.38).
+//   bf16 H=1024 fwd   1.25  1.24  1.42  1.89  1.93  2.08  3.59  4.59  8.6      bwd  1.58  1.72  2.24  2.36  2.38  2.94  5.29  6.48  12.3
+//   bf16 H=512  fwd   0.90  0.88  0.94  1.27  1.27  1.29  2.53  2.86  6.0      bwd  1.16  1.16  1.34  1.48  1.51  1.95  3.03  4.35   8.5
+//   fp32 H=512  fwd   1.12  1.42  2.05  3.02  3.00  2.98  5.88  6.08  12.4     bwd  1.28  1.82  2.74  3.59  3.53  4.18  7.32  7.92  15.9
+// (backward beyond 16 pieces bf16 at 512 units is the form of lstm_rec.h, the others that of lstm_many.h.)  The constants
+// are fitted by hand to it, and for the narrow bf16 layers to the other widths too (a tile backward 1.0 at 17 pieces, 1.4 at 64 and 512 units, 0.4 at
+// 320; with 1.2 an update of 2 x 512 units and three layers of 320 take the same time).  Without the step from four to five pieces, two short groups of
+// fp32 got five and more pieces each and ended 50 us after the long one: 2 x 512 on 1024 rows in 8; with 2.4 and 3.8 us per tile, what the wide layers
+// took before, 8192 rows in about 100 pieces of 2 x 1024 units took 2.55 ms forward and backward, now 2.38.
 inline PlanCost plan_cost(int mode, bool wide, bool fwd, int G, int workers) {
     const int teams = workers / G;
     if (mode == MODE_F32)
