@@ -288,8 +288,7 @@ __device__ __forceinline__ void plan_launches(const PlanArgs& a, PlanLds& lds) {
         plan[PLAN_GROUPS + 1] = triple ? TRIPLE_GROUPS : REC_GROUPS;
     }
     if (alone) return;
-    const PlanCost& fwd = triple ? a.fwd_three : a.fwd;
-    const PlanCost& bwd = triple ? a.bwd_three : a.bwd;
+    const PlanCost fwd = triple ? a.fwd_three : a.fwd, bwd = triple ? a.bwd_three : a.bwd;
     const int groups = triple ? TRIPLE_GROUPS : PIPE_GROUPS;
     if (n_seq <= PLAN_LDS_N && T <= PLAN_LDS_N)
         plan_body<true>(a.batch_sizes, M, n_seq, T, a.plan_fwd, a.plan_bwd, a.scratch, lds.bs, lds.len, lds.S1, fwd, bwd, groups);
