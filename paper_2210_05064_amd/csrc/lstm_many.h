@@ -27,9 +27,10 @@ template <int MODE> __host__ __device__ constexpr bool many_pays(int H) { return
 // In a launch of several layers it hands rows on about two timesteps later, and pays from this many timesteps on: forward passes of two layers with 17
 // pieces per group over 4 / 8 / 12 / 16 / 24 timesteps, as above: bf16, 512 units 111 / 106 / 102 / 101 / 99, 1024 105 / 103 / 102 / 101 / 99, 64 98 / 90 /
 // 87 / 84 / 81, 256 (6:) 100 / 98 / 96 / 93 / 90, 576 104 / 97 / 93 / 91 / 86; fp32, 256 units 109 / 103 / 100 / 98 / 96, 448 (12:) 103, 512 104 / 101 / 104 / 102 / 101.
-// One layer 101 / 97 / 97 / 95 / 94 at 1024 units.
-template <int MODE> __host__ __device__ constexpr int many_steps_fwd(int H, bool shared) {
-    return !shared ? 1 : MODE == MODE_F32 || H == 512 ? 24 : H == 1024 ? 16 : 8;
+// One layer 101 / 97 / 97 / 95 / 94 at 1024 units.  Only fp32 has the line: the forms add in another order, which in bf16 a rounding may show, and groups
+// with 17 pieces for a handful of timesteps are common in updates (2 to 6 us of a launch).
+template <int MODE> __host__ __device__ constexpr int many_steps_fwd(bool shared) {
+    return shared && MODE == MODE_F32 ? 24 : 1;
 }
 // Rows of a slot for minibatches of M rows; 0 where no launch of this width runs the form.
 inline int many_rows(int mode, int H, int M) {

@@ -582,7 +582,7 @@ __device__ __forceinline__ void rec_fwd_body(const RecFwdArgs& a, int rank, cons
     few_clear_ring<MODE>(static_cast<unsigned char*>(a.ring) + ps.id * few_ring_bytes(MODE, H), H, j0, UH);
     // From timestep t_many on at most MANY_MAX are: lstm_many.h, which has both sides of the line.
     const int t_first = !many_pays<MODE>(H) ? t0 : n_seq > MANY_MAX ? __builtin_amdgcn_readfirstlane(grp_steps(a.batch_sizes, T, MANY_MAX * X + x)) : 0;
-    const int t_many = t0 - t_first < many_steps_fwd<MODE>(H, PIPE != PIPE_NONE) ? t0 : t_first;
+    const int t_many = t0 - t_first < many_steps_fwd<MODE>(PIPE != PIPE_NONE) ? t0 : t_first;
     if (t_many < t0) many_clear_ring<MODE>(a.ring_many, ps.id, H, a.many_rows, min(n_seq, a.many_rows), j0, UH);
     rec_publish(flags, rank, 1);
     REC_PROF_DECL

@@ -94,7 +94,7 @@ def test_two_layers_fall_through_all_forms(ver, compute, hidden):
 @pytest.mark.parametrize("pieces,steps", [(51, 7), (51, 8), (51, 15), (51, 16), (51, 23), (51, 24), (51, 47), (51, 48), (75, 48), (99, 48), (147, 24), (195, 48)])
 @pytest.mark.parametrize("compute,hidden", [(0, 256), (0, 448), (1, 64), (1, 192), (1, 512), (1, 1024)])
 def test_lines_of_shared_launches(ver, compute, hidden, pieces, steps):
-    """17, 25, 33, 49 and 65 pieces per group: both sides of the least numbers of timesteps forward (8, 16, 24) and backward (24, 48)."""
+    """17, 25, 33, 49 and 65 pieces per group: both sides of the least numbers of timesteps forward (24) and backward (24, 48)."""
     run(ver, [pieces] * steps, 2, compute, hidden)
 
 
