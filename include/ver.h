@@ -334,8 +334,8 @@ int ver_pack_index_batch(const ver_pack_args* args /* host array */, int32_t n, 
  * waits time out.  ver_lstm_fwd / ver_lstm_bwd return VER_EUNSUPPORTED on a
  * device that is not a whole MI355X (gfx950 with 256 compute units; the
  * device is queried once).  Networks of several layers run the time loops of
- * two layers in one launch (three layers: all three; an odd number's top
- * layer from five on has its own), from three layers on only while few
+ * two layers in one launch (three layers: all three, or the two lower ones; an
+ * odd number's top layer has its own), from three layers on only while few
  * pieces are alive per timestep (decided on the device from info); cfg.layer_by_layer = 1 gives every layer a launch of
  * its own - a diagnostic switch, results agree up to the order
  * of fp32 additions (forward and backward must be called with the same value).
