@@ -29,12 +29,11 @@
 // throughout -> four lanes up to 4 pieces:
 //     alive pieces                     1             2             4             8      16
 //     bf16, H = 1024   forward    1.37 -> 1.25  1.34 -> 1.24          1.37     1.9    2.1
-//                      backward   1.63 -> 1.58  1.81 -> 1.72  2.14 -> 2.24     2.4    2.9
+//                      backward   1.63 -> 1.58  1.81 -> 1.61  2.14 -> 2.01     2.4    2.9
 //     bf16, H = 512    forward    1.04 -> 0.90  1.04 -> 0.88  1.05 -> 0.94     1.3    1.3
 //                      backward   1.36 -> 1.16  1.36 -> 1.16  1.58 -> 1.34     1.5    2.0
 //     fp32, H = 512    forward    1.23 -> 1.12  1.51 -> 1.42  2.13 -> 2.05     3.0    3.0
 //                      backward   1.49 -> 1.28  2.05 -> 1.82  3.06 -> 2.74     3.5    4.2
-// (Backward 4 pieces at H = 1024 are slower: all eight waves of a workgroup, two per SIMD, then own a share of the cell update, where two did.)
 // (the flag protocol took 2.2 to 2.4 us with one piece and 3.3 to 5.7 with 16.)
 // What mattered after the exchange itself: four neighbouring lanes on contiguous memory (16 pieces forward 2.74 -> 2.04 us,
 // backward 5.25 -> 2.99), reading the eight partial sums without a branch per share (0.2 us per timestep), and no wait

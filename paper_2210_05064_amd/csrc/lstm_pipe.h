@@ -84,7 +84,7 @@ constexpr int PLAN_CT_FEW = 8, PLAN_CT_FEW_FAST = 4, PLAN_CT_MANY = 2;   // up t
 // us per timestep of launches over equally long pieces (time of a launch against its timesteps; up to 8 per group two layers, from 16 on one, since with
 // as many in all three groups the workers set the pace, 1.7 us per 16 rows at H = 1024):
 //   pieces               1     2     4     5     8    16    17    32    64
-//   bf16 H=1024 fwd   1.25  1.24  1.42  1.89  1.93  2.08  3.59  4.59  8.6      bwd  1.58  1.72  2.24  2.36  2.38  2.94  5.29  6.48  12.3
+//   bf16 H=1024 fwd   1.25  1.24  1.42  1.89  1.93  2.08  3.59  4.59  8.6      bwd  1.58  1.61  2.01  2.36  2.38  2.94  5.29  6.48  12.3
 //   bf16 H=512  fwd   0.90  0.88  0.94  1.27  1.27  1.29  2.53  2.86  6.0      bwd  1.16  1.16  1.34  1.48  1.51  1.95  3.03  4.35   8.5
 //   fp32 H=512  fwd   1.12  1.42  2.05  3.02  3.00  2.98  5.88  6.08  12.4     bwd  1.28  1.82  2.74  3.59  3.53  4.18  7.32  7.92  15.9
 // (backward beyond 16 pieces bf16 at 512 units is the form of lstm_rec.h, the others that of lstm_many.h.)  The constants

@@ -6,7 +6,7 @@
 // branch.  So:
 //  * a lane adds the partial sums of one gate and applies one non-linearity (one exponential and one reciprocal behind another
 //    where a thread per unit needs three of each), and the four gates meet through DPP;
-//  * the poll is requested right behind the wave's own publication, and what the next timestep needs is made while it is on its way:
+//  * the poll is requested right behind the wave's own publication (but see LATE), and what the next timestep needs is made while it is on its way:
 //    where its rows begin, who is alive, whether a chunk has to be waited for, and backward the factors of the gate gradients that
 //    only depend on what the forward pass saved.  Between the arrival of the values and the publication there is
 //    what depends on them, and the memory operations of the owner wave, behind the MFMAs;
@@ -327,6 +327,10 @@ __device__ __forceinline__ bool quad_bwd_loop(QuadBwd<MODE, MT, NB, PIPE>& d, Fe
     typedef QuadBwd<MODE, MT, NB, PIPE> D;
     constexpr int es = D::es, UH = D::UH, COLS = D::COLS, ROW = D::ROW, PART = D::PART;
     constexpr int BPL = 16 / P, L = (NB + BPL - 1) / BPL;
+    // A poll here is four loads per lane in 32 workgroups, and right behind the publication it comes too early to be the only one (judged by the times, not
+    // counted): it is requested behind the factors.  us per timestep of two layers with 2 / 3 / 4 pieces per group, right behind the publication -> behind
+    // the factors: 1024 units 1.72 / 2.08 / 2.30 -> 1.61 / 1.90 / 2.01, 576 (2 / 4) 1.58 / 1.83 -> 1.50 / 1.67; one layer, 1024 1.61 / 1.95 / 2.08 -> 1.49 / 1.71 / 1.78.
+    constexpr bool LATE = MT == 2 && P > 2;
     const int X = ps.X, x = ps.x, H = a.H, K = 4 * H;
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -382,7 +386,7 @@ __device__ __forceinline__ bool quad_bwd_loop(QuadBwd<MODE, MT, NB, PIPE>& d, Fe
             off_bs = bs;
             quad_offsets<L, BPL>(off, (unsigned)(piece * K) * es + k_off, piece < bs, blk, s.n_blk);
         }
-        if (polls && t > 0) quad_request<L>(rs_ring, off, so_w, raw);
+        if (!LATE && polls && t > 0) quad_request<L>(rs_ring, off, so_w, raw);
         __builtin_amdgcn_sched_barrier(0);
         unsigned so_dz = (unsigned)s.base * (unsigned)(K * es);
         if (t == 0) {   // nothing is carried before the first timestep
@@ -416,6 +420,10 @@ __device__ __forceinline__ bool quad_bwd_loop(QuadBwd<MODE, MT, NB, PIPE>& d, Fe
         quad_now(base_3); quad_now(so_dz); quad_now(so_e);
         // B. dh carried to t-1: dh[piece][k] = sum_q dz[piece][q] * W_hh[q][k] for this workgroup's columns k
         bool ok = true;
+        if (LATE) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (polls) quad_request<L>(rs_ring, off, so_w, raw);
+        }
         if (polls) ok = quad_arrived<L>(rs_ring, off, so_w, raw, a.err);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (also: this wave's dz rows of timestep t+1 have completed)
         quad_touch(d.r1);
